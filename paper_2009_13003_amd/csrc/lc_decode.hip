@@ -17,78 +17,112 @@ namespace lc {
 // of the record sizes that the lane lengths imply, from 0 to the blob's stated size.
 // Errors are raised with atomicMax on a word tagged with the call's epoch, so the word
 // never needs clearing.
-// Thread 0 of a workgroup: validates the header's symbol table, builds the canonical codes and fills
-// D.info; s_len / s_code (LDS, kMaxSym entries) are left for dec_build_luts.  Returns whether the blob passes.
-__device__ __forceinline__ bool dec_symbol_table(const u32* hdr, u64 n, u32 nchunks, u64 area, u64 tw, DecSet& D,
-                                                 u32* s_len, u32* s_code) {
-    const u32 nbits = hdr[4], K = hdr[5];
+// Tables of one blob while its workgroup builds them.
+struct DecBuild {
+    u32 len[kMaxSym], code[kMaxSym], max_len;
+    uint8_t one[1u << kMultiBits];            // over the next 10 bits: symbol | len << 4 of the first code (see dec_build_luts)
+};
+
+// By the first wavefront of a workgroup, lane j holding symbol j: validates the header's symbol table, builds the canonical
+// codes and fills D.info; B.len / B.code are left for dec_build_luts.  Returns (in every lane) whether the blob passes.
+__device__ __forceinline__ bool dec_symbol_table(const u32* hdr, u64 n, u32 nchunks, u64 area, u64 tw, DecSet& D, DecBuild& B) {
+    const u32 nbits = hdr[4], K = hdr[5], lane = lane_id();
     // binary64 blobs (element type 3): 12-bit bucket ids, 64-bit representatives with the high halves at offset 320
     const bool wide = hdr[15] == (u32)kF64;
     const u32 emask = wide ? 2047u : 255u, nbuckets = 2 * (emask + 1);
     bool ok = nbits >= 1 && nbits <= 4 && K <= (1u << nbits) - 1 && hdr[6] == kW && hdr[7] == kV && hdr[8] == kR;
     if (nchunks == 0 && tw != 0) ok = false;
-    u64 cnt_sum = 0; u32 kraft = 0, active = 0, max_len = 0;
-    u32 per_len[17];
-    for (int L = 0; L <= 16; ++L) per_len[L] = 0;
-    for (u32 j = 0; j < kMaxSym; ++j) { s_len[j] = 0; s_code[j] = 0; D.info.rep_bits[j] = 0; D.info.rep_hi[j] = 0; }
-    if (ok) {
-        for (u32 j = 0; j <= K; ++j) {
-            const u32 w0 = hdr[16 + 4 * j], rep = hdr[17 + 4 * j];
-            const u64 cn = hdr[18 + 4 * j] | ((u64)hdr[19 + 4 * j] << 32);
-            const u32 bucket = w0 & 0xFFFFu, len = (w0 >> 16) & 0xFFu;
-            cnt_sum += cn;
-            if ((cn > 0) != (len > 0) || len > 15 || (w0 >> 24) != 0) { ok = false; continue; }
-            const u32 rep_hi = wide ? hdr[80 + j] : 0u;
-            if (j < K && (bucket >= nbuckets || (bucket & emask) == 0 || (bucket & emask) == emask)) ok = false;
-            if (j < K && (wide ? (rep_hi >> 20) : (rep >> 23)) != bucket) ok = false;
-            if (j == K && (rep | rep_hi) != 0) ok = false;
-            s_len[j] = len; D.info.rep_bits[j] = rep; D.info.rep_hi[j] = rep_hi;
-            if (len) { kraft += 1u << (15 - len); ++active; per_len[len]++; if (len > max_len) max_len = len; }
-        }
-        if (cnt_sum != n) ok = false;
-        if (active >= 2 && kraft != (1u << 15)) ok = false;
-        if (active == 1 && kraft != (1u << 14)) ok = false;
+    u32 len = 0, rep = 0, rep_hi = 0;
+    u64 cn = 0;
+    bool bad = false;
+    if (ok && lane <= K) {
+        const u32 j = lane, w0 = hdr[16 + 4 * j], bucket = w0 & 0xFFFFu;
+        rep = hdr[17 + 4 * j]; rep_hi = wide ? hdr[80 + j] : 0u;
+        cn = hdr[18 + 4 * j] | ((u64)hdr[19 + 4 * j] << 32);
+        len = (w0 >> 16) & 0xFFu;
+        if ((cn > 0) != (len > 0) || len > 15 || (w0 >> 24) != 0) { bad = true; len = 0; }
+        if (j < K && (bucket >= nbuckets || (bucket & emask) == 0 || (bucket & emask) == emask)) bad = true;
+        if (j < K && (wide ? (rep_hi >> 20) : (rep >> 23)) != bucket) bad = true;
+        if (j == K && (rep | rep_hi) != 0) bad = true;
     }
-    if (ok) {
-        u32 next_code[17], code = 0;
-        for (int L = 1; L <= 16; ++L) { code = (code + per_len[L - 1]) << 1; next_code[L] = code; }
-        for (u32 j = 0; j < kMaxSym; ++j) {
-            s_code[j] = s_len[j] ? next_code[s_len[j]]++ : 0;
-            D.info.len[j] = s_len[j]; D.info.code[j] = s_code[j];
-        }
+    // (counts that add up to n modulo 2^64, as one running sum would have it)
+    const u64 cnt_sum = wave_sum64(cn);
+    const u32 kraft = wave_sum32(len ? 1u << (15 - len) : 0u), active = (u32)__popcll(__ballot(len != 0));
+    if (ok && (__any(bad) || cnt_sum != n || (active >= 2 && kraft != (1u << 15)) || (active == 1 && kraft != (1u << 14)))) ok = false;
+    // canonical codes: within a length in symbol order, the first code of a length from the counts below it
+    u32 code = 0, first = 0, shorter = 0;
+    for (u32 L = 1; L < kMaxSym; ++L) {
+        const u64 m = __ballot(len == L);
+        first = (first + shorter) << 1;
+        shorter = (u32)__popcll(m);
+        if (len == L) code = first + (u32)__popcll(m & ((1ull << lane) - 1));
     }
-    D.info.K = K; D.info.max_len = max_len;
-    D.info.area = area; D.info.total_words = tw;
+    const u32 max_len = wave_max_u32(len);
+    if (lane < kMaxSym) {
+        B.len[lane] = len; B.code[lane] = code;
+        D.info.rep_bits[lane] = rep; D.info.rep_hi[lane] = rep_hi;
+        D.info.len[lane] = len; D.info.code[lane] = code;
+    }
+    if (lane == 0) { B.max_len = max_len; D.info.K = K; D.info.max_len = max_len; D.info.area = area; D.info.total_words = tw; }
     return ok;
 }
 
-// Two tables over the next P bits of a lane's string, entry = symbol | len << 4.  A prefix that
-// starts no code: symbol K with length 0 (the lane then falls short of its stated length); a
-// prefix of a code longer than P bits: 0xFF.  The first table (P = min(max_len, 7): 128 bytes,
-// one 32-bit word per LDS bank) resolves the frequent short codes without bank conflicts.
-__device__ __forceinline__ void dec_build_luts(DecSet& D, const u32* s_len, const u32* s_code, u32 t, u32 nthr) {
-    const u32 M = D.info.max_len, K = D.info.K;
-    const u32 P1 = M < kDecLut1Bits ? M : kDecLut1Bits, P2 = M < kDecLut2Bits ? M : kDecLut2Bits;
-    for (u32 pass = 0; pass < 2; ++pass) {
-        const u32 P = pass ? P2 : P1;
-        uint8_t* lut = pass ? D.lut2 : D.lut1;
-        if (pass && M <= kDecLut1Bits) break;
-        // every thread of the workgroup takes part: first "starts no code" everywhere, then each code's own range
-        // of prefixes (the ranges of a prefix code do not overlap), all threads sharing the entries of a range
-        for (u32 i = t; i < (1u << P); i += nthr) lut[i] = (uint8_t)K;
-        __syncthreads();
-        for (u32 j = 0; j <= K; ++j) {
-            const u32 L = s_len[j];
-            if (L == 0) continue;
-            if (L <= P) {
-                const u32 first = s_code[j] << (P - L), count = 1u << (P - L);
-                for (u32 i = t; i < count; i += nthr) lut[first + i] = (uint8_t)(j | (L << 4));
-            } else if (t == 0) {
-                lut[s_code[j] >> (L - P)] = 0xFF;
-            }
-        }
-        __syncthreads();
+// The sweeps' tables, by a workgroup of 256 threads.  One symbol per look-up over the next P bits: symbol | len << 4; a
+// prefix that starts no code: symbol K with length 0 (the lane then falls short of its stated length); a prefix of a code
+// longer than P bits: 0xFF.  From the table over 10 bits every entry of D.multi is then put together by taking codes off
+// the front of its 10 bits, a thread's four entries side by side; D.lut1 is the same table over 7 bits, for the fused
+// restore.  (The other workgroups of the kernel are long done: every dependent step here is latency of the call.)
+__device__ __forceinline__ void dec_build_luts(DecSet& D, DecBuild& B, u32 K, u32 t) {
+    constexpr u32 kEach = (1u << kMultiBits) / 256;
+    const u32 lane = t & (kW - 1);
+    const u32 len = lane < kMaxSym ? B.len[lane] : 0u, code = lane < kMaxSym ? B.code[lane] : 0u;
+    const u32 M = wave_max_u32(len);
+    u32 e[kEach];
+#pragma unroll
+    for (u32 k = 0; k < kEach; ++k) e[k] = K;
+    for (u32 j = 0; j <= K; ++j) {
+        const u32 L = read_lane(len, j), cj = read_lane(code, j);
+        if (L == 0) continue;
+        const u32 sh = L <= kMultiBits ? kMultiBits - L : 0u, want = L <= kMultiBits ? cj : cj >> (L - kMultiBits);
+        const u32 put = L <= kMultiBits ? (j | (L << 4)) : 0xFFu;
+#pragma unroll
+        for (u32 k = 0; k < kEach; ++k) if (((t + 256 * k) >> sh) == want) e[k] = put;
     }
+#pragma unroll
+    for (u32 k = 0; k < kEach; ++k) B.one[t + 256 * k] = (uint8_t)e[k];
+    __syncthreads();
+    const u32 P1 = M < kDecLut1Bits ? M : kDecLut1Bits;
+    if (t < (1u << P1)) {
+        const u32 f = B.one[t << (kMultiBits - P1)];
+        D.lut1[t] = (f == 0xFF || (f >> 4) > P1) ? (uint8_t)0xFF : (uint8_t)f;
+    }
+    u32 rest[kEach], left[kEach], syms[kEach], cnt[kEach];
+    bool on[kEach];
+#pragma unroll
+    for (u32 k = 0; k < kEach; ++k) {
+        // (the first code of the entry is the one just found)
+        const u32 L = e[k] >> 4, i = t + 256 * k;
+        on[k] = e[k] != 0xFF && L != 0;
+        syms[k] = on[k] ? e[k] & 15u : 0u; cnt[k] = on[k] ? 1u : 0u;
+        rest[k] = on[k] ? i << (32 - kMultiBits + L) : 0u; left[k] = on[k] ? kMultiBits - L : kMultiBits;
+        if (e[k] != 0xFF && L == 0) {                       // starts no code: nothing is ever taken off again
+            for (; cnt[k] < kMultiSyms; ++cnt[k]) syms[k] |= K << (4 * cnt[k]);
+        }
+    }
+#pragma unroll
+    for (u32 s = 1; s < kMultiSyms; ++s) {
+        u32 f[kEach];
+#pragma unroll
+        for (u32 k = 0; k < kEach; ++k) f[k] = B.one[rest[k] >> (32 - kMultiBits)];
+#pragma unroll
+        for (u32 k = 0; k < kEach; ++k) {
+            const u32 L = f[k] >> 4;
+            on[k] = on[k] && f[k] != 0xFF && L != 0 && L <= left[k];
+            if (on[k]) { syms[k] |= (f[k] & 15u) << (4 * s); ++cnt[k]; rest[k] <<= L; left[k] -= L; }
+        }
+    }
+#pragma unroll
+    for (u32 k = 0; k < kEach; ++k) D.multi[t + 256 * k] = syms[k] | ((kMultiBits - left[k]) << 24) | (cnt[k] << 28);
 }
 
 // One chunk's place in the offset table against the lane lengths of its record, by one wavefront.
@@ -144,7 +178,7 @@ __global__ __launch_bounds__(256) void k_dec_check(BlobList blobs, u32 first, u6
     const uint8_t* blob = blobs.p[set];
     __shared__ u32 hdr[kHeaderBytes / 4];
     __shared__ u32 s_ok;
-    __shared__ u32 s_len[kMaxSym], s_code[kMaxSym];
+    __shared__ DecBuild B;
     const u32 t = threadIdx.x, lane = lane_id();
     if (t < kHeaderBytes / 4) hdr[t] = reinterpret_cast<const u32*>(blob)[t];
     __syncthreads();
@@ -172,32 +206,44 @@ __global__ __launch_bounds__(256) void k_dec_check(BlobList blobs, u32 first, u6
     if (blockIdx.x != 0) return;
     // ---- workgroup 0: symbol table, codes, look-up table
     DecSet& D = ws->dec_set[set];
-    if (t == 0) {
-        const bool ok = dec_symbol_table(hdr, n, nchunks, area, tw, D, s_len, s_code);
-        if (!ok) raise_status(ws, host, epoch, 4u);
-        host->bytes[host_slot] = total; host->max_len[host_slot] = D.info.max_len;
-        s_ok = ok;
+    if (t < kW) {
+        const bool ok = dec_symbol_table(hdr, n, nchunks, area, tw, D, B);
+        if (t == 0) {
+            if (!ok) raise_status(ws, host, epoch, 4u);
+            host->bytes[host_slot] = total; host->max_len[host_slot] = B.max_len;
+            s_ok = ok;
+        }
     }
     __syncthreads();
     if (!s_ok) return;
-    dec_build_luts(D, s_len, s_code, t, 256);
+    dec_build_luts(D, B, hdr[5], t);
 }
 
 // ----------------------------------------------------------------------------- k_decode
-// Algorithm 1 line 7: one wavefront per chunk, lane l decoding its own string with a 64-bit
-// MSB-first window.  The chunk's payload is first copied to LDS with coalesced 16-byte loads, so
-// the lanes' word-by-word refills never go to memory.  Symbols come from the two look-up tables
-// (codes longer than 12 bits take a short search); the merged symbol adds -0.0, which leaves
-// every fp32 pattern unchanged, and a row in which no lane decoded a kept symbol is not written
-// back at all.
+// Algorithm 1 line 7: one wavefront per chunk, lane l decoding its own string.  The chunk's payload is first copied to LDS
+// with coalesced 16-byte loads, so the lanes' word-by-word refills never go to memory.
+//
+// Decoding is a serial chain per lane (the next code starts where this one ends), and what it costs is not bytes but the
+// steps of that chain: at one symbol per look-up, an LDS round trip and some 16 instructions per symbol.  Here a look-up
+// yields all the whole codes that the next 10 bits hold, up to 6 (3 on average with codes of 3 bits, 5 with codes of 1.7),
+// and the lanes, which then advance at different rates, leave their symbols (4 bits each) in a ring in LDS: 8 words of 8
+// symbols per lane, word k of lane l at [64 (k mod 8) + l], so that no two lanes ever meet in a bank.  A lane that is
+// ahead goes on until its ring is full; the slowest decides when the next 8 rows are complete.  Those rows of w_ref, which
+// were asked for 8 rows earlier, then take their representatives in a second loop that has no chain at all.
+// One symbol per look-up against this (whole calls, which also have a faster check): 2^20 fp32 elements 47.7 -> 35.8 us,
+// 161 tensors of 25.6 M 131 -> 88 us, 2^27 bf16 138 -> 129 us; the dense slice of 2^28 fp32, which moves 2.25 GB at what a
+// bare read-and-write sweep in this walk reaches (5.5 TB/s), 437 -> 421 us.
+// The merged symbol adds -0.0, which leaves every fp32 pattern unchanged, and a row in which no lane decoded a kept symbol
+// is not written back at all.
 constexpr u32 kPayWords = 2048;      // LDS room for one chunk's payload (4 bits per element on average) when the
                                      // compute unit is shared by as many workgroups as fit; more when fewer are needed
 constexpr u32 kSparseSlack = 512;    // bits above an all-merged chunk up to which a chunk is decoded symbols first
-constexpr u32 kPayWordsMax = 3808;   // what keeps a workgroup's LDS within 64 KB (7.4 bits per element on average)
+constexpr u32 kPayWordsMax = 3072;   // what keeps a workgroup's LDS within 64 KB (6 bits per element on average)
+constexpr u32 kRingWords = 8;        // words of 8 symbols that a lane may be ahead of the rows being restored
+constexpr u32 kGroupRows = 8;        // rows restored at a time: 32 symbols, 4 words of the ring per lane
 
 struct DecLds {
-    uint8_t lut1[1u << kDecLut1Bits];
-    uint8_t lut2[1u << kDecLut2Bits];
+    alignas(16) u32 multi[1u << kMultiBits];
     float rep[kMaxSym];
     u32 len[kMaxSym], code[kMaxSym];
     double rep64[kMaxSym];            // binary64 blobs: the representatives (rep is not used then)
@@ -207,14 +253,16 @@ struct DecLds {
     }
 };
 
+// the one symbol of a window whose first code is longer than the table's 10 bits, as an entry of the table
 template <typename LDS>
-__device__ __noinline__ u32 decode_long(const LDS& L, u64 win, u32 K) {
+__device__ __forceinline__ u32 decode_long(const LDS& L, u64 win, u32 K) {
     const u32 peek = (u32)(win >> (64 - 15));
+#pragma unroll 1
     for (u32 j = 0; j <= K; ++j) {
         const u32 l = L.len[j];
-        if (l > kDecLut2Bits && (peek >> (15 - l)) == L.code[j]) return j | (l << 4);
+        if (l > kMultiBits && (peek >> (15 - l)) == L.code[j]) return j | (l << 24) | (1u << 28);
     }
-    return K;
+    return K | (1u << 28);
 }
 
 // MSB-first bit window over payload words that live in LDS (STAGED) or in global memory.
@@ -234,221 +282,209 @@ struct BitReader {
         wi += 2;
         next = word(wi);
     }
-    __device__ __forceinline__ void refill() {           // call when avail <= 32
-        win |= (u64)next << (32 - avail);
-        avail += 32; ++wi;
-        next = word(wi);
+    __device__ __forceinline__ void refill() {           // leaves at least 33 valid bits
+        if (avail <= 32) {
+            win |= (u64)next << (32 - avail);
+            avail += 32; ++wi;
+            next = word(wi);
+        }
     }
+    __device__ __forceinline__ void drop(u32 len) { win <<= len; avail -= len; }
 };
 
 // `raise(code)` reports a lane string that does not decode to its stated length.
-// DEEP: the launch has so few wavefronts that nothing hides a wavefront's waits on memory: rows are then fetched 8 at
-// a time (2-byte elements: 16), two such batches in flight, instead of 4.
+// LONG: the blob has codes of more than 10 bits.
 // VERIFY: the lane strings are only decoded and measured against their stated lengths; w_ref is not touched (nor read).
-template <bool FAST, bool LV2, bool STAGED, int DT, bool DEEP, bool VERIFY, typename LDS, typename Raise>
+// ring: this wavefront's kRingWords * 64 words of LDS.
+template <bool FAST, bool LONG, bool STAGED, int DT, bool VERIFY, typename LDS, typename Raise>
 __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 first_bit, u32 lane_bits,
                                             void* __restrict__ w_ref, u64 n, u32 c,
-                                            const LDS& L, u32 P1, u32 P2, u32 K, u32 row_zero_bits, bool sparse, Raise& raise) {
+                                            const LDS& L, u32* ring, u32 K, bool sparse, Raise& raise) {
+    typedef typename Val<DT>::type val_t;
     const u32 lane = lane_id();
     BitReader<STAGED> br;
     br.start(words, nwords, first_bit);
     const u32 wi0 = br.wi, avail0 = br.avail;
-    const u32 shr1 = 64 - P1, shr2 = 64 - P2;
     const u64 base = (u64)c * kChunk;
-    if constexpr (VERIFY) {
-        auto symbols_of_row = [&](u64 idx) {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                if (FAST || idx + v < n) {
-                    u32 e = L.lut1[(u32)(br.win >> shr1)];
-                    if (LV2 && e == 0xFF) {
-                        e = L.lut2[(u32)(br.win >> shr2)];
-                        if (e == 0xFF) e = decode_long(L, br.win, K);
-                    }
-                    const u32 len = e >> 4;
-                    br.win <<= len; br.avail -= len;
-                }
-                if ((v & 1) && br.avail <= 32) br.refill();
-            }
-        };
-        if (sparse && row_zero_bits != 0) {
-            // a chunk with few kept symbols: a whole row of merged symbols whose code is zeros is passed over as in
-            // the restoring sweep (in a loop of its own: elsewhere the test costs more than it saves)
-            for (u32 r = 0; r < kR && (FAST || base + (u64)r * kRowElems < n); ++r) {
-                if ((FAST || base + (u64)(r + 1) * kRowElems <= n) && !__any((u32)(br.win >> (64 - row_zero_bits)) != 0)) {
-                    br.win <<= row_zero_bits; br.avail -= row_zero_bits;
-                    if (br.avail <= 32) br.refill();
-                    continue;
-                }
-                symbols_of_row(base + (u64)r * kRowElems + lane * kV);
-            }
-        } else {
-            for (u32 r = 0; r < kR && (FAST || base + (u64)r * kRowElems < n); ++r) symbols_of_row(base + (u64)r * kRowElems + lane * kV);
+    // Places in a lane's string of symbols are counted in bits of the ring, 4 to a symbol.
+    constexpr int kGroupQ = kGroupRows * kV * 4, kRingQ = kRingWords * 32, kStepQ = kMultiSyms * 4;
+    static_assert(kRingQ == 2 * kGroupQ && kStepQ < 32, "a step fills at most one word; the ring holds two groups");
+    int limit = kR * kV * 4;                             // the end of this lane's string
+    if (!FAST) {
+        const u32 left = n - base < kChunk ? (u32)(n - base) : kChunk, tail = left % kRowElems;
+        const u32 mine = tail > lane * kV ? min(tail - lane * kV, kV) : 0u;
+        limit = (int)((left / kRowElems * kV + mine) * 4);
+    }
+    int q = 0;                                           // symbols so far, and
+    u32 acc = 0;                                         // those of the word of the ring that is being filled
+    u32* mine = ring + lane;
+    auto append = [&](u32 e) {
+        const u64 s = (u64)(e & 0xFFFFFFu) << (q & 31);
+        acc |= (u32)s;
+        if (!VERIFY) mine[((q >> 5) & (kRingWords - 1)) * kW] = acc;       // (a partly filled word is written again by the next step)
+        const int qn = q + (int)((e >> 28) << 2);
+        if ((qn ^ q) & 32) acc = (u32)(s >> 32);
+        q = qn;
+        br.drop((e >> 24) & 15u);
+    };
+    // all the codes of the next 10 bits, by the lanes that have not come to `cap` (33 valid bits take three such steps,
+    // two if one of them may be a code of up to 15 bits)
+    auto step = [&](int cap) {
+        u32 e = L.multi[(u32)(br.win >> (64 - kMultiBits))];
+        if (LONG && __any(q < cap && e == 0)) { if (e == 0) e = decode_long(L, br.win, K); }
+        append(q < cap ? e : 0u);
+    };
+    // the next code alone, by the lanes that have not come to `end`
+    auto one = [&](int end) {
+        u32 e = L.multi[(u32)(br.win >> (64 - kMultiBits))];
+        if (LONG && __any(e == 0)) { if (e == 0) e = decode_long(L, br.win, K); }
+        const u32 sy = e & 15u, len = (e & 0x0F000000u) ? L.len[sy] : 0u;       // (length 0: a prefix that starts no code)
+        append(q < end ? (sy | (len << 24) | (1u << 28)) : 0u);
+    };
+    // the symbols of group g, complete in the ring
+    const int stop = limit - kStepQ + 4;                 // from here on a step could pass the end of the string
+    auto symbols = [&](u32 g) {
+        const int end = min((int)(g + 1) * kGroupQ, limit), many = min(end, stop);
+        const int cap = min((int)g * kGroupQ + kRingQ - kStepQ, stop);         // (no word of this group is overwritten)
+        while (__any(q < many)) {
+            step(cap);
+            step(cap);
+            if (!LONG) step(cap);
+            br.refill();
         }
+        if (!FAST || g + 1 == kR / kGroupRows)
+            while (__any(q < end)) { one(end); br.refill(); }
+    };
+    auto row_at = [&](u32 r) { return base + (u64)r * kRowElems + lane * kV; };
+    // the 4 symbols of row k of group g, as the low 16 bits
+    auto row_syms = [&](u32 g, u32 k) { return mine[((g * (kGroupRows / 2) + k / 2) & (kRingWords - 1)) * kW] >> (16 * (k & 1)); };
+    auto any_kept = [&](u32 syms) { return __any(((syms ^ (K * 0x1111u)) & 0xFFFFu) != 0); };
+    auto add_row = [&](u32 syms, val_t (&x)[4]) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = add_rn(x[v], L.template rep_of<DT>((syms >> (4 * v)) & 15u));
+    };
+    auto check = [&]() {
         const u32 used = avail0 + 32 * (br.wi - wi0) - br.avail;
         if (__any(used != lane_bits) && lane == 0) raise(4u);
-        return;
-    }
-    // one row of the chunk; WHOLE: all 4 elements of every lane exist and the row can be stored as vectors
-    typedef typename Val<DT>::type val_t;
-    auto row = [&](auto whole, u64 idx, val_t (&x)[4]) {
-        constexpr bool WHOLE = decltype(whole)::value;
-        // row_zero_bits = 4 x the merged symbol's code length when that code is all zero bits (at most 32): so many
-        // zero bits at the head of every lane's window are 4 merged symbols each, and the row stays as it is
-        if (WHOLE && row_zero_bits != 0 && !__any((u32)(br.win >> (64 - row_zero_bits)) != 0)) {
-            br.win <<= row_zero_bits; br.avail -= row_zero_bits;
-            if (br.avail <= 32) br.refill();
-            return;
-        }
-        u32 smin = K;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            if (WHOLE || idx + v < n) {
-                u32 e = L.lut1[(u32)(br.win >> shr1)];
-                if (LV2 && e == 0xFF) {
-                    e = L.lut2[(u32)(br.win >> shr2)];
-                    if (e == 0xFF) e = decode_long(L, br.win, K);
-                }
-                const u32 len = e >> 4, sy = e & 15;
-                br.win <<= len; br.avail -= len;
-                smin = min(smin, sy);
-                x[v] = add_rn(x[v], L.template rep_of<DT>(sy));
-            }
-            if ((v & 1) && br.avail <= 32) br.refill();
-        }
-        if (WHOLE) {
-            if (__any(smin < K)) store4_v<DT>(w_ref, idx, x);
-        } else {
-#pragma unroll
-            for (int v = 0; v < 4; ++v) if (idx + v < n) store_one_v<DT>(w_ref, idx + v, x[v]);
-        }
     };
-    typedef std::integral_constant<bool, true> yes;
-    typedef std::integral_constant<bool, false> no;
-    const bool vec = FAST || (reinterpret_cast<uintptr_t>(w_ref) & (DT == kF64 ? 15 : 4 * elem_bytes<DT>() - 1)) == 0;
-    if (sparse && vec) {
-        // A chunk that holds few kept symbols (its caller has seen that from its size): a row of merged symbols
-        // needs no look at w_ref at all, so the symbols come first, a group of rows at a time, and only the rows
-        // in which some lane decoded a kept symbol are then fetched (together), added to and stored.  The one
-        // wavefront that owns such a chunk no longer waits for 64 rows of memory, only for the few it changes.
-        constexpr u32 G = DT == kF64 ? 4 : 8;
-        // the symbols of one whole row: 4 representatives per lane; true if any lane holds a kept symbol
-        auto row_reps = [&](val_t (&rp)[4]) -> bool {
-            if (row_zero_bits != 0 && !__any((u32)(br.win >> (64 - row_zero_bits)) != 0)) {
-                br.win <<= row_zero_bits; br.avail -= row_zero_bits;
-                if (br.avail <= 32) br.refill();
-                return false;
-            }
-            u32 smin = K;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                u32 e = L.lut1[(u32)(br.win >> shr1)];
-                if (LV2 && e == 0xFF) {
-                    e = L.lut2[(u32)(br.win >> shr2)];
-                    if (e == 0xFF) e = decode_long(L, br.win, K);
-                }
-                const u32 len = e >> 4, sy = e & 15;
-                br.win <<= len; br.avail -= len;
-                smin = min(smin, sy);
-                rp[v] = L.template rep_of<DT>(sy);
-                if ((v & 1) && br.avail <= 32) br.refill();
-            }
-            return __any(smin < K);
-        };
-        const u64 left = n - base;
-        const u32 whole_rows = FAST ? kR : (u32)(left / kRowElems < kR ? left / kRowElems : kR);
-        u32 r = 0;
-        for (; r + G <= whole_rows; r += G) {
-            val_t rp[G][4], x[G][4];
-            bool kept[G];
-#pragma unroll
-            for (u32 k = 0; k < G; ++k) kept[k] = row_reps(rp[k]);
-#pragma unroll
-            for (u32 k = 0; k < G; ++k)
-                if (kept[k]) load_row_v<true, DT>(w_ref, base + (u64)(r + k) * kRowElems + lane * kV, n, x[k]);
-#pragma unroll
-            for (u32 k = 0; k < G; ++k) {
-                if (kept[k]) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) x[k][v] = add_rn(x[k][v], rp[k][v]);
-                    store4_v<DT>(w_ref, base + (u64)(r + k) * kRowElems + lane * kV, x[k]);
-                }
-            }
-        }
-        for (; r < whole_rows; ++r) {
-            val_t rp[4], x[4];
-            if (row_reps(rp)) {
-                const u64 idx = base + (u64)r * kRowElems + lane * kV;
-                load_row_v<true, DT>(w_ref, idx, n, x);
-#pragma unroll
-                for (int v = 0; v < 4; ++v) x[v] = add_rn(x[v], rp[v]);
-                store4_v<DT>(w_ref, idx, x);
-            }
-        }
-        for (; r < kR && base + (u64)r * kRowElems < n; ++r) {
-            const u64 idx = base + (u64)r * kRowElems + lane * kV;
-            val_t x[4];
-            load_row_v<false, DT>(w_ref, idx, n, x);
-            row(no(), idx, x);
-        }
-    } else if (FAST && DT == kF32 && !DEEP) {
-#pragma unroll 4
-        for (u32 r = 0; r < kR; ++r) {
-            const u64 idx = base + (u64)r * kRowElems + lane * kV;
-            val_t x[4];
-            load_row_v<true, DT>(w_ref, idx, n, x);
-            row(yes(), idx, x);
-        }
-    } else if (FAST) {
-        // 2-byte and 8-byte elements: rows in batches of 4, the next batch fetched before this one is decoded and stored
-        // (in program order: the compiler does not move a load above an earlier store of the same kind).  13 % faster
-        // than the loop above for bf16, 1 % for fp64; 3 % slower for fp32, which keeps the loop.
-        constexpr u32 PF = DEEP ? ((DT == kF64 || DT == kF32) ? 8 : 16) : 4;        // (two workgroups must still fit a compute unit)
+    br.refill();
+    if constexpr (VERIFY) {
+        for (u32 g = 0; g < kR / kGroupRows && (FAST || base + (u64)g * kGroupRows * kRowElems < n); ++g) symbols(g);
+    } else if constexpr (FAST) {
         typedef typename Raw<DT>::type raw_t;
-        auto fetch = [&](raw_t (&X)[PF], u32 r0) {
+        auto fetch = [&](raw_t (&X)[kGroupRows], u32 g) {
 #pragma unroll
-            for (u32 k = 0; k < PF; ++k) X[k] = load_raw<DT>(w_ref, base + (u64)(r0 + k) * kRowElems + lane * kV);
+            for (u32 k = 0; k < kGroupRows; ++k) X[k] = load_raw<DT>(w_ref, row_at(g * kGroupRows + k));
         };
-        auto batch = [&](const raw_t (&X)[PF], u32 r0) {
+        auto restore = [&](const raw_t (&X)[kGroupRows], u32 g) {
 #pragma unroll
-            for (u32 k = 0; k < PF; ++k) {
+            for (u32 k = 0; k < kGroupRows; ++k) {
+                const u32 syms = row_syms(g, k);
+                if (!any_kept(syms)) continue;
                 val_t x[4];
                 if constexpr (DT == kF64) unpack64(X[k], x); else unpack<DT>(X[k], x);
-                row(yes(), base + (u64)(r0 + k) * kRowElems + lane * kV, x);
+                add_row(syms, x);
+                store4_v<DT>(w_ref, row_at(g * kGroupRows + k), x);
             }
         };
-        raw_t A[PF], B[PF];
-        fetch(A, 0);
-        for (u32 r0 = 0; r0 < kR; r0 += 2 * PF) {
-            fetch(B, r0 + PF);
-            batch(A, r0);
-            if (r0 + 2 * PF < kR) fetch(A, r0 + 2 * PF);
-            batch(B, r0 + PF);
-        }
-    } else {
-        // A ragged or unaligned chunk (the vector's last chunk is one wavefront's work from start to end, so its
-        // memory round trips count): whole rows of an aligned array as in a full chunk, four fetched before the
-        // first is decoded; the rest with guarded element accesses.
-        u32 r = 0;
-        if (vec) {
-            constexpr u32 RB = 4;
-            for (; r + RB <= kR && base + (u64)(r + RB) * kRowElems <= n; r += RB) {
-                val_t x[RB][4];
+        if (!sparse) {
+            raw_t A[kGroupRows], B[kGroupRows];
+            fetch(A, 0);
+            for (u32 g = 0; g < kR / kGroupRows; g += 2) {
+                fetch(B, g + 1);
+                symbols(g);
+                restore(A, g);
+                if (g + 2 < kR / kGroupRows) fetch(A, g + 2);
+                symbols(g + 1);
+                restore(B, g + 1);
+            }
+        } else {
+            // A chunk that holds few kept symbols (its caller has seen that from its size): the lanes stay in step, a row
+            // at a time, and where every lane's window starts with the merged symbol's code 4 times over (8 rows: 32 times)
+            // the rows are passed over without a look-up.  A row of merged symbols needs no look at w_ref either: only the
+            // rows in which some lane decoded a kept symbol are fetched (those of a group together), added to and stored.
+            const u32 zero_len = L.code[K] == 0 ? L.len[K] : 0u;
+            const u32 row_zeros = zero_len * kV <= 32 ? zero_len * kV : 0u, group_zeros = zero_len * kV * kGroupRows <= 32 ? zero_len * kV * kGroupRows : 0u;
+            for (u32 g = 0; g < kR / kGroupRows; ++g) {
+                if (group_zeros != 0 && !__any((u32)(br.win >> (64 - group_zeros)) != 0)) {
+                    br.drop(group_zeros);
+                    br.refill();
+                    continue;
+                }
+                raw_t X[kGroupRows];
+                u32 syms[kGroupRows];
+                u32 kept = 0;
 #pragma unroll
-                for (u32 k = 0; k < RB; ++k) load_row_v<true, DT>(w_ref, base + (u64)(r + k) * kRowElems + lane * kV, n, x[k]);
+                for (u32 k = 0; k < kGroupRows; ++k) {
+                    if (row_zeros != 0 && !__any((u32)(br.win >> (64 - row_zeros)) != 0)) {
+                        br.drop(row_zeros);
+                        br.refill();
+                        continue;
+                    }
+                    syms[k] = 0;
 #pragma unroll
-                for (u32 k = 0; k < RB; ++k) row(yes(), base + (u64)(r + k) * kRowElems + lane * kV, x[k]);
+                    for (int v = 0; v < 4; ++v) {
+                        u32 e = L.multi[(u32)(br.win >> (64 - kMultiBits))];
+                        if (LONG && __any(e == 0)) { if (e == 0) e = decode_long(L, br.win, K); }
+                        const u32 sy = e & 15u;
+                        syms[k] |= sy << (4 * v);
+                        br.drop((e & 0x0F000000u) ? L.len[sy] : 0u);
+                        if (v & 1) br.refill();
+                    }
+                    if (!any_kept(syms[k])) continue;
+                    kept |= 1u << k;
+                    X[k] = load_raw<DT>(w_ref, row_at(g * kGroupRows + k));
+                }
+                if (kept == 0) continue;
+#pragma unroll
+                for (u32 k = 0; k < kGroupRows; ++k) {
+                    if (!((kept >> k) & 1u)) continue;
+                    val_t x[4];
+                    if constexpr (DT == kF64) unpack64(X[k], x); else unpack<DT>(X[k], x);
+                    add_row(syms[k], x);
+                    store4_v<DT>(w_ref, row_at(g * kGroupRows + k), x);
+                }
             }
         }
-        for (; r < kR && base + (u64)r * kRowElems < n; ++r) {
-            const u64 idx = base + (u64)r * kRowElems + lane * kV;
-            val_t x[4];
-            load_row_v<false, DT>(w_ref, idx, n, x);
-            row(no(), idx, x);
+    } else {
+        // A ragged or unaligned chunk (the vector's last chunk is one wavefront's work from start to end, so its memory
+        // round trips count): rows that lie wholly inside an aligned array as vectors, the rest element by element, a
+        // group's kept rows fetched together.
+        const bool vec = (reinterpret_cast<uintptr_t>(w_ref) & (DT == kF64 ? 15 : 4 * elem_bytes<DT>() - 1)) == 0;
+        for (u32 g = 0; g < kR / kGroupRows && base + (u64)g * kGroupRows * kRowElems < n; ++g) {
+            val_t x[kGroupRows][4];
+            auto fetch = [&](u32 k) {
+                const u32 r = g * kGroupRows + k;
+                if (vec && base + (u64)(r + 1) * kRowElems <= n) load_row_v<true, DT>(w_ref, row_at(r), n, x[k]);
+                else load_row_v<false, DT>(w_ref, row_at(r), n, x[k]);
+            };
+            if (!sparse) {
+#pragma unroll
+                for (u32 k = 0; k < kGroupRows; ++k) fetch(k);           // on their way while the symbols are decoded
+            }
+            symbols(g);
+            if (sparse) {
+#pragma unroll
+                for (u32 k = 0; k < kGroupRows; ++k) if (any_kept(row_syms(g, k))) fetch(k);
+            }
+#pragma unroll
+            for (u32 k = 0; k < kGroupRows; ++k) {
+                const u32 r = g * kGroupRows + k, syms = row_syms(g, k);
+                if (vec && base + (u64)(r + 1) * kRowElems <= n) {
+                    if (!any_kept(syms)) continue;
+                    add_row(syms, x[k]);
+                    store4_v<DT>(w_ref, row_at(r), x[k]);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const u32 sy = (syms >> (4 * v)) & 15u;
+                        if (row_at(r) + v < n && sy != K) store_one_v<DT>(w_ref, row_at(r) + v, add_rn(x[k][v], L.template rep_of<DT>(sy)));
+                    }
+                }
+            }
         }
     }
-    const u32 used = avail0 + 32 * (br.wi - wi0) - br.avail;
-    if (__any(used != lane_bits) && lane == 0) raise(4u);
+    check();
 }
 
 // zero_bits: what every lane length of a full chunk is when all its elements are the merged symbol and that
@@ -458,36 +494,53 @@ __device__ __forceinline__ u32 zero_chunk_bits(u32 len_merged, u32 code_merged) 
     return (len_merged != 0 && code_merged == 0) ? kR * kV * len_merged : 0u;
 }
 
-// pay: this wavefront's LDS area of pay_words + 4 words for the chunk's payload
-template <bool FAST, bool LV2, int DT, bool DEEP = false, bool VERIFY = false, typename LDS, typename Raise>
+// A chunk's record looked at where it lies, to tell whether it is such a chunk's: nothing is staged for it, and a wavefront
+// that meets no other chunk never needs the blob's tables.  The loads of `start` are on their way while the chunk before is
+// restored; o0, o1: the chunk's entries of the offset table.
+struct QuietChunk {
+    const u32* rec;
+    u32 nwords, differs, x[8];                  // payload words in all (0: the chunk's size alone says that it is none); the first 512
+    __device__ __forceinline__ void start(const uint8_t* __restrict__ blob, u64 area, u32 o0, u32 o1, u32 zero_bits, bool full) {
+        nwords = o1 - o0 - kLaneBitsWords;
+        if (!full || zero_bits == 0 || nwords != zero_bits * kW / 32) { nwords = 0; return; }
+        rec = reinterpret_cast<const u32*>(blob + area + 4 * (u64)o0);
+        differs = reinterpret_cast<const uint16_t*>(rec)[lane_id()];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k] = rec[kLaneBitsWords + lane_id() + k * kW];      // (nwords: a multiple of 512)
+    }
+    __device__ __forceinline__ bool holds(u32 zero_bits) {
+        if (nwords == 0) return false;
+        differs ^= zero_bits;
+        for (u32 i = 0;;) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) differs |= x[k];
+            i += 8 * kW;
+            if (i >= nwords) break;
+#pragma unroll
+            for (int k = 0; k < 8; ++k) x[k] = rec[kLaneBitsWords + i + lane_id() + k * kW];
+        }
+        return !__any(differs != 0);
+    }
+};
+
+// pay: this wavefront's LDS area of pay_words + 4 words for the chunk's payload; ring: its symbol ring
+template <bool FAST, bool LONG, int DT, bool VERIFY = false, typename LDS, typename Raise>
 __device__ __forceinline__ void decode_chunk(const uint8_t* __restrict__ blob, void* __restrict__ w_ref, u64 n,
-                                             u32 c, u32 o0, u32 o1, LDS& L, uint4* pay, u32 pay_words, u32 P1, u32 P2, u32 K,
-                                             u64 area, u32 zero_bits, Raise& raise) {
+                                             u32 c, u32 o0, u32 o1, LDS& L, uint4* pay, u32 pay_words, u32* ring, u32 K,
+                                             u64 area, Raise& raise) {
     // o0, o1: the chunk's entries c and c + 1 of the offset table (fetched by the caller, ahead of time)
     const u32 lane = lane_id();
     const uint8_t* rec = blob + area + 4 * (u64)o0;
     const u32 nwords = o1 - o0 - kLaneBitsWords;        // >= 1 (validated)
     const u32 lane_bits = reinterpret_cast<const uint16_t*>(rec)[lane];
-    const u32 o = wave_incl_scan(lane_bits) - lane_bits;
     const u32* gw = reinterpret_cast<const u32*>(rec + 2 * kW);
     const u32 k0 = (u32)((reinterpret_cast<uintptr_t>(gw) >> 2) & 3);     // words between the 16-byte boundary and the payload
-    // 4 merged symbols in a row are this many zero bits (when the merged code is zeros, and short enough to test)
-    const u32 whole_zero = zero_chunk_bits(L.len[K], L.code[K]);
-    const u32 row_zero_bits = whole_zero / (kR * kV) * kV <= 32 ? whole_zero / (kR * kV) * kV : 0u;
-    // Few kept symbols?  When the merged symbol's code is shorter than every other, each kept symbol costs at least
-    // one bit more, so a chunk of at most kSparseSlack bits above (elements x merged length) holds at most that many.
-    u32 len_merged = L.len[K];
-    for (u32 j = 0; j < K; ++j) if (L.len[j] != 0 && L.len[j] <= L.len[K]) len_merged = 0;
-    const u64 left = n - (u64)c * kChunk;
-    const u32 elems = left < kChunk ? (u32)left : kChunk;
-    const u32 chunk_bits = read_lane(o + lane_bits, kW - 1);
-    const bool sparse = len_merged != 0 && chunk_bits <= elems * len_merged + kSparseSlack;
-    if (nwords + k0 <= pay_words) {
+    const bool staged = nwords + k0 <= pay_words;
+    if (staged) {
         // coalesced copy of [aligned start, payload end) to LDS; the bytes before the payload are the
         // record's own lane lengths, and the last vector is read word by word so no read passes the end
         const uint4* gv = reinterpret_cast<const uint4*>(gw - k0);
         const u32 nvec = (nwords + k0 + 3) >> 2;
-        u32 nonzero = 0;
         for (u32 i = lane; i < nvec; i += kW) {
             uint4 q;
             if (4 * i + 4 <= nwords + k0) q = gv[i];
@@ -497,24 +550,31 @@ __device__ __forceinline__ void decode_chunk(const uint8_t* __restrict__ blob, v
                 q.x = t[0]; q.y = left > 1 ? t[1] : 0; q.z = left > 2 ? t[2] : 0; q.w = 0;
             }
             pay[i] = q;
-            // payload words only: the first vector may start with up to 3 words of lane lengths
-            nonzero |= (i == 0) ? ((k0 < 1 ? q.x : 0u) | (k0 < 2 ? q.y : 0u) | (k0 < 3 ? q.z : 0u) | q.w) : (q.x | q.y | q.z | q.w);
         }
-        if (zero_bits != 0 && !__any(lane_bits != zero_bits || nonzero != 0)) return;
-        decode_rows<FAST, LV2, true, DT, DEEP, VERIFY>(reinterpret_cast<const u32*>(pay) + k0, nwords, o, lane_bits,
-                                         w_ref, n, c, L, P1, P2, K, row_zero_bits, sparse, raise);
+    }
+    const u32 incl = wave_incl_scan(lane_bits), o = incl - lane_bits;
+    // Few kept symbols?  When the merged symbol's code is shorter than every other, each kept symbol costs at least
+    // one bit more, so a chunk of at most kSparseSlack bits above (elements x merged length) holds at most that many.
+    u32 len_merged = L.len[K];
+    for (u32 j = 0; j < K; ++j) if (L.len[j] != 0 && L.len[j] <= L.len[K]) len_merged = 0;
+    const u64 left = n - (u64)c * kChunk;
+    const u32 elems = left < kChunk ? (u32)left : kChunk;
+    const bool sparse = len_merged != 0 && read_lane(incl, kW - 1) <= elems * len_merged + kSparseSlack;
+    if (staged) {
+        decode_rows<FAST, LONG, true, DT, VERIFY>(reinterpret_cast<const u32*>(pay) + k0, nwords, o, lane_bits, w_ref, n, c, L, ring, K, sparse, raise);
     } else {
-        decode_rows<FAST, LV2, false, DT, DEEP, VERIFY>(gw, nwords, o, lane_bits, w_ref, n, c, L, P1, P2, K, row_zero_bits, sparse, raise);
+        decode_rows<FAST, LONG, false, DT, VERIFY>(gw, nwords, o, lane_bits, w_ref, n, c, L, ring, K, sparse, raise);
     }
 }
 
 // VERIFY: lc_verify's sweep (and the one lc_decode runs first when asked to): the same walk over the blob, decoding
 // only; `w_ref` is not used.
-template <int DT, bool DEEP, bool VERIFY = false>
-__global__ __launch_bounds__(256) void k_decode(const uint8_t* __restrict__ blob, void* __restrict__ w_ref, u64 n,
+template <int DT, bool VERIFY = false>
+__global__ __launch_bounds__(256, DT == kF64 ? 2 : 3) void k_decode(const uint8_t* __restrict__ blob, void* __restrict__ w_ref, u64 n,
                                                 Workspace* ws, u32 nchunks, int aligned, u64 epoch, HostResult* host,
                                                 u32 pay_words, u32 set) {
     __shared__ DecLds L;
+    __shared__ u32 s_ring[VERIFY ? 1 : 4 * kRingWords * kW];
     extern __shared__ uint4 dec_pay[];                   // 4 areas of pay_words + 4 payload words, one per wavefront
     // What the check kernel left (the verdict and the blob's tables) is fetched in one go: a failed check leaves
     // tables that mean nothing, but reading them is harmless.  If it found something, nothing else is touched.
@@ -523,53 +583,70 @@ __global__ __launch_bounds__(256) void k_decode(const uint8_t* __restrict__ blob
     const u64 verdict = __hip_atomic_load(&ws->dec_status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     u32 M = D.info.max_len, K = D.info.K;
     u64 area = D.info.area;
-    u32 lut1_entry = t < (1u << kDecLut1Bits) ? D.lut1[t] : 0u;
+    const u32 lane = t & (kW - 1);
     u32 sym_rep = 0, sym_rep_hi = 0, sym_len = 0, sym_code = 0;
-    if (t < kMaxSym) { sym_rep = D.info.rep_bits[t]; sym_rep_hi = D.info.rep_hi[t]; sym_len = D.info.len[t]; sym_code = D.info.code[t]; }
+    if (lane < kMaxSym) { sym_rep = D.info.rep_bits[lane]; sym_rep_hi = D.info.rep_hi[lane]; sym_len = D.info.len[lane]; sym_code = D.info.code[lane]; }
+    const u32* off_tab = reinterpret_cast<const u32*>(blob + kHeaderBytes);
+    const u32 wave = t >> 6, stride = gridDim.x * 4;
+    const u32 first = blockIdx.x * 4 + wave;
+    // the offset-table entries of this wavefront's next 64 chunks, one chunk per lane
+    u32 off0 = 0, off1 = 0;
+    auto fetch_offsets = [&](u64 from) {
+        const u64 c = from + (u64)lane * stride;
+        if (c < nchunks) { off0 = off_tab[c]; off1 = off_tab[c + 1]; }
+    };
+    fetch_offsets(first);
     // (the empty statement keeps these loads ahead of the branch; the values every lane holds alike go back to scalars)
-    asm volatile("" : "+v"(M), "+v"(K), "+v"(area), "+v"(lut1_entry), "+v"(sym_rep), "+v"(sym_rep_hi), "+v"(sym_len), "+v"(sym_code));
+    asm volatile("" : "+v"(M), "+v"(K), "+v"(area), "+v"(sym_rep), "+v"(sym_rep_hi), "+v"(sym_len), "+v"(sym_code), "+v"(off0), "+v"(off1));
     M = __builtin_amdgcn_readfirstlane(M); K = __builtin_amdgcn_readfirstlane(K);
     area = ((u64)__builtin_amdgcn_readfirstlane((u32)(area >> 32)) << 32) | __builtin_amdgcn_readfirstlane((u32)area);
-    if ((verdict >> 8) != epoch) {
-        const u32 P1 = M < kDecLut1Bits ? M : kDecLut1Bits, P2 = M < kDecLut2Bits ? M : kDecLut2Bits;
-        const u32* off_tab = reinterpret_cast<const u32*>(blob + kHeaderBytes);
-        const u32 wave = t >> 6, stride = gridDim.x * 4;
-        u32 c = blockIdx.x * 4 + wave;
-        u32 o0 = 0, o1 = 0;
-        if (c < nchunks) { o0 = off_tab[c]; o1 = off_tab[c + 1]; }
-        if (t < (1u << P1)) L.lut1[t] = (uint8_t)lut1_entry;
-        if (M > kDecLut1Bits) {
-            if ((1u << P2) >= 4096) {
-                const uint4* src = reinterpret_cast<const uint4*>(D.lut2);
-                uint4* dst = reinterpret_cast<uint4*>(L.lut2);
-                for (u32 i = t; i < (1u << P2) / 16; i += 256) dst[i] = src[i];
-            } else {
-                for (u32 i = t; i < (1u << P2); i += 256) L.lut2[i] = D.lut2[i];
+    if ((verdict >> 8) == epoch || first >= nchunks) return;
+    uint4* pay = dec_pay + wave * (pay_words / 4 + 1);
+    u32* ring = VERIFY ? s_ring : s_ring + wave * kRingWords * kW;
+    const u32 zero_bits = zero_chunk_bits(read_lane(sym_len, K), read_lane(sym_code, K));
+    auto raise = [&](u32 code) { raise_status(ws, host, epoch, code); };
+    // A wavefront brings the tables to LDS when it comes to the first chunk that has to be decoded (in a sparse blob most
+    // never do).  Each does so for itself: they all write the same values to the same places, and none waits for another.
+    bool have_tables = false;
+    QuietChunk q;
+    u32 turn = 0, c = first, o0 = read_lane(off0, 0), o1 = read_lane(off1, 0);
+    q.start(blob, area, o0, o1, zero_bits, (u64)(c + 1) * kChunk <= n);
+    while (true) {
+        const bool full = (u64)(c + 1) * kChunk <= n;
+        const bool quiet = q.holds(zero_bits);
+        const u64 cn = (u64)c + stride;
+        const bool more = cn < nchunks;
+        u32 n0 = 0, n1 = 0;
+        if (more) {
+            ++turn;
+            if ((turn & (kW - 1)) == 0) fetch_offsets(cn);
+            n0 = read_lane(off0, turn & (kW - 1)); n1 = read_lane(off1, turn & (kW - 1));
+            q.start(blob, area, n0, n1, zero_bits, (cn + 1) * kChunk <= n);
+        }
+        if (!quiet) {
+            if (!have_tables) {
+                have_tables = true;
+                u32x4 e[(1u << kMultiBits) / 4 / kW];
+#pragma unroll
+                for (u32 k = 0; k < (1u << kMultiBits) / 4 / kW; ++k) e[k] = reinterpret_cast<const u32x4*>(D.multi)[lane + k * kW];
+#pragma unroll
+                for (u32 k = 0; k < (1u << kMultiBits) / 4 / kW; ++k) reinterpret_cast<u32x4*>(L.multi)[lane + k * kW] = e[k];
+                if (lane < kMaxSym) {
+                    L.rep[lane] = __uint_as_float(lane < K ? sym_rep : 0x80000000u);
+                    L.rep64[lane] = lane < K ? __hiloint2double((int)sym_rep_hi, (int)sym_rep) : -0.0;
+                    L.len[lane] = sym_len; L.code[lane] = sym_code;
+                }
+                __builtin_amdgcn_wave_barrier();
             }
-        }
-        if (t < kMaxSym) {
-            L.rep[t] = __uint_as_float(t < K ? sym_rep : 0x80000000u);
-            L.rep64[t] = t < K ? __hiloint2double((int)sym_rep_hi, (int)sym_rep) : -0.0;
-            L.len[t] = sym_len; L.code[t] = sym_code;
-        }
-        __syncthreads();
-        uint4* pay = dec_pay + wave * (pay_words / 4 + 1);
-        const u32 zero_bits = zero_chunk_bits(L.len[K], L.code[K]);
-        auto raise = [&](u32 code) { raise_status(ws, host, epoch, code); };
-        while (c < nchunks) {
-            // the next chunk's place in the offset table is on its way while this one is decoded
-            const u32 cn = c + stride;
-            u32 n0 = 0, n1 = 0;
-            if (cn < nchunks) { n0 = off_tab[cn]; n1 = off_tab[cn + 1]; }
-            const bool full = (u64)(c + 1) * kChunk <= n;
             if (full && aligned) {
-                if (M > kDecLut1Bits) decode_chunk<true, true, DT, DEEP, VERIFY>(blob, w_ref, n, c, o0, o1, L, pay, pay_words, P1, P2, K, area, zero_bits, raise);
-                else decode_chunk<true, false, DT, DEEP, VERIFY>(blob, w_ref, n, c, o0, o1, L, pay, pay_words, P1, P2, K, area, zero_bits, raise);
+                if (M > kMultiBits) decode_chunk<true, true, DT, VERIFY>(blob, w_ref, n, c, o0, o1, L, pay, pay_words, ring, K, area, raise);
+                else decode_chunk<true, false, DT, VERIFY>(blob, w_ref, n, c, o0, o1, L, pay, pay_words, ring, K, area, raise);
             } else {
-                decode_chunk<false, true, DT, false, VERIFY>(blob, w_ref, n, c, o0, o1, L, pay, pay_words, P1, P2, K, area, full ? zero_bits : 0u, raise);
+                decode_chunk<false, true, DT, VERIFY>(blob, w_ref, n, c, o0, o1, L, pay, pay_words, ring, K, area, raise);
             }
-            c = cn; o0 = n0; o1 = n1;
         }
+        if (!more) break;
+        c = (u32)cn; o0 = n0; o1 = n1;
     }
 }
 
@@ -597,13 +674,13 @@ __global__ __launch_bounds__(256) void kb_dec_setup(BatchDecArgs a) {
 __global__ __launch_bounds__(256) void kb_dec_tables(BatchDecArgs a) {
     __shared__ u32 hdr[kHeaderBytes / 4];
     __shared__ u32 s_ok;
-    __shared__ u32 s_len[kMaxSym], s_code[kMaxSym];
+    __shared__ DecBuild B;
     const u32 t = threadIdx.x, sidx = blockIdx.x;
     const SegD& sg = a.segs[sidx];
     DecSet& D = a.sets[sidx];
     if (t < kHeaderBytes / 4) hdr[t] = reinterpret_cast<const u32*>(sg.blob)[t];
     __syncthreads();
-    if (t == 0) {
+    if (t < kW) {
         const u64 hn = hdr[2] | ((u64)hdr[3] << 32), total = hdr[10] | ((u64)hdr[11] << 32);
         const u64 area = chunk_area_of(sg.nchunks);
         // the largest blob lc_encode can produce for this n (nbits 4): header + offsets + 132 bytes per chunk + n/2
@@ -614,14 +691,16 @@ __global__ __launch_bounds__(256) void kb_dec_tables(BatchDecArgs a) {
         bool ok = head_ok;
         u32 status = 0;
         if (!head_ok) status = (sound && (hn != sg.n || hdr[15] != (u32)a.dtype)) ? 1u : 4u;
-        else if (!dec_symbol_table(hdr, sg.n, sg.nchunks, area, (total - area) / 4, D, s_len, s_code)) { ok = false; status = 4u; }
-        if (!ok) { atomicMax(&a.seg_status[sidx], status); D.info.area = 0; D.info.total_words = 0; D.info.max_len = 0; D.info.K = 0; }
-        D.info.pad[0] = ok ? 1u : 0u;                        // the chunk checks and the sweep look here first
-        D.info.pad[1] = 0;
-        s_ok = ok;
+        else if (!dec_symbol_table(hdr, sg.n, sg.nchunks, area, (total - area) / 4, D, B)) { ok = false; status = 4u; }
+        if (t == 0) {
+            if (!ok) { atomicMax(&a.seg_status[sidx], status); D.info.area = 0; D.info.total_words = 0; D.info.max_len = 0; D.info.K = 0; }
+            D.info.pad[0] = ok ? 1u : 0u;                    // the chunk checks and the sweep look here first
+            D.info.pad[1] = 0;
+            s_ok = ok;
+        }
     }
     __syncthreads();
-    if (s_ok) dec_build_luts(D, s_len, s_code, t, 256);
+    if (s_ok) dec_build_luts(D, B, hdr[5], t);
 }
 
 // Also leaves, per chunk, what the sweep needs to find it: {tensor, chunk index there, the chunk's two offset-table
@@ -645,9 +724,11 @@ __global__ __launch_bounds__(256) void kb_dec_chunks(BatchDecArgs a) {
 template <int DT>
 __global__ __launch_bounds__(64) void kb_decode(BatchDecArgs a) {
     __shared__ DecLds L;
+    __shared__ u32 ring[kRingWords * kW];
     __shared__ uint4 pay[kPayWords / 4 + 1];
     const u32 lane = threadIdx.x;
-    u32 active = 0xFFFFFFFFu, M = 0, K = 0, P1 = 0, P2 = 0;
+    u32 active = 0xFFFFFFFFu, M = 0, K = 0, zero_bits = 0;
+    bool have_tables = false;
     u64 area = 0;
     const uint4* chunk_info = reinterpret_cast<const uint4*>(a.chunk_info);
     auto info_of = [&](u32 g) {                      // (the same in every lane: back to scalar registers)
@@ -664,33 +745,37 @@ __global__ __launch_bounds__(64) void kb_decode(BatchDecArgs a) {
         // a tensor whose blob failed a check is not touched
         if (__hip_atomic_load(&a.seg_status[sidx], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) continue;
         const SegD& sg = a.segs[sidx];
+        const DecSet& D = a.sets[sidx];
         if (sidx != active) {
             active = sidx;
-            const DecSet& D = a.sets[sidx];
+            have_tables = false;
             M = D.info.max_len; K = D.info.K; area = D.info.area;
-            P1 = M < kDecLut1Bits ? M : kDecLut1Bits; P2 = M < kDecLut2Bits ? M : kDecLut2Bits;
-            __syncthreads();
-            for (u32 i = lane; i < (1u << P1); i += kW) L.lut1[i] = D.lut1[i];
-            if (M > kDecLut1Bits) {
-                const u32* src = reinterpret_cast<const u32*>(D.lut2);
-                u32* dst = reinterpret_cast<u32*>(L.lut2);
-                for (u32 i = lane; i < ((1u << P2) + 3) / 4; i += kW) dst[i] = src[i];
-            }
-            if (lane < kMaxSym) {
-                L.rep[lane] = __uint_as_float(lane < K ? D.info.rep_bits[lane] : 0x80000000u);
-                L.len[lane] = D.info.len[lane]; L.code[lane] = D.info.code[lane];
-            }
-            __syncthreads();
+            zero_bits = zero_chunk_bits(D.info.len[K], D.info.code[K]);
         }
         auto raise = [&](u32 code) { atomicMax(&a.seg_status[sidx], code); };
         const u32 c = info.y, o0 = info.z, o1 = info.w;
         const bool full = (u64)(c + 1) * kChunk <= sg.n;
-        const u32 zero_bits = full ? zero_chunk_bits(L.len[K], L.code[K]) : 0u;
+        QuietChunk q;
+        q.start(sg.blob, area, o0, o1, zero_bits, full);
+        if (q.holds(zero_bits)) continue;
+        if (!have_tables) {
+            // (brought to LDS for the first chunk of the tensor that has to be decoded)
+            have_tables = true;
+            u32x4 e[(1u << kMultiBits) / 4 / kW];
+            u32 rep = 0, len = 0, code = 0;
+#pragma unroll
+            for (u32 k = 0; k < (1u << kMultiBits) / 4 / kW; ++k) e[k] = reinterpret_cast<const u32x4*>(D.multi)[lane + k * kW];
+            if (lane < kMaxSym) { rep = D.info.rep_bits[lane]; len = D.info.len[lane]; code = D.info.code[lane]; }
+#pragma unroll
+            for (u32 k = 0; k < (1u << kMultiBits) / 4 / kW; ++k) reinterpret_cast<u32x4*>(L.multi)[lane + k * kW] = e[k];
+            if (lane < kMaxSym) { L.rep[lane] = __uint_as_float(lane < K ? rep : 0x80000000u); L.len[lane] = len; L.code[lane] = code; }
+            __builtin_amdgcn_wave_barrier();
+        }
         if (full && sg.aligned) {
-            if (M > kDecLut1Bits) decode_chunk<true, true, DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, L, pay, kPayWords, P1, P2, K, area, zero_bits, raise);
-            else decode_chunk<true, false, DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, L, pay, kPayWords, P1, P2, K, area, zero_bits, raise);
+            if (M > kMultiBits) decode_chunk<true, true, DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, L, pay, kPayWords, ring, K, area, raise);
+            else decode_chunk<true, false, DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, L, pay, kPayWords, ring, K, area, raise);
         } else {
-            decode_chunk<false, true, DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, L, pay, kPayWords, P1, P2, K, area, zero_bits, raise);
+            decode_chunk<false, true, DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, L, pay, kPayWords, ring, K, area, raise);
         }
     }
 }
@@ -1117,37 +1202,29 @@ void launch_decode(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, Work
     const u64 nchunks = num_chunks_of(n);
     if (nchunks == 0) return;
     const bool verify = w_ref == nullptr;
-    const u64 blocks = balanced_workers((nchunks + 3) / 4, (u64)tune.num_cu * tune.decode_blocks_per_cu);
+    // A blob of at most 4 chunks per wavefront that 3 workgroups per compute unit hold (what their LDS allows): the grid is
+    // just those.  A wavefront then looks ahead to its next chunk, and no second round of workgroups pays its start (8,445
+    // sparse chunks: 38 us for the call, 42 with 8 workgroups per unit; 8,192 dense ones of bf16: 139 either way).
+    // Above, smaller shares even out chunks of unlike cost, and only 2 workgroups share a unit, by the size of their
+    // payload areas: a sweep that reads and writes runs better on fewer streams (16,384 dense chunks: 421 us against 438
+    // with 3; 428 with 2 and a grid of just those).
+    const bool few = nchunks <= (u64)tune.num_cu * 3 * 4 * 4;
+    const u64 blocks = balanced_workers((nchunks + 3) / 4, (u64)tune.num_cu * (few ? 3 : tune.decode_blocks_per_cu));
     const dim3 grid((u32)blocks), wg(256);
     const int al = verify ? 1 : aligned_rows(w_ref, dtype);
-    // LDS payload areas: the usual size when every compute unit gets as many workgroups as fit beside each other
-    // (4); with fewer workgroups than that, what the unit's LDS leaves each, so that chunks with long payloads
-    // (codes of 5 and more bits on average) need not read their lane strings from memory
-    const u64 per_cu = (blocks + tune.num_cu - 1) / tune.num_cu;
-    u32 pay_words = kPayWords;
-    if (per_cu < 4) {
-        static_assert(sizeof(DecLds) + 4 * (kPayWordsMax / 4 + 1) * sizeof(uint4) <= 64 * 1024, "one workgroup's LDS");
-        const size_t room = kLdsPerCu / (size_t)per_cu - sizeof(DecLds) - 1024;
-        const u64 fit = room / 16 / 4 * 4 - 4;                      // words per wavefront, a multiple of 4
-        pay_words = (u32)(fit > kPayWordsMax ? kPayWordsMax : fit);
-        if (pay_words < kPayWords) pay_words = kPayWords;
-    }
+    // (a payload longer than its area is read from memory, lane by lane: rare below 4, or with the larger areas 6 bits per element)
+    const u32 pay_words = few && blocks > 2 * (u64)tune.num_cu ? kPayWords : kPayWordsMax;
+    static_assert(sizeof(DecLds) + 4 * kRingWords * kW * 4 + 4 * (kPayWordsMax / 4 + 1) * sizeof(uint4) <= 64 * 1024, "one workgroup's LDS");
     const size_t lds = 4 * (size_t)(pay_words / 4 + 1) * sizeof(uint4);
-    // At most two workgroups per compute unit: a wavefront has its SIMD almost to itself and nothing hides its waits
-    // on memory, so the kernel's form with rows fetched far ahead runs (it needs more registers than would let more
-    // workgroups share a unit).
-    const bool deep = per_cu <= 2;
     if (verify) {
-        hipLaunchKernelGGL((k_decode<kF32, false, true>), grid, wg, lds, s, blob, (void*)nullptr, (u64)n, ws, (u32)nchunks, al, (u64)epoch, host, pay_words, (u32)set);
+        hipLaunchKernelGGL((k_decode<kF32, true>), grid, wg, lds, s, blob, (void*)nullptr, (u64)n, ws, (u32)nchunks, al, (u64)epoch, host, pay_words, (u32)set);
         return;
     }
-#define LC_DECODE(DT) \
-    if (deep) hipLaunchKernelGGL((k_decode<DT, true>), grid, wg, lds, s, blob, w_ref, (u64)n, ws, (u32)nchunks, al, (u64)epoch, host, pay_words, (u32)set); \
-    else hipLaunchKernelGGL((k_decode<DT, false>), grid, wg, lds, s, blob, w_ref, (u64)n, ws, (u32)nchunks, al, (u64)epoch, host, pay_words, (u32)set)
-    if (dtype == kF64) { LC_DECODE(kF64); }
-    else if (dtype == kBF16) { LC_DECODE(kBF16); }
-    else if (dtype == kF16) { LC_DECODE(kF16); }
-    else { LC_DECODE(kF32); }
+#define LC_DECODE(DT) hipLaunchKernelGGL((k_decode<DT>), grid, wg, lds, s, blob, w_ref, (u64)n, ws, (u32)nchunks, al, (u64)epoch, host, pay_words, (u32)set)
+    if (dtype == kF64) LC_DECODE(kF64);
+    else if (dtype == kBF16) LC_DECODE(kBF16);
+    else if (dtype == kF16) LC_DECODE(kF16);
+    else LC_DECODE(kF32);
 #undef LC_DECODE
 }
 

@@ -11,13 +11,15 @@ typedef uint32_t u32;
 // ----------------------------------------------------------------------------- small helpers
 __device__ __forceinline__ u32 lane_id() { return __lane_id(); }
 
+// Running sums over the wavefront (all 64 lanes active): DPP shifts within rows of 16 lanes, then the row totals carried
+// across (row_bcast), no LDS traffic; a restore's chunk starts with one, and six LDS round trips were 0.25 us of it.
 __device__ __forceinline__ u32 wave_incl_scan(u32 v) {
-    const u32 lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        u32 t = __shfl_up(v, d, 64);
-        if (lane >= (u32)d) v += t;
-    }
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);     // row_shr:1
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);     // row_shr:2
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);     // row_shr:4
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);     // row_shr:8
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);     // row_bcast:15 into rows 1, 3
+    v += (u32)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);     // row_bcast:31 into rows 2, 3
     return v;
 }
 
@@ -59,11 +61,7 @@ __device__ __forceinline__ u32 wave_max_u32(u32 v) {
 __device__ __forceinline__ u32 read_lane(u32 v, u32 l) { return (u32)__builtin_amdgcn_readlane((int)v, (int)l); }
 __device__ __forceinline__ u64 read_lane64(u64 v, u32 l) { return ((u64)read_lane((u32)(v >> 32), l) << 32) | read_lane((u32)v, l); }
 
-__device__ __forceinline__ u32 wave_sum32(u32 v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-    return v;
-}
+__device__ __forceinline__ u32 wave_sum32(u32 v) { return read_lane(wave_incl_scan(v), kW - 1); }
 
 // delta of Algorithm 1 line 4: one IEEE binary32 subtraction (never fused or reassociated).
 __device__ __forceinline__ u32 delta_bits(float w, float w_ref) { return __float_as_uint(__fsub_rn(w, w_ref)); }
@@ -88,6 +86,7 @@ template <int DT> struct Raw { typedef uint2 type; };
 template <> struct Raw<kF32> { typedef float4 type; };
 template <> struct Raw<kF64> { typedef Row64 type; };
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 template <int DT> struct Val { typedef float type; typedef u32 bits; };
 template <> struct Val<kF64> { typedef double type; typedef u64 bits; };
 

@@ -108,7 +108,6 @@ __device__ __forceinline__ float max_magnitude(const u32 (&u)[EPU], float m) {
 // exponent bytes and the 16 sign bits of the 16 elements a lane holds of a batch, which are the lane's own elements of
 // 4 rows of the coding sweep's chunk -- and, being then the only sweep that sees the mantissas, tracks the smallest and
 // largest delta bit pattern of every bucket (Section 3.1.1: the representative is the mean of these two).
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 template <bool ALIGNED, int DT, bool KEYS = false>
 __global__ __launch_bounds__(1024) void k_hist(const void* __restrict__ w, const void* __restrict__ w_ref,
                                                u64 n, Workspace* ws, u32* chunk_maxexp, uint8_t* batch_max, KeyPlanes keys) {

@@ -16,8 +16,9 @@ constexpr uint32_t kLaneBitsWords = (2 * kW) / 4;   // 32 words of u16 lane leng
 constexpr uint32_t kMaxSym = 16;
 constexpr uint32_t kExtCopies = 16;
 enum ElemType { kF32 = 0, kBF16 = 1, kF16 = 2, kF64 = 3 };   // element type of the parameter arrays (= LC_F32 ...)
-constexpr uint32_t kDecLut1Bits = 7;        // first decode table: conflict-free in LDS
-constexpr uint32_t kDecLut2Bits = 12;       // second decode table, for codes of 8..12 bits
+constexpr uint32_t kDecLut1Bits = 7;        // the fused restore's decode table: conflict-free in LDS
+constexpr uint32_t kMultiBits = 10;         // the restore's decode table: up to kMultiSyms symbols per look-up
+constexpr uint32_t kMultiSyms = 6;
 
 // Written by the table kernel, read by pack / finalize.
 struct Table {
@@ -50,7 +51,9 @@ constexpr int kMaxSets = 64; // blobs one lc_decode_many call accepts (= LC_MAX_
 struct DecSet {
     DecInfo info;
     alignas(16) uint8_t lut1[1u << kDecLut1Bits];   // symbol | len << 4 over the next 7 bits
-    alignas(16) uint8_t lut2[1u << kDecLut2Bits];   // ... over the next 12 bits
+    // over the next 10 bits: as many whole codes as they hold, at most 6: their symbols (4 bits each, the first in the low
+    // bits), their total length in bits 24 .. 27, their number in bits 28 .. 30; 0: the first code is longer than 10 bits
+    alignas(16) uint32_t multi[1u << kMultiBits];
 };
 
 struct Result {
@@ -142,7 +145,7 @@ struct Tuning {
     int key_staging = 0;               // 0: by the vector's last call, 1: whenever it applies, 2: never
     int spec_waves_per_cu = 8;         // of the single sweep of the cached encode (what its LDS and registers allow)
     int batch_waves_per_cu = 8;        // of the batch kernels
-    int decode_blocks_per_cu = 9;     // (LDS lets 4 run at once; more, smaller shares even out chunks that decode to nothing)
+    int decode_blocks_per_cu = 9;     // ... of a long restore (LDS lets 3 run at once; more, smaller shares even out unlike chunks)
     int fused_waves_per_cu = 16;       // most wavefronts per compute unit
     int fused_min_waves_per_cu = 8;    // a sweep takes as many blobs as still leave LDS for this many
 };
