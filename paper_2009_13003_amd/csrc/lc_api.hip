@@ -120,8 +120,8 @@ void read_tuning(DeviceState& ds, int dev) {
     ds.tune.hist_blocks_per_cu = env_int("LC_TUNE_HIST_BLOCKS_PER_CU", ds.tune.hist_blocks_per_cu, 1, 64);
     ds.tune.hist_threads = env_int("LC_TUNE_HIST_THREADS", ds.tune.hist_threads, 64, 1024) / 64 * 64;
     ds.tune.pack_waves_per_cu = env_int("LC_TUNE_PACK_WAVES_PER_CU", ds.tune.pack_waves_per_cu, 1, 64);
+    ds.tune.unlisted_per_cu = env_int("LC_TUNE_UNLISTED_PER_CU", ds.tune.unlisted_per_cu, 0, 1024);
     ds.tune.spec_waves_per_cu = env_int("LC_TUNE_SPEC_WAVES_PER_CU", ds.tune.spec_waves_per_cu, 1, 64);
-    ds.tune.keys_waves_per_cu = env_int("LC_TUNE_KEYS_WAVES_PER_CU", ds.tune.keys_waves_per_cu, 1, 64);
     if (g_key_staging < 0) g_key_staging = env_int("LC_TUNE_KEY_STAGING", 0, 0, 2);
     ds.tune.batch_waves_per_cu = env_int("LC_TUNE_BATCH_WAVES_PER_CU", ds.tune.batch_waves_per_cu, 1, 64);
     ds.tune.decode_blocks_per_cu = env_int("LC_TUNE_DECODE_BLOCKS_PER_CU", ds.tune.decode_blocks_per_cu, 1, 64);
@@ -374,7 +374,7 @@ lc_ssize encode_impl(const void* w, const void* w_ref, uint64_t n, int nbits, vo
         Timed t(staged ? kSlotHistKeys : kSlotHist, s); launch_hist(w, w_ref, n, dtype, ws, chunk_maxexp, batch_max, keys, ds->tune, s);
     }
     const bool listed = !spec_sweep;            // sweep 1 recorded the chunk maxima, so k_table can list the chunks to read
-    { Timed t(kSlotTable, s);    launch_table(ws, n, nbits, dtype, group_words, chunk_maxexp, listed ? chunk_list : nullptr, s); }
+    { Timed t(kSlotTable, s);    launch_table(ws, n, nbits, dtype, group_words, chunk_maxexp, listed && (staged || pack_needs_list(n, dtype, ds->tune)) ? chunk_list : nullptr, s); }
     if (staged) { Timed t(kSlotPackKeys, s); launch_pack_keys(w, w_ref, n, ws, chunk_bits, group_words, chunk_maxexp, chunk_list, keys, prov, slot_words, ds->tune, s); }
     else { Timed t(kSlotPack, s); launch_pack(w, w_ref, n, dtype, ws, chunk_bits, group_words, chunk_maxexp, listed ? chunk_list : nullptr, batch_max, prov, slot_words, ds->tune, s); }
     if (async) LC_HIP(hipEventRecord(call.inputs, s));   // w and w_ref are not read past this point
@@ -453,7 +453,7 @@ int lc_encode_static(const float* w, const float* w_ref, uint64_t n, int nbits, 
     // one that was captured and never replayed to its end does not): cleared by a kernel before every call.
     launch_reset_chunks(sc.ws, sc.group_words, sc.chunk_maxexp, (uint32_t)kStaticChunks, s);
     launch_hist(w, w_ref, n, LC_F32, sc.ws, sc.chunk_maxexp, sc.batch_max, KeyPlanes{nullptr, nullptr}, ds.tune, s);
-    launch_table(sc.ws, n, nbits, LC_F32, sc.group_words, sc.chunk_maxexp, sc.chunk_list, s);
+    launch_table(sc.ws, n, nbits, LC_F32, sc.group_words, sc.chunk_maxexp, pack_needs_list(n, LC_F32, ds.tune) ? sc.chunk_list : nullptr, s);
     launch_pack(w, w_ref, n, LC_F32, sc.ws, sc.chunk_bits, sc.group_words, sc.chunk_maxexp, sc.chunk_list, sc.batch_max, sc.prov,
                 sc.slot_words, ds.tune, s);
     launch_place(o, sc.ws, sc.chunk_bits, sc.group_words, sc.prov, sc.slot_words, n, sc.chunk_maxexp, result, nullptr, nbits, LC_F32, false, s);

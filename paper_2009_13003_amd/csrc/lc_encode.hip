@@ -4,7 +4,7 @@
 //                    state for the next call, k_place the per-chunk maxima); k_reset only for a fresh scratch area
 //                    (fp64 parameters: k_hist64 -> k_table<11> -> k_pack64 -> k_place)
 // lc_encode_cached:  k_spec_table -> k_spec_sweep -> k_table -> k_pack (nothing to do on a hit) -> k_place
-// lc_encode_batch:   kb_setup -> kb_hist -> kb_table -> kb_list -> kb_pack -> kb_place (whose first workgroups write the headers)
+// lc_encode_batch:   kb_setup -> kb_hist -> kb_table -> kb_list (long lists) -> kb_pack -> kb_place (whose first workgroups write the headers)
 //
 // The paper (arXiv 2009.13003) defines what is computed: delta against the last
 // recovered state (Algorithm 1 line 4), (sign, exponent) buckets represented by the
@@ -613,17 +613,16 @@ __global__ __launch_bounds__(64) void k_spec_table(EncState* ws, Ext64* ext, con
     }
 }
 
-// ----------------------------------------------------------------------------- k_pack
-// Sweep 2: one wavefront per chunk, no communication between wavefronts.  Each lane codes its
-// 256 elements into a bit string of its own, written word by word to the chunk's slot in the
-// scratch area (lane-private, word k of lane l at slot[32 + 64 k + l]); the 64 bit lengths go
-// to the head of the slot, their sum to chunk_bits[c].  Where the strings end up in the blob is
-// decided afterwards by k_place, which knows all sizes.  A full, 16-byte aligned chunk takes
-// the fast path: rows are fetched eight at a time, one batch ahead (and the next chunk's first
-// batch before the current one ends), the table look-ups of 16 elements are issued together and
-// two symbols are coded per look-up.  Ragged or unaligned chunks take a plain path.  The
-// mantissa extremes of the kept buckets (Section 3.1.1: the representative is the mean of the
-// bucket's largest and smallest member) are tracked on the way.
+// ----------------------------------------------------------------------------- sweeps by wavefronts
+// The single sweep of lc_encode_cached, which counts and codes, and the counting sweep of a batched call: one wavefront per
+// chunk, no communication between wavefronts.  Coding, each lane codes its 256 elements into a bit string of its own,
+// written word by word to the chunk's slot in the scratch area (lane-private, word k of lane l at slot[32 + 64 k + l]); the
+// 64 bit lengths go to the head of the slot, their sum to chunk_bits[c].  Where the strings end up in the blob is decided
+// afterwards by k_place, which knows all sizes.  A full, 16-byte aligned chunk takes the fast path: rows are fetched eight
+// at a time, one batch ahead (and the next chunk's first batch before the current one ends), the table look-ups of 16
+// elements are issued together and two symbols are coded per look-up.  Ragged or unaligned chunks take a plain path.  The
+// mantissa extremes of the kept buckets (Section 3.1.1: the representative is the mean of the bucket's largest and smallest
+// member) are tracked on the way.
 constexpr int kMmCopies = 32;       // LDS copies of the per-symbol extremes, one per lane of a half wave
 
 constexpr u32 kStageRows = 32;      // code words per lane that a chunk gathers in LDS before they go to its slot
@@ -635,14 +634,13 @@ constexpr int kSpecCopies = 2;      // LDS copies of the bucket histogram in the
 // bank (512 words apart), and a delta's sign is a coin toss: bit 4 of the index is flipped for the negative half.
 __device__ __forceinline__ u32 hist_slot(u32 b, u32 copy) { return (b * kSpecCopies + copy) ^ ((b >> 8) << 4); }
 
-template <bool HIST>
 struct PackLds {
     uint8_t sym8[512];               // bucket -> symbol << 3
     u32 codelen[kMaxSym];            // (code << 5) | len
     uint2 pair[256];                 // (symbol a, symbol b) -> {code of a followed by b, its length}
     u32 mn[kMaxSym * kMmCopies], mx[kMaxSym * kMmCopies];   // extremes of the delta bit patterns per symbol
     alignas(16) u32 stage[kStageRows * kW];                 // word k of lane l at [64 k + l], as in the slot
-    u32 hist[HIST ? 512 * kSpecCopies : 1];                 // bucket populations (speculative sweep only)
+    u32 hist[512 * kSpecCopies];                            // bucket populations
 };
 
 // chunk_bits[c] = payload bits of chunk c; group_words[g] = record words of chunks 64g .. 64g+63
@@ -689,13 +687,21 @@ struct ChunkMaxima {
     }
 };
 
+// In chunk_bits beside a chunk's payload bits (at most 16384 * 15).  kMergedChunk: a full chunk whose largest exponent (sweep
+// 1 recorded it) lies below every kept bucket: all 16384 symbols are the merged one (Section 3.1.1, priority promotion) and
+// each lane's string is 256 copies of its code.  Such a chunk gets no slot: sweep 2 only notes its size, and k_place writes
+// the repeated code straight into the blob.  kRawChunk: the slot holds lane strings that k_place has to join; without it
+// the record as it goes into the blob.
+constexpr u32 kMergedChunk = 0x80000000u, kRawChunk = 0x40000000u, kChunkBits = 0x3FFFFFFFu;
+
+// Lane strings in the slot: their lengths.
 __device__ __forceinline__ void finish_lane_sizes(const ChunkRef& ch, u32 nb, u32 nw) {
     const u32 lane = lane_id();
     const u32 bits = 32 * nw + nb;
     reinterpret_cast<uint16_t*>(ch.slot)[lane] = (uint16_t)bits;
     const u32 total = wave_sum32(bits);
     if (lane == 0) {
-        *ch.bits_at = total;
+        *ch.bits_at = total | kRawChunk;
         atomicAdd(ch.group_at, kLaneBitsWords + ((total + 31) >> 5));
     }
 }
@@ -705,8 +711,8 @@ __device__ __forceinline__ void finish_lane_sizes(const ChunkRef& ch, u32 nb, u3
 // in a full chunk, four at a time and one batch ahead; what is left takes guarded element loads.
 constexpr int kPlainRows = 4;
 
-template <bool HIST, bool PACK, int DT>
-__device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds<HIST>& L, const MaximaAt at = MaximaAt{nullptr, nullptr}) {
+template <bool PACK, int DT>
+__device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds& L, const MaximaAt at = MaximaAt{nullptr, nullptr}) {
     const u32 lane = lane_id();
     const void* __restrict__ w = ch.w; const void* __restrict__ w_ref = ch.w_ref;
     const u64 n = ch.n, base = (u64)ch.c * kChunk;
@@ -722,8 +728,8 @@ __device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds<HIST>& 
         for (int v = 0; v < 4; ++v) {
             if (WHOLE || idx + v < n) {
                 const u32 u = delta_bits(xa[v], xb[v]);
-                if (HIST) atomicAdd(&L.hist[hist_slot(u >> 23, lane & (kSpecCopies - 1))], 1u);
-                if (HIST && !PACK) gmax = max(gmax, u & 0x7FFFFFFFu);
+                atomicAdd(&L.hist[hist_slot(u >> 23, lane & (kSpecCopies - 1))], 1u);
+                if (!PACK) gmax = max(gmax, u & 0x7FFFFFFFu);
                 if (!PACK) continue;
                 const u32 sy = L.sym8[u >> 23] >> 3;
                 const u32 cl = L.codelen[sy];
@@ -754,7 +760,7 @@ __device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds<HIST>& 
         auto code = [&](const float (&a)[kPlainRows][4], const float (&b)[kPlainRows][4], u32 r0) {
 #pragma unroll
             for (int k = 0; k < kPlainRows; ++k) code_row(yes(), row_at_(r0 + k), a[k], b[k]);
-            if (HIST && !PACK && at.chunk) { cm.group(gmax, r0); gmax = 0; }
+            if (!PACK && at.chunk) { cm.group(gmax, r0); gmax = 0; }
         };
         fetch(xa, xb, 0);
         for (; r < whole_rows; r += 2 * kPlainRows) {
@@ -773,7 +779,7 @@ __device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds<HIST>& 
 #pragma unroll
         for (int k = 0; k < kPlainRows; ++k) code_row(no(), row_at_(r + k), xa[k], xb[k]);
     }
-    if (HIST && !PACK && at.chunk) { cm.umax = max(cm.umax, gmax); cm.note(at); }     // (rows behind the last whole part: the chunk's maximum only)
+    if (!PACK && at.chunk) { cm.umax = max(cm.umax, gmax); cm.note(at); }     // (rows behind the last whole part: the chunk's maximum only)
     if (!PACK) return;
     if (nb > 0) slot[kLaneBitsWords + nw * kW + lane] = (u32)(acc << (32 - nb));
     finish_lane_sizes(ch, nb, nw);
@@ -781,94 +787,6 @@ __device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds<HIST>& 
 
 // element index of this lane's 4 elements in row r of chunk c
 __device__ __forceinline__ u64 row_at(u32 c, u32 r) { return (u64)c * kChunk + (u64)(r * kW + lane_id()) * kV; }
-
-// A chunk of aligned arrays of which sweep 1 has seen that only a few parts hold anything but merged elements
-// (a part = one batch of that sweep: 4 KiB of each array; bit p of `parts` set = part p has to be read).  The lone
-// wavefront that codes such a chunk would otherwise wait for all 64 rows of both arrays; here it fetches the
-// marked parts only and writes the merged code for every element of the others; the rows of a ragged chunk
-// behind its last whole part are read as they are.  Same lane strings as any path.
-template <int DT>
-__device__ __noinline__ void pack_chunk_parts(const ChunkRef ch, u32 cl_merged, PackLds<false>& L) {
-    constexpr u32 kRowsPerPart = 4096 / (kRowElems * elem_bytes<DT>());      // 4 (4-byte elements) or 8 (2-byte)
-    constexpr u32 kParts = kR / kRowsPerPart;
-    const u32 lane = lane_id();
-    u32* slot = ch.slot;
-    const u32 mm = lane & (kMmCopies - 1);
-    u64 acc = 0;
-    u32 nb = 0, nw = 0;
-    auto flush = [&]() {
-        if (nb >= 32) { slot[kLaneBitsWords + nw * kW + lane] = (u32)(acc >> (nb - 32)); ++nw; nb -= 32; }
-    };
-    // (a chunk with an unmarked part holds merged elements, so their symbol has a code; without one nothing is skipped)
-    const u32 len_merged = cl_merged & 31, per_step = len_merged ? 32 / len_merged : 1;
-    u32 run = 0;                                                             // per_step copies of the merged code
-    for (u32 i = 0; i < per_step; ++i) run = (run << len_merged) | (cl_merged >> 5);
-    auto code_element = [&](float a, float b) {
-        const u32 u = delta_bits(a, b);
-        const u32 sy = L.sym8[u >> 23] >> 3;
-        const u32 cl = L.codelen[sy];
-        atomicMin(&L.mn[sy * kMmCopies + mm], u);
-        atomicMax(&L.mx[sy * kMmCopies + mm], u);
-        acc = (acc << (cl & 31)) | (cl >> 5);
-        nb += cl & 31;
-    };
-    const u64 n = ch.n, inside = n - (u64)ch.c * kChunk;
-    const u32 whole = inside >= kChunk ? kParts : (u32)(inside / (kRowsPerPart * kRowElems));
-    for (u32 p = 0; p < whole; ++p) {
-        if ((ch.parts >> p) & 1u) {
-            float xa[kRowsPerPart][4], xb[kRowsPerPart][4];
-#pragma unroll
-            for (u32 k = 0; k < kRowsPerPart; ++k) {
-                load_row<true, DT>(ch.w, row_at(ch.c, p * kRowsPerPart + k), ch.n, xa[k]);
-                load_row<true, DT>(ch.w_ref, row_at(ch.c, p * kRowsPerPart + k), ch.n, xb[k]);
-            }
-#pragma unroll
-            for (u32 k = 0; k < kRowsPerPart; ++k) {
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    code_element(xa[k][v], xb[k][v]);
-                    if (v & 1) flush();
-                }
-            }
-        } else {
-            // the merged code kRowsPerPart * 4 times, as many copies per step as fit 32 bits
-            for (u32 left = kRowsPerPart * kV; left != 0;) {
-                const u32 k = left < per_step ? left : per_step;
-                acc = (acc << (k * len_merged)) | (u64)(run >> ((per_step - k) * len_merged));
-                nb += k * len_merged;
-                flush();
-                left -= k;
-            }
-        }
-    }
-    if (whole < kParts) {
-        // a ragged chunk's last rows (fewer than one part), fetched together, elements past the end left out
-        float xa[kRowsPerPart][4], xb[kRowsPerPart][4];
-#pragma unroll
-        for (u32 k = 0; k < kRowsPerPart; ++k) {
-            const u64 idx = row_at(ch.c, whole * kRowsPerPart + k);
-            load_row<false, DT>(ch.w, idx, n, xa[k]);
-            load_row<false, DT>(ch.w_ref, idx, n, xb[k]);
-        }
-#pragma unroll
-        for (u32 k = 0; k < kRowsPerPart; ++k) {
-            const u64 idx = row_at(ch.c, whole * kRowsPerPart + k);
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                if (idx + v < n) code_element(xa[k][v], xb[k][v]);
-                if (v & 1) flush();
-            }
-        }
-    }
-    if (nb > 0) slot[kLaneBitsWords + nw * kW + lane] = (u32)(acc << (32 - nb));
-    finish_lane_sizes(ch, nb, nw);
-}
-
-// A full chunk whose largest exponent (sweep 1 recorded it) lies below every kept bucket: all 16384 symbols
-// are the merged one (Section 3.1.1, priority promotion) and each lane's string is 256 copies of its code.
-// Such a chunk gets no slot: sweep 2 only notes its size, with kMergedChunk set in chunk_bits, and k_place
-// writes the repeated code straight into the blob.
-constexpr u32 kMergedChunk = 0x80000000u;
 
 constexpr int kPackPF = 8;          // rows per prefetch batch of the coding loop
 
@@ -886,10 +804,10 @@ __device__ __forceinline__ void fetch_first_batch(const ChunkRef& ch, typename R
 
 // A full, aligned chunk whose first batch of rows is already in A0/B0; leaves the first batch of `next`
 // there if that chunk takes this path too.
-template <bool ROWCHK, bool HIST, bool PACK, int DT>
+template <bool ROWCHK, bool PACK, int DT>
 __device__ __forceinline__ void pack_chunk_fast(const ChunkRef& cur, const ChunkRef& next,
                                                 typename Raw<DT>::type (&A0)[kPackPF], typename Raw<DT>::type (&B0)[kPackPF],
-                                                u32 K8, PackLds<HIST>& L, const MaximaAt at = MaximaAt{nullptr, nullptr},
+                                                u32 K8, PackLds& L, const MaximaAt at = MaximaAt{nullptr, nullptr},
                                                 u32 rot = 0) {
     constexpr int PF = kPackPF;
     static_assert((kR & (kR - 1)) == 0 && kR % (2 * kPackPF) == 0, "rows wrap with a mask");
@@ -926,11 +844,9 @@ __device__ __forceinline__ void pack_chunk_fast(const ChunkRef& cur, const Chunk
 #pragma unroll
             for (int v = 0; v < 4; ++v) u[4 * k + v] = delta_bits(xa[v], xb[v]);
         }
-        if (HIST) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) atomicAdd(&L.hist[hist_slot(u[i] >> 23, lane & (kSpecCopies - 1))], 1u);
-        }
-        if (HIST && !PACK && at.chunk) {
+        for (int i = 0; i < 16; ++i) atomicAdd(&L.hist[hist_slot(u[i] >> 23, lane & (kSpecCopies - 1))], 1u);
+        if (!PACK && at.chunk) {
             u32 gm = 0;
 #pragma unroll
             for (int i = 0; i < 16; ++i) gm = max(gm, u[i] & 0x7FFFFFFFu);
@@ -962,7 +878,7 @@ __device__ __forceinline__ void pack_chunk_fast(const ChunkRef& cur, const Chunk
         }
     };
     // (row: the chunk's row that step r0 starts with; rot is 0 unless this is the counting sweep)
-    auto row = [&](u32 r) { return (HIST && !PACK) ? ((r + rot) & (kR - 1)) : r; };
+    auto row = [&](u32 r) { return !PACK ? ((r + rot) & (kR - 1)) : r; };
     for (u32 r0 = 0; r0 < kR; r0 += 2 * PF) {
 #pragma unroll
         for (int k = 0; k < PF; ++k) { A1[k] = load_raw<DT>(w, row_at(c, row(r0 + PF) + k)); B1[k] = load_raw<DT>(w_ref, row_at(c, row(r0 + PF) + k)); }
@@ -971,11 +887,11 @@ __device__ __forceinline__ void pack_chunk_fast(const ChunkRef& cur, const Chunk
 #pragma unroll
             for (int k = 0; k < PF; ++k) { A0[k] = load_raw<DT>(w, row_at(c, row(r0 + 2 * PF) + k)); B0[k] = load_raw<DT>(w_ref, row_at(c, row(r0 + 2 * PF) + k)); }
         } else if (next_fast) {
-            fetch_first_batch<DT>(next, A0, B0, (HIST && !PACK) ? rot : 0u);
+            fetch_first_batch<DT>(next, A0, B0, !PACK ? rot : 0u);
         }
         group(A1, B1, row(r0 + PF)); group(A1 + 4, B1 + 4, row(r0 + PF) + 4);
     }
-    if (HIST && !PACK && at.chunk) cm.note(at);
+    if (!PACK && at.chunk) cm.note(at);
     if (!PACK) return;
     // the last, partly filled word, then rows 0 .. (most words of any lane) - 1, four rows per store
     if (nb > 0) {
@@ -994,67 +910,52 @@ __device__ __forceinline__ void pack_chunk_fast(const ChunkRef& cur, const Chunk
     finish_lane_sizes(cur, nb, nw);
 }
 
-// The coding loop of one wavefront over the chunks its source hands out.  Src::get(k) is the wavefront's
-// k-th chunk, Src::enter(chunk, L) runs before each (a batched call switches tables there), Src::K8() and
-// Src::rowchk() describe the table in force: symbol K << 3, and whether a lane's 64-bit accumulator can
-// take a whole row (31 waiting bits + 4 codes of <= 8 bits) between flushes.
-// ROWSEL: 1 / 0 = rowchk() is known to be true / false for every chunk (one vector, one table);
-// -1 = ask per chunk (a batched call, where tables change).
-// Src::take() is the wavefront's next chunk.
-template <bool HIST, bool PACK, int DT, int ROWSEL, typename Src>
-__device__ __forceinline__ void pack_loop(Src& src, PackLds<HIST>& L) {
+// The loop of one wavefront over the chunks its source hands out.  Src::take() is the wavefront's next chunk,
+// Src::enter(chunk, L) runs before each (a batched call switches tensors there), Src::K8() is symbol K << 3 of the table.
+// ROWSEL: 1 = a lane's 64-bit accumulator can take a whole row (31 waiting bits + 4 codes of <= 8 bits) between flushes.
+template <bool PACK, int DT, int ROWSEL, typename Src>
+__device__ __forceinline__ void pack_loop(Src& src, PackLds& L) {
     typedef typename Raw<DT>::type raw_t;
     raw_t A0[kPackPF], B0[kPackPF];
     // the counting sweep: every wavefront starts its chunks one batch of rows after its neighbour (see fetch_first_batch)
-    const u32 rot = (HIST && !PACK) ? (blockIdx.x % (kR / kPackPF)) * kPackPF : 0u;
+    const u32 rot = !PACK ? (blockIdx.x % (kR / kPackPF)) * kPackPF : 0u;
+    // (behind a chunk that was not coded from these arrays nothing in them lives on: without a word about that the compiler
+    // kept their registers through the calls to the other paths, 256 in all for kb_pack, one wavefront per SIMD)
+    auto forget = [&]() {
+#pragma unroll
+        for (int k = 0; k < kPackPF; ++k) { A0[k] = raw_t{}; B0[k] = raw_t{}; }
+    };
     ChunkRef cur = src.take();
     if (cur.valid && cur.fast) fetch_first_batch<DT>(cur, A0, B0, rot);
     while (cur.valid) {
         const ChunkRef next = src.take();
         src.enter(cur, L);
-        if constexpr (HIST && !PACK) {
+        if constexpr (!PACK) {
             // counting only
             const MaximaAt at = src.maxima_at(cur);
             if (!cur.fast) {
-                pack_chunk_plain<HIST, PACK, DT>(cur, L, at);
+                pack_chunk_plain<PACK, DT>(cur, L, at);
+                forget();
                 if (next.valid && next.fast) fetch_first_batch<DT>(next, A0, B0, rot);
             } else {
-                pack_chunk_fast<true, HIST, PACK, DT>(cur, next, A0, B0, src.K8(), L, at, rot);
+                pack_chunk_fast<true, PACK, DT>(cur, next, A0, B0, src.K8(), L, at, rot);
             }
         } else if (!cur.fast) {
-            if constexpr (!HIST && PACK) {
-                if (cur.by_parts) pack_chunk_parts<DT>(cur, src.merged_codelen(), L);
-                else pack_chunk_plain<HIST, PACK, DT>(cur, L);
-            } else {
-                pack_chunk_plain<HIST, PACK, DT>(cur, L);
-            }
+            pack_chunk_plain<PACK, DT>(cur, L);
+            forget();
             if (next.valid && next.fast) fetch_first_batch<DT>(next, A0, B0);
-        } else if (ROWSEL == 1 || (ROWSEL < 0 && src.rowchk())) {
-            pack_chunk_fast<true, HIST, PACK, DT>(cur, next, A0, B0, src.K8(), L);
+        } else if (ROWSEL == 1) {
+            pack_chunk_fast<true, PACK, DT>(cur, next, A0, B0, src.K8(), L);
         } else {
-            pack_chunk_fast<false, HIST, PACK, DT>(cur, next, A0, B0, src.K8(), L);
+            pack_chunk_fast<false, PACK, DT>(cur, next, A0, B0, src.K8(), L);
         }
         cur = next;
     }
 }
 
-// Which of the first `whole` parts of a chunk hold an exponent of a kept bucket (`maxima`: the largest exponent of each
-// of its parts_per_chunk parts, one byte each, 4-byte aligned); false if those are more than a quarter of a chunk's
-// parts (the chunk then takes the usual paths).
-__device__ __forceinline__ bool parts_to_read(const uint8_t* maxima, u32 parts_per_chunk, u32 min_kept_exp, u32 whole, u32* parts) {
-    const u32* p = reinterpret_cast<const u32*>(maxima);
-    u32 mask = 0;
-    for (u32 i = 0; i < parts_per_chunk / 4; ++i) {
-        const u32 word = load_uniform(p + i);
-#pragma unroll
-        for (u32 b = 0; b < 4; ++b) mask |= (((word >> (8 * b)) & 255u) >= min_kept_exp ? 1u : 0u) << (4 * i + b);
-    }
-    mask &= (1u << whole) - 1u;                   // (a ragged chunk: the bytes of its missing parts mean nothing)
-    *parts = mask;
-    return (u32)__popc(mask) <= parts_per_chunk / 4;
-}
-
-// The same for binary64 parameters: 32 parts of 512 elements per chunk, two bytes per maximum (11 exponent bits).
+// Binary64 parameters: which of the first `whole` parts of a chunk (32 of 512 elements, two bytes per recorded maximum, 11
+// exponent bits) hold an exponent of a kept bucket; false if those are more than a quarter of a chunk's parts (the chunk
+// then takes the usual path).
 __device__ __forceinline__ bool parts_to_read64(const uint16_t* maxima, u32 min_kept_exp, u32 whole, u32* parts) {
     const u32* p = reinterpret_cast<const u32*>(maxima);
     u32 mask = 0;
@@ -1078,8 +979,7 @@ struct VectorChunks {
     u32 k8; bool row;
     const u32* chunk_list; u32 listed;
     u32 pos;
-    const uint8_t* batch_max; u32 parts_per_chunk, min_kept_exp, cl_merged;     // what sweep 1 recorded per 4 KiB batch, or null
-    bool wide;                   // binary64: two bytes per recorded maximum
+    const uint8_t* batch_max; u32 parts_per_chunk, min_kept_exp, cl_merged;     // binary64: what sweep 1 recorded per 4 KiB batch, or null
     __device__ __forceinline__ u32 merged_codelen() const { return cl_merged; }
     __device__ __forceinline__ ChunkRef ref(u32 c, bool valid) const {
         ChunkRef ch;
@@ -1097,9 +997,7 @@ struct VectorChunks {
             const u64 inside = n - (u64)c * kChunk, part_elems = kChunk / parts_per_chunk;
             const u32 whole = inside >= kChunk ? parts_per_chunk : (u32)(inside / part_elems);
             // (less than one whole part: the guarded path)
-            ch.by_parts = whole != 0 && (wide ? parts_to_read64(reinterpret_cast<const uint16_t*>(batch_max) + (u64)c * parts_per_chunk, min_kept_exp, whole, &ch.parts)
-                                              : parts_to_read(batch_max + (u64)c * parts_per_chunk, parts_per_chunk, min_kept_exp, whole, &ch.parts));
-            if (ch.by_parts) ch.fast = false;        // off the pipelined path: see pack_chunk_parts
+            ch.by_parts = whole != 0 && parts_to_read64(reinterpret_cast<const uint16_t*>(batch_max) + (u64)c * parts_per_chunk, min_kept_exp, whole, &ch.parts);
         }
         return ch;
     }
@@ -1108,14 +1006,12 @@ struct VectorChunks {
         if (!chunk_list) return ref(i, i < nchunks);
         return i < listed ? ref(load_uniform(chunk_list + i), true) : ref(nchunks, false);
     }
-    template <bool HIST> __device__ __forceinline__ void enter(const ChunkRef&, PackLds<HIST>&) const {}
+    __device__ __forceinline__ void enter(const ChunkRef&, PackLds&) const {}
     __device__ __forceinline__ MaximaAt maxima_at(const ChunkRef&) const { return MaximaAt{nullptr, nullptr}; }
     __device__ __forceinline__ u32 K8() const { return k8; }
-    __device__ __forceinline__ bool rowchk() const { return row; }
 };
 
-template <bool HIST>
-__device__ __forceinline__ void pack_setup(PackLds<HIST>& L, const Table& T, u32 lane) {
+__device__ __forceinline__ void pack_setup(PackLds& L, const Table& T, u32 lane) {
     for (u32 i = lane; i < 512; i += 64) L.sym8[i] = (uint8_t)((T.symlen_of_bucket[i] & 15) << 3);
     if (lane < kMaxSym) L.codelen[lane] = T.codelen[lane];
     for (u32 i = lane; i < 256; i += 64) {
@@ -1125,8 +1021,7 @@ __device__ __forceinline__ void pack_setup(PackLds<HIST>& L, const Table& T, u32
     for (u32 i = lane; i < kMaxSym * kMmCopies; i += 64) { L.mn[i] = 0xFFFFFFFFu; L.mx[i] = 0; }
 }
 
-template <bool HIST>
-__device__ __forceinline__ void pack_merge_extremes(PackLds<HIST>& L, EncState* ws, u32 K, u32 lane) {
+__device__ __forceinline__ void pack_merge_extremes(PackLds& L, EncState* ws, u32 K, u32 lane) {
     if (lane < K) {
         u32 mn = 0xFFFFFFFFu, mx = 0;
 #pragma unroll
@@ -1144,7 +1039,7 @@ __device__ __forceinline__ void note_merged_chunks(const Table& T, u64 n, u32* c
                                                    const u32* chunk_maxexp) {
     const u32 lane = lane_id();
     const u32 nfull = (u32)(n / kChunk), min_kept_exp = T.min_kept_exp, len_merged = T.codelen[T.K] & 31;
-    for (u32 c0 = blockIdx.x * kW; c0 < nfull; c0 += gridDim.x * kW) {
+    for (u32 c0 = (blockIdx.x * blockDim.x + threadIdx.x) & ~(kW - 1); c0 < nfull; c0 += gridDim.x * blockDim.x) {
         const u32 c = c0 + lane;
         const bool merged = c < nfull && chunk_maxexp[maxexp_slot(c)] < min_kept_exp;
         if (merged) chunk_bits[c] = kMergedChunk | (kChunk * len_merged);
@@ -1153,138 +1048,349 @@ __device__ __forceinline__ void note_merged_chunks(const Table& T, u64 n, u32* c
     }
 }
 
-template <int DT>
-__global__ __launch_bounds__(64) void k_pack(const void* __restrict__ w, const void* __restrict__ w_ref, u64 n,
-                                             EncState* ws, u32* chunk_bits, u32* group_words,
-                                             const u32* chunk_maxexp, const u32* chunk_list, const uint8_t* batch_max,
-                                             u32* prov, u32 slot_words, u32 nchunks, int aligned) {
-    __shared__ PackLds<false> L;
-    const u32 lane = threadIdx.x;
-    const Table& T = ws->table;
-    if (T.status != 0 || ws->spec_ok != 0) return;     // nothing to code, or the speculative sweep already did
-    pack_setup(L, T, lane);
-    const u32 K = T.K;
-    __syncthreads();
-    VectorChunks src = {w, w_ref, n, prov, slot_words, chunk_bits, group_words, nchunks, aligned != 0, K << 3, T.max_len <= 8,
-                        chunk_list, chunk_list ? ws->list_count : 0, 0,
-                        chunk_list ? batch_max : nullptr, 4096u / (kRowElems * elem_bytes<DT>()) == 4 ? 16u : 8u, T.min_kept_exp,
-                        T.codelen[K]};
-    if (chunk_list) note_merged_chunks(T, n, chunk_bits, group_words, chunk_maxexp);
-    if (src.row) pack_loop<false, true, DT, 1>(src, L);
-    else pack_loop<false, true, DT, 0>(src, L);
-    __syncthreads();
-    pack_merge_extremes(L, ws, K, lane);
-}
+// ----------------------------------------------------------------------------- coding by workgroups
+// Sweep 2 (fp32, bf16, fp16, and from staged keys): a workgroup of eight wavefronts per chunk, wavefront v coding rows
+// 8 v .. 8 v + 7, so that every lane's string of 256 codes grows in eight parts of 32 side by side.  A workgroup codes one
+// chunk and ends: its rows are asked for before anything is known about the table, and what overlaps one chunk's waits with
+// another's work is that several workgroups share a compute unit.  The parts (up to kPartWords words of every lane) stay in
+// LDS; once all lengths are known, each thread ORs its part, shifted, into the chunk's payload there, and lane lengths and
+// payload go to the chunk's slot as the record that the blob will hold: k_place then only copies it.  A chunk whose
+// strings outgrow these areas (rare symbols only) is coded again by one wavefront, as lane strings (kRawChunk).
+// Before, a wavefront walked over chunks with its next rows in flight (2 wavefronts per SIMD, or 1, by its registers);
+// k_pack and k_place, before -> after: 2^20 fp32 elements 19.3 + 4.8 -> 7.6 + 3.6 us, 2^27 bf16 138 + 27 -> 119 + 19 us,
+// 2^28 fp32 430 + 45 -> 426 + 33 us, from keys 139 + 45 -> 114 + 33 us; 161 tensors of 25.6 M (kb_list, kb_pack, kb_place)
+// 5 + 44 + 12 -> 0 + 45 + 7 us.
+// (Workgroups that stay and walk over chunks, the next one's rows in flight: 159 us on the bf16 vector.)
+constexpr u32 kWgWaves = 8, kWgRows = kR / kWgWaves, kWgThreads = kWgWaves * kW;
+constexpr u32 kPartWords = 7;           // words of a lane's part: 32 codes of 7 bits
+constexpr u32 kPayloadWords = 2560;     // words of a chunk's payload: 5 bits per element
 
-// ----------------------------------------------------------------------------- k_pack_keys
-// Sweep 2 of an encode with staged keys: the same chunks, slots and lane strings as k_pack, coded from the 9-bit keys
-// sweep 1 left (16 exponent bytes + 16 sign bits per lane and batch of 4 rows) instead of from w and w_ref: 1.125
-// bytes per element read instead of 8.  The extremes of the kept buckets are sweep 1's business then.  A full chunk
-// takes 16 key loads per lane, all in flight together, and the next chunk's are issued before this one is coded; the
-// vector's ragged last chunk (whose tail has no keys) is coded from w and w_ref like any ragged chunk.
-constexpr u32 kKeyBatches = kR / 4;             // batches of 4 rows per chunk
-constexpr u32 kHalfBatches = kKeyBatches / 2;
+struct PackWg {
+    uint8_t sym8[512];                   // bucket -> symbol << 3
+    u32 codelen[kMaxSym];                // (code << 5) | len
+    uint2 pair[256];                     // (symbol a, symbol b) -> {code of a followed by b, its length}
+    u32 mn[kMaxSym * kMmCopies], mx[kMaxSym * kMmCopies];      // extremes of the delta bit patterns per symbol
+    u32 bits[kWgWaves][kW];              // lengths of the parts
+    u32 overflow;                        // some part does not fit its area
+    u32 part[kWgWaves][kPartWords * kW]; // word k of lane l at [64 k + l]
+    alignas(16) u32 payload[kPayloadWords];
+};
 
-// The keys of half a chunk as one lane holds them: 8 batches of 16 exponent bytes and 16 sign bits.
-struct HalfKeys { u32x4 exp[kHalfBatches]; u32 sign[kHalfBatches]; };
-
-__device__ __forceinline__ void fetch_half(const KeyPlanes& keys, u32 c, u32 half, HalfKeys& k) {
-    const u64 at = ((u64)c * kKeyBatches + half * kHalfBatches) * kW + lane_id();
-#pragma unroll
-    for (u32 b = 0; b < kHalfBatches; ++b) {
-        k.exp[b] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(keys.exp) + at + b * kW);
-        k.sign[b] = __builtin_nontemporal_load(keys.sign + at + b * kW);
-    }
-}
-
-// A lane's growing code string of one chunk.
-struct LaneString {
-    u64 acc; u32 nb, nw;                // bits waiting in acc (nb of them), words written
-    u32* lane_words;
-    __device__ __forceinline__ void start(const ChunkRef& ch) { acc = 0; nb = 0; nw = 0; lane_words = ch.slot + kLaneBitsWords + lane_id(); }
-    __device__ __forceinline__ void put(u32 word, PackLds<false>& L) {
-        if (nw < kStageRows) L.stage[nw * kW + lane_id()] = word;
-        else lane_words[nw * kW] = word;
-    }
-    __device__ __forceinline__ void flush(PackLds<false>& L) {
-        if (nb >= 32) { put((u32)(acc >> (nb - 32)), L); ++nw; nb -= 32; }
+// A lane's part while it grows.
+struct LanePart {
+    u64 acc; u32 nb, nw;                 // bits waiting in acc (nb of them), words complete
+    u32* words;                          // this lane's column of PackWg::part
+    __device__ __forceinline__ void start(PackWg& L, u32 v) { acc = 0; nb = 0; nw = 0; words = L.part[v] + lane_id(); }
+    __device__ __forceinline__ void put(u32 word) { if (nw < kPartWords) words[nw * kW] = word; }
+    __device__ __forceinline__ void append(u32 code, u32 len) {
+        acc = (acc << len) | code; nb += len;
+        if (nb >= 32) { put((u32)(acc >> (nb - 32))); ++nw; nb -= 32; }
     }
 };
 
-template <bool ROWCHK>
-__device__ __forceinline__ void code_half(const HalfKeys& k, LaneString& S, PackLds<false>& L) {
+// Two rows, their symbols (<< 3) looked up: only the chain that grows the lane's part is serial.
+__device__ __forceinline__ void code_symbols(const u32 (&t)[8], PackWg& L, LanePart& S) {
+    uint2 p[4];
 #pragma unroll
-    for (u32 b = 0; b < kHalfBatches; ++b) {
-        const u32 wv[4] = {k.exp[b].x, k.exp[b].y, k.exp[b].z, k.exp[b].w};
-        u32 t[16];
+    for (int i = 0; i < 4; ++i) p[i] = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(L.pair) + ((t[2 * i] << 4) | t[2 * i + 1]));
 #pragma unroll
-        for (int i = 0; i < 16; ++i)        // bucket id = sign << 8 | exponent, as the top 9 bits of the delta
-            t[i] = L.sym8[((wv[i >> 2] >> (8 * (i & 3))) & 255u) | (((k.sign[b] >> i) & 1u) << 8)];
-        uint2 p[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-            p[i] = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(L.pair) + ((t[2 * i] << 4) | t[2 * i + 1]));
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            S.acc = (S.acc << p[i].y) | p[i].x; S.nb += p[i].y;
-            if (!ROWCHK || (i & 1)) S.flush(L);
-        }
-    }
+    for (int i = 0; i < 4; ++i) S.append(p[i].x, p[i].y);
 }
 
-// the last, partly filled word, then the staged rows to the slot (as pack_chunk_fast), then the sizes
-__device__ __forceinline__ void finish_chunk_keys(const ChunkRef& cur, LaneString& S, PackLds<false>& L) {
+// Two rows of w and w_ref: the look-ups of the 8 elements are issued together.
+template <int DT>
+__device__ __forceinline__ void code_rows2(const typename Raw<DT>::type* a, const typename Raw<DT>::type* b, u32 K8, PackWg& L, LanePart& S) {
+    u32 u[8], t[8];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        float xa[4], xb[4];
+        unpack<DT>(a[k], xa); unpack<DT>(b[k], xb);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) u[4 * k + v] = delta_bits(xa[v], xb[v]);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) t[i] = L.sym8[u[i] >> 23];
+    u32 tmin = t[0];
+#pragma unroll
+    for (int i = 1; i < 8; ++i) tmin = min(tmin, t[i]);
+    if (__any(tmin < K8)) {              // (the merged symbol has a slot of its own that nobody reads)
+        const u32 copy = lane_id() & (kMmCopies - 1);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { atomicMin(&L.mn[t[i] * (kMmCopies / 8) + copy], u[i]); atomicMax(&L.mx[t[i] * (kMmCopies / 8) + copy], u[i]); }
+    }
+    code_symbols(t, L, S);
+}
+
+// The chunk once more, by one wavefront: lane strings straight to the slot.
+template <int DT>
+__device__ __forceinline__ void pack_chunk_raw(const ChunkRef& ch, const PackWg& L) {
     const u32 lane = lane_id();
-    if (S.nb > 0) S.put((u32)(S.acc << (32 - S.nb)), L);
-    u32 rows = min(S.nw + (S.nb > 0 ? 1u : 0u), kStageRows);
+    u32* lane_words = ch.slot + kLaneBitsWords + lane;
+    u64 acc = 0;
+    u32 nb = 0, nw = 0;
+#pragma unroll 1
+    for (u32 r = 0; r < kR; ++r) {
+        const u64 idx = row_at(ch.c, r);
+        float xa[4], xb[4];
+        load_row<false, DT>(ch.w, idx, ch.n, xa); load_row<false, DT>(ch.w_ref, idx, ch.n, xb);
 #pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) rows = max(rows, (u32)__shfl_xor(rows, d, 64));
-    const uint4* src = reinterpret_cast<const uint4*>(L.stage);
-    uint4* dst = reinterpret_cast<uint4*>(cur.slot + kLaneBitsWords);
-    for (u32 i = lane; i < rows * (kW / 4); i += kW) dst[i] = src[i];
-    finish_lane_sizes(cur, S.nb, S.nw);
+        for (int v = 0; v < 4; ++v) {
+            if (idx + v < ch.n) {
+                const u32 cl = L.codelen[L.sym8[delta_bits(xa[v], xb[v]) >> 23] >> 3];
+                acc = (acc << (cl & 31)) | (cl >> 5); nb += cl & 31;
+            }
+            if ((v & 1) && nb >= 32) { lane_words[nw * kW] = (u32)(acc >> (nb - 32)); ++nw; nb -= 32; }
+        }
+    }
+    if (nb > 0) lane_words[nw * kW] = (u32)(acc << (32 - nb));
+    finish_lane_sizes(ch, nb, nw);
 }
 
-// Half a chunk's keys are always on their way while the half before is coded, across chunk borders too.
-template <bool ROWCHK>
-__device__ __forceinline__ void pack_keys_loop(VectorChunks& src, const KeyPlanes& keys, PackLds<false>& L) {
-    HalfKeys A, B;
-    ChunkRef cur = src.take();
-    if (cur.valid && cur.fast) fetch_half(keys, cur.c, 0, A);
-    while (cur.valid) {
-        const ChunkRef next = src.take();
-        if (cur.fast) {
-            LaneString S;
-            S.start(cur);
-            fetch_half(keys, cur.c, 1, B);
-            code_half<ROWCHK>(A, S, L);
-            if (next.valid && next.fast) fetch_half(keys, next.c, 0, A);
-            code_half<ROWCHK>(B, S, L);
-            finish_chunk_keys(cur, S, L);
-        } else {
-            pack_chunk_plain<false, true, kF32>(cur, L);
-            if (next.valid && next.fast) fetch_half(keys, next.c, 0, A);
+// All parts are coded: their lengths, the payload, the record.  Returns (in every thread) whether the chunk fits its areas;
+// nothing is written for it otherwise.  Contains barriers.
+__device__ __forceinline__ bool finish_parts(const ChunkRef& ch, LanePart& S, u32 v, PackWg& L) {
+    const u32 t = threadIdx.x, lane = lane_id();
+    if (S.nb > 0) S.put((u32)(S.acc << (32 - S.nb)));
+    const u32 mine = 32 * S.nw + S.nb;
+    L.bits[v][lane] = mine;
+    if (mine > 32 * kPartWords) L.overflow = 1;
+    __syncthreads();
+    u32 before = 0, bits = 0;
+#pragma unroll
+    for (u32 k = 0; k < kWgWaves; ++k) {
+        const u32 b = L.bits[k][lane];
+        before += k < v ? b : 0u;
+        bits += b;
+    }
+    const u32 incl = wave_incl_scan(bits), total = read_lane(incl, kW - 1), nwords = (total + 31) >> 5;
+    if (L.overflow != 0 || nwords > kPayloadWords) return false;
+    {
+        const u32 o = incl - bits + before, sh = o & 31, W0 = o >> 5, have = (mine + 31) >> 5;
+        const u32 touched = mine ? ((o + mine - 1) >> 5) - W0 + 1 : 0;
+        u32 prev = 0;                                          // (a part of 7 words touches 8 of the payload)
+#pragma unroll
+        for (u32 j = 0; j <= kPartWords; ++j) {
+            const u32 w = j < have && j < kPartWords ? L.part[v][j * kW + lane] : 0;
+            if (j < touched) atomicOr(&L.payload[W0 + j], __builtin_amdgcn_alignbit(prev, w, sh));
+            prev = w;
         }
-        cur = next;
+    }
+    __syncthreads();
+    if (v == 0) {
+        reinterpret_cast<uint16_t*>(ch.slot)[lane] = (uint16_t)bits;
+        if (lane == 0) { *ch.bits_at = total; atomicAdd(ch.group_at, kLaneBitsWords + nwords); }
+    }
+    // the payload in whole vectors (what lies behind its end in the slot nobody reads)
+    const u32x4* from = reinterpret_cast<const u32x4*>(L.payload);
+    u32x4* to = reinterpret_cast<u32x4*>(ch.slot + kLaneBitsWords);
+    for (u32 i = t; i < (nwords + 3) / 4; i += kWgThreads) to[i] = from[i];
+    return true;
+}
+
+// 4 elements from index i on, those at n and behind read as zero; any alignment
+template <int DT>
+__device__ __forceinline__ typename Raw<DT>::type load_raw_guarded(const void* base, u64 i, u64 n) {
+    if constexpr (DT == kF32) {
+        const float* p = static_cast<const float*>(base) + i;
+        float x[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = i + e < n ? p[e] : 0.0f;
+        return make_float4(x[0], x[1], x[2], x[3]);
+    } else {
+        const uint16_t* p = static_cast<const uint16_t*>(base) + i;
+        u32 x[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[e] = i + e < n ? p[e] : 0u;
+        return make_uint2(x[0] | (x[1] << 16), x[2] | (x[3] << 16));
     }
 }
 
-__global__ __launch_bounds__(64) void k_pack_keys(const void* __restrict__ w, const void* __restrict__ w_ref, u64 n,
-                                                  EncState* ws, u32* chunk_bits, u32* group_words, const u32* chunk_maxexp,
-                                                  const u32* chunk_list, KeyPlanes keys, u32* prov, u32 slot_words, u32 nchunks) {
-    __shared__ PackLds<false> L;
-    const u32 lane = threadIdx.x;
+// The workgroup's tables, extremes and areas; a barrier of the caller's follows.  (kWgThreads = 512 buckets)
+__device__ __forceinline__ void pack_setup(PackWg& L, const Table& T) {
+    const u32 t = threadIdx.x;
+    const u32 sl = T.symlen_of_bucket[t];
+    const u32 ca = t < 256 ? T.codelen[t >> 4] : 0u, cb = t < 256 ? T.codelen[t & 15] : 0u, own = t < kMaxSym ? T.codelen[t] : 0u;
+    L.sym8[t] = (uint8_t)((sl & 15) << 3);
+    if (t < 256) L.pair[t] = make_uint2(((ca >> 5) << (cb & 31)) | (cb >> 5), (ca & 31) + (cb & 31));
+    if (t < kMaxSym) L.codelen[t] = own;
+    static_assert(kWgThreads == 512 && kMaxSym * kMmCopies == 512, "one entry per thread");
+    L.mn[t] = 0xFFFFFFFFu; L.mx[t] = 0;
+    if (t == 0) L.overflow = 0;
+    for (u32 i = t; i < kPayloadWords; i += kWgThreads) L.payload[i] = 0;
+}
+
+// A full chunk whose largest exponent `maxexp` lies below every kept bucket holds the merged symbol only: it gets its size
+// and no slot (as in note_merged_chunks).  Returns whether it is one, the same in every thread.
+__device__ __forceinline__ bool noted_as_merged(const ChunkRef& ch, const Table& T, u32 maxexp) {
+    if ((u64)(ch.c + 1) * kChunk > ch.n || maxexp >= T.min_kept_exp) return false;
+    if (threadIdx.x == 0) {
+        const u32 len_merged = T.codelen[T.K] & 31;
+        *ch.bits_at = kMergedChunk | (kChunk * len_merged);
+        atomicAdd(ch.group_at, kLaneBitsWords + kChunk / 32 * len_merged);
+    }
+    return true;
+}
+
+// Codes the chunk with table T (in memory).  parts: the largest exponent of each of its 4 KiB parts, one byte each (16 of
+// 4-byte elements, 8 of 2-byte), or null: parts of a full chunk below every kept bucket are then not read.
+template <int DT>
+__device__ __forceinline__ void pack_chunk_wg(const ChunkRef& ch, const Table& T, const uint8_t* parts, EncState* ws, PackWg& L) {
+    typedef typename Raw<DT>::type raw_t;
+    constexpr u32 kPartRows = 4096 / (kRowElems * elem_bytes<DT>()), H = kWgRows / 2;      // 4 or 8 rows per part
+    const u32 lane = lane_id(), v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), first_row = kWgRows * v;
+    raw_t A[kWgRows], B[kWgRows];
+    bool skip[2] = {false, false};           // rows first_row .. + 3, and the 4 behind them: merged elements only
+    if (ch.fast) {
+        if (parts) {
+#pragma unroll
+            for (u32 h = 0; h < 2; ++h) {
+                const u32 p = (first_row + H * h) / kPartRows;
+                skip[h] = ((load_uniform(reinterpret_cast<const u32*>(parts) + p / 4) >> (8 * (p % 4))) & 255u) < T.min_kept_exp;
+            }
+        }
+#pragma unroll
+        for (u32 h = 0; h < 2; ++h) {
+            if (skip[h]) continue;
+#pragma unroll
+            for (u32 k = H * h; k < H * h + H; ++k) { A[k] = load_raw<DT>(ch.w, row_at(ch.c, first_row + k)); B[k] = load_raw<DT>(ch.w_ref, row_at(ch.c, first_row + k)); }
+        }
+    } else {
+#pragma unroll
+        for (u32 k = 0; k < kWgRows; ++k) { A[k] = load_raw_guarded<DT>(ch.w, row_at(ch.c, first_row + k), ch.n); B[k] = load_raw_guarded<DT>(ch.w_ref, row_at(ch.c, first_row + k), ch.n); }
+    }
+    const u32 K8 = T.K << 3;
+    pack_setup(L, T);
+    __syncthreads();
+    LanePart S;
+    S.start(L, v);
+    if (ch.fast) {
+#pragma unroll
+        for (u32 h = 0; h < 2; ++h) {
+            if (skip[h]) {
+                // the merged code 16 times, as many copies per step as fit 32 bits (a chunk with such a part holds merged
+                // elements, so their symbol has a code)
+                const u32 cl = L.codelen[K8 >> 3], len = cl & 31, per_step = len ? 32 / len : 1;
+                u32 run = 0;
+#pragma unroll 1
+                for (u32 i = 0; i < per_step; ++i) run = (run << len) | (cl >> 5);
+#pragma unroll 1
+                for (u32 left = H * kV; left != 0;) {
+                    const u32 k = left < per_step ? left : per_step;
+                    S.append(run >> ((per_step - k) * len), k * len);
+                    left -= k;
+                }
+            } else {
+#pragma unroll
+                for (u32 k = H * h; k < H * h + H; k += 2) code_rows2<DT>(A + k, B + k, K8, L, S);
+            }
+        }
+    } else {
+#pragma unroll
+        for (u32 k = 0; k < kWgRows; ++k) {
+            const u64 idx = row_at(ch.c, first_row + k);
+            float xa[4], xb[4];
+            unpack<DT>(A[k], xa); unpack<DT>(B[k], xb);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                if (idx + e < ch.n) {
+                    const u32 u = delta_bits(xa[e], xb[e]), sy8 = L.sym8[u >> 23], cl = L.codelen[sy8 >> 3];
+                    const u32 at = sy8 * (kMmCopies / 8) + (lane & (kMmCopies - 1));
+                    atomicMin(&L.mn[at], u); atomicMax(&L.mx[at], u);
+                    S.append(cl >> 5, cl & 31);
+                }
+            }
+        }
+    }
+    const bool fits = finish_parts(ch, S, v, L);
+    // the extremes: thread t holds copy t mod 32 of symbol t / 32 (see pack_merge_extremes)
+    const u32 t = threadIdx.x;
+    u32 mn = L.mn[t], mx = L.mx[t];
+#pragma unroll
+    for (int d = kMmCopies / 2; d >= 1; d >>= 1) { mn = min(mn, (u32)__shfl_xor(mn, d, 64)); mx = max(mx, (u32)__shfl_xor(mx, d, 64)); }
+    const u32 sym = t / kMmCopies, copy = blockIdx.x % kExtCopies;
+    if (t % kMmCopies == 0 && sym < (K8 >> 3) && mn <= mx) { atomicMin(&ws->mmin[copy][sym], mn & 0x7FFFFFu); atomicMax(&ws->mmax[copy][sym], mx & 0x7FFFFFu); }
+    if (!fits && v == 0) pack_chunk_raw<DT>(ch, L);
+}
+
+// Sweep 2 of one vector, a workgroup per chunk.  chunk_list: the chunks to read (then workgroups beyond the list leave at
+// once, having seen to the sizes of the chunks off it); null: every chunk, and chunk_maxexp (or null) tells those that hold
+// merged elements only.
+// STAY: workgroups take more than one chunk (behind a speculative sweep: see launch_pack).
+template <int DT, bool STAY>
+__global__ __launch_bounds__(kWgThreads, DT == kF32 || STAY ? 4 : 8) void k_pack(const void* __restrict__ w, const void* __restrict__ w_ref, u64 n,
+                                                     EncState* ws, u32* chunk_bits, u32* group_words, const u32* chunk_maxexp,
+                                                     const u32* chunk_list, const uint8_t* batch_max, u32* prov, u32 slot_words, u32 nchunks,
+                                                     int aligned) {
+    __shared__ PackWg L;
+    const Table& T = ws->table;
+    if (T.status != 0 || ws->spec_ok != 0) return;     // nothing to code, or the speculative sweep already did
+    if (chunk_list) note_merged_chunks(T, n, chunk_bits, group_words, chunk_maxexp);
+    const u32 count = chunk_list ? ws->list_count : nchunks;
+    auto chunk = [&](u32 i) {
+        const u32 c = chunk_list ? load_uniform(chunk_list + i) : i;
+        ChunkRef ch;
+        ch.w = w; ch.w_ref = w_ref; ch.n = n; ch.c = c;
+        ch.slot = prov + (u64)c * slot_words; ch.bits_at = chunk_bits + c; ch.group_at = group_words + (c >> 6);
+        ch.fast = aligned && (u64)(c + 1) * kChunk <= n;
+        if (!chunk_list && chunk_maxexp && noted_as_merged(ch, T, chunk_maxexp[maxexp_slot(c)])) return;
+        constexpr u32 kParts = kChunk * elem_bytes<DT>() / 4096;
+        pack_chunk_wg<DT>(ch, T, chunk_list ? batch_max + (u64)c * kParts : nullptr, ws, L);
+    };
+    if constexpr (STAY) {
+        for (u32 i = blockIdx.x; i < count; i += gridDim.x) { chunk(i); __syncthreads(); }
+    } else {
+        if (blockIdx.x < count) chunk(blockIdx.x);
+    }
+}
+
+// ----------------------------------------------------------------------------- k_pack_keys
+// Sweep 2 of an encode with staged keys: as k_pack, coded from the 9-bit keys sweep 1 left (16 exponent bytes + 16 sign bits
+// per lane and batch of 4 rows) instead of from w and w_ref: 1.125 bytes per element read instead of 8.  The extremes of
+// the kept buckets are sweep 1's business then.  A wavefront's 8 rows are two key loads of each kind per lane; the
+// vector's ragged last chunk (whose tail has no keys) is coded from w and w_ref.
+constexpr u32 kKeyBatches = kR / 4;                        // batches of 4 rows per chunk
+
+__global__ __launch_bounds__(kWgThreads, 8) void k_pack_keys(const void* __restrict__ w, const void* __restrict__ w_ref, u64 n,
+                                                          EncState* ws, u32* chunk_bits, u32* group_words, const u32* chunk_maxexp,
+                                                          const u32* chunk_list, KeyPlanes keys, u32* prov, u32 slot_words) {
+    __shared__ PackWg L;
     const Table& T = ws->table;
     if (T.status != 0) return;
-    pack_setup(L, T, lane);
-    const u32 K = T.K;
-    __syncthreads();
-    // (aligned arrays by construction; no part-by-part coding: a listed chunk's keys are 18 KB, read whole)
-    VectorChunks src = {w, w_ref, n, prov, slot_words, chunk_bits, group_words, nchunks, true, K << 3, T.max_len <= 8,
-                        chunk_list, ws->list_count, 0, nullptr, 16u, T.min_kept_exp, T.codelen[K]};
     note_merged_chunks(T, n, chunk_bits, group_words, chunk_maxexp);
-    if (src.row) pack_keys_loop<true>(src, keys, L);
-    else pack_keys_loop<false>(src, keys, L);
+    if (blockIdx.x >= ws->list_count) return;
+    const u32 c = load_uniform(chunk_list + blockIdx.x);
+    ChunkRef ch;
+    ch.w = w; ch.w_ref = w_ref; ch.n = n; ch.c = c;
+    ch.slot = prov + (u64)c * slot_words; ch.bits_at = chunk_bits + c; ch.group_at = group_words + (c >> 6);
+    ch.fast = false;
+    if ((u64)(c + 1) * kChunk > n) { pack_chunk_wg<kF32>(ch, T, nullptr, ws, L); return; }
+    constexpr u32 kMine = kWgRows / 4;
+    const u32 v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const u64 at = ((u64)c * kKeyBatches + v * kMine) * kW + lane_id();
+    u32x4 exps[kMine];
+    u32 signs[kMine];
+#pragma unroll
+    for (u32 b = 0; b < kMine; ++b) {
+        exps[b] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(keys.exp) + at + b * kW);
+        signs[b] = __builtin_nontemporal_load(keys.sign + at + b * kW);
+    }
+    pack_setup(L, T);
+    __syncthreads();
+    LanePart S;
+    S.start(L, v);
+#pragma unroll
+    for (u32 b = 0; b < kMine; ++b) {
+        const u32 wv[4] = {exps[b].x, exps[b].y, exps[b].z, exps[b].w};
+#pragma unroll
+        for (int h = 0; h < 16; h += 8) {
+            u32 t[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i)             // bucket id = sign << 8 | exponent, as the top 9 bits of the delta
+                t[i] = L.sym8[((wv[(h + i) >> 2] >> (8 * (i & 3))) & 255u) | (((signs[b] >> (h + i)) & 1u) << 8)];
+            code_symbols(t, L, S);
+        }
+    }
+    if (!finish_parts(ch, S, v, L) && v == 0) pack_chunk_raw<kF32>(ch, L);
 }
 
 // ----------------------------------------------------------------------------- k_pack64
@@ -1428,7 +1534,7 @@ __global__ __launch_bounds__(64) void k_pack64(const void* __restrict__ w, const
     __syncthreads();
     VectorChunks src = {w, w_ref, n, prov, slot_words, chunk_bits, group_words, nchunks, aligned != 0, K << 3, true,
                         chunk_list, chunk_list ? ws->list_count : 0, 0, chunk_list ? part_max : nullptr, 32u, T.min_kept_exp,
-                        T.codelen[K], true};
+                        T.codelen[K]};
     if (chunk_list) note_merged_chunks(T, n, chunk_bits, group_words, chunk_maxexp);
     for (ChunkRef ch = src.take(); ch.valid; ch = src.take()) {
         if (ch.by_parts) pack_chunk64_parts(ch, src.merged_codelen(), L, K);
@@ -1452,7 +1558,7 @@ template <int DT>
 __global__ __launch_bounds__(64) void k_spec_sweep(const void* __restrict__ w, const void* __restrict__ w_ref, u64 n,
                                                    EncState* ws, u32* chunk_bits, u32* group_words, u32* prov,
                                                    u32 slot_words, u32 nchunks, int aligned) {
-    __shared__ PackLds<true> L;
+    __shared__ PackLds L;
     const u32 lane = threadIdx.x;
     const Table& T = ws->table;
     const bool spec = ws->spec != 0;
@@ -1462,9 +1568,9 @@ __global__ __launch_bounds__(64) void k_spec_sweep(const void* __restrict__ w, c
     __syncthreads();
     VectorChunks src = {w, w_ref, n, prov, slot_words, chunk_bits, group_words, nchunks, aligned != 0, K << 3,
                         !spec || T.max_len <= 8, nullptr, 0, 0, nullptr, 16u, 0u, 0u};
-    if (!spec) pack_loop<true, false, DT, 1>(src, L);
-    else if (src.row) pack_loop<true, true, DT, 1>(src, L);
-    else pack_loop<true, true, DT, 0>(src, L);
+    if (!spec) pack_loop<false, DT, 1>(src, L);
+    else if (src.row) pack_loop<true, DT, 1>(src, L);
+    else pack_loop<true, DT, 0>(src, L);
     __syncthreads();
     for (u32 b = lane; b < 512; b += 64) {
         u32 sum = 0;
@@ -1612,14 +1718,32 @@ __device__ __forceinline__ void place_chunk(uint8_t* out, EncState* ws, const u3
     const u32* slot = prov + (u64)(valid ? c : 0) * slot_words;
     const u32 own = valid ? __builtin_amdgcn_readfirstlane(chunk_bits[c]) : 0;
     const bool merged = (own & kMergedChunk) != 0;               // wave-uniform: no slot, 256 copies of one code per lane
-    const u32 bits = !valid ? 0 : merged ? (own & ~kMergedChunk) / kW : reinterpret_cast<const uint16_t*>(slot)[lane];
+    const bool record = valid && (own & (kMergedChunk | kRawChunk)) == 0;      // the slot holds the record as it is
+    const u32 bits = !valid || record ? 0 : merged ? (own & kChunkBits) / kW : reinterpret_cast<const uint16_t*>(slot)[lane];
     const u32 g = c >> 6;
-    u64 part = (valid && 64 * g + lane < c) ? kLaneBitsWords + (((chunk_bits[64 * g + lane] & ~kMergedChunk) + 31) >> 5) : 0;
+    u64 part = (valid && 64 * g + lane < c) ? kLaneBitsWords + (((chunk_bits[64 * g + lane] & kChunkBits) + 31) >> 5) : 0;
     if (valid) {
 #pragma unroll 4
         for (u32 j = lane; j < g; j += kW) part += group_words[j];
     }
     const u64 word_off = wave_sum64(part);
+    if (record) {
+        // 16-byte vectors from the slot to a place in the blob that is aligned to words only, eight in flight per lane
+        typedef u32x4 __attribute__((aligned(4))) u32x4_word;
+        const u32 nw = kLaneBitsWords + (((own & kChunkBits) + 31) >> 5), nvec = nw >> 2;
+        u32* to = reinterpret_cast<u32*>(out + chunk_area_of(nchunks)) + word_off;
+        const u32x4* from = reinterpret_cast<const u32x4*>(slot);
+        for (u32 i0 = 0; i0 < nvec; i0 += 8 * kW) {
+            u32x4 x[8];
+#pragma unroll
+            for (u32 k = 0; k < 8; ++k) if (i0 + k * kW + lane < nvec) x[k] = from[i0 + k * kW + lane];
+#pragma unroll
+            for (u32 k = 0; k < 8; ++k) if (i0 + k * kW + lane < nvec) reinterpret_cast<u32x4_word*>(to)[i0 + k * kW + lane] = x[k];
+        }
+        if (lane < (nw & 3)) to[4 * nvec + lane] = slot[4 * nvec + lane];
+        if (lane == 0) reinterpret_cast<u32*>(out + kHeaderBytes)[c] = (u32)word_off;
+        return;
+    }
     const u32 incl = wave_incl_scan(bits);
     const u32 o = incl - bits;                               // first bit of this lane's string
     const u32 total_bits = __shfl(incl, 63, 64);
@@ -1734,22 +1858,16 @@ __global__ __launch_bounds__(256) void kb_setup(BatchArgs a) {
     }
 }
 
-// The dense chunks of a batched call as a chunk source for the coding loop.
-template <bool HIST, bool PACK>
+// The dense chunks of a batched call as a chunk source for the counting loop.
 struct BatchChunks {
     BatchArgs a;
-    u32 active;                  // tensor whose counts / extremes / table the LDS holds (0xFFFFFFFF: none yet)
-    u32 k8; bool row;
+    u32 active;                  // tensor whose counts the LDS holds (0xFFFFFFFF: none yet)
     u32 pos;
-    u32 listed;                  // coding sweep: entries of a.chunk_list (the counting sweep takes every chunk)
-    u32 cl_merged;               // (code << 5) | length of the active tensor's merged symbol
-    u32 stride;                  // wavefronts that share the chunks
     __device__ __forceinline__ ChunkRef take() {
         ChunkRef ch;
-        const u32 i = blockIdx.x + (pos++) * stride;
-        ch.valid = i < (PACK ? listed : a.total_chunks);
-        const u32 g = (PACK && ch.valid) ? load_uniform(a.chunk_list + i) : i;
-        ch.seg = 0; ch.c = 0; ch.w = nullptr; ch.w_ref = nullptr; ch.n = 0; ch.fast = false; ch.vec = false; ch.by_parts = false; ch.parts = 0;
+        const u32 g = blockIdx.x + (pos++) * gridDim.x;
+        ch.valid = g < a.total_chunks;
+        ch.seg = 0; ch.c = 0; ch.w = nullptr; ch.w_ref = nullptr; ch.n = 0; ch.fast = false; ch.vec = false;
         ch.slot = nullptr; ch.bits_at = nullptr; ch.group_at = nullptr;
         if (ch.valid) {
             ch.seg = __builtin_amdgcn_readfirstlane(a.seg_of_chunk[g]);
@@ -1758,65 +1876,38 @@ struct BatchChunks {
             ch.w = sg.w; ch.w_ref = sg.w_ref; ch.n = sg.n;
             ch.fast = sg.aligned && (u64)(ch.c + 1) * kChunk <= sg.n;
             ch.vec = sg.aligned != 0;
-            ch.slot = a.prov + (u64)g * a.slot_words;
-            ch.bits_at = a.chunk_bits + g;
-            ch.group_at = a.group_words + sg.group0 + (ch.c >> 6);
-            // a tensor whose delta is not finite gets a header-only blob: nothing to code
-            if (PACK && a.states[ch.seg].table.status != 0) { ch.n = 0; ch.fast = false; }
-            else if (PACK && sg.aligned) {
-                // a mostly merged chunk: only its parts with a kept element are read (see pack_chunk_parts)
-                const u32 ppc = a.dtype == kF32 ? 16u : 8u;
-                const u64 inside = sg.n - (u64)ch.c * kChunk, part_elems = kChunk / ppc;
-                const u32 whole = inside >= kChunk ? ppc : (u32)(inside / part_elems);
-                ch.by_parts = whole != 0 && parts_to_read(a.part_max + (u64)g * kPartBytes, ppc,
-                                                         load_uniform(&a.states[ch.seg].table.min_kept_exp), whole, &ch.parts);
-                if (ch.by_parts) ch.fast = false;
-            }
         }
         return ch;
     }
-    __device__ __forceinline__ void hand_in(PackLds<HIST>& L) {
+    __device__ __forceinline__ void hand_in(PackLds& L) {
         if (active == 0xFFFFFFFFu) return;
-        const u32 lane = lane_id();
         EncState* st = &a.states[active];
-        if (HIST) {
-            for (u32 b = lane; b < 512; b += kW) {
-                u32 sum = 0;
+        for (u32 b = lane_id(); b < 512; b += kW) {
+            u32 sum = 0;
 #pragma unroll
-                for (int k = 0; k < kSpecCopies; ++k) { sum += L.hist[hist_slot(b, k)]; L.hist[hist_slot(b, k)] = 0; }
-                if (sum) atomicAdd(&st->hist[b], (u64)sum);
-            }
+            for (int k = 0; k < kSpecCopies; ++k) { sum += L.hist[hist_slot(b, k)]; L.hist[hist_slot(b, k)] = 0; }
+            if (sum) atomicAdd(&st->hist[b], (u64)sum);
         }
-        if (PACK) pack_merge_extremes(L, st, st->table.K, lane);
     }
-    __device__ __forceinline__ void enter(const ChunkRef& ch, PackLds<HIST>& L) {
+    __device__ __forceinline__ void enter(const ChunkRef& ch, PackLds& L) {
         if (ch.seg == active) return;
         hand_in(L);
         active = ch.seg;
-        if (PACK) {
-            const Table& T = a.states[active].table;
-            __syncthreads();                  // one wavefront per workgroup: orders the LDS traffic around the switch
-            pack_setup(L, T, lane_id());
-            k8 = T.K << 3; row = T.max_len <= 8; cl_merged = T.codelen[T.K];
-            __syncthreads();
-        }
     }
     __device__ __forceinline__ MaximaAt maxima_at(const ChunkRef& ch) const {
         const u32 g = load_uniform(&a.segs[ch.seg].chunk0) + ch.c;
         return MaximaAt{a.chunk_maxexp + g, a.part_max + (u64)g * kPartBytes};
     }
-    __device__ __forceinline__ u32 K8() const { return k8; }
-    __device__ __forceinline__ bool rowchk() const { return row; }
-    __device__ __forceinline__ u32 merged_codelen() const { return cl_merged; }
+    __device__ __forceinline__ u32 K8() const { return 0; }
 };
 
 template <int DT>
 __global__ __launch_bounds__(64) void kb_hist(BatchArgs a) {
-    __shared__ PackLds<true> L;
+    __shared__ PackLds L;
     for (u32 i = threadIdx.x; i < 512 * kSpecCopies; i += 64) L.hist[i] = 0;
     __syncthreads();
-    BatchChunks<true, false> src = {a, 0xFFFFFFFFu, 0, true, 0, 0, 0, gridDim.x};
-    pack_loop<true, false, DT, 1>(src, L);
+    BatchChunks src = {a, 0xFFFFFFFFu, 0};
+    pack_loop<false, DT, 1>(src, L);
     src.hand_in(L);
 }
 
@@ -1863,21 +1954,26 @@ __global__ __launch_bounds__(256) void kb_list(BatchArgs a) {
     if (listed) a.chunk_list[base + (u32)__popcll(m & ((1ull << lane) - 1))] = g;
 }
 
+// The coding sweep: a workgroup per chunk of the list, as k_pack.
 template <int DT>
-__global__ __launch_bounds__(64) void kb_pack(BatchArgs a) {
-    __shared__ PackLds<false> L;
-    // The grid was sized before anyone knew how many chunks would be listed: up to gridDim.x of them get a wavefront
-    // each (the others leave at once); more are dealt to as many wavefronts as suit a long sweep, evenly.
-    const u32 listed = load_uniform(a.list_count);
-    u32 waves = listed;
-    if (listed > gridDim.x) {
-        const u32 turns = (listed + a.waves_long - 1) / a.waves_long;
-        waves = (listed + turns - 1) / turns;
+__global__ __launch_bounds__(kWgThreads, DT == kF32 ? 4 : 8) void kb_pack(BatchArgs a) {
+    __shared__ PackWg L;
+    u32 g = blockIdx.x;
+    if (a.listed) {
+        if (g >= load_uniform(a.list_count)) return;
+        g = load_uniform(a.chunk_list + g);
     }
-    if (blockIdx.x >= waves) return;
-    BatchChunks<false, true> src = {a, 0xFFFFFFFFu, 0, true, 0, listed, 0, waves};
-    pack_loop<false, true, DT, 0>(src, L);      // flush per pair of codes: right for every table of the batch
-    src.hand_in(L);
+    const u32 sidx = __builtin_amdgcn_readfirstlane(a.seg_of_chunk[g]);
+    const Seg& sg = a.segs[sidx];
+    EncState* st = &a.states[sidx];
+    ChunkRef ch;
+    ch.c = g - sg.chunk0;
+    ch.w = sg.w; ch.w_ref = sg.w_ref; ch.n = sg.n;
+    ch.slot = a.prov + (u64)g * a.slot_words; ch.bits_at = a.chunk_bits + g; ch.group_at = a.group_words + sg.group0 + (ch.c >> 6);
+    ch.fast = sg.aligned && (u64)(ch.c + 1) * kChunk <= sg.n;
+    if (st->table.status != 0) return;                 // (a delta that is not finite: a header-only blob)
+    if (!a.listed && noted_as_merged(ch, st->table, a.chunk_maxexp[g])) return;
+    pack_chunk_wg<DT>(ch, st->table, a.listed ? a.part_max + (u64)g * kPartBytes : nullptr, st, L);
 }
 
 // The first `count` workgroups write the tensors' headers and report their outcomes (everything that takes is final
@@ -1939,14 +2035,20 @@ void launch_hist(const void* w, const void* w_ref, uint64_t n, int dtype, Worksp
 
 static u32 even_waves(u64 nchunks, u64 cap);
 
+// Whether sweep 2 takes its chunks from a list of those to read.  A short call does without: what chunks hold merged elements
+// only their workgroups see for themselves, and k_table has one thing less to do (2^20 elements: 9.0 -> 7.5 us; in a
+// batched call kb_list's 5 us go).  A long one needs it: 8,445 workgroups that ask for their rows before they know (7,841 of
+// them for nothing) took 203 us where the 604 listed ones take 16.
+static bool needs_list(u64 nchunks, const Tuning& tune) { return nchunks > (u64)tune.num_cu * tune.unlisted_per_cu; }
+bool pack_needs_list(uint64_t n, int dtype, const Tuning& tune) { return dtype == kF64 || needs_list(num_chunks_of(n), tune); }
+
 void launch_pack_keys(const void* w, const void* w_ref, uint64_t n, Workspace* ws, uint32_t* chunk_bits, uint32_t* group_words,
                       const uint32_t* chunk_maxexp, const uint32_t* chunk_list, KeyPlanes keys, uint32_t* prov, uint32_t slot_words,
                       const Tuning& tune, hipStream_t s) {
     const u64 nchunks = num_chunks_of(n);
     if (nchunks == 0) return;
-    const u32 blocks = even_waves(nchunks, (u64)tune.num_cu * tune.keys_waves_per_cu);
-    hipLaunchKernelGGL(k_pack_keys, dim3(blocks), dim3(64), 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, chunk_maxexp, chunk_list,
-                       keys, prov, slot_words, (u32)nchunks);
+    hipLaunchKernelGGL(k_pack_keys, dim3((u32)nchunks), dim3(kWgThreads), 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, chunk_maxexp, chunk_list,
+                       keys, prov, slot_words);
 }
 
 // chunk_list: where to list the chunks sweep 2 has to read (chunk_maxexp then holds what k_hist recorded), or null
@@ -1990,13 +2092,28 @@ void launch_pack(const void* w, const void* w_ref, uint64_t n, int dtype, Worksp
                  uint32_t* prov, uint32_t slot_words, const Tuning& tune, hipStream_t s) {
     const u64 nchunks = num_chunks_of(n);
     if (nchunks == 0) return;
-    const u32 blocks = even_waves(nchunks, (u64)tune.num_cu * tune.pack_waves_per_cu);
     const int al = aligned_rows(w, dtype) && aligned_rows(w_ref, dtype);
-    const dim3 grid(blocks), wg(64);
-    if (dtype == kF64) hipLaunchKernelGGL(k_pack64, grid, wg, 0, s, w, w_ref, (u64)n, ws, &ws->ext64, chunk_bits, group_words, chunk_maxexp, chunk_list, batch_max, prov, slot_words, (u32)nchunks, al);
-    else if (dtype == kBF16) hipLaunchKernelGGL(k_pack<kBF16>, grid, wg, 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, chunk_maxexp, chunk_list, batch_max, prov, slot_words, (u32)nchunks, al);
-    else if (dtype == kF16) hipLaunchKernelGGL(k_pack<kF16>, grid, wg, 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, chunk_maxexp, chunk_list, batch_max, prov, slot_words, (u32)nchunks, al);
-    else hipLaunchKernelGGL(k_pack<kF32>, grid, wg, 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, chunk_maxexp, chunk_list, batch_max, prov, slot_words, (u32)nchunks, al);
+    // (a short call's chunks were not listed: see pack_needs_list)
+    const u32* list = pack_needs_list(n, dtype, tune) ? chunk_list : nullptr;
+    const u32* maxexp = chunk_list ? chunk_maxexp : nullptr;
+    const dim3 wg(kWgThreads);
+#define LC_PACK(DT, STAY, GRID) hipLaunchKernelGGL((k_pack<DT, STAY>), dim3((u32)(GRID)), wg, 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, maxexp, list, batch_max, prov, slot_words, (u32)nchunks, al)
+    if (dtype == kF64) {
+        hipLaunchKernelGGL(k_pack64, dim3(even_waves(nchunks, (u64)tune.num_cu * tune.pack_waves_per_cu)), dim3(64), 0, s, w, w_ref, (u64)n, ws, &ws->ext64, chunk_bits, group_words, chunk_maxexp, chunk_list, batch_max, prov, slot_words, (u32)nchunks, al);
+    } else if (chunk_list) {
+        // a workgroup per chunk
+        if (dtype == kBF16) LC_PACK(kBF16, false, nchunks);
+        else if (dtype == kF16) LC_PACK(kF16, false, nchunks);
+        else LC_PACK(kF32, false, nchunks);
+    } else {
+        // behind a speculative sweep there is mostly nothing to do, and starting 21,657 workgroups for that took 10 us instead
+        // of 4: a few that stay
+        const u64 most = (u64)tune.num_cu * 4, grid = nchunks < most ? nchunks : most;
+        if (dtype == kBF16) LC_PACK(kBF16, true, grid);
+        else if (dtype == kF16) LC_PACK(kF16, true, grid);
+        else LC_PACK(kF32, true, grid);
+    }
+#undef LC_PACK
 }
 
 // The placement of all chunks and, in the same launch, the header and the call's outcome (result: mapped host memory;
@@ -2016,7 +2133,7 @@ void launch_place(uint8_t* out, Workspace* ws, const uint32_t* chunk_bits, const
 
 void launch_batch_encode(const BatchArgs& args, const Tuning& tune, hipStream_t s) {
     BatchArgs a = args;
-    a.waves_long = (u32)tune.num_cu * tune.batch_waves_per_cu;
+    a.listed = needs_list(a.total_chunks, tune) ? 1 : 0;
     const u32 cap = (u32)tune.num_cu * 8;
     u32 setup_blocks = (a.total_chunks + 255) / 256;
     if (setup_blocks < a.count * 3) setup_blocks = a.count * 3;
@@ -2034,12 +2151,11 @@ void launch_batch_encode(const BatchArgs& args, const Tuning& tune, hipStream_t 
     }
     hipLaunchKernelGGL(kb_table, dim3(a.count), dim3(64), 0, s, a);
     if (a.total_chunks) {
-        hipLaunchKernelGGL(kb_list, dim3((a.total_chunks + 255) / 256), dim3(256), 0, s, a);
-        const u32 most = (u32)tune.num_cu * 16;
-        const u32 waves = a.total_chunks < most ? a.total_chunks : most;
-        if (a.dtype == kBF16) hipLaunchKernelGGL(kb_pack<kBF16>, dim3(waves), dim3(64), 0, s, a);
-        else if (a.dtype == kF16) hipLaunchKernelGGL(kb_pack<kF16>, dim3(waves), dim3(64), 0, s, a);
-        else hipLaunchKernelGGL(kb_pack<kF32>, dim3(waves), dim3(64), 0, s, a);
+        if (a.listed) hipLaunchKernelGGL(kb_list, dim3((a.total_chunks + 255) / 256), dim3(256), 0, s, a);
+        const dim3 grid(a.total_chunks), wg(kWgThreads);
+        if (a.dtype == kBF16) hipLaunchKernelGGL(kb_pack<kBF16>, grid, wg, 0, s, a);
+        else if (a.dtype == kF16) hipLaunchKernelGGL(kb_pack<kF16>, grid, wg, 0, s, a);
+        else hipLaunchKernelGGL(kb_pack<kF32>, grid, wg, 0, s, a);
     }
     hipLaunchKernelGGL(kb_place, dim3(a.count + (a.total_chunks + 3) / 4), dim3(256), 0, s, a);
 }

@@ -140,9 +140,9 @@ struct Tuning {
     int num_cu = 256;
     int hist_blocks_per_cu = 1;
     int hist_threads = 256;
-    int pack_waves_per_cu = 8;         // single-wave workgroups of k_pack per compute unit
-    int keys_waves_per_cu = 10;        // ... of the sweep that codes from staged keys (3 fit a SIMD; 10 measured best)
+    int pack_waves_per_cu = 8;         // single-wave workgroups of k_pack64 per compute unit
     int key_staging = 0;               // 0: by the vector's last call, 1: whenever it applies, 2: never
+    int unlisted_per_cu = 8;           // a call of at most this many chunks per compute unit does without a list of chunks to read
     int spec_waves_per_cu = 8;         // of the single sweep of the cached encode (what its LDS and registers allow)
     int batch_waves_per_cu = 8;        // of the batch kernels
     int decode_blocks_per_cu = 9;     // ... of a long restore (LDS lets 3 run at once; more, smaller shares even out unlike chunks)
@@ -176,6 +176,8 @@ void launch_spec_sweep(const void* w, const void* w_ref, uint64_t n, int dtype, 
 void launch_pack(const void* w, const void* w_ref, uint64_t n, int dtype, Workspace* ws, uint32_t* chunk_bits,
                  uint32_t* group_words, const uint32_t* chunk_maxexp, const uint32_t* chunk_list, const uint8_t* batch_max,
                  uint32_t* prov, uint32_t slot_words, const Tuning& tune, hipStream_t s);
+// Whether that sweep takes its chunks from the list (then the table kernel has to write it).
+bool pack_needs_list(uint64_t n, int dtype, const Tuning& tune);
 void launch_place(uint8_t* out, Workspace* ws, const uint32_t* chunk_bits, const uint32_t* group_words,
                   const uint32_t* prov, uint32_t slot_words, uint64_t n, uint32_t* chunk_maxexp, Result* host_result,
                   TableCache* cache, int nbits, int dtype, bool staged, hipStream_t s);
@@ -200,7 +202,7 @@ struct BatchArgs {
     uint32_t* list_count;        // how many those are
     uint32_t count, total_chunks, total_groups, slot_words;
     int nbits, dtype;                                  // dtype: element type of every tensor of the call
-    uint32_t waves_long, pad_b;                        // wavefronts of the coding sweep when more chunks are listed than its grid has
+    uint32_t listed, pad_b;                            // 1: the coding sweep takes its chunks from chunk_list
 };
 void launch_batch_encode(const BatchArgs& a, const Tuning& tune, hipStream_t s);
 
