@@ -354,6 +354,8 @@ __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 fi
         }
         if (!FAST || g + 1 == kR / kGroupRows)
             while (__any(q < end)) { one(end); br.refill(); }
+        // (a ragged chunk: the step that finished a lane's string may have gone over into a word that no step has written)
+        if (!FAST && !VERIFY) mine[((q >> 5) & (kRingWords - 1)) * kW] = acc;
     };
     auto row_at = [&](u32 r) { return base + (u64)r * kRowElems + lane * kV; };
     // the 4 symbols of row k of group g, as the low 16 bits
