@@ -756,7 +756,7 @@ lc_ssize lc_decode_batch_t(const void* const* blobs, void* const* w_ref, const u
     a.chunk_info = reinterpret_cast<uint32_t*>(base);
     a.results = g_batch_dev->results;
     a.count = (uint32_t)count; a.total_chunks = chunks; a.dtype = dtype; a.pad = 0;
-    LC_HIP(hipMemcpyAsync(a.segs, g_batch->dsegs, (size_t)count * sizeof(SegD), hipMemcpyHostToDevice, s));
+    a.host_segs = g_batch_dev->dsegs;
     launch_batch_decode(a, ds->tune, s);
     LC_HIP(hipGetLastError());
     if (!release(area, s)) return -LC_ERR_HIP;
@@ -849,7 +849,7 @@ lc_ssize lc_encode_batch_t(const void* const* w, const void* const* w_ref, const
     a.results = g_batch_dev->results;
     a.count = (uint32_t)count; a.total_chunks = chunks; a.total_groups = groups;
     a.slot_words = slot_words_of(nbits); a.nbits = nbits; a.dtype = dtype;
-    LC_HIP(hipMemcpyAsync(a.segs, g_batch->segs, (size_t)count * sizeof(Seg), hipMemcpyHostToDevice, s));
+    a.host_segs = g_batch_dev->segs;
     launch_batch_encode(a, ds->tune, s);
     LC_HIP(hipGetLastError());
     if (!release(area, s)) return -LC_ERR_HIP;

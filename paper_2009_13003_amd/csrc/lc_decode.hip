@@ -3,7 +3,7 @@
 //
 // lc_decode:        k_dec_check -> k_decode (gated on the check's verdict, no host round trip between)
 // lc_decode_many:   k_dec_check (all blobs) -> k_decode_fused<T> per sweep
-// lc_decode_batch:  kb_dec_setup -> kb_dec_tables -> kb_dec_chunks -> kb_decode -> kb_dec_report
+// lc_decode_batch:  kb_dec_tables -> kb_dec_chunks -> kb_decode
 #include "lc_device.h"
 #include <type_traits>
 
@@ -653,32 +653,24 @@ __global__ __launch_bounds__(256, DT == kF64 ? 2 : 3) void k_decode(const uint8_
 }
 
 // ----------------------------------------------------------------------------- batched decode
-// lc_decode_batch: the blobs of many tensors restored in five launches.  Every blob is validated as
+// lc_decode_batch: the blobs of many tensors restored in three launches (five and a copy before: 161 tensors 90 -> 83 us).  Every blob is validated as
 // lc_decode validates it (header and symbol table per tensor, then every chunk's place in its offset
 // table) before the sweep; a tensor whose blob fails is left untouched and reported, the others are
 // restored.  The sweep deals the chunks of all tensors round-robin to single-wavefront workgroups,
 // which reload their look-up tables when they move on to another tensor's chunk.
-__global__ __launch_bounds__(256) void kb_dec_setup(BatchDecArgs a) {
-    const u32 i = blockIdx.x * blockDim.x + threadIdx.x, nthr = gridDim.x * blockDim.x;
-    for (u32 g = i; g < a.total_chunks; g += nthr) {
-        u32 lo = 0, hi = a.count - 1;
-        while (lo < hi) {
-            const u32 mid = (lo + hi + 1) >> 1;
-            if (a.segs[mid].chunk0 <= g) lo = mid; else hi = mid - 1;
-        }
-        while (lo > 0 && (a.segs[lo].nchunks == 0 || g >= a.segs[lo].chunk0 + a.segs[lo].nchunks)) --lo;
-        a.seg_of_chunk[g] = lo;
-    }
-    for (u32 t = i; t < a.count; t += nthr) a.seg_status[t] = 0;
-}
-
-// One workgroup per tensor: header, symbol table, codes, look-up tables.
+// One workgroup per tensor: what the host says about it (read from mapped host memory, kept for the kernels behind this one: a
+// copy of the list to the device ahead of the call took longer than that read), which chunks are its own, header, symbol
+// table, codes, look-up table, and its outcome so far, for the host as well.
 __global__ __launch_bounds__(256) void kb_dec_tables(BatchDecArgs a) {
     __shared__ u32 hdr[kHeaderBytes / 4];
     __shared__ u32 s_ok;
     __shared__ DecBuild B;
     const u32 t = threadIdx.x, sidx = blockIdx.x;
-    const SegD& sg = a.segs[sidx];
+    __shared__ SegD sg;
+    if (t < sizeof(SegD) / 4) reinterpret_cast<u32*>(&sg)[t] = reinterpret_cast<const u32*>(a.host_segs + sidx)[t];
+    __syncthreads();
+    if (t < sizeof(SegD) / 4) reinterpret_cast<u32*>(a.segs + sidx)[t] = reinterpret_cast<const u32*>(&sg)[t];
+    for (u32 c = t; c < sg.nchunks; c += 256) a.seg_of_chunk[sg.chunk0 + c] = sidx;
     DecSet& D = a.sets[sidx];
     if (t < kHeaderBytes / 4) hdr[t] = reinterpret_cast<const u32*>(sg.blob)[t];
     __syncthreads();
@@ -695,7 +687,9 @@ __global__ __launch_bounds__(256) void kb_dec_tables(BatchDecArgs a) {
         if (!head_ok) status = (sound && (hn != sg.n || hdr[15] != (u32)a.dtype)) ? 1u : 4u;
         else if (!dec_symbol_table(hdr, sg.n, sg.nchunks, area, (total - area) / 4, D, B)) { ok = false; status = 4u; }
         if (t == 0) {
-            if (!ok) { atomicMax(&a.seg_status[sidx], status); D.info.area = 0; D.info.total_words = 0; D.info.max_len = 0; D.info.K = 0; }
+            if (!ok) { D.info.area = 0; D.info.total_words = 0; D.info.max_len = 0; D.info.K = 0; }
+            a.seg_status[sidx] = status;
+            a.results[sidx].bytes = ok ? total : 0; a.results[sidx].status = status; a.results[sidx].used_cache = 0;
             D.info.pad[0] = ok ? 1u : 0u;                    // the chunk checks and the sweep look here first
             D.info.pad[1] = 0;
             s_ok = ok;
@@ -703,6 +697,12 @@ __global__ __launch_bounds__(256) void kb_dec_tables(BatchDecArgs a) {
     }
     __syncthreads();
     if (s_ok) dec_build_luts(D, B, hdr[5], t);
+}
+
+// A finding in a tensor's chunks: gates its sweep, and tells the host (any finding will do).
+__device__ __forceinline__ void batch_raise(const BatchDecArgs& a, u32 sidx, u32 status) {
+    atomicMax(&a.seg_status[sidx], status);
+    a.results[sidx].status = status;
 }
 
 // Also leaves, per chunk, what the sweep needs to find it: {tensor, chunk index there, the chunk's two offset-table
@@ -718,7 +718,7 @@ __global__ __launch_bounds__(256) void kb_dec_chunks(BatchDecArgs a) {
     if (I.pad[0]) {                                   // (a blob whose header failed: its tensor's status says so, the sweep skips it)
         const u32* off_tab = reinterpret_cast<const u32*>(sg.blob + kHeaderBytes);
         info.z = off_tab[c]; info.w = off_tab[c + 1];
-        if (!dec_chunk_ok(sg.blob, I.area, I.total_words, sg.nchunks, c) && lane_id() == 0) atomicMax(&a.seg_status[sidx], 4u);
+        if (!dec_chunk_ok(sg.blob, I.area, I.total_words, sg.nchunks, c) && lane_id() == 0) batch_raise(a, sidx, 4u);
     }
     if (lane_id() == 0) reinterpret_cast<uint4*>(a.chunk_info)[g] = info;
 }
@@ -754,7 +754,7 @@ __global__ __launch_bounds__(64) void kb_decode(BatchDecArgs a) {
             M = D.info.max_len; K = D.info.K; area = D.info.area;
             zero_bits = zero_chunk_bits(D.info.len[K], D.info.code[K]);
         }
-        auto raise = [&](u32 code) { atomicMax(&a.seg_status[sidx], code); };
+        auto raise = [&](u32 code) { batch_raise(a, sidx, code); };
         const u32 c = info.y, o0 = info.z, o1 = info.w;
         const bool full = (u64)(c + 1) * kChunk <= sg.n;
         QuietChunk q;
@@ -780,16 +780,6 @@ __global__ __launch_bounds__(64) void kb_decode(BatchDecArgs a) {
             decode_chunk<false, true, DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, L, pay, kPayWords, ring, K, area, raise);
         }
     }
-}
-
-__global__ __launch_bounds__(256) void kb_dec_report(BatchDecArgs a) {
-    const u32 t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= a.count) return;
-    const u32 st = a.seg_status[t];
-    const DecInfo& I = a.sets[t].info;
-    a.results[t].status = st;
-    a.results[t].bytes = st ? 0 : I.area + 4 * I.total_words;
-    a.results[t].used_cache = 0;
 }
 
 // ----------------------------------------------------------------------------- k_decode_fused
@@ -1113,11 +1103,6 @@ __global__ __launch_bounds__(64) void k_decode_fused(BlobList blobs, u32 first, 
 }
 // ----------------------------------------------------------------------------- launchers
 void launch_batch_decode(const BatchDecArgs& a, const Tuning& tune, hipStream_t s) {
-    const u32 cap = (u32)tune.num_cu * 8;
-    u32 setup_blocks = (a.total_chunks + 255) / 256;
-    if (setup_blocks > cap) setup_blocks = cap;
-    if (setup_blocks < 1) setup_blocks = 1;
-    hipLaunchKernelGGL(kb_dec_setup, dim3(setup_blocks), dim3(256), 0, s, a);
     hipLaunchKernelGGL(kb_dec_tables, dim3(a.count), dim3(256), 0, s, a);
     if (a.total_chunks) {
         hipLaunchKernelGGL(kb_dec_chunks, dim3((a.total_chunks + 3) / 4), dim3(256), 0, s, a);
@@ -1131,7 +1116,6 @@ void launch_batch_decode(const BatchDecArgs& a, const Tuning& tune, hipStream_t 
         else if (a.dtype == kF16) hipLaunchKernelGGL(kb_decode<kF16>, dim3(waves), dim3(64), 0, s, a);
         else hipLaunchKernelGGL(kb_decode<kF32>, dim3(waves), dim3(64), 0, s, a);
     }
-    hipLaunchKernelGGL(kb_dec_report, dim3((a.count + 255) / 256), dim3(256), 0, s, a);
 }
 
 void launch_dec_check(const BlobList& blobs, int first, int count, uint64_t n, int dtype, uint64_t max_total, Workspace* ws,

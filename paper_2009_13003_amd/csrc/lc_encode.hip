@@ -1830,32 +1830,24 @@ __global__ __launch_bounds__(256) void k_place(uint8_t* out, Workspace* ws, cons
 // through; the sweeps deal those dense chunks round-robin to their wavefronts exactly as for one vector,
 // and a wavefront that moves on to a chunk of another tensor first hands in what it gathered for the last
 // one (bucket counts, extremes) and loads the new tensor's table.
+// One workgroup per tensor: what the host says about it (read from mapped host memory, kept for the kernels behind this one: a
+// copy of the list to the device ahead of the call took longer than that read: 161 tensors 129 -> 125 us), which chunks are
+// its own, its groups and its state cleared.
 __global__ __launch_bounds__(256) void kb_setup(BatchArgs a) {
-    const u32 i = blockIdx.x * blockDim.x + threadIdx.x, nthr = gridDim.x * blockDim.x;
-    for (u32 g = i; g < a.total_chunks; g += nthr) {          // tensor of dense chunk g: last one starting at or before it
-        u32 lo = 0, hi = a.count - 1;
-        while (lo < hi) {
-            const u32 mid = (lo + hi + 1) >> 1;
-            if (a.segs[mid].chunk0 <= g) lo = mid; else hi = mid - 1;
-        }
-        // tensors without chunks share their successor's chunk0: step to the one that owns g
-        while (lo > 0 && (a.segs[lo].nchunks == 0 || g >= a.segs[lo].chunk0 + a.segs[lo].nchunks)) --lo;
-        a.seg_of_chunk[g] = lo;
-    }
-    for (u32 g = i; g < a.total_groups; g += nthr) a.group_words[g] = 0;
-    if (i == 0) *a.list_count = 0;
+    __shared__ Seg sg;
+    const u32 t = threadIdx.x, sidx = blockIdx.x;
+    EncState& st = a.states[sidx];
+    // (one read of it per workgroup)
+    if (t < sizeof(Seg) / 4) reinterpret_cast<u32*>(&sg)[t] = reinterpret_cast<const u32*>(a.host_segs + sidx)[t];
     constexpr u32 kExt = kExtCopies * kMaxSym;
-    constexpr u32 per = 512 + 2 * kExt + 3;                   // words of state to set per tensor
-    for (u64 k = i; k < (u64)a.count * per; k += nthr) {
-        EncState& st = a.states[k / per];
-        const u32 j = (u32)(k % per);
-        if (j < 512) st.hist[j] = 0;
-        else if (j < 512 + kExt) (&st.mmin[0][0])[j - 512] = 0x7FFFFFu;
-        else if (j < 512 + 2 * kExt) (&st.mmax[0][0])[j - 512 - kExt] = 0;
-        else if (j == 512 + 2 * kExt) st.spec = 0;
-        else if (j == 512 + 2 * kExt + 1) st.spec_ok = 0;
-        else st.table.status = 0;
-    }
+    for (u32 i = t; i < 512; i += 256) st.hist[i] = 0;
+    for (u32 i = t; i < kExt; i += 256) { (&st.mmin[0][0])[i] = 0x7FFFFFu; (&st.mmax[0][0])[i] = 0; }
+    if (t == 0) { st.spec = 0; st.spec_ok = 0; st.table.status = 0; }
+    if (t == 0 && sidx == 0) *a.list_count = 0;
+    __syncthreads();
+    if (t < sizeof(Seg) / 4) reinterpret_cast<u32*>(a.segs + sidx)[t] = reinterpret_cast<const u32*>(&sg)[t];
+    for (u32 c = t; c < sg.nchunks; c += 256) a.seg_of_chunk[sg.chunk0 + c] = sidx;
+    for (u32 g = t; g < (sg.nchunks + 63) / 64; g += 256) a.group_words[sg.group0 + g] = 0;
 }
 
 // The dense chunks of a batched call as a chunk source for the counting loop.
@@ -2134,12 +2126,7 @@ void launch_place(uint8_t* out, Workspace* ws, const uint32_t* chunk_bits, const
 void launch_batch_encode(const BatchArgs& args, const Tuning& tune, hipStream_t s) {
     BatchArgs a = args;
     a.listed = needs_list(a.total_chunks, tune) ? 1 : 0;
-    const u32 cap = (u32)tune.num_cu * 8;
-    u32 setup_blocks = (a.total_chunks + 255) / 256;
-    if (setup_blocks < a.count * 3) setup_blocks = a.count * 3;
-    if (setup_blocks > cap) setup_blocks = cap;
-    if (setup_blocks < 1) setup_blocks = 1;
-    hipLaunchKernelGGL(kb_setup, dim3(setup_blocks), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(kb_setup, dim3(a.count), dim3(256), 0, s, a);
     if (a.total_chunks) {
         // (a counting workgroup needs 19 KB of LDS: 8 fit a compute unit, and a grid of more leaves the last ones a
         // round of their own: 0.20 ms instead of 0.18 on VGG-16's 32 tensors)

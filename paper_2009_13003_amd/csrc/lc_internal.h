@@ -194,6 +194,7 @@ constexpr uint32_t kPartBytes = 16;
 // 32 parts of 8-byte elements
 constexpr uint32_t kPartMaxBytes = 64;
 struct BatchArgs {
+    const Seg* host_segs;                              // mapped host memory: what the call was given
     Seg* segs; EncState* states; Result* results;     // device (results: mapped host memory)
     uint32_t* seg_of_chunk; uint32_t* group_words; uint32_t* chunk_bits; uint32_t* prov;
     uint32_t* chunk_maxexp;      // largest |delta| exponent of every chunk (chunks of all tensors numbered through), from the counting sweep
@@ -213,6 +214,7 @@ struct SegD {
     uint32_t nchunks, chunk0, aligned, pad;
 };
 struct BatchDecArgs {
+    const SegD* host_segs;                             // mapped host memory: what the call was given
     SegD* segs; DecSet* sets; Result* results;         // device (results: mapped host memory)
     uint32_t* seg_of_chunk; uint32_t* seg_status;      // seg_status: lc_status per tensor, raised with atomicMax
     uint32_t* chunk_info;                              // per chunk {tensor, chunk index there, its two offset-table entries}, 16 bytes
