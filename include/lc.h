@@ -306,7 +306,7 @@ lc_ssize lc_decode_many_t(const void* const* blobs, int count, void* w_ref, uint
  * Many vectors in one call, each with a table of its own: tensor t is coded exactly as
  * lc_encode(w[t], w_ref[t], n[t], nbits, out[t]) would (the paper quantizes layer by layer: Figure 2,
  * Section 4.3; per-tensor tables keep small-scale tensors from being merged away by large-scale ones),
- * but the whole list takes six kernel launches instead of four per tensor.
+ * but the whole list takes five or six kernel launches instead of four per tensor.
  *   w, w_ref, out  HOST arrays of `count` DEVICE pointers (out[t]: 16-byte aligned, at least
  *                  lc_encode_bound(n[t], nbits) bytes); n: HOST array of lengths; 1 <= count <= LC_MAX_BATCH
  *   sizes          HOST array or NULL: blob size of each tensor, or -(lc_status) for a tensor whose delta
@@ -325,7 +325,7 @@ lc_ssize lc_encode_batch_t(const void* const* w, const void* const* w_ref, const
 
 /*
  * The restore of such a list: tensor t as lc_decode(blobs[t], w_ref[t], n[t]) (Algorithm 1 line 7), all tensors
- * in five launches.  Every blob is validated like lc_decode's before the sweep; a tensor whose blob fails is
+ * in three launches.  Every blob is validated like lc_decode's before the sweep; a tensor whose blob fails is
  * left untouched (its size comes back as -(lc_status)) while the others are restored.  Arrays as in
  * lc_encode_batch (blobs[t]: DEVICE pointer, 16-byte aligned; fp32 blobs only).  Returns the sum of the bytes
  * consumed, or -(lc_status) of the first failing tensor.
