@@ -1445,8 +1445,8 @@ __device__ __forceinline__ void pack_chunk64(const ChunkRef& ch, PackLds64& L, u
     finish_lane_sizes(ch, nb, nw);
 }
 
-// A chunk of which at most a quarter of the 4 KiB parts (2 rows of doubles each) hold anything but merged elements:
-// see pack_chunk_parts.
+// A chunk of which at most a quarter of the 4 KiB parts (2 rows of doubles each; bit p of `parts` set: part p has to be read)
+// hold anything but merged elements: only those are fetched, and the merged code stands for every element of the others.
 __device__ __noinline__ void pack_chunk64_parts(const ChunkRef ch, u32 cl_merged, PackLds64& L, u32 K) {
     constexpr u32 kRowsPerPart = 2, kParts = kR / kRowsPerPart;
     const u32 lane = lane_id();
