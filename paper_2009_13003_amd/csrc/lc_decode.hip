@@ -579,7 +579,8 @@ __global__ __launch_bounds__(256, DT == kF64 ? 2 : 3) void k_decode(const uint8_
     __shared__ u32 s_ring[VERIFY ? 1 : 4 * kRingWords * kW];
     extern __shared__ uint4 dec_pay[];                   // 4 areas of pay_words + 4 payload words, one per wavefront
     // What the check kernel left (the verdict and the blob's tables) is fetched in one go: a failed check leaves
-    // tables that mean nothing, but reading them is harmless.  If it found something, nothing else is touched.
+    // tables that mean nothing, but reading them is harmless.  The blob itself is not: one that was refused may end
+    // anywhere behind its header, so no load from it stands ahead of the verdict (nchunks comes from the caller's n).
     const u32 t = threadIdx.x;
     const DecSet& D = ws->dec_set[set];
     const u64 verdict = __hip_atomic_load(&ws->dec_status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -588,21 +589,21 @@ __global__ __launch_bounds__(256, DT == kF64 ? 2 : 3) void k_decode(const uint8_
     const u32 lane = t & (kW - 1);
     u32 sym_rep = 0, sym_rep_hi = 0, sym_len = 0, sym_code = 0;
     if (lane < kMaxSym) { sym_rep = D.info.rep_bits[lane]; sym_rep_hi = D.info.rep_hi[lane]; sym_len = D.info.len[lane]; sym_code = D.info.code[lane]; }
-    const u32* off_tab = reinterpret_cast<const u32*>(blob + kHeaderBytes);
     const u32 wave = t >> 6, stride = gridDim.x * 4;
     const u32 first = blockIdx.x * 4 + wave;
+    // (the empty statement keeps these loads ahead of the branch; the values every lane holds alike go back to scalars)
+    asm volatile("" : "+v"(M), "+v"(K), "+v"(area), "+v"(sym_rep), "+v"(sym_rep_hi), "+v"(sym_len), "+v"(sym_code));
+    M = __builtin_amdgcn_readfirstlane(M); K = __builtin_amdgcn_readfirstlane(K);
+    area = ((u64)__builtin_amdgcn_readfirstlane((u32)(area >> 32)) << 32) | __builtin_amdgcn_readfirstlane((u32)area);
+    if ((verdict >> 8) == epoch || first >= nchunks) return;
     // the offset-table entries of this wavefront's next 64 chunks, one chunk per lane
+    const u32* off_tab = reinterpret_cast<const u32*>(blob + kHeaderBytes);
     u32 off0 = 0, off1 = 0;
     auto fetch_offsets = [&](u64 from) {
         const u64 c = from + (u64)lane * stride;
         if (c < nchunks) { off0 = off_tab[c]; off1 = off_tab[c + 1]; }
     };
     fetch_offsets(first);
-    // (the empty statement keeps these loads ahead of the branch; the values every lane holds alike go back to scalars)
-    asm volatile("" : "+v"(M), "+v"(K), "+v"(area), "+v"(sym_rep), "+v"(sym_rep_hi), "+v"(sym_len), "+v"(sym_code), "+v"(off0), "+v"(off1));
-    M = __builtin_amdgcn_readfirstlane(M); K = __builtin_amdgcn_readfirstlane(K);
-    area = ((u64)__builtin_amdgcn_readfirstlane((u32)(area >> 32)) << 32) | __builtin_amdgcn_readfirstlane((u32)area);
-    if ((verdict >> 8) == epoch || first >= nchunks) return;
     uint4* pay = dec_pay + wave * (pay_words / 4 + 1);
     u32* ring = VERIFY ? s_ring : s_ring + wave * kRingWords * kW;
     const u32 zero_bits = zero_chunk_bits(read_lane(sym_len, K), read_lane(sym_code, K));
