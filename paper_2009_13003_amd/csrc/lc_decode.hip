@@ -246,6 +246,11 @@ struct DecLds {
     alignas(16) u32 multi[1u << kMultiBits];
     float rep[kMaxSym];
     u32 len[kMaxSym], code[kMaxSym];
+    // the codes of more than 10 bits: symbol | len << 4 at [the next 15 bits - long_base].  They are the last codes in
+    // canonical order, so the windows that start with one are the top of the 15-bit range; the code being complete, each
+    // 10-bit prefix among those holds at least two of the 16 symbols, so there are at most 8 such prefixes
+    alignas(4) uint8_t longs[8u << (15 - kMultiBits)];
+    u32 long_base;
     double rep64[kMaxSym];            // binary64 blobs: the representatives (rep is not used then)
     template <int DT> __device__ __forceinline__ typename Val<DT>::type rep_of(u32 sy) const {
         if constexpr (DT == kF64) return rep64[sy];
@@ -255,14 +260,26 @@ struct DecLds {
 
 // the one symbol of a window whose first code is longer than the table's 10 bits, as an entry of the table
 template <typename LDS>
-__device__ __forceinline__ u32 decode_long(const LDS& L, u64 win, u32 K) {
-    const u32 peek = (u32)(win >> (64 - 15));
-#pragma unroll 1
-    for (u32 j = 0; j <= K; ++j) {
-        const u32 l = L.len[j];
-        if (l > kMultiBits && (peek >> (15 - l)) == L.code[j]) return j | (l << 24) | (1u << 28);
+__device__ __forceinline__ u32 decode_long(const LDS& L, u64 win) {
+    const u32 e = L.longs[((u32)(win >> (64 - 15)) - L.long_base) & (sizeof(L.longs) - 1)];
+    return (e & 15u) | ((e >> 4) << 24) | (1u << 28);
+}
+
+// That table, by one wavefront, lane j holding the length and code of symbol j (0 in lanes without one): 4 entries per lane.
+// (A search through the symbols instead, a dependent look-up each, was most of a restore's time where such codes are
+// many: 2^24 fp32 elements of 10 layers at 4 bits 193 us, 71 with the table.)
+template <typename LDS>
+__device__ __forceinline__ void build_longs(LDS& L, u32 len, u32 code) {
+    const u32 base = 0x8000u - wave_max_u32(len > kMultiBits ? 0x8000u - (code << (15 - len)) : 0u);
+    static_assert(sizeof(L.longs) == 4 * kW, "four entries per lane");
+    u32 e[4] = {0, 0, 0, 0};                       // (nothing decodes to these: the windows past the last code do not exist)
+    for (u64 m = __ballot(len > kMultiBits); m != 0; m &= m - 1) {
+        const u32 j = (u32)__builtin_ctzll(m), lj = read_lane(len, j), cj = read_lane(code, j);
+#pragma unroll
+        for (u32 k = 0; k < 4; ++k) if (((base + 4 * lane_id() + k) >> (15 - lj)) == cj) e[k] = j | (lj << 4);
     }
-    return K | (1u << 28);
+    reinterpret_cast<u32*>(L.longs)[lane_id()] = e[0] | (e[1] << 8) | (e[2] << 16) | (e[3] << 24);
+    if (lane_id() == 0) L.long_base = base;
 }
 
 // MSB-first bit window over payload words that live in LDS (STAGED) or in global memory.
@@ -331,13 +348,13 @@ __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 fi
     // two if one of them may be a code of up to 15 bits)
     auto step = [&](int cap) {
         u32 e = L.multi[(u32)(br.win >> (64 - kMultiBits))];
-        if (LONG && __any(q < cap && e == 0)) { if (e == 0) e = decode_long(L, br.win, K); }
+        if (LONG && __any(q < cap && e == 0)) { if (e == 0) e = decode_long(L, br.win); }
         append(q < cap ? e : 0u);
     };
     // the next code alone, by the lanes that have not come to `end`
     auto one = [&](int end) {
         u32 e = L.multi[(u32)(br.win >> (64 - kMultiBits))];
-        if (LONG && __any(e == 0)) { if (e == 0) e = decode_long(L, br.win, K); }
+        if (LONG && __any(e == 0)) { if (e == 0) e = decode_long(L, br.win); }
         const u32 sy = e & 15u, len = (e & 0x0F000000u) ? L.len[sy] : 0u;       // (length 0: a prefix that starts no code)
         append(q < end ? (sy | (len << 24) | (1u << 28)) : 0u);
     };
@@ -427,7 +444,7 @@ __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 fi
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         u32 e = L.multi[(u32)(br.win >> (64 - kMultiBits))];
-                        if (LONG && __any(e == 0)) { if (e == 0) e = decode_long(L, br.win, K); }
+                        if (LONG && __any(e == 0)) { if (e == 0) e = decode_long(L, br.win); }
                         const u32 sy = e & 15u;
                         syms[k] |= sy << (4 * v);
                         br.drop((e & 0x0F000000u) ? L.len[sy] : 0u);
@@ -639,6 +656,7 @@ __global__ __launch_bounds__(256, DT == kF64 ? 2 : 3) void k_decode(const uint8_
                     L.rep64[lane] = lane < K ? __hiloint2double((int)sym_rep_hi, (int)sym_rep) : -0.0;
                     L.len[lane] = sym_len; L.code[lane] = sym_code;
                 }
+                build_longs(L, sym_len, sym_code);
                 __builtin_amdgcn_wave_barrier();
             }
             if (full && aligned) {
@@ -772,6 +790,7 @@ __global__ __launch_bounds__(64) void kb_decode(BatchDecArgs a) {
 #pragma unroll
             for (u32 k = 0; k < (1u << kMultiBits) / 4 / kW; ++k) reinterpret_cast<u32x4*>(L.multi)[lane + k * kW] = e[k];
             if (lane < kMaxSym) { L.rep[lane] = __uint_as_float(lane < K ? rep : 0x80000000u); L.len[lane] = len; L.code[lane] = code; }
+            build_longs(L, len, code);
             __builtin_amdgcn_wave_barrier();
         }
         if (full && sg.aligned) {

@@ -1,0 +1,77 @@
+"""Inputs that take a kernel off its usual path, against inputs of the same size that do not: the ratio of the two times on one
+box, the fastest of many calls each, so that neither the box nor a neighbour matters.  The bounds lie midway between what the
+paths measured when they were slow and what they measure now; outputs are compared with the oracle's."""
+import time
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import lc_oracle as orc
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def lc():
+    from paper_2009_13003_amd import lc as mod
+    return mod
+
+
+def best_us(call, reps=60):
+    for _ in range(10):
+        call()
+    best = 1e9
+    for _ in range(reps):
+        torch.cuda.synchronize()
+        t0 = time.perf_counter()
+        call()
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t0)
+    return 1e6 * best
+
+
+def in_binades(e, seed, dtype=torch.float32):
+    """A vector with |w| in the binade 2^(e - 30) where e > 0, 0 elsewhere, against zeros."""
+    g = torch.Generator(device=DEV); g.manual_seed(seed)
+    d = torch.exp2(e - 30) * (1 + 0.5 * torch.rand(e.numel(), generator=g, device=DEV))
+    w = torch.where(e > 0, d, torch.zeros_like(e)).to(dtype)
+    return w, torch.zeros_like(w)
+
+
+def blob_of(lc, w, ref, nbits):
+    out = lc.alloc_out(w.numel(), nbits, DEV)
+    return out[:lc.lc_encode_t(w, ref, nbits, out)].clone()
+
+
+def code_lengths(blob):
+    h = blob[:512].cpu().numpy()
+    return h[66:66 + 16 * (int(h[20]) + 1):16].tolist()
+
+
+def restored_as_the_oracle(lc, blob, n):
+    want, got = np.zeros(n, np.float32), torch.zeros(n, device=DEV)
+    orc.decode(blob.cpu().numpy(), want)
+    lc.lc_decode(blob, got)
+    return np.array_equal(got.cpu().numpy().view(np.uint32), want.view(np.uint32))
+
+
+def test_codes_longer_than_the_look_up(lc):
+    """The first chunk holds 8 rare symbols in 0.4 of its places, the others none of them: their codes have 11 bits behind 2^21
+    elements and 9 behind 2^18.  The restore takes as long as that chunk's wavefront, so the two differ by the second
+    look-up of the longer codes alone."""
+    times = {}
+    for n, bits in ((1 << 18, 9), (1 << 21, 11)):
+        g = torch.Generator(device=DEV); g.manual_seed(n)
+        i = torch.arange(n, device=DEV)
+        k = torch.floor(-torch.log2(torch.rand(n, generator=g, device=DEV).clamp_(min=2.0 ** -20)))
+        common = torch.where((k > 0) & (k < 8), 8 - k, torch.zeros_like(k))
+        rare = torch.randint(8, 16, (n,), generator=g, device=DEV).float() * (torch.rand(n, generator=g, device=DEV) < 0.4)
+        blob = blob_of(lc, *in_binades(torch.where(i < 16384, rare, common), n), 4)
+        assert sorted(code_lengths(blob))[-8:] == [bits] * 8, code_lengths(blob)
+        assert restored_as_the_oracle(lc, blob, n)
+        rec = torch.zeros(n, device=DEV)
+        times[bits] = best_us(lambda: lc.lc_decode(blob, rec))
+    print("restore with 9-bit and 11-bit codes: %.1f us, %.1f us" % (times[9], times[11]), flush=True)
+    assert times[11] < 2.5 * times[9], times             # (5.2 with a search through the symbols, 1.5 with a table)
