@@ -237,7 +237,9 @@ __global__ __launch_bounds__(256) void k_dec_check(BlobList blobs, u32 first, u6
 // is not written back at all.
 constexpr u32 kPayWords = 2048;      // LDS room for one chunk's payload (4 bits per element on average) when the
                                      // compute unit is shared by as many workgroups as fit; more when fewer are needed
-constexpr u32 kSparseSlack = 512;    // bits above an all-merged chunk up to which a chunk is decoded symbols first
+constexpr u32 kSparseSlack = 1024;   // bits above an all-merged chunk up to which a chunk's kept symbols are restored one by one
+                                     // (512 instead: a batch of 2^24 elements at 2 bits 49 us, 40 so; 2048: the same)
+constexpr u32 kSparseLaneSlack = 64; // the same for one lane's string
 constexpr u32 kPayWordsMax = 3072;   // what keeps a workgroup's LDS within 64 KB (6 bits per element on average)
 constexpr u32 kRingWords = 8;        // words of 8 symbols that a lane may be ahead of the rows being restored
 constexpr u32 kGroupRows = 8;        // rows restored at a time: 32 symbols, 4 words of the ring per lane
@@ -245,7 +247,6 @@ constexpr u32 kGroupRows = 8;        // rows restored at a time: 32 symbols, 4 w
 struct DecLds {
     alignas(16) u32 multi[1u << kMultiBits];
     float rep[kMaxSym];
-    u32 len[kMaxSym], code[kMaxSym];
     // the codes of more than 10 bits: symbol | len << 4 at [the next 15 bits - long_base].  They are the last codes in
     // canonical order, so the windows that start with one are the top of the 15-bit range; the code being complete, each
     // 10-bit prefix among those holds at least two of the 16 symbols, so there are at most 8 such prefixes
@@ -255,6 +256,21 @@ struct DecLds {
     template <int DT> __device__ __forceinline__ typename Val<DT>::type rep_of(u32 sy) const {
         if constexpr (DT == kF64) return rep64[sy];
         else return rep[sy];
+    }
+};
+
+// What a wavefront keeps of a blob's code in registers, the same in every lane.
+struct CodeLens {
+    u64 nibbles;                      // the length of symbol j at bits 4 j
+    u32 sparse;                       // the merged symbol's length if it is below every other's, else 0
+    __device__ __forceinline__ u32 of(u32 sy) const { return (u32)(nibbles >> (4 * sy)) & 15u; }
+    // by a whole wavefront, lane j holding the length of symbol j (0 in lanes without one)
+    __device__ __forceinline__ void set(u32 len, u32 K) {
+        const u32 lane = lane_id(), mine = lane < kMaxSym ? len << (4 * (lane & 7)) : 0u;
+        const u32 lo = wave_sum32(lane < 8 ? mine : 0u), hi = wave_sum32(lane < 8 ? 0u : mine);
+        nibbles = ((u64)hi << 32) | lo;
+        const u32 merged = read_lane(len, K);
+        sparse = __any(lane < K && len != 0 && len <= merged) ? 0u : merged;
     }
 };
 
@@ -316,7 +332,7 @@ struct BitReader {
 template <bool FAST, bool LONG, bool STAGED, int DT, bool VERIFY, typename LDS, typename Raise>
 __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 first_bit, u32 lane_bits,
                                             void* __restrict__ w_ref, u64 n, u32 c,
-                                            const LDS& L, u32* ring, u32 K, bool sparse, Raise& raise) {
+                                            const LDS& L, u32* ring, u32 K, const CodeLens& lens, Raise& raise) {
     typedef typename Val<DT>::type val_t;
     const u32 lane = lane_id();
     BitReader<STAGED> br;
@@ -355,7 +371,7 @@ __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 fi
     auto one = [&](int end) {
         u32 e = L.multi[(u32)(br.win >> (64 - kMultiBits))];
         if (LONG && __any(e == 0)) { if (e == 0) e = decode_long(L, br.win); }
-        const u32 sy = e & 15u, len = (e & 0x0F000000u) ? L.len[sy] : 0u;       // (length 0: a prefix that starts no code)
+        const u32 sy = e & 15u, len = (e & 0x0F000000u) ? lens.of(sy) : 0u;       // (length 0: a prefix that starts no code)
         append(q < end ? (sy | (len << 24) | (1u << 28)) : 0u);
     };
     // the symbols of group g, complete in the ring
@@ -406,69 +422,19 @@ __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 fi
                 store4_v<DT>(w_ref, row_at(g * kGroupRows + k), x);
             }
         };
-        if (!sparse) {
-            raw_t A[kGroupRows], B[kGroupRows];
-            fetch(A, 0);
-            for (u32 g = 0; g < kR / kGroupRows; g += 2) {
-                fetch(B, g + 1);
-                symbols(g);
-                restore(A, g);
-                if (g + 2 < kR / kGroupRows) fetch(A, g + 2);
-                symbols(g + 1);
-                restore(B, g + 1);
-            }
-        } else {
-            // A chunk that holds few kept symbols (its caller has seen that from its size): the lanes stay in step, a row
-            // at a time, and where every lane's window starts with the merged symbol's code 4 times over (8 rows: 32 times)
-            // the rows are passed over without a look-up.  A row of merged symbols needs no look at w_ref either: only the
-            // rows in which some lane decoded a kept symbol are fetched (those of a group together), added to and stored.
-            const u32 zero_len = L.code[K] == 0 ? L.len[K] : 0u;
-            const u32 row_zeros = zero_len * kV <= 32 ? zero_len * kV : 0u, group_zeros = zero_len * kV * kGroupRows <= 32 ? zero_len * kV * kGroupRows : 0u;
-            for (u32 g = 0; g < kR / kGroupRows; ++g) {
-                if (group_zeros != 0 && !__any((u32)(br.win >> (64 - group_zeros)) != 0)) {
-                    br.drop(group_zeros);
-                    br.refill();
-                    continue;
-                }
-                raw_t X[kGroupRows];
-                u32 syms[kGroupRows];
-                u32 kept = 0;
-#pragma unroll
-                for (u32 k = 0; k < kGroupRows; ++k) {
-                    if (row_zeros != 0 && !__any((u32)(br.win >> (64 - row_zeros)) != 0)) {
-                        br.drop(row_zeros);
-                        br.refill();
-                        continue;
-                    }
-                    syms[k] = 0;
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        u32 e = L.multi[(u32)(br.win >> (64 - kMultiBits))];
-                        if (LONG && __any(e == 0)) { if (e == 0) e = decode_long(L, br.win); }
-                        const u32 sy = e & 15u;
-                        syms[k] |= sy << (4 * v);
-                        br.drop((e & 0x0F000000u) ? L.len[sy] : 0u);
-                        if (v & 1) br.refill();
-                    }
-                    if (!any_kept(syms[k])) continue;
-                    kept |= 1u << k;
-                    X[k] = load_raw<DT>(w_ref, row_at(g * kGroupRows + k));
-                }
-                if (kept == 0) continue;
-#pragma unroll
-                for (u32 k = 0; k < kGroupRows; ++k) {
-                    if (!((kept >> k) & 1u)) continue;
-                    val_t x[4];
-                    if constexpr (DT == kF64) unpack64(X[k], x); else unpack<DT>(X[k], x);
-                    add_row(syms[k], x);
-                    store4_v<DT>(w_ref, row_at(g * kGroupRows + k), x);
-                }
-            }
+        raw_t A[kGroupRows], B[kGroupRows];
+        fetch(A, 0);
+        for (u32 g = 0; g < kR / kGroupRows; g += 2) {
+            fetch(B, g + 1);
+            symbols(g);
+            restore(A, g);
+            if (g + 2 < kR / kGroupRows) fetch(A, g + 2);
+            symbols(g + 1);
+            restore(B, g + 1);
         }
     } else {
         // A ragged or unaligned chunk (the vector's last chunk is one wavefront's work from start to end, so its memory
-        // round trips count): rows that lie wholly inside an aligned array as vectors, the rest element by element, a
-        // group's kept rows fetched together.
+        // round trips count): rows that lie wholly inside an aligned array as vectors, the rest element by element.
         const bool vec = (reinterpret_cast<uintptr_t>(w_ref) & (DT == kF64 ? 15 : 4 * elem_bytes<DT>() - 1)) == 0;
         for (u32 g = 0; g < kR / kGroupRows && base + (u64)g * kGroupRows * kRowElems < n; ++g) {
             val_t x[kGroupRows][4];
@@ -477,15 +443,9 @@ __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 fi
                 if (vec && base + (u64)(r + 1) * kRowElems <= n) load_row_v<true, DT>(w_ref, row_at(r), n, x[k]);
                 else load_row_v<false, DT>(w_ref, row_at(r), n, x[k]);
             };
-            if (!sparse) {
 #pragma unroll
-                for (u32 k = 0; k < kGroupRows; ++k) fetch(k);           // on their way while the symbols are decoded
-            }
+            for (u32 k = 0; k < kGroupRows; ++k) fetch(k);               // on their way while the symbols are decoded
             symbols(g);
-            if (sparse) {
-#pragma unroll
-                for (u32 k = 0; k < kGroupRows; ++k) if (any_kept(row_syms(g, k))) fetch(k);
-            }
 #pragma unroll
             for (u32 k = 0; k < kGroupRows; ++k) {
                 const u32 r = g * kGroupRows + k, syms = row_syms(g, k);
@@ -504,6 +464,61 @@ __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 fi
         }
     }
     check();
+}
+
+// A chunk of few kept symbols (the caller has seen that from its size), ragged or not: a lane goes from one to the next.  Its
+// string is runs of the merged symbol's code, all zero bits and shorter than any other, which the leading zeros of the window
+// count up to 32 bits at a time; only the symbols between them are looked up.  They are noted in the lane's column of `noted`
+// (kRingWords of them) and added to their elements when some column is full, the elements of all lanes in flight together;
+// nothing else of w_ref is read or written.
+// Against the rows around the kept symbols restored, with a look-up for each of a row's symbols: 2^20 fp32 elements of one
+// scale at 2 bits 61 -> 28 us (52 when symbol and length were one look-up), 2^26 of a drift 137 -> 38 us (93), 138 M of a
+// sparse update 37 -> 29 us (40).
+template <int DT, typename LDS, typename Raise>
+__device__ __forceinline__ void decode_sparse(const u32* words, u32 nwords, u32 first_bit, u32 lane_bits, u32 lane_elems,
+                                              void* __restrict__ w_ref, u64 base, const LDS& L, u32* noted, u32 K,
+                                              const CodeLens& lens, Raise& raise) {
+    const u32 lane = lane_id();
+    BitReader<true> br;
+    br.start(words, nwords, first_bit);
+    const u32 wi0 = br.wi, avail0 = br.avail;
+    const u32 m = lens.sparse, inv = 65536u / m + 1;               // (z inv >> 16 = z / m for z <= 32, m <= 15)
+    u32* mine = noted + lane;
+    u32 pos = 0, count = 0;
+    auto add_noted = [&]() {
+        u32 e[kRingWords];
+        typename Val<DT>::type x[kRingWords];
+        auto at = [&](u32 k) { const u32 p = e[k] >> 4; return base + (u64)((p / kV) * kRowElems + lane * kV + p % kV); };
+#pragma unroll
+        for (u32 k = 0; k < kRingWords; ++k) if (k < count) { e[k] = mine[k * kW]; x[k] = load_one_v<DT>(w_ref, at(k)); }
+#pragma unroll
+        for (u32 k = 0; k < kRingWords; ++k) if (k < count) store_one_v<DT>(w_ref, at(k), add_rn(x[k], L.template rep_of<DT>(e[k] & 15u)));
+        count = 0;
+    };
+    br.refill();
+    while (__any(pos < lane_elems)) {
+        const u32 top = (u32)(br.win >> 32), zeros = top != 0 ? (u32)__builtin_clz(top) : 32u;
+        const u32 run = min(zeros * inv >> 16, lane_elems - pos);
+        pos += run;
+        br.drop(run * m);
+        br.refill();
+        const bool kept = pos < lane_elems && (u32)(br.win >> (64 - m)) != 0;
+        if (__any(kept)) {
+            u32 e = L.multi[(u32)(br.win >> (64 - kMultiBits))];
+            if (__any(kept && e == 0)) { if (e == 0) e = decode_long(L, br.win); }
+            const u32 sy = e & 15u;
+            if (kept) {
+                mine[count * kW] = (pos << 4) | sy;
+                count += sy != K ? 1u : 0u;                        // (K: a prefix that starts no code)
+                ++pos;
+                br.drop((e & 0x0F000000u) ? lens.of(sy) : 0u);
+            }
+            br.refill();
+            if (__any(count == kRingWords)) add_noted();
+        }
+    }
+    if (__any(count != 0)) add_noted();
+    if (__any(avail0 + 32 * (br.wi - wi0) - br.avail != lane_bits) && lane == 0) raise(4u);
 }
 
 // zero_bits: what every lane length of a full chunk is when all its elements are the merged symbol and that
@@ -543,10 +558,11 @@ struct QuietChunk {
 };
 
 // pay: this wavefront's LDS area of pay_words + 4 words for the chunk's payload; ring: its symbol ring
-template <bool FAST, bool LONG, int DT, bool VERIFY = false, typename LDS, typename Raise>
+// fast: a full chunk of an aligned array; long_codes: the blob has codes of more than 10 bits
+template <int DT, bool VERIFY = false, typename LDS, typename Raise>
 __device__ __forceinline__ void decode_chunk(const uint8_t* __restrict__ blob, void* __restrict__ w_ref, u64 n,
-                                             u32 c, u32 o0, u32 o1, LDS& L, uint4* pay, u32 pay_words, u32* ring, u32 K,
-                                             u64 area, Raise& raise) {
+                                             u32 c, u32 o0, u32 o1, bool fast, bool long_codes, LDS& L, uint4* pay, u32 pay_words, u32* ring, u32 K,
+                                             const CodeLens& lens, u64 area, Raise& raise) {
     // o0, o1: the chunk's entries c and c + 1 of the offset table (fetched by the caller, ahead of time)
     const u32 lane = lane_id();
     const uint8_t* rec = blob + area + 4 * (u64)o0;
@@ -573,16 +589,25 @@ __device__ __forceinline__ void decode_chunk(const uint8_t* __restrict__ blob, v
     }
     const u32 incl = wave_incl_scan(lane_bits), o = incl - lane_bits;
     // Few kept symbols?  When the merged symbol's code is shorter than every other, each kept symbol costs at least
-    // one bit more, so a chunk of at most kSparseSlack bits above (elements x merged length) holds at most that many.
-    u32 len_merged = L.len[K];
-    for (u32 j = 0; j < K; ++j) if (L.len[j] != 0 && L.len[j] <= L.len[K]) len_merged = 0;
+    // one bit more, so a chunk of at most kSparseSlack bits above (elements x merged length) holds at most that many;
+    // and no lane may hold many of them, since the fullest sets the pace.
     const u64 left = n - (u64)c * kChunk;
-    const u32 elems = left < kChunk ? (u32)left : kChunk;
-    const bool sparse = len_merged != 0 && read_lane(incl, kW - 1) <= elems * len_merged + kSparseSlack;
+    const u32 elems = left < kChunk ? (u32)left : kChunk, tail = elems % kRowElems;
+    const u32 lane_elems = elems / kRowElems * kV + (tail > lane * kV ? min(tail - lane * kV, kV) : 0u);
+    const bool sparse = !VERIFY && staged && lens.sparse != 0 && read_lane(incl, kW - 1) <= elems * lens.sparse + kSparseSlack &&
+                        !__any(lane_bits > lane_elems * lens.sparse + kSparseLaneSlack);
+    const u32* words = reinterpret_cast<const u32*>(pay) + k0;
+    if constexpr (!VERIFY) {
+        if (sparse) { decode_sparse<DT>(words, nwords, o, lane_bits, lane_elems, w_ref, (u64)c * kChunk, L, ring, K, lens, raise); return; }
+    }
     if (staged) {
-        decode_rows<FAST, LONG, true, DT, VERIFY>(reinterpret_cast<const u32*>(pay) + k0, nwords, o, lane_bits, w_ref, n, c, L, ring, K, sparse, raise);
+        if (!fast) decode_rows<false, true, true, DT, VERIFY>(words, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, raise);
+        else if (long_codes) decode_rows<true, true, true, DT, VERIFY>(words, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, raise);
+        else decode_rows<true, false, true, DT, VERIFY>(words, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, raise);
     } else {
-        decode_rows<FAST, LONG, false, DT, VERIFY>(gw, nwords, o, lane_bits, w_ref, n, c, L, ring, K, sparse, raise);
+        if (!fast) decode_rows<false, true, false, DT, VERIFY>(gw, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, raise);
+        else if (long_codes) decode_rows<true, true, false, DT, VERIFY>(gw, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, raise);
+        else decode_rows<true, false, false, DT, VERIFY>(gw, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, raise);
     }
 }
 
@@ -628,6 +653,7 @@ __global__ __launch_bounds__(256, DT == kF64 ? 2 : 3) void k_decode(const uint8_
     // A wavefront brings the tables to LDS when it comes to the first chunk that has to be decoded (in a sparse blob most
     // never do).  Each does so for itself: they all write the same values to the same places, and none waits for another.
     bool have_tables = false;
+    CodeLens lens;
     QuietChunk q;
     u32 turn = 0, c = first, o0 = read_lane(off0, 0), o1 = read_lane(off1, 0);
     q.start(blob, area, o0, o1, zero_bits, (u64)(c + 1) * kChunk <= n);
@@ -654,17 +680,12 @@ __global__ __launch_bounds__(256, DT == kF64 ? 2 : 3) void k_decode(const uint8_
                 if (lane < kMaxSym) {
                     L.rep[lane] = __uint_as_float(lane < K ? sym_rep : 0x80000000u);
                     L.rep64[lane] = lane < K ? __hiloint2double((int)sym_rep_hi, (int)sym_rep) : -0.0;
-                    L.len[lane] = sym_len; L.code[lane] = sym_code;
                 }
-                build_longs(L, sym_len, sym_code);
+                if (M > kMultiBits) build_longs(L, sym_len, sym_code);
+                lens.set(sym_len, K);
                 __builtin_amdgcn_wave_barrier();
             }
-            if (full && aligned) {
-                if (M > kMultiBits) decode_chunk<true, true, DT, VERIFY>(blob, w_ref, n, c, o0, o1, L, pay, pay_words, ring, K, area, raise);
-                else decode_chunk<true, false, DT, VERIFY>(blob, w_ref, n, c, o0, o1, L, pay, pay_words, ring, K, area, raise);
-            } else {
-                decode_chunk<false, true, DT, VERIFY>(blob, w_ref, n, c, o0, o1, L, pay, pay_words, ring, K, area, raise);
-            }
+            decode_chunk<DT, VERIFY>(blob, w_ref, n, c, o0, o1, full && aligned, M > kMultiBits, L, pay, pay_words, ring, K, lens, area, raise);
         }
         if (!more) break;
         c = (u32)cn; o0 = n0; o1 = n1;
@@ -750,6 +771,7 @@ __global__ __launch_bounds__(64) void kb_decode(BatchDecArgs a) {
     const u32 lane = threadIdx.x;
     u32 active = 0xFFFFFFFFu, M = 0, K = 0, zero_bits = 0;
     bool have_tables = false;
+    CodeLens lens;
     u64 area = 0;
     const uint4* chunk_info = reinterpret_cast<const uint4*>(a.chunk_info);
     auto info_of = [&](u32 g) {                      // (the same in every lane: back to scalar registers)
@@ -789,16 +811,12 @@ __global__ __launch_bounds__(64) void kb_decode(BatchDecArgs a) {
             if (lane < kMaxSym) { rep = D.info.rep_bits[lane]; len = D.info.len[lane]; code = D.info.code[lane]; }
 #pragma unroll
             for (u32 k = 0; k < (1u << kMultiBits) / 4 / kW; ++k) reinterpret_cast<u32x4*>(L.multi)[lane + k * kW] = e[k];
-            if (lane < kMaxSym) { L.rep[lane] = __uint_as_float(lane < K ? rep : 0x80000000u); L.len[lane] = len; L.code[lane] = code; }
-            build_longs(L, len, code);
+            if (lane < kMaxSym) { L.rep[lane] = __uint_as_float(lane < K ? rep : 0x80000000u); }
+            if (M > kMultiBits) build_longs(L, len, code);
+            lens.set(len, K);
             __builtin_amdgcn_wave_barrier();
         }
-        if (full && sg.aligned) {
-            if (M > kMultiBits) decode_chunk<true, true, DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, L, pay, kPayWords, ring, K, area, raise);
-            else decode_chunk<true, false, DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, L, pay, kPayWords, ring, K, area, raise);
-        } else {
-            decode_chunk<false, true, DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, L, pay, kPayWords, ring, K, area, raise);
-        }
+        decode_chunk<DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, full && sg.aligned, M > kMultiBits, L, pay, kPayWords, ring, K, lens, area, raise);
     }
 }
 

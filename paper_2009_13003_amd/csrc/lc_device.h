@@ -214,6 +214,11 @@ __device__ __forceinline__ void load_row_v(const void* __restrict__ p, u64 idx, 
     else load_row<FAST, DT>(p, idx, n, x);
 }
 template <int DT>
+__device__ __forceinline__ typename Val<DT>::type load_one_v(const void* base, u64 i) {
+    if constexpr (DT == kF64) return static_cast<const double*>(base)[i];
+    else return load_one<DT>(base, i);
+}
+template <int DT>
 __device__ __forceinline__ void store4_v(void* base, u64 i, const typename Val<DT>::type (&x)[4]) {
     if constexpr (DT == kF64) store4_64(base, i, x);
     else store4<DT>(base, i, x);

@@ -75,3 +75,20 @@ def test_codes_longer_than_the_look_up(lc):
         times[bits] = best_us(lambda: lc.lc_decode(blob, rec))
     print("restore with 9-bit and 11-bit codes: %.1f us, %.1f us" % (times[9], times[11]), flush=True)
     assert times[11] < 2.5 * times[9], times             # (5.2 with a search through the symbols, 1.5 with a table)
+
+
+def test_few_kept_symbols_spread_over_most_rows(lc):
+    """Laplace updates of one scale: with 2 promotion bits about one element in a hundred is kept, with 3 most chunks are full
+    of kept symbols.  The first take no longer to restore, although hardly a row is free of them."""
+    n, times = 1 << 20, {}
+    g = torch.Generator(device=DEV); g.manual_seed(11)
+    ref = 0.05 * torch.randn(n, generator=g, device=DEV)
+    u = torch.rand(n, generator=g, device=DEV) - 0.5
+    w = ref - 1e-3 * torch.sign(u) * torch.log1p(-2 * u.abs().clamp_(max=0.49999997))
+    for nbits in (2, 3):
+        blob = blob_of(lc, w, ref, nbits)
+        assert restored_as_the_oracle(lc, blob, n)
+        rec = ref.clone()
+        times[nbits] = best_us(lambda: lc.lc_decode(blob, rec))
+    print("restore with 2 and 3 bits: %.1f us, %.1f us" % (times[2], times[3]), flush=True)
+    assert times[2] < 1.2 * times[3], times               # (1.7 with rows looked up symbol by symbol, 0.8 without)
