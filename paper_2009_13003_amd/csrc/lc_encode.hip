@@ -1055,7 +1055,8 @@ __device__ __forceinline__ void note_merged_chunks(const Table& T, u64 n, u32* c
 // another's work is that several workgroups share a compute unit.  The parts (up to kPartWords words of every lane) stay in
 // LDS; once all lengths are known, each thread ORs its part, shifted, into the chunk's payload there, and lane lengths and
 // payload go to the chunk's slot as the record that the blob will hold: k_place then only copies it.  A chunk whose
-// strings outgrow these areas (rare symbols only) is coded again by one wavefront, as lane strings (kRawChunk).
+// strings outgrow these areas (a layer above the others' scale, say: symbols that are rare in the vector as a whole) is
+// coded again, straight to its places in the payload (finish_long).
 // Before, a wavefront walked over chunks with its next rows in flight (2 wavefronts per SIMD, or 1, by its registers);
 // k_pack and k_place, before -> after: 2^20 fp32 elements 19.3 + 4.8 -> 7.6 + 3.6 us, 2^27 bf16 138 + 27 -> 119 + 19 us,
 // 2^28 fp32 430 + 45 -> 426 + 33 us, from keys 139 + 45 -> 114 + 33 us; 161 tensors of 25.6 M (kb_list, kb_pack, kb_place)
@@ -1121,34 +1122,59 @@ __device__ __forceinline__ void code_rows2(const typename Raw<DT>::type* a, cons
     code_symbols(t, L, S);
 }
 
-// The chunk once more, by one wavefront: lane strings straight to the slot.
-template <int DT>
-__device__ __forceinline__ void pack_chunk_raw(const ChunkRef& ch, const PackWg& L) {
-    const u32 lane = lane_id();
-    u32* lane_words = ch.slot + kLaneBitsWords + lane;
-    u64 acc = 0;
-    u32 nb = 0, nw = 0;
+// The symbols of a lane's part, 4 bits each, the first in the low bits of s[0]; count of them.
+struct PartSymbols { u64 s[2]; u32 count; };
+
+// A chunk whose strings outgrow the workgroup's areas, all wavefronts side by side: where each part goes is known (o: its first
+// bit in the payload), so the parts are coded again straight to their places, in as many turns as windows of kPayloadWords
+// words hold the payload (3 at most).  Contains barriers; L.payload is cleared when it is called.
+// By one wavefront instead, a row at a time: 2^24 fp32 elements of 10 layers at 4 bits 143 us the call, 101 so.
+__device__ __forceinline__ void finish_long(const ChunkRef& ch, const PartSymbols& P, u32 o, u32 nwords, PackWg& L) {
+    const u32 t = threadIdx.x;
 #pragma unroll 1
-    for (u32 r = 0; r < kR; ++r) {
-        const u64 idx = row_at(ch.c, r);
-        float xa[4], xb[4];
-        load_row<false, DT>(ch.w, idx, ch.n, xa); load_row<false, DT>(ch.w_ref, idx, ch.n, xb);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            if (idx + v < ch.n) {
-                const u32 cl = L.codelen[L.sym8[delta_bits(xa[v], xb[v]) >> 23] >> 3];
-                acc = (acc << (cl & 31)) | (cl >> 5); nb += cl & 31;
-            }
-            if ((v & 1) && nb >= 32) { lane_words[nw * kW] = (u32)(acc >> (nb - 32)); ++nw; nb -= 32; }
+    for (u32 base = 0; base < nwords; base += kPayloadWords) {
+        if (base != 0) {
+            for (u32 i = t; i < kPayloadWords; i += kWgThreads) L.payload[i] = 0;
+            __syncthreads();
         }
+        u64 acc = 0;
+        u32 nb = o & 31, at = (o >> 5) - base;                 // (words before the window wrap to large numbers)
+        auto put = [&](u32 word) { if (at < kPayloadWords) atomicOr(&L.payload[at], word); ++at; };
+        auto append = [&](u32 code, u32 len) {
+            acc = (acc << len) | code; nb += len;
+            if (nb >= 32) { put((u32)(acc >> (nb - 32))); nb -= 32; }
+        };
+        u64 s = P.s[0];
+        u32 i = 0;
+#pragma unroll 1
+        for (; i + 8 <= P.count; i += 8) {                     // two symbols per look-up, four look-ups in flight
+            uint2 p[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) { p[k] = L.pair[((u32)s & 15u) << 4 | ((u32)(s >> 4) & 15u)]; s >>= 8; }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) append(p[k].x, p[k].y);
+            if (i == 8) s = P.s[1];
+        }
+        if (i == 16) s = P.s[1];
+#pragma unroll 1
+        for (; i < P.count; ++i) {
+            const u32 cl = L.codelen[(u32)s & 15u];
+            append(cl >> 5, cl & 31);
+            s = i == 15 ? P.s[1] : s >> 4;
+        }
+        if (nb > 0) put((u32)(acc << (32 - nb)));
+        __syncthreads();
+        const u32x4* from = reinterpret_cast<const u32x4*>(L.payload);
+        u32x4* to = reinterpret_cast<u32x4*>(ch.slot + kLaneBitsWords + base);
+        for (u32 i = t; i < (min(nwords - base, kPayloadWords) + 3) / 4; i += kWgThreads) to[i] = from[i];
+        __syncthreads();
     }
-    if (nb > 0) lane_words[nw * kW] = (u32)(acc << (32 - nb));
-    finish_lane_sizes(ch, nb, nw);
 }
 
-// All parts are coded: their lengths, the payload, the record.  Returns (in every thread) whether the chunk fits its areas;
-// nothing is written for it otherwise.  Contains barriers.
-__device__ __forceinline__ bool finish_parts(const ChunkRef& ch, LanePart& S, u32 v, PackWg& L) {
+// All parts are coded: their lengths, the payload, the record.  again(): the symbols of this lane's part once more, for a chunk
+// that does not fit its areas.  Contains barriers.
+template <typename Again>
+__device__ __forceinline__ void finish_parts(const ChunkRef& ch, LanePart& S, u32 v, PackWg& L, const Again& again) {
     const u32 t = threadIdx.x, lane = lane_id();
     if (S.nb > 0) S.put((u32)(S.acc << (32 - S.nb)));
     const u32 mine = 32 * S.nw + S.nb;
@@ -1162,10 +1188,14 @@ __device__ __forceinline__ bool finish_parts(const ChunkRef& ch, LanePart& S, u3
         before += k < v ? b : 0u;
         bits += b;
     }
-    const u32 incl = wave_incl_scan(bits), total = read_lane(incl, kW - 1), nwords = (total + 31) >> 5;
-    if (L.overflow != 0 || nwords > kPayloadWords) return false;
+    const u32 incl = wave_incl_scan(bits), total = read_lane(incl, kW - 1), nwords = (total + 31) >> 5, o = incl - bits + before;
+    if (v == 0) {
+        reinterpret_cast<uint16_t*>(ch.slot)[lane] = (uint16_t)bits;
+        if (lane == 0) { *ch.bits_at = total; atomicAdd(ch.group_at, kLaneBitsWords + nwords); }
+    }
+    if (L.overflow != 0 || nwords > kPayloadWords) { finish_long(ch, again(), o, nwords, L); return; }
     {
-        const u32 o = incl - bits + before, sh = o & 31, W0 = o >> 5, have = (mine + 31) >> 5;
+        const u32 sh = o & 31, W0 = o >> 5, have = (mine + 31) >> 5;
         const u32 touched = mine ? ((o + mine - 1) >> 5) - W0 + 1 : 0;
         u32 prev = 0;                                          // (a part of 7 words touches 8 of the payload)
 #pragma unroll
@@ -1176,15 +1206,10 @@ __device__ __forceinline__ bool finish_parts(const ChunkRef& ch, LanePart& S, u3
         }
     }
     __syncthreads();
-    if (v == 0) {
-        reinterpret_cast<uint16_t*>(ch.slot)[lane] = (uint16_t)bits;
-        if (lane == 0) { *ch.bits_at = total; atomicAdd(ch.group_at, kLaneBitsWords + nwords); }
-    }
     // the payload in whole vectors (what lies behind its end in the slot nobody reads)
     const u32x4* from = reinterpret_cast<const u32x4*>(L.payload);
     u32x4* to = reinterpret_cast<u32x4*>(ch.slot + kLaneBitsWords);
     for (u32 i = t; i < (nwords + 3) / 4; i += kWgThreads) to[i] = from[i];
-    return true;
 }
 
 // 4 elements from index i on, those at n and behind read as zero; any alignment
@@ -1301,7 +1326,34 @@ __device__ __forceinline__ void pack_chunk_wg(const ChunkRef& ch, const Table& T
             }
         }
     }
-    const bool fits = finish_parts(ch, S, v, L);
+    finish_parts(ch, S, v, L, [&]() {
+        PartSymbols P;
+        P.count = 0;
+#pragma unroll 1
+        for (u32 h = 0; h < 2; ++h) {                // (a half at a time, for the registers; behind the first it moves on to s[0])
+            raw_t a[H], b[H];
+#pragma unroll
+            for (u32 k = 0; k < H; ++k) {
+                const u64 idx = row_at(ch.c, first_row + H * h + k);
+                if (ch.fast) { a[k] = load_raw<DT>(ch.w, idx); b[k] = load_raw<DT>(ch.w_ref, idx); }
+                else { a[k] = load_raw_guarded<DT>(ch.w, idx, ch.n); b[k] = load_raw_guarded<DT>(ch.w_ref, idx, ch.n); }
+            }
+            u64 s = 0;
+#pragma unroll
+            for (u32 k = 0; k < H; ++k) {
+                const u64 idx = row_at(ch.c, first_row + H * h + k);
+                float xa[4], xb[4];
+                unpack<DT>(a[k], xa); unpack<DT>(b[k], xb);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    s |= (u64)(L.sym8[delta_bits(xa[e], xb[e]) >> 23] >> 3) << (16 * k + 4 * e);
+                    P.count += idx + e < ch.n ? 1u : 0u;      // (those past the vector's end are a lane's last)
+                }
+            }
+            P.s[0] = h == 0 ? s : P.s[0]; P.s[1] = s;
+        }
+        return P;
+    });
     // the extremes: thread t holds copy t mod 32 of symbol t / 32 (see pack_merge_extremes)
     const u32 t = threadIdx.x;
     u32 mn = L.mn[t], mx = L.mx[t];
@@ -1309,8 +1361,13 @@ __device__ __forceinline__ void pack_chunk_wg(const ChunkRef& ch, const Table& T
     for (int d = kMmCopies / 2; d >= 1; d >>= 1) { mn = min(mn, (u32)__shfl_xor(mn, d, 64)); mx = max(mx, (u32)__shfl_xor(mx, d, 64)); }
     const u32 sym = t / kMmCopies, copy = blockIdx.x % kExtCopies;
     if (t % kMmCopies == 0 && sym < (K8 >> 3) && mn <= mx) { atomicMin(&ws->mmin[copy][sym], mn & 0x7FFFFFu); atomicMax(&ws->mmax[copy][sym], mx & 0x7FFFFFu); }
-    if (!fits && v == 0) pack_chunk_raw<DT>(ch, L);
 }
+
+// Which entry of the list workgroup i takes.  The list holds chunks that are 512 apart side by side, so a run of chunks of the
+// same cost (a layer's) comes back every nchunks / 512 entries, in a vector of 2^27 elements every 16: one of the 8 dies that
+// workgroups are dealt to in turn would get all of them.  Within each 8 entries the order turns by one every 16.  (300 chunks
+// of long codes in 2^27 elements: k_pack_keys 92 -> 68 us.)
+__device__ __forceinline__ u32 list_entry(u32 i, u32 count) { return (i | 7u) < count ? (i & ~7u) | ((i + (i >> 4)) & 7u) : i; }
 
 // Sweep 2 of one vector, a workgroup per chunk.  chunk_list: the chunks to read (then workgroups beyond the list leave at
 // once, having seen to the sizes of the chunks off it); null: every chunk, and chunk_maxexp (or null) tells those that hold
@@ -1327,7 +1384,7 @@ __global__ __launch_bounds__(kWgThreads, DT == kF32 || STAY ? 4 : 8) void k_pack
     if (chunk_list) note_merged_chunks(T, n, chunk_bits, group_words, chunk_maxexp);
     const u32 count = chunk_list ? ws->list_count : nchunks;
     auto chunk = [&](u32 i) {
-        const u32 c = chunk_list ? load_uniform(chunk_list + i) : i;
+        const u32 c = chunk_list ? load_uniform(chunk_list + list_entry(i, count)) : i;
         ChunkRef ch;
         ch.w = w; ch.w_ref = w_ref; ch.n = n; ch.c = c;
         ch.slot = prov + (u64)c * slot_words; ch.bits_at = chunk_bits + c; ch.group_at = group_words + (c >> 6);
@@ -1357,8 +1414,9 @@ __global__ __launch_bounds__(kWgThreads, 8) void k_pack_keys(const void* __restr
     const Table& T = ws->table;
     if (T.status != 0) return;
     note_merged_chunks(T, n, chunk_bits, group_words, chunk_maxexp);
-    if (blockIdx.x >= ws->list_count) return;
-    const u32 c = load_uniform(chunk_list + blockIdx.x);
+    const u32 count = ws->list_count;
+    if (blockIdx.x >= count) return;
+    const u32 c = load_uniform(chunk_list + list_entry(blockIdx.x, count));
     ChunkRef ch;
     ch.w = w; ch.w_ref = w_ref; ch.n = n; ch.c = c;
     ch.slot = prov + (u64)c * slot_words; ch.bits_at = chunk_bits + c; ch.group_at = group_words + (c >> 6);
@@ -1390,7 +1448,19 @@ __global__ __launch_bounds__(kWgThreads, 8) void k_pack_keys(const void* __restr
             code_symbols(t, L, S);
         }
     }
-    if (!finish_parts(ch, S, v, L) && v == 0) pack_chunk_raw<kF32>(ch, L);
+    finish_parts(ch, S, v, L, [&]() {
+        PartSymbols P;
+        P.count = kWgRows * kV;
+#pragma unroll
+        for (u32 b = 0; b < kMine; ++b) {
+            const u32x4 x = reinterpret_cast<const u32x4*>(keys.exp)[at + b * kW];
+            const u32 sign = keys.sign[at + b * kW], wv[4] = {x.x, x.y, x.z, x.w};
+            P.s[b] = 0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) P.s[b] |= (u64)(L.sym8[((wv[i >> 2] >> (8 * (i & 3))) & 255u) | (((sign >> i) & 1u) << 8)] >> 3) << (4 * i);
+        }
+        return P;
+    });
 }
 
 // ----------------------------------------------------------------------------- k_pack64

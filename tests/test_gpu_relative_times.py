@@ -92,3 +92,22 @@ def test_few_kept_symbols_spread_over_most_rows(lc):
         times[nbits] = best_us(lambda: lc.lc_decode(blob, rec))
     print("restore with 2 and 3 bits: %.1f us, %.1f us" % (times[2], times[3]), flush=True)
     assert times[2] < 1.2 * times[3], times               # (1.7 with rows looked up symbol by symbol, 0.8 without)
+
+
+def test_encode_of_a_chunk_of_long_codes(lc):
+    """One chunk of 256 whose codes are too long for the areas that a workgroup codes into at first, as a layer above the others'
+    scale has them, against the same vector without it."""
+    n, times = 1 << 22, {}
+    g = torch.Generator(device=DEV); g.manual_seed(5)
+    i = torch.arange(n, device=DEV)
+    k = torch.floor(-torch.log2(torch.rand(n, generator=g, device=DEV).clamp_(min=2.0 ** -20)))
+    common = torch.where((k > 0) & (k < 8), 8 - k, torch.zeros_like(k))
+    rare = torch.randint(8, 16, (n,), generator=g, device=DEV).float() * (torch.rand(n, generator=g, device=DEV) < 0.7)
+    for kind, where in (("long", i < 16384), ("spread", i % 256 == 0)):      # as many rare symbols, in one chunk or over all
+        w, ref = in_binades(torch.where(where, rare, common), 5)
+        out = lc.alloc_out(n, 4, DEV)
+        size = lc.lc_encode(w, ref, 4, out)
+        assert np.array_equal(out[:size].cpu().numpy(), orc.encode(w.cpu().numpy(), ref.cpu().numpy(), 4))
+        times[kind] = best_us(lambda: lc.lc_encode(w, ref, 4, out))
+    print("encode with a long chunk and without: %.1f us, %.1f us" % (times["long"], times["spread"]), flush=True)
+    assert times["long"] < 1.6 * times["spread"], times    # (2.1 when one wavefront coded such a chunk again, 1.1 now)
