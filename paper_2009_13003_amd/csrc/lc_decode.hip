@@ -235,12 +235,15 @@ __global__ __launch_bounds__(256) void k_dec_check(BlobList blobs, u32 first, u6
 // bare read-and-write sweep in this walk reaches (5.5 TB/s), 437 -> 421 us.
 // The merged symbol adds -0.0, which leaves every fp32 pattern unchanged, and a row in which no lane decoded a kept symbol
 // is not written back at all.
-constexpr u32 kPayWords = 2048;      // LDS room for one chunk's payload (4 bits per element on average) when the
-                                     // compute unit is shared by as many workgroups as fit; more when fewer are needed
+// LDS room for one chunk's payload.  A longer one is read from memory, lane by lane, 2-3 times as slow for that chunk, so a
+// launch takes as much as leaves room for the workgroups that will share a compute unit: (32 chunks of 7.5 bits per element in
+// 2^25: 98 us with 3072 words, 81 with 4224; one in 2^23: 82 and, with room for any, 74)
+constexpr u32 kPayWords = 2048;      // three: 4 bits per element on average
+constexpr u32 kPayWordsTwo = 4224;   // two: 8 bits
+constexpr u32 kPayWordsOne = kChunk * 15 / 32 + 4;  // one: 15 bits, the longest payload there is, wherever it starts in a vector
 constexpr u32 kSparseSlack = 1024;   // bits above an all-merged chunk up to which a chunk's kept symbols are restored one by one
                                      // (512 instead: a batch of 2^24 elements at 2 bits 49 us, 40 so; 2048: the same)
 constexpr u32 kSparseLaneSlack = 64; // the same for one lane's string
-constexpr u32 kPayWordsMax = 3072;   // what keeps a workgroup's LDS within 64 KB (6 bits per element on average)
 constexpr u32 kRingWords = 8;        // words of 8 symbols that a lane may be ahead of the rows being restored
 constexpr u32 kGroupRows = 8;        // rows restored at a time: 32 symbols, 4 words of the ring per lane
 
@@ -1236,10 +1239,11 @@ void launch_decode(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, Work
     const u64 blocks = balanced_workers((nchunks + 3) / 4, (u64)tune.num_cu * (few ? 3 : tune.decode_blocks_per_cu));
     const dim3 grid((u32)blocks), wg(256);
     const int al = verify ? 1 : aligned_rows(w_ref, dtype);
-    // (a payload longer than its area is read from memory, lane by lane: rare below 4, or with the larger areas 6 bits per element)
-    const u32 pay_words = few && blocks > 2 * (u64)tune.num_cu ? kPayWords : kPayWordsMax;
-    static_assert(sizeof(DecLds) + 4 * kRingWords * kW * 4 + 4 * (kPayWordsMax / 4 + 1) * sizeof(uint4) <= 64 * 1024, "one workgroup's LDS");
-    const size_t lds = 4 * (size_t)(pay_words / 4 + 1) * sizeof(uint4);
+    const u32 pay_words = blocks <= (u64)tune.num_cu ? kPayWordsOne : few && blocks > 2 * (u64)tune.num_cu ? kPayWords : kPayWordsTwo;
+    constexpr size_t fixed = sizeof(DecLds) + 4 * kRingWords * kW * 4, area = 4 * sizeof(uint4);
+    static_assert(fixed + area * (kPayWordsOne / 4 + 1) <= kLdsPerCu && fixed + area * (kPayWordsTwo / 4 + 1) <= kLdsPerCu / 2 - 1280 &&
+                  fixed + area * (kPayWords / 4 + 1) <= kLdsPerCu / 3 - 1280, "workgroups that share a compute unit (LDS is given in steps of 1280 bytes)");
+    const size_t lds = area * (pay_words / 4 + 1);
     if (verify) {
         hipLaunchKernelGGL((k_decode<kF32, true>), grid, wg, lds, s, blob, (void*)nullptr, (u64)n, ws, (u32)nchunks, al, (u64)epoch, host, pay_words, (u32)set);
         return;

@@ -83,3 +83,30 @@ def test_chunks_of_several_windows(lc, dtype, tail):
         back = np.zeros(n, np.uint16); orc.decode_t(want, back, orc.DT_BF16)
         got = rec.view(torch.int16).cpu().numpy().view(np.uint16)
     assert np.array_equal(got.view(np.uint8), back.view(np.uint8))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("n", [(1 << 22) + 5, 20_000_001, 40_000_000])
+def test_restore_of_payloads_of_every_length(lc, dtype, n):
+    """A workgroup of a restore has room for payloads of 15, 8 or 4 bits per element, by how many share a compute unit: payloads of
+    2 to 5.6 thousand words in launches of each kind."""
+    print("payloads", dtype, n, flush=True)
+    g = torch.Generator(device=DEV); g.manual_seed(n)
+    i = torch.arange(n, device=DEV)
+    k = torch.floor(-torch.log2(torch.rand(n, generator=g, device=DEV).clamp_(min=2.0 ** -20)))
+    common = torch.where((k > 0) & (k < 8), 8 - k, torch.zeros_like(k))
+    share = 0.3 + (i // CHUNK) * (0.7 / 60)
+    rare = torch.randint(8, 16, (n,), generator=g, device=DEV).float() * (torch.rand(n, generator=g, device=DEV) < share)
+    e = torch.where((i < 60 * CHUNK) & (i // CHUNK % 10 == 0), rare, common)
+    w = torch.where(e > 0, torch.exp2(e - 30), torch.zeros_like(e)).to(dtype)
+    ref = torch.zeros_like(w)
+    out = lc.alloc_out(n, 4, DEV)
+    size = lc.lc_encode_t(w, ref, 4, out)
+    blob = out[:size].clone()
+    h = blob.cpu().numpy()
+    words = np.diff(h[512:512 + 4 * 61].view(np.uint32).astype(int)) - 32
+    assert words.max() > 4300, words
+    rec, want = torch.zeros_like(w), np.zeros(n, np.float64 if dtype == torch.float64 else np.float32)
+    assert lc.lc_decode_t(blob, rec) == size
+    (orc.decode64 if dtype == torch.float64 else orc.decode)(h, want)
+    assert np.array_equal(rec.cpu().numpy().view(np.uint8), want.view(np.uint8))
