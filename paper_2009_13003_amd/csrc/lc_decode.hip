@@ -335,7 +335,7 @@ struct BitReader {
 template <bool FAST, bool LONG, bool STAGED, int DT, bool VERIFY, typename LDS, typename Raise>
 __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 first_bit, u32 lane_bits,
                                             void* __restrict__ w_ref, u64 n, u32 c,
-                                            const LDS& L, u32* ring, u32 K, const CodeLens& lens, Raise& raise) {
+                                            const LDS& L, u32* ring, u32 K, const CodeLens& lens, bool ahead, Raise& raise) {
     typedef typename Val<DT>::type val_t;
     const u32 lane = lane_id();
     BitReader<STAGED> br;
@@ -425,15 +425,27 @@ __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 fi
                 store4_v<DT>(w_ref, row_at(g * kGroupRows + k), x);
             }
         };
-        raw_t A[kGroupRows], B[kGroupRows];
-        fetch(A, 0);
-        for (u32 g = 0; g < kR / kGroupRows; g += 2) {
-            fetch(B, g + 1);
-            symbols(g);
-            restore(A, g);
-            if (g + 2 < kR / kGroupRows) fetch(A, g + 2);
-            symbols(g + 1);
-            restore(B, g + 1);
+        // (ahead: the next group's rows are asked for before this one is decoded; else only its own, and the wavefronts that
+        // share a SIMD cover each other's waits.  binary64 rows are 2 KiB: ahead, 2^25 elements 136 us against 139, but 2^26
+        // 294 against 267 and 2^27 552 against 503)
+        if (DT != kF64 || ahead) {
+            raw_t A[kGroupRows], B[kGroupRows];
+            fetch(A, 0);
+            for (u32 g = 0; g < kR / kGroupRows; g += 2) {
+                fetch(B, g + 1);
+                symbols(g);
+                restore(A, g);
+                if (g + 2 < kR / kGroupRows) fetch(A, g + 2);
+                symbols(g + 1);
+                restore(B, g + 1);
+            }
+        } else {
+            for (u32 g = 0; g < kR / kGroupRows; ++g) {
+                raw_t A[kGroupRows];
+                fetch(A, g);
+                symbols(g);
+                restore(A, g);
+            }
         }
     } else {
         // A ragged or unaligned chunk (the vector's last chunk is one wavefront's work from start to end, so its memory
@@ -561,10 +573,10 @@ struct QuietChunk {
 };
 
 // pay: this wavefront's LDS area of pay_words + 4 words for the chunk's payload; ring: its symbol ring
-// fast: a full chunk of an aligned array; long_codes: the blob has codes of more than 10 bits
+// fast: a full chunk of an aligned array; long_codes: the blob has codes of more than 10 bits; ahead: see decode_rows
 template <int DT, bool VERIFY = false, typename LDS, typename Raise>
 __device__ __forceinline__ void decode_chunk(const uint8_t* __restrict__ blob, void* __restrict__ w_ref, u64 n,
-                                             u32 c, u32 o0, u32 o1, bool fast, bool long_codes, LDS& L, uint4* pay, u32 pay_words, u32* ring, u32 K,
+                                             u32 c, u32 o0, u32 o1, bool fast, bool long_codes, bool ahead, LDS& L, uint4* pay, u32 pay_words, u32* ring, u32 K,
                                              const CodeLens& lens, u64 area, Raise& raise) {
     // o0, o1: the chunk's entries c and c + 1 of the offset table (fetched by the caller, ahead of time)
     const u32 lane = lane_id();
@@ -604,21 +616,21 @@ __device__ __forceinline__ void decode_chunk(const uint8_t* __restrict__ blob, v
         if (sparse) { decode_sparse<DT>(words, nwords, o, lane_bits, lane_elems, w_ref, (u64)c * kChunk, L, ring, K, lens, raise); return; }
     }
     if (staged) {
-        if (!fast) decode_rows<false, true, true, DT, VERIFY>(words, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, raise);
-        else if (long_codes) decode_rows<true, true, true, DT, VERIFY>(words, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, raise);
-        else decode_rows<true, false, true, DT, VERIFY>(words, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, raise);
+        if (!fast) decode_rows<false, true, true, DT, VERIFY>(words, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, ahead, raise);
+        else if (long_codes) decode_rows<true, true, true, DT, VERIFY>(words, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, ahead, raise);
+        else decode_rows<true, false, true, DT, VERIFY>(words, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, ahead, raise);
     } else {
-        if (!fast) decode_rows<false, true, false, DT, VERIFY>(gw, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, raise);
-        else if (long_codes) decode_rows<true, true, false, DT, VERIFY>(gw, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, raise);
-        else decode_rows<true, false, false, DT, VERIFY>(gw, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, raise);
+        if (!fast) decode_rows<false, true, false, DT, VERIFY>(gw, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, ahead, raise);
+        else if (long_codes) decode_rows<true, true, false, DT, VERIFY>(gw, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, ahead, raise);
+        else decode_rows<true, false, false, DT, VERIFY>(gw, nwords, o, lane_bits, w_ref, n, c, L, ring, K, lens, ahead, raise);
     }
 }
 
 // VERIFY: lc_verify's sweep (and the one lc_decode runs first when asked to): the same walk over the blob, decoding
-// only; `w_ref` is not used.
+// only; `w_ref` is not used.  flags: 1 = w_ref is aligned to rows, 2 = rows are fetched a group ahead.
 template <int DT, bool VERIFY = false>
 __global__ __launch_bounds__(256, DT == kF64 ? 2 : 3) void k_decode(const uint8_t* __restrict__ blob, void* __restrict__ w_ref, u64 n,
-                                                Workspace* ws, u32 nchunks, int aligned, u64 epoch, HostResult* host,
+                                                Workspace* ws, u32 nchunks, int flags, u64 epoch, HostResult* host,
                                                 u32 pay_words, u32 set) {
     __shared__ DecLds L;
     __shared__ u32 s_ring[VERIFY ? 1 : 4 * kRingWords * kW];
@@ -688,7 +700,7 @@ __global__ __launch_bounds__(256, DT == kF64 ? 2 : 3) void k_decode(const uint8_
                 lens.set(sym_len, K);
                 __builtin_amdgcn_wave_barrier();
             }
-            decode_chunk<DT, VERIFY>(blob, w_ref, n, c, o0, o1, full && aligned, M > kMultiBits, L, pay, pay_words, ring, K, lens, area, raise);
+            decode_chunk<DT, VERIFY>(blob, w_ref, n, c, o0, o1, full && (flags & 1) != 0, M > kMultiBits, (flags & 2) != 0, L, pay, pay_words, ring, K, lens, area, raise);
         }
         if (!more) break;
         c = (u32)cn; o0 = n0; o1 = n1;
@@ -819,7 +831,7 @@ __global__ __launch_bounds__(64) void kb_decode(BatchDecArgs a) {
             lens.set(len, K);
             __builtin_amdgcn_wave_barrier();
         }
-        decode_chunk<DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, full && sg.aligned, M > kMultiBits, L, pay, kPayWords, ring, K, lens, area, raise);
+        decode_chunk<DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, full && sg.aligned, M > kMultiBits, true, L, pay, kPayWords, ring, K, lens, area, raise);
     }
 }
 
@@ -1235,20 +1247,21 @@ void launch_decode(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, Work
     // Above, smaller shares even out chunks of unlike cost, and only 2 workgroups share a unit, by the size of their
     // payload areas: a sweep that reads and writes runs better on fewer streams (16,384 dense chunks: 421 us against 438
     // with 3; 428 with 2 and a grid of just those).
-    const bool few = nchunks <= (u64)tune.num_cu * 3 * 4 * 4;
+    // (binary64: as far as rows are fetched a group ahead, a chunk per wavefront and 2 workgroups per unit)
+    const bool few = nchunks <= (u64)tune.num_cu * (dtype == kF64 ? 2 * 4 : 3 * 4 * 4);
     const u64 blocks = balanced_workers((nchunks + 3) / 4, (u64)tune.num_cu * (few ? 3 : tune.decode_blocks_per_cu));
     const dim3 grid((u32)blocks), wg(256);
-    const int al = verify ? 1 : aligned_rows(w_ref, dtype);
+    const int flags = (verify || aligned_rows(w_ref, dtype) ? 1 : 0) | (few || dtype != kF64 ? 2 : 0);
     const u32 pay_words = blocks <= (u64)tune.num_cu ? kPayWordsOne : few && blocks > 2 * (u64)tune.num_cu ? kPayWords : kPayWordsTwo;
     constexpr size_t fixed = sizeof(DecLds) + 4 * kRingWords * kW * 4, area = 4 * sizeof(uint4);
     static_assert(fixed + area * (kPayWordsOne / 4 + 1) <= kLdsPerCu && fixed + area * (kPayWordsTwo / 4 + 1) <= kLdsPerCu / 2 - 1280 &&
                   fixed + area * (kPayWords / 4 + 1) <= kLdsPerCu / 3 - 1280, "workgroups that share a compute unit (LDS is given in steps of 1280 bytes)");
     const size_t lds = area * (pay_words / 4 + 1);
     if (verify) {
-        hipLaunchKernelGGL((k_decode<kF32, true>), grid, wg, lds, s, blob, (void*)nullptr, (u64)n, ws, (u32)nchunks, al, (u64)epoch, host, pay_words, (u32)set);
+        hipLaunchKernelGGL((k_decode<kF32, true>), grid, wg, lds, s, blob, (void*)nullptr, (u64)n, ws, (u32)nchunks, flags, (u64)epoch, host, pay_words, (u32)set);
         return;
     }
-#define LC_DECODE(DT) hipLaunchKernelGGL((k_decode<DT>), grid, wg, lds, s, blob, w_ref, (u64)n, ws, (u32)nchunks, al, (u64)epoch, host, pay_words, (u32)set)
+#define LC_DECODE(DT) hipLaunchKernelGGL((k_decode<DT>), grid, wg, lds, s, blob, w_ref, (u64)n, ws, (u32)nchunks, flags, (u64)epoch, host, pay_words, (u32)set)
     if (dtype == kF64) LC_DECODE(kF64);
     else if (dtype == kBF16) LC_DECODE(kBF16);
     else if (dtype == kF16) LC_DECODE(kF16);
