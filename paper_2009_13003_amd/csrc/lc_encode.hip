@@ -1051,7 +1051,7 @@ __device__ __forceinline__ void note_merged_chunks(const Table& T, u64 n, u32* c
 // ----------------------------------------------------------------------------- coding by workgroups
 // Sweep 2 (fp32, bf16, fp16, and from staged keys): a workgroup of eight wavefronts per chunk, wavefront v coding rows
 // 8 v .. 8 v + 7, so that every lane's string of 256 codes grows in eight parts of 32 side by side.  A workgroup codes one
-// chunk and ends: its rows are asked for before anything is known about the table, and what overlaps one chunk's waits with
+// chunk and ends: its rows are asked for as soon as it is known that they have to be read, and what overlaps one chunk's waits with
 // another's work is that several workgroups share a compute unit.  The parts (up to kPartWords words of every lane) stay in
 // LDS; once all lengths are known, each thread ORs its part, shifted, into the chunk's payload there, and lane lengths and
 // payload go to the chunk's slot as the record that the blob will hold: k_place then only copies it.  A chunk whose
@@ -1256,23 +1256,27 @@ __device__ __forceinline__ bool noted_as_merged(const ChunkRef& ch, const Table&
     return true;
 }
 
-// Codes the chunk with table T (in memory).  parts: the largest exponent of each of its 4 KiB parts, one byte each (16 of
-// 4-byte elements, 8 of 2-byte), or null: parts of a full chunk below every kept bucket are then not read.
+// What sweep 1 recorded of the parts this wavefront's rows lie in: the largest exponent of each 4 KiB part of a chunk, one byte
+// each from `parts` on (16 parts of 4-byte elements, 8 of 2-byte).  Asked for together with the chunk's own maximum.
+constexpr u32 kReadAllParts = 0xFFFFFFFFu;
 template <int DT>
-__device__ __forceinline__ void pack_chunk_wg(const ChunkRef& ch, const Table& T, const uint8_t* parts, EncState* ws, PackWg& L) {
+__device__ __forceinline__ u32 part_word(const uint8_t* parts) {
+    const u32 v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    return load_uniform(reinterpret_cast<const u32*>(parts) + (elem_bytes<DT>() == 4 ? v / 2 : v / 4));
+}
+
+// Codes the chunk with table T (in memory).  maxima: part_word of the chunk, or kReadAllParts; parts of a full, aligned chunk
+// below every kept bucket are not read.
+template <int DT>
+__device__ __forceinline__ void pack_chunk_wg(const ChunkRef& ch, const Table& T, u32 maxima, EncState* ws, PackWg& L) {
     typedef typename Raw<DT>::type raw_t;
     constexpr u32 kPartRows = 4096 / (kRowElems * elem_bytes<DT>()), H = kWgRows / 2;      // 4 or 8 rows per part
     const u32 lane = lane_id(), v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), first_row = kWgRows * v;
     raw_t A[kWgRows], B[kWgRows];
     bool skip[2] = {false, false};           // rows first_row .. + 3, and the 4 behind them: merged elements only
     if (ch.fast) {
-        if (parts) {
 #pragma unroll
-            for (u32 h = 0; h < 2; ++h) {
-                const u32 p = (first_row + H * h) / kPartRows;
-                skip[h] = ((load_uniform(reinterpret_cast<const u32*>(parts) + p / 4) >> (8 * (p % 4))) & 255u) < T.min_kept_exp;
-            }
-        }
+        for (u32 h = 0; h < 2; ++h) skip[h] = ((maxima >> (8 * ((first_row + H * h) / kPartRows % 4))) & 255u) < T.min_kept_exp;
 #pragma unroll
         for (u32 h = 0; h < 2; ++h) {
             if (skip[h]) continue;
@@ -1389,9 +1393,11 @@ __global__ __launch_bounds__(kWgThreads, DT == kF32 || STAY ? 4 : 8) void k_pack
         ch.w = w; ch.w_ref = w_ref; ch.n = n; ch.c = c;
         ch.slot = prov + (u64)c * slot_words; ch.bits_at = chunk_bits + c; ch.group_at = group_words + (c >> 6);
         ch.fast = aligned && (u64)(c + 1) * kChunk <= n;
-        if (!chunk_list && chunk_maxexp && noted_as_merged(ch, T, chunk_maxexp[maxexp_slot(c)])) return;
         constexpr u32 kParts = kChunk * elem_bytes<DT>() / 4096;
-        pack_chunk_wg<DT>(ch, T, chunk_list ? batch_max + (u64)c * kParts : nullptr, ws, L);
+        u32 largest = kReadAllParts, maxima = kReadAllParts;
+        if (chunk_maxexp) { largest = load_uniform(chunk_maxexp + maxexp_slot(c)); maxima = part_word<DT>(batch_max + (u64)c * kParts); }
+        if (!chunk_list && noted_as_merged(ch, T, largest)) return;
+        pack_chunk_wg<DT>(ch, T, maxima, ws, L);
     };
     if constexpr (STAY) {
         for (u32 i = blockIdx.x; i < count; i += gridDim.x) { chunk(i); __syncthreads(); }
@@ -1421,7 +1427,7 @@ __global__ __launch_bounds__(kWgThreads, 8) void k_pack_keys(const void* __restr
     ch.w = w; ch.w_ref = w_ref; ch.n = n; ch.c = c;
     ch.slot = prov + (u64)c * slot_words; ch.bits_at = chunk_bits + c; ch.group_at = group_words + (c >> 6);
     ch.fast = false;
-    if ((u64)(c + 1) * kChunk > n) { pack_chunk_wg<kF32>(ch, T, nullptr, ws, L); return; }
+    if ((u64)(c + 1) * kChunk > n) { pack_chunk_wg<kF32>(ch, T, kReadAllParts, ws, L); return; }
     constexpr u32 kMine = kWgRows / 4;
     const u32 v = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const u64 at = ((u64)c * kKeyBatches + v * kMine) * kW + lane_id();
@@ -2034,8 +2040,9 @@ __global__ __launch_bounds__(kWgThreads, DT == kF32 ? 4 : 8) void kb_pack(BatchA
     ch.slot = a.prov + (u64)g * a.slot_words; ch.bits_at = a.chunk_bits + g; ch.group_at = a.group_words + sg.group0 + (ch.c >> 6);
     ch.fast = sg.aligned && (u64)(ch.c + 1) * kChunk <= sg.n;
     if (st->table.status != 0) return;                 // (a delta that is not finite: a header-only blob)
-    if (!a.listed && noted_as_merged(ch, st->table, a.chunk_maxexp[g])) return;
-    pack_chunk_wg<DT>(ch, st->table, a.listed ? a.part_max + (u64)g * kPartBytes : nullptr, st, L);
+    const u32 largest = load_uniform(a.chunk_maxexp + g), maxima = part_word<DT>(a.part_max + (u64)g * kPartBytes);
+    if (!a.listed && noted_as_merged(ch, st->table, largest)) return;
+    pack_chunk_wg<DT>(ch, st->table, maxima, st, L);
 }
 
 // The first `count` workgroups write the tensors' headers and report their outcomes (everything that takes is final
@@ -2097,12 +2104,16 @@ void launch_hist(const void* w, const void* w_ref, uint64_t n, int dtype, Worksp
 
 static u32 even_waves(u64 nchunks, u64 cap);
 
-// Whether sweep 2 takes its chunks from a list of those to read.  A short call does without: what chunks hold merged elements
-// only their workgroups see for themselves, and k_table has one thing less to do (2^20 elements: 9.0 -> 7.5 us; in a
-// batched call kb_list's 5 us go).  A long one needs it: 8,445 workgroups that ask for their rows before they know (7,841 of
-// them for nothing) took 203 us where the 604 listed ones take 16.
-static bool needs_list(u64 nchunks, const Tuning& tune) { return nchunks > (u64)tune.num_cu * tune.unlisted_per_cu; }
-bool pack_needs_list(uint64_t n, int dtype, const Tuning& tune) { return dtype == kF64 || needs_list(num_chunks_of(n), tune); }
+// Whether sweep 2 takes its chunks from a list of those to read.  Writing the list is work for the table's kernel, and taking
+// chunks from it one more wait on memory for every workgroup; without it a workgroup finds out by itself that its chunk holds
+// merged elements only, a wait each before it makes room for the next.  Without / with a list, whole calls, us: 2^20 fp32
+// 39.3 / 40.8; 2^24 dense 87 / 88, sparse 64 / 59; 2^25 dense 128 / 134, sparse 90 / 81 (before: 86), 3 * 2^24 sparse 117 /
+// 105.  2-byte elements, whose chunks take half the time to read: 2^23 dense 55.6 / 56.9, sparse 43.8 / 41.0; 2^24 dense
+// 69.9 / 71.6, sparse 53.4 / 45.1.  A batched call has a kernel of its own for the list: 1,000 chunks 94 / 96, 2,000 140 / 142.
+static bool needs_list(u64 nchunks, int per_cu, const Tuning& tune) { return nchunks > (u64)tune.num_cu * per_cu; }
+bool pack_needs_list(uint64_t n, int dtype, const Tuning& tune) {
+    return dtype == kF64 || needs_list(num_chunks_of(n), dtype == kF32 ? tune.unlisted_per_cu : tune.unlisted_per_cu / 2, tune);
+}
 
 void launch_pack_keys(const void* w, const void* w_ref, uint64_t n, Workspace* ws, uint32_t* chunk_bits, uint32_t* group_words,
                       const uint32_t* chunk_maxexp, const uint32_t* chunk_list, KeyPlanes keys, uint32_t* prov, uint32_t slot_words,
@@ -2195,7 +2206,7 @@ void launch_place(uint8_t* out, Workspace* ws, const uint32_t* chunk_bits, const
 
 void launch_batch_encode(const BatchArgs& args, const Tuning& tune, hipStream_t s) {
     BatchArgs a = args;
-    a.listed = needs_list(a.total_chunks, tune) ? 1 : 0;
+    a.listed = needs_list(a.total_chunks, tune.batch_unlisted_per_cu, tune) ? 1 : 0;
     hipLaunchKernelGGL(kb_setup, dim3(a.count), dim3(256), 0, s, a);
     if (a.total_chunks) {
         // (a counting workgroup needs 19 KB of LDS: 8 fit a compute unit, and a grid of more leaves the last ones a

@@ -142,7 +142,9 @@ struct Tuning {
     int hist_threads = 256;
     int pack_waves_per_cu = 8;         // single-wave workgroups of k_pack64 per compute unit
     int key_staging = 0;               // 0: by the vector's last call, 1: whenever it applies, 2: never
-    int unlisted_per_cu = 8;           // a call of at most this many chunks per compute unit does without a list of chunks to read
+    int unlisted_per_cu = 4;           // a call of at most this many chunks of 4-byte elements (half of 2-byte) per compute unit does
+                                       // without a list of chunks to read (below 16: see stage_keys)
+    int batch_unlisted_per_cu = 8;     // ... a batched call
     int spec_waves_per_cu = 8;         // of the single sweep of the cached encode (what its LDS and registers allow)
     int batch_waves_per_cu = 8;        // of the batch kernels
     int decode_blocks_per_cu = 9;     // ... of a long restore (LDS lets 3 run at once; more, smaller shares even out unlike chunks)

@@ -111,3 +111,20 @@ def test_encode_of_a_chunk_of_long_codes(lc):
         times[kind] = best_us(lambda: lc.lc_encode(w, ref, 4, out))
     print("encode with a long chunk and without: %.1f us, %.1f us" % (times["long"], times["spread"]), flush=True)
     assert times["long"] < 1.6 * times["spread"], times    # (2.1 when one wavefront coded such a chunk again, 1.1 now)
+
+
+def test_encode_of_chunks_with_few_parts_to_read(lc):
+    """A vector short enough to go without a list of chunks, of whose 16 parts of 4 KiB per chunk one holds kept elements: the second
+    sweep reads that one, and the call takes well less than one that has to read every part."""
+    n, times = 1 << 24, {}
+    g = torch.Generator(device=DEV); g.manual_seed(6)
+    i = torch.arange(n, device=DEV)
+    e = torch.randint(1, 8, (n,), generator=g, device=DEV).float()
+    for kind, where in (("one", (i // 1024) % 16 == 5), ("all", i % 16 == 5)):
+        w, ref = in_binades(torch.where(where, e, torch.zeros_like(e)), 6)
+        out = lc.alloc_out(n, 3, DEV)
+        size = lc.lc_encode(w, ref, 3, out)
+        assert np.array_equal(out[:size].cpu().numpy(), orc.encode(w.cpu().numpy(), ref.cpu().numpy(), 3))
+        times[kind] = best_us(lambda: lc.lc_encode(w, ref, 3, out))
+    print("encode with one part in 16 and with all: %.1f us, %.1f us" % (times["one"], times["all"]), flush=True)
+    assert times["one"] < 0.92 * times["all"], times         # (0.99 when all parts were read, 0.85 now)
