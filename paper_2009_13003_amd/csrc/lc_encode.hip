@@ -2180,8 +2180,9 @@ void launch_pack(const void* w, const void* w_ref, uint64_t n, int dtype, Worksp
         else LC_PACK(kF32, false, nchunks);
     } else {
         // behind a speculative sweep there is mostly nothing to do, and starting 21,657 workgroups for that took 10 us instead
-        // of 4: a few that stay
-        const u64 most = (u64)tune.num_cu * 4, grid = nchunks < most ? nchunks : most;
+        // of 4: as many as start in that time, which take several chunks each when there is (354.8 M elements, coded anew /
+        // confirmed: 4 per unit 1027 / 604 us, 8 1012 / 603, 16 1027 / 605, 64 1018 / 611; 2^26 236 / 154, 233 / 154)
+        const u64 most = (u64)tune.num_cu * 8, grid = nchunks < most ? nchunks : most;
         if (dtype == kBF16) LC_PACK(kBF16, true, grid);
         else if (dtype == kF16) LC_PACK(kF16, true, grid);
         else LC_PACK(kF32, true, grid);

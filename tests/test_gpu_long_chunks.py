@@ -73,6 +73,13 @@ def test_chunks_of_several_windows(lc, dtype, tail):
     out.fill_(0xA5)
     sizes = lc.lc_encode_batch([w], [ref], 4, [out])
     assert sizes == [want.size] and np.array_equal(out[:want.size].cpu().numpy(), want)
+    # behind a cached table that this vector voids, by workgroups that take several chunks each
+    cache, other = lc.new_cache(DEV), torch.zeros_like(w[:CHUNK])
+    other[::3] = 1000.0
+    lc.lc_encode_cached_t(other, torch.zeros_like(other), 4, lc.alloc_out(CHUNK, 4, DEV), cache)
+    out.fill_(0xA5)
+    size, used = lc.lc_encode_cached_t(w, ref, 4, out, cache)
+    assert not used and size == want.size and np.array_equal(out[:size].cpu().numpy(), want)
     rec = torch.zeros_like(w)                                  # and their restore, whose payloads are the longest there are
     assert lc.lc_verify(out[:want.size], n, dtype) == want.size
     assert lc.lc_decode_t(out[:want.size], rec) == want.size
