@@ -375,7 +375,7 @@ lc_ssize encode_impl(const void* w, const void* w_ref, uint64_t n, int nbits, vo
     }
     const bool listed = !spec_sweep;            // sweep 1 recorded the chunk maxima, so k_table can list the chunks to read
     { Timed t(kSlotTable, s);    launch_table(ws, n, nbits, dtype, group_words, chunk_maxexp, listed && (staged || pack_needs_list(n, dtype, ds->tune)) ? chunk_list : nullptr, s); }
-    if (staged) { Timed t(kSlotPackKeys, s); launch_pack_keys(w, w_ref, n, ws, chunk_bits, group_words, chunk_maxexp, chunk_list, keys, prov, slot_words, ds->tune, s); }
+    if (staged) { Timed t(kSlotPackKeys, s); launch_pack_keys(w, w_ref, n, ws, chunk_bits, group_words, chunk_maxexp, chunk_list, keys, prov, slot_words, s); }
     else { Timed t(kSlotPack, s); launch_pack(w, w_ref, n, dtype, ws, chunk_bits, group_words, chunk_maxexp, listed ? chunk_list : nullptr, batch_max, prov, slot_words, ds->tune, s); }
     if (async) LC_HIP(hipEventRecord(call.inputs, s));   // w and w_ref are not read past this point
     { Timed t(kSlotPlace, s);    launch_place(o, ws, chunk_bits, group_words, prov, slot_words, n, chunk_maxexp, result, cache, nbits, dtype, staged, s); }

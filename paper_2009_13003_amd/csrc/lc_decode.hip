@@ -10,13 +10,6 @@
 namespace lc {
 
 // ----------------------------------------------------------------------------- k_dec_check
-// Everything lc_decode verifies before w_ref is touched, in one launch.  Every workgroup
-// re-reads the header and does the cheap sanity checks that keep its own reads in bounds;
-// workgroup 0 additionally validates the symbol table, rebuilds the canonical codes and the
-// look-up table; each wavefront checks one chunk: the offset table must be the running sum
-// of the record sizes that the lane lengths imply, from 0 to the blob's stated size.
-// Errors are raised with atomicMax on a word tagged with the call's epoch, so the word
-// never needs clearing.
 // Tables of one blob while its workgroup builds them.
 struct DecBuild {
     u32 len[kMaxSym], code[kMaxSym], max_len;
@@ -104,7 +97,7 @@ __device__ __forceinline__ void dec_build_luts(DecSet& D, DecBuild& B, u32 K, u3
         const u32 L = e[k] >> 4, i = t + 256 * k;
         on[k] = e[k] != 0xFF && L != 0;
         syms[k] = on[k] ? e[k] & 15u : 0u; cnt[k] = on[k] ? 1u : 0u;
-        rest[k] = on[k] ? i << (32 - kMultiBits + L) : 0u; left[k] = on[k] ? kMultiBits - L : kMultiBits;
+        rest[k] = on[k] && L < kMultiBits ? i << (32 - kMultiBits + L) : 0u; left[k] = on[k] ? kMultiBits - L : kMultiBits;
         if (e[k] != 0xFF && L == 0) {                       // starts no code: nothing is ever taken off again
             for (; cnt[k] < kMultiSyms; ++cnt[k]) syms[k] |= K << (4 * cnt[k]);
         }
@@ -170,6 +163,13 @@ __device__ __forceinline__ void raise_status(Workspace* ws, HostResult* host, u6
     host->dec_status = word;              // what the host reads after waiting for the stream (any finding will do)
 }
 
+// Everything lc_decode verifies before w_ref is touched, in one launch.  Every workgroup
+// re-reads the header and does the cheap sanity checks that keep its own reads in bounds;
+// workgroup 0 additionally validates the symbol table, rebuilds the canonical codes and the
+// look-up table; each wavefront checks one chunk: the offset table must be the running sum
+// of the record sizes that the lane lengths imply, from 0 to the blob's stated size.
+// Errors are raised with atomicMax on a word tagged with the call's epoch, so the word
+// never needs clearing.
 // PER: chunks per wavefront, 1 or 4 (4 when one chunk each would take many rounds of workgroups: several blobs, or a long one)
 template <int PER>
 __global__ __launch_bounds__(256) void k_dec_check(BlobList blobs, u32 first, u64 n, u64 max_total, Workspace* ws,
@@ -1159,10 +1159,10 @@ void launch_batch_decode(const BatchDecArgs& a, const Tuning& tune, hipStream_t 
     hipLaunchKernelGGL(kb_dec_tables, dim3(a.count), dim3(256), 0, s, a);
     if (a.total_chunks) {
         hipLaunchKernelGGL(kb_dec_chunks, dim3((a.total_chunks + 3) / 4), dim3(256), 0, s, a);
-        // single-wavefront workgroups, three times as many as the compute units hold at once (12 each, by their LDS)
+        // single-wavefront workgroups, three to four times as many as the compute units hold at once (10 each, by their LDS)
         // as long as there are chunks for them: workgroups that draw cheap chunks (nothing but merged symbols) make
         // room for the next, which evens out the load better than a fixed deal of chunks to resident wavefronts
-        // (VGG-16's 32 tensors: 60 us against 80)
+        // (40 tensors of 2^28 elements, 12 / 20 / 36 / 60 per unit: 520, 451, 444, 441 us at 4 bits, 103, 89, 84, 82 at 2)
         u32 waves = (u32)tune.num_cu * (u32)tune.decode_blocks_per_cu * 4u;
         if (waves > a.total_chunks) waves = a.total_chunks;
         if (a.dtype == kBF16) hipLaunchKernelGGL(kb_decode<kBF16>, dim3(waves), dim3(64), 0, s, a);
@@ -1241,14 +1241,16 @@ void launch_decode(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, Work
     const u64 nchunks = num_chunks_of(n);
     if (nchunks == 0) return;
     const bool verify = w_ref == nullptr;
-    // A blob of at most 4 chunks per wavefront that 3 workgroups per compute unit hold (what their LDS allows): the grid is
-    // just those.  A wavefront then looks ahead to its next chunk, and no second round of workgroups pays its start (8,445
-    // sparse chunks: 38 us for the call, 42 with 8 workgroups per unit; 8,192 dense ones of bf16: 139 either way).
-    // Above, smaller shares even out chunks of unlike cost, and only 2 workgroups share a unit, by the size of their
-    // payload areas: a sweep that reads and writes runs better on fewer streams (16,384 dense chunks: 421 us against 438
-    // with 3; 428 with 2 and a grid of just those).
-    // (binary64: as far as rows are fetched a group ahead, a chunk per wavefront and 2 workgroups per unit)
-    const bool few = nchunks <= (u64)tune.num_cu * (dtype == kF64 ? 2 * 4 : 3 * 4 * 4);
+    // Up to so many chunks per compute unit the grid is just what 3 workgroups of it hold by their LDS (decode_blocks_per_cu has
+    // no say): a wavefront then looks ahead to its next chunk, and no second round of workgroups pays its start.  Above,
+    // smaller shares even out chunks of unlike cost, and only 2 workgroups share a unit, by the size of their payload
+    // areas: a sweep that reads and writes runs better on fewer streams.  Where the one passes the other depends on the
+    // bytes of a row and on what the chunks hold; few / many, us, fp32: 7,000 chunks dense 212 / 199, layered 176 / 152,
+    // sparse 31 / 31; 8,445 236 / 238, 176 / 155, 29 / 32; 16,384 441 / 423, 295 / 258, 32 / 35.  bf16, dense: 8,192
+    // 128 / 138, 12,288 176 / 189, 16,384 228 / 243.  binary64: as far as rows are fetched a group ahead, a chunk per
+    // wavefront and 2 workgroups per unit.  A verifying sweep only reads.
+    const u64 few_per_cu = verify ? 48 : dtype == kF64 ? 8 : dtype == kF32 ? 24 : 72;
+    const bool few = nchunks <= (u64)tune.num_cu * few_per_cu;
     const u64 blocks = balanced_workers((nchunks + 3) / 4, (u64)tune.num_cu * (few ? 3 : tune.decode_blocks_per_cu));
     const dim3 grid((u32)blocks), wg(256);
     const int flags = (verify || aligned_rows(w_ref, dtype) ? 1 : 0) | (few || dtype != kF64 ? 2 : 0);

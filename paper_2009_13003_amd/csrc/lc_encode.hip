@@ -1902,10 +1902,9 @@ __global__ __launch_bounds__(256) void k_place(uint8_t* out, Workspace* ws, cons
 }
 
 // ----------------------------------------------------------------------------- batched encode
-// lc_encode_batch: many vectors, one table each, in six launches.  The chunks of all tensors are numbered
-// through; the sweeps deal those dense chunks round-robin to their wavefronts exactly as for one vector,
-// and a wavefront that moves on to a chunk of another tensor first hands in what it gathered for the last
-// one (bucket counts, extremes) and loads the new tensor's table.
+// lc_encode_batch: many vectors, one table each, in five launches, six where the chunks to read are listed.  The chunks of all
+// tensors are numbered through.  The counting sweep deals them round-robin to its wavefronts, and one that moves on to a chunk
+// of another tensor hands in the last one's counts; the coding sweep is a workgroup per chunk, as for one vector.
 // One workgroup per tensor: what the host says about it (read from mapped host memory, kept for the kernels behind this one: a
 // copy of the list to the device ahead of the call took longer than that read: 161 tensors 129 -> 125 us), which chunks are
 // its own, its groups and its state cleared.
@@ -2102,8 +2101,6 @@ void launch_hist(const void* w, const void* w_ref, uint64_t n, int dtype, Worksp
     else launch_hist_t<kF32>(w, w_ref, n, ws, chunk_maxexp, batch_max, (u32)blocks, threads, s);
 }
 
-static u32 even_waves(u64 nchunks, u64 cap);
-
 // Whether sweep 2 takes its chunks from a list of those to read.  Writing the list is work for the table's kernel, and taking
 // chunks from it one more wait on memory for every workgroup; without it a workgroup finds out by itself that its chunk holds
 // merged elements only, a wait each before it makes room for the next.  Without / with a list, whole calls, us: 2^20 fp32
@@ -2117,7 +2114,7 @@ bool pack_needs_list(uint64_t n, int dtype, const Tuning& tune) {
 
 void launch_pack_keys(const void* w, const void* w_ref, uint64_t n, Workspace* ws, uint32_t* chunk_bits, uint32_t* group_words,
                       const uint32_t* chunk_maxexp, const uint32_t* chunk_list, KeyPlanes keys, uint32_t* prov, uint32_t slot_words,
-                      const Tuning& tune, hipStream_t s) {
+                      hipStream_t s) {
     const u64 nchunks = num_chunks_of(n);
     if (nchunks == 0) return;
     hipLaunchKernelGGL(k_pack_keys, dim3((u32)nchunks), dim3(kWgThreads), 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, chunk_maxexp, chunk_list,
