@@ -1247,9 +1247,9 @@ void launch_decode(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, Work
     // areas: a sweep that reads and writes runs better on fewer streams.  Where the one passes the other depends on the
     // bytes of a row and on what the chunks hold; few / many, us, fp32: 7,000 chunks dense 212 / 199, layered 176 / 152,
     // sparse 31 / 31; 8,445 236 / 238, 176 / 155, 29 / 32; 16,384 441 / 423, 295 / 258, 32 / 35.  bf16, dense: 8,192
-    // 128 / 138, 12,288 176 / 189, 16,384 228 / 243.  binary64: as far as rows are fetched a group ahead, a chunk per
-    // wavefront and 2 workgroups per unit.  A verifying sweep only reads.
-    const u64 few_per_cu = verify ? 48 : dtype == kF64 ? 8 : dtype == kF32 ? 24 : 72;
+    // 128 / 138, 16,384 228 / 243, 32,768 423 / 453, 49,152 661 / 719.  binary64: as far as rows are fetched a group
+    // ahead, a chunk per wavefront and 2 workgroups per unit.  A verifying sweep only reads.
+    const u64 few_per_cu = verify ? 48 : dtype == kF64 ? 8 : dtype == kF32 ? 24 : 256;
     const bool few = nchunks <= (u64)tune.num_cu * few_per_cu;
     const u64 blocks = balanced_workers((nchunks + 3) / 4, (u64)tune.num_cu * (few ? 3 : tune.decode_blocks_per_cu));
     const dim3 grid((u32)blocks), wg(256);

@@ -147,7 +147,7 @@ struct Tuning {
     int batch_unlisted_per_cu = 8;     // ... a batched call
     int spec_waves_per_cu = 8;         // of the single sweep of the cached encode (what its LDS and registers allow)
     int batch_waves_per_cu = 8;        // of the batch kernels
-    int decode_blocks_per_cu = 9;     // ... of a long restore (LDS lets 3 run at once; more, smaller shares even out unlike chunks)
+    int decode_blocks_per_cu = 9;      // ... of a long restore (LDS lets 2 run at once; more, smaller shares even out unlike chunks)
     int fused_waves_per_cu = 16;       // most wavefronts per compute unit
     int fused_min_waves_per_cu = 8;    // a sweep takes as many blobs as still leave LDS for this many
 };
