@@ -438,14 +438,29 @@ def chain_leg(device, steps):
                 fused_speedup=round(t_seq / t_many, 3), restored_equals_tracked=same_seq and same_many)
 
 
+def sources_hash():
+    """What a profile's summary names: the first 16 digits of the SHA-256 over csrc/*.hip and *.h in the order of their names."""
+    import hashlib
+    csrc = os.path.join(ROOT, "paper_2009_13003_amd", "csrc")
+    h = hashlib.sha256()
+    for f in sorted(os.listdir(csrc)):
+        if f.endswith((".hip", ".h")):
+            h.update(open(os.path.join(csrc, f), "rb").read())
+    return h.hexdigest()[:16]
+
+
 def traffic_from_profiles(workload):
     """({kernel: HBM bytes per launch}, source file) as rocprofv3 --pmc counted them for this workload in a run of its
     own (profiles/<workload>_hbm_traffic_pmc.txt: lines `traffic_bytes_per_launch <kernel> <bytes>`), or ({}, None).
-    These are constants of the committed summary, not measurements of this run: the summary names the library
-    build it was taken from."""
+    These are constants of the committed summary, not measurements of this run: a summary names the library
+    sources it was taken from, and one of other sources than these counts for nothing."""
     name = "%s_hbm_traffic_pmc.txt" % workload
     out = {}
+    def of_these_sources(path):
+        return ("sha256[:16] = %s." % sources_hash()) in open(path).read()
     try:
+        if not of_these_sources(os.path.join(ROOT, "profiles", name)):
+            return {}, None
         for line in open(os.path.join(ROOT, "profiles", name)):
             f = line.split()
             if len(f) == 3 and f[0] == "traffic_bytes_per_launch":
@@ -453,7 +468,8 @@ def traffic_from_profiles(workload):
     except OSError:
         return {}, None
     try:                                         # the kernels of the cached encode: counted in a run of their own
-        for line in open(os.path.join(ROOT, "profiles", "%s_cached_hbm_traffic_pmc.txt" % workload)):
+        cached = os.path.join(ROOT, "profiles", "%s_cached_hbm_traffic_pmc.txt" % workload)
+        for line in open(cached) if of_these_sources(cached) else ():
             f = line.split()
             if len(f) == 3 and f[0] == "traffic_bytes_per_launch":
                 out.setdefault(f[1], float(f[2]))
