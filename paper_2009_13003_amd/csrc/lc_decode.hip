@@ -240,6 +240,7 @@ __global__ __launch_bounds__(256) void k_dec_check(BlobList blobs, u32 first, u6
 // 2^25: 98 us with 3072 words, 81 with 4224; one in 2^23: 82 and, with room for any, 74)
 constexpr u32 kPayWords = 2048;      // three: 4 bits per element on average
 constexpr u32 kPayWordsTwo = 4224;   // two: 8 bits
+constexpr u32 kPayWordsVerify = 3040;               // three of the verifying sweep, which has no ring (2^28 dense elements 95 us, 119 with two)
 constexpr u32 kPayWordsOne = kChunk * 15 / 32 + 4;  // one: 15 bits, the longest payload there is, wherever it starts in a vector
 constexpr u32 kSparseSlack = 1024;   // bits above an all-merged chunk up to which a chunk's kept symbols are restored one by one
                                      // (512 instead: a batch of 2^24 elements at 2 bits 49 us, 40 so; 2048: the same)
@@ -1254,7 +1255,7 @@ void launch_decode(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, Work
     const u64 blocks = balanced_workers((nchunks + 3) / 4, (u64)tune.num_cu * (few ? 3 : tune.decode_blocks_per_cu));
     const dim3 grid((u32)blocks), wg(256);
     const int flags = (verify || aligned_rows(w_ref, dtype) ? 1 : 0) | (few || dtype != kF64 ? 2 : 0);
-    const u32 pay_words = blocks <= (u64)tune.num_cu ? kPayWordsOne : few && blocks > 2 * (u64)tune.num_cu ? kPayWords : kPayWordsTwo;
+    const u32 pay_words = blocks <= (u64)tune.num_cu ? kPayWordsOne : few && blocks > 2 * (u64)tune.num_cu ? kPayWords : verify ? kPayWordsVerify : kPayWordsTwo;
     constexpr size_t fixed = sizeof(DecLds) + 4 * kRingWords * kW * 4, area = 4 * sizeof(uint4);
     static_assert(fixed + area * (kPayWordsOne / 4 + 1) <= kLdsPerCu && fixed + area * (kPayWordsTwo / 4 + 1) <= kLdsPerCu / 2 - 1280 &&
                   fixed + area * (kPayWords / 4 + 1) <= kLdsPerCu / 3 - 1280, "workgroups that share a compute unit (LDS is given in steps of 1280 bytes)");
