@@ -11,6 +11,7 @@
 // mean of their extremes and x-bit priority promotion (Section 3.1.1), Huffman
 // coding of the bucket indices (Section 3.1.2).  How it is laid out on the GPU is this library's own.
 #include "lc_device.h"
+#include <stddef.h>
 #include <type_traits>
 
 namespace lc {
@@ -335,71 +336,162 @@ __global__ __launch_bounds__(1024) void k_hist64(const void* __restrict__ w, con
 }
 
 // ----------------------------------------------------------------------------- k_table
-// Priority promotion (Section 3.1.1) and the Huffman table (Section 3.1.2), one wavefront.  Lane l looks at one exponent level (both signs) per step, from
-// the largest exponent down; a ballot/popcount scan ranks the non-empty buckets (+ before - at
-// equal exponent).  Lane 0 then builds the code lengths with two queues and the canonical codes
-// with per-length counters.
+// Priority promotion (Section 3.1.1) and the Huffman table (Section 3.1.2): one workgroup and, where a chain of single
+// steps is left, its first wavefront.  Nothing here is bound by bytes; it is the latency of that chain, which every encode
+// waits for.  So the buckets are ranked by all threads at once, and the chain keeps to scalar registers: see code_lengths.
+// One wavefront with 64-bit weights, ranking included, against this: 2^20 fp32 at 3 bits 8.1 -> 4.6 us, a 2^27 bf16 vector
+// at 4 bits (with its list of chunks) 14.1 -> 9.1 us, 161 tensors 11.9 -> 6.2 us.
 template <int EB>                         // EB: exponent bits of the parameters' delta (8, or 11 for binary64)
 struct TableLds {
-    uint8_t sym[2u << EB];
-    u64 cnt[kMaxSym + 1];
-    u32 kept[kMaxSym], len[kMaxSym + 1];
+    alignas(8) uint8_t sym[2u << EB];     // bucket -> symbol, 0xFF: merged
+    u64 cnt[kMaxSym];
+    u32 kept[kMaxSym];
+    u32 found[kW];                        // candidates among the buckets of one step of one wavefront, in order of rank
+    u32 nonfinite, zero_class;
+    uint8_t symlen[kMaxSym];              // symbol | length << 4; the last entry: the merged symbol's (there are at most 15 others)
 };
+template <int EB> constexpr u32 table_threads() { return EB == 8 ? 512u : 1024u; }
+template <int EB> constexpr u32 table_steps() { return (2u << EB) / table_threads<EB>(); }
+
+// Places of the buckets in order of priority: larger exponent first, + before - at equal exponent.
+template <int EB> __device__ __forceinline__ u32 bucket_at(u32 i) { return ((i & 1u) << EB) | (((1u << EB) - 1) - (i >> 1)); }
+
+// Ranks the non-empty normal buckets and fills S (all but symlen); thread t of table_threads holds the population of the
+// bucket at place t + s * table_threads in c[s].  By a workgroup of at least that many threads (the others hold zeros);
+// contains a barrier, and the caller's comes before S is read.  Returns the number of candidates.
+template <int EB>
+__device__ __forceinline__ u32 rank_buckets(TableLds<EB>& S, const u64 (&c)[table_steps<EB>()], u32 kmax) {
+    constexpr u32 kThreads = table_threads<EB>(), kSteps = table_steps<EB>(), kWaves = kThreads / kW, kEmax = (1u << EB) - 1;
+    static_assert(kSteps * kWaves <= kW, "one lane per count of the scan");
+    const u32 t = threadIdx.x, lane = lane_id(), wave = t / kW;
+    u64 m[kSteps];
+#pragma unroll
+    for (u32 s = 0; s < kSteps; ++s) {
+        const u32 E = bucket_at<EB>(t + s * kThreads) & kEmax;
+        const u64 any = __ballot(c[s] != 0);
+        m[s] = __ballot(c[s] != 0 && E != 0 && E != kEmax);
+        if (lane == 0 && t < kThreads) S.found[s * kWaves + wave] = (u32)__popcll(m[s]);
+        // (the two buckets of infinities and NaN are places 0 and 1, those of zeros and subnormals the last two)
+        if (s == 0 && t == 0) S.nonfinite = (any & 3u) != 0 ? 1u : 0u;
+        if (s == kSteps - 1 && t == kThreads - 1) S.zero_class = (any >> (kW - 2)) != 0 ? 1u : 0u;
+    }
+    if (t < kMaxSym) { S.cnt[t] = 0; S.kept[t] = 0; }
+    __syncthreads();
+    const u32 mine = lane < kSteps * kWaves ? S.found[lane] : 0u, incl = wave_incl_scan(mine), excl = incl - mine;
+    if (t < kThreads) {
+#pragma unroll
+        for (u32 s = 0; s < kSteps; ++s) {
+            const u32 b = bucket_at<EB>(t + s * kThreads);
+            const u32 r = read_lane(excl, __builtin_amdgcn_readfirstlane(s * kWaves + wave)) + (u32)__popcll(m[s] & ((1ull << lane) - 1));
+            const bool keep = ((m[s] >> lane) & 1) != 0 && r < kmax;
+            S.sym[b] = keep ? (uint8_t)r : (uint8_t)0xFF;
+            if (keep) { S.kept[r] = b; S.cnt[r] = c[s]; }
+        }
+    }
+    return read_lane(incl, kW - 1);
+}
+
+// Huffman code lengths by one wavefront, lane j < 16 holding the count of symbol j (0: does not occur; so do the other lanes);
+// at least two occur, and their counts add up to at most 2^32.  Repeatedly joins the two smallest nodes under the order
+// (weight, leaf before joined node, symbol index / creation order) with two queues, both sorted: the leaves, moved to lanes
+// 0 .. 15 in ascending order, and the joined nodes in creation order in lanes 32 and up.  A node remembers its parent only;
+// the depths follow by doubling the step towards the root four times.  Weights of 32 bits are enough: a node that is ever
+// compared leaves something out.
+__device__ __forceinline__ u32 code_lengths(u32 count) {
+    constexpr u32 kNone = 0xFFFFFFFFu, kNodes = 32;
+    const u32 lane = lane_id();
+    const u32 key = count - 1;                               // (absent: the largest of all)
+    const u32 nl = (u32)__popcll(__ballot(count != 0));
+    u32 place = 0;
+#pragma unroll
+    for (u32 i = 0; i < kMaxSym; ++i) {
+        const u32 ki = read_lane(key, i);
+        place += (ki < key || (ki == key && i < lane)) ? 1u : 0u;
+    }
+    if (lane >= kMaxSym) place = lane;
+    u32 w = (u32)__builtin_amdgcn_ds_permute((int)(place * 4), (int)count);
+    if (lane >= nl) w = kNone;
+    u32 parent = lane, li = 0, qi = 0, lw = read_lane(w, 0), nw = kNone;
+    for (u32 ni = 0; ni + 1 < nl; ++ni) {
+        u32 sum = 0;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const bool leaf = lw <= nw;
+            const u32 pick = leaf ? li : kNodes + qi;
+            sum += leaf ? lw : nw;
+            li += leaf ? 1u : 0u; qi += leaf ? 0u : 1u;
+            if (lane == pick) parent = kNodes + ni;
+            // (behind the last leaf and the last node there is nothing: kNone)
+            const u32 next = read_lane(w, leaf ? li : kNodes + qi);
+            lw = leaf ? next : lw; nw = leaf ? nw : next;
+        }
+        if (lane == kNodes + ni) w = sum;
+        if (qi == ni) nw = sum;                              // the queue of nodes was empty: its head
+    }
+    u32 depth = parent != lane ? 1u : 0u, up = parent * 4;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {                            // (no symbol of 16 lies deeper than 15)
+        const u32 d = (u32)__builtin_amdgcn_ds_bpermute((int)up, (int)depth), u = (u32)__builtin_amdgcn_ds_bpermute((int)up, (int)up);
+        depth += d; up = u;
+    }
+    const u32 len = (u32)__builtin_amdgcn_ds_bpermute((int)(place * 4), (int)depth);
+    return count != 0 ? len : 0u;
+}
+
+// Canonical codes by one wavefront, lane j holding the length of symbol j: within a length in symbol order, the first code
+// of a length from the counts below it.
+__device__ __forceinline__ u32 canonical_code(u32 len) {
+    u32 code = 0, first = 0, shorter = 0;
+#pragma unroll
+    for (u32 L = 1; L < kMaxSym; ++L) {
+        const u64 m = __ballot(len == L);
+        first = (first + shorter) << 1;
+        shorter = (u32)__popcll(m);
+        if (len == L) code = first + (u32)__popcll(m & ((1ull << lane_id()) - 1));
+    }
+    return code;
+}
+
+// The counts of the symbols, one per lane of a wavefront: the kept buckets' and, in lane K, what is left of n.
+__device__ __forceinline__ u64 symbol_count(const u64* cnt, u32 K, u64 n) {
+    const u32 lane = lane_id();
+    const u64 c = lane < K ? cnt[lane] : 0ull;
+    const u32 kept = wave_sum32((u32)c);                     // (modulo 2^32: n <= 2^32, and no kept bucket holds them all unless K > 0)
+    const u64 rest = K == 0 ? n : (u64)((u32)n - kept);
+    return lane == K ? rest : c;
+}
 
 // When the sweep before it coded speculatively with a cached table (ws->spec), the kernel also decides
 // whether that stands: this checkpoint's kept set must be the cached one and exactly the symbols with a
 // cached code must occur, in a coding of at most n * nbits payload bits.  If so the cached lengths are kept and the sweep's output is final (spec_ok);
 // if not, the traces of the speculative coding are cleared and the table is this checkpoint's own.
-// With chunk_list (and a workgroup of more than one wavefront) the other wavefronts meanwhile list the chunks
+// With chunk_list (and a workgroup of 1024 threads) the wavefronts but the first meanwhile list the chunks
 // that sweep 2 has to read: all but the full chunks whose largest exponent lies below every kept bucket.
 template <int EB>
 __device__ __forceinline__ void table_build(EncState* ws, Ext64* ext, u64 n, int nbits, u32* group_words, u32 ngroups,
                                             const u32* chunk_maxexp, u32* chunk_list) {
     __shared__ TableLds<EB> S;
-    constexpr u32 kEmax = (1u << EB) - 1, kSteps = (1u << EB) / kW, kNeg = 1u << EB;
+    constexpr u32 kEmax = (1u << EB) - 1, kThreads = table_threads<EB>(), kSteps = table_steps<EB>();
     const unsigned long long* hist = EB == 8 ? ws->hist : ext->hist;
-    __shared__ u32 s_reuse, s_min_kept_exp, s_listed;
-    const u32 lane = lane_id();
-    const bool active = threadIdx.x < kW;
+    __shared__ u32 s_reuse, s_listed;
+    const u32 lane = lane_id(), t = threadIdx.x;
+    const bool active = t < kW;
     const u32 kmax = (1u << nbits) - 1;
+    u64 cnt[kSteps];
+#pragma unroll
+    for (u32 s = 0; s < kSteps; ++s) cnt[s] = t < kThreads ? hist[bucket_at<EB>(t + s * kThreads)] : 0;
+    const u32 spec = ws->spec;
     // The groups' record sizes start from zero in every call: the last call's placement read them to its end, so they
     // are cleared here, ahead of the coding sweep that adds to them (a cached table's speculative coding has already
     // added to them: then k_spec_table has cleared them).
-    if (group_words && !ws->spec) for (u32 i = threadIdx.x; i < ngroups; i += blockDim.x) group_words[i] = 0;
-    if (active) for (u32 i = lane; i <= kMaxSym; i += kW) { S.cnt[i] = 0; S.len[i] = 0; if (i < kMaxSym) S.kept[i] = 0; }
-    u32 total = 0;
-    bool nonfinite = false, zero_class = false;
-    // all counts of this lane first (8, or 64 for binary64), the ranking steps below then run without waiting on memory
-    // (binary64, 32 steps with the loads inside the loop: 28 us for the kernel instead of 24)
-    u64 cnt0[kSteps], cnt1[kSteps];
-#pragma unroll
-    for (u32 step = 0; step < kSteps; ++step) {
-        cnt0[step] = active ? hist[kEmax - (step * kW + lane)] : 0;
-        cnt1[step] = active ? hist[kNeg + kEmax - (step * kW + lane)] : 0;
-    }
-#pragma unroll
-    for (u32 step = 0; step < kSteps; ++step) {
-        if (!active) break;
-        const u32 E = kEmax - (step * kW + lane);
-        const u64 c0 = cnt0[step], c1 = cnt1[step];
-        const bool normal = E >= 1 && E <= kEmax - 1;
-        const bool cand0 = normal && c0 > 0, cand1 = normal && c1 > 0;
-        const u64 m0 = __ballot(cand0), m1 = __ballot(cand1), lt = (1ull << lane) - 1;
-        const u32 r0 = total + __popcll(m0 & lt) + __popcll(m1 & lt), r1 = r0 + (cand0 ? 1u : 0u);
-        S.sym[E] = 0xFF; S.sym[kNeg + E] = 0xFF;
-        if (cand0 && r0 < kmax) { S.kept[r0] = E; S.cnt[r0] = c0; S.sym[E] = (uint8_t)r0; }
-        if (cand1 && r1 < kmax) { S.kept[r1] = kNeg + E; S.cnt[r1] = c1; S.sym[kNeg + E] = (uint8_t)r1; }
-        total += __popcll(m0) + __popcll(m1);
-        nonfinite = nonfinite || __any(E == kEmax && (c0 | c1) != 0);
-        zero_class = zero_class || __any(E == 0 && (c0 | c1) != 0);
-    }
+    if (group_words && !spec) for (u32 i = t; i < ngroups; i += blockDim.x) group_words[i] = 0;
     // The other wavefronts list chunks; the maxima of their first batch are already on their way while the
-    // first wavefront ranks the buckets (a chunk with a ragged end is always read).  Work item t stands for
+    // buckets are ranked (a chunk with a ragged end is always read).  Work item t stands for
     // slot (hi << 9) | lo of the transposed maxima, hi = t / per_row, so that a wavefront's loads fall on a few
     // cache lines; its chunk is (lo << 9) | hi.  One batch covers the 16384 chunks of a 2^28-element call.
     constexpr u32 kListBatch = 18;
-    const bool lister = chunk_list && threadIdx.x >= kW;
-    const u32 workers = blockDim.x - kW, list_first = (threadIdx.x - kW) & ~(kW - 1);
+    const bool lister = chunk_list && t >= kW;
+    const u32 workers = blockDim.x - kW, list_first = (t - kW) & ~(kW - 1);
     const u32 nchunks = (u32)num_chunks_of(n), nfull = (u32)(n / kChunk);
     const u32 per_row = nchunks > 512 ? (nchunks + 511) >> 9 : 1, items = 512 * per_row;
     const float inv_per_row = 1.0f / (float)per_row;
@@ -416,12 +508,11 @@ __device__ __forceinline__ void table_build(EncState* ws, Ext64* ext, u64 n, int
         }
     };
     if (lister) fetch_maxima(list_first);
-    const u32 K = total < kmax ? total : kmax;              // (meaningful in the first wavefront only)
+    const u32 total = rank_buckets<EB>(S, cnt, kmax), K = total < kmax ? total : kmax;
+    if (t == 0) s_listed = 0;
     __syncthreads();
-    if (threadIdx.x == 0) { s_min_kept_exp = K ? (S.kept[K - 1] & kEmax) : kEmax + 1; s_listed = 0; }   // kept buckets are in descending exponent order
-    __syncthreads();
+    const u32 min_kept_exp = K ? (S.kept[K - 1] & kEmax) : kEmax + 1;   // kept buckets are in descending exponent order
     if (lister) {
-        const u32 min_kept_exp = s_min_kept_exp;
         for (u32 t0 = list_first; t0 < items; t0 += kListBatch * workers) {
             if (t0 != list_first) fetch_maxima(t0);
             u64 m[kListBatch];
@@ -443,20 +534,15 @@ __device__ __forceinline__ void table_build(EncState* ws, Ext64* ext, u64 n, int
         }
     }
     if (active) {
-        // The first wavefront builds the code.  Lane j holds what belongs to symbol j (count, length, code),
-        // to the j-th lightest leaf and to the j-th joined node; single values travel between lanes by
-        // readlane, so that no step waits on memory.
+        // The first wavefront builds the code; lane j holds what belongs to symbol j.
         Table& T = ws->table;
-        u64 c = lane < K ? S.cnt[lane] : 0;
-        u64 kept_total = 0;
-        for (u32 j = 0; j < K; ++j) kept_total += read_lane64(c, j);
-        if (lane == K) c = n - kept_total;
+        const bool nonfinite = S.nonfinite != 0;
+        const u64 c = symbol_count(S.cnt, K, n);
         const u32 msym = K + 1;
-        const bool have = lane < msym && c != 0;
-        const u32 nl = (u32)__popcll(__ballot(have));
+        const u32 nl = (u32)__popcll(__ballot(c != 0));
         u32 len = 0;
         bool reuse = false;
-        if (ws->spec) {
+        if (spec) {
             bool differs = false;
             u32 cached_len = 0;
             if (lane < K) differs = T.kept[lane] != S.kept[lane];
@@ -467,77 +553,36 @@ __device__ __forceinline__ void table_build(EncState* ws, Ext64* ext, u64 n, int
             reuse = !nonfinite && T.K == K && !__any(differs) && payload_bits <= n * (u64)nbits;
             if (reuse) len = cached_len;
         }
-        if (!reuse && nl == 1) len = have ? 1u : 0u;
-        if (!reuse && nl >= 2) {
-            // place of every occurring symbol in ascending (count, symbol) order, then the leaves in that order
-            u32 place = 0;
-            for (u32 i = 0; i < msym; ++i) {
-                const u64 ci = read_lane64(c, i);
-                place += (ci != 0 && (ci < c || (ci == c && i < lane))) ? 1u : 0u;
-            }
-            u64 leaf_w = 0; u32 leaf_sym = 0;
-            for (u32 i = 0; i < msym; ++i) {
-                const u64 ci = read_lane64(c, i);
-                const u32 pi = read_lane(place, i);
-                if (ci != 0 && pi == lane) { leaf_w = ci; leaf_sym = i; }
-            }
-            // two queues: sorted leaves and joined nodes in creation order (their weights never decrease);
-            // on equal weight the leaf is taken first.  Ids >= 16 are joined nodes.
-            u64 node_w = 0; u32 left = 0, right = 0;
-            u32 li = 0, qi = 0, ni = 0;
-            for (u32 k = 0; k + 1 < nl; ++k) {
-                u32 pick[2]; u64 wsum = 0;
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    const u64 lw = read_lane64(leaf_w, li < nl ? li : 0), nw = read_lane64(node_w, qi < ni ? qi : 0);
-                    const bool take_leaf = li < nl && (qi >= ni || lw <= nw);
-                    if (take_leaf) { pick[q] = read_lane(leaf_sym, li); wsum += lw; ++li; }
-                    else { pick[q] = 16 + qi; wsum += nw; ++qi; }
-                }
-                if (lane == ni) { node_w = wsum; left = pick[0]; right = pick[1]; }
-                ++ni;
-            }
-            u32 depth = 0;                                   // of node `lane`; the root (the last node) has depth 0
-            for (int i = (int)ni - 1; i >= 0; --i) {
-                const u32 d = read_lane(depth, (u32)i) + 1, ch[2] = {read_lane(left, (u32)i), read_lane(right, (u32)i)};
-#pragma unroll
-                for (int q = 0; q < 2; ++q) {
-                    if (ch[q] >= 16) { if (lane == ch[q] - 16) depth = d; }
-                    else if (lane == ch[q]) len = d;
-                }
-            }
-        }
-        // canonical codes: within a length in symbol order, the first code of a length from the counts below it
-        u32 code = 0, first = 0, shorter = 0;
-        for (u32 L = 1; L < kMaxSym; ++L) {
-            const u64 m = __ballot(len == L);
-            first = (first + shorter) << 1;
-            shorter = (u32)__popcll(m);
-            if (len == L) code = first + (u32)__popcll(m & ((1ull << lane) - 1));
-        }
-        const u32 max_len = wave_max_u32(len);
+        if (!reuse && nl == 1) len = c != 0 ? 1u : 0u;
+        if (!reuse && nl >= 2) len = code_lengths((u32)c);
+        const u32 code = canonical_code(len), max_len = wave_max_u32(len);
         if (lane < kMaxSym) {
             T.codelen[lane] = lane < msym ? ((code << 5) | len) : 0;
             T.kept[lane] = lane < K ? S.kept[lane] : 0;
             T.cnt[lane] = lane < msym ? c : 0;
+            if (lane != kMaxSym - 1) S.symlen[lane] = (uint8_t)(lane | (len << 4));
         }
-        if (lane <= kMaxSym) S.len[lane] = len;
+        if (lane == K) S.symlen[kMaxSym - 1] = (uint8_t)(lane | (len << 4));
         if (lane == 0) {
             s_reuse = reuse;
             ws->spec_ok = reuse;
-            T.K = K; T.max_len = max_len; T.k_E = total + (zero_class ? 1u : 0u);
-            T.min_kept_exp = s_min_kept_exp;
+            T.K = K; T.max_len = max_len; T.k_E = total + S.zero_class;
+            T.min_kept_exp = min_kept_exp;
             T.status = nonfinite ? 2u : 0u;
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) ws->list_count = s_listed;
+    if (t == 0) ws->list_count = s_listed;
     uint8_t* symlen_of_bucket = EB == 8 ? ws->table.symlen_of_bucket : ext->symlen_of_bucket;
-    if (active) for (u32 b = lane; b < (2u << EB); b += kW) {
-        const u32 sy = S.sym[b] == 0xFF ? K : S.sym[b];
-        symlen_of_bucket[b] = (uint8_t)(sy | (S.len[sy] << 4));
+    static_assert(offsetof(Table, symlen_of_bucket) % 8 == 0 && offsetof(Ext64, symlen_of_bucket) % 8 == 0, "8 buckets per store");
+    for (u32 i = t; i < (2u << EB) / 8; i += blockDim.x) {
+        const u64 sy = reinterpret_cast<const u64*>(S.sym)[i];
+        u64 out = 0;
+#pragma unroll
+        for (u32 k = 0; k < 8; ++k) out |= (u64)S.symlen[(u32)(sy >> (8 * k)) & 15u] << (8 * k);     // (0xFF: the last entry)
+        reinterpret_cast<u64*>(symlen_of_bucket)[i] = out;
     }
-    if (active && ws->spec && !s_reuse) {          // the speculative coding is void: forget its extremes and sizes
+    if (active && spec && !s_reuse) {              // the speculative coding is void: forget its extremes and sizes
         for (u32 i = lane; i < ngroups; i += kW) group_words[i] = 0;
         clear_extremes(ws, lane, kW);
     }
@@ -1978,7 +2023,7 @@ __global__ __launch_bounds__(64) void kb_hist(BatchArgs a) {
     src.hand_in(L);
 }
 
-__global__ __launch_bounds__(64) void kb_table(BatchArgs a) {
+__global__ __launch_bounds__(table_threads<8>()) void kb_table(BatchArgs a) {
     table_build<8>(&a.states[blockIdx.x], nullptr, a.segs[blockIdx.x].n, a.nbits, nullptr, 0, nullptr, nullptr);
 }
 
@@ -2124,7 +2169,7 @@ void launch_pack_keys(const void* w, const void* w_ref, uint64_t n, Workspace* w
 // chunk_list: where to list the chunks sweep 2 has to read (chunk_maxexp then holds what k_hist recorded), or null
 void launch_table(Workspace* ws, uint64_t n, int nbits, int dtype, uint32_t* group_words, const uint32_t* chunk_maxexp,
                   uint32_t* chunk_list, hipStream_t s) {
-    const dim3 wg(chunk_list ? 1024 : 64);
+    const dim3 wg(chunk_list || dtype == kF64 ? 1024 : table_threads<8>());
     const u32 ngroups = (u32)((num_chunks_of(n) + 63) / 64);
     if (dtype == kF64) hipLaunchKernelGGL(k_table<11>, dim3(1), wg, 0, s, ws, &ws->ext64, (u64)n, nbits, group_words, ngroups, chunk_maxexp, chunk_list);
     else hipLaunchKernelGGL(k_table<8>, dim3(1), wg, 0, s, ws, (Ext64*)nullptr, (u64)n, nbits, group_words, ngroups, chunk_maxexp, chunk_list);
@@ -2215,7 +2260,7 @@ void launch_batch_encode(const BatchArgs& args, const Tuning& tune, hipStream_t 
         else if (a.dtype == kF16) hipLaunchKernelGGL(kb_hist<kF16>, dim3(waves), dim3(64), 0, s, a);
         else hipLaunchKernelGGL(kb_hist<kF32>, dim3(waves), dim3(64), 0, s, a);
     }
-    hipLaunchKernelGGL(kb_table, dim3(a.count), dim3(64), 0, s, a);
+    hipLaunchKernelGGL(kb_table, dim3(a.count), dim3(table_threads<8>()), 0, s, a);
     if (a.total_chunks) {
         if (a.listed) hipLaunchKernelGGL(kb_list, dim3((a.total_chunks + 255) / 256), dim3(256), 0, s, a);
         const dim3 grid(a.total_chunks), wg(kWgThreads);
