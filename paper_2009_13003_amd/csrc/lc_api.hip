@@ -44,6 +44,7 @@ struct DeviceState {
     // had to read.  Decides whether the next encode of that vector stages keys (see stage_keys()).
     struct Hint { const void* w = nullptr; uint64_t n = 0; float listed = 0; };
     Hint hint[kHints];
+    uint32_t one_blocks = 0;     // workgroups of the short encodes now in progress (see encode_impl)
 };
 
 // A call in progress: where its kernels report (g_pinned[slot]) and, for lc_encode_async, its events.  Asynchronous
@@ -84,7 +85,7 @@ uint64_t g_prof_n[kNumSlots];
 hipEvent_t g_ev[kNumSlots][2];
 bool g_ev_made = false;
 const char* const kSlotNames[kNumSlots] = {"k_reset", "k_hist", "k_table", "k_pack", "k_place", "k_spec_table", "k_spec_sweep",
-                                           "k_dec_check", "k_decode", "k_decode_fused", "k_hist_keys", "k_pack_keys", "k_verify"};
+                                           "k_dec_check", "k_decode", "k_decode_fused", "k_hist_keys", "k_pack_keys", "k_verify", "k_encode_one"};
 
 int env_int(const char* name, int dflt, int lo, int hi) {
     const char* v = getenv(name);
@@ -121,6 +122,8 @@ void read_tuning(DeviceState& ds, int dev) {
     ds.tune.hist_threads = env_int("LC_TUNE_HIST_THREADS", ds.tune.hist_threads, 64, 1024) / 64 * 64;
     ds.tune.pack_waves_per_cu = env_int("LC_TUNE_PACK_WAVES_PER_CU", ds.tune.pack_waves_per_cu, 1, 64);
     ds.tune.unlisted_per_cu = env_int("LC_TUNE_UNLISTED_PER_CU", ds.tune.unlisted_per_cu, 0, 15);   // (calls of 16 and more may stage keys, which takes a list)
+    ds.tune.one_per_cu = env_int("LC_TUNE_ONE_PER_CU", ds.tune.one_per_cu, 0, 2);
+    ds.tune.one_wait = env_int("LC_TUNE_ONE_WAIT", ds.tune.one_wait, 0, 1 << 20);
     ds.tune.spec_waves_per_cu = env_int("LC_TUNE_SPEC_WAVES_PER_CU", ds.tune.spec_waves_per_cu, 1, 64);
     if (g_key_staging < 0) g_key_staging = env_int("LC_TUNE_KEY_STAGING", 0, 0, 2);
     ds.tune.batch_waves_per_cu = env_int("LC_TUNE_BATCH_WAVES_PER_CU", ds.tune.batch_waves_per_cu, 1, 64);
@@ -329,7 +332,7 @@ void note_outcome(DeviceState* ds, const void* w, uint64_t n, const Result& r) {
 // cache holds a usable table, codes with it; k_table confirms or voids that, and only then does the
 // second sweep have anything to do).
 lc_ssize encode_impl(const void* w, const void* w_ref, uint64_t n, int nbits, void* out, int dtype, TableCache* cache,
-                     int* used, void* stream, bool async) {
+                     int* used, void* stream, bool async, bool try_one = true) {
     if (nbits < 1 || nbits > 4 || n > LC_MAX_N || !out || misaligned(out, 16)) return -LC_ERR_BADARG;
     if (dtype != LC_F32 && dtype != LC_BF16 && dtype != LC_F16 && dtype != LC_F64) return -LC_ERR_BADARG;
     const uintptr_t esize = dtype == LC_F32 ? 4 : dtype == LC_F64 ? 8 : 2;
@@ -365,6 +368,42 @@ lc_ssize encode_impl(const void* w, const void* w_ref, uint64_t n, int nbits, vo
     // call did not run to its end, is cleared first.
     if (!area->clean) { Timed t(kSlotReset, s); launch_reset(ws, group_words, chunk_maxexp, s); }
     area->clean = false;
+    // A short vector that the caller waits for: one launch, whose workgroups wait for each other (k_encode_one).  They fit the
+    // chip together as long as all such calls in progress have at most kOneResident workgroups per compute unit (two of
+    // k_encode_one fit one by their registers and LDS); a call beyond that, and one whose workgroups did not meet in time
+    // because other work held the chip, takes four kernels.  Whole calls, four kernels / one, us: fp32 2^14 31.7 / 29.6, 2^20
+    // 38.1 / 31.2, 2^22 44.2 / 37.0, 2^23 54.3 / 45.4; bf16 2^20 35.7 / 30.8, 2^23 45.7 / 41.3; with a cached table that holds,
+    // 2^16 55.9 / 29.5, 2^23 66.5 / 44.4.  Beyond that a chunk's deltas no longer fit the registers of a chip-wide grid.
+    const uint32_t nchunks = (uint32_t)num_chunks_of(n);
+    constexpr uint32_t kOneResident = 2;
+    if (try_one && !async && !staged && dtype != LC_F64 && nchunks >= 1 && nchunks <= (uint32_t)(ds->tune.num_cu * ds->tune.one_per_cu) &&
+        ds->one_blocks + nchunks <= kOneResident * (uint32_t)ds->tune.num_cu) {
+        Result& r = g_pinned[slot].enc;
+        r.status = LC_ERR_HIP;                                 // (stays so unless the workgroups met)
+        { Timed t(kSlotEncodeOne, s); launch_encode_one(w, w_ref, n, nbits, dtype, o, ws, chunk_bits, cache, result, ++g_epoch, (uint32_t)ds->tune.one_wait, s); }
+        LC_HIP(hipGetLastError());
+        if (!release(area, s)) return -LC_ERR_HIP;
+        area->clean = true;
+        ds->one_blocks += nchunks;
+        const bool serial = g_prof;
+        if (!serial) lock.unlock();
+        const hipError_t waited = hipStreamSynchronize(s);
+        if (!serial) lock.lock();
+        ds->one_blocks -= nchunks;
+        if (waited != hipSuccess) { (void)hipGetLastError(); area->clean = false; return -LC_ERR_HIP; }
+        if (r.status == LC_ERR_HIP) {
+            // they did not meet: what they left in the scratch area is cleared by the next call that takes it
+            area->clean = false;
+            free_slot(slot);
+            undo.armed = false;
+            lock.unlock();
+            return encode_impl(w, w_ref, n, nbits, out, dtype, cache, used, stream, async, false);
+        }
+        const int slots[] = {kSlotEncodeOne};
+        collect(slots, 1);
+        if (used) *used = (int)r.used_cache;
+        return r.status != LC_OK ? -(lc_ssize)r.status : (lc_ssize)r.bytes;
+    }
     // (binary64 with a cache: two sweeps, the second one coding with the cached lengths when k_table confirms them)
     const bool spec_sweep = cache && dtype != LC_F64;
     if (cache) { Timed t(kSlotSpecTable, s); launch_spec_table(ws, cache, n, nbits, dtype, group_words, s); }

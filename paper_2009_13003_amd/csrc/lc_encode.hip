@@ -45,6 +45,7 @@ __global__ void k_reset(Workspace* ws, u32* group_words, u32 ngroups, u32* chunk
     clear_encode_state(ws, group_words, ngroups, threadIdx.x, blockDim.x);
     clear_ext64(&ws->ext64, threadIdx.x, blockDim.x);
     clear_bucket_extremes(ws, threadIdx.x, blockDim.x);
+    if (threadIdx.x < 2) ws->one.arrived[threadIdx.x] = 0;
     for (u32 i = threadIdx.x; i < nchunks; i += blockDim.x) chunk_maxexp[i] = 0;
 }
 
@@ -1117,9 +1118,9 @@ struct PackWg {
     uint2 pair[256];                     // (symbol a, symbol b) -> {code of a followed by b, its length}
     u32 mn[kMaxSym * kMmCopies], mx[kMaxSym * kMmCopies];      // extremes of the delta bit patterns per symbol
     u32 bits[kWgWaves][kW];              // lengths of the parts
-    u32 overflow;                        // some part does not fit its area
-    u32 part[kWgWaves][kPartWords * kW]; // word k of lane l at [64 k + l]
+    alignas(16) u32 part[kWgWaves][kPartWords * kW]; // word k of lane l at [64 k + l]
     alignas(16) u32 payload[kPayloadWords];
+    u32 overflow;                        // some part does not fit its area
 };
 
 // A lane's part while it grows.
@@ -1143,17 +1144,9 @@ __device__ __forceinline__ void code_symbols(const u32 (&t)[8], PackWg& L, LaneP
     for (int i = 0; i < 4; ++i) S.append(p[i].x, p[i].y);
 }
 
-// Two rows of w and w_ref: the look-ups of the 8 elements are issued together.
-template <int DT>
-__device__ __forceinline__ void code_rows2(const typename Raw<DT>::type* a, const typename Raw<DT>::type* b, u32 K8, PackWg& L, LanePart& S) {
-    u32 u[8], t[8];
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-        float xa[4], xb[4];
-        unpack<DT>(a[k], xa); unpack<DT>(b[k], xb);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) u[4 * k + v] = delta_bits(xa[v], xb[v]);
-    }
+// Two rows' deltas: the look-ups of the 8 elements are issued together.
+__device__ __forceinline__ void code_deltas(const u32* u, u32 K8, PackWg& L, LanePart& S) {
+    u32 t[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) t[i] = L.sym8[u[i] >> 23];
     u32 tmin = t[0];
@@ -1167,6 +1160,28 @@ __device__ __forceinline__ void code_rows2(const typename Raw<DT>::type* a, cons
     code_symbols(t, L, S);
 }
 
+// Two rows of w and w_ref.
+template <int DT>
+__device__ __forceinline__ void code_rows2(const typename Raw<DT>::type* a, const typename Raw<DT>::type* b, u32 K8, PackWg& L, LanePart& S) {
+    u32 u[8];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        float xa[4], xb[4];
+        unpack<DT>(a[k], xa); unpack<DT>(b[k], xb);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) u[4 * k + v] = delta_bits(xa[v], xb[v]);
+    }
+    code_deltas(u, K8, L, S);
+}
+
+// The first `count` words of the payload to memory, in 16-byte vectors that are aligned to words only.
+__device__ __forceinline__ void copy_payload(u32* to, u32 count, const PackWg& L) {
+    typedef u32x4 __attribute__((aligned(4))) u32x4_word;
+    const u32 nvec = count / 4;
+    for (u32 i = threadIdx.x; i < nvec; i += kWgThreads) reinterpret_cast<u32x4_word*>(to)[i] = reinterpret_cast<const u32x4*>(L.payload)[i];
+    if (threadIdx.x < (count & 3)) to[4 * nvec + threadIdx.x] = L.payload[4 * nvec + threadIdx.x];
+}
+
 // The symbols of a lane's part, 4 bits each, the first in the low bits of s[0]; count of them.
 struct PartSymbols { u64 s[2]; u32 count; };
 
@@ -1174,7 +1189,7 @@ struct PartSymbols { u64 s[2]; u32 count; };
 // bit in the payload), so the parts are coded again straight to their places, in as many turns as windows of kPayloadWords
 // words hold the payload (3 at most).  Contains barriers; L.payload is cleared when it is called.
 // By one wavefront instead, a row at a time: 2^24 fp32 elements of 10 layers at 4 bits 143 us the call, 101 so.
-__device__ __forceinline__ void finish_long(const ChunkRef& ch, const PartSymbols& P, u32 o, u32 nwords, PackWg& L) {
+__device__ __forceinline__ void finish_long(u32* payload, const PartSymbols& P, u32 o, u32 nwords, PackWg& L) {
     const u32 t = threadIdx.x;
 #pragma unroll 1
     for (u32 base = 0; base < nwords; base += kPayloadWords) {
@@ -1209,10 +1224,52 @@ __device__ __forceinline__ void finish_long(const ChunkRef& ch, const PartSymbol
         }
         if (nb > 0) put((u32)(acc << (32 - nb)));
         __syncthreads();
-        const u32x4* from = reinterpret_cast<const u32x4*>(L.payload);
-        u32x4* to = reinterpret_cast<u32x4*>(ch.slot + kLaneBitsWords + base);
-        for (u32 i = t; i < (min(nwords - base, kPayloadWords) + 3) / 4; i += kWgThreads) to[i] = from[i];
+        copy_payload(payload + base, min(nwords - base, kPayloadWords), L);
         __syncthreads();
+    }
+}
+
+// Where the strings of a chunk go, once all parts are coded: known to every thread after part_places (which contains a barrier).
+struct PartPlaces {
+    u32 mine, o;             // this lane's part: its bits, and its first bit in the payload
+    u32 bits;                // the lane's whole string
+    u32 total, nwords;       // the chunk's payload in bits and in words
+    bool overflow;           // it does not fit the workgroup's areas
+};
+__device__ __forceinline__ PartPlaces part_places(LanePart& S, u32 v, PackWg& L) {
+    const u32 lane = lane_id();
+    if (S.nb > 0) S.put((u32)(S.acc << (32 - S.nb)));
+    PartPlaces P;
+    P.mine = 32 * S.nw + S.nb;
+    L.bits[v][lane] = P.mine;
+    if (P.mine > 32 * kPartWords) L.overflow = 1;
+    __syncthreads();
+    u32 before = 0;
+    P.bits = 0;
+#pragma unroll
+    for (u32 k = 0; k < kWgWaves; ++k) {
+        const u32 b = L.bits[k][lane];
+        before += k < v ? b : 0u;
+        P.bits += b;
+    }
+    const u32 incl = wave_incl_scan(P.bits);
+    P.total = read_lane(incl, kW - 1);
+    P.nwords = (P.total + 31) >> 5;
+    P.o = incl - P.bits + before;
+    P.overflow = L.overflow != 0 || P.nwords > kPayloadWords;
+    return P;
+}
+
+// The parts joined into the payload (cleared before); the caller's barrier follows.
+__device__ __forceinline__ void join_parts(const PartPlaces& P, u32 v, PackWg& L) {
+    const u32 sh = P.o & 31, W0 = P.o >> 5, have = (P.mine + 31) >> 5;
+    const u32 touched = P.mine ? ((P.o + P.mine - 1) >> 5) - W0 + 1 : 0;
+    u32 prev = 0;                                          // (a part of 7 words touches 8 of the payload)
+#pragma unroll
+    for (u32 j = 0; j <= kPartWords; ++j) {
+        const u32 w = j < have && j < kPartWords ? L.part[v][j * kW + lane_id()] : 0;
+        if (j < touched) atomicOr(&L.payload[W0 + j], __builtin_amdgcn_alignbit(prev, w, sh));
+        prev = w;
     }
 }
 
@@ -1221,35 +1278,14 @@ __device__ __forceinline__ void finish_long(const ChunkRef& ch, const PartSymbol
 template <typename Again>
 __device__ __forceinline__ void finish_parts(const ChunkRef& ch, LanePart& S, u32 v, PackWg& L, const Again& again) {
     const u32 t = threadIdx.x, lane = lane_id();
-    if (S.nb > 0) S.put((u32)(S.acc << (32 - S.nb)));
-    const u32 mine = 32 * S.nw + S.nb;
-    L.bits[v][lane] = mine;
-    if (mine > 32 * kPartWords) L.overflow = 1;
-    __syncthreads();
-    u32 before = 0, bits = 0;
-#pragma unroll
-    for (u32 k = 0; k < kWgWaves; ++k) {
-        const u32 b = L.bits[k][lane];
-        before += k < v ? b : 0u;
-        bits += b;
-    }
-    const u32 incl = wave_incl_scan(bits), total = read_lane(incl, kW - 1), nwords = (total + 31) >> 5, o = incl - bits + before;
+    const PartPlaces P = part_places(S, v, L);
+    const u32 nwords = P.nwords;
     if (v == 0) {
-        reinterpret_cast<uint16_t*>(ch.slot)[lane] = (uint16_t)bits;
-        if (lane == 0) { *ch.bits_at = total; atomicAdd(ch.group_at, kLaneBitsWords + nwords); }
+        reinterpret_cast<uint16_t*>(ch.slot)[lane] = (uint16_t)P.bits;
+        if (lane == 0) { *ch.bits_at = P.total; atomicAdd(ch.group_at, kLaneBitsWords + nwords); }
     }
-    if (L.overflow != 0 || nwords > kPayloadWords) { finish_long(ch, again(), o, nwords, L); return; }
-    {
-        const u32 sh = o & 31, W0 = o >> 5, have = (mine + 31) >> 5;
-        const u32 touched = mine ? ((o + mine - 1) >> 5) - W0 + 1 : 0;
-        u32 prev = 0;                                          // (a part of 7 words touches 8 of the payload)
-#pragma unroll
-        for (u32 j = 0; j <= kPartWords; ++j) {
-            const u32 w = j < have && j < kPartWords ? L.part[v][j * kW + lane] : 0;
-            if (j < touched) atomicOr(&L.payload[W0 + j], __builtin_amdgcn_alignbit(prev, w, sh));
-            prev = w;
-        }
-    }
+    if (P.overflow) { finish_long(ch.slot + kLaneBitsWords, again(), P.o, nwords, L); return; }
+    join_parts(P, v, L);
     __syncthreads();
     // the payload in whole vectors (what lies behind its end in the slot nobody reads)
     const u32x4* from = reinterpret_cast<const u32x4*>(L.payload);
@@ -1714,49 +1750,22 @@ __global__ __launch_bounds__(64) void k_spec_sweep(const void* __restrict__ w, c
 // resident anyway, one chunk's latency what counts) takes instead.
 constexpr u32 kPlaceWords = 1024, kPlaceWordsFew = 2048;
 
+// What the header says of symbol t, held by thread t (of 0 .. 15) of the workgroup that writes it; and of the whole.
+struct BlobSymbol { u32 codelen, kept; u64 cnt; u32 mn, mx; u64 mn64, mx64; };      // mn, mx / mn64, mx64: the mantissas' extremes
+struct BlobFacts { u32 status, K, k_E, max_len, used_cache, listed; u64 total_words; };
+
 // Representatives (Section 3.1.1: mean of the bucket's largest and smallest member, rounded once
 // to fp32, ties to even, done on the mantissas since both share a binade), the header, the last
-// offset entry, the result for the host; then the scratch state is cleared for the next call.
-// The header of one vector's blob and the call's outcome for the host, by a workgroup of 256 threads.  group_words: the
-// record sizes of the vector's groups of 64 chunks; their sum is the size of the chunk area.  Everything a thread needs
-// from memory is asked for before the first use of any of it (the workgroup runs beside a whole placement sweep: every
-// dependent round trip costs microseconds there).
-__device__ __forceinline__ void finalize_blob(uint8_t* out, EncState* ws, Result* host_result, TableCache* cache,
-                                              u64 n, int nbits, u32 nchunks, u32 dtype, const u32* group_words,
-                                              const Ext64* ext = nullptr, const u32* bucket_min = nullptr,
-                                              const u32* bucket_max = nullptr) {
+// offset entry, the result for the host; by a workgroup of at least 128 threads.
+__device__ __forceinline__ void write_header(uint8_t* out, const BlobSymbol& my, const BlobFacts& f, Result* host_result,
+                                             TableCache* cache, u64 n, int nbits, u32 nchunks, u32 dtype) {
     __shared__ u32 hdr[kHeaderBytes / 4];
-    __shared__ unsigned long long s_total;
     const u32 t = threadIdx.x;
-    const Table& T = ws->table;
-    u64 part = 0;
-    for (u32 g = t; g < (nchunks + 63) / 64; g += blockDim.x) part += group_words[g];
-    if (t == 0) s_total = 0;
-    // this thread's symbol (threads 0 .. 15): code, bucket, population, extremes
-    const u32 sym = t < kMaxSym ? t : 0;
-    const u32 my_codelen = T.codelen[sym], my_kept = T.kept[sym];
-    const u64 my_cnt = T.cnt[sym];
-    u32 mn = 0x7FFFFFu, mx = 0;
-    u64 mn64 = 0, mx64 = 0;
-    if (dtype != kF64) {
-#pragma unroll
-        for (u32 k = 0; k < kExtCopies; ++k) { mn = min(mn, ws->mmin[k][sym]); mx = max(mx, ws->mmax[k][sym]); }
-        // (an encode with staged keys: the extremes of every bucket were gathered by sweep 1)
-        if (bucket_min) { mn = bucket_min[my_kept & 511u] & 0x7FFFFFu; mx = bucket_max[my_kept & 511u] & 0x7FFFFFu; }
-    } else {
-        mn64 = ext->mmin[sym]; mx64 = ext->mmax[sym];
-    }
-    const u32 status = T.status, K = T.K, k_E = T.k_E, max_len = T.max_len;
-    const u32 spec_ok = ws->spec_ok, listed = ws->list_count;
     if (t < kHeaderBytes / 4) hdr[t] = 0;
     __syncthreads();
-    part = wave_sum64(part);
-    if (lane_id() == 0 && part) atomicAdd(&s_total, (unsigned long long)part);
-    __syncthreads();
-    const u64 total_words = s_total;
-    const bool ok = status == 0;
+    const bool ok = f.status == 0;
     const u64 area = chunk_area_of(nchunks);
-    const u64 total = ok ? area + 4 * total_words : kHeaderBytes;
+    const u64 total = ok ? area + 4 * f.total_words : kHeaderBytes;
     if (t == 0) {
         hdr[0] = 0x3142434Cu;                     // "LCB1"
         hdr[1] = 1u | (kHeaderBytes << 16);
@@ -1764,31 +1773,31 @@ __device__ __forceinline__ void finalize_blob(uint8_t* out, EncState* ws, Result
         hdr[4] = (u32)nbits;
         hdr[6] = kW; hdr[7] = kV; hdr[8] = kR;
         hdr[10] = (u32)total; hdr[11] = (u32)(total >> 32);
-        hdr[12] = status;
+        hdr[12] = f.status;
         hdr[15] = dtype;
-        if (ok) { hdr[5] = K; hdr[9] = nchunks; hdr[13] = k_E; hdr[14] = max_len; }
-        host_result->bytes = total; host_result->status = status; host_result->used_cache = spec_ok;
-        host_result->listed = listed; host_result->pad_r = 0;
-        if (cache && ok) { cache->valid = 1; cache->nbits = (u32)nbits; cache->K = K; cache->pad = 0; }
+        if (ok) { hdr[5] = f.K; hdr[9] = nchunks; hdr[13] = f.k_E; hdr[14] = f.max_len; }
+        host_result->bytes = total; host_result->status = f.status; host_result->used_cache = f.used_cache;
+        host_result->listed = f.listed; host_result->pad_r = 0;
+        if (cache && ok) { cache->valid = 1; cache->nbits = (u32)nbits; cache->K = f.K; cache->pad = 0; }
     }
     if (cache && ok && t < kMaxSym) {              // what this blob was coded with, for the next call
-        cache->kept[t] = t < K ? my_kept : 0;
-        cache->len[t] = t <= K ? (my_codelen & 31) : 0;
+        cache->kept[t] = t < f.K ? my.kept : 0;
+        cache->len[t] = t <= f.K ? (my.codelen & 31) : 0;
     }
-    if (ok && t <= K) {
-        const u32 len = my_codelen & 31;
+    if (ok && t <= f.K) {
+        const u32 len = my.codelen & 31;
         // representative = midrange of the bucket's extremes, rounded once to nearest even (Section 3.1.1):
         // halve the mantissa sum; an odd sum lies halfway between two mantissas and goes to the even one
         u32 bucket = 0xFFFFu, rep = 0;
-        if (t < K && dtype != kF64) {
-            bucket = my_kept;
-            const u32 sum = mn + mx;
+        if (t < f.K && dtype != kF64) {
+            bucket = my.kept;
+            const u32 sum = my.mn + my.mx;
             u32 mm = sum >> 1;
             if ((sum & 1) && (mm & 1)) ++mm;
             rep = (bucket << 23) | mm;
-        } else if (t < K) {                            // binary64: 52-bit mantissas, high half at header offset 320 + 4 t
-            bucket = my_kept;
-            const u64 sum = mn64 + mx64;
+        } else if (t < f.K) {                          // binary64: 52-bit mantissas, high half at header offset 320 + 4 t
+            bucket = my.kept;
+            const u64 sum = my.mn64 + my.mx64;
             u64 mm = sum >> 1;
             if ((sum & 1) && (mm & 1)) ++mm;
             const u64 rep64 = ((u64)bucket << 52) | mm;
@@ -1797,8 +1806,8 @@ __device__ __forceinline__ void finalize_blob(uint8_t* out, EncState* ws, Result
         }
         hdr[16 + 4 * t + 0] = bucket | (len << 16);
         hdr[16 + 4 * t + 1] = rep;
-        hdr[16 + 4 * t + 2] = (u32)my_cnt;
-        hdr[16 + 4 * t + 3] = (u32)(my_cnt >> 32);
+        hdr[16 + 4 * t + 2] = (u32)my.cnt;
+        hdr[16 + 4 * t + 3] = (u32)(my.cnt >> 32);
     }
     __syncthreads();
     if (t < kHeaderBytes / 4) reinterpret_cast<u32*>(out)[t] = hdr[t];
@@ -1806,9 +1815,42 @@ __device__ __forceinline__ void finalize_blob(uint8_t* out, EncState* ws, Result
         // last offset entry and the zero padding of the offset table
         u32* off_tab = reinterpret_cast<u32*>(out + kHeaderBytes);
         const u32 entries = (u32)((area - kHeaderBytes) / 4);
-        if (t == 0) off_tab[nchunks] = (u32)total_words;
+        if (t == 0) off_tab[nchunks] = (u32)f.total_words;
         if (t >= 1 && t < 4 && nchunks + t < entries) off_tab[nchunks + t] = 0;
     }
+}
+
+// The header of one vector's blob and the call's outcome for the host, by a workgroup of 256 threads.  group_words: the
+// record sizes of the vector's groups of 64 chunks; their sum is the size of the chunk area.  Everything a thread needs
+// from memory is asked for before the first use of any of it (the workgroup runs beside a whole placement sweep: every
+// dependent round trip costs microseconds there).
+__device__ __forceinline__ void finalize_blob(uint8_t* out, EncState* ws, Result* host_result, TableCache* cache,
+                                              u64 n, int nbits, u32 nchunks, u32 dtype, const u32* group_words,
+                                              const Ext64* ext = nullptr, const u32* bucket_min = nullptr,
+                                              const u32* bucket_max = nullptr) {
+    __shared__ unsigned long long s_total;
+    const u32 t = threadIdx.x;
+    const Table& T = ws->table;
+    u64 part = 0;
+    for (u32 g = t; g < (nchunks + 63) / 64; g += blockDim.x) part += group_words[g];
+    if (t == 0) s_total = 0;
+    const u32 sym = t < kMaxSym ? t : 0;
+    BlobSymbol my = {T.codelen[sym], T.kept[sym], T.cnt[sym], 0x7FFFFFu, 0, 0, 0};
+    if (dtype != kF64) {
+#pragma unroll
+        for (u32 k = 0; k < kExtCopies; ++k) { my.mn = min(my.mn, ws->mmin[k][sym]); my.mx = max(my.mx, ws->mmax[k][sym]); }
+        // (an encode with staged keys: the extremes of every bucket were gathered by sweep 1)
+        if (bucket_min) { my.mn = bucket_min[my.kept & 511u] & 0x7FFFFFu; my.mx = bucket_max[my.kept & 511u] & 0x7FFFFFu; }
+    } else {
+        my.mn64 = ext->mmin[sym]; my.mx64 = ext->mmax[sym];
+    }
+    BlobFacts f = {T.status, T.K, T.k_E, T.max_len, ws->spec_ok, ws->list_count, 0};
+    __syncthreads();
+    part = wave_sum64(part);
+    if (lane_id() == 0 && part) atomicAdd(&s_total, (unsigned long long)part);
+    __syncthreads();
+    f.total_words = s_total;
+    write_header(out, my, f, host_result, cache, n, nbits, nchunks, dtype);
     __syncthreads();
 }
 
@@ -1944,6 +1986,254 @@ __global__ __launch_bounds__(256) void k_place(uint8_t* out, Workspace* ws, cons
     if (c < nchunks && lane_id() == 0) chunk_maxexp[maxexp_slot(c)] = 0;
     // the last workgroup may hold idle wavefronts
     place_chunk<PW>(out, ws, chunk_bits, group_words, prov, slot_words, nchunks, c, c < nchunks && ws->table.status == 0);
+}
+
+// ----------------------------------------------------------------------------- k_encode_one
+// A short vector in one launch: a workgroup per chunk, all of them resident together, that keeps its deltas in registers
+// from the count to the code.  What such a call costs in four kernels is not bytes but their starts, the gaps between them
+// and every chunk's round trips to memory (chunk maxima, table, slot, slot again): 2^20 fp32 elements 7.0 + 4.6 + 7.9 + 3.7
+// us and three gaps, 38.1 us the call (30.4 so).  Here the workgroups meet twice: when all counts are in (each then builds the table for itself, from
+// the same counts), and when all record sizes are known (each then knows where its record goes).
+//
+// The meeting.  Everything that passes between workgroups goes through agent-scope atomic operations, whose completion each
+// waits for before it arrives (no fence: writing back the L2 of a die from every workgroup costs more than the launches
+// saved).  A workgroup may wait for one that has not started, because others' kernels hold the chip: the host launches
+// this kernel only while all workgroups of such calls fit the chip together, and the wait is bounded.  When it is given up, that
+// is one atomic decision for all (the first to change the flag, to "all here" or to "given up", is right); the header's
+// workgroup then does not report, and the host runs the call in four kernels.
+struct GridMeeting {
+    OneSync* sync;
+    u64 tag;                 // of this call; the lowest bit says "given up"
+    u32 count, limit;        // workgroups of the grid; how often to look
+    // the flag's value once it belongs to this call, `mine` if nobody has set it yet (by one thread)
+    __device__ __forceinline__ u64 settle(u32 which, u64 mine) const {
+        u64 seen = __hip_atomic_load(&sync->flag[which], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        while ((seen | 1) != (tag | 1)) {        // (only this call's workgroups write it meanwhile: at most two turns)
+            if (__hip_atomic_compare_exchange_strong(&sync->flag[which], &seen, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return mine;
+        }
+        return seen;
+    }
+    __device__ __forceinline__ void arrive(u32 which) const {        // by one thread, behind the others' waits for their own operations
+        if (__hip_atomic_fetch_add(&sync->arrived[which], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == count) {
+            __hip_atomic_store(&sync->arrived[which], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            settle(which, tag);
+        }
+    }
+    __device__ __forceinline__ bool wait(u32 which) const {          // by the same thread; whether all are here
+        for (u32 i = 0; i < limit; ++i) {
+            const u64 seen = __hip_atomic_load(&sync->flag[which], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if ((seen | 1) == (tag | 1)) return seen == tag;
+            __builtin_amdgcn_s_sleep(1);
+        }
+        return settle(which, tag | 1) == tag;
+    }
+};
+__device__ __forceinline__ void wait_own_operations() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+template <typename T> __device__ __forceinline__ T load_shared(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
+// A cached table's lengths (lc_encode_cached; see k_spec_table), by one wavefront, lane j holding symbol j: whether the cache
+// is usable.
+__device__ __forceinline__ bool cached_table(const TableCache* cache, int nbits, u32* kept, u32* len) {
+    const u32 lane = lane_id(), K = cache->K;
+    const u32 kmax = (1u << nbits) - 1;
+    if (cache->valid != 1 || cache->nbits != (u32)nbits || K > kmax) return false;
+    const u32 b = lane < K ? cache->kept[lane] : 0u, e = b & 255u, l = lane <= K ? cache->len[lane] : 0u;
+    const u32 order = (e << 1) | (1u - ((b >> 8) & 1u));             // larger exponent first, + before -
+    const u32 before = __shfl_up(order, 1, 64);
+    bool bad = lane < K && (b >= 512u || e == 0 || e == 255u || (lane > 0 && order >= before));
+    bad = bad || l > 15;
+    const u32 active = (u32)__popcll(__ballot(l != 0)), kraft = wave_sum32(l && l <= 15 ? 1u << (15 - l) : 0u);
+    if (__any(bad) || (active >= 2 && kraft != (1u << 15)) || (active == 1 && kraft != (1u << 14))) return false;
+    *kept = b; *len = l;
+    return true;
+}
+
+constexpr u32 kOneCopies = 8;       // copies of the bucket counts in memory: a workgroup adds to one of them (Ext64::hist, which only
+                                    // binary64 calls use otherwise, and which they leave cleared as well)
+static_assert(kOneCopies * 512 == kBuckets64, "the copies fill Ext64::hist");
+struct OneArgs {
+    const void* w; const void* w_ref; u64 n;
+    uint8_t* out; Workspace* ws; u32* record_words; TableCache* cache; Result* host_result;
+    u64 tag; u32 nchunks, limit;
+    int nbits, aligned;
+};
+
+template <int DT>
+__global__ __launch_bounds__(kWgThreads, 4) void k_encode_one(OneArgs a) {
+    typedef typename Raw<DT>::type raw_t;
+    __shared__ PackWg L;
+    __shared__ TableLds<8> S;
+    __shared__ u32 s_go, s_status, s_k, s_max_len, s_reuse, s_cached, s_cached_kept[kMaxSym], s_cached_len[kMaxSym];
+    __shared__ u32 s_before[kWgWaves], s_all[kWgWaves];
+    Workspace* ws = a.ws;
+    const u64 n = a.n;
+    const u32 t = threadIdx.x, lane = lane_id(), v = __builtin_amdgcn_readfirstlane(t >> 6), c = blockIdx.x, first_row = kWgRows * v;
+    const bool full = a.aligned && (u64)(c + 1) * kChunk <= n;
+    const GridMeeting meet = {&ws->one, a.tag, a.nchunks, a.limit};
+    const u32 xcopy = c % kOneCopies;
+    // ---- this wavefront's 8 rows, as deltas
+    u32 u[kWgRows * kV];
+    {
+        raw_t A[kWgRows], B[kWgRows];
+        if (full) {
+#pragma unroll
+            for (u32 k = 0; k < kWgRows; ++k) { A[k] = load_raw<DT>(a.w, row_at(c, first_row + k)); B[k] = load_raw<DT>(a.w_ref, row_at(c, first_row + k)); }
+        } else {
+#pragma unroll
+            for (u32 k = 0; k < kWgRows; ++k) { A[k] = load_raw_guarded<DT>(a.w, row_at(c, first_row + k), n); B[k] = load_raw_guarded<DT>(a.w_ref, row_at(c, first_row + k), n); }
+        }
+        // the counts of this chunk, 8 copies in LDS (as in k_hist), where the parts and the payload go later
+        static_assert(sizeof(L.part) + sizeof(L.payload) >= 4 * 512 * kHistCopies && offsetof(PackWg, payload) == offsetof(PackWg, part) + sizeof(L.part), "room for the counts");
+        u32* h = &L.part[0][0];
+        for (u32 i = t; i < 512 * kHistCopies; i += kWgThreads) h[i] = 0;
+        if (v == 1 && a.cache) {
+            u32 kept = 0, len = 0;
+            const bool ok = cached_table(a.cache, a.nbits, &kept, &len);
+            if (lane < kMaxSym) { s_cached_kept[lane] = kept; s_cached_len[lane] = len; }
+            if (lane == 0) s_cached = ok ? a.cache->K + 1 : 0;
+        }
+        __syncthreads();
+#pragma unroll
+        for (u32 k = 0; k < kWgRows; ++k) {
+            float xa[4], xb[4];
+            unpack<DT>(A[k], xa); unpack<DT>(B[k], xb);
+#pragma unroll
+            for (u32 e = 0; e < kV; ++e) {
+                u[kV * k + e] = delta_bits(xa[e], xb[e]);
+                if (full || row_at(c, first_row + k) + e < n) atomicAdd(&h[(u[kV * k + e] >> 23) * kHistCopies + (lane & (kHistCopies - 1))], 1u);
+            }
+        }
+        __syncthreads();
+        u32 sum = 0;
+#pragma unroll
+        for (u32 k = 0; k < kHistCopies; ++k) sum += h[t * kHistCopies + k];
+        if (sum) atomicAdd(&ws->ext64.hist[xcopy * 512 + t], (u64)sum);
+        wait_own_operations();
+        __syncthreads();
+    }
+    // ---- all counts are in
+    if (t == 0) { meet.arrive(0); s_go = meet.wait(0) ? 1u : 0u; }
+    L.mn[t] = 0xFFFFFFFFu; L.mx[t] = 0;
+    if (t == 0) L.overflow = 0;
+    for (u32 i = t; i < kPayloadWords; i += kWgThreads) L.payload[i] = 0;
+    __syncthreads();
+    if (!s_go) return;
+    const u32 kmax = (1u << a.nbits) - 1;
+    u64 part[kOneCopies], cnt[1] = {0};
+#pragma unroll
+    for (u32 k = 0; k < kOneCopies; ++k) part[k] = load_shared(&ws->ext64.hist[k * 512 + bucket_at<8>(t)]);
+#pragma unroll
+    for (u32 k = 0; k < kOneCopies; ++k) cnt[0] += part[k];
+    const u32 candidates = rank_buckets<8>(S, cnt, kmax), K = candidates < kmax ? candidates : kmax;
+    __syncthreads();
+    if (v == 0) {
+        // the code, as in table_build
+        const u64 own = symbol_count(S.cnt, K, n);
+        const u32 nl = (u32)__popcll(__ballot(own != 0));
+        u32 len = 0;
+        bool reuse = false;
+        if (a.cache && s_cached != 0) {
+            const u32 cached_len = lane <= K && lane < kMaxSym ? s_cached_len[lane] : 0u;
+            const bool differs = (lane < K && s_cached_kept[lane] != S.kept[lane]) || (lane <= K && (cached_len != 0) != (own != 0));
+            const u64 payload_bits = wave_sum64(own * cached_len);
+            reuse = S.nonfinite == 0 && s_cached == K + 1 && !__any(differs) && payload_bits <= n * (u64)a.nbits;
+            if (reuse) len = cached_len;
+        }
+        if (!reuse && nl == 1) len = own != 0 ? 1u : 0u;
+        if (!reuse && nl >= 2) len = code_lengths((u32)own);
+        const u32 code = canonical_code(len), max_len = wave_max_u32(len);
+        if (lane < kMaxSym) L.codelen[lane] = lane <= K ? ((code << 5) | len) : 0u;
+        if (lane == K) S.cnt[lane] = own;
+        if (lane == 0) { s_max_len = max_len; s_reuse = reuse ? 1u : 0u; }
+    }
+    L.sym8[t] = (uint8_t)((S.sym[t] == 0xFF ? K : S.sym[t]) << 3);
+    __syncthreads();
+    if (t < 256) {
+        const u32 ca = L.codelen[t >> 4], cb = L.codelen[t & 15];
+        L.pair[t] = make_uint2(((ca >> 5) << (cb & 31)) | (cb >> 5), (ca & 31) + (cb & 31));
+    }
+    __syncthreads();
+    const bool finite = S.nonfinite == 0;
+    const u32 K8 = K << 3;
+    // ---- this chunk's code (of a vector with a delta that is not finite there is none)
+    LanePart P;
+    P.start(L, v);
+    if (finite) {
+        if (full) {
+#pragma unroll
+            for (u32 i = 0; i < kWgRows * kV; i += 8) code_deltas(u + i, K8, L, P);
+        } else {
+#pragma unroll
+            for (u32 k = 0; k < kWgRows; ++k) {
+#pragma unroll
+                for (u32 e = 0; e < kV; ++e) {
+                    if (row_at(c, first_row + k) + e < n) {
+                        const u32 x = u[kV * k + e], sy8 = L.sym8[x >> 23], cl = L.codelen[sy8 >> 3];
+                        const u32 at = sy8 * (kMmCopies / 8) + (lane & (kMmCopies - 1));
+                        atomicMin(&L.mn[at], x); atomicMax(&L.mx[at], x);
+                        P.append(cl >> 5, cl & 31);
+                    }
+                }
+            }
+        }
+    }
+    const PartPlaces at = part_places(P, v, L);
+    {
+        // the extremes: thread t holds copy t mod 32 of symbol t / 32
+        u32 mn = L.mn[t], mx = L.mx[t];
+#pragma unroll
+        for (int d = kMmCopies / 2; d >= 1; d >>= 1) { mn = min(mn, (u32)__shfl_xor(mn, d, 64)); mx = max(mx, (u32)__shfl_xor(mx, d, 64)); }
+        const u32 sym = t / kMmCopies, copy = c % kExtCopies;
+        if (t % kMmCopies == 0 && sym < K && mn <= mx) { atomicMin(&ws->mmin[copy][sym], mn & 0x7FFFFFu); atomicMax(&ws->mmax[copy][sym], mx & 0x7FFFFFu); }
+    }
+    if (t == 0) __hip_atomic_store(&a.record_words[c], kLaneBitsWords + at.nwords, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    wait_own_operations();
+    __syncthreads();
+    // ---- all sizes and extremes are known
+    if (t == 0) meet.arrive(1);
+    if (!at.overflow) join_parts(at, v, L);
+    if (t == 0) s_go = meet.wait(1) ? 1u : 0u;
+    __syncthreads();
+    if (!s_go) return;
+    u32 before = 0, all = 0;
+    for (u32 i = t; i < a.nchunks; i += kWgThreads) { const u32 words = load_shared(&a.record_words[i]); all += words; before += i < c ? words : 0u; }
+    before = wave_sum32(before); all = wave_sum32(all);
+    if (lane == 0) { s_before[v] = before; s_all[v] = all; }
+    __syncthreads();
+    before = 0; all = 0;
+#pragma unroll
+    for (u32 k = 0; k < kWgWaves; ++k) { before += s_before[k]; all += s_all[k]; }
+    if (finite) {
+        u32* rec = reinterpret_cast<u32*>(a.out + chunk_area_of(a.nchunks)) + before;
+        if (v == 0) reinterpret_cast<uint16_t*>(rec)[lane] = (uint16_t)at.bits;
+        if (t == 0) reinterpret_cast<u32*>(a.out + kHeaderBytes)[c] = before;
+        if (!at.overflow) copy_payload(rec + kLaneBitsWords, at.nwords, L);
+        else {
+            PartSymbols Q;
+            Q.count = 0;
+#pragma unroll
+            for (u32 i = 0; i < kWgRows * kV; ++i) {
+                if (i % 16 == 0) Q.s[i / 16] = 0;
+                Q.s[i / 16] |= (u64)(L.sym8[u[i] >> 23] >> 3) << (4 * (i % 16));
+                Q.count += row_at(c, first_row + i / kV) + i % kV < n ? 1u : 0u;
+            }
+            finish_long(rec + kLaneBitsWords, Q, at.o, at.nwords, L);
+        }
+    }
+    if (c != 0) return;
+    // ---- the first workgroup: the header, the outcome, and the scratch state as the next call expects it (the others are
+    // through with the counts, and only it reads the extremes)
+    const u32 sym = t < kMaxSym ? t : 0;
+    BlobSymbol my = {L.codelen[sym], S.kept[sym], S.cnt[sym], 0x7FFFFFu, 0, 0, 0};
+    if (t < kMaxSym) {
+#pragma unroll
+        for (u32 k = 0; k < kExtCopies; ++k) { my.mn = min(my.mn, load_shared(&ws->mmin[k][sym])); my.mx = max(my.mx, load_shared(&ws->mmax[k][sym])); }
+    }
+    const BlobFacts f = {finite ? 0u : 2u, K, candidates + S.zero_class, s_max_len, s_reuse, a.nchunks, all};
+    write_header(a.out, my, f, a.host_result, a.cache, n, a.nbits, a.nchunks, (u32)DT);
+    for (u32 i = t; i < kBuckets64; i += kWgThreads) ws->ext64.hist[i] = 0;
+    __syncthreads();
+    clear_extremes(ws, t, kWgThreads);
 }
 
 // ----------------------------------------------------------------------------- batched encode
@@ -2164,6 +2454,16 @@ void launch_pack_keys(const void* w, const void* w_ref, uint64_t n, Workspace* w
     if (nchunks == 0) return;
     hipLaunchKernelGGL(k_pack_keys, dim3((u32)nchunks), dim3(kWgThreads), 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, chunk_maxexp, chunk_list,
                        keys, prov, slot_words);
+}
+
+void launch_encode_one(const void* w, const void* w_ref, uint64_t n, int nbits, int dtype, uint8_t* out, Workspace* ws, uint32_t* record_words,
+                       TableCache* cache, Result* host_result, uint64_t epoch, uint32_t limit, hipStream_t s) {
+    const u32 nchunks = (u32)num_chunks_of(n);
+    const OneArgs a = {w, w_ref, (u64)n, out, ws, record_words, cache, host_result, (u64)epoch << 1, nchunks, limit, nbits,
+                       aligned_rows(w, dtype) && aligned_rows(w_ref, dtype) ? 1 : 0};
+    if (dtype == kBF16) hipLaunchKernelGGL(k_encode_one<kBF16>, dim3(nchunks), dim3(kWgThreads), 0, s, a);
+    else if (dtype == kF16) hipLaunchKernelGGL(k_encode_one<kF16>, dim3(nchunks), dim3(kWgThreads), 0, s, a);
+    else hipLaunchKernelGGL(k_encode_one<kF32>, dim3(nchunks), dim3(kWgThreads), 0, s, a);
 }
 
 // chunk_list: where to list the chunks sweep 2 has to read (chunk_maxexp then holds what k_hist recorded), or null

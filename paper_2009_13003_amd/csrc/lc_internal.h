@@ -108,6 +108,14 @@ struct Ext64 {
     uint8_t symlen_of_bucket[kBuckets64];
 };
 
+// Where the workgroups of a short encode meet (k_encode_one): how many have arrived (zero between calls), and what was
+// decided, tagged with the call.  Arrivals and the flag that is looked at meanwhile lie in lines of their own.
+struct OneSync {
+    unsigned long long flag[2];
+    uint32_t pad_f[28];
+    uint32_t arrived[2], pad_a[2];
+};
+
 struct Workspace : EncState {
     unsigned long long dec_status;   // (epoch << 8) | lc_status, raised with atomicMax
     DecSet dec_set[kMaxSets];        // one per blob of the call
@@ -115,6 +123,7 @@ struct Workspace : EncState {
     // An encode with staged keys: smallest / largest delta bit pattern of every (sign, exponent) bucket, gathered by
     // sweep 1 (which is then the only sweep that sees the mantissas).  Left cleared (all ones / zero) like the rest.
     uint32_t bucket_min[512], bucket_max[512];
+    OneSync one;
 };
 
 constexpr size_t kWorkspaceFixed = (sizeof(Workspace) + 255) / 256 * 256;
@@ -132,7 +141,7 @@ __host__ __device__ inline uint32_t slot_words_of(int nbits) { return kLaneBitsW
 __host__ __device__ inline uint64_t chunk_area_of(uint64_t nchunks) { return kHeaderBytes + (4 * (nchunks + 1) + 15) / 16 * 16; }
 
 enum Slot { kSlotReset = 0, kSlotHist, kSlotTable, kSlotPack, kSlotPlace, kSlotSpecTable, kSlotSpecSweep,
-            kSlotDecCheck, kSlotDecode, kSlotDecodeFused, kSlotHistKeys, kSlotPackKeys, kSlotVerify, kNumSlots };
+            kSlotDecCheck, kSlotDecode, kSlotDecodeFused, kSlotHistKeys, kSlotPackKeys, kSlotVerify, kSlotEncodeOne, kNumSlots };
 
 // Launch shapes; defaults chosen by measurement, overridable through LC_TUNE_* environment
 // variables (read once) for sweeps.
@@ -145,6 +154,8 @@ struct Tuning {
     int unlisted_per_cu = 4;           // a call of at most this many chunks of 4-byte elements (half of 2-byte) per compute unit does
                                        // without a list of chunks to read (below 16: see stage_keys)
     int batch_unlisted_per_cu = 8;     // ... a batched call
+    int one_per_cu = 2;                // chunks per compute unit up to which a call is encoded in one launch (0: never)
+    int one_wait = 4096;               // how often its workgroups look for each other before they give up
     int spec_waves_per_cu = 8;         // of the single sweep of the cached encode (what its LDS and registers allow)
     int batch_waves_per_cu = 8;        // of the batch kernels
     int decode_blocks_per_cu = 9;      // ... of a long restore (LDS lets 2 run at once; more, smaller shares even out unlike chunks)
@@ -183,6 +194,10 @@ bool pack_needs_list(uint64_t n, int dtype, const Tuning& tune);
 void launch_place(uint8_t* out, Workspace* ws, const uint32_t* chunk_bits, const uint32_t* group_words,
                   const uint32_t* prov, uint32_t slot_words, uint64_t n, uint32_t* chunk_maxexp, Result* host_result,
                   TableCache* cache, int nbits, int dtype, bool staged, hipStream_t s);
+// A whole encode of at most tune.one_per_cu chunks per compute unit.  host_result is written only if the workgroups met.
+// epoch: of this call, never used before on this scratch area; record_words: one word per chunk of scratch.
+void launch_encode_one(const void* w, const void* w_ref, uint64_t n, int nbits, int dtype, uint8_t* out, Workspace* ws, uint32_t* record_words,
+                       TableCache* cache, Result* host_result, uint64_t epoch, uint32_t limit, hipStream_t s);
 // One tensor of a batched call (lc_encode_batch): every tensor has its own EncState, blob and run of
 // chunks; chunks, groups of 64 chunks and slots of all tensors are numbered through ("dense" indices).
 struct Seg {
