@@ -31,6 +31,7 @@ struct Area {
     hipEvent_t idle = nullptr;    // recorded behind the last call that used it
     bool clean = false;           // its encode state is known to be cleared
     uint64_t stamp = 0;           // when it was last taken
+    uint64_t met[kMeetLines] = {};   // what its counters of k_encode_one stand at, if it is clean
 };
 
 struct DeviceState {
@@ -366,21 +367,21 @@ lc_ssize encode_impl(const void* w, const void* w_ref, uint64_t n, int nbits, vo
     Result* result = &g_pinned_dev[slot].enc;
     // Every call leaves the encode state cleared behind it; a fresh scratch area, or one whose last
     // call did not run to its end, is cleared first.
-    if (!area->clean) { Timed t(kSlotReset, s); launch_reset(ws, group_words, chunk_maxexp, s); }
+    if (!area->clean) { Timed t(kSlotReset, s); launch_reset(ws, group_words, chunk_maxexp, s); memset(area->met, 0, sizeof(area->met)); }
     area->clean = false;
     // A short vector that the caller waits for: one launch, whose workgroups wait for each other (k_encode_one).  They fit the
     // chip together as long as all such calls in progress have at most kOneResident workgroups per compute unit (two of
     // k_encode_one fit one by their registers and LDS); a call beyond that, and one whose workgroups did not meet in time
-    // because other work held the chip, takes four kernels.  Whole calls, four kernels / one, us: fp32 2^14 31.7 / 29.6, 2^20
-    // 38.1 / 31.2, 2^22 44.2 / 37.0, 2^23 54.3 / 45.4; bf16 2^20 35.7 / 30.8, 2^23 45.7 / 41.3; with a cached table that holds,
-    // 2^16 55.9 / 29.5, 2^23 66.5 / 44.4.  Beyond that a chunk's deltas no longer fit the registers of a chip-wide grid.
+    // because other work held the chip, takes four kernels.  Whole calls, four kernels / one, us: fp32 2^14 34.1 / 27.3, 2^20
+    // 40.8 / 29.0, 2^22 46.6 / 30.1, 2^23 56.6 / 45.0; bf16 2^20 38.2 / 28.0, 2^23 48.3 / 42.5; with a cached table that holds,
+    // 2^16 57.0 / 27.8, 2^23 66.5 / 45.7.  Beyond that a chunk's deltas no longer fit the registers of a chip-wide grid.
     const uint32_t nchunks = (uint32_t)num_chunks_of(n);
     constexpr uint32_t kOneResident = 2;
     if (try_one && !async && !staged && dtype != LC_F64 && nchunks >= 1 && nchunks <= (uint32_t)(ds->tune.num_cu * ds->tune.one_per_cu) &&
         ds->one_blocks + nchunks <= kOneResident * (uint32_t)ds->tune.num_cu) {
         Result& r = g_pinned[slot].enc;
         r.status = LC_ERR_HIP;                                 // (stays so unless the workgroups met)
-        { Timed t(kSlotEncodeOne, s); launch_encode_one(w, w_ref, n, nbits, dtype, o, ws, chunk_bits, cache, result, ++g_epoch, (uint32_t)ds->tune.one_wait, s); }
+        { Timed t(kSlotEncodeOne, s); launch_encode_one(w, w_ref, n, nbits, dtype, o, ws, chunk_bits, cache, result, area->met, (uint32_t)ds->tune.one_wait, s); }
         LC_HIP(hipGetLastError());
         if (!release(area, s)) return -LC_ERR_HIP;
         area->clean = true;

@@ -61,6 +61,33 @@ __device__ __forceinline__ u32 wave_max_u32(u32 v) {
 __device__ __forceinline__ u32 read_lane(u32 v, u32 l) { return (u32)__builtin_amdgcn_readlane((int)v, (int)l); }
 __device__ __forceinline__ u64 read_lane64(u64 v, u32 l) { return ((u64)read_lane((u32)(v >> 32), l) << 32) | read_lane((u32)v, l); }
 
+// The sum over lanes l, l ^ 16, l ^ 32 and l ^ 48, in all four (gfx950: rows and halves change places without LDS).
+__device__ __forceinline__ u32 rows_sum(u32 v) {
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = a[0] + a[1];
+    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return b[0] + b[1];
+}
+
+// The value of lane l, which may differ from lane to lane.
+__device__ __forceinline__ u32 gather_lane(u32 v, u32 l) { return (u32)__builtin_amdgcn_ds_bpermute((int)(l * 4), (int)v); }
+
+// Canonical codes by one wavefront, lane j < 16 holding the length of symbol j (0: none): a code, left-justified, is the sum
+// of the shares of the code space of the symbols before it, shorter ones first and by index within a length.  Each row of 16
+// lanes takes a quarter of the symbols that may come before.  (lanes 16 and up: nothing)
+__device__ __forceinline__ u32 canonical_code(u32 len) {
+    const u32 lane = lane_id(), j = lane & 15;
+    const u32 place = len ? len * 16 + lane : 0xFFFFu;
+    const u32 mine = gather_lane(place, j);
+    u32 before[4], sum = 0;
+#pragma unroll
+    for (u32 r = 0; r < 4; ++r) before[r] = gather_lane(place, (lane >> 4) * 4 + r);
+#pragma unroll
+    for (u32 r = 0; r < 4; ++r) sum += before[r] < mine ? 0x8000u >> (before[r] >> 4) : 0u;
+    sum = rows_sum(sum);
+    return len ? sum >> (15 - len) : 0u;
+}
+
 __device__ __forceinline__ u32 wave_sum32(u32 v) { return read_lane(wave_incl_scan(v), kW - 1); }
 
 // delta of Algorithm 1 line 4: one IEEE binary32 subtraction (never fused or reassociated).

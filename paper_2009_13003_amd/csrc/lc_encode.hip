@@ -27,7 +27,6 @@ __device__ __forceinline__ void clear_extremes(EncState* ws, u32 tid, u32 nthr) 
 
 __device__ __forceinline__ void clear_encode_state(EncState* ws, u32* group_words, u32 ngroups, u32 tid, u32 nthr) {
     for (u32 i = tid; i < ngroups; i += nthr) group_words[i] = 0;
-    for (u32 i = tid; i < 512; i += nthr) ws->hist[i] = 0;
     clear_extremes(ws, tid, nthr);
     if (tid == 0) { ws->spec = 0; ws->spec_ok = 0; ws->list_count = 0; }
 }
@@ -45,14 +44,15 @@ __global__ void k_reset(Workspace* ws, u32* group_words, u32 ngroups, u32* chunk
     clear_encode_state(ws, group_words, ngroups, threadIdx.x, blockDim.x);
     clear_ext64(&ws->ext64, threadIdx.x, blockDim.x);
     clear_bucket_extremes(ws, threadIdx.x, blockDim.x);
-    if (threadIdx.x < 2) ws->one.arrived[threadIdx.x] = 0;
+    for (u32 i = threadIdx.x; i < 512; i += blockDim.x) ws->hist[i] = 0;       // (where k_encode_one's workgroups meet)
     for (u32 i = threadIdx.x; i < nchunks; i += blockDim.x) chunk_maxexp[i] = 0;
 }
 
 // The same for a scratch area that only ever serves calls of at most `nchunks` chunks (their entries of the
 // transposed maxima, their groups of 64 chunks): what such an area needs cleared before every call of its own.
-__global__ void k_reset_chunks(EncState* ws, u32* group_words, u32 ngroups, u32* chunk_maxexp, u32 nchunks) {
+__global__ void k_reset_chunks(Workspace* ws, u32* group_words, u32 ngroups, u32* chunk_maxexp, u32 nchunks) {
     clear_encode_state(ws, group_words, ngroups, threadIdx.x, blockDim.x);
+    clear_ext64(&ws->ext64, threadIdx.x, blockDim.x);
     for (u32 c = threadIdx.x; c < nchunks; c += blockDim.x) chunk_maxexp[maxexp_slot(c)] = 0;
 }
 
@@ -60,7 +60,7 @@ __global__ void k_reset_chunks(EncState* ws, u32* group_words, u32 ngroups, u32*
 // Sweep 1 (Section 3.1.1, exponent-based quantization): population of each of the 2^9
 // (sign, exponent) buckets.  LDS histogram replicated 8 times (copy = lane & 7, copies
 // of one bin in different banks) so that lanes hitting the same popular bucket rarely
-// collide; merged into 64-bit global counters once per workgroup.
+// collide; merged into 64-bit global counters once per workgroup (one of kHistCells copies of them).
 constexpr int kHistCopies = 8;
 
 // One 16-byte unit = EPU consecutive elements (4 fp32, 8 bf16 / fp16): counting does not care which lane
@@ -225,7 +225,7 @@ __global__ __launch_bounds__(1024) void k_hist(const void* __restrict__ w, const
             if (KEYS) { lo = min(lo, mn[bk * kHistCopies + k]); hi = max(hi, mx[bk * kHistCopies + k]); }
         }
         if (sum) {
-            atomicAdd(&ws->hist[bk], (u64)sum);
+            atomicAdd(&ws->ext64.hist[(blockIdx.x % kHistCells) * 512 + bk], (u64)sum);
             if (KEYS) { atomicMin(&ws->bucket_min[bk], lo); atomicMax(&ws->bucket_max[bk], hi); }
         }
     }
@@ -340,8 +340,8 @@ __global__ __launch_bounds__(1024) void k_hist64(const void* __restrict__ w, con
 // Priority promotion (Section 3.1.1) and the Huffman table (Section 3.1.2): one workgroup and, where a chain of single
 // steps is left, its first wavefront.  Nothing here is bound by bytes; it is the latency of that chain, which every encode
 // waits for.  So the buckets are ranked by all threads at once, and the chain keeps to scalar registers: see code_lengths.
-// One wavefront with 64-bit weights, ranking included, against this: 2^20 fp32 at 3 bits 8.1 -> 4.6 us, a 2^27 bf16 vector
-// at 4 bits (with its list of chunks) 14.1 -> 9.1 us, 161 tensors 11.9 -> 6.2 us.
+// One wavefront with 64-bit weights, ranking included, against this: a 2^27 bf16 vector at 4 bits (with its list of chunks)
+// 14.1 -> 8.6 us, 161 tensors 11.9 -> 5.1 us.
 template <int EB>                         // EB: exponent bits of the parameters' delta (8, or 11 for binary64)
 struct TableLds {
     alignas(8) uint8_t sym[2u << EB];     // bucket -> symbol, 0xFF: merged
@@ -395,62 +395,50 @@ __device__ __forceinline__ u32 rank_buckets(TableLds<EB>& S, const u64 (&c)[tabl
 // Huffman code lengths by one wavefront, lane j < 16 holding the count of symbol j (0: does not occur; so do the other lanes);
 // at least two occur, and their counts add up to at most 2^32.  Repeatedly joins the two smallest nodes under the order
 // (weight, leaf before joined node, symbol index / creation order) with two queues, both sorted: the leaves, moved to lanes
-// 0 .. 15 in ascending order, and the joined nodes in creation order in lanes 32 and up.  A node remembers its parent only;
-// the depths follow by doubling the step towards the root four times.  Weights of 32 bits are enough: a node that is ever
+// 0 .. 15 in ascending order, and the joined nodes in creation order in lanes 32 and up.  The loop keeps to scalar registers
+// and real branches (as selects its conditions took 410 cycles a turn, so 110).  A node remembers its parent only; the depths
+// follow by doubling the step towards the root four times.  Weights of 32 bits are enough: a node that is ever
 // compared leaves something out.
 __device__ __forceinline__ u32 code_lengths(u32 count) {
     constexpr u32 kNone = 0xFFFFFFFFu, kNodes = 32;
-    const u32 lane = lane_id();
-    const u32 key = count - 1;                               // (absent: the largest of all)
+    const u32 lane = lane_id(), j = lane & 15;
     const u32 nl = (u32)__popcll(__ballot(count != 0));
-    u32 place = 0;
+    // where each goes: how many come before it, a quarter of them counted in each row of 16 lanes (absent: behind all others)
+    const u32 key = count - 1, mine = gather_lane(key, j);
+    u32 other[4], place = 0;
 #pragma unroll
-    for (u32 i = 0; i < kMaxSym; ++i) {
-        const u32 ki = read_lane(key, i);
-        place += (ki < key || (ki == key && i < lane)) ? 1u : 0u;
-    }
-    if (lane >= kMaxSym) place = lane;
-    u32 w = (u32)__builtin_amdgcn_ds_permute((int)(place * 4), (int)count);
+    for (u32 r = 0; r < 4; ++r) other[r] = gather_lane(key, (lane >> 4) * 4 + r);
+#pragma unroll
+    for (u32 r = 0; r < 4; ++r) place += (other[r] < mine || (other[r] == mine && (lane >> 4) * 4 + r < j)) ? 1u : 0u;
+    place = rows_sum(place);
+    u32 w = (u32)__builtin_amdgcn_ds_permute((int)(place * 4), (int)(mine + 1));      // (four lanes write each, the same)
     if (lane >= nl) w = kNone;
-    u32 parent = lane, li = 0, qi = 0, lw = read_lane(w, 0), nw = kNone;
-    for (u32 ni = 0; ni + 1 < nl; ++ni) {
+    u32 parent = lane, li = 0, qi = kNodes, lw = read_lane(w, 0), nw = kNone;
+#pragma unroll 1
+    for (u32 ni = kNodes; ni < kNodes + nl - 1; ++ni) {
         u32 sum = 0;
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const bool leaf = lw <= nw;
-            const u32 pick = leaf ? li : kNodes + qi;
-            sum += leaf ? lw : nw;
-            li += leaf ? 1u : 0u; qi += leaf ? 0u : 1u;
-            if (lane == pick) parent = kNodes + ni;
             // (behind the last leaf and the last node there is nothing: kNone)
-            const u32 next = read_lane(w, leaf ? li : kNodes + qi);
-            lw = leaf ? next : lw; nw = leaf ? nw : next;
+            if (lw <= nw) {
+                asm volatile("");
+                sum += lw; parent = lane == li ? ni : parent; ++li; lw = read_lane(w, li);
+            } else {
+                asm volatile("");
+                sum += nw; parent = lane == qi ? ni : parent; ++qi; nw = read_lane(w, qi);
+            }
         }
-        if (lane == kNodes + ni) w = sum;
+        w = lane == ni ? sum : w;
         if (qi == ni) nw = sum;                              // the queue of nodes was empty: its head
     }
-    u32 depth = parent != lane ? 1u : 0u, up = parent * 4;
+    u32 depth = parent != lane ? 1u : 0u, up = parent;
 #pragma unroll
     for (int k = 0; k < 4; ++k) {                            // (no symbol of 16 lies deeper than 15)
-        const u32 d = (u32)__builtin_amdgcn_ds_bpermute((int)up, (int)depth), u = (u32)__builtin_amdgcn_ds_bpermute((int)up, (int)up);
+        const u32 d = gather_lane(depth, up), u = gather_lane(up, up);
         depth += d; up = u;
     }
-    const u32 len = (u32)__builtin_amdgcn_ds_bpermute((int)(place * 4), (int)depth);
+    const u32 len = gather_lane(depth, place);
     return count != 0 ? len : 0u;
-}
-
-// Canonical codes by one wavefront, lane j holding the length of symbol j: within a length in symbol order, the first code
-// of a length from the counts below it.
-__device__ __forceinline__ u32 canonical_code(u32 len) {
-    u32 code = 0, first = 0, shorter = 0;
-#pragma unroll
-    for (u32 L = 1; L < kMaxSym; ++L) {
-        const u64 m = __ballot(len == L);
-        first = (first + shorter) << 1;
-        shorter = (u32)__popcll(m);
-        if (len == L) code = first + (u32)__popcll(m & ((1ull << lane_id()) - 1));
-    }
-    return code;
 }
 
 // The counts of the symbols, one per lane of a wavefront: the kept buckets' and, in lane K, what is left of n.
@@ -468,19 +456,27 @@ __device__ __forceinline__ u64 symbol_count(const u64* cnt, u32 K, u64 n) {
 // if not, the traces of the speculative coding are cleared and the table is this checkpoint's own.
 // With chunk_list (and a workgroup of 1024 threads) the wavefronts but the first meanwhile list the chunks
 // that sweep 2 has to read: all but the full chunks whose largest exponent lies below every kept bucket.
-template <int EB>
+// (EB 8: the counts of a vector are CELLS copies in ext, those of a tensor of a batched call one array in its state)
+template <int EB, u32 CELLS = 1>
 __device__ __forceinline__ void table_build(EncState* ws, Ext64* ext, u64 n, int nbits, u32* group_words, u32 ngroups,
                                             const u32* chunk_maxexp, u32* chunk_list) {
     __shared__ TableLds<EB> S;
     constexpr u32 kEmax = (1u << EB) - 1, kThreads = table_threads<EB>(), kSteps = table_steps<EB>();
-    const unsigned long long* hist = EB == 8 ? ws->hist : ext->hist;
+    const unsigned long long* hist = EB == 8 && CELLS == 1 ? ws->hist : ext->hist;
     __shared__ u32 s_reuse, s_listed;
     const u32 lane = lane_id(), t = threadIdx.x;
     const bool active = t < kW;
     const u32 kmax = (1u << nbits) - 1;
     u64 cnt[kSteps];
 #pragma unroll
-    for (u32 s = 0; s < kSteps; ++s) cnt[s] = t < kThreads ? hist[bucket_at<EB>(t + s * kThreads)] : 0;
+    for (u32 s = 0; s < kSteps; ++s) {
+        u64 part[CELLS];
+#pragma unroll
+        for (u32 k = 0; k < CELLS; ++k) part[k] = t < kThreads ? hist[k * 512 + bucket_at<EB>(t + s * kThreads)] : 0;
+        cnt[s] = 0;
+#pragma unroll
+        for (u32 k = 0; k < CELLS; ++k) cnt[s] += part[k];
+    }
     const u32 spec = ws->spec;
     // The groups' record sizes start from zero in every call: the last call's placement read them to its end, so they
     // are cleared here, ahead of the coding sweep that adds to them (a cached table's speculative coding has already
@@ -592,7 +588,7 @@ __device__ __forceinline__ void table_build(EncState* ws, Ext64* ext, u64 n, int
 template <int EB>
 __global__ __launch_bounds__(1024) void k_table(EncState* ws, Ext64* ext, u64 n, int nbits, u32* group_words, u32 ngroups,
                                                  const u32* chunk_maxexp, u32* chunk_list) {
-    table_build<EB>(ws, ext, n, nbits, group_words, ngroups, chunk_maxexp, chunk_list);
+    table_build<EB, EB == 8 ? kHistCells : 1>(ws, ext, n, nbits, group_words, ngroups, chunk_maxexp, chunk_list);
 }
 
 // ----------------------------------------------------------------------------- k_spec_table
@@ -1112,10 +1108,12 @@ constexpr u32 kWgWaves = 8, kWgRows = kR / kWgWaves, kWgThreads = kWgWaves * kW;
 constexpr u32 kPartWords = 7;           // words of a lane's part: 32 codes of 7 bits
 constexpr u32 kPayloadWords = 2560;     // words of a chunk's payload: 5 bits per element
 
+constexpr u32 kPairs = kMaxSym + 1;
+
 struct PackWg {
     uint8_t sym8[512];                   // bucket -> symbol << 3
     u32 codelen[kMaxSym];                // (code << 5) | len
-    uint2 pair[256];                     // (symbol a, symbol b) -> {code of a followed by b, its length}
+    uint2 pair[kPairs * kPairs];         // (symbol a, symbol b) -> {code of a followed by b, its length}; symbol 16: none, no bits
     u32 mn[kMaxSym * kMmCopies], mx[kMaxSym * kMmCopies];      // extremes of the delta bit patterns per symbol
     u32 bits[kWgWaves][kW];              // lengths of the parts
     alignas(16) u32 part[kWgWaves][kPartWords * kW]; // word k of lane l at [64 k + l]
@@ -1139,7 +1137,7 @@ struct LanePart {
 __device__ __forceinline__ void code_symbols(const u32 (&t)[8], PackWg& L, LanePart& S) {
     uint2 p[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) p[i] = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(L.pair) + ((t[2 * i] << 4) | t[2 * i + 1]));
+    for (int i = 0; i < 4; ++i) p[i] = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(L.pair) + (t[2 * i] * kPairs + t[2 * i + 1]));
 #pragma unroll
     for (int i = 0; i < 4; ++i) S.append(p[i].x, p[i].y);
 }
@@ -1210,7 +1208,7 @@ __device__ __forceinline__ void finish_long(u32* payload, const PartSymbols& P, 
         for (; i + 8 <= P.count; i += 8) {                     // two symbols per look-up, four look-ups in flight
             uint2 p[4];
 #pragma unroll
-            for (int k = 0; k < 4; ++k) { p[k] = L.pair[((u32)s & 15u) << 4 | ((u32)(s >> 4) & 15u)]; s >>= 8; }
+            for (int k = 0; k < 4; ++k) { p[k] = L.pair[((u32)s & 15u) * kPairs + ((u32)(s >> 4) & 15u)]; s >>= 8; }
 #pragma unroll
             for (int k = 0; k < 4; ++k) append(p[k].x, p[k].y);
             if (i == 8) s = P.s[1];
@@ -1311,13 +1309,20 @@ __device__ __forceinline__ typename Raw<DT>::type load_raw_guarded(const void* b
     }
 }
 
+__device__ __forceinline__ void pair_setup(PackWg& L, const u32* codelen) {
+    const u32 t = threadIdx.x, a = t / kPairs, b = t % kPairs;
+    if (t >= kPairs * kPairs) return;
+    const u32 ca = a < kMaxSym ? codelen[a] : 0u, cb = b < kMaxSym ? codelen[b] : 0u;
+    L.pair[t] = make_uint2(((ca >> 5) << (cb & 31)) | (cb >> 5), (ca & 31) + (cb & 31));
+}
+
 // The workgroup's tables, extremes and areas; a barrier of the caller's follows.  (kWgThreads = 512 buckets)
 __device__ __forceinline__ void pack_setup(PackWg& L, const Table& T) {
     const u32 t = threadIdx.x;
     const u32 sl = T.symlen_of_bucket[t];
-    const u32 ca = t < 256 ? T.codelen[t >> 4] : 0u, cb = t < 256 ? T.codelen[t & 15] : 0u, own = t < kMaxSym ? T.codelen[t] : 0u;
+    const u32 own = t < kMaxSym ? T.codelen[t] : 0u;
+    pair_setup(L, T.codelen);
     L.sym8[t] = (uint8_t)((sl & 15) << 3);
-    if (t < 256) L.pair[t] = make_uint2(((ca >> 5) << (cb & 31)) | (cb >> 5), (ca & 31) + (cb & 31));
     if (t < kMaxSym) L.codelen[t] = own;
     static_assert(kWgThreads == 512 && kMaxSym * kMmCopies == 512, "one entry per thread");
     L.mn[t] = 0xFFFFFFFFu; L.mx[t] = 0;
@@ -1713,7 +1718,7 @@ __global__ __launch_bounds__(64) void k_pack64(const void* __restrict__ w, const
 // w_ref.  k_table then either confirms the coding or voids it.
 template <int DT>
 __global__ __launch_bounds__(64) void k_spec_sweep(const void* __restrict__ w, const void* __restrict__ w_ref, u64 n,
-                                                   EncState* ws, u32* chunk_bits, u32* group_words, u32* prov,
+                                                   Workspace* ws, u32* chunk_bits, u32* group_words, u32* prov,
                                                    u32 slot_words, u32 nchunks, int aligned) {
     __shared__ PackLds L;
     const u32 lane = threadIdx.x;
@@ -1733,7 +1738,7 @@ __global__ __launch_bounds__(64) void k_spec_sweep(const void* __restrict__ w, c
         u32 sum = 0;
 #pragma unroll
         for (int k = 0; k < kSpecCopies; ++k) sum += L.hist[hist_slot(b, k)];
-        if (sum) atomicAdd(&ws->hist[b], (u64)sum);
+        if (sum) atomicAdd(&ws->ext64.hist[(blockIdx.x % kHistCells) * 512 + b], (u64)sum);
     }
     if (spec) pack_merge_extremes(L, ws, K, lane);
 }
@@ -1864,7 +1869,7 @@ __device__ __forceinline__ void finalize_vector(uint8_t* out, Workspace* ws, Res
     finalize_blob(out, ws, host_result, cache, n, nbits, nchunks, dtype, group_words, &ws->ext64, staged ? ws->bucket_min : nullptr,
                   staged ? ws->bucket_max : nullptr);
     clear_encode_state(ws, nullptr, 0, threadIdx.x, blockDim.x);
-    if (dtype == kF64) clear_ext64(&ws->ext64, threadIdx.x, blockDim.x);
+    clear_ext64(&ws->ext64, threadIdx.x, blockDim.x);
     if (staged) clear_bucket_extremes(ws, threadIdx.x, blockDim.x);
     // (no fence: the host reads its result after waiting for the stream, and the end of the kernel makes every store
     // visible; a system-scope fence here would have to write back what the other workgroups have just placed)
@@ -1992,40 +1997,38 @@ __global__ __launch_bounds__(256) void k_place(uint8_t* out, Workspace* ws, cons
 // A short vector in one launch: a workgroup per chunk, all of them resident together, that keeps its deltas in registers
 // from the count to the code.  What such a call costs in four kernels is not bytes but their starts, the gaps between them
 // and every chunk's round trips to memory (chunk maxima, table, slot, slot again): 2^20 fp32 elements 7.0 + 4.6 + 7.9 + 3.7
-// us and three gaps, 38.1 us the call (30.4 so).  Here the workgroups meet twice: when all counts are in (each then builds the table for itself, from
+// us and three gaps, 40.8 us the call (29.0 so).  Here the workgroups meet twice: when all counts are in (each then builds the table for itself, from
 // the same counts), and when all record sizes are known (each then knows where its record goes).
 //
 // The meeting.  Everything that passes between workgroups goes through agent-scope atomic operations, whose completion each
 // waits for before it arrives (no fence: writing back the L2 of a die from every workgroup costs more than the launches
 // saved).  A workgroup may wait for one that has not started, because others' kernels hold the chip: the host launches
-// this kernel only while all workgroups of such calls fit the chip together, and the wait is bounded.  When it is given up, that
-// is one atomic decision for all (the first to change the flag, to "all here" or to "given up", is right); the header's
-// workgroup then does not report, and the host runs the call in four kernels.
+// this kernel only while all workgroups of such calls fit the chip together, and the wait is bounded.  It is given up by
+// marking a counter that is not yet full, so either every counter filled up unmarked, and no one can give up any more, or one
+// is marked, and no one finds them full; the header's workgroup then does not report, and the host runs the call in four
+// kernels.  A meeting of 64 workgroups takes 1.2 us, of 256 1.5 (one counter for all: 1.4 and 3.7).
 struct GridMeeting {
     OneSync* sync;
-    u64 tag;                 // of this call; the lowest bit says "given up"
-    u32 count, limit;        // workgroups of the grid; how often to look
-    // the flag's value once it belongs to this call, `mine` if nobody has set it yet (by one thread)
-    __device__ __forceinline__ u64 settle(u32 which, u64 mine) const {
-        u64 seen = __hip_atomic_load(&sync->flag[which], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        while ((seen | 1) != (tag | 1)) {        // (only this call's workgroups write it meanwhile: at most two turns)
-            if (__hip_atomic_compare_exchange_strong(&sync->flag[which], &seen, mine, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return mine;
-        }
-        return seen;
-    }
+    u64 goal;                // lane k: what counter k stands at when all have arrived
+    u32 lines, limit;        // counters; how often to look
     __device__ __forceinline__ void arrive(u32 which) const {        // by one thread, behind the others' waits for their own operations
-        if (__hip_atomic_fetch_add(&sync->arrived[which], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == count) {
-            __hip_atomic_store(&sync->arrived[which], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            settle(which, tag);
-        }
+        __hip_atomic_fetch_add(&sync->line[which][blockIdx.x % lines].arrived, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    __device__ __forceinline__ bool wait(u32 which) const {          // by the same thread; whether all are here
-        for (u32 i = 0; i < limit; ++i) {
-            const u64 seen = __hip_atomic_load(&sync->flag[which], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if ((seen | 1) == (tag | 1)) return seen == tag;
-            __builtin_amdgcn_s_sleep(1);
+    __device__ __forceinline__ bool wait(u32 which) const {          // by one wavefront; whether all have arrived
+        const u32 lane = lane_id();
+        unsigned long long* mine = &sync->line[which][lane < lines ? lane : 0].arrived;
+        for (u32 i = 0;; ++i) {
+            u64 seen = __hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (__any(lane < lines && (seen & kGivenUp) != 0)) return false;
+            const u64 missing = __ballot(lane < lines && seen != goal);
+            if (missing == 0) return true;
+            if (i >= limit) {                        // (fails only if another has arrived there: at most as often as there are workgroups)
+                bool marked = false;
+                if (lane == (u32)__builtin_ctzll(missing))
+                    marked = __hip_atomic_compare_exchange_strong(mine, &seen, seen | kGivenUp, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (__any(marked)) return false;
+            } else if (i >= 64) __builtin_amdgcn_s_sleep(8);
         }
-        return settle(which, tag | 1) == tag;
     }
 };
 __device__ __forceinline__ void wait_own_operations() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
@@ -2048,29 +2051,38 @@ __device__ __forceinline__ bool cached_table(const TableCache* cache, int nbits,
     return true;
 }
 
-constexpr u32 kOneCopies = 8;       // copies of the bucket counts in memory: a workgroup adds to one of them (Ext64::hist, which only
-                                    // binary64 calls use otherwise, and which they leave cleared as well)
-static_assert(kOneCopies * 512 == kBuckets64, "the copies fill Ext64::hist");
 struct OneArgs {
     const void* w; const void* w_ref; u64 n;
     uint8_t* out; Workspace* ws; u32* record_words; TableCache* cache; Result* host_result;
-    u64 tag; u32 nchunks, limit;
+    u64 goal[kMeetLines];
+    u32 nchunks, lines, limit;
     int nbits, aligned;
 };
+constexpr u32 kOneCopies = 16;      // LDS copies of the chunk's counts (8 of them serve a wavefront in twice the time: it is not
+                                    // hidden behind a stream here), then 8 of the buckets' smallest and largest patterns
+constexpr u32 kAbsent = 0xFFFFFFFFu;    // the delta that stands for what a ragged chunk lacks: of a bucket that no vector that is coded holds
 
 template <int DT>
 __global__ __launch_bounds__(kWgThreads, 4) void k_encode_one(OneArgs a) {
     typedef typename Raw<DT>::type raw_t;
     __shared__ PackWg L;
     __shared__ TableLds<8> S;
-    __shared__ u32 s_go, s_status, s_k, s_max_len, s_reuse, s_cached, s_cached_kept[kMaxSym], s_cached_len[kMaxSym];
+    __shared__ u32 s_go, s_max_len, s_reuse, s_cached, s_cached_kept[kMaxSym], s_cached_len[kMaxSym], s_codelen[kMaxSym];
     __shared__ u32 s_before[kWgWaves], s_all[kWgWaves];
+    // the counts and extremes lie where the coding's tables and areas go later
+    static_assert(sizeof(PackWg) >= 4 * 512 * kOneCopies && alignof(PackWg) >= 16, "room for the counts");
+    u32* const area = reinterpret_cast<u32*>(&L);
     Workspace* ws = a.ws;
     const u64 n = a.n;
     const u32 t = threadIdx.x, lane = lane_id(), v = __builtin_amdgcn_readfirstlane(t >> 6), c = blockIdx.x, first_row = kWgRows * v;
     const bool full = a.aligned && (u64)(c + 1) * kChunk <= n;
-    const GridMeeting meet = {&ws->one, a.tag, a.nchunks, a.limit};
-    const u32 xcopy = c % kOneCopies;
+    GridMeeting meet = {ws->meeting(), 0, a.lines, a.limit};
+#pragma unroll
+    for (u32 k = 0; k < kMeetLines; ++k) meet.goal = lane == k ? a.goal[k] : meet.goal;
+    auto fill = [&](u32 from, u32 count, u32 value) {
+        const u32x4 x = {value, value, value, value};
+        for (u32 i = t; i < count / 4; i += kWgThreads) reinterpret_cast<u32x4*>(area + from)[i] = x;
+    };
     // ---- this wavefront's 8 rows, as deltas
     u32 u[kWgRows * kV];
     {
@@ -2082,48 +2094,58 @@ __global__ __launch_bounds__(kWgThreads, 4) void k_encode_one(OneArgs a) {
 #pragma unroll
             for (u32 k = 0; k < kWgRows; ++k) { A[k] = load_raw_guarded<DT>(a.w, row_at(c, first_row + k), n); B[k] = load_raw_guarded<DT>(a.w_ref, row_at(c, first_row + k), n); }
         }
-        // the counts of this chunk, 8 copies in LDS (as in k_hist), where the parts and the payload go later
-        static_assert(sizeof(L.part) + sizeof(L.payload) >= 4 * 512 * kHistCopies && offsetof(PackWg, payload) == offsetof(PackWg, part) + sizeof(L.part), "room for the counts");
-        u32* h = &L.part[0][0];
-        for (u32 i = t; i < 512 * kHistCopies; i += kWgThreads) h[i] = 0;
+        fill(0, 512 * kOneCopies, 0);
         if (v == 1 && a.cache) {
             u32 kept = 0, len = 0;
             const bool ok = cached_table(a.cache, a.nbits, &kept, &len);
             if (lane < kMaxSym) { s_cached_kept[lane] = kept; s_cached_len[lane] = len; }
             if (lane == 0) s_cached = ok ? a.cache->K + 1 : 0;
         }
-        __syncthreads();
 #pragma unroll
         for (u32 k = 0; k < kWgRows; ++k) {
             float xa[4], xb[4];
             unpack<DT>(A[k], xa); unpack<DT>(B[k], xb);
 #pragma unroll
-            for (u32 e = 0; e < kV; ++e) {
-                u[kV * k + e] = delta_bits(xa[e], xb[e]);
-                if (full || row_at(c, first_row + k) + e < n) atomicAdd(&h[(u[kV * k + e] >> 23) * kHistCopies + (lane & (kHistCopies - 1))], 1u);
-            }
+            for (u32 e = 0; e < kV; ++e) u[kV * k + e] = delta_bits(xa[e], xb[e]);
         }
-        __syncthreads();
+        if (!full) {
+#pragma unroll
+            for (u32 i = 0; i < kWgRows * kV; ++i) if (row_at(c, first_row + i / kV) + i % kV >= n) u[i] = kAbsent;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (u32 i = 0; i < kWgRows * kV; ++i) atomicAdd(&area[(u[i] >> 23) * kOneCopies + (lane & (kOneCopies - 1))], 1u);
+    __syncthreads();
+    {
         u32 sum = 0;
 #pragma unroll
-        for (u32 k = 0; k < kHistCopies; ++k) sum += h[t * kHistCopies + k];
-        if (sum) atomicAdd(&ws->ext64.hist[xcopy * 512 + t], (u64)sum);
-        wait_own_operations();
-        __syncthreads();
+        for (u32 k = 0; k < kOneCopies / 4; ++k) { const u32x4 x = reinterpret_cast<const u32x4*>(area)[t * (kOneCopies / 4) + k]; sum += x.x + x.y + x.z + x.w; }
+        if (t == kAbsent >> 23 && (u64)(c + 1) * kChunk > n) sum -= (u32)((u64)(c + 1) * kChunk - n);
+        if (sum) atomicAdd(&ws->ext64.hist[(c % kHistCells) * 512 + t], (u64)sum);
+    }
+    wait_own_operations();
+    __syncthreads();
+    if (t == 0) meet.arrive(0);
+    // meanwhile the extremes of this chunk's buckets (Section 3.1.1: a representative is the mean of the two), 8 copies
+    constexpr u32 kExt = 8;
+    fill(0, 512 * kExt, 0xFFFFFFFFu); fill(512 * kExt, 512 * kExt, 0);
+    __syncthreads();
+#pragma unroll
+    for (u32 i = 0; i < kWgRows * kV; ++i) {
+        const u32 at = (u[i] >> 23) * kExt + (lane & (kExt - 1));
+        atomicMin(&area[at], u[i]); atomicMax(&area[512 * kExt + at], u[i]);
     }
     // ---- all counts are in
-    if (t == 0) { meet.arrive(0); s_go = meet.wait(0) ? 1u : 0u; }
-    L.mn[t] = 0xFFFFFFFFu; L.mx[t] = 0;
-    if (t == 0) L.overflow = 0;
-    for (u32 i = t; i < kPayloadWords; i += kWgThreads) L.payload[i] = 0;
+    if (v == 0) { const bool go = meet.wait(0); if (lane == 0) s_go = go ? 1u : 0u; }
     __syncthreads();
     if (!s_go) return;
     const u32 kmax = (1u << a.nbits) - 1;
-    u64 part[kOneCopies], cnt[1] = {0};
+    u64 part[kHistCells], cnt[1] = {0};
 #pragma unroll
-    for (u32 k = 0; k < kOneCopies; ++k) part[k] = load_shared(&ws->ext64.hist[k * 512 + bucket_at<8>(t)]);
+    for (u32 k = 0; k < kHistCells; ++k) part[k] = load_shared(&ws->ext64.hist[k * 512 + bucket_at<8>(t)]);
 #pragma unroll
-    for (u32 k = 0; k < kOneCopies; ++k) cnt[0] += part[k];
+    for (u32 k = 0; k < kHistCells; ++k) cnt[0] += part[k];
     const u32 candidates = rank_buckets<8>(S, cnt, kmax), K = candidates < kmax ? candidates : kmax;
     __syncthreads();
     if (v == 0) {
@@ -2133,7 +2155,7 @@ __global__ __launch_bounds__(kWgThreads, 4) void k_encode_one(OneArgs a) {
         u32 len = 0;
         bool reuse = false;
         if (a.cache && s_cached != 0) {
-            const u32 cached_len = lane <= K && lane < kMaxSym ? s_cached_len[lane] : 0u;
+            const u32 cached_len = lane <= K ? s_cached_len[lane] : 0u;
             const bool differs = (lane < K && s_cached_kept[lane] != S.kept[lane]) || (lane <= K && (cached_len != 0) != (own != 0));
             const u64 payload_bits = wave_sum64(own * cached_len);
             reuse = S.nonfinite == 0 && s_cached == K + 1 && !__any(differs) && payload_bits <= n * (u64)a.nbits;
@@ -2142,59 +2164,55 @@ __global__ __launch_bounds__(kWgThreads, 4) void k_encode_one(OneArgs a) {
         if (!reuse && nl == 1) len = own != 0 ? 1u : 0u;
         if (!reuse && nl >= 2) len = code_lengths((u32)own);
         const u32 code = canonical_code(len), max_len = wave_max_u32(len);
-        if (lane < kMaxSym) L.codelen[lane] = lane <= K ? ((code << 5) | len) : 0u;
+        if (lane < kMaxSym) s_codelen[lane] = lane <= K ? ((code << 5) | len) : 0u;
         if (lane == K) S.cnt[lane] = own;
         if (lane == 0) { s_max_len = max_len; s_reuse = reuse ? 1u : 0u; }
-    }
-    L.sym8[t] = (uint8_t)((S.sym[t] == 0xFF ? K : S.sym[t]) << 3);
-    __syncthreads();
-    if (t < 256) {
-        const u32 ca = L.codelen[t >> 4], cb = L.codelen[t & 15];
-        L.pair[t] = make_uint2(((ca >> 5) << (cb & 31)) | (cb >> 5), (ca & 31) + (cb & 31));
+    } else if (v <= kMaxSym * kExt / kW) {
+        // the extremes of the kept buckets, 8 lanes to a symbol, to one of kExtCopies copies (see pack_merge_extremes)
+        const u32 i = t - kW, sym = i / kExt, at = (sym < K ? S.kept[sym] : 0u) * kExt + i % kExt;
+        u32 mn = area[at], mx = area[512 * kExt + at];
+#pragma unroll
+        for (int d = 1; d < (int)kExt; d <<= 1) { mn = min(mn, (u32)__shfl_xor(mn, d, 64)); mx = max(mx, (u32)__shfl_xor(mx, d, 64)); }
+        const u32 copy = c % kExtCopies;
+        if (i % kExt == 0 && sym < K && mn <= mx) { atomicMin(&ws->mmin[copy][sym], mn & 0x7FFFFFu); atomicMax(&ws->mmax[copy][sym], mx & 0x7FFFFFu); }
     }
     __syncthreads();
     const bool finite = S.nonfinite == 0;
-    const u32 K8 = K << 3;
+    const u32 sy = S.sym[t] == 0xFF ? K : S.sym[t];
+    L.sym8[t] = (uint8_t)((t == kAbsent >> 23 ? kMaxSym : sy) << 3);
+    pair_setup(L, s_codelen);
+    if (t < kMaxSym) L.codelen[t] = s_codelen[t];
+    if (t == 0) L.overflow = 0;
+    for (u32 i = t; i < kPayloadWords; i += kWgThreads) L.payload[i] = 0;
+    __syncthreads();
     // ---- this chunk's code (of a vector with a delta that is not finite there is none)
     LanePart P;
     P.start(L, v);
     if (finite) {
-        if (full) {
 #pragma unroll
-            for (u32 i = 0; i < kWgRows * kV; i += 8) code_deltas(u + i, K8, L, P);
-        } else {
+        for (u32 i = 0; i < kWgRows * kV; i += 8) {
+            u32 sym[8];
 #pragma unroll
-            for (u32 k = 0; k < kWgRows; ++k) {
-#pragma unroll
-                for (u32 e = 0; e < kV; ++e) {
-                    if (row_at(c, first_row + k) + e < n) {
-                        const u32 x = u[kV * k + e], sy8 = L.sym8[x >> 23], cl = L.codelen[sy8 >> 3];
-                        const u32 at = sy8 * (kMmCopies / 8) + (lane & (kMmCopies - 1));
-                        atomicMin(&L.mn[at], x); atomicMax(&L.mx[at], x);
-                        P.append(cl >> 5, cl & 31);
-                    }
-                }
-            }
+            for (u32 k = 0; k < 8; ++k) sym[k] = L.sym8[u[i + k] >> 23];
+            code_symbols(sym, L, P);
         }
     }
     const PartPlaces at = part_places(P, v, L);
-    {
-        // the extremes: thread t holds copy t mod 32 of symbol t / 32
-        u32 mn = L.mn[t], mx = L.mx[t];
-#pragma unroll
-        for (int d = kMmCopies / 2; d >= 1; d >>= 1) { mn = min(mn, (u32)__shfl_xor(mn, d, 64)); mx = max(mx, (u32)__shfl_xor(mx, d, 64)); }
-        const u32 sym = t / kMmCopies, copy = c % kExtCopies;
-        if (t % kMmCopies == 0 && sym < K && mn <= mx) { atomicMin(&ws->mmin[copy][sym], mn & 0x7FFFFFu); atomicMax(&ws->mmax[copy][sym], mx & 0x7FFFFFu); }
-    }
     if (t == 0) __hip_atomic_store(&a.record_words[c], kLaneBitsWords + at.nwords, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     wait_own_operations();
     __syncthreads();
     // ---- all sizes and extremes are known
     if (t == 0) meet.arrive(1);
     if (!at.overflow) join_parts(at, v, L);
-    if (t == 0) s_go = meet.wait(1) ? 1u : 0u;
+    if (v == 0) { const bool go = meet.wait(1); if (lane == 0) s_go = go ? 1u : 0u; }
     __syncthreads();
     if (!s_go) return;
+    const u32 sym = t < kMaxSym ? t : 0;
+    BlobSymbol my = {s_codelen[sym], S.kept[sym], S.cnt[sym], 0x7FFFFFu, 0, 0, 0};
+    if (c == 0 && t < kMaxSym) {
+#pragma unroll
+        for (u32 k = 0; k < kExtCopies; ++k) { my.mn = min(my.mn, load_shared(&ws->mmin[k][sym])); my.mx = max(my.mx, load_shared(&ws->mmax[k][sym])); }
+    }
     u32 before = 0, all = 0;
     for (u32 i = t; i < a.nchunks; i += kWgThreads) { const u32 words = load_shared(&a.record_words[i]); all += words; before += i < c ? words : 0u; }
     before = wave_sum32(before); all = wave_sum32(all);
@@ -2203,37 +2221,28 @@ __global__ __launch_bounds__(kWgThreads, 4) void k_encode_one(OneArgs a) {
     before = 0; all = 0;
 #pragma unroll
     for (u32 k = 0; k < kWgWaves; ++k) { before += s_before[k]; all += s_all[k]; }
-    if (finite) {
-        u32* rec = reinterpret_cast<u32*>(a.out + chunk_area_of(a.nchunks)) + before;
-        if (v == 0) reinterpret_cast<uint16_t*>(rec)[lane] = (uint16_t)at.bits;
-        if (t == 0) reinterpret_cast<u32*>(a.out + kHeaderBytes)[c] = before;
-        if (!at.overflow) copy_payload(rec + kLaneBitsWords, at.nwords, L);
-        else {
-            PartSymbols Q;
-            Q.count = 0;
-#pragma unroll
-            for (u32 i = 0; i < kWgRows * kV; ++i) {
-                if (i % 16 == 0) Q.s[i / 16] = 0;
-                Q.s[i / 16] |= (u64)(L.sym8[u[i] >> 23] >> 3) << (4 * (i % 16));
-                Q.count += row_at(c, first_row + i / kV) + i % kV < n ? 1u : 0u;
-            }
-            finish_long(rec + kLaneBitsWords, Q, at.o, at.nwords, L);
-        }
+    if (c == 0) {
+        // the first workgroup: the header, the outcome, and the scratch state as the next call expects it (the others are
+        // through with the counts, and only it reads the extremes)
+        const BlobFacts f = {finite ? 0u : 2u, K, candidates + S.zero_class, s_max_len, s_reuse, a.nchunks, all};
+        write_header(a.out, my, f, a.host_result, a.cache, n, a.nbits, a.nchunks, (u32)DT);
+        for (u32 i = t; i < kBuckets64 / 2; i += kWgThreads) reinterpret_cast<ulonglong2*>(ws->ext64.hist)[i] = make_ulonglong2(0, 0);
+        clear_extremes(ws, t, kWgThreads);
     }
-    if (c != 0) return;
-    // ---- the first workgroup: the header, the outcome, and the scratch state as the next call expects it (the others are
-    // through with the counts, and only it reads the extremes)
-    const u32 sym = t < kMaxSym ? t : 0;
-    BlobSymbol my = {L.codelen[sym], S.kept[sym], S.cnt[sym], 0x7FFFFFu, 0, 0, 0};
-    if (t < kMaxSym) {
+    if (!finite) return;
+    u32* rec = reinterpret_cast<u32*>(a.out + chunk_area_of(a.nchunks)) + before;
+    if (v == 0) reinterpret_cast<uint16_t*>(rec)[lane] = (uint16_t)at.bits;
+    if (t == 0) reinterpret_cast<u32*>(a.out + kHeaderBytes)[c] = before;
+    if (!at.overflow) { copy_payload(rec + kLaneBitsWords, at.nwords, L); return; }
+    PartSymbols Q;
+    Q.count = 0;
 #pragma unroll
-        for (u32 k = 0; k < kExtCopies; ++k) { my.mn = min(my.mn, load_shared(&ws->mmin[k][sym])); my.mx = max(my.mx, load_shared(&ws->mmax[k][sym])); }
+    for (u32 i = 0; i < kWgRows * kV; ++i) {
+        if (i % 16 == 0) Q.s[i / 16] = 0;
+        Q.s[i / 16] |= (u64)((L.sym8[u[i] >> 23] >> 3) & 15u) << (4 * (i % 16));
+        Q.count += u[i] != kAbsent ? 1u : 0u;                     // (those past the vector's end are a lane's last)
     }
-    const BlobFacts f = {finite ? 0u : 2u, K, candidates + S.zero_class, s_max_len, s_reuse, a.nchunks, all};
-    write_header(a.out, my, f, a.host_result, a.cache, n, a.nbits, a.nchunks, (u32)DT);
-    for (u32 i = t; i < kBuckets64; i += kWgThreads) ws->ext64.hist[i] = 0;
-    __syncthreads();
-    clear_extremes(ws, t, kWgThreads);
+    finish_long(rec + kLaneBitsWords, Q, at.o, at.nwords, L);
 }
 
 // ----------------------------------------------------------------------------- batched encode
@@ -2457,10 +2466,11 @@ void launch_pack_keys(const void* w, const void* w_ref, uint64_t n, Workspace* w
 }
 
 void launch_encode_one(const void* w, const void* w_ref, uint64_t n, int nbits, int dtype, uint8_t* out, Workspace* ws, uint32_t* record_words,
-                       TableCache* cache, Result* host_result, uint64_t epoch, uint32_t limit, hipStream_t s) {
-    const u32 nchunks = (u32)num_chunks_of(n);
-    const OneArgs a = {w, w_ref, (u64)n, out, ws, record_words, cache, host_result, (u64)epoch << 1, nchunks, limit, nbits,
-                       aligned_rows(w, dtype) && aligned_rows(w_ref, dtype) ? 1 : 0};
+                       TableCache* cache, Result* host_result, uint64_t (&met)[kMeetLines], uint32_t limit, hipStream_t s) {
+    const u32 nchunks = (u32)num_chunks_of(n), lines = nchunks <= kMeetOneLine ? 1 : kMeetLines;
+    OneArgs a = {w, w_ref, (u64)n, out, ws, record_words, cache, host_result, {}, nchunks, lines, limit, nbits,
+                 aligned_rows(w, dtype) && aligned_rows(w_ref, dtype) ? 1 : 0};
+    for (u32 k = 0; k < lines; ++k) a.goal[k] = met[k] += (nchunks + lines - 1 - k) / lines;
     if (dtype == kBF16) hipLaunchKernelGGL(k_encode_one<kBF16>, dim3(nchunks), dim3(kWgThreads), 0, s, a);
     else if (dtype == kF16) hipLaunchKernelGGL(k_encode_one<kF16>, dim3(nchunks), dim3(kWgThreads), 0, s, a);
     else hipLaunchKernelGGL(k_encode_one<kF32>, dim3(nchunks), dim3(kWgThreads), 0, s, a);
@@ -2472,7 +2482,7 @@ void launch_table(Workspace* ws, uint64_t n, int nbits, int dtype, uint32_t* gro
     const dim3 wg(chunk_list || dtype == kF64 ? 1024 : table_threads<8>());
     const u32 ngroups = (u32)((num_chunks_of(n) + 63) / 64);
     if (dtype == kF64) hipLaunchKernelGGL(k_table<11>, dim3(1), wg, 0, s, ws, &ws->ext64, (u64)n, nbits, group_words, ngroups, chunk_maxexp, chunk_list);
-    else hipLaunchKernelGGL(k_table<8>, dim3(1), wg, 0, s, ws, (Ext64*)nullptr, (u64)n, nbits, group_words, ngroups, chunk_maxexp, chunk_list);
+    else hipLaunchKernelGGL(k_table<8>, dim3(1), wg, 0, s, ws, &ws->ext64, (u64)n, nbits, group_words, ngroups, chunk_maxexp, chunk_list);
 }
 
 // Single-wave workgroups for a sweep over `nchunks` chunks dealt round-robin, at most `cap`: the largest count that

@@ -101,19 +101,24 @@ struct EncState {
 // largest exponent of every 4 KiB batch of sweep 1.
 // What an encode of binary64 parameters keeps instead of EncState's counts, extremes and bucket map: 2^12
 // (sign, exponent) buckets, 52-bit mantissas (Section 3.1.1, footnote on the bucket count).  Left cleared like them.
-constexpr uint32_t kBuckets64 = 4096;
+// An encode of the other types counts its 512 buckets in the same array, in kHistCells copies: a workgroup adds to copy (its
+// index mod kHistCells).  Atomic additions to one 128-byte line are served one after the other, some 50 cycles each, so the
+// 256 workgroups of sweep 1, which finish together, would queue for 13,000 cycles at one copy (at 8: 2,700).
+constexpr uint32_t kBuckets64 = 4096, kHistCells = 8;
+static_assert(kHistCells * 512 == kBuckets64, "the copies fill the array");
 struct Ext64 {
     unsigned long long hist[kBuckets64];
     unsigned long long mmin[kMaxSym], mmax[kMaxSym];
     uint8_t symlen_of_bucket[kBuckets64];
 };
 
-// Where the workgroups of a short encode meet (k_encode_one): how many have arrived (zero between calls), and what was
-// decided, tagged with the call.  Arrivals and the flag that is looked at meanwhile lie in lines of their own.
+// Where the workgroups of a short encode meet (k_encode_one): counters of arrivals, workgroup i at counter i mod kMeetLines (one
+// counter for all in a small grid), each in a line of its own (see kHistCells).  They only ever grow, the host knows
+// what they stand at; the highest bit says that the meeting was given up.
+constexpr uint32_t kMeetLines = 8, kMeetOneLine = 16;        // up to kMeetOneLine workgroups: one counter
+constexpr uint64_t kGivenUp = 1ull << 63;
 struct OneSync {
-    unsigned long long flag[2];
-    uint32_t pad_f[28];
-    uint32_t arrived[2], pad_a[2];
+    struct alignas(128) { unsigned long long arrived; } line[2][kMeetLines];
 };
 
 struct Workspace : EncState {
@@ -123,8 +128,10 @@ struct Workspace : EncState {
     // An encode with staged keys: smallest / largest delta bit pattern of every (sign, exponent) bucket, gathered by
     // sweep 1 (which is then the only sweep that sees the mantissas).  Left cleared (all ones / zero) like the rest.
     uint32_t bucket_min[512], bucket_max[512];
-    OneSync one;
+    // (a vector's counts are in ext64: the array of EncState that a tensor of a batched call uses for them is free)
+    __host__ __device__ OneSync* meeting() { return reinterpret_cast<OneSync*>(hist); }
 };
+static_assert(sizeof(OneSync) <= sizeof(EncState::hist), "the counters fit");
 
 constexpr size_t kWorkspaceFixed = (sizeof(Workspace) + 255) / 256 * 256;
 constexpr uint32_t kMaxGroups = 4096;       // 2^32 elements / 16384 per chunk / 64 chunks per group
@@ -195,9 +202,10 @@ void launch_place(uint8_t* out, Workspace* ws, const uint32_t* chunk_bits, const
                   const uint32_t* prov, uint32_t slot_words, uint64_t n, uint32_t* chunk_maxexp, Result* host_result,
                   TableCache* cache, int nbits, int dtype, bool staged, hipStream_t s);
 // A whole encode of at most tune.one_per_cu chunks per compute unit.  host_result is written only if the workgroups met.
-// epoch: of this call, never used before on this scratch area; record_words: one word per chunk of scratch.
+// met: what the scratch area's counters stand at (all zero once it is cleared), moved on by the call; record_words: one word per
+// chunk of scratch.
 void launch_encode_one(const void* w, const void* w_ref, uint64_t n, int nbits, int dtype, uint8_t* out, Workspace* ws, uint32_t* record_words,
-                       TableCache* cache, Result* host_result, uint64_t epoch, uint32_t limit, hipStream_t s);
+                       TableCache* cache, Result* host_result, uint64_t (&met)[kMeetLines], uint32_t limit, hipStream_t s);
 // One tensor of a batched call (lc_encode_batch): every tensor has its own EncState, blob and run of
 // chunks; chunks, groups of 64 chunks and slots of all tensors are numbered through ("dense" indices).
 struct Seg {
