@@ -31,7 +31,10 @@ struct Area {
     hipEvent_t idle = nullptr;    // recorded behind the last call that used it
     bool clean = false;           // its encode state is known to be cleared
     uint64_t stamp = 0;           // when it was last taken
-    uint64_t met[kMeetLines] = {};   // what its counters of k_encode_one stand at, if it is clean
+    // what its counters of k_encode_one (both meetings) and of k_decode_one stand at, as long as that is known
+    uint64_t met[kMeetLines] = {}, met_dec[kMeetLines] = {};
+    bool counted = false;
+    void cleared() { clean = true; counted = true; memset(met, 0, sizeof(met)); memset(met_dec, 0, sizeof(met_dec)); }
 };
 
 struct DeviceState {
@@ -86,7 +89,7 @@ uint64_t g_prof_n[kNumSlots];
 hipEvent_t g_ev[kNumSlots][2];
 bool g_ev_made = false;
 const char* const kSlotNames[kNumSlots] = {"k_reset", "k_hist", "k_table", "k_pack", "k_place", "k_spec_table", "k_spec_sweep",
-                                           "k_dec_check", "k_decode", "k_decode_fused", "k_hist_keys", "k_pack_keys", "k_verify", "k_encode_one"};
+                                           "k_dec_check", "k_decode", "k_decode_fused", "k_hist_keys", "k_pack_keys", "k_verify", "k_encode_one", "k_decode_one"};
 
 int env_int(const char* name, int dflt, int lo, int hi) {
     const char* v = getenv(name);
@@ -124,6 +127,7 @@ void read_tuning(DeviceState& ds, int dev) {
     ds.tune.pack_waves_per_cu = env_int("LC_TUNE_PACK_WAVES_PER_CU", ds.tune.pack_waves_per_cu, 1, 64);
     ds.tune.unlisted_per_cu = env_int("LC_TUNE_UNLISTED_PER_CU", ds.tune.unlisted_per_cu, 0, 15);   // (calls of 16 and more may stage keys, which takes a list)
     ds.tune.one_per_cu = env_int("LC_TUNE_ONE_PER_CU", ds.tune.one_per_cu, 0, 2);
+    ds.tune.one_dec_per_cu = env_int("LC_TUNE_ONE_DEC_PER_CU", ds.tune.one_dec_per_cu, 0, 2);
     ds.tune.one_wait = env_int("LC_TUNE_ONE_WAIT", ds.tune.one_wait, 0, 1 << 20);
     ds.tune.spec_waves_per_cu = env_int("LC_TUNE_SPEC_WAVES_PER_CU", ds.tune.spec_waves_per_cu, 1, 64);
     if (g_key_staging < 0) g_key_staging = env_int("LC_TUNE_KEY_STAGING", 0, 0, 2);
@@ -181,7 +185,7 @@ Area* acquire(DeviceState* ds, hipStream_t s, size_t need, int* err) {
         if (hipStreamWaitEvent(s, a->idle, 0) != hipSuccess) { (void)hipGetLastError(); *err = LC_ERR_HIP; return nullptr; }
     }
     if (ds->user) {
-        if (a->mem != ds->user) { a->mem = ds->user; a->bytes = ds->user_bytes; a->user = true; a->clean = false; a->used = false; }
+        if (a->mem != ds->user) { a->mem = ds->user; a->bytes = ds->user_bytes; a->user = true; a->cleared(); a->clean = false; a->used = false; }
     } else if (a->bytes < need) {
         if (a->mem) {
             if (a->used) (void)hipEventSynchronize(a->idle);         // its last call must be through with the old memory
@@ -194,7 +198,8 @@ Area* acquire(DeviceState* ds, hipStream_t s, size_t need, int* err) {
         // has been seen to land behind the reset kernel that follows, which left the smallest mantissas at zero)
         if (hipMemsetAsync(a->mem, 0, kWorkspaceHead, s) != hipSuccess) { (void)hipGetLastError(); (void)hipFree(a->mem); a->mem = nullptr; *err = LC_ERR_HIP; return nullptr; }
         a->bytes = want; a->user = false; a->used = false;
-        a->clean = false;        // new memory (possibly at the old address): its encode state is not set up yet
+        a->cleared();
+        a->clean = false;        // new memory (possibly at the old address): all zero, its encode state is not set up yet
     }
     a->stream = s; a->stamp = ++ds->clock;
     return a;
@@ -329,6 +334,10 @@ void note_outcome(DeviceState* ds, const void* w, uint64_t n, const Result& r) {
     h->w = w; h->n = n; h->listed = (float)r.listed / (float)num_chunks_of(n);
 }
 
+// Workgroups per compute unit that the calls in one launch (k_encode_one, k_decode_one) may have on the chip at once: two of
+// either, or one of each, fit a unit by their registers and LDS.
+constexpr uint32_t kOneResident = 2;
+
 // lc_encode (cache == nullptr: two sweeps) and lc_encode_cached (one sweep that counts and, when the
 // cache holds a usable table, codes with it; k_table confirms or voids that, and only then does the
 // second sweep have anything to do).
@@ -367,16 +376,14 @@ lc_ssize encode_impl(const void* w, const void* w_ref, uint64_t n, int nbits, vo
     Result* result = &g_pinned_dev[slot].enc;
     // Every call leaves the encode state cleared behind it; a fresh scratch area, or one whose last
     // call did not run to its end, is cleared first.
-    if (!area->clean) { Timed t(kSlotReset, s); launch_reset(ws, group_words, chunk_maxexp, s); memset(area->met, 0, sizeof(area->met)); }
+    if (!area->clean || !area->counted) { Timed t(kSlotReset, s); launch_reset(ws, group_words, chunk_maxexp, s); area->cleared(); }
     area->clean = false;
     // A short vector that the caller waits for: one launch, whose workgroups wait for each other (k_encode_one).  They fit the
-    // chip together as long as all such calls in progress have at most kOneResident workgroups per compute unit (two of
-    // k_encode_one fit one by their registers and LDS); a call beyond that, and one whose workgroups did not meet in time
+    // chip together as long as all such calls in progress have at most kOneResident workgroups per compute unit; a call beyond that, and one whose workgroups did not meet in time
     // because other work held the chip, takes four kernels.  Whole calls, four kernels / one, us: fp32 2^14 34.1 / 27.3, 2^20
     // 40.8 / 29.0, 2^22 46.6 / 30.1, 2^23 56.6 / 45.0; bf16 2^20 38.2 / 28.0, 2^23 48.3 / 42.5; with a cached table that holds,
     // 2^16 57.0 / 27.8, 2^23 66.5 / 45.7.  Beyond that a chunk's deltas no longer fit the registers of a chip-wide grid.
     const uint32_t nchunks = (uint32_t)num_chunks_of(n);
-    constexpr uint32_t kOneResident = 2;
     if (try_one && !async && !staged && dtype != LC_F64 && nchunks >= 1 && nchunks <= (uint32_t)(ds->tune.num_cu * ds->tune.one_per_cu) &&
         ds->one_blocks + nchunks <= kOneResident * (uint32_t)ds->tune.num_cu) {
         Result& r = g_pinned[slot].enc;
@@ -391,10 +398,10 @@ lc_ssize encode_impl(const void* w, const void* w_ref, uint64_t n, int nbits, vo
         const hipError_t waited = hipStreamSynchronize(s);
         if (!serial) lock.lock();
         ds->one_blocks -= nchunks;
-        if (waited != hipSuccess) { (void)hipGetLastError(); area->clean = false; return -LC_ERR_HIP; }
+        if (waited != hipSuccess) { (void)hipGetLastError(); area->counted = false; return -LC_ERR_HIP; }
         if (r.status == LC_ERR_HIP) {
             // they did not meet: what they left in the scratch area is cleared by the next call that takes it
-            area->clean = false;
+            area->counted = false;
             free_slot(slot);
             undo.armed = false;
             lock.unlock();
@@ -559,7 +566,8 @@ namespace {
 // blob_bytes: what the caller says its buffer holds (SIZE_MAX: not stated); the header's total may not pass it
 // verify_only: nothing but the blob is read (lc_verify); else the restore, after the same lane-string check if the
 // option asks for it
-lc_ssize decode_impl(const void* blob, size_t blob_bytes, void* w_ref, uint64_t n, int dtype, void* stream, bool verify_only = false) {
+lc_ssize decode_impl(const void* blob, size_t blob_bytes, void* w_ref, uint64_t n, int dtype, void* stream, bool verify_only = false,
+                     bool try_one = true) {
     if (!blob || misaligned(blob, 16) || n > LC_MAX_N) return -LC_ERR_BADARG;
     if (blob_bytes < kHeaderBytes) return -LC_ERR_BAD_BLOB;
     if (dtype != LC_F32 && dtype != LC_BF16 && dtype != LC_F16 && dtype != LC_F64) return -LC_ERR_BADARG;
@@ -574,13 +582,49 @@ lc_ssize decode_impl(const void* blob, size_t blob_bytes, void* w_ref, uint64_t 
     Workspace* ws = static_cast<Workspace*>(area->mem);
     const int slot = take_slot(false);
     if (slot < 0) return -LC_ERR_HIP;
-    struct Undo { int slot; ~Undo() { free_slot(slot); } } undo{slot};     // (the lock is held on every return)
+    struct Undo { int slot; ~Undo() { if (slot >= 0) free_slot(slot); } } undo{slot};     // (the lock is held on every other return)
     HostResult* host = &g_pinned_dev[slot];
     const uint8_t* b = static_cast<const uint8_t*>(blob);
     const uint64_t epoch = ++g_epoch;
+    const uint64_t bound = lc_encode_bound(n, 4), max_total = blob_bytes < bound ? blob_bytes : bound;
+    // A short vector in one launch, whose workgroups wait for each other's findings before they touch w_ref (see encode_impl for
+    // when).  Two kernels / one, us: fp32 2^14 33.9 / 23.5, 2^20 35.4 / 24.9, 2^22 37.8 / 25.8, 2^23 40.4 / 29.0; bf16 2^20 35.2 /
+    // 26.2, 2^23 37.2 / 31.7; fp64 2^20 39.8 / 27.8; codes above 10 bits in an array that is off alignment 2^20 89.5 / 35.9; hardly a
+    // kept symbol 2^20 26.2 / 23.7, 2^22 24.8 / 23.0, 2^23 25.2 / 26.3.
+    const uint32_t nchunks = (uint32_t)num_chunks_of(n);
+    if (try_one && !verify_only && !g_verify_first && nchunks >= 1 && nchunks <= (uint32_t)(ds->tune.num_cu * ds->tune.one_dec_per_cu) &&
+        ds->one_blocks + nchunks <= kOneResident * (uint32_t)ds->tune.num_cu) {
+        HostResult& r = g_pinned[slot];
+        r.bytes[0] = UINT64_MAX;                               // (stays so unless the workgroups met)
+        if (!area->counted) {
+            const Scratch sc(ws, 0, 1);
+            Timed t(kSlotReset, s);
+            launch_reset(ws, sc.group_words, sc.chunk_maxexp, s);
+            area->cleared();
+        }
+        { Timed t(kSlotDecodeOne, s); launch_decode_one(b, w_ref, n, dtype, max_total, ws, epoch, host, area->met_dec, (uint32_t)ds->tune.one_wait, s); }
+        LC_HIP(hipGetLastError());
+        if (!release(area, s)) return -LC_ERR_HIP;
+        ds->one_blocks += nchunks;
+        const bool serial = g_prof;
+        if (!serial) lock.unlock();
+        const hipError_t waited = hipStreamSynchronize(s);
+        if (!serial) lock.lock();
+        ds->one_blocks -= nchunks;
+        if (waited != hipSuccess) { (void)hipGetLastError(); area->counted = false; return -LC_ERR_HIP; }
+        const int slots[] = {kSlotDecodeOne};
+        collect(slots, 1);
+        if ((r.dec_status >> 8) == epoch) { if (r.bytes[0] == UINT64_MAX) area->counted = false; return -(lc_ssize)(r.dec_status & 0xFF); }
+        if (r.bytes[0] != UINT64_MAX) return (lc_ssize)r.bytes[0];
+        // they did not meet, and none has touched w_ref: the next call that takes the scratch area clears what they left there
+        area->counted = false;
+        free_slot(slot);
+        undo.slot = -1;
+        lock.unlock();
+        return decode_impl(blob, blob_bytes, w_ref, n, dtype, stream, verify_only, false);
+    }
     BlobList list;
     for (int t = 0; t < kMaxSets; ++t) list.p[t] = b;
-    const uint64_t bound = lc_encode_bound(n, 4), max_total = blob_bytes < bound ? blob_bytes : bound;
     { Timed t(kSlotDecCheck, s); launch_dec_check(list, 0, 1, n, dtype, max_total, ws, epoch, host, s); }
     // (a finding of the verifying sweep gates the restoring one on the device, like a finding of the check)
     if (verify_only || g_verify_first) { Timed t(kSlotVerify, s); launch_decode(b, nullptr, n, dtype, ws, 0, epoch, host, ds->tune, s); }

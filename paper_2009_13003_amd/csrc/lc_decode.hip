@@ -1,7 +1,7 @@
 // Decode kernels of the LC-Checkpoint compress / restore path for gfx950 (wave64): restore by
 // accumulation (Algorithm 1 line 7; Section 3, C1).
 //
-// lc_decode:        k_dec_check -> k_decode (gated on the check's verdict, no host round trip between)
+// lc_decode:        k_dec_check -> k_decode (gated on the check's verdict, no host round trip between); a short vector: k_decode_one
 // lc_decode_many:   k_dec_check (all blobs) -> k_decode_fused<T> per sweep
 // lc_decode_batch:  kb_dec_tables -> kb_dec_chunks -> kb_decode
 #include "lc_device.h"
@@ -16,106 +16,33 @@ struct DecBuild {
     uint8_t one[1u << kMultiBits];            // over the next 10 bits: symbol | len << 4 of the first code (see dec_build_luts)
 };
 
-// By the first wavefront of a workgroup, lane j holding symbol j: validates the header's symbol table, builds the canonical
-// codes and fills D.info; B.len / B.code are left for dec_build_luts.  Returns (in every lane) whether the blob passes.
+// The same by the first wavefront of a workgroup, left in D.info for the sweep and in B for dec_build_luts.
 __device__ __forceinline__ bool dec_symbol_table(const u32* hdr, u64 n, u32 nchunks, u64 area, u64 tw, DecSet& D, DecBuild& B) {
-    const u32 nbits = hdr[4], K = hdr[5], lane = lane_id();
-    // binary64 blobs (element type 3): 12-bit bucket ids, 64-bit representatives with the high halves at offset 320
-    const bool wide = hdr[15] == (u32)kF64;
-    const u32 emask = wide ? 2047u : 255u, nbuckets = 2 * (emask + 1);
-    bool ok = nbits >= 1 && nbits <= 4 && K <= (1u << nbits) - 1 && hdr[6] == kW && hdr[7] == kV && hdr[8] == kR;
-    if (nchunks == 0 && tw != 0) ok = false;
-    u32 len = 0, rep = 0, rep_hi = 0;
-    u64 cn = 0;
-    bool bad = false;
-    if (ok && lane <= K) {
-        const u32 j = lane, w0 = hdr[16 + 4 * j], bucket = w0 & 0xFFFFu;
-        rep = hdr[17 + 4 * j]; rep_hi = wide ? hdr[80 + j] : 0u;
-        cn = hdr[18 + 4 * j] | ((u64)hdr[19 + 4 * j] << 32);
-        len = (w0 >> 16) & 0xFFu;
-        if ((cn > 0) != (len > 0) || len > 15 || (w0 >> 24) != 0) { bad = true; len = 0; }
-        if (j < K && (bucket >= nbuckets || (bucket & emask) == 0 || (bucket & emask) == emask)) bad = true;
-        if (j < K && (wide ? (rep_hi >> 20) : (rep >> 23)) != bucket) bad = true;
-        if (j == K && (rep | rep_hi) != 0) bad = true;
-    }
-    // (counts that add up to n modulo 2^64, as one running sum would have it)
-    const u64 cnt_sum = wave_sum64(cn);
-    const u32 kraft = wave_sum32(len ? 1u << (15 - len) : 0u), active = (u32)__popcll(__ballot(len != 0));
-    if (ok && (__any(bad) || cnt_sum != n || (active >= 2 && kraft != (1u << 15)) || (active == 1 && kraft != (1u << 14)))) ok = false;
-    // canonical codes: within a length in symbol order, the first code of a length from the counts below it
-    u32 code = 0, first = 0, shorter = 0;
-    for (u32 L = 1; L < kMaxSym; ++L) {
-        const u64 m = __ballot(len == L);
-        first = (first + shorter) << 1;
-        shorter = (u32)__popcll(m);
-        if (len == L) code = first + (u32)__popcll(m & ((1ull << lane) - 1));
-    }
-    const u32 max_len = wave_max_u32(len);
+    const u32 lane = lane_id();
+    DecSymbol sy;
+    const bool ok = dec_symbols(hdr, n, nchunks, tw, &sy);
+    const u32 max_len = wave_max_u32(sy.len);
     if (lane < kMaxSym) {
-        B.len[lane] = len; B.code[lane] = code;
-        D.info.rep_bits[lane] = rep; D.info.rep_hi[lane] = rep_hi;
-        D.info.len[lane] = len; D.info.code[lane] = code;
+        B.len[lane] = sy.len; B.code[lane] = sy.code;
+        D.info.rep_bits[lane] = sy.rep; D.info.rep_hi[lane] = sy.rep_hi;
+        D.info.len[lane] = sy.len; D.info.code[lane] = sy.code;
     }
-    if (lane == 0) { B.max_len = max_len; D.info.K = K; D.info.max_len = max_len; D.info.area = area; D.info.total_words = tw; }
+    if (lane == 0) { B.max_len = max_len; D.info.K = hdr[5]; D.info.max_len = max_len; D.info.area = area; D.info.total_words = tw; }
     return ok;
 }
 
-// The sweeps' tables, by a workgroup of 256 threads.  One symbol per look-up over the next P bits: symbol | len << 4; a
-// prefix that starts no code: symbol K with length 0 (the lane then falls short of its stated length); a prefix of a code
-// longer than P bits: 0xFF.  From the table over 10 bits every entry of D.multi is then put together by taking codes off
-// the front of its 10 bits, a thread's four entries side by side; D.lut1 is the same table over 7 bits, for the fused
-// restore.  (The other workgroups of the kernel are long done: every dependent step here is latency of the call.)
+// By a workgroup of 256 threads, from what dec_symbol_table left in B; D.lut1 is the table of single symbols over 7 bits, for
+// the fused restore.
 __device__ __forceinline__ void dec_build_luts(DecSet& D, DecBuild& B, u32 K, u32 t) {
-    constexpr u32 kEach = (1u << kMultiBits) / 256;
     const u32 lane = t & (kW - 1);
     const u32 len = lane < kMaxSym ? B.len[lane] : 0u, code = lane < kMaxSym ? B.code[lane] : 0u;
-    const u32 M = wave_max_u32(len);
-    u32 e[kEach];
-#pragma unroll
-    for (u32 k = 0; k < kEach; ++k) e[k] = K;
-    for (u32 j = 0; j <= K; ++j) {
-        const u32 L = read_lane(len, j), cj = read_lane(code, j);
-        if (L == 0) continue;
-        const u32 sh = L <= kMultiBits ? kMultiBits - L : 0u, want = L <= kMultiBits ? cj : cj >> (L - kMultiBits);
-        const u32 put = L <= kMultiBits ? (j | (L << 4)) : 0xFFu;
-#pragma unroll
-        for (u32 k = 0; k < kEach; ++k) if (((t + 256 * k) >> sh) == want) e[k] = put;
-    }
-#pragma unroll
-    for (u32 k = 0; k < kEach; ++k) B.one[t + 256 * k] = (uint8_t)e[k];
-    __syncthreads();
-    const u32 P1 = M < kDecLut1Bits ? M : kDecLut1Bits;
+    // (a prefix that starts no code: nothing is ever taken off again, and the lane falls short of its stated length)
+    dec_build_multi<256>(D.multi, B.one, nullptr, (K * 0x111111u) | (kMultiSyms << 28), len, code, K, t);
+    const u32 M = wave_max_u32(len), P1 = M < kDecLut1Bits ? M : kDecLut1Bits;
     if (t < (1u << P1)) {
         const u32 f = B.one[t << (kMultiBits - P1)];
         D.lut1[t] = (f == 0xFF || (f >> 4) > P1) ? (uint8_t)0xFF : (uint8_t)f;
     }
-    u32 rest[kEach], left[kEach], syms[kEach], cnt[kEach];
-    bool on[kEach];
-#pragma unroll
-    for (u32 k = 0; k < kEach; ++k) {
-        // (the first code of the entry is the one just found)
-        const u32 L = e[k] >> 4, i = t + 256 * k;
-        on[k] = e[k] != 0xFF && L != 0;
-        syms[k] = on[k] ? e[k] & 15u : 0u; cnt[k] = on[k] ? 1u : 0u;
-        rest[k] = on[k] && L < kMultiBits ? i << (32 - kMultiBits + L) : 0u; left[k] = on[k] ? kMultiBits - L : kMultiBits;
-        if (e[k] != 0xFF && L == 0) {                       // starts no code: nothing is ever taken off again
-            for (; cnt[k] < kMultiSyms; ++cnt[k]) syms[k] |= K << (4 * cnt[k]);
-        }
-    }
-#pragma unroll
-    for (u32 s = 1; s < kMultiSyms; ++s) {
-        u32 f[kEach];
-#pragma unroll
-        for (u32 k = 0; k < kEach; ++k) f[k] = B.one[rest[k] >> (32 - kMultiBits)];
-#pragma unroll
-        for (u32 k = 0; k < kEach; ++k) {
-            const u32 L = f[k] >> 4;
-            on[k] = on[k] && f[k] != 0xFF && L != 0 && L <= left[k];
-            if (on[k]) { syms[k] |= (f[k] & 15u) << (4 * s); ++cnt[k]; rest[k] <<= L; left[k] -= L; }
-        }
-    }
-#pragma unroll
-    for (u32 k = 0; k < kEach; ++k) D.multi[t + 256 * k] = syms[k] | ((kMultiBits - left[k]) << 24) | (cnt[k] << 28);
 }
 
 // One chunk's place in the offset table against the lane lengths of its record, by one wavefront.
@@ -155,12 +82,6 @@ __device__ __forceinline__ bool dec_chunks_ok4(const uint8_t* blob, u64 area, u6
         all = all && ok[k] && (o[k + 1] - o[k] == kLaneBitsWords + ((sum + 31) >> 5)) && sum > 0 && !__any(lb[k] > kR * kV * 15);
     }
     return all;
-}
-
-__device__ __forceinline__ void raise_status(Workspace* ws, HostResult* host, u64 epoch, u32 status) {
-    const u64 word = (epoch << 8) | status;
-    atomicMax(&ws->dec_status, word);     // gates the decode sweep on the device
-    host->dec_status = word;              // what the host reads after waiting for the stream (any finding will do)
 }
 
 // Everything lc_decode verifies before w_ref is touched, in one launch.  Every workgroup
@@ -242,26 +163,9 @@ constexpr u32 kPayWords = 2048;      // three: 4 bits per element on average
 constexpr u32 kPayWordsTwo = 4224;   // two: 8 bits
 constexpr u32 kPayWordsVerify = 3040;               // three of the verifying sweep, which has no ring (2^28 dense elements 95 us, 119 with two)
 constexpr u32 kPayWordsOne = kChunk * 15 / 32 + 4;  // one: 15 bits, the longest payload there is, wherever it starts in a vector
-constexpr u32 kSparseSlack = 1024;   // bits above an all-merged chunk up to which a chunk's kept symbols are restored one by one
-                                     // (512 instead: a batch of 2^24 elements at 2 bits 49 us, 40 so; 2048: the same)
 constexpr u32 kSparseLaneSlack = 64; // the same for one lane's string
 constexpr u32 kRingWords = 8;        // words of 8 symbols that a lane may be ahead of the rows being restored
 constexpr u32 kGroupRows = 8;        // rows restored at a time: 32 symbols, 4 words of the ring per lane
-
-struct DecLds {
-    alignas(16) u32 multi[1u << kMultiBits];
-    float rep[kMaxSym];
-    // the codes of more than 10 bits: symbol | len << 4 at [the next 15 bits - long_base].  They are the last codes in
-    // canonical order, so the windows that start with one are the top of the 15-bit range; the code being complete, each
-    // 10-bit prefix among those holds at least two of the 16 symbols, so there are at most 8 such prefixes
-    alignas(4) uint8_t longs[8u << (15 - kMultiBits)];
-    u32 long_base;
-    double rep64[kMaxSym];            // binary64 blobs: the representatives (rep is not used then)
-    template <int DT> __device__ __forceinline__ typename Val<DT>::type rep_of(u32 sy) const {
-        if constexpr (DT == kF64) return rep64[sy];
-        else return rep[sy];
-    }
-};
 
 // What a wavefront keeps of a blob's code in registers, the same in every lane.
 struct CodeLens {
@@ -276,57 +180,6 @@ struct CodeLens {
         const u32 merged = read_lane(len, K);
         sparse = __any(lane < K && len != 0 && len <= merged) ? 0u : merged;
     }
-};
-
-// the one symbol of a window whose first code is longer than the table's 10 bits, as an entry of the table
-template <typename LDS>
-__device__ __forceinline__ u32 decode_long(const LDS& L, u64 win) {
-    const u32 e = L.longs[((u32)(win >> (64 - 15)) - L.long_base) & (sizeof(L.longs) - 1)];
-    return (e & 15u) | ((e >> 4) << 24) | (1u << 28);
-}
-
-// That table, by one wavefront, lane j holding the length and code of symbol j (0 in lanes without one): 4 entries per lane.
-// (A search through the symbols instead, a dependent look-up each, was most of a restore's time where such codes are
-// many: 2^24 fp32 elements of 10 layers at 4 bits 193 us, 71 with the table.)
-template <typename LDS>
-__device__ __forceinline__ void build_longs(LDS& L, u32 len, u32 code) {
-    const u32 base = 0x8000u - wave_max_u32(len > kMultiBits ? 0x8000u - (code << (15 - len)) : 0u);
-    static_assert(sizeof(L.longs) == 4 * kW, "four entries per lane");
-    u32 e[4] = {0, 0, 0, 0};                       // (nothing decodes to these: the windows past the last code do not exist)
-    for (u64 m = __ballot(len > kMultiBits); m != 0; m &= m - 1) {
-        const u32 j = (u32)__builtin_ctzll(m), lj = read_lane(len, j), cj = read_lane(code, j);
-#pragma unroll
-        for (u32 k = 0; k < 4; ++k) if (((base + 4 * lane_id() + k) >> (15 - lj)) == cj) e[k] = j | (lj << 4);
-    }
-    reinterpret_cast<u32*>(L.longs)[lane_id()] = e[0] | (e[1] << 8) | (e[2] << 16) | (e[3] << 24);
-    if (lane_id() == 0) L.long_base = base;
-}
-
-// MSB-first bit window over payload words that live in LDS (STAGED) or in global memory.
-template <bool STAGED>
-struct BitReader {
-    const u32* pw;                   // payload words (index 0 = first word of the chunk's payload)
-    u32 last;                        // index of the last payload word (reads are clamped to it)
-    u64 win;                         // next bits, left aligned
-    u32 avail, wi, next;             // valid bits in win; index of `next`; the word after the window
-    __device__ __forceinline__ u32 word(u32 i) const { return pw[min(i, last)]; }
-    __device__ __forceinline__ void start(const u32* words, u32 nwords, u32 first_bit) {
-        pw = words; last = nwords - 1;
-        wi = first_bit >> 5;
-        const u32 sh = first_bit & 31;
-        win = (((u64)word(wi) << 32) | word(wi + 1)) << sh;
-        avail = 64 - sh;
-        wi += 2;
-        next = word(wi);
-    }
-    __device__ __forceinline__ void refill() {           // leaves at least 33 valid bits
-        if (avail <= 32) {
-            win |= (u64)next << (32 - avail);
-            avail += 32; ++wi;
-            next = word(wi);
-        }
-    }
-    __device__ __forceinline__ void drop(u32 len) { win <<= len; avail -= len; }
 };
 
 // `raise(code)` reports a lane string that does not decode to its stated length.

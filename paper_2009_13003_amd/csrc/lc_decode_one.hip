@@ -1,0 +1,255 @@
+// The restore of a short vector in one launch (gfx950, wave64): Algorithm 1 line 7; Section 3, C1.
+#include "lc_meeting.h"
+
+namespace lc {
+
+// ----------------------------------------------------------------------------- k_decode_one
+// The restore of a short vector in one launch: a workgroup of eight wavefronts per chunk, all of them resident together.
+// With a wavefront per chunk most of the chip idles while each lane's string of 256 codes is taken apart step by step and
+// its rows are restored behind that, 37,000 cycles at 2^20 elements, behind a check kernel of 15,000; so, all of it is 25,000
+// (whole calls, two kernels / one, us: see decode_impl).  Here every workgroup checks
+// the header and its chunk for itself and builds the tables in LDS; the workgroups meet (GridMeeting) between their findings
+// and the first store, so that a blob that is refused leaves w_ref untouched, and the meeting's wait lies behind the decoding.
+//
+// A string is decoded in eight segments at once, one per wavefront: cut at eighths of its bits, each segment is
+// first taken from its cut, in the middle of some code.  A prefix code falls into step with itself after a few codes, so
+// where such a segment passes its end is mostly right; each is then taken again from where the one before it ended, until no
+// start moves any more.  The first segment starts right, so after turn k the first k are right whatever the string, and
+// mostly all are after two.  Then the segments' numbers of symbols are known, and a last turn notes the symbols in
+// their places.  (A segment's end is the first code that starts at or behind the cut, so that it does not depend on the steps.)
+constexpr u32 kSegs = 8, kOneDecThreads = kSegs * kW, kOneSegRows = kR / kSegs;
+constexpr u32 kOnePayWords = kChunk * 15 / 32;               // the longest payload there is
+
+struct OneDecLds {
+    DecLds tab;
+    uint8_t one[1u << kMultiBits];
+    uint16_t ends[1u << kMultiBits];
+    u32 hdr[kHeaderBytes / 4];
+    alignas(16) u32 pay[kOnePayWords];
+    u32 syms[kR * kV / 8][kW];           // 8 symbols of 4 bits per word: row k of lane l is in [k / 2][l]
+    u32 end[kSegs][kW], count[kSegs][kW];
+    u32 go, moved[kSegs + 1];            // (the last: some string is wrong)
+};
+
+struct OneDecArgs {
+    const uint8_t* blob; void* w_ref; u64 n, max_total;
+    Workspace* ws; HostResult* host; u64 epoch;
+    u64 goal[kMeetLines];
+    u32 nchunks, lines, limit;
+};
+
+// This lane's segment from bit `from` of its string to the first code that starts at `to` or behind: where that is, and how many
+// symbols lie between.  NOTE: they go to the lane's column of `noted`, from symbol `at` on (never past its 256).  *bad: a prefix
+// that starts no code.  LONG: some codes are longer than 10 bits.
+constexpr u32 kNoCode = kMultiBits << 24;                    // the table's entry for one: no symbols
+template <bool NOTE, bool LONG>
+__device__ __forceinline__ u32 take_segment(const OneDecLds& L, u32 nwords, u32 first_bit, u32 from, u32 to,
+                                            u32* noted, u32 at, u32* count, bool* bad) {
+    constexpr u32 kStep = LONG ? 15 : kMultiBits;            // bits a step may take
+    BitReader<true> br;
+    br.start(L.pay, nwords, first_bit + from);
+    u32 pos = from, i = at;
+    bool none = false;
+    auto look = [&](bool on) {
+        u32 e = L.tab.multi[(u32)(br.win >> (64 - kMultiBits))];
+        if (LONG && __any(on && e == 0)) { if (e == 0) e = decode_long(L.tab, br.win); }
+        none = none || (on && e == kNoCode);
+        return e;
+    };
+    auto take = [&](u32 sy, u32 len, u32 m) {
+        if (NOTE) {
+            const u64 s = (u64)sy << (4 * (i & 7));
+            const u32 w = i >> 3;
+            if (w < kR * kV / 8) atomicOr(&noted[w * kW], (u32)s);
+            if ((s >> 32) != 0 && w + 1 < kR * kV / 8) atomicOr(&noted[(w + 1) * kW], (u32)(s >> 32));
+        }
+        i += m; pos += len;
+        br.drop(len);
+    };
+    while (__any(pos + kStep <= to)) {                       // whole steps (33 valid bits take three of 10 or two of 15)
+        br.refill();
+#pragma unroll
+        for (int rep = 0; rep < (LONG ? 2 : 3); ++rep) {
+            const bool on = pos + kStep <= to;
+            const u32 e = look(on), x = on ? e : 0u;
+            take(x & 0xFFFFFFu, (x >> 24) & 15u, x >> 28);
+        }
+    }
+    while (__any(pos < to)) {                                // the rest, up to the first code's end that is not before `to`
+        br.refill();
+        const bool on = pos < to;
+        const u32 e = look(on), r = to - pos;
+        const u32 ends = L.ends[(u32)(br.win >> (64 - kMultiBits))], m = on && r <= kMultiBits ? ends >> r : 0u;
+        u32 len = (e >> 24) & 15u, k = e >> 28;
+        if (m != 0) { len = r + (u32)__builtin_ctz(m); k = (u32)__builtin_popcount(ends & ((2u << len) - 1)); }
+        if (!on) { len = 0; k = 0; }
+        take(e & ((1u << (4 * k)) - 1), len, k);
+    }
+    *count = i - at; *bad = none;
+    return pos;
+}
+
+template <int DT>
+__global__ __launch_bounds__(kOneDecThreads, 4) void k_decode_one(OneDecArgs a) {
+    typedef typename Val<DT>::type val_t;
+    __shared__ OneDecLds L;
+    const u32 t = threadIdx.x, lane = lane_id(), v = __builtin_amdgcn_readfirstlane(t >> 6), c = blockIdx.x;
+    const u64 n = a.n, base = (u64)c * kChunk;
+    GridMeeting meet = {a.ws->meeting(), 0, a.lines, a.limit};
+#pragma unroll
+    for (u32 k = 0; k < kMeetLines; ++k) meet.goal = lane == k ? a.goal[k] : meet.goal;
+    if (t < kHeaderBytes / 4) L.hdr[t] = reinterpret_cast<const u32*>(a.blob)[t];
+    for (u32 i = t; i < kR * kV / 8 * kW; i += kOneDecThreads) L.syms[0][i] = 0;
+    __syncthreads();
+    // ---- the header: every workgroup comes to the same findings (as k_dec_check's)
+    const u32* hdr = L.hdr;
+    const u64 hn = hdr[2] | ((u64)hdr[3] << 32), total = hdr[10] | ((u64)hdr[11] << 32), area = chunk_area_of(a.nchunks);
+    const bool sound = hdr[0] == 0x3142434Cu && hdr[1] == (1u | (kHeaderBytes << 16)) && hdr[12] == 0;
+    const bool head_ok = sound && hn == n && hdr[15] == (u32)DT && hdr[9] == a.nchunks && total >= area && total <= a.max_total && ((total - area) & 3) == 0;
+    if (!head_ok) {
+        // (a sound blob for another vector or element type: a bad argument)
+        if (t == 0) {
+            if (c == 0) { raise_status(a.ws, a.host, a.epoch, sound && (hn != n || hdr[15] != (u32)DT) ? 1u : 4u); a.host->bytes[0] = 0; a.host->max_len[0] = 0; }
+            meet.arrive(2);
+        }
+        return;
+    }
+    const u64 tw = (total - area) / 4;
+    const u32 K = hdr[5];
+    // ---- this chunk's record: its place in the offset table, its lane lengths, its payload
+    const u32* off_tab = reinterpret_cast<const u32*>(a.blob + kHeaderBytes);
+    const u64 o0 = load_uniform(off_tab + c), o1 = load_uniform(off_tab + c + 1);
+    bool ok = o0 <= o1 && o1 <= tw && o1 - o0 >= kLaneBitsWords && (c > 0 || o0 == 0) && (c + 1 < a.nchunks || o1 == tw);
+    u32 bits = 0, nwords = 0;
+    if (ok) {
+        typedef u32x4 __attribute__((aligned(4))) u32x4_word;
+        const u32* rec = reinterpret_cast<const u32*>(a.blob + area) + o0;
+        nwords = (u32)min(o1 - o0 - kLaneBitsWords, (u64)kOnePayWords);          // (more than that is refused below)
+        bits = reinterpret_cast<const uint16_t*>(rec)[lane];
+        const u32* from = rec + kLaneBitsWords;
+        for (u32 i = t; i < nwords / 4; i += kOneDecThreads) reinterpret_cast<u32x4*>(L.pay)[i] = reinterpret_cast<const u32x4_word*>(from)[i];
+        if (t < (nwords & 3)) L.pay[nwords / 4 * 4 + t] = from[nwords / 4 * 4 + t];
+    }
+    const u32 incl = wave_incl_scan(bits), sum = read_lane(incl, kW - 1);
+    ok = ok && o1 - o0 == kLaneBitsWords + ((sum + 31) >> 5) && sum > 0 && !__any(bits > kR * kV * 15);
+    // ---- the symbols and their codes (by every wavefront: none waits for another's)
+    DecSymbol sy = {0, 0, 0, 0};
+    const bool table_ok = dec_symbols(hdr, n, a.nchunks, tw, &sy);
+    if (v == 0) {
+        if (lane < kMaxSym) {
+            L.tab.rep[lane] = __uint_as_float(lane < K ? sy.rep : 0x80000000u);
+            L.tab.rep64[lane] = lane < K ? __hiloint2double((int)sy.rep_hi, (int)sy.rep) : -0.0;
+        }
+        if (wave_max_u32(sy.len) > kMultiBits) build_longs(L.tab, sy.len, sy.code);
+        if (t < kSegs + 1) L.moved[t] = 0;
+    }
+    // This wavefront's 8 rows of w_ref, on their way while the strings are decoded; of a chunk of few kept symbols (see kSparseSlack)
+    // only the rows that hold one, and only when that is known (2^23 fp32 elements, sparse: 28.4 us with all of them, 26.0 so).
+    const u32 elems = n - base < kChunk ? (u32)(n - base) : kChunk;
+    const bool sparse = sum <= elems * read_lane(sy.len, K & 15u) + kSparseSlack;
+    val_t x[kOneSegRows][kV];
+    auto row = [&](u32 k) { return base + (u64)(v * kOneSegRows + k) * kRowElems; };
+    auto fetch = [&](u32 k) {
+        if (row(k) + kRowElems <= n) load_row_any<DT>(a.w_ref, row(k) + lane * kV, x[k]);
+        else load_row_v<false, DT>(a.w_ref, row(k) + lane * kV, n, x[k]);
+    };
+    const bool late = DT == kF64 || sparse;                  // (binary64: their registers would spill meanwhile)
+    if (!late) {
+#pragma unroll
+        for (u32 k = 0; k < kOneSegRows; ++k) fetch(k);
+    }
+    const u32 max_len = wave_max_u32(sy.len);
+    ok = ok && table_ok;                                     // (the same in every thread)
+    if (t == 0) {
+        if (!ok) raise_status(a.ws, a.host, a.epoch, 4u);
+        meet.arrive(2, !ok);
+    }
+    bool go = ok;
+    if (ok) {
+        dec_build_multi<kOneDecThreads>(L.tab.multi, L.one, L.ends, kNoCode, sy.len, sy.code, K, t);
+        __syncthreads();
+        // ---- the string of every lane, a segment per wavefront
+        const u32 first_bit = incl - bits, cut = bits * v / kSegs, to = bits * (v + 1) / kSegs;
+        const bool long_codes = max_len > kMultiBits;
+        u32 start = cut, count = 0, end;
+        bool bad = false;
+        auto segment = [&]() {
+            end = long_codes ? take_segment<false, true>(L, nwords, first_bit, start, to, nullptr, 0, &count, &bad)
+                             : take_segment<false, false>(L, nwords, first_bit, start, to, nullptr, 0, &count, &bad);
+            L.end[v][lane] = end;
+        };
+        segment();
+        __syncthreads();
+#pragma unroll 1
+        for (u32 turn = 0; turn < kSegs; ++turn) {           // (after turn k the first k + 2 segments are right)
+            const u32 now = v ? L.end[v - 1][lane] : 0u;
+            const bool moves = __any(now != start);
+            __syncthreads();                                 // (everyone has read the ends)
+            if (moves) {
+                start = now;
+                segment();
+                if (lane == 0) L.moved[turn] = 1;
+            }
+            __syncthreads();
+            if (L.moved[turn] == 0) break;
+        }
+        L.count[v][lane] = count;
+        __syncthreads();
+        u32 before = 0, all = 0;
+#pragma unroll
+        for (u32 k = 0; k < kSegs; ++k) { const u32 m = L.count[k][lane]; before += k < v ? m : 0u; all += m; }
+        const u32 tail = elems % kRowElems;
+        const u32 mine = elems / kRowElems * kV + (tail > lane * kV ? min(tail - lane * kV, kV) : 0u);
+        // a string that does not hold its lane's symbols in exactly its stated length
+        const bool wrong = bad || all != mine || (v == kSegs - 1 && end != bits);
+        if (__any(wrong) && lane == 0) { L.moved[kSegs] = 1; raise_status(a.ws, a.host, a.epoch, 4u); }
+        const u64 seen = v == 0 ? meet.look(2) : 0ull;       // (on its way meanwhile)
+        if (long_codes) take_segment<true, true>(L, nwords, first_bit, start, to, &L.syms[0][lane], before, &count, &bad);
+        else take_segment<true, false>(L, nwords, first_bit, start, to, &L.syms[0][lane], before, &count, &bad);
+        if (v == 0) { const bool met = meet.wait(2, seen); if (lane == 0) L.go = met ? 1u : 0u; }
+        __syncthreads();
+        go = L.go != 0 && L.moved[kSegs] == 0;
+    }
+    if (!go) return;
+    if (c == 0 && t == 0) { a.host->bytes[0] = total; a.host->max_len[0] = max_len; }
+    // ---- Algorithm 1 line 7; a row without a kept symbol stays as it is
+    u32 syms[kOneSegRows];
+    u32 keeps = 0;
+#pragma unroll
+    for (u32 k = 0; k < kOneSegRows; ++k) {
+        syms[k] = (L.syms[(v * kOneSegRows + k) / 2][lane] >> (16 * (k & 1))) & 0xFFFFu;
+        // (places behind the vector's end hold symbol 0: they are masked where they count)
+        keeps |= __any(syms[k] != K * 0x1111u) ? 1u << k : 0u;
+    }
+    if (late) {
+#pragma unroll
+        for (u32 k = 0; k < kOneSegRows; ++k) if ((keeps >> k) & 1u) fetch(k);
+    }
+#pragma unroll
+    for (u32 k = 0; k < kOneSegRows; ++k) {
+        if (((keeps >> k) & 1u) == 0) continue;
+#pragma unroll
+        for (u32 e = 0; e < kV; ++e) x[k][e] = add_rn(x[k][e], L.tab.template rep_of<DT>((syms[k] >> (4 * e)) & 15u));
+        if (row(k) + kRowElems <= n) store4_any<DT>(a.w_ref, row(k) + lane * kV, x[k]);
+        else {
+#pragma unroll
+            for (u32 e = 0; e < kV; ++e)
+                if (row(k) + lane * kV + e < n && ((syms[k] >> (4 * e)) & 15u) != K) store_one_v<DT>(a.w_ref, row(k) + lane * kV + e, x[k][e]);
+        }
+    }
+}
+
+void launch_decode_one(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, uint64_t max_total, Workspace* ws, uint64_t epoch, HostResult* host,
+                       uint64_t (&met)[kMeetLines], uint32_t limit, hipStream_t s) {
+    const u32 nchunks = (u32)num_chunks_of(n), lines = nchunks <= kMeetOneLine ? 1 : kMeetLines;
+    OneDecArgs a = {blob, w_ref, (u64)n, (u64)max_total, ws, host, (u64)epoch, {}, nchunks, lines, limit};
+    for (u32 k = 0; k < lines; ++k) a.goal[k] = met[k] += (nchunks + lines - 1 - k) / lines;
+#define LC_ONE(DT) hipLaunchKernelGGL(k_decode_one<DT>, dim3(nchunks), dim3(kOneDecThreads), 0, s, a)
+    if (dtype == kF64) LC_ONE(kF64);
+    else if (dtype == kBF16) LC_ONE(kBF16);
+    else if (dtype == kF16) LC_ONE(kF16);
+    else LC_ONE(kF32);
+#undef LC_ONE
+}
+
+}  // namespace lc

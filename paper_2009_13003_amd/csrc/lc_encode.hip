@@ -10,7 +10,7 @@
 // recovered state (Algorithm 1 line 4), (sign, exponent) buckets represented by the
 // mean of their extremes and x-bit priority promotion (Section 3.1.1), Huffman
 // coding of the bucket indices (Section 3.1.2).  How it is laid out on the GPU is this library's own.
-#include "lc_device.h"
+#include "lc_meeting.h"
 #include <stddef.h>
 #include <type_traits>
 
@@ -390,6 +390,14 @@ __device__ __forceinline__ u32 rank_buckets(TableLds<EB>& S, const u64 (&c)[tabl
         }
     }
     return read_lane(incl, kW - 1);
+}
+
+// The sum over lanes l, l ^ 16, l ^ 32 and l ^ 48, in all four (gfx950: rows and halves change places without LDS).
+__device__ __forceinline__ u32 rows_sum(u32 v) {
+    const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = a[0] + a[1];
+    const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return b[0] + b[1];
 }
 
 // Huffman code lengths by one wavefront, lane j < 16 holding the count of symbol j (0: does not occur; so do the other lanes);
@@ -1998,42 +2006,7 @@ __global__ __launch_bounds__(256) void k_place(uint8_t* out, Workspace* ws, cons
 // from the count to the code.  What such a call costs in four kernels is not bytes but their starts, the gaps between them
 // and every chunk's round trips to memory (chunk maxima, table, slot, slot again): 2^20 fp32 elements 7.0 + 4.6 + 7.9 + 3.7
 // us and three gaps, 40.8 us the call (29.0 so).  Here the workgroups meet twice: when all counts are in (each then builds the table for itself, from
-// the same counts), and when all record sizes are known (each then knows where its record goes).
-//
-// The meeting.  Everything that passes between workgroups goes through agent-scope atomic operations, whose completion each
-// waits for before it arrives (no fence: writing back the L2 of a die from every workgroup costs more than the launches
-// saved).  A workgroup may wait for one that has not started, because others' kernels hold the chip: the host launches
-// this kernel only while all workgroups of such calls fit the chip together, and the wait is bounded.  It is given up by
-// marking a counter that is not yet full, so either every counter filled up unmarked, and no one can give up any more, or one
-// is marked, and no one finds them full; the header's workgroup then does not report, and the host runs the call in four
-// kernels.  A meeting of 64 workgroups takes 1.2 us, of 256 1.5 (one counter for all: 1.4 and 3.7).
-struct GridMeeting {
-    OneSync* sync;
-    u64 goal;                // lane k: what counter k stands at when all have arrived
-    u32 lines, limit;        // counters; how often to look
-    __device__ __forceinline__ void arrive(u32 which) const {        // by one thread, behind the others' waits for their own operations
-        __hip_atomic_fetch_add(&sync->line[which][blockIdx.x % lines].arrived, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __device__ __forceinline__ bool wait(u32 which) const {          // by one wavefront; whether all have arrived
-        const u32 lane = lane_id();
-        unsigned long long* mine = &sync->line[which][lane < lines ? lane : 0].arrived;
-        for (u32 i = 0;; ++i) {
-            u64 seen = __hip_atomic_load(mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (__any(lane < lines && (seen & kGivenUp) != 0)) return false;
-            const u64 missing = __ballot(lane < lines && seen != goal);
-            if (missing == 0) return true;
-            if (i >= limit) {                        // (fails only if another has arrived there: at most as often as there are workgroups)
-                bool marked = false;
-                if (lane == (u32)__builtin_ctzll(missing))
-                    marked = __hip_atomic_compare_exchange_strong(mine, &seen, seen | kGivenUp, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (__any(marked)) return false;
-            } else if (i >= 64) __builtin_amdgcn_s_sleep(8);
-        }
-    }
-};
-__device__ __forceinline__ void wait_own_operations() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
-template <typename T> __device__ __forceinline__ T load_shared(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
-
+// the same counts), and when all record sizes are known (each then knows where its record goes); see GridMeeting.
 // A cached table's lengths (lc_encode_cached; see k_spec_table), by one wavefront, lane j holding symbol j: whether the cache
 // is usable.
 __device__ __forceinline__ bool cached_table(const TableCache* cache, int nbits, u32* kept, u32* len) {
@@ -2056,7 +2029,7 @@ struct OneArgs {
     uint8_t* out; Workspace* ws; u32* record_words; TableCache* cache; Result* host_result;
     u64 goal[kMeetLines];
     u32 nchunks, lines, limit;
-    int nbits, aligned;
+    int nbits;
 };
 constexpr u32 kOneCopies = 16;      // LDS copies of the chunk's counts (8 of them serve a wavefront in twice the time: it is not
                                     // hidden behind a stream here), then 8 of the buckets' smallest and largest patterns
@@ -2075,7 +2048,7 @@ __global__ __launch_bounds__(kWgThreads, 4) void k_encode_one(OneArgs a) {
     Workspace* ws = a.ws;
     const u64 n = a.n;
     const u32 t = threadIdx.x, lane = lane_id(), v = __builtin_amdgcn_readfirstlane(t >> 6), c = blockIdx.x, first_row = kWgRows * v;
-    const bool full = a.aligned && (u64)(c + 1) * kChunk <= n;
+    const bool full = (u64)(c + 1) * kChunk <= n;
     GridMeeting meet = {ws->meeting(), 0, a.lines, a.limit};
 #pragma unroll
     for (u32 k = 0; k < kMeetLines; ++k) meet.goal = lane == k ? a.goal[k] : meet.goal;
@@ -2089,10 +2062,15 @@ __global__ __launch_bounds__(kWgThreads, 4) void k_encode_one(OneArgs a) {
         raw_t A[kWgRows], B[kWgRows];
         if (full) {
 #pragma unroll
-            for (u32 k = 0; k < kWgRows; ++k) { A[k] = load_raw<DT>(a.w, row_at(c, first_row + k)); B[k] = load_raw<DT>(a.w_ref, row_at(c, first_row + k)); }
+            for (u32 k = 0; k < kWgRows; ++k) { A[k] = load_raw_any<DT>(a.w, row_at(c, first_row + k)); B[k] = load_raw_any<DT>(a.w_ref, row_at(c, first_row + k)); }
         } else {
 #pragma unroll
-            for (u32 k = 0; k < kWgRows; ++k) { A[k] = load_raw_guarded<DT>(a.w, row_at(c, first_row + k), n); B[k] = load_raw_guarded<DT>(a.w_ref, row_at(c, first_row + k), n); }
+            for (u32 k = 0; k < kWgRows; ++k) {
+                const u64 i = row_at(c, first_row + k);
+                const bool whole = i - lane * kV + kRowElems <= n;          // (the same in every lane)
+                A[k] = whole ? load_raw_any<DT>(a.w, i) : load_raw_guarded<DT>(a.w, i, n);
+                B[k] = whole ? load_raw_any<DT>(a.w_ref, i) : load_raw_guarded<DT>(a.w_ref, i, n);
+            }
         }
         fill(0, 512 * kOneCopies, 0);
         if (v == 1 && a.cache) {
@@ -2468,8 +2446,7 @@ void launch_pack_keys(const void* w, const void* w_ref, uint64_t n, Workspace* w
 void launch_encode_one(const void* w, const void* w_ref, uint64_t n, int nbits, int dtype, uint8_t* out, Workspace* ws, uint32_t* record_words,
                        TableCache* cache, Result* host_result, uint64_t (&met)[kMeetLines], uint32_t limit, hipStream_t s) {
     const u32 nchunks = (u32)num_chunks_of(n), lines = nchunks <= kMeetOneLine ? 1 : kMeetLines;
-    OneArgs a = {w, w_ref, (u64)n, out, ws, record_words, cache, host_result, {}, nchunks, lines, limit, nbits,
-                 aligned_rows(w, dtype) && aligned_rows(w_ref, dtype) ? 1 : 0};
+    OneArgs a = {w, w_ref, (u64)n, out, ws, record_words, cache, host_result, {}, nchunks, lines, limit, nbits};
     for (u32 k = 0; k < lines; ++k) a.goal[k] = met[k] += (nchunks + lines - 1 - k) / lines;
     if (dtype == kBF16) hipLaunchKernelGGL(k_encode_one<kBF16>, dim3(nchunks), dim3(kWgThreads), 0, s, a);
     else if (dtype == kF16) hipLaunchKernelGGL(k_encode_one<kF16>, dim3(nchunks), dim3(kWgThreads), 0, s, a);

@@ -112,13 +112,13 @@ struct Ext64 {
     uint8_t symlen_of_bucket[kBuckets64];
 };
 
-// Where the workgroups of a short encode meet (k_encode_one): counters of arrivals, workgroup i at counter i mod kMeetLines (one
+// Where the workgroups of a short encode (k_encode_one, twice) and of a short restore (k_decode_one) meet: counters of arrivals, workgroup i at counter i mod kMeetLines (one
 // counter for all in a small grid), each in a line of its own (see kHistCells).  They only ever grow, the host knows
-// what they stand at; the highest bit says that the meeting was given up.
+// what they stand at; the highest bit says that the meeting was given up, those from kRefused on that a workgroup refused.
 constexpr uint32_t kMeetLines = 8, kMeetOneLine = 16;        // up to kMeetOneLine workgroups: one counter
-constexpr uint64_t kGivenUp = 1ull << 63;
+constexpr uint64_t kGivenUp = 1ull << 63, kRefused = 1ull << 48;
 struct OneSync {
-    struct alignas(128) { unsigned long long arrived; } line[2][kMeetLines];
+    struct alignas(128) { unsigned long long arrived; } line[3][kMeetLines];
 };
 
 struct Workspace : EncState {
@@ -148,7 +148,7 @@ __host__ __device__ inline uint32_t slot_words_of(int nbits) { return kLaneBitsW
 __host__ __device__ inline uint64_t chunk_area_of(uint64_t nchunks) { return kHeaderBytes + (4 * (nchunks + 1) + 15) / 16 * 16; }
 
 enum Slot { kSlotReset = 0, kSlotHist, kSlotTable, kSlotPack, kSlotPlace, kSlotSpecTable, kSlotSpecSweep,
-            kSlotDecCheck, kSlotDecode, kSlotDecodeFused, kSlotHistKeys, kSlotPackKeys, kSlotVerify, kSlotEncodeOne, kNumSlots };
+            kSlotDecCheck, kSlotDecode, kSlotDecodeFused, kSlotHistKeys, kSlotPackKeys, kSlotVerify, kSlotEncodeOne, kSlotDecodeOne, kNumSlots };
 
 // Launch shapes; defaults chosen by measurement, overridable through LC_TUNE_* environment
 // variables (read once) for sweeps.
@@ -161,7 +161,8 @@ struct Tuning {
     int unlisted_per_cu = 4;           // a call of at most this many chunks of 4-byte elements (half of 2-byte) per compute unit does
                                        // without a list of chunks to read (below 16: see stage_keys)
     int batch_unlisted_per_cu = 8;     // ... a batched call
-    int one_per_cu = 2;                // chunks per compute unit up to which a call is encoded in one launch (0: never)
+    int one_per_cu = 2;                // chunks per compute unit up to which a call is encoded in one launch (0: never),
+    int one_dec_per_cu = 2;            // ... and restored
     int one_wait = 4096;               // how often its workgroups look for each other before they give up
     int spec_waves_per_cu = 8;         // of the single sweep of the cached encode (what its LDS and registers allow)
     int batch_waves_per_cu = 8;        // of the batch kernels
@@ -255,6 +256,10 @@ void launch_dec_check(const BlobList& blobs, int first, int count, uint64_t n, i
 // (set: which of the workspace's decode sets the check kernel filled for this blob; w_ref null: only verify the lane strings)
 void launch_decode(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, Workspace* ws, int set, uint64_t epoch, HostResult* host,
                    const Tuning& tune, hipStream_t s);
+// A whole restore of at most tune.one_dec_per_cu chunks per compute unit: checks and applies the blob.  host->bytes[0] and
+// max_len[0] are written only if the workgroups met or the header is refused.  met: as launch_encode_one.
+void launch_decode_one(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, uint64_t max_total, Workspace* ws, uint64_t epoch, HostResult* host,
+                       uint64_t (&met)[kMeetLines], uint32_t limit, hipStream_t s);
 // Both apply blobs.p[first .. first+count), count <= kMaxMany, using dec_set[first ..]; the fused
 // kernel requires every code of these blobs to be at most kDecLut1Bits long.
 // pay_words: LDS words each wavefront gets for the payloads of one chunk of all `count` blobs.
