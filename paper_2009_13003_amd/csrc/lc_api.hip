@@ -563,6 +563,53 @@ lc_ssize lc_encode_cached(const float* w, const float* w_ref, uint64_t n, int nb
 }  // extern "C"
 
 namespace {
+// A short vector in one launch, whose workgroups wait for each other's findings before they touch w_ref (see encode_impl for
+// when).  Two kernels / one, us: fp32 2^14 33.9 / 23.5, 2^20 35.4 / 24.9, 2^22 37.8 / 25.8, 2^23 40.4 / 29.0; bf16 2^20 35.2 /
+// 26.2, 2^23 37.2 / 31.7; fp64 2^20 39.8 / 27.8; codes above 10 bits in an array that is off alignment 2^20 89.5 / 35.9; hardly a
+// kept symbol 2^20 26.2 / 23.7, 2^22 24.8 / 23.0, 2^23 25.2 / 26.3.
+// count blobs: beyond a chunk per compute unit a few only, of many the fused sweep is the faster one there (8 blobs of 2^23 113.7 /
+// 130.5 us, 2 55.7 / 47.6).
+bool decode_in_one(const DeviceState* ds, uint64_t n, int count) {
+    const uint64_t nchunks = num_chunks_of(n), cus = (uint64_t)ds->tune.num_cu, per_cu = count <= 4 ? ds->tune.one_dec_per_cu : ds->tune.one_dec_per_cu ? 1 : 0;
+    // (an LC_TUNE_* shape for the fused sweep asks for that sweep)
+    if (count > 1 && ds->tune.fused_min_waves_per_cu != Tuning().fused_min_waves_per_cu) return false;
+    return !g_verify_first && nchunks >= 1 && nchunks <= cus * per_cu && ds->one_blocks + nchunks <= kOneResident * cus;
+}
+constexpr lc_ssize kNotMet = INT64_MIN;
+// The bytes restored or -(status); kNotMet: the workgroups did not meet, and none has touched w_ref.  lock: dropped meanwhile (null: kept).
+lc_ssize run_decode_one(DeviceState* ds, Area* area, const BlobList& list, int count, void* w_ref, uint64_t n, int dtype, uint64_t max_total,
+                        int slot, uint64_t epoch, hipStream_t s, std::unique_lock<std::mutex>* lock) {
+    HostResult& r = g_pinned[slot];
+    r.bytes[0] = UINT64_MAX;                                   // (stays so unless the workgroups met)
+    Workspace* ws = static_cast<Workspace*>(area->mem);
+    if (!area->counted) {                                      // (an earlier call's did not)
+        const Scratch sc(ws, 0, 1);
+        Timed t(kSlotReset, s);
+        launch_reset(ws, sc.group_words, sc.chunk_maxexp, s);
+        area->cleared();
+    }
+    const uint32_t nchunks = (uint32_t)num_chunks_of(n);
+    { Timed t(kSlotDecodeOne, s); launch_decode_one(list, count, w_ref, n, dtype, max_total, ws, epoch, &g_pinned_dev[slot], area->met_dec, (uint32_t)ds->tune.one_wait, s); }
+    LC_HIP(hipGetLastError());
+    if (!release(area, s)) return -LC_ERR_HIP;
+    ds->one_blocks += nchunks;
+    const bool drop = lock && !g_prof;                         // (see encode_impl)
+    if (drop) lock->unlock();
+    const hipError_t waited = hipStreamSynchronize(s);
+    if (drop) lock->lock();
+    ds->one_blocks -= nchunks;
+    if (waited != hipSuccess) { (void)hipGetLastError(); area->counted = false; return -LC_ERR_HIP; }
+    const int slots[] = {kSlotDecodeOne};
+    collect(slots, 1);
+    const bool found = (r.dec_status >> 8) == epoch;
+    if (found || r.bytes[0] == UINT64_MAX) area->counted = false;     // (refused or given up: what stands on the counters goes)
+    if (found) return -(lc_ssize)(r.dec_status & 0xFF);
+    if (r.bytes[0] == UINT64_MAX) return kNotMet;
+    lc_ssize total = 0;
+    for (int i = 0; i < count; ++i) total += (lc_ssize)r.bytes[i];
+    return total;
+}
+
 // blob_bytes: what the caller says its buffer holds (SIZE_MAX: not stated); the header's total may not pass it
 // verify_only: nothing but the blob is read (lc_verify); else the restore, after the same lane-string check if the
 // option asks for it
@@ -587,44 +634,16 @@ lc_ssize decode_impl(const void* blob, size_t blob_bytes, void* w_ref, uint64_t 
     const uint8_t* b = static_cast<const uint8_t*>(blob);
     const uint64_t epoch = ++g_epoch;
     const uint64_t bound = lc_encode_bound(n, 4), max_total = blob_bytes < bound ? blob_bytes : bound;
-    // A short vector in one launch, whose workgroups wait for each other's findings before they touch w_ref (see encode_impl for
-    // when).  Two kernels / one, us: fp32 2^14 33.9 / 23.5, 2^20 35.4 / 24.9, 2^22 37.8 / 25.8, 2^23 40.4 / 29.0; bf16 2^20 35.2 /
-    // 26.2, 2^23 37.2 / 31.7; fp64 2^20 39.8 / 27.8; codes above 10 bits in an array that is off alignment 2^20 89.5 / 35.9; hardly a
-    // kept symbol 2^20 26.2 / 23.7, 2^22 24.8 / 23.0, 2^23 25.2 / 26.3.
-    const uint32_t nchunks = (uint32_t)num_chunks_of(n);
-    if (try_one && !verify_only && !g_verify_first && nchunks >= 1 && nchunks <= (uint32_t)(ds->tune.num_cu * ds->tune.one_dec_per_cu) &&
-        ds->one_blocks + nchunks <= kOneResident * (uint32_t)ds->tune.num_cu) {
-        HostResult& r = g_pinned[slot];
-        r.bytes[0] = UINT64_MAX;                               // (stays so unless the workgroups met)
-        if (!area->counted) {
-            const Scratch sc(ws, 0, 1);
-            Timed t(kSlotReset, s);
-            launch_reset(ws, sc.group_words, sc.chunk_maxexp, s);
-            area->cleared();
-        }
-        { Timed t(kSlotDecodeOne, s); launch_decode_one(b, w_ref, n, dtype, max_total, ws, epoch, host, area->met_dec, (uint32_t)ds->tune.one_wait, s); }
-        LC_HIP(hipGetLastError());
-        if (!release(area, s)) return -LC_ERR_HIP;
-        ds->one_blocks += nchunks;
-        const bool serial = g_prof;
-        if (!serial) lock.unlock();
-        const hipError_t waited = hipStreamSynchronize(s);
-        if (!serial) lock.lock();
-        ds->one_blocks -= nchunks;
-        if (waited != hipSuccess) { (void)hipGetLastError(); area->counted = false; return -LC_ERR_HIP; }
-        const int slots[] = {kSlotDecodeOne};
-        collect(slots, 1);
-        if ((r.dec_status >> 8) == epoch) { if (r.bytes[0] == UINT64_MAX) area->counted = false; return -(lc_ssize)(r.dec_status & 0xFF); }
-        if (r.bytes[0] != UINT64_MAX) return (lc_ssize)r.bytes[0];
-        // they did not meet, and none has touched w_ref: the next call that takes the scratch area clears what they left there
-        area->counted = false;
+    BlobList list;
+    for (int t = 0; t < kMaxSets; ++t) list.p[t] = b;
+    if (try_one && !verify_only && decode_in_one(ds, n, 1)) {
+        const lc_ssize r = run_decode_one(ds, area, list, 1, w_ref, n, dtype, max_total, slot, epoch, s, &lock);
+        if (r != kNotMet) return r;
         free_slot(slot);
         undo.slot = -1;
         lock.unlock();
         return decode_impl(blob, blob_bytes, w_ref, n, dtype, stream, verify_only, false);
     }
-    BlobList list;
-    for (int t = 0; t < kMaxSets; ++t) list.p[t] = b;
     { Timed t(kSlotDecCheck, s); launch_dec_check(list, 0, 1, n, dtype, max_total, ws, epoch, host, s); }
     // (a finding of the verifying sweep gates the restoring one on the device, like a finding of the check)
     if (verify_only || g_verify_first) { Timed t(kSlotVerify, s); launch_decode(b, nullptr, n, dtype, ws, 0, epoch, host, ds->tune, s); }
@@ -697,6 +716,10 @@ lc_ssize lc_decode_many_t(const void* const* blobs, int count, void* w_ref, uint
     const uint64_t epoch = ++g_epoch, bound = lc_encode_bound(n, 4);
     BlobList list;
     for (int t = 0; t < kMaxSets; ++t) list.p[t] = static_cast<const uint8_t*>(blobs[t < count ? t : 0]);
+    if (decode_in_one(ds, n, count)) {
+        const lc_ssize r = run_decode_one(ds, area, list, count, w_ref, n, dtype, bound, slot, epoch, s, nullptr);
+        if (r != kNotMet) return r;
+    }
     // every blob is validated (one launch, one grid row per blob) before w_ref is touched
     { Timed tm(kSlotDecCheck, s); launch_dec_check(list, 0, count, n, dtype, bound, ws, epoch, host, s); }
     if (g_verify_first) {

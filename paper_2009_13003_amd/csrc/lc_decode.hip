@@ -37,11 +37,11 @@ __device__ __forceinline__ void dec_build_luts(DecSet& D, DecBuild& B, u32 K, u3
     const u32 lane = t & (kW - 1);
     const u32 len = lane < kMaxSym ? B.len[lane] : 0u, code = lane < kMaxSym ? B.code[lane] : 0u;
     // (a prefix that starts no code: nothing is ever taken off again, and the lane falls short of its stated length)
-    dec_build_multi<256>(D.multi, B.one, nullptr, (K * 0x111111u) | (kMultiSyms << 28), len, code, K, t);
+    dec_build_multi<256>(D.multi, B.one, nullptr, (K * 0x111111u) | (kMultiSyms << 28), len, code, t);
     const u32 M = wave_max_u32(len), P1 = M < kDecLut1Bits ? M : kDecLut1Bits;
     if (t < (1u << P1)) {
         const u32 f = B.one[t << (kMultiBits - P1)];
-        D.lut1[t] = (f == 0xFF || (f >> 4) > P1) ? (uint8_t)0xFF : (uint8_t)f;
+        D.lut1[t] = f == kOneNone ? (uint8_t)K : (f >> 4) > P1 ? (uint8_t)0xFF : (uint8_t)f;
     }
 }
 

@@ -28,14 +28,18 @@ struct OneDecLds {
     alignas(16) u32 pay[kOnePayWords];
     u32 syms[kR * kV / 8][kW];           // 8 symbols of 4 bits per word: row k of lane l is in [k / 2][l]
     u32 end[kSegs][kW], count[kSegs][kW];
+    u64 total0;
     u32 go, moved[kSegs + 1];            // (the last: some string is wrong)
 };
 
+// Several blobs of one vector (lc_decode_many): one after the other, the running values in registers; w_ref is read and written
+// once, behind the one meeting.  Check, wait and fused sweep against this, us: 8 blobs of 2^20 fp32 elements at 3 bits 111.9 / 100.5,
+// 3 of 2^17 at 4 bits 103 / 53, 12 of 2^19 bf16 at 4 bits 378 / 175, 8 of 2^22 binary64 295 / 122.
 struct OneDecArgs {
-    const uint8_t* blob; void* w_ref; u64 n, max_total;
+    BlobList blobs; void* w_ref; u64 n, max_total;
     Workspace* ws; HostResult* host; u64 epoch;
     u64 goal[kMeetLines];
-    u32 nchunks, lines, limit;
+    u32 count, nchunks, lines, limit;
 };
 
 // This lane's segment from bit `from` of its string to the first code that starts at `to` or behind: where that is, and how many
@@ -89,7 +93,14 @@ __device__ __forceinline__ u32 take_segment(const OneDecLds& L, u32 nwords, u32 
     return pos;
 }
 
-template <int DT>
+// x + the representative, as the parameters' type holds it (16-bit types: rounded after every blob)
+template <int DT> __device__ __forceinline__ typename Val<DT>::type restored(typename Val<DT>::type x, typename Val<DT>::type rep) {
+    if constexpr (DT == kF64) return add_rn(x, rep);
+    else return stored<DT>(add_rn(x, rep));
+}
+
+// MANY: more than one blob.
+template <int DT, bool MANY>
 __global__ __launch_bounds__(kOneDecThreads, 4) void k_decode_one(OneDecArgs a) {
     typedef typename Val<DT>::type val_t;
     __shared__ OneDecLds L;
@@ -98,75 +109,88 @@ __global__ __launch_bounds__(kOneDecThreads, 4) void k_decode_one(OneDecArgs a) 
     GridMeeting meet = {a.ws->meeting(), 0, a.lines, a.limit};
 #pragma unroll
     for (u32 k = 0; k < kMeetLines; ++k) meet.goal = lane == k ? a.goal[k] : meet.goal;
-    if (t < kHeaderBytes / 4) L.hdr[t] = reinterpret_cast<const u32*>(a.blob)[t];
-    for (u32 i = t; i < kR * kV / 8 * kW; i += kOneDecThreads) L.syms[0][i] = 0;
-    __syncthreads();
-    // ---- the header: every workgroup comes to the same findings (as k_dec_check's)
-    const u32* hdr = L.hdr;
-    const u64 hn = hdr[2] | ((u64)hdr[3] << 32), total = hdr[10] | ((u64)hdr[11] << 32), area = chunk_area_of(a.nchunks);
-    const bool sound = hdr[0] == 0x3142434Cu && hdr[1] == (1u | (kHeaderBytes << 16)) && hdr[12] == 0;
-    const bool head_ok = sound && hn == n && hdr[15] == (u32)DT && hdr[9] == a.nchunks && total >= area && total <= a.max_total && ((total - area) & 3) == 0;
-    if (!head_ok) {
-        // (a sound blob for another vector or element type: a bad argument)
-        if (t == 0) {
-            if (c == 0) { raise_status(a.ws, a.host, a.epoch, sound && (hn != n || hdr[15] != (u32)DT) ? 1u : 4u); a.host->bytes[0] = 0; a.host->max_len[0] = 0; }
-            meet.arrive(2);
-        }
-        return;
-    }
-    const u64 tw = (total - area) / 4;
-    const u32 K = hdr[5];
-    // ---- this chunk's record: its place in the offset table, its lane lengths, its payload
-    const u32* off_tab = reinterpret_cast<const u32*>(a.blob + kHeaderBytes);
-    const u64 o0 = load_uniform(off_tab + c), o1 = load_uniform(off_tab + c + 1);
-    bool ok = o0 <= o1 && o1 <= tw && o1 - o0 >= kLaneBitsWords && (c > 0 || o0 == 0) && (c + 1 < a.nchunks || o1 == tw);
-    u32 bits = 0, nwords = 0;
-    if (ok) {
-        typedef u32x4 __attribute__((aligned(4))) u32x4_word;
-        const u32* rec = reinterpret_cast<const u32*>(a.blob + area) + o0;
-        nwords = (u32)min(o1 - o0 - kLaneBitsWords, (u64)kOnePayWords);          // (more than that is refused below)
-        bits = reinterpret_cast<const uint16_t*>(rec)[lane];
-        const u32* from = rec + kLaneBitsWords;
-        for (u32 i = t; i < nwords / 4; i += kOneDecThreads) reinterpret_cast<u32x4*>(L.pay)[i] = reinterpret_cast<const u32x4_word*>(from)[i];
-        if (t < (nwords & 3)) L.pay[nwords / 4 * 4 + t] = from[nwords / 4 * 4 + t];
-    }
-    const u32 incl = wave_incl_scan(bits), sum = read_lane(incl, kW - 1);
-    ok = ok && o1 - o0 == kLaneBitsWords + ((sum + 31) >> 5) && sum > 0 && !__any(bits > kR * kV * 15);
-    // ---- the symbols and their codes (by every wavefront: none waits for another's)
-    DecSymbol sy = {0, 0, 0, 0};
-    const bool table_ok = dec_symbols(hdr, n, a.nchunks, tw, &sy);
-    if (v == 0) {
-        if (lane < kMaxSym) {
-            L.tab.rep[lane] = __uint_as_float(lane < K ? sy.rep : 0x80000000u);
-            L.tab.rep64[lane] = lane < K ? __hiloint2double((int)sy.rep_hi, (int)sy.rep) : -0.0;
-        }
-        if (wave_max_u32(sy.len) > kMultiBits) build_longs(L.tab, sy.len, sy.code);
-        if (t < kSegs + 1) L.moved[t] = 0;
-    }
-    // This wavefront's 8 rows of w_ref, on their way while the strings are decoded; of a chunk of few kept symbols (see kSparseSlack)
-    // only the rows that hold one, and only when that is known (2^23 fp32 elements, sparse: 28.4 us with all of them, 26.0 so).
-    const u32 elems = n - base < kChunk ? (u32)(n - base) : kChunk;
-    const bool sparse = sum <= elems * read_lane(sy.len, K & 15u) + kSparseSlack;
+    // this wavefront's 8 rows of w_ref, and which of them hold a kept symbol
     val_t x[kOneSegRows][kV];
+    u32 keeps = 0;
     auto row = [&](u32 k) { return base + (u64)(v * kOneSegRows + k) * kRowElems; };
     auto fetch = [&](u32 k) {
         if (row(k) + kRowElems <= n) load_row_any<DT>(a.w_ref, row(k) + lane * kV, x[k]);
         else load_row_v<false, DT>(a.w_ref, row(k) + lane * kV, n, x[k]);
     };
-    const bool late = DT == kF64 || sparse;                  // (binary64: their registers would spill meanwhile)
-    if (!late) {
+    if (MANY) {
 #pragma unroll
         for (u32 k = 0; k < kOneSegRows; ++k) fetch(k);
     }
-    const u32 max_len = wave_max_u32(sy.len);
-    ok = ok && table_ok;                                     // (the same in every thread)
-    if (t == 0) {
-        if (!ok) raise_status(a.ws, a.host, a.epoch, 4u);
-        meet.arrive(2, !ok);
-    }
-    bool go = ok;
-    if (ok) {
-        dec_build_multi<kOneDecThreads>(L.tab.multi, L.one, L.ends, kNoCode, sy.len, sy.code, K, t);
+    const u32 elems = n - base < kChunk ? (u32)(n - base) : kChunk, tail = elems % kRowElems;
+    const u32 mine = elems / kRowElems * kV + (tail > lane * kV ? min(tail - lane * kV, kV) : 0u);
+    const u64 area = chunk_area_of(a.nchunks);
+    bool refuse = false;                                     // (the same in every thread)
+#pragma unroll 1
+    for (u32 b = 0; b < (MANY ? a.count : 1u); ++b) {
+        const uint8_t* blob = a.blobs.p[b];
+        const bool last = !MANY || b + 1 == a.count;
+        if (MANY && b) __syncthreads();                      // (everyone is through with the blob before)
+        if (t < kHeaderBytes / 4) L.hdr[t] = reinterpret_cast<const u32*>(blob)[t];
+        for (u32 i = t; i < kR * kV / 8 * kW; i += kOneDecThreads) L.syms[0][i] = 0;
+        if (t < kSegs + 1) L.moved[t] = 0;
+        __syncthreads();
+        // ---- the header: every workgroup comes to the same findings (as k_dec_check's)
+        const u32* hdr = L.hdr;
+        const u64 hn = hdr[2] | ((u64)hdr[3] << 32), total = hdr[10] | ((u64)hdr[11] << 32);
+        const bool sound = hdr[0] == 0x3142434Cu && hdr[1] == (1u | (kHeaderBytes << 16)) && hdr[12] == 0;
+        const bool head_ok = sound && hn == n && hdr[15] == (u32)DT && hdr[9] == a.nchunks && total >= area && total <= a.max_total && ((total - area) & 3) == 0;
+        if (!head_ok) {
+            // (a sound blob for another vector or element type: a bad argument)
+            if (t == 0) {
+                if (c == 0) { raise_status(a.ws, a.host, a.epoch, sound && (hn != n || hdr[15] != (u32)DT) ? 1u : 4u); a.host->bytes[0] = 0; }
+                meet.arrive(2);
+            }
+            return;
+        }
+        const u64 tw = (total - area) / 4;
+        const u32 K = hdr[5];
+        // ---- this chunk's record: its place in the offset table, its lane lengths, its payload
+        const u32* off_tab = reinterpret_cast<const u32*>(blob + kHeaderBytes);
+        const u64 o0 = load_uniform(off_tab + c), o1 = load_uniform(off_tab + c + 1);
+        bool ok = o0 <= o1 && o1 <= tw && o1 - o0 >= kLaneBitsWords && (c > 0 || o0 == 0) && (c + 1 < a.nchunks || o1 == tw);
+        u32 bits = 0, nwords = 0;
+        if (ok) {
+            typedef u32x4 __attribute__((aligned(4))) u32x4_word;
+            const u32* rec = reinterpret_cast<const u32*>(blob + area) + o0;
+            nwords = (u32)min(o1 - o0 - kLaneBitsWords, (u64)kOnePayWords);          // (more than that is refused below)
+            bits = reinterpret_cast<const uint16_t*>(rec)[lane];
+            const u32* from = rec + kLaneBitsWords;
+            for (u32 i = t; i < nwords / 4; i += kOneDecThreads) reinterpret_cast<u32x4*>(L.pay)[i] = reinterpret_cast<const u32x4_word*>(from)[i];
+            if (t < (nwords & 3)) L.pay[nwords / 4 * 4 + t] = from[nwords / 4 * 4 + t];
+        }
+        const u32 incl = wave_incl_scan(bits), sum = read_lane(incl, kW - 1);
+        ok = ok && o1 - o0 == kLaneBitsWords + ((sum + 31) >> 5) && sum > 0 && !__any(bits > kR * kV * 15);
+        // ---- the symbols and their codes (by every wavefront: none waits for another's)
+        DecSymbol sy = {0, 0, 0, 0};
+        ok = dec_symbols(hdr, n, a.nchunks, tw, &sy) && ok;
+        const u32 max_len = wave_max_u32(sy.len);
+        if (v == 0) {
+            if (lane < kMaxSym) {
+                L.tab.rep[lane] = __uint_as_float(lane < K ? sy.rep : 0x80000000u);
+                L.tab.rep64[lane] = lane < K ? __hiloint2double((int)sy.rep_hi, (int)sy.rep) : -0.0;
+            }
+            if (max_len > kMultiBits) build_longs(L.tab, sy.len, sy.code);
+        }
+        // The rows of w_ref are on their way while the strings are decoded; of a chunk of few kept symbols (see kSparseSlack)
+        // only those that hold one, and only when that is known (2^23 fp32 elements, sparse: 28.4 us with all of them, 26.0 so).
+        const bool sparse = sum <= elems * read_lane(sy.len, K & 15u) + kSparseSlack;
+        const bool late = !MANY && (DT == kF64 || sparse);   // (binary64: their registers would spill meanwhile)
+        if (!MANY && !late) {
+#pragma unroll
+            for (u32 k = 0; k < kOneSegRows; ++k) fetch(k);
+        }
+        refuse = refuse || !ok;
+        if (t == 0) {
+            if (!ok) raise_status(a.ws, a.host, a.epoch, 4u);
+            if (last || refuse) meet.arrive(2, refuse);      // (what is found from here on in this workgroup keeps only its own rows back)
+        }
+        if (refuse) return;
+        dec_build_multi<kOneDecThreads>(L.tab.multi, L.one, L.ends, kNoCode, sy.len, sy.code, t);
         __syncthreads();
         // ---- the string of every lane, a segment per wavefront
         const u32 first_bit = incl - bits, cut = bits * v / kSegs, to = bits * (v + 1) / kSegs;
@@ -198,53 +222,76 @@ __global__ __launch_bounds__(kOneDecThreads, 4) void k_decode_one(OneDecArgs a) 
         u32 before = 0, all = 0;
 #pragma unroll
         for (u32 k = 0; k < kSegs; ++k) { const u32 m = L.count[k][lane]; before += k < v ? m : 0u; all += m; }
-        const u32 tail = elems % kRowElems;
-        const u32 mine = elems / kRowElems * kV + (tail > lane * kV ? min(tail - lane * kV, kV) : 0u);
         // a string that does not hold its lane's symbols in exactly its stated length
         const bool wrong = bad || all != mine || (v == kSegs - 1 && end != bits);
         if (__any(wrong) && lane == 0) { L.moved[kSegs] = 1; raise_status(a.ws, a.host, a.epoch, 4u); }
-        const u64 seen = v == 0 ? meet.look(2) : 0ull;       // (on its way meanwhile)
+        const u64 seen = last && v == 0 ? meet.look(2) : 0ull;       // (on its way meanwhile)
         if (long_codes) take_segment<true, true>(L, nwords, first_bit, start, to, &L.syms[0][lane], before, &count, &bad);
         else take_segment<true, false>(L, nwords, first_bit, start, to, &L.syms[0][lane], before, &count, &bad);
-        if (v == 0) { const bool met = meet.wait(2, seen); if (lane == 0) L.go = met ? 1u : 0u; }
+        if (last && v == 0) { const bool met = meet.wait(2, seen); if (lane == 0) L.go = met ? 1u : 0u; }
         __syncthreads();
-        go = L.go != 0 && L.moved[kSegs] == 0;
-    }
-    if (!go) return;
-    if (c == 0 && t == 0) { a.host->bytes[0] = total; a.host->max_len[0] = max_len; }
-    // ---- Algorithm 1 line 7; a row without a kept symbol stays as it is
-    u32 syms[kOneSegRows];
-    u32 keeps = 0;
+        if (L.moved[kSegs] != 0) {
+            if (!last && t == 0) meet.arrive(2, true);
+            return;
+        }
+        if (last && !L.go) return;
+        if (c == 0 && t == 0) { a.host->max_len[b] = max_len; if (last || b) a.host->bytes[b] = total; }
+        if (MANY && c == 0 && t == 0 && b == 0) L.total0 = total;        // (bytes[0] says that the workgroups met)
+        // ---- Algorithm 1 line 7; a row without a kept symbol stays as it is
+        u32 syms[kOneSegRows], here = 0;
 #pragma unroll
-    for (u32 k = 0; k < kOneSegRows; ++k) {
-        syms[k] = (L.syms[(v * kOneSegRows + k) / 2][lane] >> (16 * (k & 1))) & 0xFFFFu;
-        // (places behind the vector's end hold symbol 0: they are masked where they count)
-        keeps |= __any(syms[k] != K * 0x1111u) ? 1u << k : 0u;
-    }
-    if (late) {
+        for (u32 k = 0; k < kOneSegRows; ++k) {
+            syms[k] = (L.syms[(v * kOneSegRows + k) / 2][lane] >> (16 * (k & 1))) & 0xFFFFu;
+            // (places behind the vector's end hold symbol 0: they are masked where they are stored)
+            here |= __any(syms[k] != K * 0x1111u) ? 1u << k : 0u;
+        }
+        keeps |= here;
+        if (late) {
 #pragma unroll
-        for (u32 k = 0; k < kOneSegRows; ++k) if ((keeps >> k) & 1u) fetch(k);
+            for (u32 k = 0; k < kOneSegRows; ++k) if ((here >> k) & 1u) fetch(k);
+        }
+#pragma unroll
+        for (u32 k = 0; k < kOneSegRows; ++k) {
+            if (((here >> k) & 1u) == 0) continue;
+            if constexpr (MANY) {
+#pragma unroll
+                for (u32 e = 0; e < kV; ++e) {
+                    const u32 one = (syms[k] >> (4 * e)) & 15u;
+                    x[k][e] = one != K ? restored<DT>(x[k][e], L.tab.template rep_of<DT>(one)) : x[k][e];
+                }
+            } else {
+#pragma unroll
+                for (u32 e = 0; e < kV; ++e) x[k][e] = add_rn(x[k][e], L.tab.template rep_of<DT>((syms[k] >> (4 * e)) & 15u));
+                if (row(k) + kRowElems <= n) store4_any<DT>(a.w_ref, row(k) + lane * kV, x[k]);
+                else {
+#pragma unroll
+                    for (u32 e = 0; e < kV; ++e)
+                        if (row(k) + lane * kV + e < n && ((syms[k] >> (4 * e)) & 15u) != K) store_one_v<DT>(a.w_ref, row(k) + lane * kV + e, x[k][e]);
+                }
+            }
+        }
     }
+    if (!MANY) return;
+    if (c == 0 && t == 0) a.host->bytes[0] = L.total0;
 #pragma unroll
     for (u32 k = 0; k < kOneSegRows; ++k) {
         if (((keeps >> k) & 1u) == 0) continue;
-#pragma unroll
-        for (u32 e = 0; e < kV; ++e) x[k][e] = add_rn(x[k][e], L.tab.template rep_of<DT>((syms[k] >> (4 * e)) & 15u));
         if (row(k) + kRowElems <= n) store4_any<DT>(a.w_ref, row(k) + lane * kV, x[k]);
         else {
 #pragma unroll
             for (u32 e = 0; e < kV; ++e)
-                if (row(k) + lane * kV + e < n && ((syms[k] >> (4 * e)) & 15u) != K) store_one_v<DT>(a.w_ref, row(k) + lane * kV + e, x[k][e]);
+                if (row(k) + lane * kV + e < n) store_one_v<DT>(a.w_ref, row(k) + lane * kV + e, x[k][e]);
         }
     }
 }
 
-void launch_decode_one(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, uint64_t max_total, Workspace* ws, uint64_t epoch, HostResult* host,
-                       uint64_t (&met)[kMeetLines], uint32_t limit, hipStream_t s) {
+void launch_decode_one(const BlobList& blobs, int count, void* w_ref, uint64_t n, int dtype, uint64_t max_total, Workspace* ws, uint64_t epoch,
+                       HostResult* host, uint64_t (&met)[kMeetLines], uint32_t limit, hipStream_t s) {
     const u32 nchunks = (u32)num_chunks_of(n), lines = nchunks <= kMeetOneLine ? 1 : kMeetLines;
-    OneDecArgs a = {blob, w_ref, (u64)n, (u64)max_total, ws, host, (u64)epoch, {}, nchunks, lines, limit};
+    OneDecArgs a = {blobs, w_ref, (u64)n, (u64)max_total, ws, host, (u64)epoch, {}, (u32)count, nchunks, lines, limit};
     for (u32 k = 0; k < lines; ++k) a.goal[k] = met[k] += (nchunks + lines - 1 - k) / lines;
-#define LC_ONE(DT) hipLaunchKernelGGL(k_decode_one<DT>, dim3(nchunks), dim3(kOneDecThreads), 0, s, a)
+#define LC_ONE(DT) do { if (count > 1) hipLaunchKernelGGL((k_decode_one<DT, true>), dim3(nchunks), dim3(kOneDecThreads), 0, s, a); \
+                        else hipLaunchKernelGGL((k_decode_one<DT, false>), dim3(nchunks), dim3(kOneDecThreads), 0, s, a); } while (0)
     if (dtype == kF64) LC_ONE(kF64);
     else if (dtype == kBF16) LC_ONE(kBF16);
     else if (dtype == kF16) LC_ONE(kF16);

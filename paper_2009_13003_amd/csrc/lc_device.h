@@ -334,12 +334,13 @@ __device__ __forceinline__ bool dec_symbols(const u32* hdr, u64 n, u32 nchunks, 
 }
 
 // The sweeps' tables, by a workgroup of THREADS threads.  One symbol per look-up over the next 10 bits in `one`: symbol | len << 4;
-// a prefix that starts no code: symbol K with length 0; a prefix of a code longer than 10 bits: 0xFF.  From it every entry of
+// a prefix that starts no code: kOneNone; a prefix of a code longer than 10 bits: 0xFF.  From it every entry of
 // the table of several symbols is then put together by taking codes off the front of its 10 bits, a thread's entries
 // side by side (none: the entry of a prefix that starts no code).  ends (or null): bit b of an entry: one of its codes ends with
 // bit b.  len, code: of symbol (lane) in every wavefront.  (Every dependent step here is latency of the call.)  Contains a barrier.
+constexpr u32 kOneNone = 0xF0;
 template <u32 THREADS>
-__device__ __forceinline__ void dec_build_multi(u32* multi, uint8_t* one, uint16_t* ends, u32 none, u32 len, u32 code, u32 K, u32 t) {
+__device__ __forceinline__ void dec_build_multi(u32* multi, uint8_t* one, uint16_t* ends, u32 none, u32 len, u32 code, u32 t) {
     constexpr u32 kEach = (1u << kMultiBits) / THREADS;
     // A code, left-justified, is the largest of those not above a window that starts with it.
     const u32 key = len ? (code << (15 - len)) << 8 | len << 4 | (lane_id() & 15u) : 0xFFFFFFFFu;
@@ -359,37 +360,32 @@ __device__ __forceinline__ void dec_build_multi(u32* multi, uint8_t* one, uint16
     for (u32 k = 0; k < kEach; ++k) {
         const u32 at = (t + THREADS * k) << (15 - kMultiBits), L = (e[k] >> 4) & 15u;
         const bool starts = L != 0 && at < (e[k] >> 8) + (0x8000u >> L);
-        e[k] = L > kMultiBits ? 0xFFu : starts ? e[k] & 0xFFu : K;
-        // (some window of this prefix starts a longer code if the next one up does: the code is then complete)
+        e[k] = L > kMultiBits ? 0xFFu : starts ? e[k] & 0xFFu : kOneNone;
         one[t + THREADS * k] = (uint8_t)e[k];
     }
     __syncthreads();
+    // (a prefix that gives no code, and a code longer than what is left, stop an entry for good: the same look-up again)
     u32 rest[kEach], left[kEach], syms[kEach], cnt[kEach], end[kEach];
-    bool on[kEach];
 #pragma unroll
-    for (u32 k = 0; k < kEach; ++k) {
-        // (the first code of the entry is the one just found)
-        const u32 L = e[k] >> 4, i = t + THREADS * k;
-        on[k] = e[k] != 0xFF && L != 0;
-        syms[k] = on[k] ? e[k] & 15u : 0u; cnt[k] = on[k] ? 1u : 0u; end[k] = on[k] ? 1u << L : 0u;
-        rest[k] = on[k] && L < kMultiBits ? i << (32 - kMultiBits + L) : 0u; left[k] = on[k] ? kMultiBits - L : kMultiBits;
-    }
-#pragma unroll 1
-    for (u32 s = 1; s < kMultiSyms; ++s) {
+    for (u32 k = 0; k < kEach; ++k) { rest[k] = (t + THREADS * k) << (32 - kMultiBits); left[k] = kMultiBits; syms[k] = 0; cnt[k] = 0; end[k] = 0; }
+#pragma unroll
+    for (u32 s = 0; s < kMultiSyms; ++s) {
         u32 f[kEach];
 #pragma unroll
-        for (u32 k = 0; k < kEach; ++k) f[k] = one[rest[k] >> (32 - kMultiBits)];
+        for (u32 k = 0; k < kEach; ++k) f[k] = s == 0 ? e[k] : one[rest[k] >> (32 - kMultiBits)];
 #pragma unroll
         for (u32 k = 0; k < kEach; ++k) {
-            const u32 L = f[k] >> 4;
-            on[k] = on[k] && f[k] != 0xFF && L != 0 && L <= left[k];
-            if (on[k]) { syms[k] |= (f[k] & 15u) << (4 * s); ++cnt[k]; rest[k] <<= L; left[k] -= L; end[k] |= 1u << (kMultiBits - left[k]); }
+            const u32 L = f[k] >> 4 <= left[k] ? f[k] >> 4 : 0u;
+            syms[k] |= L ? (f[k] & 15u) << (4 * s) : 0u;
+            cnt[k] += L ? 1u : 0u;
+            rest[k] <<= L; left[k] -= L;
+            end[k] |= 1u << (kMultiBits - left[k]);
         }
     }
 #pragma unroll
     for (u32 k = 0; k < kEach; ++k) {
         const u32 i = t + THREADS * k;
-        multi[i] = e[k] != 0xFF && (e[k] >> 4) == 0 ? none : syms[k] | ((kMultiBits - left[k]) << 24) | (cnt[k] << 28);
+        multi[i] = e[k] == kOneNone ? none : syms[k] | ((kMultiBits - left[k]) << 24) | (cnt[k] << 28);
         if (ends) ends[i] = (uint16_t)end[k];
     }
 }

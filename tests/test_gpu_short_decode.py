@@ -93,10 +93,9 @@ def test_largest(lc, chunks):
     for dtype in (torch.float32, torch.float64):
         print("largest", chunks, dtype, flush=True)
         blob, start = case(lc, "deep", chunks * CHUNK, 0, dtype, 3)
-        rec, many = start.clone(), start.clone()
+        rec = start.clone()
         lc.lc_decode_t(blob, rec)
-        lc.lc_decode_many_t([blob], many)                    # (not this path)
-        assert torch.equal(rec.view(torch.uint8), many.view(torch.uint8))
+        assert torch.equal(rec.view(torch.uint8), torch.from_numpy(restored(blob.cpu().numpy(), start)).to(DEV))
 
 
 @pytest.mark.parametrize("kind", ["one length", "deep", "one symbol"])
@@ -130,6 +129,36 @@ def test_damaged_blobs(lc, kind):
     rec = start.clone()                                      # and nothing of it stays behind
     lc.lc_decode(blob, rec)
     assert np.array_equal(host(rec).view(np.uint8), restored(h, start))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16, torch.float64])
+@pytest.mark.parametrize("n,offset,kinds", [(7, 0, ["deep", "one bit"]), (CHUNK + 900, 1, ["deep", "uneven", "one symbol"]), (5 * CHUNK, 0, ["one length"] * 3),
+                                            (21 * CHUNK - 2, 0, ["deep", "one symbol", "one bit", "uneven", "deep", "one length", "deep", "uneven", "deep"])])
+def test_several_blobs(lc, dtype, n, offset, kinds):
+    """lc_decode_many in one launch: as one restore after the other (16-bit values rounded after every blob)."""
+    print("several", dtype, n, offset, len(kinds), flush=True)
+    blobs, start = [], None
+    for k, kind in enumerate(kinds):
+        blob, start = case(lc, kind, n, offset, dtype, 4 - k % 2, seed=k)
+        blobs.append(blob)
+    rec = start.clone()
+    assert lc.lc_decode_many_t(blobs, rec[offset:]) == sum(b.numel() for b in blobs)
+    want = start.clone()
+    for blob in blobs:
+        h = restored(blob.cpu().numpy(), want[offset:])
+        want[offset:].view(torch.uint8).copy_(torch.from_numpy(h))
+    assert torch.equal(rec.view(torch.uint8), want.view(torch.uint8))
+    for at in sorted({0, len(blobs) // 2, len(blobs) - 1}):  # one of them damaged: nothing is touched
+        for byte, bit, status in ((8, 1, lc.ERR_BADARG), (67, 0, lc.ERR_BAD_BLOB), (512, 4, lc.ERR_BAD_BLOB)):
+            bad = [b.clone() for b in blobs]
+            bad[at][byte] ^= 1 << bit
+            rec = start.clone()
+            with pytest.raises(lc.LcError) as e:
+                lc.lc_decode_many_t(bad, rec[offset:])
+            assert e.value.status == status and torch.equal(rec.view(torch.uint8), start.view(torch.uint8)), (at, byte)
+    rec = start.clone()
+    lc.lc_decode_many_t(blobs, rec[offset:])
+    assert torch.equal(rec.view(torch.uint8), want.view(torch.uint8))
 
 
 def test_many_threads(lc):
@@ -173,6 +202,10 @@ for k in range(60):
         rec = start.clone()
         assert lc.lc_decode(blob, rec) == blob.numel()
         assert np.array_equal(host(rec).view(np.uint8), restored(blob.cpu().numpy(), start)), (k, turn)
+        many = start.clone()
+        lc.lc_decode_many_t([blob, blob], many)
+        lc.lc_decode(blob, rec)
+        assert torch.equal(rec, many), (k, turn)
 print('same')
 """ % ROOT
     env = dict(os.environ, LC_TUNE_ONE_WAIT=looks)
