@@ -32,6 +32,8 @@ struct OneDecLds {
     u32 go, moved[kSegs + 1];            // (the last: some string is wrong)
 };
 
+static_assert(2 * (sizeof(OneDecLds) + 1280) <= kLdsPerCu, "two workgroups per compute unit: the host counts on that many being resident");
+
 // Several blobs of one vector (lc_decode_many): one after the other, the running values in registers; w_ref is read and written
 // once, behind the one meeting.  Check, wait and fused sweep against this, us: 8 blobs of 2^20 fp32 elements at 3 bits 111.9 / 100.5,
 // 3 of 2^17 at 4 bits 103 / 53, 12 of 2^19 bf16 at 4 bits 378 / 175, 8 of 2^22 binary64 295 / 122.

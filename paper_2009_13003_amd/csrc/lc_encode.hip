@@ -2044,6 +2044,7 @@ __global__ __launch_bounds__(kWgThreads, 4) void k_encode_one(OneArgs a) {
     __shared__ u32 s_before[kWgWaves], s_all[kWgWaves];
     // the counts and extremes lie where the coding's tables and areas go later
     static_assert(sizeof(PackWg) >= 4 * 512 * kOneCopies && alignof(PackWg) >= 16, "room for the counts");
+    static_assert(2 * (sizeof(PackWg) + sizeof(TableLds<8>) + 2560) <= kLdsPerCu, "two workgroups per compute unit: the host counts on that many being resident");
     u32* const area = reinterpret_cast<u32*>(&L);
     Workspace* ws = a.ws;
     const u64 n = a.n;
