@@ -29,12 +29,16 @@ struct Area {
     hipStream_t stream = nullptr; // the stream of the last call that used it
     bool used = false;
     hipEvent_t idle = nullptr;    // recorded behind the last call that used it
-    bool clean = false;           // its encode state is known to be cleared
+    bool clean = false;           // its encode state is known to be cleared, but for what counted and open say
     uint64_t stamp = 0;           // when it was last taken
     // what its counters of k_encode_one (both meetings) and of k_decode_one stand at, as long as that is known
     uint64_t met[kMeetLines] = {}, met_dec[kMeetLines] = {};
     bool counted = false;
-    void cleared() { clean = true; counted = true; memset(met, 0, sizeof(met)); memset(met_dec, 0, sizeof(met_dec)); }
+    // Encodes in one launch whose outcome the host does not know yet.  One that is given up leaves its counts, and perhaps its
+    // extremes, behind, and the thread that waits for it may be the last to learn of that: while there are any, an encode that
+    // takes the area clears them first, on its own stream (which is ordered behind theirs).
+    uint32_t open = 0;
+    void counters_cleared() { counted = true; memset(met, 0, sizeof(met)); memset(met_dec, 0, sizeof(met_dec)); }
 };
 
 struct DeviceState {
@@ -185,7 +189,7 @@ Area* acquire(DeviceState* ds, hipStream_t s, size_t need, int* err) {
         if (hipStreamWaitEvent(s, a->idle, 0) != hipSuccess) { (void)hipGetLastError(); *err = LC_ERR_HIP; return nullptr; }
     }
     if (ds->user) {
-        if (a->mem != ds->user) { a->mem = ds->user; a->bytes = ds->user_bytes; a->user = true; a->cleared(); a->clean = false; a->used = false; }
+        if (a->mem != ds->user) { a->mem = ds->user; a->bytes = ds->user_bytes; a->user = true; a->counters_cleared(); a->clean = false; a->used = false; }
     } else if (a->bytes < need) {
         if (a->mem) {
             if (a->used) (void)hipEventSynchronize(a->idle);         // its last call must be through with the old memory
@@ -198,7 +202,7 @@ Area* acquire(DeviceState* ds, hipStream_t s, size_t need, int* err) {
         // has been seen to land behind the reset kernel that follows, which left the smallest mantissas at zero)
         if (hipMemsetAsync(a->mem, 0, kWorkspaceHead, s) != hipSuccess) { (void)hipGetLastError(); (void)hipFree(a->mem); a->mem = nullptr; *err = LC_ERR_HIP; return nullptr; }
         a->bytes = want; a->user = false; a->used = false;
-        a->cleared();
+        a->counters_cleared();
         a->clean = false;        // new memory (possibly at the old address): all zero, its encode state is not set up yet
     }
     a->stream = s; a->stamp = ++ds->clock;
@@ -375,8 +379,10 @@ lc_ssize encode_impl(const void* w, const void* w_ref, uint64_t n, int nbits, vo
     struct Undo { int slot; bool armed; ~Undo() { if (armed) free_slot(slot); } } undo{slot, true};   // (the lock is still held on every early return)
     Result* result = &g_pinned_dev[slot].enc;
     // Every call leaves the encode state cleared behind it; a fresh scratch area, or one whose last
-    // call did not run to its end, is cleared first.
-    if (!area->clean || !area->counted) { Timed t(kSlotReset, s); launch_reset(ws, group_words, chunk_maxexp, s); area->cleared(); }
+    // call did not run to its end, is cleared first.  A call in one launch that was given up, or may have been, has
+    // touched no more than launch_reset_one clears.
+    if (!area->clean) { Timed t(kSlotReset, s); launch_reset(ws, group_words, chunk_maxexp, s); area->counters_cleared(); }
+    else if (!area->counted || area->open) { Timed t(kSlotReset, s); launch_reset_one(ws, s); area->counters_cleared(); }
     area->clean = false;
     // A short vector that the caller waits for: one launch, whose workgroups wait for each other (k_encode_one).  They fit the
     // chip together as long as all such calls in progress have at most kOneResident workgroups per compute unit; a call beyond that, and one whose workgroups did not meet in time
@@ -392,13 +398,15 @@ lc_ssize encode_impl(const void* w, const void* w_ref, uint64_t n, int nbits, vo
         LC_HIP(hipGetLastError());
         if (!release(area, s)) return -LC_ERR_HIP;
         area->clean = true;
+        ++area->open;
         ds->one_blocks += nchunks;
         const bool serial = g_prof;
         if (!serial) lock.unlock();
         const hipError_t waited = hipStreamSynchronize(s);
         if (!serial) lock.lock();
         ds->one_blocks -= nchunks;
-        if (waited != hipSuccess) { (void)hipGetLastError(); area->counted = false; return -LC_ERR_HIP; }
+        if (area->open) --area->open;                          // (lc_shutdown meanwhile: the areas are new)
+        if (waited != hipSuccess) { (void)hipGetLastError(); area->clean = false; return -LC_ERR_HIP; }
         if (r.status == LC_ERR_HIP) {
             // they did not meet: what they left in the scratch area is cleared by the next call that takes it
             area->counted = false;
@@ -582,16 +590,13 @@ lc_ssize run_decode_one(DeviceState* ds, Area* area, const BlobList& list, int c
     HostResult& r = g_pinned[slot];
     r.bytes[0] = UINT64_MAX;                                   // (stays so unless the workgroups met)
     Workspace* ws = static_cast<Workspace*>(area->mem);
-    if (!area->counted) {                                      // (an earlier call's did not)
-        const Scratch sc(ws, 0, 1);
-        Timed t(kSlotReset, s);
-        launch_reset(ws, sc.group_words, sc.chunk_maxexp, s);
-        area->cleared();
-    }
+    // An earlier call's did not meet, or refused.  (Where that is not known yet, the marks it may have left are seen, or, by a
+    // call that looks at fewer counters, not seen: every workgroup of a restore arrives once whatever happens, so the
+    // counters stand where the host believes them to.)
+    if (!area->counted) { Timed t(kSlotReset, s); launch_reset_one(ws, s); area->counters_cleared(); }
     const uint32_t nchunks = (uint32_t)num_chunks_of(n);
     { Timed t(kSlotDecodeOne, s); launch_decode_one(list, count, w_ref, n, dtype, max_total, ws, epoch, &g_pinned_dev[slot], area->met_dec, (uint32_t)ds->tune.one_wait, s); }
-    LC_HIP(hipGetLastError());
-    if (!release(area, s)) return -LC_ERR_HIP;
+    if (hipGetLastError() != hipSuccess || !release(area, s)) { area->counted = false; return -LC_ERR_HIP; }
     ds->one_blocks += nchunks;
     const bool drop = lock && !g_prof;                         // (see encode_impl)
     if (drop) lock->unlock();

@@ -56,6 +56,13 @@ __global__ void k_reset_chunks(Workspace* ws, u32* group_words, u32 ngroups, u32
     for (u32 c = threadIdx.x; c < nchunks; c += blockDim.x) chunk_maxexp[maxexp_slot(c)] = 0;
 }
 
+// What a call in one launch (k_encode_one, k_decode_one) leaves behind that was given up or refused.
+__global__ void k_reset_one(Workspace* ws) {
+    for (u32 i = threadIdx.x; i < 512; i += blockDim.x) ws->hist[i] = 0;       // (where the workgroups meet)
+    clear_ext64(&ws->ext64, threadIdx.x, blockDim.x);
+    clear_extremes(ws, threadIdx.x, blockDim.x);
+}
+
 // ----------------------------------------------------------------------------- k_hist
 // Sweep 1 (Section 3.1.1, exponent-based quantization): population of each of the 2^9
 // (sign, exponent) buckets.  LDS histogram replicated 8 times (copy = lane & 7, copies
@@ -2389,6 +2396,8 @@ __global__ __launch_bounds__(256) void kb_place(BatchArgs a) {
 void launch_reset(Workspace* ws, uint32_t* group_words, uint32_t* chunk_maxexp, hipStream_t s) {
     hipLaunchKernelGGL(k_reset, dim3(1), dim3(1024), 0, s, ws, group_words, (u32)kMaxGroups, chunk_maxexp, (u32)kMaxChunks);
 }
+
+void launch_reset_one(Workspace* ws, hipStream_t s) { hipLaunchKernelGGL(k_reset_one, dim3(1), dim3(1024), 0, s, ws); }
 
 void launch_reset_chunks(Workspace* ws, uint32_t* group_words, uint32_t* chunk_maxexp, uint32_t nchunks, hipStream_t s) {
     hipLaunchKernelGGL(k_reset_chunks, dim3(1), dim3(1024), 0, s, ws, group_words, (nchunks + 63) / 64, chunk_maxexp, nchunks);

@@ -173,6 +173,9 @@ struct Tuning {
 
 // Launchers (lc_encode.hip, lc_decode.hip).
 void launch_reset(Workspace* ws, uint32_t* group_words, uint32_t* chunk_maxexp, hipStream_t s);
+// The same for what a call in one launch (k_encode_one, k_decode_one) that did not end well leaves behind: the counters of the
+// meetings, counts and extremes.
+void launch_reset_one(Workspace* ws, hipStream_t s);
 void launch_reset_chunks(Workspace* ws, uint32_t* group_words, uint32_t* chunk_maxexp, uint32_t nchunks, hipStream_t s);
 // The keys of an encode with staged keys (fp32, 16-byte aligned arrays): sweep 1 leaves, for every whole batch of 4 rows
 // (1024 elements) and lane, the 16 exponent bytes of the lane's elements (row-major: byte 4 k + v = row k, element v) and

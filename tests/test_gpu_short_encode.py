@@ -1,7 +1,7 @@
 """Encodes of short vectors, which run in one launch whose workgroups meet twice, against the same call in four kernels (the
 asynchronous one) and the oracle, byte for byte: whole, ragged and single chunks, unaligned arrays, every element type that
 takes this path, chunks of long codes, deltas that are not finite, cached tables, the largest size and the first one beyond it,
-calls of many threads at once, and workgroups that give up meeting."""
+calls of many threads at once, and workgroups that give up meeting, also while other threads' calls take the same scratch area."""
 import os
 import subprocess
 import sys
@@ -164,6 +164,7 @@ import sys, torch, numpy as np
 sys.path.insert(0, %r)
 from tests.test_gpu_short_encode import pair, four_kernels, CHUNK, DEV
 from paper_2009_13003_amd import lc
+lc.lc_profile(True)
 for k in range(60):
     n = (k * 37 %% 250 + 1) * CHUNK + k
     w, r = pair(n, torch.float32, 0, k)
@@ -175,8 +176,65 @@ for k in range(60):
         size, used = lc.lc_encode_cached_t(w, r, 3, out, cache)
         want, used4 = four_kernels(lc, w, r, 3, lc.alloc_out(n, 3, DEV), cache4)
         assert used == used4 == bool(turn) and np.array_equal(out[:size].cpu().numpy(), want) and torch.equal(cache, cache4), (k, turn)
+p = lc.lc_profile_read()
+given_up = p['k_hist'][1] + p['k_spec_sweep'][1]            # (waited for: the asynchronous calls are not timed)
+assert given_up > 5 and given_up + p['k_encode_one'][1] == 180, p
 print('same')
 """ % ROOT
     env = dict(os.environ, LC_TUNE_ONE_WAIT=looks)
     res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, env=env, cwd=ROOT, timeout=100)
+    assert res.returncode == 0 and "same" in res.stdout, res.stdout[-2000:] + res.stderr[-2000:]
+
+
+CROSSED = """
+import sys, threading, torch, numpy as np
+sys.path.insert(0, %r)
+from tests.test_gpu_short_encode import pair, four_kernels, oracle_blob, CHUNK, DEV
+from paper_2009_13003_amd import lc
+which = sys.argv[1]
+jobs = []
+for k, (chunks, how) in enumerate([(40, 'wait'), (600, 'wait'), (3, 'wait'), (200, 'wait'), (700, 'async'), (12, 'wait'), (90, 'async'), (256, 'wait'), (530, 'cached'), (17, 'wait')]):
+    w, r = pair(chunks * CHUNK + 11 * k, torch.float32, 0, k)
+    w = r + (w - r) * 2.0 ** (3 * k - 12)                    # other buckets in every job
+    want, _ = four_kernels(lc, w, r, 3, lc.alloc_out(w.numel(), 3, DEV))
+    if chunks < 100:
+        assert np.array_equal(want, oracle_blob(w, r, 3))
+    jobs.append((w, r, how, torch.from_numpy(want).to(DEV)))
+torch.cuda.synchronize()
+streams = [torch.cuda.Stream() for _ in range({'one stream': 1, 'own streams': len(jobs), 'one area': 3}[which])]
+if which == 'one area':
+    size = lc.lc_workspace_bytes(701 * CHUNK, 3)
+    area = torch.empty((size + 255) // 256 * 256, dtype=torch.uint8, device=DEV)
+    lc.lc_set_workspace(area)
+wrong = []
+
+def work(i):
+    w, r, how, want = jobs[i]
+    out, spare = lc.alloc_out(w.numel(), 3, DEV), lc.alloc_out(w.numel(), 3, DEV)
+    with torch.cuda.stream(streams[i %% len(streams)]):
+        for turn in range(25):
+            out.zero_()
+            if how == 'wait':
+                size = lc.lc_encode(w, r, 3, out)
+            elif how == 'async':
+                size, _ = lc.lc_encode_wait(lc.lc_encode_async_t(w, r, 3, out))
+            else:
+                size, _ = lc.lc_encode_cached_t(w, r, 3, out, lc.new_cache(DEV))
+            if size != want.numel() or not torch.equal(out[:size], want):
+                wrong.append((i, turn))
+
+threads = [threading.Thread(target=work, args=(i,)) for i in range(len(jobs))]
+[t.start() for t in threads]
+[t.join() for t in threads]
+assert not wrong, wrong
+print('same')
+"""
+
+
+@pytest.mark.parametrize("which", ["one stream", "own streams", "one area"])
+def test_calls_that_give_up_beside_other_threads_calls(which):
+    """A call that is given up leaves counts behind in its scratch area; other threads' calls, long, asynchronous and cached ones, take the
+    area before its own thread knows: on one stream, on more streams than there are areas, and in a caller's one area."""
+    env = dict(os.environ, LC_TUNE_ONE_WAIT="0")
+    res = subprocess.run([sys.executable, "-c", CROSSED % ROOT, which], capture_output=True, text=True, env=env, cwd=ROOT, timeout=100)
     assert res.returncode == 0 and "same" in res.stdout, res.stdout[-2000:] + res.stderr[-2000:]

@@ -1,0 +1,190 @@
+"""The host side of the library (lc_api.hip) built for the CPU, with a stand-in for the HIP runtime and for the kernels' launchers
+that notes what is launched: the order of launches where calls in one launch are given up, and what another thread's call does that
+takes the same scratch area before the first one's outcome is known (made to come in while the first thread waits, the lock
+dropped)."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_2009_13003_amd", "csrc")
+
+HIP = r"""
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+#include <stdlib.h>
+#include <string.h>
+#define __device__
+#define __host__
+#define __align__(x)
+typedef int hipError_t;
+typedef void* hipStream_t;
+typedef struct FakeEvent { hipStream_t s; }* hipEvent_t;
+enum { hipSuccess = 0, hipErrorUnknown = 999 };
+enum { hipDeviceAttributeMultiprocessorCount, hipHostMallocMapped = 1, hipHostMallocPortable = 2, hipEventDisableTiming = 2 };
+hipError_t hipStreamSynchronize(hipStream_t s);
+hipError_t hipGetLastError();
+static inline hipError_t hipGetDevice(int* d) { *d = 0; return 0; }
+static inline hipError_t hipSetDevice(int) { return 0; }
+static inline hipError_t hipDeviceGetAttribute(int* v, int, int) { *v = 256; return 0; }
+static inline hipError_t hipDeviceSynchronize() { return 0; }
+static inline hipError_t hipMalloc(void** p, size_t n) { *p = aligned_alloc(256, (n + 255) / 256 * 256); return *p ? 0 : 1; }
+static inline hipError_t hipFree(void* p) { free(p); return 0; }
+static inline hipError_t hipHostMalloc(void** p, size_t n, int) { *p = calloc(1, n); return 0; }
+static inline hipError_t hipHostFree(void* p) { free(p); return 0; }
+static inline hipError_t hipHostGetDevicePointer(void** p, void* h, int) { *p = h; return 0; }
+static inline hipError_t hipMemset(void* p, int v, size_t n) { memset(p, v, n); return 0; }
+static inline hipError_t hipMemsetAsync(void* p, int v, size_t n, hipStream_t) { memset(p, v, n); return 0; }
+static inline hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)calloc(1, sizeof(FakeEvent)); return 0; }
+static inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, int) { return hipEventCreate(e); }
+static inline hipError_t hipEventDestroy(hipEvent_t e) { free(e); return 0; }
+static inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { e->s = s; return 0; }
+static inline hipError_t hipEventQuery(hipEvent_t) { return 0; }            // every stream is through with its work at once
+static inline hipError_t hipEventSynchronize(hipEvent_t) { return 0; }
+static inline hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 0; return 0; }
+static inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t) { return 0; }
+static inline hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, int) { return 0; }
+#define HIP_SYMBOL(x) (x)
+static inline hipError_t hipGetSymbolAddress(void** p, void* x) { *p = x; return 0; }
+"""
+
+MAIN = r"""
+#include "lc_api.hip"
+#include <functional>
+#include <stdio.h>
+#include <string>
+
+// ---- what is launched: a letter each, and what the stand-ins leave for the host
+//   0 k_reset   r k_reset_one   E / D one launch   h first sweep   t table   s single sweep   p second sweep   P placement
+//   c check     v verify        d restore          f fused restore
+static std::string launched;
+static bool meet = true;                 // whether the workgroups of a call in one launch meet
+static int fail_launches = 0;            // the next launches that fail
+static std::function<void()> waiting;    // runs (once) in a thread that waits for its stream
+hipError_t hipGetLastError() { if (fail_launches > 0) { --fail_launches; return hipErrorUnknown; } return 0; }
+hipError_t hipStreamSynchronize(hipStream_t) { if (waiting) { auto f = waiting; waiting = nullptr; f(); } return 0; }
+
+namespace lc {
+static void done(Result* r) { r->bytes = 1000; r->status = 0; r->used_cache = 0; r->listed = 0; }
+void launch_reset(Workspace*, uint32_t*, uint32_t*, hipStream_t) { launched += '0'; }
+void launch_reset_chunks(Workspace*, uint32_t*, uint32_t*, uint32_t, hipStream_t) {}
+void launch_reset_one(Workspace*, hipStream_t) { launched += 'r'; }
+void launch_hist(const void*, const void*, uint64_t, int, Workspace*, uint32_t*, uint8_t*, KeyPlanes, const Tuning&, hipStream_t) { launched += 'h'; }
+void launch_pack_keys(const void*, const void*, uint64_t, Workspace*, uint32_t*, uint32_t*, const uint32_t*, const uint32_t*, KeyPlanes, uint32_t*, uint32_t, hipStream_t) { launched += 'p'; }
+void launch_table(Workspace*, uint64_t, int, int, uint32_t*, const uint32_t*, uint32_t*, hipStream_t) { launched += 't'; }
+void launch_spec_table(Workspace*, const TableCache*, uint64_t, int, int, uint32_t*, hipStream_t) {}
+void launch_spec_sweep(const void*, const void*, uint64_t, int, Workspace*, uint32_t*, uint32_t*, uint32_t*, uint32_t, const Tuning&, hipStream_t) { launched += 's'; }
+void launch_pack(const void*, const void*, uint64_t, int, Workspace*, uint32_t*, uint32_t*, const uint32_t*, const uint32_t*, const uint8_t*, uint32_t*, uint32_t, const Tuning&, hipStream_t) { launched += 'p'; }
+bool pack_needs_list(uint64_t, int, const Tuning&) { return false; }
+void launch_place(uint8_t*, Workspace*, const uint32_t*, const uint32_t*, const uint32_t*, uint32_t, uint64_t, uint32_t*, Result* r, TableCache*, int, int, bool, hipStream_t) { launched += 'P'; done(r); }
+void launch_encode_one(const void*, const void*, uint64_t, int, int, uint8_t*, Workspace*, uint32_t*, TableCache*, Result* r, uint64_t (&)[kMeetLines], uint32_t, hipStream_t) { launched += 'E'; if (meet) done(r); }
+void launch_batch_encode(const BatchArgs&, const Tuning&, hipStream_t) {}
+void launch_batch_decode(const BatchDecArgs&, const Tuning&, hipStream_t) {}
+void launch_dec_check(const BlobList&, int, int count, uint64_t, int, uint64_t, Workspace*, uint64_t, HostResult* host, hipStream_t) {
+    launched += 'c';
+    for (int i = 0; i < count; ++i) { host->bytes[i] = 1000; host->max_len[i] = 3; }
+}
+void launch_decode(const uint8_t*, void* w_ref, uint64_t, int, Workspace*, int, uint64_t, HostResult*, const Tuning&, hipStream_t) { launched += w_ref ? 'd' : 'v'; }
+void launch_decode_one(const BlobList&, int count, void*, uint64_t, int, uint64_t, Workspace*, uint64_t, HostResult* host, uint64_t (&)[kMeetLines], uint32_t, hipStream_t) {
+    launched += 'D';
+    if (meet) for (int i = 0; i < count; ++i) host->bytes[i] = 1000;
+}
+void launch_decode_fused(const BlobList&, int, int, void*, uint64_t, int, Workspace*, uint64_t, HostResult*, uint32_t, bool, const Tuning&, hipStream_t) { launched += 'f'; }
+size_t fused_lds_bytes(int, uint32_t) { return 1; }
+}  // namespace lc
+
+static int wrong = 0;
+static void expect(const char* what, const std::string& want) {
+    if (launched != want) { printf("%s: %s, not %s\n", what, launched.c_str(), want.c_str()); ++wrong; }
+    launched.clear();
+}
+alignas(256) static char mem[4][64];
+static const uint64_t kShort = 40 * 16384, kShortest = 3 * 16384, kLong = 600 * 16384;
+static void* stream(intptr_t i) { return (void*)i; }
+static lc_ssize encode(uint64_t n, intptr_t s) { return lc_encode((const float*)mem[0], (const float*)mem[1], n, 3, mem[2], stream(s)); }
+static int encode_async(uint64_t n, intptr_t s) { return lc_encode_async((const float*)mem[0], (const float*)mem[1], n, 3, mem[2], nullptr, stream(s)); }
+static lc_ssize decode(uint64_t n, intptr_t s) { return lc_decode(mem[2], (float*)mem[0], n, stream(s)); }
+static lc_ssize decode_many(int count, uint64_t n, intptr_t s) {
+    const void* blobs[2] = {mem[2], mem[2]};
+    return lc_decode_many(blobs, count, (float*)mem[0], n, stream(s));
+}
+static void ok(lc_ssize r, lc_ssize want = 1000) { if (r != want) { printf("result %lld, not %lld\n", (long long)r, (long long)want); ++wrong; } }
+static void fresh() { lc_shutdown(); meet = true; waiting = nullptr; launched.clear(); }
+// the one scratch area of a caller: every stream's calls take it
+static void* caller_area() {
+    const size_t bytes = (lc_workspace_bytes(kLong, 3) + 255) / 256 * 256;
+    void* p = aligned_alloc(256, bytes);
+    lc_set_workspace(p, bytes);
+    return p;
+}
+
+SCENARIOS
+int main() { scenarios(); lc_shutdown(); if (!wrong) puts("as expected"); return wrong != 0; }
+"""
+
+# each: the body of scenarios()
+GIVEN_UP = r"""
+static void scenarios() {
+    // alone
+    fresh(); ok(encode(kShort, 1)); expect("fresh area", "0E");
+    ok(encode(kShort, 1)); ok(encode(kLong, 1)); ok(encode(kShort, 1)); expect("a larger area, then nothing to clear", "E0htpPE");
+    meet = false; ok(encode(kShort, 1)); expect("given up", "ErhtpP");
+    meet = true; ok(encode(kLong, 1)); expect("and cleared", "htpP");
+
+    for (int user = 0; user < 2; ++user)
+        for (int second = 1; second <= 2; ++second)                     // the second call's stream (the area of another one counts as idle)
+            for (int kind = 0; kind < 4; ++kind) {
+                fresh();
+                void* area = user ? caller_area() : nullptr;
+                ok(encode(kShort, 1)); ok(encode(kLong, 1)); launched.clear();
+                // another thread's call comes in while the first one's outcome is open
+                int ticket = -1;
+                meet = false;
+                waiting = [&] {
+                    meet = true;
+                    if (kind == 0) ticket = encode_async(kLong, second);
+                    if (kind == 1) ok(encode(kLong, second));
+                    if (kind == 2) ticket = encode_async(kShortest, second);
+                    if (kind == 3) ok(encode(kShortest, second));            // fewer counters to look at than the first
+                };
+                ok(encode(kShort, 1));
+                if (ticket >= 0) ok(lc_encode_wait(ticket, nullptr));
+                expect("behind an open call", std::string(kind == 3 ? "ErE" : "ErhtpP") + "rhtpP");
+                // and one behind a call that did meet, while a third is open
+                waiting = [&] { waiting = [&] { ok(encode(kLong, second)); }; ok(encode(kShort, second)); };
+                ok(encode(kShort, 1));
+                expect("two open calls", "ErErhtpP");
+                ok(encode(kLong, second)); expect("none open", "htpP");
+                fresh();
+                free(area);
+            }
+
+    fresh(); ok(encode(kShort, 1)); launched.clear();
+    fail_launches = 1; ok(encode(kShort, 1), -LC_ERR_HIP); ok(encode(kLong, 1)); expect("a launch that failed", "E0htpP");
+    // restores: the counters are known again after a refusal, a given-up call, a launch that failed
+    fresh(); ok(decode(kShort, 1)); expect("fresh area", "D");
+    meet = false; ok(decode(kShort, 1)); meet = true; ok(decode(kShort, 1)); expect("given up", "DcdrD");
+    fail_launches = 1; ok(decode(kShort, 1), -LC_ERR_HIP); ok(decode(kShort, 1)); expect("a launch that failed", "DrD");
+    ok(encode(kLong, 1)); expect("an area that only restores used", "0htpP");
+}
+"""
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
+@pytest.mark.parametrize("scenarios", ["GIVEN_UP"])
+def test_order_of_launches(tmp_path, scenarios):
+    (tmp_path / "hip").mkdir()
+    (tmp_path / "hip" / "hip_runtime.h").write_text(HIP)
+    for name in ("lc_api.hip", "lc_internal.h"):
+        text = open(os.path.join(CSRC, name)).read().replace("../../include/", os.path.join(ROOT, "include") + "/")
+        (tmp_path / name).write_text(text)
+    (tmp_path / "main.cpp").write_text(MAIN.replace("SCENARIOS", globals()[scenarios]))
+    exe = tmp_path / "calls"
+    res = subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-pthread", "-I", str(tmp_path), str(tmp_path / "main.cpp"), "-o", str(exe)],
+                         capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-3000:]
+    run = subprocess.run([str(exe)], capture_output=True, text=True, timeout=30)
+    assert run.returncode == 0 and "as expected" in run.stdout, run.stdout[-3000:]
