@@ -20,6 +20,11 @@
  * issued from several threads; the library keeps a scratch area per stream in use
  * (see lc_encode_async), so calls on different streams overlap on the device.
  *
+ * An encode (not of binary64) or a restore of at most 2 chunks per compute unit that waits for its stream is one
+ * launch, whose workgroups wait for each other.  Beside work that holds part of the chip for longer than they wait, some
+ * 0.1 ms, it is given up, with nothing written, and runs as several kernels like a longer call's; so do, at once, the
+ * next 16 such calls that use its scratch area (after every further one twice as many, up to 1,024).  Results are the same.
+ *
  * ---------------------------------------------------------------------------
  * LCB1 blob layout (little-endian).  The paper says only "save to disk"; this
  * layout is this library's.

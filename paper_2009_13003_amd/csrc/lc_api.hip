@@ -38,6 +38,16 @@ struct Area {
     // extremes, behind, and the thread that waits for it may be the last to learn of that: while there are any, an encode that
     // takes the area clears them first, on its own stream (which is ordered behind theirs).
     uint32_t open = 0;
+    // Where a call in one launch was given up, other work (or the stream's own mask) keeps part of the chip from it, and the next
+    // would mostly be given up as well, at a cost (see encode_impl): the next `rest` calls that take the area, twice as many
+    // after every further one, run in several kernels at once.
+    uint32_t rest = 0, rest_len = 0;
+    static constexpr uint32_t kMostRest = 1024;
+    bool rested() { return rest == 0 || (--rest, false); }
+    void gave_up(const Tuning& tune) {
+        rest_len = rest_len ? (rest_len < kMostRest / 2 ? 2 * rest_len : kMostRest) : (uint32_t)tune.one_rest;
+        rest = rest_len;
+    }
     void counters_cleared() { counted = true; memset(met, 0, sizeof(met)); memset(met_dec, 0, sizeof(met_dec)); }
 };
 
@@ -132,7 +142,8 @@ void read_tuning(DeviceState& ds, int dev) {
     ds.tune.unlisted_per_cu = env_int("LC_TUNE_UNLISTED_PER_CU", ds.tune.unlisted_per_cu, 0, 15);   // (calls of 16 and more may stage keys, which takes a list)
     ds.tune.one_per_cu = env_int("LC_TUNE_ONE_PER_CU", ds.tune.one_per_cu, 0, 2);
     ds.tune.one_dec_per_cu = env_int("LC_TUNE_ONE_DEC_PER_CU", ds.tune.one_dec_per_cu, 0, 2);
-    ds.tune.one_wait = env_int("LC_TUNE_ONE_WAIT", ds.tune.one_wait, 0, 1 << 20);
+    ds.tune.one_wait = env_int("LC_TUNE_ONE_WAIT", ds.tune.one_wait, -1, 1 << 20);
+    ds.tune.one_rest = env_int("LC_TUNE_ONE_REST", ds.tune.one_rest, 0, (int)Area::kMostRest);
     ds.tune.spec_waves_per_cu = env_int("LC_TUNE_SPEC_WAVES_PER_CU", ds.tune.spec_waves_per_cu, 1, 64);
     if (g_key_staging < 0) g_key_staging = env_int("LC_TUNE_KEY_STAGING", 0, 0, 2);
     ds.tune.batch_waves_per_cu = env_int("LC_TUNE_BATCH_WAVES_PER_CU", ds.tune.batch_waves_per_cu, 1, 64);
@@ -385,16 +396,19 @@ lc_ssize encode_impl(const void* w, const void* w_ref, uint64_t n, int nbits, vo
     else if (!area->counted || area->open) { Timed t(kSlotReset, s); launch_reset_one(ws, s); area->counters_cleared(); }
     area->clean = false;
     // A short vector that the caller waits for: one launch, whose workgroups wait for each other (k_encode_one).  They fit the
-    // chip together as long as all such calls in progress have at most kOneResident workgroups per compute unit; a call beyond that, and one whose workgroups did not meet in time
-    // because other work held the chip, takes four kernels.  Whole calls, four kernels / one, us: fp32 2^14 34.1 / 27.3, 2^20
+    // chip together as long as all such calls in progress have at most kOneResident workgroups per compute unit; a call beyond
+    // that takes four kernels, and so does, once more, one whose workgroups did not meet in time because other work held the
+    // chip.  Such a call of 300 chunks beside a kernel that holds half of the compute units for 3 ms: 1,607 us with 4,096 looks,
+    // 456 with 1,024, 166 with 256, 94 with 64, against 57 in four kernels at once.  With 64 looks all calls meet as well where the
+    // chip is free; 256 (0.1 ms) leave room for other work's short kernels, and Area::rest sees to the next calls.  Whole calls, four kernels / one, us: fp32 2^14 34.1 / 27.3, 2^20
     // 40.8 / 29.0, 2^22 46.6 / 30.1, 2^23 56.6 / 45.0; bf16 2^20 38.2 / 28.0, 2^23 48.3 / 42.5; with a cached table that holds,
     // 2^16 57.0 / 27.8, 2^23 66.5 / 45.7.  Beyond that a chunk's deltas no longer fit the registers of a chip-wide grid.
     const uint32_t nchunks = (uint32_t)num_chunks_of(n);
     if (try_one && !async && !staged && dtype != LC_F64 && nchunks >= 1 && nchunks <= (uint32_t)(ds->tune.num_cu * ds->tune.one_per_cu) &&
-        ds->one_blocks + nchunks <= kOneResident * (uint32_t)ds->tune.num_cu) {
+        ds->one_blocks + nchunks <= kOneResident * (uint32_t)ds->tune.num_cu && area->rested()) {
         Result& r = g_pinned[slot].enc;
         r.status = LC_ERR_HIP;                                 // (stays so unless the workgroups met)
-        { Timed t(kSlotEncodeOne, s); launch_encode_one(w, w_ref, n, nbits, dtype, o, ws, chunk_bits, cache, result, area->met, (uint32_t)ds->tune.one_wait, s); }
+        { Timed t(kSlotEncodeOne, s); launch_encode_one(w, w_ref, n, nbits, dtype, o, ws, chunk_bits, cache, result, area->met, ds->tune.one_wait, s); }
         LC_HIP(hipGetLastError());
         if (!release(area, s)) return -LC_ERR_HIP;
         area->clean = true;
@@ -410,11 +424,13 @@ lc_ssize encode_impl(const void* w, const void* w_ref, uint64_t n, int nbits, vo
         if (r.status == LC_ERR_HIP) {
             // they did not meet: what they left in the scratch area is cleared by the next call that takes it
             area->counted = false;
+            area->gave_up(ds->tune);
             free_slot(slot);
             undo.armed = false;
             lock.unlock();
             return encode_impl(w, w_ref, n, nbits, out, dtype, cache, used, stream, async, false);
         }
+        area->rest_len = 0;
         const int slots[] = {kSlotEncodeOne};
         collect(slots, 1);
         if (used) *used = (int)r.used_cache;
@@ -584,9 +600,9 @@ bool decode_in_one(const DeviceState* ds, uint64_t n, int count) {
     return !g_verify_first && nchunks >= 1 && nchunks <= cus * per_cu && ds->one_blocks + nchunks <= kOneResident * cus;
 }
 constexpr lc_ssize kNotMet = INT64_MIN;
-// The bytes restored or -(status); kNotMet: the workgroups did not meet, and none has touched w_ref.  lock: dropped meanwhile (null: kept).
+// The bytes restored or -(status); kNotMet: the workgroups did not meet, and none has touched w_ref.  lock: dropped meanwhile.
 lc_ssize run_decode_one(DeviceState* ds, Area* area, const BlobList& list, int count, void* w_ref, uint64_t n, int dtype, uint64_t max_total,
-                        int slot, uint64_t epoch, hipStream_t s, std::unique_lock<std::mutex>* lock) {
+                        int slot, uint64_t epoch, hipStream_t s, std::unique_lock<std::mutex>& lock) {
     HostResult& r = g_pinned[slot];
     r.bytes[0] = UINT64_MAX;                                   // (stays so unless the workgroups met)
     Workspace* ws = static_cast<Workspace*>(area->mem);
@@ -595,13 +611,13 @@ lc_ssize run_decode_one(DeviceState* ds, Area* area, const BlobList& list, int c
     // counters stand where the host believes them to.)
     if (!area->counted) { Timed t(kSlotReset, s); launch_reset_one(ws, s); area->counters_cleared(); }
     const uint32_t nchunks = (uint32_t)num_chunks_of(n);
-    { Timed t(kSlotDecodeOne, s); launch_decode_one(list, count, w_ref, n, dtype, max_total, ws, epoch, &g_pinned_dev[slot], area->met_dec, (uint32_t)ds->tune.one_wait, s); }
+    { Timed t(kSlotDecodeOne, s); launch_decode_one(list, count, w_ref, n, dtype, max_total, ws, epoch, &g_pinned_dev[slot], area->met_dec, ds->tune.one_wait, s); }
     if (hipGetLastError() != hipSuccess || !release(area, s)) { area->counted = false; return -LC_ERR_HIP; }
     ds->one_blocks += nchunks;
-    const bool drop = lock && !g_prof;                         // (see encode_impl)
-    if (drop) lock->unlock();
+    const bool serial = g_prof;                                // (see encode_impl)
+    if (!serial) lock.unlock();
     const hipError_t waited = hipStreamSynchronize(s);
-    if (drop) lock->lock();
+    if (!serial) lock.lock();
     ds->one_blocks -= nchunks;
     if (waited != hipSuccess) { (void)hipGetLastError(); area->counted = false; return -LC_ERR_HIP; }
     const int slots[] = {kSlotDecodeOne};
@@ -609,7 +625,8 @@ lc_ssize run_decode_one(DeviceState* ds, Area* area, const BlobList& list, int c
     const bool found = (r.dec_status >> 8) == epoch;
     if (found || r.bytes[0] == UINT64_MAX) area->counted = false;     // (refused or given up: what stands on the counters goes)
     if (found) return -(lc_ssize)(r.dec_status & 0xFF);
-    if (r.bytes[0] == UINT64_MAX) return kNotMet;
+    if (r.bytes[0] == UINT64_MAX) { area->gave_up(ds->tune); return kNotMet; }
+    area->rest_len = 0;
     lc_ssize total = 0;
     for (int i = 0; i < count; ++i) total += (lc_ssize)r.bytes[i];
     return total;
@@ -641,8 +658,8 @@ lc_ssize decode_impl(const void* blob, size_t blob_bytes, void* w_ref, uint64_t 
     const uint64_t bound = lc_encode_bound(n, 4), max_total = blob_bytes < bound ? blob_bytes : bound;
     BlobList list;
     for (int t = 0; t < kMaxSets; ++t) list.p[t] = b;
-    if (try_one && !verify_only && decode_in_one(ds, n, 1)) {
-        const lc_ssize r = run_decode_one(ds, area, list, 1, w_ref, n, dtype, max_total, slot, epoch, s, &lock);
+    if (try_one && !verify_only && decode_in_one(ds, n, 1) && area->rested()) {
+        const lc_ssize r = run_decode_one(ds, area, list, 1, w_ref, n, dtype, max_total, slot, epoch, s, lock);
         if (r != kNotMet) return r;
         free_slot(slot);
         undo.slot = -1;
@@ -667,45 +684,15 @@ lc_ssize decode_impl(const void* blob, size_t blob_bytes, void* w_ref, uint64_t 
     if ((g_pinned[slot].dec_status >> 8) == epoch) return -(lc_ssize)(g_pinned[slot].dec_status & 0xFF);
     return (lc_ssize)g_pinned[slot].bytes[0];
 }
-}  // namespace
 
-extern "C" {
-
-lc_ssize lc_decode_t(const void* blob, void* w_ref, uint64_t n, int dtype, void* stream) {
-    return decode_impl(blob, SIZE_MAX, w_ref, n, dtype, stream);
-}
-
-lc_ssize lc_decode_sized(const void* blob, size_t blob_bytes, void* w_ref, uint64_t n, int dtype, void* stream) {
-    return decode_impl(blob, blob_bytes, w_ref, n, dtype, stream);
-}
-
-lc_ssize lc_verify(const void* blob, size_t blob_bytes, uint64_t n, int dtype, void* stream) {
-    return decode_impl(blob, blob_bytes, nullptr, n, dtype, stream, true);
-}
-
-lc_ssize lc_encode_sized(const void* w, const void* w_ref, uint64_t n, int nbits, void* out, size_t out_bytes, int dtype,
-                         void* stream) {
-    const size_t bound = lc_encode_bound(n, nbits);
-    if (bound == 0) return -LC_ERR_BADARG;
-    if (out_bytes < bound) return -LC_ERR_OUT_TOO_SMALL;
-    return encode_impl(w, w_ref, n, nbits, out, dtype, nullptr, nullptr, stream, false);
-}
-
-lc_ssize lc_decode(const void* blob, float* w_ref, uint64_t n, void* stream) {
-    return lc_decode_t(blob, w_ref, n, LC_F32, stream);
-}
-
-lc_ssize lc_decode_many(const void* const* blobs, int count, float* w_ref, uint64_t n, void* stream) {
-    return lc_decode_many_t(blobs, count, w_ref, n, LC_F32, stream);
-}
-
-lc_ssize lc_decode_many_t(const void* const* blobs, int count, void* w_ref, uint64_t n, int dtype, void* stream) {
+lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint64_t n, int dtype, void* stream, bool try_one = true) {
     if (!blobs || count < 1 || count > LC_MAX_MANY || n > LC_MAX_N) return -LC_ERR_BADARG;
     if (dtype != LC_F32 && dtype != LC_BF16 && dtype != LC_F16 && dtype != LC_F64) return -LC_ERR_BADARG;
     if (n && (!w_ref || misaligned(w_ref, dtype == LC_F32 ? 4 : dtype == LC_F64 ? 8 : 2))) return -LC_ERR_BADARG;
     for (int i = 0; i < count; ++i) if (!blobs[i] || misaligned(blobs[i], 16)) return -LC_ERR_BADARG;
-    // (a call of several phases: it keeps the lock, so that no other call's check moves into its area between them)
-    std::lock_guard<std::mutex> lock(g_mu);
+    // (a call of several phases: it keeps the lock, so that no other call's check moves into its area between them; in one
+    // launch it is a single phase)
+    std::unique_lock<std::mutex> lock(g_mu);
     int err = 0;
     DeviceState* ds = device_state(&err);
     if (!ds) return -(lc_ssize)err;
@@ -715,15 +702,19 @@ lc_ssize lc_decode_many_t(const void* const* blobs, int count, void* w_ref, uint
     Workspace* ws = static_cast<Workspace*>(area->mem);
     const int slot = take_slot(false);
     if (slot < 0) return -LC_ERR_HIP;
-    struct Undo { int slot; ~Undo() { free_slot(slot); } } undo{slot};
+    struct Undo { int slot; ~Undo() { if (slot >= 0) free_slot(slot); } } undo{slot};     // (the lock is held on every other return)
     HostResult* host = &g_pinned_dev[slot];
     const HostResult& got = g_pinned[slot];
     const uint64_t epoch = ++g_epoch, bound = lc_encode_bound(n, 4);
     BlobList list;
     for (int t = 0; t < kMaxSets; ++t) list.p[t] = static_cast<const uint8_t*>(blobs[t < count ? t : 0]);
-    if (decode_in_one(ds, n, count)) {
-        const lc_ssize r = run_decode_one(ds, area, list, count, w_ref, n, dtype, bound, slot, epoch, s, nullptr);
+    if (try_one && decode_in_one(ds, n, count) && area->rested()) {
+        const lc_ssize r = run_decode_one(ds, area, list, count, w_ref, n, dtype, bound, slot, epoch, s, lock);
         if (r != kNotMet) return r;
+        free_slot(slot);
+        undo.slot = -1;
+        lock.unlock();
+        return decode_many_impl(blobs, count, w_ref, n, dtype, stream, false);
     }
     // every blob is validated (one launch, one grid row per blob) before w_ref is touched
     { Timed tm(kSlotDecCheck, s); launch_dec_check(list, 0, count, n, dtype, bound, ws, epoch, host, s); }
@@ -785,6 +776,41 @@ lc_ssize lc_decode_many_t(const void* const* blobs, int count, void* w_ref, uint
     collect(slots, 2);
     if ((got.dec_status >> 8) == epoch) return -(lc_ssize)(got.dec_status & 0xFF);
     return (lc_ssize)total;
+}
+}  // namespace
+
+extern "C" {
+
+lc_ssize lc_decode_t(const void* blob, void* w_ref, uint64_t n, int dtype, void* stream) {
+    return decode_impl(blob, SIZE_MAX, w_ref, n, dtype, stream);
+}
+
+lc_ssize lc_decode_sized(const void* blob, size_t blob_bytes, void* w_ref, uint64_t n, int dtype, void* stream) {
+    return decode_impl(blob, blob_bytes, w_ref, n, dtype, stream);
+}
+
+lc_ssize lc_verify(const void* blob, size_t blob_bytes, uint64_t n, int dtype, void* stream) {
+    return decode_impl(blob, blob_bytes, nullptr, n, dtype, stream, true);
+}
+
+lc_ssize lc_encode_sized(const void* w, const void* w_ref, uint64_t n, int nbits, void* out, size_t out_bytes, int dtype,
+                         void* stream) {
+    const size_t bound = lc_encode_bound(n, nbits);
+    if (bound == 0) return -LC_ERR_BADARG;
+    if (out_bytes < bound) return -LC_ERR_OUT_TOO_SMALL;
+    return encode_impl(w, w_ref, n, nbits, out, dtype, nullptr, nullptr, stream, false);
+}
+
+lc_ssize lc_decode(const void* blob, float* w_ref, uint64_t n, void* stream) {
+    return lc_decode_t(blob, w_ref, n, LC_F32, stream);
+}
+
+lc_ssize lc_decode_many_t(const void* const* blobs, int count, void* w_ref, uint64_t n, int dtype, void* stream) {
+    return decode_many_impl(blobs, count, w_ref, n, dtype, stream);
+}
+
+lc_ssize lc_decode_many(const void* const* blobs, int count, float* w_ref, uint64_t n, void* stream) {
+    return decode_many_impl(blobs, count, w_ref, n, LC_F32, stream);
 }
 
 }  // extern "C"

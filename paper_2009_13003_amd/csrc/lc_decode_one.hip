@@ -288,10 +288,10 @@ __global__ __launch_bounds__(kOneDecThreads, 4) void k_decode_one(OneDecArgs a) 
 }
 
 void launch_decode_one(const BlobList& blobs, int count, void* w_ref, uint64_t n, int dtype, uint64_t max_total, Workspace* ws, uint64_t epoch,
-                       HostResult* host, uint64_t (&met)[kMeetLines], uint32_t limit, hipStream_t s) {
-    const u32 nchunks = (u32)num_chunks_of(n), lines = nchunks <= kMeetOneLine ? 1 : kMeetLines;
-    OneDecArgs a = {blobs, w_ref, (u64)n, (u64)max_total, ws, host, (u64)epoch, {}, (u32)count, nchunks, lines, limit};
-    for (u32 k = 0; k < lines; ++k) a.goal[k] = met[k] += (nchunks + lines - 1 - k) / lines;
+                       HostResult* host, uint64_t (&met)[kMeetLines], int looks, hipStream_t s) {
+    const u32 nchunks = (u32)num_chunks_of(n);
+    OneDecArgs a = {blobs, w_ref, (u64)n, (u64)max_total, ws, host, (u64)epoch, {}, (u32)count, nchunks, 0, 0};
+    set_goals(a, nchunks, met, looks);
 #define LC_ONE(DT) do { if (count > 1) hipLaunchKernelGGL((k_decode_one<DT, true>), dim3(nchunks), dim3(kOneDecThreads), 0, s, a); \
                         else hipLaunchKernelGGL((k_decode_one<DT, false>), dim3(nchunks), dim3(kOneDecThreads), 0, s, a); } while (0)
     if (dtype == kF64) LC_ONE(kF64);

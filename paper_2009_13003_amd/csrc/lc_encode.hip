@@ -2454,10 +2454,10 @@ void launch_pack_keys(const void* w, const void* w_ref, uint64_t n, Workspace* w
 }
 
 void launch_encode_one(const void* w, const void* w_ref, uint64_t n, int nbits, int dtype, uint8_t* out, Workspace* ws, uint32_t* record_words,
-                       TableCache* cache, Result* host_result, uint64_t (&met)[kMeetLines], uint32_t limit, hipStream_t s) {
-    const u32 nchunks = (u32)num_chunks_of(n), lines = nchunks <= kMeetOneLine ? 1 : kMeetLines;
-    OneArgs a = {w, w_ref, (u64)n, out, ws, record_words, cache, host_result, {}, nchunks, lines, limit, nbits};
-    for (u32 k = 0; k < lines; ++k) a.goal[k] = met[k] += (nchunks + lines - 1 - k) / lines;
+                       TableCache* cache, Result* host_result, uint64_t (&met)[kMeetLines], int looks, hipStream_t s) {
+    const u32 nchunks = (u32)num_chunks_of(n);
+    OneArgs a = {w, w_ref, (u64)n, out, ws, record_words, cache, host_result, {}, nchunks, 0, 0, nbits};
+    set_goals(a, nchunks, met, looks);
     if (dtype == kBF16) hipLaunchKernelGGL(k_encode_one<kBF16>, dim3(nchunks), dim3(kWgThreads), 0, s, a);
     else if (dtype == kF16) hipLaunchKernelGGL(k_encode_one<kF16>, dim3(nchunks), dim3(kWgThreads), 0, s, a);
     else hipLaunchKernelGGL(k_encode_one<kF32>, dim3(nchunks), dim3(kWgThreads), 0, s, a);

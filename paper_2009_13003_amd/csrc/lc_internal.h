@@ -163,7 +163,8 @@ struct Tuning {
     int batch_unlisted_per_cu = 8;     // ... a batched call
     int one_per_cu = 2;                // chunks per compute unit up to which a call is encoded in one launch (0: never),
     int one_dec_per_cu = 2;            // ... and restored
-    int one_wait = 4096;               // how often its workgroups look for each other before they give up
+    int one_wait = 256;                // how often its workgroups look for each other before they give up (-1: they never meet)
+    int one_rest = 16;                 // calls that do not try it behind one that was given up, and then twice as many (0: all try)
     int spec_waves_per_cu = 8;         // of the single sweep of the cached encode (what its LDS and registers allow)
     int batch_waves_per_cu = 8;        // of the batch kernels
     int decode_blocks_per_cu = 9;      // ... of a long restore (LDS lets 2 run at once; more, smaller shares even out unlike chunks)
@@ -206,10 +207,10 @@ void launch_place(uint8_t* out, Workspace* ws, const uint32_t* chunk_bits, const
                   const uint32_t* prov, uint32_t slot_words, uint64_t n, uint32_t* chunk_maxexp, Result* host_result,
                   TableCache* cache, int nbits, int dtype, bool staged, hipStream_t s);
 // A whole encode of at most tune.one_per_cu chunks per compute unit.  host_result is written only if the workgroups met.
-// met: what the scratch area's counters stand at (all zero once it is cleared), moved on by the call; record_words: one word per
-// chunk of scratch.
+// met: what the scratch area's counters stand at (all zero once it is cleared), moved on by the call; looks: see
+// Tuning::one_wait; record_words: one word per chunk of scratch.
 void launch_encode_one(const void* w, const void* w_ref, uint64_t n, int nbits, int dtype, uint8_t* out, Workspace* ws, uint32_t* record_words,
-                       TableCache* cache, Result* host_result, uint64_t (&met)[kMeetLines], uint32_t limit, hipStream_t s);
+                       TableCache* cache, Result* host_result, uint64_t (&met)[kMeetLines], int looks, hipStream_t s);
 // One tensor of a batched call (lc_encode_batch): every tensor has its own EncState, blob and run of
 // chunks; chunks, groups of 64 chunks and slots of all tensors are numbered through ("dense" indices).
 struct Seg {
@@ -263,7 +264,7 @@ void launch_decode(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, Work
 // host->bytes[0] is written only if the workgroups met or a header is refused; dec_status may say then that a string is wrong.
 // met: as launch_encode_one.
 void launch_decode_one(const BlobList& blobs, int count, void* w_ref, uint64_t n, int dtype, uint64_t max_total, Workspace* ws, uint64_t epoch,
-                       HostResult* host, uint64_t (&met)[kMeetLines], uint32_t limit, hipStream_t s);
+                       HostResult* host, uint64_t (&met)[kMeetLines], int looks, hipStream_t s);
 // Both apply blobs.p[first .. first+count), count <= kMaxMany, using dec_set[first ..]; the fused
 // kernel requires every code of these blobs to be at most kDecLut1Bits long.
 // pay_words: LDS words each wavefront gets for the payloads of one chunk of all `count` blobs.

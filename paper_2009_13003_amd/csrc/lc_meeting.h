@@ -39,6 +39,15 @@ struct GridMeeting {
     }
     __device__ __forceinline__ bool wait(u32 which) const { return wait(which, look(which)); }
 };
+// The host's side: the counters' goals for a grid of nchunks workgroups.  looks < 0: a goal that no arrival reaches, so that every
+// workgroup gives up at its first look.
+template <typename Args>
+inline void set_goals(Args& a, uint32_t nchunks, uint64_t (&met)[kMeetLines], int looks) {
+    a.lines = nchunks <= kMeetOneLine ? 1 : kMeetLines;
+    a.limit = looks < 0 ? 0 : (u32)looks;
+    for (u32 k = 0; k < a.lines; ++k) a.goal[k] = met[k] += (nchunks + a.lines - 1 - k) / a.lines;
+    if (looks < 0) ++a.goal[0];
+}
 __device__ __forceinline__ void wait_own_operations() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 template <typename T> __device__ __forceinline__ T load_shared(const T* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 

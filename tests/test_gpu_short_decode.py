@@ -188,13 +188,15 @@ def test_many_threads(lc):
     assert not wrong
 
 
-@pytest.mark.parametrize("looks", ["0", "1"])
+@pytest.mark.parametrize("looks", ["-1", "0", "1"])
 def test_workgroups_that_give_up(looks):
+    """-1: every call; with a little patience hardly any (their wait begins behind the decoding)."""
     code = """
 import sys, torch, numpy as np
 sys.path.insert(0, %r)
 from tests.test_gpu_short_decode import case, restored, host, CHUNK
 from paper_2009_13003_amd import lc
+lc.lc_profile(True)
 for k in range(60):
     n = (k * 37 %% 250 + 1) * CHUNK + k
     blob, start = case(lc, 'deep', n, 0, torch.float32, 3)
@@ -206,8 +208,11 @@ for k in range(60):
         lc.lc_decode_many_t([blob, blob], many)
         lc.lc_decode(blob, rec)
         assert torch.equal(rec, many), (k, turn)
+p = lc.lc_profile_read()
+given_up = p['k_decode'][1], p['k_decode_fused'][1]
+assert p['k_decode_one'][1] == 540 and (given_up == (360, 180) or sys.argv[1] != '-1'), p
 print('same')
 """ % ROOT
-    env = dict(os.environ, LC_TUNE_ONE_WAIT=looks)
-    res = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, env=env, cwd=ROOT, timeout=100)
+    env = dict(os.environ, LC_TUNE_ONE_WAIT=looks, LC_TUNE_ONE_REST="0")
+    res = subprocess.run([sys.executable, "-c", code, looks], capture_output=True, text=True, env=env, cwd=ROOT, timeout=100)
     assert res.returncode == 0 and "same" in res.stdout, res.stdout[-2000:] + res.stderr[-2000:]

@@ -1,7 +1,7 @@
 """The host side of the library (lc_api.hip) built for the CPU, with a stand-in for the HIP runtime and for the kernels' launchers
 that notes what is launched: the order of launches where calls in one launch are given up, and what another thread's call does that
 takes the same scratch area before the first one's outcome is known (made to come in while the first thread waits, the lock
-dropped)."""
+dropped); and what is learned from a call that was given up."""
 import os
 import shutil
 import subprocess
@@ -80,7 +80,7 @@ void launch_spec_sweep(const void*, const void*, uint64_t, int, Workspace*, uint
 void launch_pack(const void*, const void*, uint64_t, int, Workspace*, uint32_t*, uint32_t*, const uint32_t*, const uint32_t*, const uint8_t*, uint32_t*, uint32_t, const Tuning&, hipStream_t) { launched += 'p'; }
 bool pack_needs_list(uint64_t, int, const Tuning&) { return false; }
 void launch_place(uint8_t*, Workspace*, const uint32_t*, const uint32_t*, const uint32_t*, uint32_t, uint64_t, uint32_t*, Result* r, TableCache*, int, int, bool, hipStream_t) { launched += 'P'; done(r); }
-void launch_encode_one(const void*, const void*, uint64_t, int, int, uint8_t*, Workspace*, uint32_t*, TableCache*, Result* r, uint64_t (&)[kMeetLines], uint32_t, hipStream_t) { launched += 'E'; if (meet) done(r); }
+void launch_encode_one(const void*, const void*, uint64_t, int, int, uint8_t*, Workspace*, uint32_t*, TableCache*, Result* r, uint64_t (&)[kMeetLines], int, hipStream_t) { launched += 'E'; if (meet) done(r); }
 void launch_batch_encode(const BatchArgs&, const Tuning&, hipStream_t) {}
 void launch_batch_decode(const BatchDecArgs&, const Tuning&, hipStream_t) {}
 void launch_dec_check(const BlobList&, int, int count, uint64_t, int, uint64_t, Workspace*, uint64_t, HostResult* host, hipStream_t) {
@@ -88,7 +88,7 @@ void launch_dec_check(const BlobList&, int, int count, uint64_t, int, uint64_t, 
     for (int i = 0; i < count; ++i) { host->bytes[i] = 1000; host->max_len[i] = 3; }
 }
 void launch_decode(const uint8_t*, void* w_ref, uint64_t, int, Workspace*, int, uint64_t, HostResult*, const Tuning&, hipStream_t) { launched += w_ref ? 'd' : 'v'; }
-void launch_decode_one(const BlobList&, int count, void*, uint64_t, int, uint64_t, Workspace*, uint64_t, HostResult* host, uint64_t (&)[kMeetLines], uint32_t, hipStream_t) {
+void launch_decode_one(const BlobList&, int count, void*, uint64_t, int, uint64_t, Workspace*, uint64_t, HostResult* host, uint64_t (&)[kMeetLines], int, hipStream_t) {
     launched += 'D';
     if (meet) for (int i = 0; i < count; ++i) host->bytes[i] = 1000;
 }
@@ -172,9 +172,41 @@ static void scenarios() {
 }
 """
 
+REST = r"""
+static std::string times(int k, const char* x) { std::string r; while (k--) r += x; return r; }
+static void scenarios() {
+    // the calls behind one that was given up do not try: 16, then twice as many each time, up to 1024, until one is not given up
+    for (int what = 0; what < 3; ++what) {
+        fresh();
+        const char* one = what == 0 ? "E" : "D", *several = what == 0 ? "htpP" : what == 1 ? "cd" : "cf";
+        auto call = [&] { ok(what == 0 ? encode(kShort, 1) : what == 1 ? decode(kShort, 1) : decode_many(2, kShort, 1), what == 2 ? 2000 : 1000); };
+        call(); launched.clear();
+        for (int round = 0; round < 2; ++round) {
+            for (int len = 16; len <= 4096; len *= 2) {
+                const int rest = len < 1024 ? len : 1024;
+                meet = false; call(); meet = true;
+                // (what the last one left on the counters is cleared by the next that needs them, or adds to the counts)
+                expect("given up", std::string(len > 16 && what ? "r" : "") + one + (what == 0 ? "r" : "") + several);
+                for (int i = 0; i < rest; ++i) call();
+                expect("resting", times(rest, several));
+            }
+            call(); expect("tried again", std::string(what ? "r" : "") + one);
+            for (int i = 0; i < 5; ++i) call();
+            expect("and met", times(5, one));
+        }
+    }
+    // a restore of several blobs in one launch waits with the lock dropped: other calls go on
+    fresh(); ok(decode(kShort, 1)); launched.clear();
+    waiting = [] { ok(encode(kLong, 2)); };
+    ok(decode_many(2, kShort, 1), 2000); expect("beside a restore of several blobs", "D0htpP");
+    meet = false; waiting = [] { ok(encode(kLong, 2)); };
+    ok(decode_many(2, kShort, 1), 2000); expect("... that is given up", "DhtpPcf");
+}
+"""
+
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
-@pytest.mark.parametrize("scenarios", ["GIVEN_UP"])
+@pytest.mark.parametrize("scenarios", ["GIVEN_UP", "REST"])
 def test_order_of_launches(tmp_path, scenarios):
     (tmp_path / "hip").mkdir()
     (tmp_path / "hip" / "hip_runtime.h").write_text(HIP)
@@ -186,5 +218,6 @@ def test_order_of_launches(tmp_path, scenarios):
     res = subprocess.run(["g++", "-std=c++17", "-O1", "-w", "-pthread", "-I", str(tmp_path), str(tmp_path / "main.cpp"), "-o", str(exe)],
                          capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-3000:]
-    run = subprocess.run([str(exe)], capture_output=True, text=True, timeout=30)
+    env = dict(os.environ, LC_TUNE_ONE_REST="0") if scenarios == "GIVEN_UP" else {k: v for k, v in os.environ.items() if not k.startswith("LC_TUNE")}
+    run = subprocess.run([str(exe)], capture_output=True, text=True, timeout=30, env=env)
     assert run.returncode == 0 and "as expected" in run.stdout, run.stdout[-3000:]
