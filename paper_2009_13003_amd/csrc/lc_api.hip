@@ -590,7 +590,7 @@ namespace {
 // A short vector in one launch, whose workgroups wait for each other's findings before they touch w_ref (see encode_impl for
 // when).  Two kernels / one, us: fp32 2^14 33.9 / 23.5, 2^20 35.4 / 24.9, 2^22 37.8 / 25.8, 2^23 40.4 / 29.0; bf16 2^20 35.2 /
 // 26.2, 2^23 37.2 / 31.7; fp64 2^20 39.8 / 27.8; codes above 10 bits in an array that is off alignment 2^20 89.5 / 35.9; hardly a
-// kept symbol 2^20 26.2 / 23.7, 2^22 24.8 / 23.0, 2^23 25.2 / 26.3.
+// kept symbol 2^20 24.0 / 19.9, 2^22 23.6 / 19.7, 2^23 23.0 / 22.6; none 19.8 / 16.5, 19.8 / 17.1, 19.9 / 17.8.
 // count blobs: beyond a chunk per compute unit a few only, of many the fused sweep is the faster one there (8 blobs of 2^23 113.7 /
 // 130.5 us, 2 55.7 / 47.6).
 bool decode_in_one(const DeviceState* ds, uint64_t n, int count) {

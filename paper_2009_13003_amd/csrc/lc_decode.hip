@@ -163,7 +163,6 @@ constexpr u32 kPayWords = 2048;      // three: 4 bits per element on average
 constexpr u32 kPayWordsTwo = 4224;   // two: 8 bits
 constexpr u32 kPayWordsVerify = 3040;               // three of the verifying sweep, which has no ring (2^28 dense elements 95 us, 119 with two)
 constexpr u32 kPayWordsOne = kChunk * 15 / 32 + 4;  // one: 15 bits, the longest payload there is, wherever it starts in a vector
-constexpr u32 kSparseLaneSlack = 64; // the same for one lane's string
 constexpr u32 kRingWords = 8;        // words of 8 symbols that a lane may be ahead of the rows being restored
 constexpr u32 kGroupRows = 8;        // rows restored at a time: 32 symbols, 4 words of the ring per lane
 

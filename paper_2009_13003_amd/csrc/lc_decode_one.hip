@@ -30,6 +30,7 @@ struct OneDecLds {
     u32 end[kSegs][kW], count[kSegs][kW];
     u64 total0;
     u32 go, moved[kSegs + 1];            // (the last: some string is wrong)
+    u32 set, few;                        // some bit of the payload is set; its kept symbols are in the notes
 };
 
 static_assert(2 * (sizeof(OneDecLds) + 1280) <= kLdsPerCu, "two workgroups per compute unit: the host counts on that many being resident");
@@ -95,6 +96,45 @@ __device__ __forceinline__ u32 take_segment(const OneDecLds& L, u32 nwords, u32 
     return pos;
 }
 
+// A chunk of few kept symbols, by one wavefront: each lane goes from one kept symbol of its string to the next (the merged symbol's
+// code is `m` zero bits, shorter than any other: see decode_sparse) and notes them, place << 4 | symbol, in its column of `noted`.
+// The codes are few enough to be compared with (key: code_key of lane j), so that such a chunk needs no tables.
+// Returns how many, which may be more than the kFewNotes that are noted; *wrong: not `elems` symbols in `bits` bits.
+constexpr u32 kFewNotes = kR * kV / 8, kFewEach = kFewNotes / kSegs;
+__device__ __forceinline__ u32 take_few(const OneDecLds& L, u32 nwords, u32 first_bit, u32 bits, u32 elems, u32 m, u32 key, u32* noted, bool* wrong) {
+    BitReader<true> br;
+    br.start(L.pay, nwords, first_bit);
+    const u32 wi0 = br.wi, avail0 = br.avail, inv = 65536u / m + 1;         // (z inv >> 16 = z / m for z <= 32, m <= 15)
+    u32 pos = 0, count = 0;
+    bool none = false;
+    br.refill();
+    while (__any(pos < elems)) {
+        const u32 top = (u32)(br.win >> 32), zeros = top != 0 ? (u32)__builtin_clz(top) : 32u;
+        const u32 run = min(zeros * inv >> 16, elems - pos);
+        pos += run;
+        br.drop(run * m);
+        br.refill();
+        const bool kept = pos < elems && (u32)(br.win >> (64 - m)) != 0;
+        if (__any(kept)) {
+            const u32 at = (u32)(br.win >> (64 - 15)) << 8 | 0xFFu;
+            u32 best = 0;
+#pragma unroll
+            for (u32 j = 0; j < kMaxSym; ++j) { const u32 kj = read_lane(key, j); best = max(best, kj <= at ? kj : 0u); }
+            const u32 len = (best >> 4) & 15u;
+            if (kept) {
+                none = none || len == 0 || (at >> 8) >= (best >> 8) + (0x8000u >> len);      // starts no code
+                if (count < kFewNotes) noted[count * kW] = (pos << 4) | (best & 15u);
+                ++count;
+                pos = none ? elems : pos + 1;
+                br.drop(len);
+            }
+            br.refill();
+        }
+    }
+    *wrong = none || avail0 + 32 * (br.wi - wi0) - br.avail != bits;
+    return count;
+}
+
 // x + the representative, as the parameters' type holds it (16-bit types: rounded after every blob)
 template <int DT> __device__ __forceinline__ typename Val<DT>::type restored(typename Val<DT>::type x, typename Val<DT>::type rep) {
     if constexpr (DT == kF64) return add_rn(x, rep);
@@ -135,6 +175,7 @@ __global__ __launch_bounds__(kOneDecThreads, 4) void k_decode_one(OneDecArgs a) 
         if (t < kHeaderBytes / 4) L.hdr[t] = reinterpret_cast<const u32*>(blob)[t];
         for (u32 i = t; i < kR * kV / 8 * kW; i += kOneDecThreads) L.syms[0][i] = 0;
         if (t < kSegs + 1) L.moved[t] = 0;
+        if (t == 0) L.set = 0;
         __syncthreads();
         // ---- the header: every workgroup comes to the same findings (as k_dec_check's)
         const u32* hdr = L.hdr;
@@ -155,15 +196,19 @@ __global__ __launch_bounds__(kOneDecThreads, 4) void k_decode_one(OneDecArgs a) 
         const u32* off_tab = reinterpret_cast<const u32*>(blob + kHeaderBytes);
         const u64 o0 = load_uniform(off_tab + c), o1 = load_uniform(off_tab + c + 1);
         bool ok = o0 <= o1 && o1 <= tw && o1 - o0 >= kLaneBitsWords && (c > 0 || o0 == 0) && (c + 1 < a.nchunks || o1 == tw);
-        u32 bits = 0, nwords = 0;
+        u32 bits = 0, nwords = 0, set = 0;
         if (ok) {
             typedef u32x4 __attribute__((aligned(4))) u32x4_word;
             const u32* rec = reinterpret_cast<const u32*>(blob + area) + o0;
             nwords = (u32)min(o1 - o0 - kLaneBitsWords, (u64)kOnePayWords);          // (more than that is refused below)
             bits = reinterpret_cast<const uint16_t*>(rec)[lane];
             const u32* from = rec + kLaneBitsWords;
-            for (u32 i = t; i < nwords / 4; i += kOneDecThreads) reinterpret_cast<u32x4*>(L.pay)[i] = reinterpret_cast<const u32x4_word*>(from)[i];
-            if (t < (nwords & 3)) L.pay[nwords / 4 * 4 + t] = from[nwords / 4 * 4 + t];
+            for (u32 i = t; i < nwords / 4; i += kOneDecThreads) {
+                const u32x4 x = reinterpret_cast<const u32x4_word*>(from)[i];
+                reinterpret_cast<u32x4*>(L.pay)[i] = x;
+                set |= x.x | x.y | x.z | x.w;
+            }
+            if (t < (nwords & 3)) { const u32 x = from[nwords / 4 * 4 + t]; L.pay[nwords / 4 * 4 + t] = x; set |= x; }
         }
         const u32 incl = wave_incl_scan(bits), sum = read_lane(incl, kW - 1);
         ok = ok && o1 - o0 == kLaneBitsWords + ((sum + 31) >> 5) && sum > 0 && !__any(bits > kR * kV * 15);
@@ -180,7 +225,8 @@ __global__ __launch_bounds__(kOneDecThreads, 4) void k_decode_one(OneDecArgs a) 
         }
         // The rows of w_ref are on their way while the strings are decoded; of a chunk of few kept symbols (see kSparseSlack)
         // only those that hold one, and only when that is known (2^23 fp32 elements, sparse: 28.4 us with all of them, 26.0 so).
-        const bool sparse = sum <= elems * read_lane(sy.len, K & 15u) + kSparseSlack;
+        const u32 len_merged = read_lane(sy.len, K & 15u);
+        const bool sparse = sum <= elems * len_merged + kSparseSlack;
         const bool late = !MANY && (DT == kF64 || sparse);   // (binary64: their registers would spill meanwhile)
         if (!MANY && !late) {
 #pragma unroll
@@ -192,44 +238,87 @@ __global__ __launch_bounds__(kOneDecThreads, 4) void k_decode_one(OneDecArgs a) 
             if (last || refuse) meet.arrive(2, refuse);      // (what is found from here on in this workgroup keeps only its own rows back)
         }
         if (refuse) return;
-        dec_build_multi<kOneDecThreads>(L.tab.multi, L.one, L.ends, kNoCode, sy.len, sy.code, t);
-        __syncthreads();
-        // ---- the string of every lane, a segment per wavefront
-        const u32 first_bit = incl - bits, cut = bits * v / kSegs, to = bits * (v + 1) / kSegs;
-        const bool long_codes = max_len > kMultiBits;
-        u32 start = cut, count = 0, end;
-        bool bad = false;
-        auto segment = [&]() {
-            end = long_codes ? take_segment<false, true>(L, nwords, first_bit, start, to, nullptr, 0, &count, &bad)
-                             : take_segment<false, false>(L, nwords, first_bit, start, to, nullptr, 0, &count, &bad);
-            L.end[v][lane] = end;
-        };
-        segment();
-        __syncthreads();
-#pragma unroll 1
-        for (u32 turn = 0; turn < kSegs; ++turn) {           // (after turn k the first k + 2 segments are right)
-            const u32 now = v ? L.end[v - 1][lane] : 0u;
-            const bool moves = __any(now != start);
-            __syncthreads();                                 // (everyone has read the ends)
-            if (moves) {
-                start = now;
-                segment();
-                if (lane == 0) L.moved[turn] = 1;
+        // A chunk of merged symbols only, whose code is that of no bit set: so is every word of its payload, and nothing is left to
+        // do.  (A restore that changes nothing, 512 chunks of fp32: 23.4 -> 17.8 us; 19.9 by k_dec_check and k_decode, which look
+        // for such chunks too.)
+        bool quiet = len_merged != 0 && read_lane(sy.code, K & 15u) == 0 && !__any(bits != mine * len_merged);
+        if (quiet) {
+            if (set != 0) L.set = 1;
+            __syncthreads();
+            quiet = L.set == 0;
+        }
+        // ... and one of few others.  (Heavy tails at 3 bits, 64 / 256 / 512 chunks: 22.6 / 23.0 / 25.0 -> 19.9 / 19.7 / 22.6 us;
+        // 24.0 / 23.6 / 23.0 by the two kernels.)
+        const u32 first_bit = incl - bits;
+        bool few = !MANY && !quiet && sparse && len_merged != 0 && read_lane(sy.code, K & 15u) == 0 && !__any(bits > mine * len_merged + kSparseLaneSlack);
+        if (few) {
+            if (v == 0) {
+                bool wrong;
+                const u32 count = take_few(L, nwords, first_bit, bits, mine, len_merged, code_key(sy.len, sy.code), &L.syms[0][lane], &wrong);
+                const bool noted = !__any(count > kFewNotes);
+                L.count[0][lane] = count;
+                if (noted && __any(wrong) && lane == 0) { L.moved[kSegs] = 1; raise_status(a.ws, a.host, a.epoch, 4u); }
+                if (lane == 0) L.few = noted ? 1u : 0u;
             }
             __syncthreads();
-            if (L.moved[turn] == 0) break;
+            few = L.few != 0;
+            if (!few) {                                      // (as if nothing had been noted)
+                for (u32 i = t; i < kR * kV / 8 * kW; i += kOneDecThreads) L.syms[0][i] = 0;
+            }
         }
-        L.count[v][lane] = count;
-        __syncthreads();
-        u32 before = 0, all = 0;
+        val_t few_x[kFewEach];
+        u32 few_at[kFewEach], few_count = 0;
+        if (few) {
+            // note k of a lane is wavefront k mod 8's; its element is on its way while the workgroups meet
+            few_count = L.count[0][lane];
 #pragma unroll
-        for (u32 k = 0; k < kSegs; ++k) { const u32 m = L.count[k][lane]; before += k < v ? m : 0u; all += m; }
-        // a string that does not hold its lane's symbols in exactly its stated length
-        const bool wrong = bad || all != mine || (v == kSegs - 1 && end != bits);
-        if (__any(wrong) && lane == 0) { L.moved[kSegs] = 1; raise_status(a.ws, a.host, a.epoch, 4u); }
-        const u64 seen = last && v == 0 ? meet.look(2) : 0ull;       // (on its way meanwhile)
-        if (long_codes) take_segment<true, true>(L, nwords, first_bit, start, to, &L.syms[0][lane], before, &count, &bad);
-        else take_segment<true, false>(L, nwords, first_bit, start, to, &L.syms[0][lane], before, &count, &bad);
+            for (u32 k = 0; k < kFewEach; ++k) {
+                few_at[k] = L.syms[v + kSegs * k][lane];
+                const u32 p = few_at[k] >> 4;
+                if (v + kSegs * k < few_count) few_x[k] = load_one_v<DT>(a.w_ref, base + (p / kV) * kRowElems + lane * kV + p % kV);
+            }
+        }
+        u64 seen = last && v == 0 && (quiet || few) ? meet.look(2) : 0ull;
+        if (!quiet && !few) {
+            dec_build_multi<kOneDecThreads>(L.tab.multi, L.one, L.ends, kNoCode, sy.len, sy.code, t);
+            __syncthreads();
+            // ---- the string of every lane, a segment per wavefront
+            const u32 cut = bits * v / kSegs, to = bits * (v + 1) / kSegs;
+            const bool long_codes = max_len > kMultiBits;
+            u32 start = cut, count = 0, end;
+            bool bad = false;
+            auto segment = [&]() {
+                end = long_codes ? take_segment<false, true>(L, nwords, first_bit, start, to, nullptr, 0, &count, &bad)
+                                 : take_segment<false, false>(L, nwords, first_bit, start, to, nullptr, 0, &count, &bad);
+                L.end[v][lane] = end;
+            };
+            segment();
+            __syncthreads();
+#pragma unroll 1
+            for (u32 turn = 0; turn < kSegs; ++turn) {           // (after turn k the first k + 2 segments are right)
+                const u32 now = v ? L.end[v - 1][lane] : 0u;
+                const bool moves = __any(now != start);
+                __syncthreads();                                 // (everyone has read the ends)
+                if (moves) {
+                    start = now;
+                    segment();
+                    if (lane == 0) L.moved[turn] = 1;
+                }
+                __syncthreads();
+                if (L.moved[turn] == 0) break;
+            }
+            L.count[v][lane] = count;
+            __syncthreads();
+            u32 before = 0, all = 0;
+#pragma unroll
+            for (u32 k = 0; k < kSegs; ++k) { const u32 m = L.count[k][lane]; before += k < v ? m : 0u; all += m; }
+            // a string that does not hold its lane's symbols in exactly its stated length
+            const bool wrong = bad || all != mine || (v == kSegs - 1 && end != bits);
+            if (__any(wrong) && lane == 0) { L.moved[kSegs] = 1; raise_status(a.ws, a.host, a.epoch, 4u); }
+            if (last && v == 0) seen = meet.look(2);             // (on its way meanwhile)
+            if (long_codes) take_segment<true, true>(L, nwords, first_bit, start, to, &L.syms[0][lane], before, &count, &bad);
+            else take_segment<true, false>(L, nwords, first_bit, start, to, &L.syms[0][lane], before, &count, &bad);
+        }
         if (last && v == 0) { const bool met = meet.wait(2, seen); if (lane == 0) L.go = met ? 1u : 0u; }
         __syncthreads();
         if (L.moved[kSegs] != 0) {
@@ -239,6 +328,16 @@ __global__ __launch_bounds__(kOneDecThreads, 4) void k_decode_one(OneDecArgs a) 
         if (last && !L.go) return;
         if (c == 0 && t == 0) { a.host->max_len[b] = max_len; if (last || b) a.host->bytes[b] = total; }
         if (MANY && c == 0 && t == 0 && b == 0) L.total0 = total;        // (bytes[0] says that the workgroups met)
+        if (quiet) continue;
+        if (few) {
+#pragma unroll
+            for (u32 k = 0; k < kFewEach; ++k) {
+                const u32 p = few_at[k] >> 4;
+                if (v + kSegs * k < few_count)
+                    store_one_v<DT>(a.w_ref, base + (p / kV) * kRowElems + lane * kV + p % kV, add_rn(few_x[k], L.tab.template rep_of<DT>(few_at[k] & 15u)));
+            }
+            continue;
+        }
         // ---- Algorithm 1 line 7; a row without a kept symbol stays as it is
         u32 syms[kOneSegRows], here = 0;
 #pragma unroll

@@ -333,6 +333,10 @@ __device__ __forceinline__ bool dec_symbols(const u32* hdr, u64 n, u32 nchunks, 
     return ok;
 }
 
+// A code, left-justified, is the largest of those not above a window that starts with it: code, length and symbol of lane j <
+// 16, so that they compare in that order.
+__device__ __forceinline__ u32 code_key(u32 len, u32 code) { return len ? (code << (15 - len)) << 8 | len << 4 | (lane_id() & 15u) : 0xFFFFFFFFu; }
+
 // The sweeps' tables, by a workgroup of THREADS threads.  One symbol per look-up over the next 10 bits in `one`: symbol | len << 4;
 // a prefix that starts no code: kOneNone; a prefix of a code longer than 10 bits: 0xFF.  From it every entry of
 // the table of several symbols is then put together by taking codes off the front of its 10 bits, a thread's entries
@@ -342,8 +346,7 @@ constexpr u32 kOneNone = 0xF0;
 template <u32 THREADS>
 __device__ __forceinline__ void dec_build_multi(u32* multi, uint8_t* one, uint16_t* ends, u32 none, u32 len, u32 code, u32 t) {
     constexpr u32 kEach = (1u << kMultiBits) / THREADS;
-    // A code, left-justified, is the largest of those not above a window that starts with it.
-    const u32 key = len ? (code << (15 - len)) << 8 | len << 4 | (lane_id() & 15u) : 0xFFFFFFFFu;
+    const u32 key = code_key(len, code);
     u32 e[kEach];
 #pragma unroll
     for (u32 k = 0; k < kEach; ++k) e[k] = 0;
@@ -392,6 +395,7 @@ __device__ __forceinline__ void dec_build_multi(u32* multi, uint8_t* one, uint16
 
 constexpr u32 kSparseSlack = 1024;   // bits above an all-merged chunk up to which a chunk's kept symbols are restored one by one
                                      // (512 instead: a batch of 2^24 elements at 2 bits 49 us, 40 so; 2048: the same)
+constexpr u32 kSparseLaneSlack = 64; // the same for one lane's string
 
 struct DecLds {
     alignas(16) u32 multi[1u << kMultiBits];

@@ -55,6 +55,16 @@ def binades(kind, n, g):
         return (torch.rand(n, generator=g, device=DEV) < 0.4).float()
     if kind == "one symbol":
         return torch.zeros(n, device=DEV)
+    if kind == "few":                                        # behind chunk 0, which fixes the code (merged: 1 bit, the others 2), few kept ones
+        e = torch.zeros(n, device=DEV)
+        e[:CHUNK] = torch.floor(2.5 * torch.rand(min(n, CHUNK), generator=g, device=DEV))
+        for chunk in range(1, (n + CHUNK - 1) // CHUNK - 1):
+            # (32 symbols of a lane are noted, a lane of more than 64 bits above its merged ones takes the usual path)
+            for lane, count in ((3, 1), (chunk % 64, 30 + chunk), (63, 5)):
+                p = torch.randperm(256, generator=g, device=DEV)[:count]
+                e[chunk * CHUNK + (p // 4) * 256 + lane * 4 + p % 4] = 1 + (p % 2).float()
+        e[n - 1] = 2
+        return e
     k = torch.floor(-torch.log2(torch.rand(n, generator=g, device=DEV).clamp_(min=2.0 ** -20)))
     e = torch.where((k > 0) & (k < 16), 16 - k, torch.zeros_like(k))
     if kind == "uneven":                                     # every lane: kept symbols in the first quarter of its rows, few behind
@@ -77,7 +87,7 @@ def case(lc, kind, n, offset, dtype, nbits, seed=0):
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16, torch.float64])
 @pytest.mark.parametrize("n,offset", [(1, 0), (5, 1), (1025, 0), (CHUNK, 0), (CHUNK + 3, 1), (3 * CHUNK - 1, 0), (18 * CHUNK + 777, 0), (33 * CHUNK, 1)])
-@pytest.mark.parametrize("kind", ["one length", "one bit", "one symbol", "deep", "uneven"])
+@pytest.mark.parametrize("kind", ["one length", "one bit", "one symbol", "deep", "uneven", "few"])
 def test_short_restores(lc, kind, n, offset, dtype):
     for nbits in (4, 3) if kind in ("deep", "one length") else (4,):
         print("short", kind, n, offset, dtype, nbits, flush=True)
@@ -98,7 +108,7 @@ def test_largest(lc, chunks):
         assert torch.equal(rec.view(torch.uint8), torch.from_numpy(restored(blob.cpu().numpy(), start)).to(DEV))
 
 
-@pytest.mark.parametrize("kind", ["one length", "deep", "one symbol"])
+@pytest.mark.parametrize("kind", ["one length", "deep", "one symbol", "few"])
 def test_damaged_blobs(lc, kind):
     """The verifying sweep's and the oracle's verdict on blobs with one bit flipped; found before the first store in the header and the offsets."""
     n = 5 * CHUNK + 1234
@@ -132,7 +142,7 @@ def test_damaged_blobs(lc, kind):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16, torch.float64])
-@pytest.mark.parametrize("n,offset,kinds", [(7, 0, ["deep", "one bit"]), (CHUNK + 900, 1, ["deep", "uneven", "one symbol"]), (5 * CHUNK, 0, ["one length"] * 3),
+@pytest.mark.parametrize("n,offset,kinds", [(7, 0, ["deep", "one bit"]), (CHUNK + 900, 1, ["deep", "uneven", "one symbol", "few"]), (5 * CHUNK, 0, ["one length"] * 3),
                                             (21 * CHUNK - 2, 0, ["deep", "one symbol", "one bit", "uneven", "deep", "one length", "deep", "uneven", "deep"])])
 def test_several_blobs(lc, dtype, n, offset, kinds):
     """lc_decode_many in one launch: as one restore after the other (16-bit values rounded after every blob)."""
