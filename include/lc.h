@@ -294,7 +294,8 @@ lc_ssize lc_verify(const void* blob, size_t blob_bytes, uint64_t n, int dtype, v
  * w_ref in this order.  The result is bit for bit what `count` successive lc_decode calls
  * give (one fp32 add per blob and element, in blob order), but w_ref is read and written
  * once per sweep of several blobs (up to 8; as many as the decoder's on-chip memory takes
- * at full occupancy, typically 4 to 6) instead of once per blob.
+ * at full occupancy, typically 4 to 6) instead of once per blob; of a short vector, in most calls, once for the whole
+ * list, in one launch.
  *   blobs  HOST array of `count` DEVICE pointers to LCB1 blobs (16-byte aligned), each with
  *          header n equal to `n`; 1 <= count <= LC_MAX_MANY
  * Every blob is validated as in lc_decode before w_ref is touched.  Waits for `stream`;
@@ -302,9 +303,9 @@ lc_ssize lc_verify(const void* blob, size_t blob_bytes, uint64_t n, int dtype, v
  */
 lc_ssize lc_decode_many(const void* const* blobs, int count, float* w_ref, uint64_t n, void* stream);
 /* The same for parameters of type dtype, every blob of that type: bit for bit what `count` successive lc_decode_t
- * calls give, i.e. the running value is rounded to the storage type after every blob's addition.  LC_F64: every
- * blob is validated first as for the other types, then the blobs are applied one sweep each (one read and one write
- * of w_ref per blob). */
+ * calls give, i.e. the running value is rounded to the storage type after every blob's addition.  LC_F64: as for the
+ * other types, but beyond 2 chunks per compute unit (one, where the blobs hold few kept symbols) the blobs are applied
+ * one sweep each (one read and one write of w_ref per blob). */
 lc_ssize lc_decode_many_t(const void* const* blobs, int count, void* w_ref, uint64_t n, int dtype, void* stream);
 
 /*

@@ -591,13 +591,35 @@ namespace {
 // when).  Two kernels / one, us: fp32 2^14 33.9 / 23.5, 2^20 35.4 / 24.9, 2^22 37.8 / 25.8, 2^23 40.4 / 29.0; bf16 2^20 35.2 /
 // 26.2, 2^23 37.2 / 31.7; fp64 2^20 39.8 / 27.8; codes above 10 bits in an array that is off alignment 2^20 89.5 / 35.9; hardly a
 // kept symbol 2^20 24.0 / 19.9, 2^22 23.6 / 19.7, 2^23 23.0 / 22.6; none 19.8 / 16.5, 19.8 / 17.1, 19.9 / 17.8.
-// count blobs: beyond a chunk per compute unit a few only, of many the fused sweep is the faster one there (8 blobs of 2^23 113.7 /
-// 130.5 us, 2 55.7 / 47.6).
-bool decode_in_one(const DeviceState* ds, uint64_t n, int count) {
-    const uint64_t nchunks = num_chunks_of(n), cus = (uint64_t)ds->tune.num_cu, per_cu = count <= 4 ? ds->tune.one_dec_per_cu : ds->tune.one_dec_per_cu ? 1 : 0;
-    // (an LC_TUNE_* shape for the fused sweep asks for that sweep)
-    if (count > 1 && ds->tune.fused_min_waves_per_cu != Tuning().fused_min_waves_per_cu) return false;
-    return !g_verify_first && nchunks >= 1 && nchunks <= cus * per_cu && ds->one_blocks + nchunks <= kOneResident * cus;
+bool fits_in_one(const DeviceState* ds, uint64_t n) {
+    const uint64_t nchunks = num_chunks_of(n), cus = (uint64_t)ds->tune.num_cu;
+    return !g_verify_first && nchunks >= 1 && nchunks <= cus * ds->tune.one_dec_per_cu && ds->one_blocks + nchunks <= kOneResident * cus;
+}
+// Several blobs in one launch, without a look at them first?  Check and sweeps / one launch, as a ratio of whole calls, at 64, 256 /
+// 320, 512 chunks, by (fp32) symbols of one scale at 3 bits; heavy tails at 3; of one scale at 2; all 16 symbols as frequent at 4:
+//   aligned, 2 blobs 1.28 1.26 / 1.12 1.11; 1.51 1.53 / 1.35 1.32; 1.35 1.34 / 1.17 1.17; 0.99 1.03 / 0.85 0.89
+//            3       1.14 1.12 / 0.98 1.00; 1.36 1.38 / 1.22 1.23; 1.19 1.20 / 1.04 1.05; 1.07 1.12 / 0.90 1.00
+//            4       1.04 1.02 / 0.90 0.92; 1.25 1.25 / 1.12 1.13; 1.09 1.08 / 0.94 0.96; 0.86 0.92 / 0.73 0.80
+//            5       1.17 1.22 / 1.02 1.07; 1.19 1.21 / 1.08 1.10; 1.04 1.07 / 0.91 0.94; 0.93 1.00 / 0.80 0.90
+//            8       0.92 0.94 / 0.81 0.84; 1.18 1.22 / 1.04 1.06; 1.01 1.05 / 0.88 0.91; 0.78 0.84 / 0.66 0.74
+//            16      0.86 0.90 / 0.75 0.80; 1.05 1.08 / 0.94 0.98; 0.89 0.93 / 0.79 0.83; 0.76 0.84 / 0.66 0.73
+// (the fused sweep takes 4 of them at a time), bf16 up to a tenth more; off alignment 1.14 to 5.3 at every size and count.
+// binary64, whose other route is a sweep per blob: up to a chunk per compute unit 0.87 to 2.3, above that 1.4 to 2.9 where the strings
+// are dense and 0.66 to 0.95 where they are not.
+bool many_in_one(const DeviceState* ds, uint64_t n, int count, const void* w_ref, int dtype) {
+    if (!fits_in_one(ds, n)) return false;
+    const bool one_each = num_chunks_of(n) <= (uint64_t)ds->tune.num_cu;
+    if (count == 1 || dtype == LC_F64) return count == 1 || one_each;
+    return misaligned(w_ref, dtype == LC_F32 ? 16 : 8) || count <= (one_each ? 5 : 3);
+}
+// ... once they have been checked: codes above 7 bits, for which the fused sweep has a slow form only (1.3 to 4.1 without the
+// check); binary64, strings of 1.5 bits per element and more.
+bool many_in_one_checked(const DeviceState* ds, uint64_t n, int count, int dtype, const HostResult& got) {
+    if (!fits_in_one(ds, n)) return false;
+    int longs = 0;
+    uint64_t bytes = 0;
+    for (int i = 0; i < count; ++i) { longs += got.max_len[i] > kDecLut1Bits; bytes += got.bytes[i] - chunk_area_of(num_chunks_of(n)); }
+    return dtype == LC_F64 ? 16 * bytes > 3 * n * (uint64_t)count : 4 * longs >= count;
 }
 constexpr lc_ssize kNotMet = INT64_MIN;
 // The bytes restored or -(status); kNotMet: the workgroups did not meet, and none has touched w_ref.  lock: dropped meanwhile.
@@ -658,7 +680,7 @@ lc_ssize decode_impl(const void* blob, size_t blob_bytes, void* w_ref, uint64_t 
     const uint64_t bound = lc_encode_bound(n, 4), max_total = blob_bytes < bound ? blob_bytes : bound;
     BlobList list;
     for (int t = 0; t < kMaxSets; ++t) list.p[t] = b;
-    if (try_one && !verify_only && decode_in_one(ds, n, 1) && area->rested()) {
+    if (try_one && !verify_only && fits_in_one(ds, n) && area->rested()) {
         const lc_ssize r = run_decode_one(ds, area, list, 1, w_ref, n, dtype, max_total, slot, epoch, s, lock);
         if (r != kNotMet) return r;
         free_slot(slot);
@@ -708,14 +730,16 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
     const uint64_t epoch = ++g_epoch, bound = lc_encode_bound(n, 4);
     BlobList list;
     for (int t = 0; t < kMaxSets; ++t) list.p[t] = static_cast<const uint8_t*>(blobs[t < count ? t : 0]);
-    if (try_one && decode_in_one(ds, n, count) && area->rested()) {
+    auto in_one = [&]() {
         const lc_ssize r = run_decode_one(ds, area, list, count, w_ref, n, dtype, bound, slot, epoch, s, lock);
         if (r != kNotMet) return r;
         free_slot(slot);
         undo.slot = -1;
         lock.unlock();
         return decode_many_impl(blobs, count, w_ref, n, dtype, stream, false);
-    }
+    };
+    const bool unseen = many_in_one(ds, n, count, w_ref, dtype);
+    if (try_one && unseen && area->rested()) return in_one();
     // every blob is validated (one launch, one grid row per blob) before w_ref is touched
     { Timed tm(kSlotDecCheck, s); launch_dec_check(list, 0, count, n, dtype, bound, ws, epoch, host, s); }
     if (g_verify_first) {
@@ -725,6 +749,7 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
     if (!release(area, s)) return -LC_ERR_HIP;
     LC_HIP(hipStreamSynchronize(s));
     if ((got.dec_status >> 8) == epoch) return -(lc_ssize)(got.dec_status & 0xFF);
+    if (try_one && !unseen && many_in_one_checked(ds, n, count, dtype, got) && area->rested()) return in_one();
     uint64_t total = 0;
     for (int i = 0; i < count; ++i) total += got.bytes[i];
     if (dtype == LC_F64) {

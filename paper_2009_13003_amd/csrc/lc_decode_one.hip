@@ -390,7 +390,8 @@ void launch_decode_one(const BlobList& blobs, int count, void* w_ref, uint64_t n
                        HostResult* host, uint64_t (&met)[kMeetLines], int looks, hipStream_t s) {
     const u32 nchunks = (u32)num_chunks_of(n);
     OneDecArgs a = {blobs, w_ref, (u64)n, (u64)max_total, ws, host, (u64)epoch, {}, (u32)count, nchunks, 0, 0};
-    set_goals(a, nchunks, met, looks);
+    // (one workgroup's chunk may take all that much longer than another's, with every blob)
+    set_goals(a, nchunks, met, looks < 0 ? looks : looks * count);
 #define LC_ONE(DT) do { if (count > 1) hipLaunchKernelGGL((k_decode_one<DT, true>), dim3(nchunks), dim3(kOneDecThreads), 0, s, a); \
                         else hipLaunchKernelGGL((k_decode_one<DT, false>), dim3(nchunks), dim3(kOneDecThreads), 0, s, a); } while (0)
     if (dtype == kF64) LC_ONE(kF64);

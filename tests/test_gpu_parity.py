@@ -621,7 +621,7 @@ def test_fused_restore_eight_blobs_per_sweep():
     a sweep takes up to 8 blobs: every width of the fused kernel against the oracle."""
     import os, subprocess, sys
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-    env = dict(os.environ, LC_TUNE_FUSED_MIN_WAVES_PER_CU="2")
+    env = dict(os.environ, LC_TUNE_FUSED_MIN_WAVES_PER_CU="2", LC_TUNE_ONE_DEC_PER_CU="0")
     r = subprocess.run([sys.executable, "-c", FUSED_WIDE % root], env=env, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0 and r.stdout.strip().endswith("ok"), r.stdout + r.stderr
 

@@ -171,6 +171,34 @@ def test_several_blobs(lc, dtype, n, offset, kinds):
     assert torch.equal(rec.view(torch.uint8), want.view(torch.uint8))
 
 
+@pytest.mark.parametrize("dtype,chunks,kind,count,kernels", [
+    (torch.float32, 20, "deep", 6, {"k_dec_check", "k_decode_one"}), (torch.bfloat16, 257, "deep", 4, {"k_dec_check", "k_decode_one"}),
+    (torch.float64, 257, "deep", 2, {"k_dec_check", "k_decode_one"}), (torch.float64, 257, "few", 2, {"k_dec_check", "k_decode"}),
+    (torch.float32, 20, "one bit", 6, {"k_dec_check", "k_decode_fused"}), (torch.float32, 257, "one bit", 3, {"k_decode_one"}),
+    (torch.float64, 256, "deep", 33, {"k_decode_one"})])
+def test_several_blobs_by_what_the_check_finds(lc, dtype, chunks, kind, count, kernels):
+    """Lists that go into one launch only once their codes or sizes are known, and those beside them that do not."""
+    print("by the check", dtype, chunks, kind, count, flush=True)
+    blobs, start = [], None
+    for k in range(min(count, 3)):
+        blob, start = case(lc, kind, chunks * CHUNK, 0, dtype, 4, seed=k)
+        blobs.append(blob)
+    blobs = [blobs[k % len(blobs)] for k in range(count)]
+    rec, want = start.clone(), start.clone()
+    lc.lc_profile(True)
+    assert lc.lc_decode_many_t(blobs, rec) == sum(b.numel() for b in blobs)
+    ran = {k for k, v in lc.lc_profile_read().items() if v[1]}
+    lc.lc_profile(False)
+    for kernel in ("k_decode_one", "k_decode_fused"):        # (the others of a list are not timed)
+        assert (kernel in ran) == (kernel in kernels), ran
+    for blob in blobs[:1] if count > 8 else blobs:
+        want.view(torch.uint8).copy_(torch.from_numpy(restored(blob.cpu().numpy(), want)))
+    if count > 8:                                            # (the oracle for the first, single restores for the rest)
+        for blob in blobs[1:]:
+            lc.lc_decode_t(blob, want)
+    assert torch.equal(rec.view(torch.uint8), want.view(torch.uint8))
+
+
 def test_many_threads(lc):
     """More calls at once than fit the chip in one launch each, encodes among them."""
     jobs = [case(lc, "deep", k * CHUNK + 31 * k, 0, torch.float32, 3) for k in (3, 60, 130, 200, 256, 255, 90, 17)]

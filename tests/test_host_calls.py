@@ -1,7 +1,7 @@
 """The host side of the library (lc_api.hip) built for the CPU, with a stand-in for the HIP runtime and for the kernels' launchers
 that notes what is launched: the order of launches where calls in one launch are given up, and what another thread's call does that
 takes the same scratch area before the first one's outcome is known (made to come in while the first thread waits, the lock
-dropped); and what is learned from a call that was given up."""
+dropped); what is learned from a call that was given up; and which way lists of blobs go."""
 import os
 import shutil
 import subprocess
@@ -62,6 +62,8 @@ MAIN = r"""
 //   c check     v verify        d restore          f fused restore
 static std::string launched;
 static bool meet = true;                 // whether the workgroups of a call in one launch meet
+static uint64_t blob_bytes = 1000;       // of every blob that is checked or restored, and its longest code
+static uint32_t blob_max_len = 3;
 static int fail_launches = 0;            // the next launches that fail
 static std::function<void()> waiting;    // runs (once) in a thread that waits for its stream
 hipError_t hipGetLastError() { if (fail_launches > 0) { --fail_launches; return hipErrorUnknown; } return 0; }
@@ -85,12 +87,12 @@ void launch_batch_encode(const BatchArgs&, const Tuning&, hipStream_t) {}
 void launch_batch_decode(const BatchDecArgs&, const Tuning&, hipStream_t) {}
 void launch_dec_check(const BlobList&, int, int count, uint64_t, int, uint64_t, Workspace*, uint64_t, HostResult* host, hipStream_t) {
     launched += 'c';
-    for (int i = 0; i < count; ++i) { host->bytes[i] = 1000; host->max_len[i] = 3; }
+    for (int i = 0; i < count; ++i) { host->bytes[i] = blob_bytes; host->max_len[i] = blob_max_len; }
 }
 void launch_decode(const uint8_t*, void* w_ref, uint64_t, int, Workspace*, int, uint64_t, HostResult*, const Tuning&, hipStream_t) { launched += w_ref ? 'd' : 'v'; }
 void launch_decode_one(const BlobList&, int count, void*, uint64_t, int, uint64_t, Workspace*, uint64_t, HostResult* host, uint64_t (&)[kMeetLines], int, hipStream_t) {
     launched += 'D';
-    if (meet) for (int i = 0; i < count; ++i) host->bytes[i] = 1000;
+    if (meet) for (int i = 0; i < count; ++i) host->bytes[i] = blob_bytes;
 }
 void launch_decode_fused(const BlobList&, int, int, void*, uint64_t, int, Workspace*, uint64_t, HostResult*, uint32_t, bool, const Tuning&, hipStream_t) { launched += 'f'; }
 size_t fused_lds_bytes(int, uint32_t) { return 1; }
@@ -108,8 +110,14 @@ static lc_ssize encode(uint64_t n, intptr_t s) { return lc_encode((const float*)
 static int encode_async(uint64_t n, intptr_t s) { return lc_encode_async((const float*)mem[0], (const float*)mem[1], n, 3, mem[2], nullptr, stream(s)); }
 static lc_ssize decode(uint64_t n, intptr_t s) { return lc_decode(mem[2], (float*)mem[0], n, stream(s)); }
 static lc_ssize decode_many(int count, uint64_t n, intptr_t s) {
-    const void* blobs[2] = {mem[2], mem[2]};
+    const void* blobs[LC_MAX_MANY];
+    for (auto& b : blobs) b = mem[2];
     return lc_decode_many(blobs, count, (float*)mem[0], n, stream(s));
+}
+static lc_ssize decode_many_t(int count, uint64_t n, int dtype, int offset = 0) {
+    const void* blobs[LC_MAX_MANY];
+    for (auto& b : blobs) b = mem[2];
+    return lc_decode_many_t(blobs, count, mem[0] + offset, n, dtype, stream(1));
 }
 static void ok(lc_ssize r, lc_ssize want = 1000) { if (r != want) { printf("result %lld, not %lld\n", (long long)r, (long long)want); ++wrong; } }
 static void fresh() { lc_shutdown(); meet = true; waiting = nullptr; launched.clear(); }
@@ -204,9 +212,47 @@ static void scenarios() {
 }
 """
 
+MANY = r"""
+static void scenarios() {
+    // several blobs: in one launch as they come where that is the faster way whatever they hold, else by what the check finds
+    fresh();
+    const uint64_t small = 64 * 16384, large = 300 * 16384, beyond = 513 * 16384;
+    auto is = [&](const char* want, int count, uint64_t n, int dtype, int offset = 0) {
+        const std::string what = std::to_string(count) + " blobs, " + std::to_string(n / 16384) + " chunks, type " + std::to_string(dtype);
+        ok(decode_many_t(count, n, dtype, offset), (lc_ssize)blob_bytes * count);
+        expect(what.c_str(), want);
+    };
+    for (int dtype : {LC_F32, LC_BF16, LC_F16}) {
+        for (uint32_t len : {7u, 8u}) {
+            blob_max_len = len;
+            is("D", 1, small, dtype); is("D", 5, small, dtype); is(len > 7 ? "cD" : "cf", 6, small, dtype);
+            is("D", 3, large, dtype); is(len > 7 ? "cD" : "cf", 4, large, dtype);
+            is("D", 64, small, dtype, dtype == LC_F32 ? 4 : 2); is("D", 8, large, dtype, dtype == LC_F32 ? 8 : 4);
+            is("cf", 2, beyond, dtype);
+        }
+    }
+    blob_max_len = 3;
+    blob_bytes = 16384;
+    is("D", 8, small, LC_F64); is("cdd", 2, large, LC_F64); is("cdd", 2, beyond, LC_F64);
+    blob_bytes = large / 4;
+    is("cD", 2, large, LC_F64); is("cD", 8, large, LC_F64, 8); is("cdd", 2, beyond, LC_F64);
+    // given up behind the check
+    blob_bytes = 1000; blob_max_len = 9; meet = false;
+    is("cDcff", 16, small, LC_F32);
+    meet = true;
+    is("cff", 16, small, LC_F32);
+    // the check of the strings comes first where that is asked for
+    fresh();
+    lc_set_option(LC_OPT_VERIFY_FIRST, 1);
+    is("cvvf", 2, small, LC_F32);
+    lc_set_option(LC_OPT_VERIFY_FIRST, 0);
+    is("D", 2, small, LC_F32);
+}
+"""
+
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="needs g++")
-@pytest.mark.parametrize("scenarios", ["GIVEN_UP", "REST"])
+@pytest.mark.parametrize("scenarios", ["GIVEN_UP", "REST", "MANY"])
 def test_order_of_launches(tmp_path, scenarios):
     (tmp_path / "hip").mkdir()
     (tmp_path / "hip" / "hip_runtime.h").write_text(HIP)
