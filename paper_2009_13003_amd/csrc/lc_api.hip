@@ -402,10 +402,15 @@ lc_ssize encode_impl(const void* w, const void* w_ref, uint64_t n, int nbits, vo
     // 456 with 1,024, 166 with 256, 94 with 64, against 57 in four kernels at once.  With 64 looks all calls meet as well where the
     // chip is free; 256 (0.1 ms) leave room for other work's short kernels, and Area::rest sees to the next calls.  Whole calls, four kernels / one, us: fp32 2^14 34.1 / 27.3, 2^20
     // 40.8 / 29.0, 2^22 46.6 / 30.1, 2^23 56.6 / 45.0; bf16 2^20 38.2 / 28.0, 2^23 48.3 / 42.5; with a cached table that holds,
-    // 2^16 57.0 / 27.8, 2^23 66.5 / 45.7.  Beyond that a chunk's deltas no longer fit the registers of a chip-wide grid.
+    // 2^16 57.0 / 27.8, 2^23 66.5 / 45.7; fp32 of heavy tails, whose second sweep passes over most of the vector, 2^22 36.7 / 30.4,
+    // 2^23 42.4 / 44.1; unchanged vectors 2^20 27.4 / 26.6, 2^23 39.2 / 41.1.  Beyond that a chunk's deltas no longer fit the
+    // registers of a chip-wide grid.  Aligned 2-byte types without a cache stop at 448 chunks: at 512 symbols of one scale 43.5 /
+    // 43.7 (3 bits) and 46.5 / 44.4 (4), ten layers' 41.3 / 44.0, heavy tails 38.1 / 43.2; at 448 the last two 39.7 / 39.6 and
+    // 39.6 / 38.8.
     const uint32_t nchunks = (uint32_t)num_chunks_of(n);
-    if (try_one && !async && !staged && dtype != LC_F64 && nchunks >= 1 && nchunks <= (uint32_t)(ds->tune.num_cu * ds->tune.one_per_cu) &&
-        ds->one_blocks + nchunks <= kOneResident * (uint32_t)ds->tune.num_cu && area->rested()) {
+    const bool plain16 = esize == 2 && !cache && !misaligned(w, 8) && !misaligned(w_ref, 8);
+    const uint32_t most_in_one = (uint32_t)(ds->tune.num_cu * ds->tune.one_per_cu) * (plain16 ? 7 : 8) / 8;
+    if (try_one && !async && !staged && dtype != LC_F64 && nchunks >= 1 && nchunks <= most_in_one && ds->one_blocks + nchunks <= kOneResident * (uint32_t)ds->tune.num_cu && area->rested()) {
         Result& r = g_pinned[slot].enc;
         r.status = LC_ERR_HIP;                                 // (stays so unless the workgroups met)
         { Timed t(kSlotEncodeOne, s); launch_encode_one(w, w_ref, n, nbits, dtype, o, ws, chunk_bits, cache, result, area->met, ds->tune.one_wait, s); }

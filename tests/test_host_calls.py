@@ -103,7 +103,7 @@ static void expect(const char* what, const std::string& want) {
     if (launched != want) { printf("%s: %s, not %s\n", what, launched.c_str(), want.c_str()); ++wrong; }
     launched.clear();
 }
-alignas(256) static char mem[4][64];
+alignas(256) static char mem[4][256];
 static const uint64_t kShort = 40 * 16384, kShortest = 3 * 16384, kLong = 600 * 16384;
 static void* stream(intptr_t i) { return (void*)i; }
 static lc_ssize encode(uint64_t n, intptr_t s) { return lc_encode((const float*)mem[0], (const float*)mem[1], n, 3, mem[2], stream(s)); }
@@ -172,6 +172,20 @@ static void scenarios() {
 
     fresh(); ok(encode(kShort, 1)); launched.clear();
     fail_launches = 1; ok(encode(kShort, 1), -LC_ERR_HIP); ok(encode(kLong, 1)); expect("a launch that failed", "E0htpP");
+    // 2-byte types up to 448 chunks where they are aligned and have no cache
+    fresh();
+    for (int dtype : {LC_F32, LC_BF16, LC_F16})
+        for (int offset : {0, 2, 4, 8})
+            for (int cached = 0; cached < 2; ++cached)
+                for (uint64_t chunks : {448, 449, 512, 513}) {
+                    if (dtype == LC_F32 && offset == 2) continue;
+                    const char* w = mem[0] + offset;
+                    const bool one = chunks <= (dtype == LC_F32 || cached || offset % 8 ? 512u : 448u);
+                    ok(cached ? lc_encode_cached_t(w, mem[1], chunks * 16384, 3, mem[2], dtype, mem[3], nullptr, stream(1))
+                              : lc_encode_t(w, mem[1], chunks * 16384, 3, mem[2], dtype, stream(1)));
+                    if (launched[0] == '0') launched.erase(0, 1);           // (the area grows)
+                    expect("by size", one ? "E" : cached ? "stpP" : "htpP");
+                }
     // restores: the counters are known again after a refusal, a given-up call, a launch that failed
     fresh(); ok(decode(kShort, 1)); expect("fresh area", "D");
     meet = false; ok(decode(kShort, 1)); meet = true; ok(decode(kShort, 1)); expect("given up", "DcdrD");
