@@ -37,7 +37,9 @@ static_assert(2 * (sizeof(OneDecLds) + 1280) <= kLdsPerCu, "two workgroups per c
 
 // Several blobs of one vector (lc_decode_many): one after the other, the running values in registers; w_ref is read and written
 // once, behind the one meeting.  Check, wait and fused sweep against this, us: 8 blobs of 2^20 fp32 elements at 3 bits 111.9 / 100.5,
-// 3 of 2^17 at 4 bits 103 / 53, 12 of 2^19 bf16 at 4 bits 378 / 175, 8 of 2^22 binary64 295 / 122.
+// 3 of 2^17 at 4 bits 103 / 53, 12 of 2^19 bf16 at 4 bits 378 / 175, 8 of 2^22 binary64 295 / 122.  (The running values take
+// binary64 to the 128 registers that two workgroups per compute unit leave: 20 spill, 52 bytes per lane, and in every type 42
+// scalar ones to lanes of vector registers.)
 struct OneDecArgs {
     BlobList blobs; void* w_ref; u64 n, max_total;
     Workspace* ws; HostResult* host; u64 epoch;
