@@ -2,7 +2,7 @@
 // accumulation (Algorithm 1 line 7; Section 3, C1).
 //
 // lc_decode:        k_dec_check -> k_decode (gated on the check's verdict, no host round trip between); a short vector: k_decode_one
-// lc_decode_many:   k_dec_check (all blobs) -> k_decode_fused<T> per sweep
+// lc_decode_many:   k_dec_check (all blobs) -> k_decode_fused<T> per sweep; of a short vector mostly k_decode_one
 // lc_decode_batch:  kb_dec_tables -> kb_dec_chunks -> kb_decode
 #include "lc_device.h"
 #include <type_traits>

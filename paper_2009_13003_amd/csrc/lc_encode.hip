@@ -3,7 +3,9 @@
 // lc_encode:         k_hist -> k_table -> k_pack -> k_place (whose first workgroup writes the header) (which also clears the scratch
 //                    state for the next call, k_place the per-chunk maxima); k_reset only for a fresh scratch area
 //                    (fp64 parameters: k_hist64 -> k_table<11> -> k_pack64 -> k_place)
+//                    with staged keys: k_hist<..., KEYS> -> k_table -> k_pack_keys -> k_place
 // lc_encode_cached:  k_spec_table -> k_spec_sweep -> k_table -> k_pack (nothing to do on a hit) -> k_place
+// both, of a short vector (fp32, bf16, fp16) that the caller waits for: k_encode_one; k_reset_one behind one that was given up
 // lc_encode_batch:   kb_setup -> kb_hist -> kb_table -> kb_list (long lists) -> kb_pack -> kb_place (whose first workgroups write the headers)
 //
 // The paper (arXiv 2009.13003) defines what is computed: delta against the last

@@ -161,8 +161,8 @@ struct Tuning {
     int unlisted_per_cu = 4;           // a call of at most this many chunks of 4-byte elements (half of 2-byte) per compute unit does
                                        // without a list of chunks to read (below 16: see stage_keys)
     int batch_unlisted_per_cu = 8;     // ... a batched call
-    int one_per_cu = 2;                // chunks per compute unit up to which a call is encoded in one launch (0: never),
-    int one_dec_per_cu = 2;            // ... and restored
+    int one_per_cu = 2;                // chunks per compute unit up to which a call is encoded in one launch (0: never; see encode_impl),
+    int one_dec_per_cu = 2;            // ... and restored (see many_in_one)
     int one_wait = 256;                // how often its workgroups look for each other before they give up (-1: they never meet)
     int one_rest = 16;                 // calls that do not try it behind one that was given up, and then twice as many (0: all try)
     int spec_waves_per_cu = 8;         // of the single sweep of the cached encode (what its LDS and registers allow)

@@ -62,3 +62,27 @@ def test_chunks_that_fit_and_chunks_that_do_not(lc, dtype, nbits, n, offset):
     sizes = lc.lc_encode_batch([w[:half], w], [ref[:half], ref], nbits, outs)
     assert np.array_equal(outs[0][:sizes[0]].cpu().numpy(), oracle_blob(w[:half], ref[:half], nbits))
     assert sizes[1] == want.size and np.array_equal(out[:sizes[1]].cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("n,offset", [(5 * 16384 + 1029, 0), (5 * 16384 + 255, 1), (600 * 16384, 0), (2 * 2048 * 16384 + 3, 0)])
+def test_behind_a_cache_that_does_not_hold(lc, dtype, n, offset):
+    """An empty cache, and one of other data: the sweep in which a workgroup may take several chunks (the largest), again and again on
+    the scratch area that the call before has left, against the plain encode's blob, which has a sweep 2 of its own."""
+    nbits = 4
+    print("cache", dtype, n, offset, flush=True)
+    w, ref = mixed(n, dtype, offset, n)
+    other = (w.float() * 2.0 ** -7).to(dtype)
+    out = lc.alloc_out(n, nbits, DEV)
+    plain = {}
+    for name, x in (("w", w), ("other", other)):
+        size, _ = lc.lc_encode_wait(lc.lc_encode_async_t(x, ref, nbits, out))
+        plain[name] = out[:size].clone()
+    if n < 10 * 16384 and dtype != torch.float16:
+        assert np.array_equal(plain["w"].cpu().numpy(), oracle_blob(w, ref, nbits))
+    for turn in range(4):
+        cache = lc.new_cache(DEV)
+        for name, x in (("w", w), ("other", other), ("w", w)):
+            out.fill_(0xA5)
+            size, used = lc.lc_encode_wait(lc.lc_encode_async_t(x, ref, nbits, out, cache=cache))
+            assert not used and torch.equal(out[:size], plain[name]), (turn, name)
