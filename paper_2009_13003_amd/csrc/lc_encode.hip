@@ -2014,7 +2014,7 @@ __global__ __launch_bounds__(256) void k_place(uint8_t* out, Workspace* ws, cons
 // A short vector in one launch: a workgroup per chunk, all of them resident together, that keeps its deltas in registers
 // from the count to the code.  What such a call costs in four kernels is not bytes but their starts, the gaps between them
 // and every chunk's round trips to memory (chunk maxima, table, slot, slot again): 2^20 fp32 elements 7.0 + 4.6 + 7.9 + 3.7
-// us and three gaps, 40.8 us the call (29.0 so).  Here the workgroups meet twice: when all counts are in (each then builds the table for itself, from
+// us and three gaps, 40.8 us the call (15.2 and 28.5 so).  Here the workgroups meet twice: when all counts are in (each then builds the table for itself, from
 // the same counts), and when all record sizes are known (each then knows where its record goes); see GridMeeting.
 // A cached table's lengths (lc_encode_cached; see k_spec_table), by one wavefront, lane j holding symbol j: whether the cache
 // is usable.

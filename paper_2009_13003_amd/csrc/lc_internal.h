@@ -260,7 +260,7 @@ void launch_dec_check(const BlobList& blobs, int first, int count, uint64_t n, i
 // (set: which of the workspace's decode sets the check kernel filled for this blob; w_ref null: only verify the lane strings)
 void launch_decode(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, Workspace* ws, int set, uint64_t epoch, HostResult* host,
                    const Tuning& tune, hipStream_t s);
-// A whole restore of at most tune.one_dec_per_cu chunks per compute unit: checks blobs.p[0 .. count) and applies them in order.
+// A whole restore of at most tune.one_dec_per_cu chunks per compute unit (which lists: see many_in_one): checks blobs.p[0 .. count) and applies them in order.
 // host->bytes[0] is written only if the workgroups met or a header is refused; dec_status may say then that a string is wrong.
 // met: as launch_encode_one.
 void launch_decode_one(const BlobList& blobs, int count, void* w_ref, uint64_t n, int dtype, uint64_t max_total, Workspace* ws, uint64_t epoch,
