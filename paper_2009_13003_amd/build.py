@@ -7,7 +7,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblc.so")
 SOURCES = ["lc_encode.hip", "lc_decode.hip", "lc_decode_one.hip", "lc_api.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-shared", "-fPIC", "-ffp-contract=off",
-         # packed fp32 instructions stay off on the test machines
+         # packed fp32 instructions stay off: some of their forms have given wrong results on this hardware
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
 
