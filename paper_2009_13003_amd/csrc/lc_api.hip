@@ -770,7 +770,14 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
         if ((got.dec_status >> 8) == epoch) return -(lc_ssize)(got.dec_status & 0xFF);
         return (lc_ssize)total;
     }
-    // Sweeps of up to kMaxMany blobs through the fused kernel.  Its LDS payload area is sized to 1.1 x the blobs'
+    // Sweeps of several blobs, by one of two kernels.  k_decode_pairs takes up to 8 blobs (4 where some keep more than 7 buckets) at
+    // a time, all alike in that; a run of them that takes several sweeps is shared out evenly.  It wins where it saves
+    // sweeps, once there is a chunk for most wavefronts it runs: k_decode_fused / it, us, fp32: 3 bits, 2^25 elements, 2 to 4
+    // blobs 81 86 90 / 93 99 104, 5 blobs 145 / 110, 8 blobs 152 / 145, 2^26 8 blobs 270 / 217, 2^28.4 1,287 / 945; 4 bits
+    // 2^25 2, 3, 4, 8 blobs 88 141 150 269 / 100 118 129 226, ten to fifty layers' 435 to 445 / 213 to 336; by chunks, 8 blobs at 3
+    // bits: 7 130 / 112, 92 117 / 117, 245 102 / 110, 733 114 / 113.  Arrays off alignment, for which the other has a slow form
+    // only, 2.1 to 4.1 times as fast.
+    // k_decode_fused takes up to kMaxFused.  Its LDS payload area is sized to 1.1 x the blobs'
     // average chunk payloads (a chunk above that still decodes, from memory), and a sweep takes only as many
     // blobs as leave room for fused_min_waves_per_cu wavefronts per compute unit.  Blobs with codes longer than
     // the first decode table (7 bits) are grouped apart from those without: they take the kernel's LONG form.
@@ -780,11 +787,28 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
         uint32_t w = ((uint32_t)(words * 1.1) + 63u) & ~63u;
         return w < kFusedMinWords ? kFusedMinWords : w;
     };
+    const uint64_t cus = (uint64_t)ds->tune.num_cu;
+    const bool many = nchunks >= 3 * cus || 4 * nchunks <= cus;
+    const bool by_rows = !misaligned(w_ref, dtype == LC_F32 ? 16 : 8);
+    auto wide = [&](int i) { return got.kept[i] > 7; };
     for (int g0 = 0; g0 < count;) {
+        int run = 1;
+        while (g0 + run < count && wide(g0 + run) == wide(g0)) ++run;
+        const int most = wide(g0) ? kMaxWide : kMaxMany, sweeps = (run + most - 1) / most, pairs = (run + sweeps - 1) / sweeps;
+        if (pairs > 1 && (!by_rows || (many && pairs >= (wide(g0) ? 3 : 5)))) {
+            uint64_t bytes = 0;                                 // the longest blob's
+            for (int i = g0; i < g0 + pairs; ++i) bytes = got.bytes[i] > bytes ? got.bytes[i] : bytes;
+            const uint32_t row_bits = nchunks ? (uint32_t)(16 * 8 * (bytes - area_at) / (nchunks * kW * kR)) : 0;
+            Timed tm(kSlotDecodeFused, s);
+            launch_decode_fused(list, g0, pairs, w_ref, n, dtype, ws, epoch, host, kPairsForm | (row_bits & 0xFFFFu), wide(g0), ds->tune, s);
+            LC_HIP(hipGetLastError());
+            g0 += pairs;
+            continue;
+        }
         const bool short_codes = got.max_len[g0] <= kDecLut1Bits;
         int T = 0;
         double words = 0;
-        while (g0 + T < count && T < kMaxMany && (got.max_len[g0 + T] <= kDecLut1Bits) == short_codes) {
+        while (T < run && T < kMaxFused && (got.max_len[g0 + T] <= kDecLut1Bits) == short_codes) {
             if (nchunks) {
                 const double avg = (double)(got.bytes[g0 + T] - area_at) / 4.0 / (double)nchunks - kLaneBitsWords + 6.0;
                 if (T > 0 && fused_lds_bytes(T + 1, pay_words_of(words + avg)) > lds_budget) break;

@@ -2,7 +2,7 @@
 // accumulation (Algorithm 1 line 7; Section 3, C1).
 //
 // lc_decode:        k_dec_check -> k_decode (gated on the check's verdict, no host round trip between); a short vector: k_decode_one
-// lc_decode_many:   k_dec_check (all blobs) -> k_decode_fused<T> per sweep; of a short vector mostly k_decode_one
+// lc_decode_many:   k_dec_check (all blobs) -> k_decode_fused<T> or k_decode_pairs<T> per sweep; of a short vector mostly k_decode_one
 // lc_decode_batch:  kb_dec_tables -> kb_dec_chunks -> kb_decode
 #include "lc_device.h"
 #include <type_traits>
@@ -131,7 +131,7 @@ __global__ __launch_bounds__(256) void k_dec_check(BlobList blobs, u32 first, u6
         const bool ok = dec_symbol_table(hdr, n, nchunks, area, tw, D, B);
         if (t == 0) {
             if (!ok) raise_status(ws, host, epoch, 4u);
-            host->bytes[host_slot] = total; host->max_len[host_slot] = B.max_len;
+            host->bytes[host_slot] = total; host->max_len[host_slot] = B.max_len; host->kept[host_slot] = hdr[5];
             s_ok = ok;
         }
     }
@@ -690,7 +690,7 @@ __global__ __launch_bounds__(64) void kb_decode(BatchDecArgs a) {
 
 // ----------------------------------------------------------------------------- k_decode_fused
 // Restore from several checkpoints in one sweep (Section 3, C1: u_t = u_0 + sum of the decoded
-// deltas; Section 3.2, checkpoint merging): up to kMaxMany blobs of the same n are decoded side
+// deltas; Section 3.2, checkpoint merging): up to kMaxFused blobs of the same n are decoded side
 // by side and their values added to w_ref in blob order, one fp32 add per blob and element, so
 // the result equals that of applying the blobs one call after the other, with one read and
 // one write of w_ref instead of one per blob.
@@ -1007,6 +1007,426 @@ __global__ __launch_bounds__(64) void k_decode_fused(BlobList blobs, u32 first, 
         else fused_chunk<T, false, LONG, DT>(H, pay, pay_words, w_ref, n, ws, host, c, nchunks, epoch);
     }
 }
+// ----------------------------------------------------------------------------- k_decode_pairs
+// The same for more blobs in one sweep, up to 8 where the other kernel takes 4.  What stands in the way of that is the LDS: with
+// the payloads of whole chunks in it, 8 blobs leave room for 4 wavefronts, one per SIMD, each of which waits out its own
+// look-ups (8 blobs of 355 M elements 1,470 us, two sweeps of 4 by the other kernel 1,240).
+// - Of its strings a lane has a window of kWords words per blob in LDS, 2 KB per blob and wavefront: two wavefronts per SIMD.  A
+//   lane's windows lie in a bank of its own, so that no two lanes meet when they read at places of their own; a read at any
+//   place of a whole payload costs the LDS 7 cycles instead of 2.6.
+// - The windows move on a few at a time, the words asked for 4 rows ahead and ahead of the rows of w_ref (a wait for them, in
+//   order, would else wait for those rows as well: 1,140 us, 930 so); a blob whose windows some lane would leave within two rows
+//   is served at once.  A string is read some four times that way, all of it past the L2: 2 GB beside 3.4.
+// - A step takes two symbols: one look-up over the next 10 bits gives both and their length together, one more their two
+//   representatives (8 bytes at an aligned place cost the LDS hardly more than 4).  18 vector and 5 LDS instructions per row of
+//   4 symbols and blob; one symbol per look-up took 24 and 9.
+// 8 blobs of 355 M elements, codes of 1.65 bits: 1,240 us in two sweeps, 910 so; vector issue 49 %, LDS 60 % of the time, and
+// 5.9 TB/s past the L2.  Without the windows' words it would take 740, without w_ref 750.
+// WIDE: some blob of the sweep has more than 8 symbols: pairs of 4-bit symbols, 11 bits to look up, since its codes
+// are longer, and twice the words.  Two codes that do not fit the table's bits (under 0.1 % of the pairs of codes of
+// 1.7 bits on average, 0.3 % of those of 3.5; most of them in a layer whose symbols are all rare ones) are told from their
+// entry and taken one by one.
+// Arrays that are off alignment take the same loads and stores.
+constexpr u32 kPairsWaves = 8;
+constexpr u32 kPairEscape = 0x8000;
+template <int T, bool WIDE>
+struct PairsLds {
+    static constexpr u32 kBits = WIDE ? 11 : 10, kSym = WIDE ? 4 : 3, kSyms = 1u << kSym;
+    static constexpr u32 kWords = WIDE ? 16 : 8;
+    static constexpr u32 kTurns = T > 4 ? 4 : 2;                           // windows that may move on at a time
+    static constexpr u32 kStepBits = 2 * kV * (WIDE ? 15 : 7);             // the most that two rows take
+    lc_f32x2 rep[T][kSyms * kSyms];                // first symbol | second << kSym -> representatives (-0.0: merged symbol)
+    alignas(16) uint16_t lut[T][1u << kBits];    // next bits -> that index | length of both << 8; or kPairEscape | first symbol |
+                                                 // its length << 8 (0: longer than the table's bits)
+    // Codes one by one: the symbols in canonical order (shorter codes first, then by index) have increasing left-justified
+    // codes, so the rank of the symbol a window starts with is the number of codes not above the window.
+    alignas(16) u32 lj[T][kSyms];                // rank -> code, left-justified in 32 bits
+    u32 e_rank[T][kSyms];                        // rank -> len << 4 | symbol
+    u32 len[T][kSyms];                           // of every symbol
+    const uint8_t* rec_base[T];                  // start of the chunk records
+    const u32* off_tab[T];
+    u32 nranks[T], merged[T];                    // symbols with a code; the merged symbol
+    u32 zero_bits[T];                            // lane length of a chunk of merged symbols only (0: never skip)
+    u32 stop;
+    // word k of lane l's window of blob t: [wave][t][k][l] (the word in front of a window is read, never used)
+    alignas(kWords * 256) u32 win[kPairsWaves][T][kWords][kW];
+};
+
+// A wavefront's places in one chunk's strings.  p: 31 + bits from the start of a window's words, which start at word `from`
+// of the blob's payload of this chunk.
+template <int T, bool WIDE>
+struct PairsStrings {
+    typedef PairsLds<T, WIDE> Lds;
+    const u32* gw[T];                            // the payloads in memory
+    u32 nw[T];                                   // and their words
+    u32 p[T], from[T];
+    // The window's next 32 bits: the low half of {word[(p >> 5) - 1], word[p >> 5]} >> (~p & 31).  (A damaged string may run on;
+    // its words are then any of the window's.)
+    static __device__ __forceinline__ u32 next(const Lds& L, u32 wave, int t, u32 p) {
+        const u32 at = ((p << 3) & ((Lds::kWords - 1) * 256)) | (lane_id() * 4);
+        const u32* w = reinterpret_cast<const u32*>(reinterpret_cast<const uint8_t*>(&L.win[wave][t][0][0]) + at);
+        return __builtin_amdgcn_alignbit(*(w - kW), *w, ~p);
+    }
+};
+
+// A window's words on their way.
+template <int T, bool WIDE>
+struct PairsWords {
+    static constexpr u32 kVecs = PairsLds<T, WIDE>::kWords / 4;
+    typedef u32x4 __attribute__((aligned(4))) vec_any;
+    u32x4 q[kVecs];
+    u32 from;
+    // A window may reach past the payload into the next record, which is longer; in the blob's last chunk (last) it may not.
+    __device__ __forceinline__ void fetch(const PairsStrings<T, WIDE>& S, int t, bool last) {
+        from = min(S.from[t] + ((S.p[t] - 31) >> 5), S.nw[t]);
+        if (!last) {
+            const u32* w = S.gw[t] + from;
+#pragma unroll
+            for (u32 k = 0; k < kVecs; ++k) q[k] = *reinterpret_cast<const vec_any*>(w + 4 * k);
+        } else {
+            const u32 end = S.nw[t] - 1;
+#pragma unroll
+            for (u32 k = 0; k < kVecs; ++k) {
+                const u32 f = from + 4 * k;
+                q[k] = u32x4{S.gw[t][min(f, end)], S.gw[t][min(f + 1, end)], S.gw[t][min(f + 2, end)], S.gw[t][min(f + 3, end)]};
+            }
+        }
+    }
+    __device__ __forceinline__ void place(PairsStrings<T, WIDE>& S, PairsLds<T, WIDE>& L, u32 wave, int t) const {
+        u32* w = &L.win[wave][t][0][lane_id()];
+#pragma unroll
+        for (u32 k = 0; k < kVecs; ++k) { w[(4 * k) * kW] = q[k].x; w[(4 * k + 1) * kW] = q[k].y; w[(4 * k + 2) * kW] = q[k].z; w[(4 * k + 3) * kW] = q[k].w; }
+        S.p[t] += 32 * (S.from[t] - from);
+        S.from[t] = from;
+    }
+};
+
+// The symbol a window starts with: len << 4 | symbol (a prefix that starts no code: the merged symbol, length 0).
+template <int T, bool WIDE>
+__device__ __forceinline__ u32 pairs_one(const PairsLds<T, WIDE>& L, int t, u32 win) {
+    u32 r = 0;
+    u32x4 lj[PairsLds<T, WIDE>::kSyms / 4];                  // (all of them asked for at once: behind the last code, all ones)
+#pragma unroll
+    for (u32 k = 0; k < PairsLds<T, WIDE>::kSyms / 4; ++k) lj[k] = reinterpret_cast<const u32x4*>(L.lj[t])[k];
+#pragma unroll
+    for (u32 k = 0; k < PairsLds<T, WIDE>::kSyms / 4; ++k) r += (win >= lj[k].x) + (win >= lj[k].y) + (win >= lj[k].z) + (win >= lj[k].w);
+    r = min(r, L.nranks[t]) - 1;                             // (the first code is 0)
+    const u32 e = L.e_rank[t][r];
+    return ((win ^ L.lj[t][r]) >> (32 - (e >> 4))) == 0 ? e : L.merged[t];
+}
+
+// Two symbols that do not fit the table together, as an entry of it (of up to 30 bits); e: what it holds for the window's bits.
+template <int T, bool WIDE>
+__device__ __forceinline__ u32 pairs_slow(const PairsLds<T, WIDE>& L, u32 wave, int t, u32 p, u32 win, u32 e) {
+    constexpr u32 kBits = PairsLds<T, WIDE>::kBits, kSym = PairsLds<T, WIDE>::kSym, kMask = (1u << kSym) - 1;
+    u32 first = e & kMask, len = (e >> 8) & 31u;
+    if (WIDE && len == 0) { const u32 a = pairs_one(L, t, win); first = a & 15u; len = a >> 4; }
+    const u32 rest = PairsStrings<T, WIDE>::next(L, wave, t, p + len), f = L.lut[t][rest >> (32 - kBits)];
+    u32 second = f & kMask, l2 = (f >> 8) & 31u;
+    if ((f & kPairEscape) == 0) l2 = l2 ? L.len[t][second] : 0u;              // (length 0: a prefix that starts no code)
+    else if (WIDE && l2 == 0) { const u32 b = pairs_one(L, t, rest); second = b & 15u; l2 = b >> 4; }
+    return first | second << kSym | (len + l2) << 8;
+}
+
+// x << and x + the second byte of e, in one instruction each (the compiler takes two or three).
+__device__ __forceinline__ u32 shl_byte1(u32 x, u32 e) {
+    u32 r;
+    asm("v_lshlrev_b32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:BYTE_1 src1_sel:DWORD" : "=v"(r) : "v"(e), "v"(x));
+    return r;
+}
+__device__ __forceinline__ u32 add_byte1(u32 x, u32 e) {
+    u32 r;
+    asm("v_add_u32_sdwa %0, %1, %2 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:BYTE_1" : "=v"(r) : "v"(x), "v"(e));
+    return r;
+}
+
+// The next 4 symbols of every blob: their representatives, and the positions behind them.  Written step by step across the
+// blobs, so that the T look-ups of a step are in flight together.
+template <int T, bool WIDE>
+__device__ __forceinline__ void pairs_symbols(const PairsLds<T, WIDE>& L, u32 wave, PairsStrings<T, WIDE>& S, lc_f32x2 (&rep)[2][T]) {
+    constexpr u32 kBits = PairsLds<T, WIDE>::kBits;
+    u32 win[T], e[2][T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) win[t] = PairsStrings<T, WIDE>::next(L, wave, t, S.p[t]);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        u32 escapes = 0;
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            e[h][t] = L.lut[t][win[t] >> (32 - kBits)];
+            asm("" : "+v"(e[h][t]));             // keep it a 32-bit value (no 16-bit shift plus re-extension)
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t) escapes |= e[h][t];
+        if (__any((escapes & kPairEscape) != 0)) {
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const bool slow = (e[h][t] & kPairEscape) != 0;
+                if (slow) e[h][t] = pairs_slow(L, wave, t, S.p[t], win[t], e[h][t]);
+                const u32 p = add_byte1(S.p[t], e[h][t]);
+                if (h == 0) win[t] = slow ? PairsStrings<T, WIDE>::next(L, wave, t, p) : shl_byte1(win[t], e[h][t]);
+                S.p[t] = p;
+            }
+        } else {
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                if (h == 0) win[t] = shl_byte1(win[t], e[h][t]);
+                S.p[t] = add_byte1(S.p[t], e[h][t]);
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        rep[0][t] = L.rep[t][e[0][t] & 0xFFu];
+        rep[1][t] = L.rep[t][e[1][t] & 0xFFu];
+    }
+}
+
+// A row's 4 elements and 4 symbols of every blob: the additions, in blob order.
+template <int T, int DT>
+__device__ __forceinline__ void pairs_add(float (&x)[4], const lc_f32x2 (&rep)[2][T]) {
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            x[2 * h] = __fadd_rn(x[2 * h], rep[h][t].x); x[2 * h + 1] = __fadd_rn(x[2 * h + 1], rep[h][t].y);
+            if constexpr (DT != kF32) {          // (the running value as it reads back after a store)
+                const u32 u = narrow16_pair(x[2 * h], x[2 * h + 1], DT == kBF16);
+                x[2 * h] = widen16(u & 0xFFFFu, DT == kBF16); x[2 * h + 1] = widen16(u >> 16, DT == kBF16);
+            }
+        }
+    }
+}
+
+// (plain stores: 957 us for 932)
+template <int DT>
+__device__ __forceinline__ void pairs_store(void* w_ref, u64 idx, const float (&x)[4]) {
+    if constexpr (DT == kF32) __builtin_nontemporal_store(f32x4{x[0], x[1], x[2], x[3]}, reinterpret_cast<f32x4_any*>(static_cast<float*>(w_ref) + idx));
+    else *reinterpret_cast<u32x2_any*>(static_cast<uint16_t*>(w_ref) + idx) =
+             u32x2{narrow16_pair(x[0], x[1], DT == kBF16), narrow16_pair(x[2], x[3], DT == kBF16)};
+}
+
+// off: the chunk's entries of blob t's offset table in lane t (its start) and lane kMaxMany + t (its end); lane_bits: the lane
+// lengths of its records
+template <int T, bool WIDE, int DT>
+__device__ __forceinline__ void pairs_chunk(PairsLds<T, WIDE>& L, u32 wave, void* __restrict__ w_ref, u64 n, Workspace* ws, HostResult* host,
+                                            u32 c, u32 nchunks, u32 off, const u32 (&lane_bits)[T], u32 turns, u32 row_bits, u64 epoch) {
+    typedef PairsLds<T, WIDE> Lds;
+    typedef typename Raw<DT>::type RowT;
+    const u32 lane = lane_id();
+    PairsStrings<T, WIDE> S;
+    const bool last = c + 1 == nchunks;
+    bool loud = false;
+#pragma unroll
+    for (int t = 0; t < T; ++t) {
+        const u32 o0 = read_lane(off, t), o1 = read_lane(off, kMaxMany + t);
+        S.gw[t] = reinterpret_cast<const u32*>(uniform_ptr(L.rec_base[t]) + 4 * (u64)o0 + 2 * kW);
+        S.nw[t] = o1 - o0 - kLaneBitsWords;               // >= 1 (validated)
+        loud = loud || L.zero_bits[t] == 0 || lane_bits[t] != L.zero_bits[t];
+    }
+    if (!__any(loud)) {
+        // every lane has the length of merged symbols only (see zero_chunk_bits); if so, nothing changes and w_ref is not read
+        u32 nonzero = 0;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+            for (u32 i = lane; i < S.nw[t]; i += kW) nonzero |= S.gw[t][i];
+        if (!__any(nonzero != 0)) return;
+    }
+    {
+        PairsWords<T, WIDE> F[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) {
+            S.p[t] = 31 + wave_incl_scan(lane_bits[t]) - lane_bits[t];
+            S.from[t] = 0;
+            F[t].fetch(S, t, last);
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t) F[t].place(S, L, wave, t);
+    }
+    u32 first_bit[T];
+#pragma unroll
+    for (int t = 0; t < T; ++t) first_bit[t] = S.p[t] + 32 * S.from[t];
+
+    // The windows move on, up to `turns` of them every 4 rows: those of blob `turn` and the next ones', unless they will do until
+    // the blob's next turn.  The words are asked for 4 rows before they are put in place.
+    constexpr u32 kMost = Lds::kWords * 32 - 1 - Lds::kStepBits;
+    PairsWords<T, WIDE> F[Lds::kTurns];
+    u32 turn = 0, asked = 0;
+    auto place_words = [&]() {
+#pragma unroll
+        for (u32 i = 0; i < Lds::kTurns; ++i)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                if ((asked >> i & 1u) != 0 && (turn + i) % T == (u32)t) F[i].place(S, L, wave, t);
+    };
+    auto ask_for_words = [&](u32 rows_left) {
+        turn = (turn + turns) % T;
+        asked = 0;
+        const u32 until = min(rows_left, 4 * (T + turns - 1) / turns + 4) * row_bits / 16, enough = until < kMost ? kMost - until : 0;
+#pragma unroll
+        for (u32 i = 0; i < Lds::kTurns; ++i)
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                if (i < turns && (turn + i) % T == (u32)t && __any(S.p[t] > enough)) { asked |= 1u << i; F[i].fetch(S, t, last); }
+    };
+    // ... and at once, where a lane may run out of words within the next two rows
+    auto have_words = [&]() {
+        u32 most = 0;
+#pragma unroll
+        for (int t = 0; t < T; ++t) most = max(most, S.p[t]);
+        if (!__any(most > kMost)) return;
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+            if (__any(S.p[t] > kMost)) { PairsWords<T, WIDE> now; now.fetch(S, t, last); now.place(S, L, wave, t); }
+    };
+    const u64 base = (u64)c * kChunk + lane * kV, left = n - (u64)c * kChunk;
+    const u32 rows = left < kChunk ? (u32)left / kRowElems : kR;
+    auto row = [&](const RowT& raw, u32 r) {
+        float x[4];
+        lc_f32x2 rep[2][T];
+        unpack<DT>(raw, x);
+        pairs_symbols(L, wave, S, rep);
+        pairs_add<T, DT>(x, rep);
+        pairs_store<DT>(w_ref, base + (u64)r * kRowElems, x);
+    };
+    // 8 to 12 rows are on their way ahead of the one being decoded
+    constexpr u32 PF = 4;
+    RowT A[PF], B[PF], C[PF];
+    auto fetch = [&](RowT (&X)[PF], u32 at) {
+#pragma unroll
+        for (u32 k = 0; k < PF; ++k) X[k] = load_raw_any<DT>(w_ref, base + (u64)(at + k) * kRowElems);
+    };
+    const u32 whole = rows / PF * PF;
+    u32 r = 0;
+    if (whole > 0) fetch(A, 0);
+    if (whole > PF) fetch(B, PF);
+#pragma unroll 1
+    for (; r < whole; r += PF) {
+        place_words();                                       // (ahead of the rows, whose loads it would wait for)
+        ask_for_words(rows - r);
+        if (r + 2 * PF < whole) fetch(C, r + 2 * PF);
+#pragma unroll
+        for (u32 k = 0; k < PF; k += 2) {
+            have_words();
+            row(A[k], r + k);
+            row(A[k + 1], r + k + 1);
+        }
+#pragma unroll
+        for (u32 k = 0; k < PF; ++k) { A[k] = B[k]; B[k] = C[k]; }
+    }
+#pragma unroll 1
+    for (; r < rows; ++r) { have_words(); row(load_raw_any<DT>(w_ref, base + (u64)r * kRowElems), r); }
+    if (rows < kR) {
+        // what is left of a ragged chunk, element by element
+        have_words();
+#pragma unroll 1
+        for (u32 v = 0; v < kV; ++v) {
+            const u64 i = base + (u64)rows * kRowElems + v;
+            if (i >= n) continue;
+            float x = load_one<DT>(w_ref, i);
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                const u32 e = pairs_one(L, t, PairsStrings<T, WIDE>::next(L, wave, t, S.p[t]));
+                S.p[t] += e >> 4;
+                x = stored<DT>(__fadd_rn(x, L.rep[t][e & 15u].x));
+            }
+            store_one<DT>(w_ref, i, x);
+        }
+    }
+    bool bad = false;
+#pragma unroll
+    for (int t = 0; t < T; ++t) bad = bad || (S.p[t] + 32 * S.from[t] - first_bit[t] != lane_bits[t]);
+    if (__any(bad) && lane == 0) raise_status(ws, host, epoch, 4u);
+}
+
+// turns: windows that may move on every 4 rows, of a blob each; row_bits: 16 times the bits that a lane takes per row, at most
+template <int T, bool WIDE, int DT>
+__global__ __launch_bounds__(kPairsWaves * kW, T > 4 || WIDE ? 2 : 4) void k_decode_pairs(BlobList blobs, u32 first, void* __restrict__ w_ref, u64 n,
+                                                     Workspace* ws, u32 nchunks, u64 epoch, HostResult* host, u32 turns, u32 row_bits) {
+    typedef PairsLds<T, WIDE> Lds;
+    __shared__ Lds L;
+    const u32 tid = threadIdx.x, lane = tid & (kW - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid == 0) L.stop = (__hip_atomic_load(&ws->dec_status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 8) == epoch;
+    __syncthreads();
+    if (L.stop) return;                                  // a check found something: touch nothing
+    static_assert(kMaxMany <= (int)kPairsWaves, "a wavefront per blob");
+    if (wave < T) {
+        const u32 t = wave;
+        const DecSet& D = ws->dec_set[first + t];
+        const u32 K = D.info.K, len = lane < kMaxSym ? D.info.len[lane] : 0u, code = lane < kMaxSym ? D.info.code[lane] : 0u;
+        const u32 rep = lane < K ? D.info.rep_bits[lane & (kMaxSym - 1)] : 0x80000000u;
+        const u32 coded = (u32)__popcll(__ballot(len != 0));
+        u32x4 m[4];                                          // the tables of all the whole codes of 10 bits: entries 4 (64 k + lane) and on
+#pragma unroll
+        for (u32 k = 0; k < 4; ++k) m[k] = reinterpret_cast<const u32x4*>(D.multi)[k * kW + lane];
+        if (lane == 0) {
+            const uint8_t* blob = blobs.p[first + t];
+            L.zero_bits[t] = zero_chunk_bits(read_lane(len, K), read_lane(code, K));
+            L.rec_base[t] = blob + D.info.area;
+            L.off_tab[t] = reinterpret_cast<const u32*>(blob + kHeaderBytes);
+            L.nranks[t] = coded; L.merged[t] = K;
+        }
+        // the first two symbols of `bits`, which start with entry e's 10
+        auto entry = [&](u32 e, u32 bits) {
+            const u32 s0 = e & 15u, L0 = gather_lane(len, s0);
+            u32 count = e >> 28, s1 = (e >> 4) & 15u;
+            if (WIDE) {
+                const u32 rest = (bits << L0) & ((1u << Lds::kBits) - 1), e1 = D.multi[rest >> (Lds::kBits - kMultiBits)];
+                const u32 l1 = gather_lane(len, e1 & 15u);
+                if (count == 1 && e1 != 0 && ((e1 >> 24) & 15u) != 0 && L0 + l1 <= Lds::kBits) { count = 2; s1 = e1 & 15u; }
+            }
+            const u32 both = L0 + gather_lane(len, s1);
+            const bool none = e != 0 && ((e >> 24) & 15u) == 0;           // a prefix that starts no code
+            return none ? K | K << Lds::kSym : count >= 2 ? s0 | s1 << Lds::kSym | both << 8 : count == 1 ? kPairEscape | s0 | L0 << 8 : kPairEscape;
+        };
+#pragma unroll
+        for (u32 k = 0; k < 4; ++k) {
+            const u32 i = 4 * (k * kW + lane), e[4] = {m[k].x, m[k].y, m[k].z, m[k].w};
+            if constexpr (!WIDE) {
+                reinterpret_cast<u32x2*>(L.lut[t])[k * kW + lane] = u32x2{entry(e[0], i) | entry(e[1], i + 1) << 16, entry(e[2], i + 2) | entry(e[3], i + 3) << 16};
+            } else {
+                u32 two[4];
+#pragma unroll
+                for (u32 j = 0; j < 4; ++j) two[j] = entry(e[j], 2 * (i + j)) | entry(e[j], 2 * (i + j) + 1) << 16;
+                reinterpret_cast<u32x4*>(L.lut[t])[k * kW + lane] = u32x4{two[0], two[1], two[2], two[3]};
+            }
+        }
+#pragma unroll
+        for (u32 i = lane; i < Lds::kSyms * Lds::kSyms; i += kW)
+            L.rep[t][i] = lc_f32x2{__uint_as_float(gather_lane(rep, i & (Lds::kSyms - 1))), __uint_as_float(gather_lane(rep, i >> Lds::kSym))};
+        // a symbol's rank in canonical order (shorter codes first, then by index)
+        const u32 place = lane < kMaxSym && len ? len * kMaxSym + lane : 0xFFFFu;
+        u32 rank = 0;
+        for (u32 j = 0; j < Lds::kSyms; ++j) rank += read_lane(place, j) < place ? 1u : 0u;
+        if (lane < Lds::kSyms) L.len[t][lane] = len;
+        if (lane >= coded && lane < Lds::kSyms) L.lj[t][lane] = 0xFFFFFFFFu;
+        if (lane < Lds::kSyms && len) { L.lj[t][rank] = code << (32 - len); L.e_rank[t][rank] = (len << 4) | lane; }
+    }
+    __syncthreads();
+    // a chunk's entries of the T offset tables are asked for two chunks ahead, its lane lengths one
+    const u32 which = lane & (kMaxMany - 1);
+    const u32* off_tab = lane < 2 * kMaxMany && which < T ? L.off_tab[which] + lane / kMaxMany : nullptr;
+    auto offsets = [&](u64 c) { return off_tab && c < nchunks ? off_tab[c] : 0u; };
+    auto lengths = [&](u64 c, u32 off, u32 (&lane_bits)[T]) {
+        if (c >= nchunks) return;
+#pragma unroll
+        for (int t = 0; t < T; ++t) lane_bits[t] = reinterpret_cast<const uint16_t*>(uniform_ptr(L.rec_base[t]) + 4 * (u64)read_lane(off, t))[lane];
+    };
+    const u32 stride = gridDim.x * kPairsWaves;
+    u64 c = blockIdx.x + (u64)gridDim.x * wave;             // (few chunks: on as many compute units as there are)
+    u32 off = offsets(c), next = offsets(c + stride), bits[T] = {};
+    lengths(c, off, bits);
+    while (c < nchunks) {
+        const u32 after = offsets(c + 2 * (u64)stride);
+        u32 next_bits[T] = {};
+        lengths(c + stride, next, next_bits);
+        pairs_chunk<T, WIDE, DT>(L, wave, w_ref, n, ws, host, (u32)c, nchunks, off, bits, turns, row_bits, epoch);
+#pragma unroll
+        for (int t = 0; t < T; ++t) bits[t] = next_bits[t];
+        off = next; next = after;
+        c += stride;
+    }
+}
 // ----------------------------------------------------------------------------- launchers
 void launch_batch_decode(const BatchDecArgs& a, const Tuning& tune, hipStream_t s) {
     hipLaunchKernelGGL(kb_dec_tables, dim3(a.count), dim3(256), 0, s, a);
@@ -1039,6 +1459,40 @@ void launch_dec_check(const BlobList& blobs, int first, int count, uint64_t n, i
 
 
 
+template <int T, bool WIDE>
+static void launch_pairs_t(const BlobList& blobs, int first, void* w_ref, uint64_t n, int dtype, Workspace* ws, uint64_t epoch,
+                           HostResult* host, u32 cus, u32 turns, u32 row_bits, hipStream_t s) {
+    static_assert(sizeof(PairsLds<T, WIDE>) <= kLdsPerCu, "a workgroup fits a compute unit");
+    // (two workgroups of up to 4 blobs share a compute unit by their LDS and registers)
+    const u64 need = num_chunks_of(n), cap = (u64)cus * (2 * sizeof(PairsLds<T, WIDE>) + 2 * 1280 <= kLdsPerCu ? 2 : 1);
+    const dim3 grid((u32)(need < cap ? need : cap)), wg(kPairsWaves * kW);
+#define LC_PAIRS(DT) hipLaunchKernelGGL((k_decode_pairs<T, WIDE, DT>), grid, wg, 0, s, blobs, (u32)first, w_ref, (u64)n, ws, (u32)num_chunks_of(n), (u64)epoch, host, turns, row_bits)
+    if (dtype == kBF16) LC_PAIRS(kBF16);
+    else if (dtype == kF16) LC_PAIRS(kF16);
+    else LC_PAIRS(kF32);
+#undef LC_PAIRS
+}
+
+static void launch_pairs(const BlobList& blobs, int first, int count, void* w_ref, uint64_t n, int dtype, Workspace* ws,
+                         uint64_t epoch, HostResult* host, uint32_t row_bits, bool wide, const Tuning& tune,
+                         hipStream_t s) {
+    // A window's turn comes every 4 T / turns rows, with words as of 4 rows before: its strings should take no more than some
+    // 170 (wide: 350) bits in that time.  (the fullest lane: some 15 % more than the average, and half a bit)
+    const double full = 1.15 / 16 * row_bits + 0.5, room = (wide ? 350 : 170) / full / 4 - 1;
+    const u32 turns = count <= room ? 1 : count <= 2 * room || count <= 4 ? 2 : 4, bits16 = (u32)(16 * full);
+#define LC_PAIRS(T, W) launch_pairs_t<T, W>(blobs, first, w_ref, n, dtype, ws, epoch, host, (u32)tune.num_cu, turns, bits16, s)
+    switch (count) {
+        case 2: if (wide) LC_PAIRS(2, true); else LC_PAIRS(2, false); break;
+        case 3: if (wide) LC_PAIRS(3, true); else LC_PAIRS(3, false); break;
+        case 4: if (wide) LC_PAIRS(4, true); else LC_PAIRS(4, false); break;
+        case 5: LC_PAIRS(5, false); break;
+        case 6: LC_PAIRS(6, false); break;
+        case 7: LC_PAIRS(7, false); break;
+        case 8: LC_PAIRS(8, false); break;
+    }
+#undef LC_PAIRS
+}
+
 template <int T, int DT>
 static void launch_fused_td(const BlobList& blobs, int first, void* w_ref, uint64_t n, Workspace* ws, uint64_t epoch,
                             HostResult* host, u32 blocks, u32 pay_words, bool long_codes, hipStream_t s) {
@@ -1059,8 +1513,7 @@ static void launch_fused_t(const BlobList& blobs, int first, void* w_ref, uint64
 }
 
 size_t fused_lds_bytes(int count, uint32_t pay_words) {
-    static const size_t head[kMaxMany] = {sizeof(FusedHead<1>), sizeof(FusedHead<2>), sizeof(FusedHead<3>), sizeof(FusedHead<4>),
-                                          sizeof(FusedHead<5>), sizeof(FusedHead<6>), sizeof(FusedHead<7>), sizeof(FusedHead<8>)};
+    static const size_t head[kMaxFused] = {sizeof(FusedHead<1>), sizeof(FusedHead<2>), sizeof(FusedHead<3>), sizeof(FusedHead<4>)};
     return head[count - 1] + 4 * (size_t)(pay_words + kFusedSlack);
 }
 
@@ -1069,6 +1522,7 @@ void launch_decode_fused(const BlobList& blobs, int first, int count, void* w_re
                          hipStream_t s) {
     const u64 nchunks = num_chunks_of(n);
     if (nchunks == 0) return;
+    if (pay_words & kPairsForm) { launch_pairs(blobs, first, count, w_ref, n, dtype, ws, epoch, host, pay_words & ~kPairsForm, long_codes, tune, s); return; }
     // one wavefront per workgroup; as many workgroups per compute unit as their LDS areas allow
     u64 per_cu = kLdsPerCu / fused_lds_bytes(count, pay_words);
     if (per_cu > (u64)tune.fused_waves_per_cu) per_cu = tune.fused_waves_per_cu;
@@ -1080,11 +1534,7 @@ void launch_decode_fused(const BlobList& blobs, int first, int count, void* w_re
         case 1: launch_fused_t<1>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
         case 2: launch_fused_t<2>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
         case 3: launch_fused_t<3>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
-        case 4: launch_fused_t<4>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
-        case 5: launch_fused_t<5>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
-        case 6: launch_fused_t<6>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
-        case 7: launch_fused_t<7>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
-        default: launch_fused_t<8>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
+        default: launch_fused_t<4>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
     }
 }
 

@@ -44,7 +44,9 @@ struct DecInfo {
     uint32_t rep_hi[kMaxSym];    // binary64 blobs: high halves of the representatives (rep_bits holds the low halves)
 };
 
-constexpr int kMaxMany = 8;  // blobs one fused restore sweep can apply
+constexpr int kMaxMany = 8;  // blobs one restore sweep of several can apply (k_decode_pairs),
+constexpr int kMaxWide = 4;  // ... if one of them keeps more than 7 buckets,
+constexpr int kMaxFused = 4; // ... of the other form (k_decode_fused)
 constexpr int kMaxSets = 64; // blobs one lc_decode_many call accepts (= LC_MAX_MANY), each with a set of its own
 
 // Everything the decode sweep needs to know about one blob, written by k_dec_check.
@@ -79,6 +81,7 @@ struct HostResult {
     unsigned long long dec_status;               // lc_decode*: (epoch << 8) | lc_status of the worst finding
     unsigned long long bytes[kMaxSets];          // lc_decode*: total_bytes of each blob
     uint32_t max_len[kMaxSets];                  // lc_decode*: longest code of each blob
+    uint32_t kept[kMaxSets];                     // ... its kept buckets
 };
 
 // What the encode kernels of one vector share: bucket populations, extremes of the kept buckets, the
@@ -265,9 +268,13 @@ void launch_decode(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, Work
 // met: as launch_encode_one.
 void launch_decode_one(const BlobList& blobs, int count, void* w_ref, uint64_t n, int dtype, uint64_t max_total, Workspace* ws, uint64_t epoch,
                        HostResult* host, uint64_t (&met)[kMeetLines], int looks, hipStream_t s);
-// Both apply blobs.p[first .. first+count), count <= kMaxMany, using dec_set[first ..]; the fused
-// kernel requires every code of these blobs to be at most kDecLut1Bits long.
-// pay_words: LDS words each wavefront gets for the payloads of one chunk of all `count` blobs.
+// Applies blobs.p[first .. first+count), count <= kMaxFused, using dec_set[first ..].
+// pay_words: LDS words each wavefront gets for the payloads of one chunk of all `count` blobs; long_codes: some code is longer
+// than kDecLut1Bits.
+// With pay_words = kPairsForm | bits, by k_decode_pairs: 2 <= count <= kMaxMany (kMaxWide if wide).  bits: 16 times the
+// bits of a lane and row, on average, in the blob of the longest strings; long_codes is then wide: some blob keeps more than 7
+// buckets.
+constexpr uint32_t kPairsForm = 1u << 31;
 void launch_decode_fused(const BlobList& blobs, int first, int count, void* w_ref, uint64_t n, int dtype, Workspace* ws,
                          uint64_t epoch, HostResult* host, uint32_t pay_words, bool long_codes, const Tuning& tune,
                          hipStream_t s);
