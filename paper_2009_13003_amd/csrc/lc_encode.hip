@@ -1140,23 +1140,33 @@ struct PackWg {
 
 // A lane's part while it grows.
 struct LanePart {
-    u64 acc; u32 nb, nw;                 // bits waiting in acc (nb of them), words complete
-    u32* words;                          // this lane's column of PackWg::part
-    __device__ __forceinline__ void start(PackWg& L, u32 v) { acc = 0; nb = 0; nw = 0; words = L.part[v] + lane_id(); }
-    __device__ __forceinline__ void put(u32 word) { if (nw < kPartWords) words[nw * kW] = word; }
+    u32 acc, nb;                         // the last nb < 32 bits of acc wait (what stands above them is of no account)
+    u32 *words, *first;                  // where the next word goes in this lane's column of PackWg::part, and the first one
+    __device__ __forceinline__ void start(PackWg& L, u32 v) { acc = 0; nb = 0; words = first = L.part[v] + lane_id(); }
+    __device__ __forceinline__ void put(u32 word) { if (words < first + kPartWords * kW) *words = word; words += kW; }
+    // len <= 31; what stands above `code` is zero
     __device__ __forceinline__ void append(u32 code, u32 len) {
+        const u32 before = acc, had = nb;
         acc = (acc << len) | code; nb += len;
-        if (nb >= 32) { put((u32)(acc >> (nb - 32))); ++nw; nb -= 32; }
+        if (nb >= 32) { put(__builtin_amdgcn_alignbit(before, code << (32 - len), had)); nb -= 32; }
     }
+    __device__ __forceinline__ u32 bits() const { return 32 * ((u32)(words - first) / kW) + nb; }
 };
 
-// Two rows, their symbols (<< 3) looked up: only the chain that grows the lane's part is serial.
+// Two rows, their symbols (<< 3) looked up: only the chain that grows the lane's part is serial.  Four codes are put together
+// first, as long as they take at most 31 bits in every lane (codes of up to 7 bits always do), and join the part at once.
 __device__ __forceinline__ void code_symbols(const u32 (&t)[8], PackWg& L, LanePart& S) {
     uint2 p[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) p[i] = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(L.pair) + (t[2 * i] * kPairs + t[2 * i + 1]));
+    const u32 len0 = p[0].y + p[1].y, len1 = p[2].y + p[3].y;
+    if (__any(max(len0, len1) > 31)) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) S.append(p[i].x, p[i].y);
+        for (int i = 0; i < 4; ++i) S.append(p[i].x, p[i].y);
+    } else {
+        S.append((p[0].x << p[1].y) | p[1].x, len0);
+        S.append((p[2].x << p[3].y) | p[3].x, len1);
+    }
 }
 
 // Two rows' deltas: the look-ups of the 8 elements are issued together.
@@ -1253,9 +1263,9 @@ struct PartPlaces {
 };
 __device__ __forceinline__ PartPlaces part_places(LanePart& S, u32 v, PackWg& L) {
     const u32 lane = lane_id();
-    if (S.nb > 0) S.put((u32)(S.acc << (32 - S.nb)));
     PartPlaces P;
-    P.mine = 32 * S.nw + S.nb;
+    P.mine = S.bits();
+    if (S.nb > 0) S.put(S.acc << (32 - S.nb));
     L.bits[v][lane] = P.mine;
     if (P.mine > 32 * kPartWords) L.overflow = 1;
     __syncthreads();
@@ -1399,9 +1409,9 @@ __device__ __forceinline__ void pack_chunk_wg(const ChunkRef& ch, const Table& T
 #pragma unroll
         for (u32 h = 0; h < 2; ++h) {
             if (skip[h]) {
-                // the merged code 16 times, as many copies per step as fit 32 bits (a chunk with such a part holds merged
+                // the merged code 16 times, as many copies per step as fit 31 bits (a chunk with such a part holds merged
                 // elements, so their symbol has a code)
-                const u32 cl = L.codelen[K8 >> 3], len = cl & 31, per_step = len ? 32 / len : 1;
+                const u32 cl = L.codelen[K8 >> 3], len = cl & 31, per_step = len ? 31 / len : 1;
                 u32 run = 0;
 #pragma unroll 1
                 for (u32 i = 0; i < per_step; ++i) run = (run << len) | (cl >> 5);
