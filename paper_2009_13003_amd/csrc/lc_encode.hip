@@ -673,7 +673,7 @@ __global__ __launch_bounds__(64) void k_spec_table(EncState* ws, Ext64* ext, con
 }
 
 // ----------------------------------------------------------------------------- sweeps by wavefronts
-// The single sweep of lc_encode_cached, which counts and codes, and the counting sweep of a batched call: one wavefront per
+// The single sweep of lc_encode_cached, which counts and codes (only counts where the cache holds no usable table): one wavefront per
 // chunk, no communication between wavefronts.  Coding, each lane codes its 256 elements into a bit string of its own,
 // written word by word to the chunk's slot in the scratch area (lane-private, word k of lane l at slot[32 + 64 k + l]); the
 // 64 bit lengths go to the head of the slot, their sum to chunk_bits[c].  Where the strings end up in the blob is decided
@@ -711,39 +711,10 @@ struct ChunkRef {
     u64 n;
     u32 c;
     u32* slot; u32* bits_at; u32* group_at;
-    u32 seg;                     // batched calls: which tensor
     bool valid, fast;            // fast: a full chunk of aligned arrays
     bool vec;                    // the arrays are aligned for 4-element accesses (whole rows of a ragged chunk too)
     bool by_parts;               // a chunk of aligned arrays that is mostly merged: coded part by part, and
     u32 parts;                   // which of its whole parts have to be read
-};
-
-// Where the counting sweep of a batched call notes a chunk's largest exponent and those of its 4 KiB parts (one byte
-// each); both null where nobody wants them.  (Not part of ChunkRef: the coding kernels carry that in registers.)
-struct MaximaAt {
-    u32* chunk;
-    uint8_t* parts;
-};
-
-// The counting sweep of a batched call also notes the largest |delta| exponent of every chunk and of each of its 4 KiB
-// parts (one wavefront owns the chunk: plain stores).  From these the chunks that hold merged elements only are told
-// before the coding sweep, and of a mostly merged chunk the parts that have to be read.
-template <int DT>
-struct ChunkMaxima {
-    static constexpr u32 kRowsPerPart = 4096 / (kRowElems * elem_bytes<DT>());      // 4 (4-byte elements) or 8 (2-byte)
-    static constexpr u32 kParts = kR / kRowsPerPart;
-    u32 umax = 0, part_max = 0;               // the chunk's largest |delta| pattern (per lane); lane p: exponent of part p
-    // `gm`: this lane's largest pattern among the 4 rows that start at row r0
-    __device__ __forceinline__ void group(u32 gm, u32 r0) {
-        umax = max(umax, gm);
-        const u32 pm = wave_max_u32(gm) >> 23;
-        if (lane_id() == r0 / kRowsPerPart) part_max = max(part_max, pm);
-    }
-    __device__ __forceinline__ void note(const MaximaAt& at) {
-        const u32 m = wave_max_u32(umax);
-        if (lane_id() == 0) *at.chunk = m >> 23;
-        if (lane_id() < kParts) at.parts[lane_id()] = (uint8_t)part_max;
-    }
 };
 
 // In chunk_bits beside a chunk's payload bits (at most 16384 * 15).  kMergedChunk: a full chunk whose largest exponent (sweep
@@ -771,7 +742,7 @@ __device__ __forceinline__ void finish_lane_sizes(const ChunkRef& ch, u32 nb, u3
 constexpr int kPlainRows = 4;
 
 template <bool PACK, int DT>
-__device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds& L, const MaximaAt at = MaximaAt{nullptr, nullptr}) {
+__device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds& L) {
     const u32 lane = lane_id();
     const void* __restrict__ w = ch.w; const void* __restrict__ w_ref = ch.w_ref;
     const u64 n = ch.n, base = (u64)ch.c * kChunk;
@@ -779,8 +750,6 @@ __device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds& L, con
     const u32 mm = lane & (kMmCopies - 1);
     u64 acc = 0;
     u32 nb = 0, nw = 0;
-    ChunkMaxima<DT> cm;                       // counting only
-    u32 gmax = 0;                             // ... this lane's largest |delta| pattern since it was last handed to cm
     auto code_row = [&](auto whole, u64 idx, const float (&xa)[4], const float (&xb)[4]) {
         constexpr bool WHOLE = decltype(whole)::value;
 #pragma unroll
@@ -788,7 +757,6 @@ __device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds& L, con
             if (WHOLE || idx + v < n) {
                 const u32 u = delta_bits(xa[v], xb[v]);
                 atomicAdd(&L.hist[hist_slot(u >> 23, lane & (kSpecCopies - 1))], 1u);
-                if (!PACK) gmax = max(gmax, u & 0x7FFFFFFFu);
                 if (!PACK) continue;
                 const u32 sy = L.sym8[u >> 23] >> 3;
                 const u32 cl = L.codelen[sy];
@@ -819,7 +787,6 @@ __device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds& L, con
         auto code = [&](const float (&a)[kPlainRows][4], const float (&b)[kPlainRows][4], u32 r0) {
 #pragma unroll
             for (int k = 0; k < kPlainRows; ++k) code_row(yes(), row_at_(r0 + k), a[k], b[k]);
-            if (!PACK && at.chunk) { cm.group(gmax, r0); gmax = 0; }
         };
         fetch(xa, xb, 0);
         for (; r < whole_rows; r += 2 * kPlainRows) {
@@ -838,7 +805,6 @@ __device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds& L, con
 #pragma unroll
         for (int k = 0; k < kPlainRows; ++k) code_row(no(), row_at_(r + k), xa[k], xb[k]);
     }
-    if (!PACK && at.chunk) { cm.umax = max(cm.umax, gmax); cm.note(at); }     // (rows behind the last whole part: the chunk's maximum only)
     if (!PACK) return;
     if (nb > 0) slot[kLaneBitsWords + nw * kW + lane] = (u32)(acc << (32 - nb));
     finish_lane_sizes(ch, nb, nw);
@@ -848,7 +814,6 @@ __device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds& L, con
 __device__ __forceinline__ u64 row_at(u32 c, u32 r) { return (u64)c * kChunk + (u64)(r * kW + lane_id()) * kV; }
 
 constexpr int kPackPF = 8;          // rows per prefetch batch of the coding loop
-
 
 // `rot`: the row a wavefront starts a chunk with (a multiple of kPackPF; rows wrap around).  Coding has to take the
 // rows in order (0); counting does not, and wavefronts that start their chunks together on the same row keep asking the
@@ -866,8 +831,7 @@ __device__ __forceinline__ void fetch_first_batch(const ChunkRef& ch, typename R
 template <bool ROWCHK, bool PACK, int DT>
 __device__ __forceinline__ void pack_chunk_fast(const ChunkRef& cur, const ChunkRef& next,
                                                 typename Raw<DT>::type (&A0)[kPackPF], typename Raw<DT>::type (&B0)[kPackPF],
-                                                u32 K8, PackLds& L, const MaximaAt at = MaximaAt{nullptr, nullptr},
-                                                u32 rot = 0) {
+                                                u32 K8, PackLds& L, u32 rot = 0) {
     constexpr int PF = kPackPF;
     static_assert((kR & (kR - 1)) == 0 && kR % (2 * kPackPF) == 0, "rows wrap with a mask");
     typedef typename Raw<DT>::type raw_t;
@@ -880,7 +844,6 @@ __device__ __forceinline__ void pack_chunk_fast(const ChunkRef& cur, const Chunk
     u32* lane_words = cur.slot + kLaneBitsWords + lane;
     u64 acc = 0;
     u32 nb = 0, nw = 0;                       // bits waiting in acc, words written
-    ChunkMaxima<DT> cm;                       // counting only
     // Lanes fill their words at different times; gathering them in LDS and storing whole rows at
     // the end of the chunk turns many partial-line stores into a few full ones.
     auto flush = [&]() {
@@ -894,7 +857,7 @@ __device__ __forceinline__ void pack_chunk_fast(const ChunkRef& cur, const Chunk
     // Four rows at a time: all table look-ups of the 16 elements are issued together, so the
     // LDS latency is paid twice per group instead of three times per row; only the shift/or
     // chain that grows the lane's bit string is serial.
-    auto group = [&](const raw_t* a, const raw_t* b, u32 r0) {
+    auto group = [&](const raw_t* a, const raw_t* b) {
         u32 u[16], t[16];
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
@@ -905,12 +868,6 @@ __device__ __forceinline__ void pack_chunk_fast(const ChunkRef& cur, const Chunk
         }
 #pragma unroll
         for (int i = 0; i < 16; ++i) atomicAdd(&L.hist[hist_slot(u[i] >> 23, lane & (kSpecCopies - 1))], 1u);
-        if (!PACK && at.chunk) {
-            u32 gm = 0;
-#pragma unroll
-            for (int i = 0; i < 16; ++i) gm = max(gm, u[i] & 0x7FFFFFFFu);
-            cm.group(gm, r0);
-        }
         if (!PACK) return;
 #pragma unroll
         for (int i = 0; i < 16; ++i) t[i] = L.sym8[u[i] >> 23];
@@ -941,16 +898,15 @@ __device__ __forceinline__ void pack_chunk_fast(const ChunkRef& cur, const Chunk
     for (u32 r0 = 0; r0 < kR; r0 += 2 * PF) {
 #pragma unroll
         for (int k = 0; k < PF; ++k) { A1[k] = load_raw<DT>(w, row_at(c, row(r0 + PF) + k)); B1[k] = load_raw<DT>(w_ref, row_at(c, row(r0 + PF) + k)); }
-        group(A0, B0, row(r0)); group(A0 + 4, B0 + 4, row(r0) + 4);
+        group(A0, B0); group(A0 + 4, B0 + 4);
         if (r0 + 2 * PF < kR) {
 #pragma unroll
             for (int k = 0; k < PF; ++k) { A0[k] = load_raw<DT>(w, row_at(c, row(r0 + 2 * PF) + k)); B0[k] = load_raw<DT>(w_ref, row_at(c, row(r0 + 2 * PF) + k)); }
         } else if (next_fast) {
             fetch_first_batch<DT>(next, A0, B0, !PACK ? rot : 0u);
         }
-        group(A1, B1, row(r0 + PF)); group(A1 + 4, B1 + 4, row(r0 + PF) + 4);
+        group(A1, B1); group(A1 + 4, B1 + 4);
     }
-    if (!PACK && at.chunk) cm.note(at);
     if (!PACK) return;
     // the last, partly filled word, then rows 0 .. (most words of any lane) - 1, four rows per store
     if (nb > 0) {
@@ -970,7 +926,7 @@ __device__ __forceinline__ void pack_chunk_fast(const ChunkRef& cur, const Chunk
 }
 
 // The loop of one wavefront over the chunks its source hands out.  Src::take() is the wavefront's next chunk,
-// Src::enter(chunk, L) runs before each (a batched call switches tensors there), Src::K8() is symbol K << 3 of the table.
+// Src::K8() is symbol K << 3 of the table.
 // ROWSEL: 1 = a lane's 64-bit accumulator can take a whole row (31 waiting bits + 4 codes of <= 8 bits) between flushes.
 template <bool PACK, int DT, int ROWSEL, typename Src>
 __device__ __forceinline__ void pack_loop(Src& src, PackLds& L) {
@@ -988,16 +944,14 @@ __device__ __forceinline__ void pack_loop(Src& src, PackLds& L) {
     if (cur.valid && cur.fast) fetch_first_batch<DT>(cur, A0, B0, rot);
     while (cur.valid) {
         const ChunkRef next = src.take();
-        src.enter(cur, L);
         if constexpr (!PACK) {
             // counting only
-            const MaximaAt at = src.maxima_at(cur);
             if (!cur.fast) {
-                pack_chunk_plain<PACK, DT>(cur, L, at);
+                pack_chunk_plain<PACK, DT>(cur, L);
                 forget();
                 if (next.valid && next.fast) fetch_first_batch<DT>(next, A0, B0, rot);
             } else {
-                pack_chunk_fast<true, PACK, DT>(cur, next, A0, B0, src.K8(), L, at, rot);
+                pack_chunk_fast<true, PACK, DT>(cur, next, A0, B0, src.K8(), L, rot);
             }
         } else if (!cur.fast) {
             pack_chunk_plain<PACK, DT>(cur, L);
@@ -1050,7 +1004,6 @@ struct VectorChunks {
         ch.slot = prov + (u64)c * slot_words;
         ch.bits_at = chunk_bits + c;
         ch.group_at = group_words + (c >> 6);
-        ch.seg = 0;
         ch.parts = 0; ch.by_parts = false;
         if (valid && aligned && batch_max) {
             const u64 inside = n - (u64)c * kChunk, part_elems = kChunk / parts_per_chunk;
@@ -1065,8 +1018,6 @@ struct VectorChunks {
         if (!chunk_list) return ref(i, i < nchunks);
         return i < listed ? ref(load_uniform(chunk_list + i), true) : ref(nchunks, false);
     }
-    __device__ __forceinline__ void enter(const ChunkRef&, PackLds&) const {}
-    __device__ __forceinline__ MaximaAt maxima_at(const ChunkRef&) const { return MaximaAt{nullptr, nullptr}; }
     __device__ __forceinline__ u32 K8() const { return k8; }
 };
 
@@ -2248,8 +2199,7 @@ __global__ __launch_bounds__(kWgThreads, 4) void k_encode_one(OneArgs a) {
 
 // ----------------------------------------------------------------------------- batched encode
 // lc_encode_batch: many vectors, one table each, in five launches, six where the chunks to read are listed.  The chunks of all
-// tensors are numbered through.  The counting sweep deals them round-robin to its wavefronts, and one that moves on to a chunk
-// of another tensor hands in the last one's counts; the coding sweep is a workgroup per chunk, as for one vector.
+// tensors are numbered through; the counting and the coding sweep are a workgroup per chunk.
 // One workgroup per tensor: what the host says about it (read from mapped host memory, kept for the kernels behind this one: a
 // copy of the list to the device ahead of the call took longer than that read: 161 tensors 129 -> 125 us), which chunks are
 // its own, its groups and its state cleared.
@@ -2270,57 +2220,83 @@ __global__ __launch_bounds__(256) void kb_setup(BatchArgs a) {
     for (u32 g = t; g < (sg.nchunks + 63) / 64; g += 256) a.group_words[sg.group0 + g] = 0;
 }
 
-// The dense chunks of a batched call as a chunk source for the counting loop.
-struct BatchChunks {
-    BatchArgs a;
-    u32 active;                  // tensor whose counts the LDS holds (0xFFFFFFFF: none yet)
-    u32 pos;
-    __device__ __forceinline__ ChunkRef take() {
-        ChunkRef ch;
-        const u32 g = blockIdx.x + (pos++) * gridDim.x;
-        ch.valid = g < a.total_chunks;
-        ch.seg = 0; ch.c = 0; ch.w = nullptr; ch.w_ref = nullptr; ch.n = 0; ch.fast = false; ch.vec = false;
-        ch.slot = nullptr; ch.bits_at = nullptr; ch.group_at = nullptr;
-        if (ch.valid) {
-            ch.seg = __builtin_amdgcn_readfirstlane(a.seg_of_chunk[g]);
-            const Seg& sg = a.segs[ch.seg];
-            ch.c = g - sg.chunk0;
-            ch.w = sg.w; ch.w_ref = sg.w_ref; ch.n = sg.n;
-            ch.fast = sg.aligned && (u64)(ch.c + 1) * kChunk <= sg.n;
-            ch.vec = sg.aligned != 0;
+// The counting sweep of a batched call: a workgroup of 8 wavefronts per chunk, whose loads are all on their way at once, or
+// (STAY) per `run` chunks in a row, whose counts it hands in together where they are one tensor's.  Arrays off alignment take the
+// same loads.  Against a wavefront per chunk, whole calls (with the two codes per append of then), us: 161 tensors of 25.6 M fp32
+// 117 -> 113, 32 of 138 M 268 -> 249, 60 of 2^25 bf16 130 -> 105, off alignment fp32 200 -> 160, bf16 353 -> 152.
+// It also notes the largest |delta| exponent of every chunk and of each of its 4 KiB parts: from these the chunks that hold
+// merged elements only are told before the coding sweep, and of a mostly merged chunk the parts that have to be read.
+template <int DT, bool STAY>
+__global__ __launch_bounds__(kWgThreads, 4) void kb_hist(BatchArgs a, u32 run) {
+    typedef typename Raw<DT>::type raw_t;
+    constexpr u32 kCopies = 16, kPartRows = 4096 / (kRowElems * elem_bytes<DT>());      // 4 rows per 4 KiB part, or 8
+    __shared__ alignas(16) u32 hist[512 * kCopies];
+    __shared__ u32 s_largest[kWgWaves];
+    const u32 t = threadIdx.x, lane = lane_id(), v = __builtin_amdgcn_readfirstlane(t >> 6), first_row = kWgRows * v;
+    const u32 first = blockIdx.x * (STAY ? run : 1u), end = STAY ? min(first + run, a.total_chunks) : first + 1;
+    for (u32 i = t; i < 512 * kCopies / 4; i += kWgThreads) reinterpret_cast<u32x4*>(hist)[i] = u32x4{0, 0, 0, 0};
+    u32 sidx = load_uniform(a.seg_of_chunk + first);
+#pragma unroll 1
+    for (u32 g = first; g < end; ++g) {
+        const u32 next = g + 1 < end ? load_uniform(a.seg_of_chunk + g + 1) : 0xFFFFFFFFu;
+        const Seg& sg = a.segs[sidx];
+        const u64 n = sg.n;
+        const u32 c = g - sg.chunk0;
+        const bool full = (u64)(c + 1) * kChunk <= n;
+        raw_t A[kWgRows], B[kWgRows];
+        if (full) {
+#pragma unroll
+            for (u32 k = 0; k < kWgRows; ++k) { A[k] = load_raw_any<DT>(sg.w, row_at(c, first_row + k)); B[k] = load_raw_any<DT>(sg.w_ref, row_at(c, first_row + k)); }
+        } else {
+#pragma unroll
+            for (u32 k = 0; k < kWgRows; ++k) {
+                const u64 i = row_at(c, first_row + k);
+                const bool whole = i - lane * kV + kRowElems <= n;              // (the same in every lane)
+                A[k] = whole ? load_raw_any<DT>(sg.w, i) : load_raw_guarded<DT>(sg.w, i, n);
+                B[k] = whole ? load_raw_any<DT>(sg.w_ref, i) : load_raw_guarded<DT>(sg.w_ref, i, n);
+            }
         }
-        return ch;
-    }
-    __device__ __forceinline__ void hand_in(PackLds& L) {
-        if (active == 0xFFFFFFFFu) return;
-        EncState* st = &a.states[active];
-        for (u32 b = lane_id(); b < 512; b += kW) {
+        __syncthreads();                             // (the counts are cleared, the last chunk's maxima read)
+        u32 largest = 0;
+#pragma unroll
+        for (u32 part = 0; part < kWgRows / kPartRows; ++part) {
+            u32 most = 0;
+#pragma unroll
+            for (u32 k = part * kPartRows; k < (part + 1) * kPartRows; ++k) {
+                float xa[4], xb[4];
+                unpack<DT>(A[k], xa); unpack<DT>(B[k], xb);
+#pragma unroll
+                for (u32 e = 0; e < kV; ++e) {
+                    const u32 u = delta_bits(xa[e], xb[e]);
+                    if (full || row_at(c, first_row + k) + e < n) {
+                        atomicAdd(&hist[(u >> 23) * kCopies + (lane & (kCopies - 1))], 1u);
+                        most = max(most, u & 0x7FFFFFFFu);
+                    }
+                }
+            }
+            most = wave_max_u32(most) >> 23;
+            if (lane == 0) a.part_max[(u64)g * kPartBytes + first_row / kPartRows + part] = (uint8_t)most;
+            largest = max(largest, most);
+        }
+        if (lane == 0) s_largest[v] = largest;
+        __syncthreads();
+        if (t == 0) {
+#pragma unroll
+            for (u32 k = 0; k < kWgWaves; ++k) largest = max(largest, s_largest[k]);
+            a.chunk_maxexp[g] = largest;
+        }
+        if (next != sidx) {
             u32 sum = 0;
 #pragma unroll
-            for (int k = 0; k < kSpecCopies; ++k) { sum += L.hist[hist_slot(b, k)]; L.hist[hist_slot(b, k)] = 0; }
-            if (sum) atomicAdd(&st->hist[b], (u64)sum);
+            for (u32 k = 0; k < kCopies / 4; ++k) {
+                u32x4* x = reinterpret_cast<u32x4*>(hist) + t * (kCopies / 4) + k;
+                sum += x->x + x->y + x->z + x->w;
+                if (STAY) *x = u32x4{0, 0, 0, 0};
+            }
+            if (sum) atomicAdd(&a.states[sidx].hist[t], (u64)sum);
         }
+        sidx = next;
     }
-    __device__ __forceinline__ void enter(const ChunkRef& ch, PackLds& L) {
-        if (ch.seg == active) return;
-        hand_in(L);
-        active = ch.seg;
-    }
-    __device__ __forceinline__ MaximaAt maxima_at(const ChunkRef& ch) const {
-        const u32 g = load_uniform(&a.segs[ch.seg].chunk0) + ch.c;
-        return MaximaAt{a.chunk_maxexp + g, a.part_max + (u64)g * kPartBytes};
-    }
-    __device__ __forceinline__ u32 K8() const { return 0; }
-};
-
-template <int DT>
-__global__ __launch_bounds__(64) void kb_hist(BatchArgs a) {
-    __shared__ PackLds L;
-    for (u32 i = threadIdx.x; i < 512 * kSpecCopies; i += 64) L.hist[i] = 0;
-    __syncthreads();
-    BatchChunks src = {a, 0xFFFFFFFFu, 0};
-    pack_loop<false, DT, 1>(src, L);
-    src.hand_in(L);
 }
 
 __global__ __launch_bounds__(table_threads<8>()) void kb_table(BatchArgs a) {
@@ -2564,13 +2540,18 @@ void launch_batch_encode(const BatchArgs& args, const Tuning& tune, hipStream_t 
     a.listed = needs_list(a.total_chunks, tune.batch_unlisted_per_cu, tune) ? 1 : 0;
     hipLaunchKernelGGL(kb_setup, dim3(a.count), dim3(256), 0, s, a);
     if (a.total_chunks) {
-        // (a counting workgroup needs 19 KB of LDS: 8 fit a compute unit, and a grid of more leaves the last ones a
-        // round of their own: 0.20 ms instead of 0.18 on VGG-16's 32 tensors)
-        const int per_cu = tune.batch_waves_per_cu < 8 ? tune.batch_waves_per_cu : 8;
-        const u32 waves = even_waves(a.total_chunks, (u64)tune.num_cu * per_cu);
-        if (a.dtype == kBF16) hipLaunchKernelGGL(kb_hist<kBF16>, dim3(waves), dim3(64), 0, s, a);
-        else if (a.dtype == kF16) hipLaunchKernelGGL(kb_hist<kF16>, dim3(waves), dim3(64), 0, s, a);
-        else hipLaunchKernelGGL(kb_hist<kF32>, dim3(waves), dim3(64), 0, s, a);
+        // A workgroup per chunk as the dispatcher hands them out, or two per compute unit that stay: a tensor's workgroups hand in
+        // some 40 counts each to the same few lines of memory, and few streams of long bursts read faster.  Whole calls, us, per
+        // chunk / staying: fp32 2^24.6 115 / 117, 2^25 131 / 137, 2^26 233 / 215, 138 M 284 / 249, 2^27 471 / 435; bf16 2^25 105 /
+        // 115, 2^26 158 / 165, 2^27 270 / 258.  (1, 3 and 4 per unit 458, 467, 443 for the last fp32 one)
+        const bool stay = a.total_chunks >= (u32)tune.num_cu * (a.dtype == kF32 ? 12u : 24u);
+        const u32 most = 2 * (u32)tune.num_cu, run = stay ? (a.total_chunks + most - 1) / most : 1;
+        const dim3 grid((a.total_chunks + run - 1) / run), wg(kWgThreads);
+#define LC_HIST(DT) do { if (stay) hipLaunchKernelGGL((kb_hist<DT, true>), grid, wg, 0, s, a, run); else hipLaunchKernelGGL((kb_hist<DT, false>), grid, wg, 0, s, a, run); } while (0)
+        if (a.dtype == kBF16) LC_HIST(kBF16);
+        else if (a.dtype == kF16) LC_HIST(kF16);
+        else LC_HIST(kF32);
+#undef LC_HIST
     }
     hipLaunchKernelGGL(kb_table, dim3(a.count), dim3(table_threads<8>()), 0, s, a);
     if (a.total_chunks) {

@@ -169,7 +169,6 @@ struct Tuning {
     int one_wait = 256;                // how often its workgroups look for each other before they give up (-1: they never meet)
     int one_rest = 16;                 // calls that do not try it behind one that was given up, and then twice as many (0: all try)
     int spec_waves_per_cu = 8;         // of the single sweep of the cached encode (what its LDS and registers allow)
-    int batch_waves_per_cu = 8;        // of the batch kernels
     int decode_blocks_per_cu = 9;      // ... of a long restore (LDS lets 2 run at once; more, smaller shares even out unlike chunks)
     int fused_waves_per_cu = 16;       // most wavefronts per compute unit
     int fused_min_waves_per_cu = 8;    // a sweep takes as many blobs as still leave LDS for this many
