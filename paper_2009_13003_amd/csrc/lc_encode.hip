@@ -84,18 +84,13 @@ __device__ __forceinline__ void unpack_unit(const float4& t, float (&x)[EPU]) {
     }
 }
 
-template <bool ALIGNED, int DT, int EPU>
+// 16 bytes of either array, which may be aligned to its elements only: the hardware takes vectors at any address.  Off alignment,
+// against 16 bytes put together from single elements in this sweep alone (laplace but for the heavy-tailed ones): fp32 2^24 78 -> 73
+// us the call, 2^26 heavy-tailed 125 -> 112, 2^26 bf16 155 -> 153; aligned arrays the same to 1 %.
+typedef f32x4 __attribute__((aligned(2))) f32x4_anywhere;
 __device__ __forceinline__ float4 load_unit(const void* __restrict__ p, u64 unit) {
-    if (ALIGNED) return load_stream(reinterpret_cast<const float4*>(p) + unit);
-    // whole units only, so every element is in range; assemble the same 16 bytes from element loads
-    if constexpr (DT == kF32) {
-        const float* q = static_cast<const float*>(p) + unit * 4;
-        return make_float4(q[0], q[1], q[2], q[3]);
-    } else {
-        const uint16_t* q = static_cast<const uint16_t*>(p) + unit * 8;
-        return make_float4(__uint_as_float(q[0] | ((u32)q[1] << 16)), __uint_as_float(q[2] | ((u32)q[3] << 16)),
-                           __uint_as_float(q[4] | ((u32)q[5] << 16)), __uint_as_float(q[6] | ((u32)q[7] << 16)));
-    }
+    const f32x4 v = __builtin_nontemporal_load(static_cast<const f32x4_anywhere*>(p) + unit);
+    return make_float4(v.x, v.y, v.z, v.w);
 }
 
 // Largest magnitude among the EPU deltas of one unit and m (its exponent field is the largest biased exponent).
@@ -119,13 +114,13 @@ __device__ __forceinline__ float max_magnitude(const u32 (&u)[EPU], float m) {
 // exponent bytes and the 16 sign bits of the 16 elements a lane holds of a batch, which are the lane's own elements of
 // 4 rows of the coding sweep's chunk -- and, being then the only sweep that sees the mantissas, tracks the smallest and
 // largest delta bit pattern of every bucket (Section 3.1.1: the representative is the mean of these two).
-template <bool ALIGNED, int DT, bool KEYS = false>
+template <int DT, bool KEYS = false>
 __global__ __launch_bounds__(1024) void k_hist(const void* __restrict__ w, const void* __restrict__ w_ref,
                                                u64 n, Workspace* ws, u32* chunk_maxexp, uint8_t* batch_max, KeyPlanes keys) {
     __shared__ u32 h[512 * kHistCopies];
     __shared__ u32 mn[KEYS ? 512 * kHistCopies : 1], mx[KEYS ? 512 * kHistCopies : 1];
     __shared__ uint16_t pend[1024 / kW][kW];         // per wavefront: the maxima of its batches not yet written out
-    static_assert(!KEYS || (ALIGNED && DT == kF32), "keys are staged for aligned binary32 arrays only");
+    static_assert(!KEYS || DT == kF32, "keys are staged for binary32 arrays only");
     constexpr int EPU = 16 / (int)elem_bytes<DT>();
     const u32 tid = threadIdx.x, nthr = blockDim.x;
     for (u32 i = tid; i < 512 * kHistCopies; i += nthr) { h[i] = 0; if (KEYS) { mn[i] = 0xFFFFFFFFu; mx[i] = 0; } }
@@ -143,7 +138,7 @@ __global__ __launch_bounds__(1024) void k_hist(const void* __restrict__ w, const
     auto fetch = [&](float4 (&a)[PF], float4 (&bb)[PF], u64 batch) {
         const u64 at = batch * kBatchUnits + (tid & (kW - 1));
 #pragma unroll
-        for (int k = 0; k < PF; ++k) { a[k] = load_unit<ALIGNED, DT, EPU>(w, at + k * kW); bb[k] = load_unit<ALIGNED, DT, EPU>(w_ref, at + k * kW); }
+        for (int k = 0; k < PF; ++k) { a[k] = load_unit(w, at + k * kW); bb[k] = load_unit(w_ref, at + k * kW); }
     };
     u32 pending = 0;                                 // maxima waiting in pend, those of batches pend_first, + stride, ...
     u64 pend_first = b;
@@ -215,7 +210,7 @@ __global__ __launch_bounds__(1024) void k_hist(const void* __restrict__ w, const
     // what is left of the vector: fewer than one batch of units, then fewer than one unit of elements
     if (blockIdx.x == 0) {
         for (u64 u = nbatch * kBatchUnits + tid; u < nu; u += nthr) {
-            const float mf = count_unit(load_unit<ALIGNED, DT, EPU>(w, u), load_unit<ALIGNED, DT, EPU>(w_ref, u), 0.f);
+            const float mf = count_unit(load_unit(w, u), load_unit(w_ref, u), 0.f);
             atomicMax(&chunk_maxexp[maxexp_slot((u32)((u * EPU) / kChunk))], __float_as_uint(mf) >> 23);
         }
         if (tid < (u32)(n - EPU * nu)) {
@@ -246,16 +241,6 @@ __global__ __launch_bounds__(1024) void k_hist(const void* __restrict__ w, const
 // counts and chunk maxima of the binary64 delta.
 constexpr int kHistCopies64 = 2;
 
-template <bool ALIGNED>
-__device__ __forceinline__ float4 load_unit64(const void* __restrict__ p, u64 unit) {
-    if (ALIGNED) return load_stream(reinterpret_cast<const float4*>(p) + unit);
-    const double* q = static_cast<const double*>(p) + unit * 2;
-    const double a = q[0], b = q[1];
-    return make_float4(__int_as_float(__double2loint(a)), __int_as_float(__double2hiint(a)),
-                       __int_as_float(__double2loint(b)), __int_as_float(__double2hiint(b)));
-}
-
-template <bool ALIGNED>
 __global__ __launch_bounds__(1024) void k_hist64(const void* __restrict__ w, const void* __restrict__ w_ref,
                                                  u64 n, Ext64* ext, u32* chunk_maxexp, uint16_t* part_max) {
     __shared__ u32 h[kBuckets64 * kHistCopies64];
@@ -276,7 +261,7 @@ __global__ __launch_bounds__(1024) void k_hist64(const void* __restrict__ w, con
     auto fetch = [&](float4 (&a)[PF], float4 (&bb)[PF], u64 batch) {
         const u64 at = batch * kBatchUnits + (tid & (kW - 1));
 #pragma unroll
-        for (int k = 0; k < PF; ++k) { a[k] = load_unit64<ALIGNED>(w, at + k * kW); bb[k] = load_unit64<ALIGNED>(w_ref, at + k * kW); }
+        for (int k = 0; k < PF; ++k) { a[k] = load_unit(w, at + k * kW); bb[k] = load_unit(w_ref, at + k * kW); }
     };
     u32 pending = 0;
     u64 pend_first = b;
@@ -329,7 +314,7 @@ __global__ __launch_bounds__(1024) void k_hist64(const void* __restrict__ w, con
     }
     if (blockIdx.x == 0) {
         for (u64 u = nbatch * kBatchUnits + tid; u < nu; u += nthr) {
-            const u32 m = count_unit(load_unit64<ALIGNED>(w, u), load_unit64<ALIGNED>(w_ref, u), 0);
+            const u32 m = count_unit(load_unit(w, u), load_unit(w_ref, u), 0);
             atomicMax(&chunk_maxexp[maxexp_slot((u32)((u * EPU) / kChunk))], m);
         }
         if (tid < (u32)(n - EPU * nu)) {
@@ -677,9 +662,10 @@ __global__ __launch_bounds__(64) void k_spec_table(EncState* ws, Ext64* ext, con
 // chunk, no communication between wavefronts.  Coding, each lane codes its 256 elements into a bit string of its own,
 // written word by word to the chunk's slot in the scratch area (lane-private, word k of lane l at slot[32 + 64 k + l]); the
 // 64 bit lengths go to the head of the slot, their sum to chunk_bits[c].  Where the strings end up in the blob is decided
-// afterwards by k_place, which knows all sizes.  A full, 16-byte aligned chunk takes the fast path: rows are fetched eight
+// afterwards by k_place, which knows all sizes.  A full chunk takes the fast path, off alignment too (2^25 fp32 laplace elements
+// off alignment 150 us the call by element loads, 95 so, as aligned; bf16 200 -> 89): rows are fetched eight
 // at a time, one batch ahead (and the next chunk's first batch before the current one ends), the table look-ups of 16
-// elements are issued together and two symbols are coded per look-up.  Ragged or unaligned chunks take a plain path.  The
+// elements are issued together and two symbols are coded per look-up.  A ragged chunk takes a plain path.  The
 // mantissa extremes of the kept buckets (Section 3.1.1: the representative is the mean of the bucket's largest and smallest
 // member) are tracked on the way.
 constexpr int kMmCopies = 32;       // LDS copies of the per-symbol extremes, one per lane of a half wave
@@ -711,9 +697,8 @@ struct ChunkRef {
     u64 n;
     u32 c;
     u32* slot; u32* bits_at; u32* group_at;
-    bool valid, fast;            // fast: a full chunk of aligned arrays
-    bool vec;                    // the arrays are aligned for 4-element accesses (whole rows of a ragged chunk too)
-    bool by_parts;               // a chunk of aligned arrays that is mostly merged: coded part by part, and
+    bool valid, fast;            // fast: a full chunk
+    bool by_parts;               // a chunk that is mostly merged: coded part by part, and
     u32 parts;                   // which of its whole parts have to be read
 };
 
@@ -737,7 +722,7 @@ __device__ __forceinline__ void finish_lane_sizes(const ChunkRef& ch, u32 nb, u3
 }
 
 // Any size, any alignment, one symbol per look-up.  The vector's ragged last chunk is one wavefront's work from
-// start to end, so its memory round trips count: the rows that lie wholly inside an aligned vector are fetched as
+// start to end, so its memory round trips count: the rows that lie wholly inside the vector are fetched as
 // in a full chunk, four at a time and one batch ahead; what is left takes guarded element loads.
 constexpr int kPlainRows = 4;
 
@@ -774,15 +759,15 @@ __device__ __noinline__ void pack_chunk_plain(const ChunkRef ch, PackLds& L) {
     typedef std::integral_constant<bool, true> yes;
     typedef std::integral_constant<bool, false> no;
     auto row_at_ = [&](u32 r) { return base + (u64)r * kRowElems + lane * kV; };
-    // whole rows of an aligned vector, in batches of kPlainRows
+    // whole rows, in batches of kPlainRows
     u32 r = 0;
     const u64 inside = n > base ? n - base : 0;
-    const u32 whole_rows = ch.vec ? (u32)min((u64)kR, inside / kRowElems) / kPlainRows * kPlainRows : 0u;
+    const u32 whole_rows = (u32)min((u64)kR, inside / kRowElems) / kPlainRows * kPlainRows;
     if (whole_rows) {
         float xa[kPlainRows][4], xb[kPlainRows][4], ya[kPlainRows][4], yb[kPlainRows][4];
         auto fetch = [&](float (&a)[kPlainRows][4], float (&b)[kPlainRows][4], u32 r0) {
 #pragma unroll
-            for (int k = 0; k < kPlainRows; ++k) { load_row<true, DT>(w, row_at_(r0 + k), n, a[k]); load_row<true, DT>(w_ref, row_at_(r0 + k), n, b[k]); }
+            for (int k = 0; k < kPlainRows; ++k) { load_row_any<DT>(w, row_at_(r0 + k), a[k]); load_row_any<DT>(w_ref, row_at_(r0 + k), b[k]); }
         };
         auto code = [&](const float (&a)[kPlainRows][4], const float (&b)[kPlainRows][4], u32 r0) {
 #pragma unroll
@@ -823,10 +808,10 @@ template <int DT>
 __device__ __forceinline__ void fetch_first_batch(const ChunkRef& ch, typename Raw<DT>::type (&A)[kPackPF],
                                                   typename Raw<DT>::type (&B)[kPackPF], u32 rot = 0) {
 #pragma unroll
-    for (int k = 0; k < kPackPF; ++k) { A[k] = load_raw<DT>(ch.w, row_at(ch.c, rot + k)); B[k] = load_raw<DT>(ch.w_ref, row_at(ch.c, rot + k)); }
+    for (int k = 0; k < kPackPF; ++k) { A[k] = load_raw_any<DT>(ch.w, row_at(ch.c, rot + k)); B[k] = load_raw_any<DT>(ch.w_ref, row_at(ch.c, rot + k)); }
 }
 
-// A full, aligned chunk whose first batch of rows is already in A0/B0; leaves the first batch of `next`
+// A full chunk whose first batch of rows is already in A0/B0; leaves the first batch of `next`
 // there if that chunk takes this path too.
 template <bool ROWCHK, bool PACK, int DT>
 __device__ __forceinline__ void pack_chunk_fast(const ChunkRef& cur, const ChunkRef& next,
@@ -897,11 +882,11 @@ __device__ __forceinline__ void pack_chunk_fast(const ChunkRef& cur, const Chunk
     auto row = [&](u32 r) { return !PACK ? ((r + rot) & (kR - 1)) : r; };
     for (u32 r0 = 0; r0 < kR; r0 += 2 * PF) {
 #pragma unroll
-        for (int k = 0; k < PF; ++k) { A1[k] = load_raw<DT>(w, row_at(c, row(r0 + PF) + k)); B1[k] = load_raw<DT>(w_ref, row_at(c, row(r0 + PF) + k)); }
+        for (int k = 0; k < PF; ++k) { A1[k] = load_raw_any<DT>(w, row_at(c, row(r0 + PF) + k)); B1[k] = load_raw_any<DT>(w_ref, row_at(c, row(r0 + PF) + k)); }
         group(A0, B0); group(A0 + 4, B0 + 4);
         if (r0 + 2 * PF < kR) {
 #pragma unroll
-            for (int k = 0; k < PF; ++k) { A0[k] = load_raw<DT>(w, row_at(c, row(r0 + 2 * PF) + k)); B0[k] = load_raw<DT>(w_ref, row_at(c, row(r0 + 2 * PF) + k)); }
+            for (int k = 0; k < PF; ++k) { A0[k] = load_raw_any<DT>(w, row_at(c, row(r0 + 2 * PF) + k)); B0[k] = load_raw_any<DT>(w_ref, row_at(c, row(r0 + 2 * PF) + k)); }
         } else if (next_fast) {
             fetch_first_batch<DT>(next, A0, B0, !PACK ? rot : 0u);
         }
@@ -988,7 +973,7 @@ struct VectorChunks {
     const void* w; const void* w_ref;
     u64 n;
     u32* prov; u32 slot_words; u32* chunk_bits; u32* group_words;
-    u32 nchunks; bool aligned;
+    u32 nchunks;
     u32 k8; bool row;
     const u32* chunk_list; u32 listed;
     u32 pos;
@@ -999,13 +984,12 @@ struct VectorChunks {
         ch.c = c;
         ch.valid = valid;
         ch.w = w; ch.w_ref = w_ref; ch.n = n;
-        ch.fast = aligned && (u64)(c + 1) * kChunk <= n;
-        ch.vec = aligned;
+        ch.fast = (u64)(c + 1) * kChunk <= n;
         ch.slot = prov + (u64)c * slot_words;
         ch.bits_at = chunk_bits + c;
         ch.group_at = group_words + (c >> 6);
         ch.parts = 0; ch.by_parts = false;
-        if (valid && aligned && batch_max) {
+        if (valid && batch_max) {
             const u64 inside = n - (u64)c * kChunk, part_elems = kChunk / parts_per_chunk;
             const u32 whole = inside >= kChunk ? parts_per_chunk : (u32)(inside / part_elems);
             // (less than one whole part: the guarded path)
@@ -1329,8 +1313,10 @@ __device__ __forceinline__ u32 part_word(const uint8_t* parts) {
     return load_uniform(reinterpret_cast<const u32*>(parts) + (elem_bytes<DT>() == 4 ? v / 2 : v / 4));
 }
 
-// Codes the chunk with table T (in memory).  maxima: part_word of the chunk, or kReadAllParts; parts of a full, aligned chunk
-// below every kept bucket are not read.
+// Codes the chunk with table T (in memory).  maxima: part_word of the chunk, or kReadAllParts; parts of a full chunk
+// below every kept bucket are not read.  A full chunk takes vector loads at any alignment, in one wait; by guarded loads of single
+// elements, off alignment, fp32 2^25 laplace elements 146 us the call and 120 so, 2^24 94 and 78, bf16 2^26 225 and 155, 32 layers
+// of 2^20 in a batch fp32 202 and 143, bf16 354 and 120 (aligned ones the same to 1 %).
 template <int DT>
 __device__ __forceinline__ void pack_chunk_wg(const ChunkRef& ch, const Table& T, u32 maxima, EncState* ws, PackWg& L) {
     typedef typename Raw<DT>::type raw_t;
@@ -1345,7 +1331,7 @@ __device__ __forceinline__ void pack_chunk_wg(const ChunkRef& ch, const Table& T
         for (u32 h = 0; h < 2; ++h) {
             if (skip[h]) continue;
 #pragma unroll
-            for (u32 k = H * h; k < H * h + H; ++k) { A[k] = load_raw<DT>(ch.w, row_at(ch.c, first_row + k)); B[k] = load_raw<DT>(ch.w_ref, row_at(ch.c, first_row + k)); }
+            for (u32 k = H * h; k < H * h + H; ++k) { A[k] = load_raw_any<DT>(ch.w, row_at(ch.c, first_row + k)); B[k] = load_raw_any<DT>(ch.w_ref, row_at(ch.c, first_row + k)); }
         }
     } else {
 #pragma unroll
@@ -1403,7 +1389,7 @@ __device__ __forceinline__ void pack_chunk_wg(const ChunkRef& ch, const Table& T
 #pragma unroll
             for (u32 k = 0; k < H; ++k) {
                 const u64 idx = row_at(ch.c, first_row + H * h + k);
-                if (ch.fast) { a[k] = load_raw<DT>(ch.w, idx); b[k] = load_raw<DT>(ch.w_ref, idx); }
+                if (ch.fast) { a[k] = load_raw_any<DT>(ch.w, idx); b[k] = load_raw_any<DT>(ch.w_ref, idx); }
                 else { a[k] = load_raw_guarded<DT>(ch.w, idx, ch.n); b[k] = load_raw_guarded<DT>(ch.w_ref, idx, ch.n); }
             }
             u64 s = 0;
@@ -1444,8 +1430,7 @@ __device__ __forceinline__ u32 list_entry(u32 i, u32 count) { return (i | 7u) < 
 template <int DT, bool STAY>
 __global__ __launch_bounds__(kWgThreads, DT == kF32 || STAY ? 4 : 8) void k_pack(const void* __restrict__ w, const void* __restrict__ w_ref, u64 n,
                                                      EncState* ws, u32* chunk_bits, u32* group_words, const u32* chunk_maxexp,
-                                                     const u32* chunk_list, const uint8_t* batch_max, u32* prov, u32 slot_words, u32 nchunks,
-                                                     int aligned) {
+                                                     const u32* chunk_list, const uint8_t* batch_max, u32* prov, u32 slot_words, u32 nchunks) {
     __shared__ PackWg L;
     const Table& T = ws->table;
     if (T.status != 0 || ws->spec_ok != 0) return;     // nothing to code, or the speculative sweep already did
@@ -1456,7 +1441,7 @@ __global__ __launch_bounds__(kWgThreads, DT == kF32 || STAY ? 4 : 8) void k_pack
         ChunkRef ch;
         ch.w = w; ch.w_ref = w_ref; ch.n = n; ch.c = c;
         ch.slot = prov + (u64)c * slot_words; ch.bits_at = chunk_bits + c; ch.group_at = group_words + (c >> 6);
-        ch.fast = aligned && (u64)(c + 1) * kChunk <= n;
+        ch.fast = (u64)(c + 1) * kChunk <= n;
         constexpr u32 kParts = kChunk * elem_bytes<DT>() / 4096;
         u32 largest = kReadAllParts, maxima = kReadAllParts;
         if (chunk_maxexp) { largest = load_uniform(chunk_maxexp + maxexp_slot(c)); maxima = part_word<DT>(batch_max + (u64)c * kParts); }
@@ -1545,7 +1530,7 @@ struct PackLds64 {
     unsigned long long mn[kMaxSym * kMmCopies64], mx[kMaxSym * kMmCopies64];
 };
 
-template <bool WHOLE>            // WHOLE: a full chunk of 16-byte aligned arrays
+template <bool WHOLE>            // WHOLE: a full chunk
 __device__ __forceinline__ void pack_chunk64(const ChunkRef& ch, PackLds64& L, u32 K) {
     constexpr int RB = 4;
     const u32 lane = lane_id();
@@ -1559,7 +1544,8 @@ __device__ __forceinline__ void pack_chunk64(const ChunkRef& ch, PackLds64& L, u
 #pragma unroll
         for (int k = 0; k < RB; ++k) {
             const u64 idx = base + (u64)(r0 + k) * kRowElems + lane * kV;
-            load_row64<WHOLE>(ch.w, idx, n, xa[k]); load_row64<WHOLE>(ch.w_ref, idx, n, xb[k]);
+            if (WHOLE) { load_row_any<kF64>(ch.w, idx, xa[k]); load_row_any<kF64>(ch.w_ref, idx, xb[k]); }
+            else { load_row64<false>(ch.w, idx, n, xa[k]); load_row64<false>(ch.w_ref, idx, n, xb[k]); }
         }
 #pragma unroll
         for (int k = 0; k < RB; ++k) {
@@ -1616,8 +1602,8 @@ __device__ __noinline__ void pack_chunk64_parts(const ChunkRef ch, u32 cl_merged
             double xa[kRowsPerPart][4], xb[kRowsPerPart][4];
 #pragma unroll
             for (u32 k = 0; k < kRowsPerPart; ++k) {
-                load_row64<true>(ch.w, row_idx(p * kRowsPerPart + k), n, xa[k]);
-                load_row64<true>(ch.w_ref, row_idx(p * kRowsPerPart + k), n, xb[k]);
+                load_row_any<kF64>(ch.w, row_idx(p * kRowsPerPart + k), xa[k]);
+                load_row_any<kF64>(ch.w_ref, row_idx(p * kRowsPerPart + k), xb[k]);
             }
 #pragma unroll
             for (u32 k = 0; k < kRowsPerPart; ++k) {
@@ -1662,7 +1648,7 @@ __device__ __noinline__ void pack_chunk64_parts(const ChunkRef ch, u32 cl_merged
 __global__ __launch_bounds__(64) void k_pack64(const void* __restrict__ w, const void* __restrict__ w_ref, u64 n,
                                                EncState* ws, Ext64* ext, u32* chunk_bits, u32* group_words,
                                                const u32* chunk_maxexp, const u32* chunk_list, const uint8_t* part_max, u32* prov,
-                                               u32 slot_words, u32 nchunks, int aligned) {
+                                               u32 slot_words, u32 nchunks) {
     __shared__ PackLds64 L;
     const u32 lane = threadIdx.x;
     const Table& T = ws->table;
@@ -1672,7 +1658,7 @@ __global__ __launch_bounds__(64) void k_pack64(const void* __restrict__ w, const
     if (lane < kMaxSym) L.codelen[lane] = T.codelen[lane];
     for (u32 i = lane; i < kMaxSym * kMmCopies64; i += kW) { L.mn[i] = ~0ull; L.mx[i] = 0; }
     __syncthreads();
-    VectorChunks src = {w, w_ref, n, prov, slot_words, chunk_bits, group_words, nchunks, aligned != 0, K << 3, true,
+    VectorChunks src = {w, w_ref, n, prov, slot_words, chunk_bits, group_words, nchunks, K << 3, true,
                         chunk_list, chunk_list ? ws->list_count : 0, 0, chunk_list ? part_max : nullptr, 32u, T.min_kept_exp,
                         T.codelen[K]};
     if (chunk_list) note_merged_chunks(T, n, chunk_bits, group_words, chunk_maxexp);
@@ -1697,7 +1683,7 @@ __global__ __launch_bounds__(64) void k_pack64(const void* __restrict__ w, const
 template <int DT>
 __global__ __launch_bounds__(64) void k_spec_sweep(const void* __restrict__ w, const void* __restrict__ w_ref, u64 n,
                                                    Workspace* ws, u32* chunk_bits, u32* group_words, u32* prov,
-                                                   u32 slot_words, u32 nchunks, int aligned) {
+                                                   u32 slot_words, u32 nchunks) {
     __shared__ PackLds L;
     const u32 lane = threadIdx.x;
     const Table& T = ws->table;
@@ -1706,7 +1692,7 @@ __global__ __launch_bounds__(64) void k_spec_sweep(const void* __restrict__ w, c
     if (spec) pack_setup(L, T, lane);
     const u32 K = spec ? T.K : 0;
     __syncthreads();
-    VectorChunks src = {w, w_ref, n, prov, slot_words, chunk_bits, group_words, nchunks, aligned != 0, K << 3,
+    VectorChunks src = {w, w_ref, n, prov, slot_words, chunk_bits, group_words, nchunks, K << 3,
                         !spec || T.max_len <= 8, nullptr, 0, 0, nullptr, 16u, 0u, 0u};
     if (!spec) pack_loop<false, DT, 1>(src, L);
     else if (src.row) pack_loop<true, DT, 1>(src, L);
@@ -2358,7 +2344,7 @@ __global__ __launch_bounds__(kWgThreads, DT == kF32 ? 4 : 8) void kb_pack(BatchA
     ch.c = g - sg.chunk0;
     ch.w = sg.w; ch.w_ref = sg.w_ref; ch.n = sg.n;
     ch.slot = a.prov + (u64)g * a.slot_words; ch.bits_at = a.chunk_bits + g; ch.group_at = a.group_words + sg.group0 + (ch.c >> 6);
-    ch.fast = sg.aligned && (u64)(ch.c + 1) * kChunk <= sg.n;
+    ch.fast = (u64)(ch.c + 1) * kChunk <= sg.n;
     if (st->table.status != 0) return;                 // (a delta that is not finite: a header-only blob)
     const u32 largest = load_uniform(a.chunk_maxexp + g), maxima = part_word<DT>(a.part_max + (u64)g * kPartBytes);
     if (!a.listed && noted_as_merged(ch, st->table, largest)) return;
@@ -2394,14 +2380,6 @@ void launch_reset_chunks(Workspace* ws, uint32_t* group_words, uint32_t* chunk_m
     hipLaunchKernelGGL(k_reset_chunks, dim3(1), dim3(1024), 0, s, ws, group_words, (nchunks + 63) / 64, chunk_maxexp, nchunks);
 }
 
-template <int DT>
-static void launch_hist_t(const void* w, const void* w_ref, uint64_t n, Workspace* ws, u32* chunk_maxexp, uint8_t* batch_max,
-                          u32 blocks, u32 threads, hipStream_t s) {
-    const KeyPlanes none = {nullptr, nullptr};
-    if (aligned16(w) && aligned16(w_ref)) hipLaunchKernelGGL((k_hist<true, DT>), dim3(blocks), dim3(threads), 0, s, w, w_ref, (u64)n, ws, chunk_maxexp, batch_max, none);
-    else hipLaunchKernelGGL((k_hist<false, DT>), dim3(blocks), dim3(threads), 0, s, w, w_ref, (u64)n, ws, chunk_maxexp, batch_max, none);
-}
-
 // keys.exp != null: stage keys (binary32, both arrays 16-byte aligned: the caller has checked)
 void launch_hist(const void* w, const void* w_ref, uint64_t n, int dtype, Workspace* ws, uint32_t* chunk_maxexp, uint8_t* batch_max,
                  KeyPlanes keys, const Tuning& tune, hipStream_t s) {
@@ -2414,14 +2392,15 @@ void launch_hist(const void* w, const void* w_ref, uint64_t n, int dtype, Worksp
     if (blocks < 1) blocks = 1;
     if (dtype == kF64) {
         uint16_t* part_max = reinterpret_cast<uint16_t*>(batch_max);
-        if (aligned16(w) && aligned16(w_ref)) hipLaunchKernelGGL(k_hist64<true>, dim3((u32)blocks), dim3(threads), 0, s, w, w_ref, (u64)n, &ws->ext64, chunk_maxexp, part_max);
-        else hipLaunchKernelGGL(k_hist64<false>, dim3((u32)blocks), dim3(threads), 0, s, w, w_ref, (u64)n, &ws->ext64, chunk_maxexp, part_max);
+        hipLaunchKernelGGL(k_hist64, dim3((u32)blocks), dim3(threads), 0, s, w, w_ref, (u64)n, &ws->ext64, chunk_maxexp, part_max);
         return;
     }
-    if (dtype == kBF16) launch_hist_t<kBF16>(w, w_ref, n, ws, chunk_maxexp, batch_max, (u32)blocks, threads, s);
-    else if (dtype == kF16) launch_hist_t<kF16>(w, w_ref, n, ws, chunk_maxexp, batch_max, (u32)blocks, threads, s);
-    else if (keys.exp) hipLaunchKernelGGL((k_hist<true, kF32, true>), dim3((u32)blocks), dim3(threads), 0, s, w, w_ref, (u64)n, ws, chunk_maxexp, batch_max, keys);
-    else launch_hist_t<kF32>(w, w_ref, n, ws, chunk_maxexp, batch_max, (u32)blocks, threads, s);
+#define LC_HIST(DT, KEYS) hipLaunchKernelGGL((k_hist<DT, KEYS>), dim3((u32)blocks), dim3(threads), 0, s, w, w_ref, (u64)n, ws, chunk_maxexp, batch_max, keys)
+    if (dtype == kBF16) LC_HIST(kBF16, false);
+    else if (dtype == kF16) LC_HIST(kF16, false);
+    else if (keys.exp) LC_HIST(kF32, true);
+    else LC_HIST(kF32, false);
+#undef LC_HIST
 }
 
 // Whether sweep 2 takes its chunks from a list of those to read.  Writing the list is work for the table's kernel, and taking
@@ -2482,11 +2461,10 @@ void launch_spec_sweep(const void* w, const void* w_ref, uint64_t n, int dtype, 
     const u64 nchunks = num_chunks_of(n);
     if (nchunks == 0) return;
     const u32 blocks = even_waves(nchunks, (u64)tune.num_cu * tune.spec_waves_per_cu);
-    const int al = aligned_rows(w, dtype) && aligned_rows(w_ref, dtype);
     const dim3 grid(blocks), wg(64);
-    if (dtype == kBF16) hipLaunchKernelGGL(k_spec_sweep<kBF16>, grid, wg, 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, prov, slot_words, (u32)nchunks, al);
-    else if (dtype == kF16) hipLaunchKernelGGL(k_spec_sweep<kF16>, grid, wg, 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, prov, slot_words, (u32)nchunks, al);
-    else hipLaunchKernelGGL(k_spec_sweep<kF32>, grid, wg, 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, prov, slot_words, (u32)nchunks, al);
+    if (dtype == kBF16) hipLaunchKernelGGL(k_spec_sweep<kBF16>, grid, wg, 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, prov, slot_words, (u32)nchunks);
+    else if (dtype == kF16) hipLaunchKernelGGL(k_spec_sweep<kF16>, grid, wg, 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, prov, slot_words, (u32)nchunks);
+    else hipLaunchKernelGGL(k_spec_sweep<kF32>, grid, wg, 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, prov, slot_words, (u32)nchunks);
 }
 
 // chunk_maxexp, chunk_list: what k_hist recorded and k_table listed for this vector, or both null
@@ -2495,14 +2473,13 @@ void launch_pack(const void* w, const void* w_ref, uint64_t n, int dtype, Worksp
                  uint32_t* prov, uint32_t slot_words, const Tuning& tune, hipStream_t s) {
     const u64 nchunks = num_chunks_of(n);
     if (nchunks == 0) return;
-    const int al = aligned_rows(w, dtype) && aligned_rows(w_ref, dtype);
     // (a short call's chunks were not listed: see pack_needs_list)
     const u32* list = pack_needs_list(n, dtype, tune) ? chunk_list : nullptr;
     const u32* maxexp = chunk_list ? chunk_maxexp : nullptr;
     const dim3 wg(kWgThreads);
-#define LC_PACK(DT, STAY, GRID) hipLaunchKernelGGL((k_pack<DT, STAY>), dim3((u32)(GRID)), wg, 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, maxexp, list, batch_max, prov, slot_words, (u32)nchunks, al)
+#define LC_PACK(DT, STAY, GRID) hipLaunchKernelGGL((k_pack<DT, STAY>), dim3((u32)(GRID)), wg, 0, s, w, w_ref, (u64)n, ws, chunk_bits, group_words, maxexp, list, batch_max, prov, slot_words, (u32)nchunks)
     if (dtype == kF64) {
-        hipLaunchKernelGGL(k_pack64, dim3(even_waves(nchunks, (u64)tune.num_cu * tune.pack_waves_per_cu)), dim3(64), 0, s, w, w_ref, (u64)n, ws, &ws->ext64, chunk_bits, group_words, chunk_maxexp, chunk_list, batch_max, prov, slot_words, (u32)nchunks, al);
+        hipLaunchKernelGGL(k_pack64, dim3(even_waves(nchunks, (u64)tune.num_cu * tune.pack_waves_per_cu)), dim3(64), 0, s, w, w_ref, (u64)n, ws, &ws->ext64, chunk_bits, group_words, chunk_maxexp, chunk_list, batch_max, prov, slot_words, (u32)nchunks);
     } else if (chunk_list) {
         // a workgroup per chunk
         if (dtype == kBF16) LC_PACK(kBF16, false, nchunks);

@@ -218,7 +218,7 @@ void launch_encode_one(const void* w, const void* w_ref, uint64_t n, int nbits, 
 struct Seg {
     const void* w; const void* w_ref; uint8_t* out;
     uint64_t n;
-    uint32_t nchunks, chunk0, group0, aligned;
+    uint32_t nchunks, chunk0, group0, pad;
 };
 constexpr int kMaxBatch = 1024;
 constexpr uint32_t kPartBytes = 16;
