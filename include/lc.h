@@ -190,7 +190,7 @@ int lc_encode_static(const float* w, const float* w_ref, uint64_t n, int nbits, 
  * lc_encode on the widened vectors, and the restore computes fl32(float(w_ref[i]) + representative) and
  * rounds it once, to nearest even, back to the storage type (elements of the merged bucket keep their
  * bits).  dtype: LC_F32 (then these are lc_encode / lc_decode), LC_BF16, LC_F16, LC_F64; w, w_ref: arrays of
- * that type, aligned to the element size (four elements' alignment makes restores of long vectors faster).  LC_F64: the whole method in binary64 (Section 3.1.1, footnote on
+ * that type, aligned to the element size.  LC_F64: the whole method in binary64 (Section 3.1.1, footnote on
  * the bucket count): delta = fl64(w - w_ref), buckets by sign and the 11 exponent bits, representatives the
  * exactly rounded binary64 midranges, restore by one binary64 addition.  The blob records the element type at header offset 60 (0 for fp32 blobs) and restores only
  * into that type (else LC_ERR_BADARG); otherwise arguments, results and errors as lc_encode / lc_decode.

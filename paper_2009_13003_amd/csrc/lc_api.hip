@@ -607,7 +607,7 @@ bool fits_in_one(const DeviceState* ds, uint64_t n) {
 //            5       1.17 1.22 / 1.02 1.07; 1.19 1.21 / 1.08 1.10; 1.04 1.07 / 0.91 0.94; 0.93 1.00 / 0.80 0.90
 //            8       0.92 0.94 / 0.81 0.84; 1.18 1.22 / 1.04 1.06; 1.01 1.05 / 0.88 0.91; 0.78 0.84 / 0.66 0.74
 //            16      0.86 0.90 / 0.75 0.80; 1.05 1.08 / 0.94 0.98; 0.89 0.93 / 0.79 0.83; 0.76 0.84 / 0.66 0.73
-// (the fused sweep takes 4 of them at a time), bf16 up to a tenth more; off alignment 1.14 to 5.3 at every size and count.
+// (against sweeps of up to 4 blobs), bf16 up to a tenth more; off alignment 1.14 to 5.3 at every size and count.
 // binary64, whose other route is a sweep per blob: up to a chunk per compute unit 0.87 to 2.3, above that 1.4 to 2.9 where the strings
 // are dense and 0.66 to 0.95 where they are not.
 bool many_in_one(const DeviceState* ds, uint64_t n, int count, const void* w_ref, int dtype) {
@@ -936,7 +936,7 @@ lc_ssize lc_decode_batch_t(const void* const* blobs, void* const* w_ref, const u
     for (int t = 0; t < count; ++t) {
         SegD& sg = g_batch->dsegs[t];
         sg.blob = static_cast<const uint8_t*>(blobs[t]); sg.w_ref = w_ref[t]; sg.n = n[t];
-        sg.nchunks = (uint32_t)num_chunks_of(n[t]); sg.chunk0 = chunks; sg.aligned = !misaligned(w_ref[t], 4 * esize); sg.pad = 0;
+        sg.nchunks = (uint32_t)num_chunks_of(n[t]); sg.chunk0 = chunks;
         chunks += sg.nchunks;
         g_batch->results[t].bytes = 0; g_batch->results[t].status = LC_ERR_HIP; g_batch->results[t].used_cache = 0;
     }

@@ -263,9 +263,11 @@ __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 fi
         for (u32 g = 0; g < kR / kGroupRows && (FAST || base + (u64)g * kGroupRows * kRowElems < n); ++g) symbols(g);
     } else if constexpr (FAST) {
         typedef typename Raw<DT>::type raw_t;
+        // (binary64: plain loads, since a lane's 32 bytes are two loads from the same lines: marked non-temporal, 2^24
+        // elements 76 us and 62 so, 2^26 267 and 243, layers of 2^25 125 and 98)
         auto fetch = [&](raw_t (&X)[kGroupRows], u32 g) {
 #pragma unroll
-            for (u32 k = 0; k < kGroupRows; ++k) X[k] = load_raw<DT>(w_ref, row_at(g * kGroupRows + k));
+            for (u32 k = 0; k < kGroupRows; ++k) X[k] = load_raw_any<DT, DT != kF64>(w_ref, row_at(g * kGroupRows + k));
         };
         auto restore = [&](const raw_t (&X)[kGroupRows], u32 g) {
 #pragma unroll
@@ -275,12 +277,16 @@ __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 fi
                 val_t x[4];
                 if constexpr (DT == kF64) unpack64(X[k], x); else unpack<DT>(X[k], x);
                 add_row(syms, x);
-                store4_v<DT>(w_ref, row_at(g * kGroupRows + k), x);
+                store4_any<DT>(w_ref, row_at(g * kGroupRows + k), x);
             }
         };
         // (ahead: the next group's rows are asked for before this one is decoded; else only its own, and the wavefronts that
-        // share a SIMD cover each other's waits.  binary64 rows are 2 KiB: ahead, 2^25 elements 136 us against 139, but 2^26
-        // 294 against 267 and 2^27 552 against 503)
+        // share a SIMD cover each other's waits.  binary64 rows are 2 KiB: ahead, 2^24 elements 62 us against 64, layers of 2^25
+        // 98 against 96, of 2^26 210 against 200)
+        // Off alignment the same rows: the hardware takes vectors at any address.  Against guarded loads and stores of single
+        // elements and a look-up for codes of any length, 2^27 elements in layers 350 -> 187 us (fp32; aligned 180) and
+        // 462 -> 175 (bf16; 156), a batch of 32 layers of 2^20 96 -> 87 and 135 -> 93; binary64 in layers 2^25 115 -> 99, of one
+        // scale 2^24 83 -> 62, 2^25 129 -> 132, 2^26 250 -> 244.
         if (DT != kF64 || ahead) {
             raw_t A[kGroupRows], B[kGroupRows];
             fetch(A, 0);
@@ -301,15 +307,14 @@ __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 fi
             }
         }
     } else {
-        // A ragged or unaligned chunk (the vector's last chunk is one wavefront's work from start to end, so its memory
-        // round trips count): rows that lie wholly inside an aligned array as vectors, the rest element by element.
-        const bool vec = (reinterpret_cast<uintptr_t>(w_ref) & (DT == kF64 ? 15 : 4 * elem_bytes<DT>() - 1)) == 0;
+        // A ragged chunk (the vector's last chunk is one wavefront's work from start to end, so its memory round trips
+        // count): rows that lie wholly inside the array as vectors, the rest element by element.
         for (u32 g = 0; g < kR / kGroupRows && base + (u64)g * kGroupRows * kRowElems < n; ++g) {
             val_t x[kGroupRows][4];
             auto fetch = [&](u32 k) {
                 const u32 r = g * kGroupRows + k;
-                if (vec && base + (u64)(r + 1) * kRowElems <= n) load_row_v<true, DT>(w_ref, row_at(r), n, x[k]);
-                else load_row_v<false, DT>(w_ref, row_at(r), n, x[k]);
+                if (base + (u64)(r + 1) * kRowElems <= n) load_row_any<DT, DT != kF64>(w_ref, row_at(r), x[k]);
+                else load_row_v<DT>(w_ref, row_at(r), n, x[k]);
             };
 #pragma unroll
             for (u32 k = 0; k < kGroupRows; ++k) fetch(k);               // on their way while the symbols are decoded
@@ -317,10 +322,10 @@ __device__ __forceinline__ void decode_rows(const u32* words, u32 nwords, u32 fi
 #pragma unroll
             for (u32 k = 0; k < kGroupRows; ++k) {
                 const u32 r = g * kGroupRows + k, syms = row_syms(g, k);
-                if (vec && base + (u64)(r + 1) * kRowElems <= n) {
+                if (base + (u64)(r + 1) * kRowElems <= n) {
                     if (!any_kept(syms)) continue;
                     add_row(syms, x[k]);
-                    store4_v<DT>(w_ref, row_at(r), x[k]);
+                    store4_any<DT>(w_ref, row_at(r), x[k]);
                 } else {
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
@@ -426,7 +431,7 @@ struct QuietChunk {
 };
 
 // pay: this wavefront's LDS area of pay_words + 4 words for the chunk's payload; ring: its symbol ring
-// fast: a full chunk of an aligned array; long_codes: the blob has codes of more than 10 bits; ahead: see decode_rows
+// fast: a full chunk; long_codes: the blob has codes of more than 10 bits; ahead: see decode_rows
 template <int DT, bool VERIFY = false, typename LDS, typename Raise>
 __device__ __forceinline__ void decode_chunk(const uint8_t* __restrict__ blob, void* __restrict__ w_ref, u64 n,
                                              u32 c, u32 o0, u32 o1, bool fast, bool long_codes, bool ahead, LDS& L, uint4* pay, u32 pay_words, u32* ring, u32 K,
@@ -480,10 +485,10 @@ __device__ __forceinline__ void decode_chunk(const uint8_t* __restrict__ blob, v
 }
 
 // VERIFY: lc_verify's sweep (and the one lc_decode runs first when asked to): the same walk over the blob, decoding
-// only; `w_ref` is not used.  flags: 1 = w_ref is aligned to rows, 2 = rows are fetched a group ahead.
+// only; `w_ref` is not used.  ahead: rows are fetched a group ahead.
 template <int DT, bool VERIFY = false>
 __global__ __launch_bounds__(256, DT == kF64 ? 2 : 3) void k_decode(const uint8_t* __restrict__ blob, void* __restrict__ w_ref, u64 n,
-                                                Workspace* ws, u32 nchunks, int flags, u64 epoch, HostResult* host,
+                                                Workspace* ws, u32 nchunks, int ahead, u64 epoch, HostResult* host,
                                                 u32 pay_words, u32 set) {
     __shared__ DecLds L;
     __shared__ u32 s_ring[VERIFY ? 1 : 4 * kRingWords * kW];
@@ -553,7 +558,7 @@ __global__ __launch_bounds__(256, DT == kF64 ? 2 : 3) void k_decode(const uint8_
                 lens.set(sym_len, K);
                 __builtin_amdgcn_wave_barrier();
             }
-            decode_chunk<DT, VERIFY>(blob, w_ref, n, c, o0, o1, full && (flags & 1) != 0, M > kMultiBits, (flags & 2) != 0, L, pay, pay_words, ring, K, lens, area, raise);
+            decode_chunk<DT, VERIFY>(blob, w_ref, n, c, o0, o1, full, M > kMultiBits, ahead != 0, L, pay, pay_words, ring, K, lens, area, raise);
         }
         if (!more) break;
         c = (u32)cn; o0 = n0; o1 = n1;
@@ -684,7 +689,7 @@ __global__ __launch_bounds__(64) void kb_decode(BatchDecArgs a) {
             lens.set(len, K);
             __builtin_amdgcn_wave_barrier();
         }
-        decode_chunk<DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, full && sg.aligned, M > kMultiBits, true, L, pay, kPayWords, ring, K, lens, area, raise);
+        decode_chunk<DT>(sg.blob, sg.w_ref, sg.n, c, o0, o1, full, M > kMultiBits, true, L, pay, kPayWords, ring, K, lens, area, raise);
     }
 }
 
@@ -1556,17 +1561,17 @@ void launch_decode(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, Work
     const bool few = nchunks <= (u64)tune.num_cu * few_per_cu;
     const u64 blocks = balanced_workers((nchunks + 3) / 4, (u64)tune.num_cu * (few ? 3 : tune.decode_blocks_per_cu));
     const dim3 grid((u32)blocks), wg(256);
-    const int flags = (verify || aligned_rows(w_ref, dtype) ? 1 : 0) | (few || dtype != kF64 ? 2 : 0);
+    const int ahead = few || dtype != kF64;
     const u32 pay_words = blocks <= (u64)tune.num_cu ? kPayWordsOne : few && blocks > 2 * (u64)tune.num_cu ? kPayWords : verify ? kPayWordsVerify : kPayWordsTwo;
     constexpr size_t fixed = sizeof(DecLds) + 4 * kRingWords * kW * 4, area = 4 * sizeof(uint4);
     static_assert(fixed + area * (kPayWordsOne / 4 + 1) <= kLdsPerCu && fixed + area * (kPayWordsTwo / 4 + 1) <= kLdsPerCu / 2 - 1280 &&
                   fixed + area * (kPayWords / 4 + 1) <= kLdsPerCu / 3 - 1280, "workgroups that share a compute unit (LDS is given in steps of 1280 bytes)");
     const size_t lds = area * (pay_words / 4 + 1);
     if (verify) {
-        hipLaunchKernelGGL((k_decode<kF32, true>), grid, wg, lds, s, blob, (void*)nullptr, (u64)n, ws, (u32)nchunks, flags, (u64)epoch, host, pay_words, (u32)set);
+        hipLaunchKernelGGL((k_decode<kF32, true>), grid, wg, lds, s, blob, (void*)nullptr, (u64)n, ws, (u32)nchunks, ahead, (u64)epoch, host, pay_words, (u32)set);
         return;
     }
-#define LC_DECODE(DT) hipLaunchKernelGGL((k_decode<DT>), grid, wg, lds, s, blob, w_ref, (u64)n, ws, (u32)nchunks, flags, (u64)epoch, host, pay_words, (u32)set)
+#define LC_DECODE(DT) hipLaunchKernelGGL((k_decode<DT>), grid, wg, lds, s, blob, w_ref, (u64)n, ws, (u32)nchunks, ahead, (u64)epoch, host, pay_words, (u32)set)
     if (dtype == kF64) LC_DECODE(kF64);
     else if (dtype == kBF16) LC_DECODE(kBF16);
     else if (dtype == kF16) LC_DECODE(kF16);

@@ -141,13 +141,14 @@ typedef double f64x2 __attribute__((ext_vector_type(2)));
 typedef f32x4 __attribute__((aligned(4))) f32x4_any;
 typedef u32x2 __attribute__((aligned(2))) u32x2_any;
 typedef f64x2 __attribute__((aligned(8))) f64x2_any;
-template <int DT>
+template <int DT, bool STREAM = true>            // STREAM false (binary64): plain loads
 __device__ __forceinline__ typename Raw<DT>::type load_raw_any(const void* base, u64 i) {
     if constexpr (DT == kF32) {
         const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_any*>(static_cast<const float*>(base) + i));
         return make_float4(v.x, v.y, v.z, v.w);
     } else if constexpr (DT == kF64) {
         const f64x2_any* p = reinterpret_cast<const f64x2_any*>(static_cast<const double*>(base) + i);
+        if constexpr (!STREAM) { const f64x2 a = p[0], b = p[1]; return Row64{{a.x, a.y, b.x, b.y}}; }
         const f64x2 a = __builtin_nontemporal_load(p), b = __builtin_nontemporal_load(p + 1);
         return Row64{{a.x, a.y, b.x, b.y}};
     } else {
@@ -229,6 +230,7 @@ __device__ __forceinline__ void store4_any(void* base, u64 i, const typename Val
         const f32x4 v = {x[0], x[1], x[2], x[3]};
         __builtin_nontemporal_store(v, reinterpret_cast<f32x4_any*>(static_cast<float*>(base) + i));
     } else if constexpr (DT == kF64) {
+        // (plain stores: marked non-temporal, the two 16-byte halves of a lane's 32 bytes made the restore 15 % slower)
         f64x2_any* p = reinterpret_cast<f64x2_any*>(static_cast<double*>(base) + i);
         p[0] = f64x2{x[0], x[1]}; p[1] = f64x2{x[2], x[3]};
     } else {
@@ -237,20 +239,10 @@ __device__ __forceinline__ void store4_any(void* base, u64 i, const typename Val
     }
 }
 
-// the same for binary64 parameters
-template <bool FAST>
+// a row that may end inside, by elements, of binary64 parameters
 __device__ __forceinline__ void load_row64(const void* __restrict__ p, u64 idx, u64 n, double (&x)[4]) {
-    if (FAST) {
-        unpack64(load_raw<kF64>(p, idx), x);
-    } else {
 #pragma unroll
-        for (int v = 0; v < 4; ++v) x[v] = (idx + v < n) ? static_cast<const double*>(p)[idx + v] : 0.0;
-    }
-}
-// (plain stores: marked non-temporal, the two 16-byte halves of a lane's 32 bytes made this sweep 15 % slower)
-__device__ __forceinline__ void store4_64(void* base, u64 i, const double (&x)[4]) {
-    double2* q = reinterpret_cast<double2*>(static_cast<double*>(base) + i);
-    q[0] = make_double2(x[0], x[1]); q[1] = make_double2(x[2], x[3]);
+    for (int v = 0; v < 4; ++v) x[v] = (idx + v < n) ? static_cast<const double*>(p)[idx + v] : 0.0;
 }
 
 template <bool FAST, int DT = kF32>
@@ -263,27 +255,22 @@ __device__ __forceinline__ void load_row(const void* __restrict__ p, u64 idx, u6
     }
 }
 
-template <int DT>
+template <int DT, bool STREAM = true>
 __device__ __forceinline__ void load_row_any(const void* __restrict__ p, u64 idx, typename Val<DT>::type (&x)[4]) {
-    if constexpr (DT == kF64) unpack64(load_raw_any<kF64>(p, idx), x);
+    if constexpr (DT == kF64) unpack64(load_raw_any<kF64, STREAM>(p, idx), x);
     else unpack<DT>(load_raw_any<DT>(p, idx), x);
 }
 
-// ---- the same three accesses and the restoring addition for any element type, on the type the arithmetic runs in
-template <bool FAST, int DT>
+// ---- the same accesses and the restoring addition for any element type, on the type the arithmetic runs in
+template <int DT>
 __device__ __forceinline__ void load_row_v(const void* __restrict__ p, u64 idx, u64 n, typename Val<DT>::type (&x)[4]) {
-    if constexpr (DT == kF64) load_row64<FAST>(p, idx, n, x);
-    else load_row<FAST, DT>(p, idx, n, x);
+    if constexpr (DT == kF64) load_row64(p, idx, n, x);
+    else load_row<false, DT>(p, idx, n, x);
 }
 template <int DT>
 __device__ __forceinline__ typename Val<DT>::type load_one_v(const void* base, u64 i) {
     if constexpr (DT == kF64) return static_cast<const double*>(base)[i];
     else return load_one<DT>(base, i);
-}
-template <int DT>
-__device__ __forceinline__ void store4_v(void* base, u64 i, const typename Val<DT>::type (&x)[4]) {
-    if constexpr (DT == kF64) store4_64(base, i, x);
-    else store4<DT>(base, i, x);
 }
 template <int DT>
 __device__ __forceinline__ void store_one_v(void* base, u64 i, typename Val<DT>::type x) {

@@ -1545,7 +1545,7 @@ __device__ __forceinline__ void pack_chunk64(const ChunkRef& ch, PackLds64& L, u
         for (int k = 0; k < RB; ++k) {
             const u64 idx = base + (u64)(r0 + k) * kRowElems + lane * kV;
             if (WHOLE) { load_row_any<kF64>(ch.w, idx, xa[k]); load_row_any<kF64>(ch.w_ref, idx, xb[k]); }
-            else { load_row64<false>(ch.w, idx, n, xa[k]); load_row64<false>(ch.w_ref, idx, n, xb[k]); }
+            else { load_row64(ch.w, idx, n, xa[k]); load_row64(ch.w_ref, idx, n, xb[k]); }
         }
 #pragma unroll
         for (int k = 0; k < RB; ++k) {
@@ -1628,8 +1628,8 @@ __device__ __noinline__ void pack_chunk64_parts(const ChunkRef ch, u32 cl_merged
         double xa[kRowsPerPart][4], xb[kRowsPerPart][4];
 #pragma unroll
         for (u32 k = 0; k < kRowsPerPart; ++k) {
-            load_row64<false>(ch.w, row_idx(whole * kRowsPerPart + k), n, xa[k]);
-            load_row64<false>(ch.w_ref, row_idx(whole * kRowsPerPart + k), n, xb[k]);
+            load_row64(ch.w, row_idx(whole * kRowsPerPart + k), n, xa[k]);
+            load_row64(ch.w_ref, row_idx(whole * kRowsPerPart + k), n, xb[k]);
         }
 #pragma unroll
         for (u32 k = 0; k < kRowsPerPart; ++k) {

@@ -243,7 +243,7 @@ void launch_batch_encode(const BatchArgs& a, const Tuning& tune, hipStream_t s);
 struct SegD {
     const uint8_t* blob; void* w_ref;
     uint64_t n;
-    uint32_t nchunks, chunk0, aligned, pad;
+    uint32_t nchunks, chunk0;
 };
 struct BatchDecArgs {
     const SegD* host_segs;                             // mapped host memory: what the call was given

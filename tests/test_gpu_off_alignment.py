@@ -40,3 +40,31 @@ def test_same_blob(lc, dtype, n):
                     size2, hit = lc.lc_encode_cached_t(w, ref, 3, want2, caches[0])
                     assert lc.lc_encode_cached_t(bw, br, 3, got, caches[1]) == (size2, hit), turn
                     assert torch.equal(got[:size2], want2[:size2]), turn
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16, torch.float64])
+@pytest.mark.parametrize("n", [1023, 600 * CHUNK, 600 * CHUNK + 7 * 1024 + 1, 2100 * CHUNK - 1])
+def test_same_restore(lc, dtype, n):
+    """Restores, alone and in a batch with a short vector: the bits of the aligned restore, and nothing written beside the array."""
+    print("restore off alignment", dtype, n, flush=True)
+    g = torch.Generator(device=DEV); g.manual_seed(n % 1009)
+    ref = (0.05 * torch.randn(n, generator=g, device=DEV)).to(dtype)
+    dense = 1e-3 * torch.randn(n, generator=g, device=DEV)
+    layers = dense * 10.0 ** -(torch.arange(n, device=DEV) // CHUNK % 7).float()            # long codes in some chunks
+    for nbits, d in ((3, dense), (4, layers), (1, dense * (torch.rand(n, generator=g, device=DEV) < 0.002))):
+        w = (ref.to(torch.float64) + d).to(dtype)
+        blob = lc.alloc_out(n, nbits, DEV); blob = blob[:lc.lc_encode_t(w, ref, nbits, blob)].contiguous()
+        want = ref.clone(); lc.lc_decode_t(blob, want)
+        whole = {2: torch.int16, 4: torch.int32, 8: torch.int64}[ref.element_size()]
+        for batch in (False, True) if dtype != torch.float64 else (False,):
+            for off in (1, 2, 3):
+                buf = torch.full((n + 8,), float("nan"), dtype=dtype, device=DEV)
+                guard = buf.view(whole)[:1].clone()
+                buf[off:off + n] = ref
+                if batch:
+                    lc.DecodeBatch([blob, blob], [buf[off:off + n], ref.clone()]).run()
+                else:
+                    lc.lc_decode_t(blob, buf[off:off + n])
+                assert torch.equal(buf[off:off + n].view(whole), want.view(whole)), (nbits, off, batch)
+                beside = torch.cat([buf.view(whole)[:off], buf.view(whole)[off + n:]])
+                assert bool((beside == guard).all()), (nbits, off, batch)
