@@ -774,7 +774,9 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
     // sweeps, once there is a chunk for most wavefronts it runs: k_decode_fused / it, us, fp32: 3 bits, 2^25 elements, 2 to 4
     // blobs 81 86 90 / 93 99 104, 5 blobs 145 / 110, 8 blobs 152 / 145, 2^26 8 blobs 270 / 217, 2^28.4 1,287 / 945; 4 bits
     // 2^25 2, 3, 4, 8 blobs 88 141 150 269 / 100 118 129 226, ten to fifty layers' 435 to 445 / 213 to 336; by chunks, 8 blobs at 3
-    // bits: 7 130 / 112, 92 117 / 117, 245 102 / 110, 733 114 / 113.  Arrays off alignment, for which the other has a slow form
+    // bits: 4 109 to 131 / 110 to 123, 15 95 to 111 / 112 to 122, 64 95 to 123 / 116, 245 102 / 110, 733 114 / 113, and at 2 bits
+    // 15 96 to 112 / 93 to 100, 64 97 to 111 / 96 to 104 (6 blobs 76 / 80): a few chunks keep too few wavefronts busy to hide the wider look-up, but
+    // where at most 3 buckets are kept.  Arrays off alignment, for which the other has a slow form
     // only, 2.1 to 4.1 times as fast.
     // k_decode_fused takes up to kMaxFused.  Its LDS payload area is sized to 1.1 x the blobs'
     // average chunk payloads (a chunk above that still decodes, from memory), and a sweep takes only as many
@@ -787,14 +789,18 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
         return w < kFusedMinWords ? kFusedMinWords : w;
     };
     const uint64_t cus = (uint64_t)ds->tune.num_cu;
-    const bool many = nchunks >= 3 * cus || 4 * nchunks <= cus;
+    auto many = [&](int i, int end) {                           // blobs i to end - 1
+        if (nchunks >= 3 * cus || 64 * nchunks <= cus) return true;
+        while (i < end && got.kept[i] <= 3) ++i;
+        return i == end && 4 * nchunks <= cus;
+    };
     const bool by_rows = !misaligned(w_ref, dtype == LC_F32 ? 16 : 8);
     auto wide = [&](int i) { return got.kept[i] > 7; };
     for (int g0 = 0; g0 < count;) {
         int run = 1;
         while (g0 + run < count && wide(g0 + run) == wide(g0)) ++run;
         const int most = wide(g0) ? kMaxWide : kMaxMany, sweeps = (run + most - 1) / most, pairs = (run + sweeps - 1) / sweeps;
-        if (pairs > 1 && (!by_rows || (many && pairs >= (wide(g0) ? 3 : 5)))) {
+        if (pairs > 1 && (!by_rows || (pairs >= (wide(g0) ? 3 : 5) && many(g0, g0 + pairs)))) {
             uint64_t bytes = 0;                                 // the longest blob's
             for (int i = g0; i < g0 + pairs; ++i) bytes = got.bytes[i] > bytes ? got.bytes[i] : bytes;
             const uint32_t row_bits = nchunks ? (uint32_t)(16 * 8 * (bytes - area_at) / (nchunks * kW * kR)) : 0;
