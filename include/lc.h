@@ -292,8 +292,8 @@ lc_ssize lc_verify(const void* blob, size_t blob_bytes, uint64_t n, int dtype, v
  * deltas; Section 3.2, checkpoint merging): applies blobs[0], blobs[1], ... blobs[count-1] to
  * w_ref in this order.  The result is bit for bit what `count` successive lc_decode calls
  * give (one fp32 add per blob and element, in blob order), but w_ref is read and written
- * once per sweep of several blobs (up to 8; as many as the decoder's on-chip memory takes
- * at full occupancy, typically 4 to 6) instead of once per blob; of a short vector, in most calls, once for the whole
+ * once per sweep of several blobs (up to 8; 4 of blobs that keep more
+ * than 7 buckets) instead of once per blob; of a short vector, in most calls, once for the whole
  * list, in one launch.
  *   blobs  HOST array of `count` DEVICE pointers to LCB1 blobs (16-byte aligned), each with
  *          header n equal to `n`; 1 <= count <= LC_MAX_MANY
