@@ -1221,7 +1221,7 @@ __device__ __forceinline__ void pairs_chunk(PairsLds<T, WIDE>& L, u32 wave, void
     const u32 lane = lane_id();
     PairsStrings<T, WIDE> S;
     const bool last = c + 1 == nchunks;
-    bool loud = false;
+    bool loud = n - (u64)c * kChunk < kChunk;                // (a ragged chunk's lanes are not alike)
 #pragma unroll
     for (int t = 0; t < T; ++t) {
         const u32 o0 = read_lane(off, t), o1 = read_lane(off, kMaxMany + t);
