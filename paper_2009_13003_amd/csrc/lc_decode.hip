@@ -1052,7 +1052,7 @@ struct PairsLds {
     const u32* off_tab[T];
     u32 nranks[T], merged[T];                    // symbols with a code; the merged symbol
     u32 zero_bits[T];                            // lane length of a chunk of merged symbols only (0: never skip)
-    u32 stop;
+    u32 stop, taken;                             // chunks that its wavefronts have taken
     // word k of lane l's window of blob t: [wave][t][k][l] (the word in front of a window is read, never used)
     alignas(kWords * 256) u32 win[kPairsWaves][T][kWords][kW];
 };
@@ -1212,10 +1212,10 @@ __device__ __forceinline__ void pairs_store(void* w_ref, u64 idx, const float (&
 }
 
 // off: the chunk's entries of blob t's offset table in lane t (its start) and lane kMaxMany + t (its end); lane_bits: the lane
-// lengths of its records
-template <int T, bool WIDE, int DT>
+// lengths of its records; midway: called at most once, where loads for the next chunk cost no wait
+template <int T, bool WIDE, int DT, typename Midway>
 __device__ __forceinline__ void pairs_chunk(PairsLds<T, WIDE>& L, u32 wave, void* __restrict__ w_ref, u64 n, Workspace* ws, HostResult* host,
-                                            u32 c, u32 nchunks, u32 off, const u32 (&lane_bits)[T], u32 turns, u32 row_bits, u64 epoch) {
+                                            u32 c, u32 nchunks, u32 off, const u32 (&lane_bits)[T], u32 turns, u32 row_bits, u64 epoch, Midway& midway) {
     typedef PairsLds<T, WIDE> Lds;
     typedef typename Raw<DT>::type RowT;
     const u32 lane = lane_id();
@@ -1229,29 +1229,38 @@ __device__ __forceinline__ void pairs_chunk(PairsLds<T, WIDE>& L, u32 wave, void
         S.nw[t] = o1 - o0 - kLaneBitsWords;               // >= 1 (validated)
         loud = loud || L.zero_bits[t] == 0 || lane_bits[t] != L.zero_bits[t];
     }
-    if (!__any(loud)) {
+    const bool quiet = !__any(loud);
+    if (quiet) {
         // every lane has the length of merged symbols only (see zero_chunk_bits); if so, nothing changes and w_ref is not read
-        u32 nonzero = 0;
+        // (a payload of zero_bits per lane: a multiple of 512 words, the first of all blobs asked for at once; a word of one blob
+        // after the other, 5 blobs of a sparse update of 2^27 elements 200 us; chunks taken as below and so, 138)
+        typedef typename PairsWords<T, WIDE>::vec_any vec_any;
+        u32x4 x[T][2], any = {0, 0, 0, 0};
 #pragma unroll
         for (int t = 0; t < T; ++t)
-            for (u32 i = lane; i < S.nw[t]; i += kW) nonzero |= S.gw[t][i];
-        if (!__any(nonzero != 0)) return;
+#pragma unroll
+            for (u32 h = 0; h < 2; ++h) x[t][h] = *reinterpret_cast<const vec_any*>(S.gw[t] + 4 * (h * kW + lane));
+        midway();
+#pragma unroll
+        for (int t = 0; t < T; ++t) any |= x[t][0] | x[t][1];
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+            for (u32 i = 4 * (2 * kW + lane); i < S.nw[t]; i += 4 * kW) any |= *reinterpret_cast<const vec_any*>(S.gw[t] + i);
+        if (!__any((any.x | any.y | any.z | any.w) != 0)) return;
     }
+    u32 end[T];                                              // where the lane's strings end
     {
         PairsWords<T, WIDE> F[T];
 #pragma unroll
         for (int t = 0; t < T; ++t) {
-            S.p[t] = 31 + wave_incl_scan(lane_bits[t]) - lane_bits[t];
+            end[t] = 31 + wave_incl_scan(lane_bits[t]);
+            S.p[t] = end[t] - lane_bits[t];
             S.from[t] = 0;
             F[t].fetch(S, t, last);
         }
 #pragma unroll
         for (int t = 0; t < T; ++t) F[t].place(S, L, wave, t);
     }
-    u32 first_bit[T];
-#pragma unroll
-    for (int t = 0; t < T; ++t) first_bit[t] = S.p[t] + 32 * S.from[t];
-
     // The windows move on, up to `turns` of them every 4 rows: those of blob `turn` and the next ones', unless they will do until
     // the blob's next turn.  The words are asked for 4 rows before they are put in place.
     constexpr u32 kMost = Lds::kWords * 32 - 1 - Lds::kStepBits;
@@ -1309,6 +1318,7 @@ __device__ __forceinline__ void pairs_chunk(PairsLds<T, WIDE>& L, u32 wave, void
     for (; r < whole; r += PF) {
         place_words();                                       // (ahead of the rows, whose loads it would wait for)
         ask_for_words(rows - r);
+        if (r == kR / 2 && !quiet) midway();
         if (r + 2 * PF < whole) fetch(C, r + 2 * PF);
 #pragma unroll
         for (u32 k = 0; k < PF; k += 2) {
@@ -1340,7 +1350,7 @@ __device__ __forceinline__ void pairs_chunk(PairsLds<T, WIDE>& L, u32 wave, void
     }
     bool bad = false;
 #pragma unroll
-    for (int t = 0; t < T; ++t) bad = bad || (S.p[t] + 32 * S.from[t] - first_bit[t] != lane_bits[t]);
+    for (int t = 0; t < T; ++t) bad = bad || S.p[t] + 32 * S.from[t] != end[t];
     if (__any(bad) && lane == 0) raise_status(ws, host, epoch, 4u);
 }
 
@@ -1351,6 +1361,7 @@ __global__ __launch_bounds__(kPairsWaves * kW, T > 4 || WIDE ? 2 : 4) void k_dec
     typedef PairsLds<T, WIDE> Lds;
     __shared__ Lds L;
     const u32 tid = threadIdx.x, lane = tid & (kW - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    if (tid == 0) L.taken = kPairsWaves;
     if (tid == 0) L.stop = (__hip_atomic_load(&ws->dec_status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> 8) == epoch;
     __syncthreads();
     if (L.stop) return;                                  // a check found something: touch nothing
@@ -1408,28 +1419,40 @@ __global__ __launch_bounds__(kPairsWaves * kW, T > 4 || WIDE ? 2 : 4) void k_dec
         if (lane < Lds::kSyms && len) { L.lj[t][rank] = code << (32 - len); L.e_rank[t][rank] = (len << 4) | lane; }
     }
     __syncthreads();
-    // a chunk's entries of the T offset tables are asked for two chunks ahead, its lane lengths one
-    const u32 which = lane & (kMaxMany - 1);
-    const u32* off_tab = lane < 2 * kMaxMany && which < T ? L.off_tab[which] + lane / kMaxMany : nullptr;
-    auto offsets = [&](u64 c) { return off_tab && c < nchunks ? off_tab[c] : 0u; };
-    auto lengths = [&](u64 c, u32 off, u32 (&lane_bits)[T]) {
+    // A workgroup's wavefronts take its chunks as they come to them, one ahead: what a chunk costs differs a lot where some hold
+    // merged symbols only (dealt out in advance, 8 blobs of a sparse
+    // update of 2^27 elements 273 us, of 2^28 416; so, 186 and 252; of equally dense chunks the same to 1 %).  The next chunk's entries of the T offset tables are asked for
+    // ahead of this one, its lane lengths halfway through.
+    auto chunk = [&](u32 k) { return blockIdx.x + gridDim.x * k; };         // (few chunks: on as many compute units as there are)
+    auto take = [&]() {
+        u32 k = 0;
+        if (lane == 0) k = atomicAdd(&L.taken, 1u);
+        return chunk(__builtin_amdgcn_readfirstlane(k));
+    };
+    auto offsets = [&](u32 c) {
+        const u32 which = lane & (kMaxMany - 1);
+        return lane < 2 * kMaxMany && which < T && c < nchunks ? L.off_tab[which][c + lane / kMaxMany] : 0u;
+    };
+    auto lengths = [&](u32 c, u32 off, u32 (&lane_bits)[T]) {
         if (c >= nchunks) return;
 #pragma unroll
         for (int t = 0; t < T; ++t) lane_bits[t] = reinterpret_cast<const uint16_t*>(uniform_ptr(L.rec_base[t]) + 4 * (u64)read_lane(off, t))[lane];
     };
-    const u32 stride = gridDim.x * kPairsWaves;
-    u64 c = blockIdx.x + (u64)gridDim.x * wave;             // (few chunks: on as many compute units as there are)
-    u32 off = offsets(c), next = offsets(c + stride), bits[T] = {};
+    u32 c = chunk(wave);                                    // (at most 2^18 chunks, and 8 more takings than those per workgroup)
+    u32 off = offsets(c), bits[T] = {};
     lengths(c, off, bits);
     while (c < nchunks) {
-        const u32 after = offsets(c + 2 * (u64)stride);
+        const u32 after = take();
+        const u32 next = offsets(after);
         u32 next_bits[T] = {};
-        lengths(c + stride, next, next_bits);
-        pairs_chunk<T, WIDE, DT>(L, wave, w_ref, n, ws, host, (u32)c, nchunks, off, bits, turns, row_bits, epoch);
+        bool have = false;
+        auto midway = [&]() { lengths(after, next, next_bits); have = true; };
+        pairs_chunk<T, WIDE, DT>(L, wave, w_ref, n, ws, host, c, nchunks, off, bits, turns, row_bits, epoch, midway);
+        if (!have) lengths(after, next, next_bits);
 #pragma unroll
         for (int t = 0; t < T; ++t) bits[t] = next_bits[t];
-        off = next; next = after;
-        c += stride;
+        off = next;
+        c = after;
     }
 }
 // ----------------------------------------------------------------------------- launchers

@@ -128,3 +128,26 @@ def test_encode_of_chunks_with_few_parts_to_read(lc):
         times[kind] = best_us(lambda: lc.lc_encode(w, ref, 3, out))
     print("encode with one part in 16 and with all: %.1f us, %.1f us" % (times["one"], times["all"]), flush=True)
     assert times["one"] < 0.92 * times["all"], times         # (0.99 when all parts were read, 0.85 now)
+
+
+def test_long_lists_of_sparse_updates(lc):
+    """Five checkpoints of 2^27 elements in one call, none changed, or with a few heavy tails in a tenth of their chunks, against
+    four, which another kernel restores: a blob more costs no more than its share."""
+    n = 1 << 27
+    g = torch.Generator(device=DEV); g.manual_seed(9)
+    for kind, slow, now in (("unchanged", 1.47, 0.87), ("heavy tails", 1.42, 1.09)):
+        d = torch.zeros(n, device=DEV)
+        if kind == "heavy tails":
+            for _ in range(3):
+                d += torch.randn(n, generator=g, device=DEV) ** 2
+            d = 1e-4 * torch.randn(n, generator=g, device=DEV) / torch.sqrt(d / 3 + 1e-30) * (torch.rand(n, generator=g, device=DEV) >= 0.1)
+        blob, times, single, many = blob_of(lc, d, torch.zeros_like(d), 3), {}, torch.zeros(n, device=DEV), torch.zeros(n, device=DEV)
+        blobs = [blob.clone() for _ in range(5)]
+        for b in blobs:
+            lc.lc_decode(b, single)
+        lc.lc_decode_many(blobs, many)
+        assert torch.equal(single, many)
+        for count in (4, 5):
+            times[count] = best_us(lambda: lc.lc_decode_many(blobs[:count], many), reps=30)
+        print("%s, 4 and 5 blobs: %.1f us, %.1f us" % (kind, times[4], times[5]), flush=True)
+        assert times[5] < 0.5 * (slow + now) * times[4], (kind, times)
