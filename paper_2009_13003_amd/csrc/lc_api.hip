@@ -803,9 +803,8 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
         if (pairs > 1 && (!by_rows || (pairs >= (wide(g0) ? 3 : 5) && many(g0, g0 + pairs)))) {
             uint64_t bytes = 0;                                 // the longest blob's
             for (int i = g0; i < g0 + pairs; ++i) bytes = got.bytes[i] > bytes ? got.bytes[i] : bytes;
-            const uint32_t row_bits = nchunks ? (uint32_t)(16 * 8 * (bytes - area_at) / (nchunks * kW * kR)) : 0;
-            Timed tm(kSlotDecodeFused, s);
-            launch_decode_fused(list, g0, pairs, w_ref, n, dtype, ws, epoch, host, kPairsForm | (row_bits & 0xFFFFu), wide(g0), ds->tune, s);
+            const double row_bits = nchunks ? 8.0 * (double)(bytes - area_at) / (double)(nchunks * kW * kR) : 0;
+            { Timed tm(kSlotDecodeFused, s); launch_decode_pairs(list, g0, pairs, w_ref, n, dtype, ws, epoch, host, row_bits, wide(g0), ds->tune, s); }
             LC_HIP(hipGetLastError());
             g0 += pairs;
             continue;

@@ -1491,7 +1491,7 @@ template <int T, bool WIDE>
 static void launch_pairs_t(const BlobList& blobs, int first, void* w_ref, uint64_t n, int dtype, Workspace* ws, uint64_t epoch,
                            HostResult* host, u32 cus, u32 turns, u32 row_bits, hipStream_t s) {
     static_assert(sizeof(PairsLds<T, WIDE>) <= kLdsPerCu, "a workgroup fits a compute unit");
-    // (two workgroups of up to 4 blobs share a compute unit by their LDS and registers)
+    // (two workgroups of up to 4 blobs that keep at most 7 buckets share a compute unit by their LDS and registers)
     const u64 need = num_chunks_of(n), cap = (u64)cus * (2 * sizeof(PairsLds<T, WIDE>) + 2 * 1280 <= kLdsPerCu ? 2 : 1);
     const dim3 grid((u32)(need < cap ? need : cap)), wg(kPairsWaves * kW);
 #define LC_PAIRS(DT) hipLaunchKernelGGL((k_decode_pairs<T, WIDE, DT>), grid, wg, 0, s, blobs, (u32)first, w_ref, (u64)n, ws, (u32)num_chunks_of(n), (u64)epoch, host, turns, row_bits)
@@ -1501,12 +1501,12 @@ static void launch_pairs_t(const BlobList& blobs, int first, void* w_ref, uint64
 #undef LC_PAIRS
 }
 
-static void launch_pairs(const BlobList& blobs, int first, int count, void* w_ref, uint64_t n, int dtype, Workspace* ws,
-                         uint64_t epoch, HostResult* host, uint32_t row_bits, bool wide, const Tuning& tune,
-                         hipStream_t s) {
+void launch_decode_pairs(const BlobList& blobs, int first, int count, void* w_ref, uint64_t n, int dtype, Workspace* ws,
+                         uint64_t epoch, HostResult* host, double row_bits, bool wide, const Tuning& tune, hipStream_t s) {
+    if (n == 0) return;
     // A window's turn comes every 4 T / turns rows, with words as of 4 rows before: its strings should take no more than some
     // 170 (wide: 350) bits in that time.  (the fullest lane: some 15 % more than the average, and half a bit)
-    const double full = 1.15 / 16 * row_bits + 0.5, room = (wide ? 350 : 170) / full / 4 - 1;
+    const double full = 1.15 * row_bits + 0.5, room = (wide ? 350 : 170) / full / 4 - 1;
     const u32 turns = count <= room ? 1 : count <= 2 * room || count <= 4 ? 2 : 4, bits16 = (u32)(16 * full);
 #define LC_PAIRS(T, W) launch_pairs_t<T, W>(blobs, first, w_ref, n, dtype, ws, epoch, host, (u32)tune.num_cu, turns, bits16, s)
     switch (count) {
@@ -1550,7 +1550,6 @@ void launch_decode_fused(const BlobList& blobs, int first, int count, void* w_re
                          hipStream_t s) {
     const u64 nchunks = num_chunks_of(n);
     if (nchunks == 0) return;
-    if (pay_words & kPairsForm) { launch_pairs(blobs, first, count, w_ref, n, dtype, ws, epoch, host, pay_words & ~kPairsForm, long_codes, tune, s); return; }
     // one wavefront per workgroup; as many workgroups per compute unit as their LDS areas allow
     u64 per_cu = kLdsPerCu / fused_lds_bytes(count, pay_words);
     if (per_cu > (u64)tune.fused_waves_per_cu) per_cu = tune.fused_waves_per_cu;

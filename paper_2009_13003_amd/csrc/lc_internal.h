@@ -270,13 +270,13 @@ void launch_decode_one(const BlobList& blobs, int count, void* w_ref, uint64_t n
 // Applies blobs.p[first .. first+count), count <= kMaxFused, using dec_set[first ..].
 // pay_words: LDS words each wavefront gets for the payloads of one chunk of all `count` blobs; long_codes: some code is longer
 // than kDecLut1Bits.
-// With pay_words = kPairsForm | bits, by k_decode_pairs: 2 <= count <= kMaxMany (kMaxWide if wide).  bits: 16 times the
-// bits of a lane and row, on average, in the blob of the longest strings; long_codes is then wide: some blob keeps more than 7
-// buckets.
-constexpr uint32_t kPairsForm = 1u << 31;
 void launch_decode_fused(const BlobList& blobs, int first, int count, void* w_ref, uint64_t n, int dtype, Workspace* ws,
                          uint64_t epoch, HostResult* host, uint32_t pay_words, bool long_codes, const Tuning& tune,
                          hipStream_t s);
+// The same by k_decode_pairs, 2 <= count <= kMaxMany (kMaxWide if wide).  row_bits: the bits of a lane and row, on average, in the
+// blob of the longest strings; wide: some blob keeps more than 7 buckets.
+void launch_decode_pairs(const BlobList& blobs, int first, int count, void* w_ref, uint64_t n, int dtype, Workspace* ws,
+                         uint64_t epoch, HostResult* host, double row_bits, bool wide, const Tuning& tune, hipStream_t s);
 
 constexpr uint32_t kLdsPerCu = 160 * 1024;        // gfx950
 constexpr uint32_t kFusedMinWords = 1024;

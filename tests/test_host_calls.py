@@ -95,6 +95,7 @@ void launch_decode_one(const BlobList&, int count, void*, uint64_t, int, uint64_
     if (meet) for (int i = 0; i < count; ++i) host->bytes[i] = blob_bytes;
 }
 void launch_decode_fused(const BlobList&, int, int, void*, uint64_t, int, Workspace*, uint64_t, HostResult*, uint32_t, bool, const Tuning&, hipStream_t) { launched += 'f'; }
+void launch_decode_pairs(const BlobList&, int, int, void*, uint64_t, int, Workspace*, uint64_t, HostResult*, double, bool, const Tuning&, hipStream_t) { launched += 'f'; }
 size_t fused_lds_bytes(int, uint32_t) { return 1; }
 }  // namespace lc
 
