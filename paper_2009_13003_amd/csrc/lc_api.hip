@@ -103,7 +103,8 @@ uint64_t g_prof_n[kNumSlots];
 hipEvent_t g_ev[kNumSlots][2];
 bool g_ev_made = false;
 const char* const kSlotNames[kNumSlots] = {"k_reset", "k_hist", "k_table", "k_pack", "k_place", "k_spec_table", "k_spec_sweep",
-                                           "k_dec_check", "k_decode", "k_decode_fused", "k_hist_keys", "k_pack_keys", "k_verify", "k_encode_one", "k_decode_one"};
+                                           "k_dec_check", "k_decode", "k_decode_fused", "k_hist_keys", "k_pack_keys", "k_verify", "k_encode_one", "k_decode_one",
+                                           "k_decode_pairs"};
 
 int env_int(const char* name, int dflt, int lo, int hi) {
     const char* v = getenv(name);
@@ -149,6 +150,7 @@ void read_tuning(DeviceState& ds, int dev) {
     ds.tune.decode_blocks_per_cu = env_int("LC_TUNE_DECODE_BLOCKS_PER_CU", ds.tune.decode_blocks_per_cu, 1, 64);
     ds.tune.fused_waves_per_cu = env_int("LC_TUNE_FUSED_WAVES_PER_CU", ds.tune.fused_waves_per_cu, 1, 32);
     ds.tune.fused_min_waves_per_cu = env_int("LC_TUNE_FUSED_MIN_WAVES_PER_CU", ds.tune.fused_min_waves_per_cu, 1, 32);
+    ds.tune.pairs = env_int("LC_TUNE_PAIRS", ds.tune.pairs, 0, 2);
     ds.tuned = true;
 }
 
@@ -769,69 +771,91 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
         if ((got.dec_status >> 8) == epoch) return -(lc_ssize)(got.dec_status & 0xFF);
         return (lc_ssize)total;
     }
-    // Sweeps of several blobs, by one of two kernels.  k_decode_pairs takes up to 8 blobs (4 where some keep more than 7 buckets) at
-    // a time, all alike in that; a run of them that takes several sweeps is shared out evenly.  It wins where it saves
-    // sweeps, once there is a chunk for most wavefronts it runs: k_decode_fused / it, us, fp32: 3 bits, 2^25 elements, 2 to 4
-    // blobs 81 86 90 / 93 99 104, 5 blobs 145 / 110, 8 blobs 152 / 145, 2^26 8 blobs 270 / 217, 2^28.4 1,287 / 945; 4 bits
-    // 2^25 2, 3, 4, 8 blobs 88 141 150 269 / 100 118 129 226, ten to fifty layers' 435 to 445 / 213 to 336; by chunks, 8 blobs at 3
-    // bits: 4 109 to 131 / 110 to 123, 15 95 to 111 / 112 to 122, 64 95 to 123 / 116, 245 102 / 110, 733 114 / 113, and at 2 bits
-    // 15 96 to 112 / 93 to 100, 64 97 to 111 / 96 to 104 (6 blobs 76 / 80): a few chunks keep too few wavefronts busy to hide the wider look-up, but
-    // where at most 3 buckets are kept.  Arrays off alignment, for which the other has a slow form
-    // only, 2.1 to 4.1 times as fast.
-    // k_decode_fused takes up to kMaxFused.  Its LDS payload area is sized to 1.1 x the blobs'
-    // average chunk payloads (a chunk above that still decodes, from memory), and a sweep takes only as many
-    // blobs as leave room for fused_min_waves_per_cu wavefronts per compute unit.  Blobs with codes longer than
-    // the first decode table (7 bits) are grouped apart from those without: they take the kernel's LONG form.
+    // Sweeps of several blobs, by one of two kernels.
+    // k_decode_fused takes up to 8 blobs.  Its LDS payload area is sized to 1.1 x the blobs' average chunk payloads (a chunk above
+    // that still decodes, from memory), and a sweep takes only as many blobs as leave room for fused_min_waves_per_cu wavefronts
+    // per compute unit: 4 at 1.7 bits per element, some 6 sparse ones.  Blobs with codes longer than the first decode table (7
+    // bits) are grouped apart from those without: they take the kernel's LONG form.  More than fit a sweep are shared out evenly.
+    // k_decode_pairs takes up to 8, or 4 where some keep more than 7 buckets (16 symbols): runs of blobs alike in that, shared out
+    // evenly.  The first / the second, whole calls, us, fp32, by chunks and blobs:
+    //   3 bits, one scale: 64 chunks, 8 blobs 95 / 106; 600, 5, 8, 12: 92 / 90, 113 / 113, 155 / 166; 800, 5, 8, 12: 96 / 91, 114 / 116,
+    //     160 / 172; 1,200, 5, 6, 8, 12: 108 / 96, 114 / 105, 125 / 125, 174 / 187; 2,048, 4, 5, 8, 12: 90 / 97, 141 / 108, 152 / 139, 213 /
+    //     207; 8,192, 5, 8: 498 / 300, 657 / 403; 21,657, 8: 1,725 / 1,005
+    //   2 bits: 64, 8, 12: 96 / 95, 122 / 132; 800, 5, 8, 12: 81 / 80, 111 / 102, 152 / 146; 2,048, 8: 152 / 117
+    //   3 bits, heavy tails: 64, 8: 99 / 96; 600, 5, 8: 85 / 79, 120 / 100; 800, 8: 127 / 100; 8,192, 5, 8: 172 / 138, 268 / 186
+    //   4 bits: 4, 3: 101 / 77; 64, 2, 3, 8: 70 / 71, 102 / 79, 196 / 149; 2,048, 2, 3, 8: 89 / 103, 144 / 120, 278 / 227; ten layers', 64, 4:
+    //     207 / 147, 8,192, 3, 8: 1,030 / 354, 2,523 / 865; of a short vector with hardly a kept symbol, whose codes all have at most 7
+    //     bits, 4, 3, 6: 56 / 66, 75 / 103
+    // So: of 16 symbols 3 and more blobs by the second, unless all their codes are short and the first takes as few sweeps.  Of 8
+    // symbols 5 and more, from 6 chunks per compute unit on, and from 3 on unless the first takes dense ones in full sweeps of 4.
+    // (Left: sparse lists of one to three chunks per compute unit.)  Arrays off alignment, for which the first has a slow form
+    // only, 2.1 to 4.1 times as fast by the second.
     const uint64_t nchunks = num_chunks_of(n), area_at = chunk_area_of(nchunks);
     const size_t lds_budget = kLdsPerCu / (size_t)ds->tune.fused_min_waves_per_cu;
     auto pay_words_of = [](double words) {
         uint32_t w = ((uint32_t)(words * 1.1) + 63u) & ~63u;
         return w < kFusedMinWords ? kFusedMinWords : w;
     };
-    const uint64_t cus = (uint64_t)ds->tune.num_cu;
-    auto many = [&](int i, int end) {                           // blobs i to end - 1
-        if (nchunks >= 3 * cus || 64 * nchunks <= cus) return true;
-        while (i < end && got.kept[i] <= 3) ++i;
-        return i == end && 4 * nchunks <= cus;
-    };
-    const bool by_rows = !misaligned(w_ref, dtype == LC_F32 ? 16 : 8);
-    auto wide = [&](int i) { return got.kept[i] > 7; };
-    for (int g0 = 0; g0 < count;) {
-        int run = 1;
-        while (g0 + run < count && wide(g0 + run) == wide(g0)) ++run;
-        const int most = wide(g0) ? kMaxWide : kMaxMany, sweeps = (run + most - 1) / most, pairs = (run + sweeps - 1) / sweeps;
-        if (pairs > 1 && (!by_rows || (pairs >= (wide(g0) ? 3 : 5) && many(g0, g0 + pairs)))) {
-            uint64_t bytes = 0;                                 // the longest blob's
-            for (int i = g0; i < g0 + pairs; ++i) bytes = got.bytes[i] > bytes ? got.bytes[i] : bytes;
-            const double row_bits = nchunks ? 8.0 * (double)(bytes - area_at) / (double)(nchunks * kW * kR) : 0;
-            { Timed tm(kSlotDecodeFused, s); launch_decode_pairs(list, g0, pairs, w_ref, n, dtype, ws, epoch, host, row_bits, wide(g0), ds->tune, s); }
-            LC_HIP(hipGetLastError());
-            g0 += pairs;
-            continue;
-        }
-        const bool short_codes = got.max_len[g0] <= kDecLut1Bits;
+    // the blobs from i on that a sweep of k_decode_fused takes, up to `end`, and the payload words of them together
+    auto fused = [&](int i, int end, double* words) {
+        const bool short_codes = got.max_len[i] <= kDecLut1Bits;
         int T = 0;
-        double words = 0;
-        while (T < run && T < kMaxFused && (got.max_len[g0 + T] <= kDecLut1Bits) == short_codes) {
+        *words = 0;
+        while (i + T < end && T < kMaxMany && (got.max_len[i + T] <= kDecLut1Bits) == short_codes) {
             if (nchunks) {
-                const double avg = (double)(got.bytes[g0 + T] - area_at) / 4.0 / (double)nchunks - kLaneBitsWords + 6.0;
-                if (T > 0 && fused_lds_bytes(T + 1, pay_words_of(words + avg)) > lds_budget) break;
-                words += avg;
+                const double avg = (double)(got.bytes[i + T] - area_at) / 4.0 / (double)nchunks - kLaneBitsWords + 6.0;
+                if (T > 0 && fused_lds_bytes(T + 1, pay_words_of(*words + avg)) > lds_budget) break;
+                *words += avg;
             }
             ++T;
         }
-        {
-            const uint32_t pay_words = pay_words_of(words);
+        return T;
+    };
+    auto fused_sweeps = [&](int i, int end) {
+        int sweeps = 0;
+        double words;
+        for (; i < end; ++sweeps) i += fused(i, end, &words);
+        return sweeps;
+    };
+    const uint64_t cus = (uint64_t)ds->tune.num_cu;
+    const bool by_rows = !misaligned(w_ref, dtype == LC_F32 ? 16 : 8);
+    auto wide = [&](int i) { return got.kept[i] > 7; };
+    const int slots[] = {kSlotDecCheck, kSlotDecodeFused, kSlotDecodePairs};
+    collect(slots, 1);
+    for (int g0 = 0; g0 < count;) {
+        int run = 1;
+        double words = 0;
+        while (g0 + run < count && wide(g0 + run) == wide(g0)) ++run;
+        int T = fused(g0, g0 + run, &words);
+        const int most = wide(g0) ? kMaxWide : kMaxMany, sweeps = (run + most - 1) / most, pairs = (run + sweeps - 1) / sweeps;
+        bool longs = false;
+        for (int i = g0; i < g0 + run; ++i) longs = longs || got.max_len[i] > kDecLut1Bits;
+        const bool worth = wide(g0) ? pairs >= 3 && (longs || sweeps < fused_sweeps(g0, g0 + run))
+                                    : pairs >= 5 && nchunks >= 3 * cus && (nchunks >= 6 * cus || T > 4 || run % T != 0);
+        const bool by_pairs = pairs > 1 && (!by_rows || ds->tune.pairs == 1 || (ds->tune.pairs == 0 && worth));
+        if (by_pairs) {
+            uint64_t bytes = 0;                                 // the longest blob's
+            for (int i = g0; i < g0 + pairs; ++i) bytes = got.bytes[i] > bytes ? got.bytes[i] : bytes;
+            const double row_bits = nchunks ? 8.0 * (double)(bytes - area_at) / (double)(nchunks * kW * kR) : 0;
+            Timed tm(kSlotDecodePairs, s);
+            launch_decode_pairs(list, g0, pairs, w_ref, n, dtype, ws, epoch, host, row_bits, wide(g0), ds->tune, s);
+            T = pairs;
+        } else {
+            // (shared out evenly over as many sweeps as the blobs of like code lengths take)
+            const bool short_codes = got.max_len[g0] <= kDecLut1Bits;
+            int like = 1;
+            while (like < run && (got.max_len[g0 + like] <= kDecLut1Bits) == short_codes) ++like;
+            const int rounds = fused_sweeps(g0, g0 + like), even = (like + rounds - 1) / rounds;
+            if (even < T && fused_sweeps(g0 + even, g0 + like) < rounds) T = fused(g0, g0 + even, &words);
             Timed tm(kSlotDecodeFused, s);
-            launch_decode_fused(list, g0, T, w_ref, n, dtype, ws, epoch, host, pay_words, !short_codes, ds->tune, s);
+            launch_decode_fused(list, g0, T, w_ref, n, dtype, ws, epoch, host, pay_words_of(words), !short_codes, ds->tune, s);
         }
         LC_HIP(hipGetLastError());
         g0 += T;
+        if (g_prof) { LC_HIP(hipStreamSynchronize(s)); collect(slots + (by_pairs ? 2 : 1), 1); }     // (each sweep has a kernel's one pair of events)
     }
     if (!release(area, s)) return -LC_ERR_HIP;
     LC_HIP(hipStreamSynchronize(s));
-    int slots[2] = {kSlotDecCheck, kSlotDecodeFused};
-    collect(slots, 2);
     if ((got.dec_status >> 8) == epoch) return -(lc_ssize)(got.dec_status & 0xFF);
     return (lc_ssize)total;
 }

@@ -695,7 +695,7 @@ __global__ __launch_bounds__(64) void kb_decode(BatchDecArgs a) {
 
 // ----------------------------------------------------------------------------- k_decode_fused
 // Restore from several checkpoints in one sweep (Section 3, C1: u_t = u_0 + sum of the decoded
-// deltas; Section 3.2, checkpoint merging): up to kMaxFused blobs of the same n are decoded side
+// deltas; Section 3.2, checkpoint merging): up to kMaxMany blobs of the same n are decoded side
 // by side and their values added to w_ref in blob order, one fp32 add per blob and element, so
 // the result equals that of applying the blobs one call after the other, with one read and
 // one write of w_ref instead of one per blob.
@@ -1013,8 +1013,8 @@ __global__ __launch_bounds__(64) void k_decode_fused(BlobList blobs, u32 first, 
     }
 }
 // ----------------------------------------------------------------------------- k_decode_pairs
-// The same for more blobs in one sweep, up to 8 where the other kernel takes 4.  What stands in the way of that is the LDS: with
-// the payloads of whole chunks in it, 8 blobs leave room for 4 wavefronts, one per SIMD, each of which waits out its own
+// The same for more blobs in one sweep, up to 8 where the other kernel takes 4 (dense ones; of sparse ones some 6).  What stands in the way of
+// that is the LDS: with the payloads of whole chunks in it, 8 blobs leave room for 4 wavefronts, one per SIMD, each of which waits out its own
 // look-ups (8 blobs of 355 M elements 1,470 us, two sweeps of 4 by the other kernel 1,240).
 // - Of its strings a lane has a window of kWords words per blob in LDS, 2 KB per blob and wavefront: two wavefronts per SIMD.  A
 //   lane's windows lie in a bank of its own, so that no two lanes meet when they read at places of their own; a read at any
@@ -1541,7 +1541,8 @@ static void launch_fused_t(const BlobList& blobs, int first, void* w_ref, uint64
 }
 
 size_t fused_lds_bytes(int count, uint32_t pay_words) {
-    static const size_t head[kMaxFused] = {sizeof(FusedHead<1>), sizeof(FusedHead<2>), sizeof(FusedHead<3>), sizeof(FusedHead<4>)};
+    static const size_t head[kMaxMany] = {sizeof(FusedHead<1>), sizeof(FusedHead<2>), sizeof(FusedHead<3>), sizeof(FusedHead<4>),
+                                          sizeof(FusedHead<5>), sizeof(FusedHead<6>), sizeof(FusedHead<7>), sizeof(FusedHead<8>)};
     return head[count - 1] + 4 * (size_t)(pay_words + kFusedSlack);
 }
 
@@ -1561,7 +1562,11 @@ void launch_decode_fused(const BlobList& blobs, int first, int count, void* w_re
         case 1: launch_fused_t<1>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
         case 2: launch_fused_t<2>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
         case 3: launch_fused_t<3>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
-        default: launch_fused_t<4>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
+        case 4: launch_fused_t<4>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
+        case 5: launch_fused_t<5>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
+        case 6: launch_fused_t<6>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
+        case 7: launch_fused_t<7>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
+        default: launch_fused_t<8>(blobs, first, w_ref, n, dtype, ws, epoch, host, b, pay_words, long_codes, s); break;
     }
 }
 

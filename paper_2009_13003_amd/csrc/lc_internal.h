@@ -44,9 +44,8 @@ struct DecInfo {
     uint32_t rep_hi[kMaxSym];    // binary64 blobs: high halves of the representatives (rep_bits holds the low halves)
 };
 
-constexpr int kMaxMany = 8;  // blobs one restore sweep of several can apply (k_decode_pairs),
-constexpr int kMaxWide = 4;  // ... if one of them keeps more than 7 buckets,
-constexpr int kMaxFused = 4; // ... of the other form (k_decode_fused)
+constexpr int kMaxMany = 8;  // blobs one restore sweep of several can apply,
+constexpr int kMaxWide = 4;  // ... by k_decode_pairs, if one of them keeps more than 7 buckets
 constexpr int kMaxSets = 64; // blobs one lc_decode_many call accepts (= LC_MAX_MANY), each with a set of its own
 
 // Everything the decode sweep needs to know about one blob, written by k_dec_check.
@@ -151,7 +150,8 @@ __host__ __device__ inline uint32_t slot_words_of(int nbits) { return kLaneBitsW
 __host__ __device__ inline uint64_t chunk_area_of(uint64_t nchunks) { return kHeaderBytes + (4 * (nchunks + 1) + 15) / 16 * 16; }
 
 enum Slot { kSlotReset = 0, kSlotHist, kSlotTable, kSlotPack, kSlotPlace, kSlotSpecTable, kSlotSpecSweep,
-            kSlotDecCheck, kSlotDecode, kSlotDecodeFused, kSlotHistKeys, kSlotPackKeys, kSlotVerify, kSlotEncodeOne, kSlotDecodeOne, kNumSlots };
+            kSlotDecCheck, kSlotDecode, kSlotDecodeFused, kSlotHistKeys, kSlotPackKeys, kSlotVerify, kSlotEncodeOne, kSlotDecodeOne,
+            kSlotDecodePairs, kNumSlots };
 
 // Launch shapes; defaults chosen by measurement, overridable through LC_TUNE_* environment
 // variables (read once) for sweeps.
@@ -172,6 +172,7 @@ struct Tuning {
     int decode_blocks_per_cu = 9;      // ... of a long restore (LDS lets 2 run at once; more, smaller shares even out unlike chunks)
     int fused_waves_per_cu = 16;       // most wavefronts per compute unit
     int fused_min_waves_per_cu = 8;    // a sweep takes as many blobs as still leave LDS for this many
+    int pairs = 0;                     // lists of several blobs by k_decode_pairs: 0 where that is faster (see decode_many_impl), 1 all, 2 none
 };
 
 // Launchers (lc_encode.hip, lc_decode.hip).
@@ -267,7 +268,7 @@ void launch_decode(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, Work
 // met: as launch_encode_one.
 void launch_decode_one(const BlobList& blobs, int count, void* w_ref, uint64_t n, int dtype, uint64_t max_total, Workspace* ws, uint64_t epoch,
                        HostResult* host, uint64_t (&met)[kMeetLines], int looks, hipStream_t s);
-// Applies blobs.p[first .. first+count), count <= kMaxFused, using dec_set[first ..].
+// Applies blobs.p[first .. first+count), count <= kMaxMany, using dec_set[first ..].
 // pay_words: LDS words each wavefront gets for the payloads of one chunk of all `count` blobs; long_codes: some code is longer
 // than kDecLut1Bits.
 void launch_decode_fused(const BlobList& blobs, int first, int count, void* w_ref, uint64_t n, int dtype, Workspace* ws,

@@ -59,11 +59,12 @@ MAIN = r"""
 
 // ---- what is launched: a letter each, and what the stand-ins leave for the host
 //   0 k_reset   r k_reset_one   E / D one launch   h first sweep   t table   s single sweep   p second sweep   P placement
-//   c check     v verify        d restore          f fused restore
+//   c check     v verify        d restore          f / g fused restore, by symbols or by pairs of them
 static std::string launched;
 static bool meet = true;                 // whether the workgroups of a call in one launch meet
 static uint64_t blob_bytes = 1000;       // of every blob that is checked or restored, and its longest code
-static uint32_t blob_max_len = 3;
+static uint32_t blob_max_len = 3, blob_kept = 3;
+static int fused_fits = 8;               // blobs that a fused sweep by symbols takes at once
 static int fail_launches = 0;            // the next launches that fail
 static std::function<void()> waiting;    // runs (once) in a thread that waits for its stream
 hipError_t hipGetLastError() { if (fail_launches > 0) { --fail_launches; return hipErrorUnknown; } return 0; }
@@ -87,7 +88,7 @@ void launch_batch_encode(const BatchArgs&, const Tuning&, hipStream_t) {}
 void launch_batch_decode(const BatchDecArgs&, const Tuning&, hipStream_t) {}
 void launch_dec_check(const BlobList&, int, int count, uint64_t, int, uint64_t, Workspace*, uint64_t, HostResult* host, hipStream_t) {
     launched += 'c';
-    for (int i = 0; i < count; ++i) { host->bytes[i] = blob_bytes; host->max_len[i] = blob_max_len; }
+    for (int i = 0; i < count; ++i) { host->bytes[i] = blob_bytes; host->max_len[i] = blob_max_len; host->kept[i] = blob_kept; }
 }
 void launch_decode(const uint8_t*, void* w_ref, uint64_t, int, Workspace*, int, uint64_t, HostResult*, const Tuning&, hipStream_t) { launched += w_ref ? 'd' : 'v'; }
 void launch_decode_one(const BlobList&, int count, void*, uint64_t, int, uint64_t, Workspace*, uint64_t, HostResult* host, uint64_t (&)[kMeetLines], int, hipStream_t) {
@@ -95,8 +96,8 @@ void launch_decode_one(const BlobList&, int count, void*, uint64_t, int, uint64_
     if (meet) for (int i = 0; i < count; ++i) host->bytes[i] = blob_bytes;
 }
 void launch_decode_fused(const BlobList&, int, int, void*, uint64_t, int, Workspace*, uint64_t, HostResult*, uint32_t, bool, const Tuning&, hipStream_t) { launched += 'f'; }
-void launch_decode_pairs(const BlobList&, int, int, void*, uint64_t, int, Workspace*, uint64_t, HostResult*, double, bool, const Tuning&, hipStream_t) { launched += 'f'; }
-size_t fused_lds_bytes(int, uint32_t) { return 1; }
+void launch_decode_pairs(const BlobList&, int, int, void*, uint64_t, int, Workspace*, uint64_t, HostResult*, double, bool, const Tuning&, hipStream_t) { launched += 'g'; }
+size_t fused_lds_bytes(int count, uint32_t) { return count <= fused_fits ? 1 : 1 << 20; }
 }  // namespace lc
 
 static int wrong = 0;
@@ -121,6 +122,7 @@ static lc_ssize decode_many_t(int count, uint64_t n, int dtype, int offset = 0) 
     return lc_decode_many_t(blobs, count, mem[0] + offset, n, dtype, stream(1));
 }
 static void ok(lc_ssize r, lc_ssize want = 1000) { if (r != want) { printf("result %lld, not %lld\n", (long long)r, (long long)want); ++wrong; } }
+static std::string times(int k, const char* x) { std::string r; while (k--) r += x; return r; }
 static void fresh() { lc_shutdown(); meet = true; waiting = nullptr; launched.clear(); }
 // the one scratch area of a caller: every stream's calls take it
 static void* caller_area() {
@@ -196,7 +198,6 @@ static void scenarios() {
 """
 
 REST = r"""
-static std::string times(int k, const char* x) { std::string r; while (k--) r += x; return r; }
 static void scenarios() {
     // the calls behind one that was given up do not try: 16, then twice as many each time, up to 1024, until one is not given up
     for (int what = 0; what < 3; ++what) {
@@ -251,6 +252,35 @@ static void scenarios() {
     is("D", 8, small, LC_F64); is("cdd", 2, large, LC_F64); is("cdd", 2, beyond, LC_F64);
     blob_bytes = large / 4;
     is("cD", 2, large, LC_F64); is("cD", 8, large, LC_F64, 8); is("cdd", 2, beyond, LC_F64);
+    // which of the two kernels takes a list, and in how many sweeps: of few symbols the second from 5 blobs and 3 or 6 chunks per
+    // compute unit on, of 16 from 3 blobs on; either shares them out evenly
+    blob_bytes = 1000;
+    for (uint64_t per_cu : {2, 3, 5, 6, 20})
+        for (int fits : {2, 4, 6, 8})
+            for (int count = 2; count <= 20; ++count) {
+                const int in_fused = (count + fits - 1) / fits;
+                const uint64_t size = (per_cu * 256 + 1) * 16384;
+                fused_fits = fits;
+                for (uint32_t kept : {0u, 7u}) {
+                    blob_kept = kept;
+                    std::string want = "c";
+                    for (int left = count; left > 0;) {              // (the last few of 9, 10, ... may be too few for the second)
+                        const int sweeps = (left + 7) / 8, pairs = (left + sweeps - 1) / sweeps, rounds = (left + fits - 1) / fits;
+                        const bool second = pairs >= 5 && per_cu >= 3 && (per_cu >= 6 || fits > 4 || left % fits);
+                        want += second ? "g" : "f";
+                        left -= second ? pairs : (left + rounds - 1) / rounds;
+                    }
+                    is(want.c_str(), count, size, LC_F32);
+                    is(("c" + times((count + 7) / 8, "g")).c_str(), count, size, LC_BF16, 2);
+                }
+                blob_kept = 15;
+                const int sweeps = (count + 3) / 4;
+                if (count > 2 && count != 5) is(("c" + times(sweeps < in_fused ? sweeps : in_fused, sweeps < in_fused ? "g" : "f")).c_str(), count, size, LC_F16);
+                blob_max_len = 8;
+                if (count > 2 && count != 5) is(("c" + times(sweeps, "g")).c_str(), count, size, LC_F32);
+                blob_max_len = 3;
+            }
+    blob_kept = 3; fused_fits = 8;
     // given up behind the check
     blob_bytes = 1000; blob_max_len = 9; meet = false;
     is("cDcff", 16, small, LC_F32);
