@@ -776,8 +776,7 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
     // that still decodes, from memory), and a sweep takes only as many blobs as leave room for fused_min_waves_per_cu wavefronts
     // per compute unit: 4 at 1.7 bits per element, some 6 sparse ones.  Blobs with codes longer than the first decode table (7
     // bits) are grouped apart from those without: they take the kernel's LONG form.  More than fit a sweep are shared out evenly.
-    // k_decode_pairs takes up to 8, or 4 where some keep more than 7 buckets (16 symbols): runs of blobs alike in that, shared out
-    // evenly.  The first / the second, whole calls, us, fp32, by chunks and blobs:
+    // k_decode_pairs takes up to 8, or 4 where some keep more than 7 buckets (16 symbols); also shared out evenly.  The first / the second, whole calls, us, fp32, by chunks and blobs:
     //   3 bits, one scale: 64 chunks, 8 blobs 95 / 106; 600, 5, 8, 12: 92 / 90, 113 / 113, 155 / 166; 800, 5, 8, 12: 96 / 91, 114 / 116,
     //     160 / 172; 1,200, 5, 6, 8, 12: 108 / 96, 114 / 105, 125 / 125, 174 / 187; 2,048, 4, 5, 8, 12: 90 / 97, 141 / 108, 152 / 139, 213 /
     //     207; 8,192, 5, 8: 498 / 300, 657 / 403; 21,657, 8: 1,725 / 1,005
@@ -788,7 +787,9 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
     //     bits, 4, 3, 6: 56 / 66, 75 / 103
     // So: of 16 symbols 3 and more blobs by the second, unless all their codes are short and the first takes as few sweeps.  Of 8
     // symbols 5 and more, from 6 chunks per compute unit on, and from 3 on unless the first takes dense ones in full sweeps of 4.
-    // (Left: sparse lists of one to three chunks per compute unit.)  Arrays off alignment, for which the first has a slow form
+    // (Left: sparse lists of one to three chunks per compute unit.)  Between such runs of 8 symbols, blobs of either kind go
+    // together, since the tables of 16 hold them too: 3 and 4 bits in turn, 8 blobs, told apart and so a sweep each / together, 64
+    // chunks 249 / 140, 600 307 / 154, 8,192 1,880 / 599, off alignment 600 557 / 155.  Arrays off alignment, for which the first has a slow form
     // only, 2.1 to 4.1 times as fast by the second.
     const uint64_t nchunks = num_chunks_of(n), area_at = chunk_area_of(nchunks);
     const size_t lds_budget = kLdsPerCu / (size_t)ds->tune.fused_min_waves_per_cu;
@@ -818,41 +819,60 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
         return sweeps;
     };
     const uint64_t cus = (uint64_t)ds->tune.num_cu;
-    const bool by_rows = !misaligned(w_ref, dtype == LC_F32 ? 16 : 8);
+    const bool by_rows = !misaligned(w_ref, dtype == LC_F32 ? 16 : 8), all = !by_rows || ds->tune.pairs == 1, none = by_rows && ds->tune.pairs == 2;
     auto wide = [&](int i) { return got.kept[i] > 7; };
+    auto shared = [](int blobs, int most) { const int sweeps = (blobs + most - 1) / most; return (blobs + sweeps - 1) / sweeps; };
+    auto run_of = [&](int i) {                                  // blobs of at most 8 symbols from i on
+        const int first = i;
+        while (i < count && !wide(i)) ++i;
+        return i - first;
+    };
+    auto own_sweeps = [&](int i, int run) {                     // whether k_decode_pairs takes such a run in sweeps of its own
+        double words;
+        if (none || run == 0 || shared(run, kMaxMany) < 5) return false;
+        if (all || nchunks >= 6 * cus) return true;
+        const int T = fused(i, i + run, &words);
+        return nchunks >= 3 * cus && (T > 4 || run % T != 0);
+    };
     const int slots[] = {kSlotDecCheck, kSlotDecodeFused, kSlotDecodePairs};
     collect(slots, 1);
     for (int g0 = 0; g0 < count;) {
-        int run = 1;
+        // the blobs from g0 on up to the next run that has sweeps of its own: of 8 symbols only, or some of 16
+        const int run = run_of(g0);
+        int end = g0 + run, T = 0, used = 1;
         double words = 0;
-        while (g0 + run < count && wide(g0 + run) == wide(g0)) ++run;
-        int T = fused(g0, g0 + run, &words);
-        const int most = wide(g0) ? kMaxWide : kMaxMany, sweeps = (run + most - 1) / most, pairs = (run + sweeps - 1) / sweeps;
         bool longs = false;
-        for (int i = g0; i < g0 + run; ++i) longs = longs || got.max_len[i] > kDecLut1Bits;
-        const bool worth = wide(g0) ? pairs >= 3 && (longs || sweeps < fused_sweeps(g0, g0 + run))
-                                    : pairs >= 5 && nchunks >= 3 * cus && (nchunks >= 6 * cus || T > 4 || run % T != 0);
-        const bool by_pairs = pairs > 1 && (!by_rows || ds->tune.pairs == 1 || (ds->tune.pairs == 0 && worth));
-        if (by_pairs) {
+        if (!own_sweeps(g0, run)) {
+            while (end < count) {
+                const int next = run_of(++end);
+                if (own_sweeps(end, next)) break;
+                end += next;
+            }
+        }
+        const bool sixteen = end > g0 + run;
+        const int pairs = shared(end - g0, sixteen ? kMaxWide : kMaxMany);
+        for (int i = g0; i < end; ++i) longs = longs || got.max_len[i] > kDecLut1Bits;
+        if (pairs > 1 && (all || (sixteen ? !none && pairs >= 3 && pairs > run && (longs || (end - g0 + pairs - 1) / pairs < fused_sweeps(g0, end)) : own_sweeps(g0, run)))) {
             uint64_t bytes = 0;                                 // the longest blob's
             for (int i = g0; i < g0 + pairs; ++i) bytes = got.bytes[i] > bytes ? got.bytes[i] : bytes;
             const double row_bits = nchunks ? 8.0 * (double)(bytes - area_at) / (double)(nchunks * kW * kR) : 0;
             Timed tm(kSlotDecodePairs, s);
-            launch_decode_pairs(list, g0, pairs, w_ref, n, dtype, ws, epoch, host, row_bits, wide(g0), ds->tune, s);
-            T = pairs;
+            launch_decode_pairs(list, g0, pairs, w_ref, n, dtype, ws, epoch, host, row_bits, pairs > run, ds->tune, s);
+            T = pairs; used = 2;
         } else {
+            T = fused(g0, end, &words);
             // (shared out evenly over as many sweeps as the blobs of like code lengths take)
             const bool short_codes = got.max_len[g0] <= kDecLut1Bits;
-            int like = 1;
-            while (like < run && (got.max_len[g0 + like] <= kDecLut1Bits) == short_codes) ++like;
-            const int rounds = fused_sweeps(g0, g0 + like), even = (like + rounds - 1) / rounds;
-            if (even < T && fused_sweeps(g0 + even, g0 + like) < rounds) T = fused(g0, g0 + even, &words);
+            int like = g0 + 1;
+            while (like < end && (got.max_len[like] <= kDecLut1Bits) == short_codes) ++like;
+            const int rounds = fused_sweeps(g0, like), even = (like - g0 + rounds - 1) / rounds;
+            if (even < T && fused_sweeps(g0 + even, like) < rounds) T = fused(g0, g0 + even, &words);
             Timed tm(kSlotDecodeFused, s);
             launch_decode_fused(list, g0, T, w_ref, n, dtype, ws, epoch, host, pay_words_of(words), !short_codes, ds->tune, s);
         }
         LC_HIP(hipGetLastError());
         g0 += T;
-        if (g_prof) { LC_HIP(hipStreamSynchronize(s)); collect(slots + (by_pairs ? 2 : 1), 1); }     // (each sweep has a kernel's one pair of events)
+        if (g_prof) { LC_HIP(hipStreamSynchronize(s)); collect(slots + used, 1); }     // (each sweep has a kernel's one pair of events)
     }
     if (!release(area, s)) return -LC_ERR_HIP;
     LC_HIP(hipStreamSynchronize(s));

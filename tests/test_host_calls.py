@@ -64,6 +64,7 @@ static std::string launched;
 static bool meet = true;                 // whether the workgroups of a call in one launch meet
 static uint64_t blob_bytes = 1000;       // of every blob that is checked or restored, and its longest code
 static uint32_t blob_max_len = 3, blob_kept = 3;
+static std::vector<uint32_t> kept_of;    // ... of each blob of a list, where they differ
 static int fused_fits = 8;               // blobs that a fused sweep by symbols takes at once
 static int fail_launches = 0;            // the next launches that fail
 static std::function<void()> waiting;    // runs (once) in a thread that waits for its stream
@@ -88,7 +89,7 @@ void launch_batch_encode(const BatchArgs&, const Tuning&, hipStream_t) {}
 void launch_batch_decode(const BatchDecArgs&, const Tuning&, hipStream_t) {}
 void launch_dec_check(const BlobList&, int, int count, uint64_t, int, uint64_t, Workspace*, uint64_t, HostResult* host, hipStream_t) {
     launched += 'c';
-    for (int i = 0; i < count; ++i) { host->bytes[i] = blob_bytes; host->max_len[i] = blob_max_len; host->kept[i] = blob_kept; }
+    for (int i = 0; i < count; ++i) { host->bytes[i] = blob_bytes; host->max_len[i] = blob_max_len; host->kept[i] = kept_of.empty() ? blob_kept : kept_of[i]; }
 }
 void launch_decode(const uint8_t*, void* w_ref, uint64_t, int, Workspace*, int, uint64_t, HostResult*, const Tuning&, hipStream_t) { launched += w_ref ? 'd' : 'v'; }
 void launch_decode_one(const BlobList&, int count, void*, uint64_t, int, uint64_t, Workspace*, uint64_t, HostResult* host, uint64_t (&)[kMeetLines], int, hipStream_t) {
@@ -280,6 +281,24 @@ static void scenarios() {
                 if (count > 2 && count != 5) is(("c" + times(sweeps, "g")).c_str(), count, size, LC_F32);
                 blob_max_len = 3;
             }
+    // lists of both kinds: one blob of more than 8 symbols takes its neighbours along, but for a run that has sweeps of its own
+    auto mixed = [&](const char* want, std::vector<uint32_t> kept, uint64_t chunks, int offset = 0) {
+        kept_of = kept;
+        is(want, (int)kept.size(), chunks * 16384, LC_F32, offset);
+        kept_of.clear();
+    };
+    std::vector<uint32_t> turns;
+    for (int i = 0; i < 7; ++i) { turns.push_back(7); turns.push_back(15); }
+    for (uint64_t chunks : {600, 8192}) {
+        for (int offset : {0, 4}) {
+            fused_fits = 3; mixed(offset ? "cgggg" : "cggff", turns, chunks, offset);
+            fused_fits = 2; mixed("cgggg", turns, chunks, offset);
+            mixed("cg", {0, 15, 0, 15}, chunks, offset); mixed("cgg", {15, 15, 15, 0, 15, 15, 15}, chunks, offset);
+        }
+        fused_fits = 8; mixed("cff", turns, chunks); mixed("cgggg", turns, chunks, 8);
+        fused_fits = 4; blob_max_len = 8; mixed("cgggg", turns, chunks); blob_max_len = 3;
+    }
+    mixed("cfg", {15, 7, 7, 7, 7, 7, 7}, 8192); mixed("cgf", {7, 7, 7, 7, 7, 7, 15}, 8192); blob_max_len = 8; mixed("cfg", {7, 7, 7, 7, 15, 15, 15}, 8192); blob_max_len = 3;
     blob_kept = 3; fused_fits = 8;
     // given up behind the check
     blob_bytes = 1000; blob_max_len = 9; meet = false;
