@@ -790,7 +790,8 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
     // (Left: sparse lists of one to three chunks per compute unit.)  Between such runs of 8 symbols, blobs of either kind go
     // together, since the tables of 16 hold them too: 3 and 4 bits in turn, 8 blobs, told apart and so a sweep each / together, 64
     // chunks 249 / 140, 600 307 / 154, 8,192 1,880 / 599, off alignment 600 557 / 155.  Arrays off alignment, for which the first has a slow form
-    // only, 2.1 to 4.1 times as fast by the second.
+    // only, 2.1 to 4.1 times as fast by the second; a blob alone there goes to the kernel of single restores, whose loads and stores
+    // do at any address: 600 chunks 87 / 54, 8,192 499 / 243, heavy tails 475 / 42 (aligned ones 57 / 53, 123 / 134 of 4,096, 252 / 228).
     const uint64_t nchunks = num_chunks_of(n), area_at = chunk_area_of(nchunks);
     const size_t lds_budget = kLdsPerCu / (size_t)ds->tune.fused_min_waves_per_cu;
     auto pay_words_of = [](double words) {
@@ -834,7 +835,7 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
         const int T = fused(i, i + run, &words);
         return nchunks >= 3 * cus && (T > 4 || run % T != 0);
     };
-    const int slots[] = {kSlotDecCheck, kSlotDecodeFused, kSlotDecodePairs};
+    const int slots[] = {kSlotDecCheck, kSlotDecodeFused, kSlotDecodePairs, kSlotDecode};
     collect(slots, 1);
     for (int g0 = 0; g0 < count;) {
         // the blobs from g0 on up to the next run that has sweeps of its own: of 8 symbols only, or some of 16
@@ -859,6 +860,11 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
             Timed tm(kSlotDecodePairs, s);
             launch_decode_pairs(list, g0, pairs, w_ref, n, dtype, ws, epoch, host, row_bits, pairs > run, ds->tune, s);
             T = pairs; used = 2;
+        } else if (!by_rows) {
+            // (one blob between such runs, or a list of one)
+            Timed tm(kSlotDecode, s);
+            launch_decode(list.p[g0], w_ref, n, dtype, ws, g0, epoch, host, ds->tune, s);
+            T = 1; used = 3;
         } else {
             T = fused(g0, end, &words);
             // (shared out evenly over as many sweeps as the blobs of like code lengths take)

@@ -51,7 +51,7 @@ def check(n, offset, nbits, kinds, what, sweeps):
     assert lc.lc_decode_many_t(blobs, rec[offset:]) == sum(b.numel() for b in blobs)
     ran = {k: v[1] for k, v in lc.lc_profile_read().items() if v[1]}
     lc.lc_profile(False)
-    assert (sweeps is None and ran["k_decode_pairs"] > 1) or ran == {"k_dec_check": 1, "k_decode_pairs": sweeps}, (what, ran)
+    assert (sweeps is None and ran["k_decode_pairs"] > 1) or ran == dict(sweeps if isinstance(sweeps, dict) else {"k_decode_pairs": sweeps}, k_dec_check=1), (what, ran)
     raw = lambda t: t.cpu().view(torch.int32 if dtype == torch.float32 else torch.int16).numpy()
     want = raw(start[offset:]).copy()
     want = want.view({0: np.float32, 1: np.uint16, 2: np.float16}[name])
@@ -71,6 +71,9 @@ check(3 * CHUNK + 77, 0, [3] * 5 + [4] * 6 + [3] * 9, (["flat", "spread"] * 10)[
 check(3 * CHUNK + 77, 0, [3, 4] * 7, ["flat", "spread"] * 7, "mixed", 4)
 check(3 * CHUNK + 77, 1, [3, 4] * 7, (KINDS * 2)[:14], "mixed", None)
 check(3 * CHUNK, 0, [2, 3, 1, 3, 2, 3, 3, 1, 2, 3, 3, 3, 1], ["none"] * 13, "unchanged", 2)
+# (off alignment, one blob that has a sweep to itself: the kernel of single restores)
+check(5 * CHUNK + 9, 3, [4] + [3] * 6, ["flat", "spread"] * 3 + ["flat"], "one and several", {"k_decode": 1, "k_decode_pairs": 1})
+check(5 * CHUNK + 9, 1, [3], ["spread"], "one", {"k_decode": 1})
 # (more chunks than wavefronts, 8 or 16 per compute unit)
 check(2101 * CHUNK + 1025, 0, [3] * 6, ["spread", "few", "none"] + ["flat"] * 3, "several chunks to a wavefront, narrow", 1)
 check(4501 * CHUNK + 77, 1, [3] * 3, ["few", "spread", "none"], "several chunks to a wavefront, two workgroups per unit", 1)

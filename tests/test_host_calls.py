@@ -299,6 +299,8 @@ static void scenarios() {
         fused_fits = 4; blob_max_len = 8; mixed("cgggg", turns, chunks); blob_max_len = 3;
     }
     mixed("cfg", {15, 7, 7, 7, 7, 7, 7}, 8192); mixed("cgf", {7, 7, 7, 7, 7, 7, 15}, 8192); blob_max_len = 8; mixed("cfg", {7, 7, 7, 7, 15, 15, 15}, 8192); blob_max_len = 3;
+    mixed("cdg", {15, 7, 7, 7, 7, 7, 7}, 8192, 4); mixed("cgd", {7, 7, 7, 7, 7, 7, 15}, 600, 4); mixed("cdggd", {15, 7, 7, 7, 7, 7, 7, 7, 7, 7, 7, 15}, 8192, 4);
+    is("cd", 1, beyond, LC_F32, 4); is("cd", 1, beyond, LC_BF16, 2); is("cf", 1, beyond, LC_F32);
     blob_kept = 3; fused_fits = 8;
     // given up behind the check
     blob_bytes = 1000; blob_max_len = 9; meet = false;
