@@ -326,7 +326,8 @@ namespace {
 // Whether this encode stages keys: sweep 1 then also writes 9 bits per element and sweep 2 reads those instead of w
 // and w_ref again (10.25 + c/8 bytes per element moved instead of 16 + c/8).  That pays when sweep 2 has to read most
 // of the vector; when it passes over most chunks (sparse updates) the plain second sweep is cheaper, since the keys
-// of chunks nobody reads are written for nothing.  How much sweep 2 reads is known only after sweep 1, so the choice
+// of chunks nobody reads are written for nothing.  (Arrays off 16 bytes keep the plain sweep; staged, which no kernel's loads stand
+// in the way of, dense 2^26 elements would take 163 us for 206, 2^28 580 for 785, heavy tails of 2^26 147 for 130.)  How much sweep 2 reads is known only after sweep 1, so the choice
 // follows what the last encode of the same vector found (a training loop checkpoints the same tensors again and
 // again); a vector seen for the first time takes the plain path.  The blob is the same either way.
 DeviceState::Hint* hint_of(DeviceState* ds, const void* w, uint64_t n) {
@@ -407,7 +408,8 @@ lc_ssize encode_impl(const void* w, const void* w_ref, uint64_t n, int nbits, vo
     // 2^23 42.4 / 44.1; unchanged vectors 2^20 27.4 / 26.6, 2^23 39.2 / 41.1.  Beyond that a chunk's deltas no longer fit the
     // registers of a chip-wide grid.  Aligned 2-byte types without a cache stop at 448 chunks: at 512 symbols of one scale 43.5 /
     // 43.7 (3 bits) and 46.5 / 44.4 (4), ten layers' 41.3 / 44.0, heavy tails 38.1 / 43.2; at 448 the last two 39.7 / 39.6 and
-    // 39.6 / 38.8.
+    // 39.6 / 38.8.  Off alignment 512 46.2 / 44.1, 49.6 / 45.1, 54.2 / 49.7, 40.8 / 43.7, and of a ragged 480 49.3 / 43.4, 51.4 / 44.5,
+    // 54.1 / 48.8, 46.0 / 43.1.
     const uint32_t nchunks = (uint32_t)num_chunks_of(n);
     const bool plain16 = esize == 2 && !cache && !misaligned(w, 8) && !misaligned(w_ref, 8);
     const uint32_t most_in_one = (uint32_t)(ds->tune.num_cu * ds->tune.one_per_cu) * (plain16 ? 7 : 8) / 8;
@@ -603,13 +605,20 @@ bool fits_in_one(const DeviceState* ds, uint64_t n) {
 }
 // Several blobs in one launch, without a look at them first?  Check and sweeps / one launch, as a ratio of whole calls, at 64, 256 /
 // 320, 512 chunks, by (fp32) symbols of one scale at 3 bits; heavy tails at 3; of one scale at 2; all 16 symbols as frequent at 4:
-//   aligned, 2 blobs 1.28 1.26 / 1.12 1.11; 1.51 1.53 / 1.35 1.32; 1.35 1.34 / 1.17 1.17; 0.99 1.03 / 0.85 0.89
-//            3       1.14 1.12 / 0.98 1.00; 1.36 1.38 / 1.22 1.23; 1.19 1.20 / 1.04 1.05; 1.07 1.12 / 0.90 1.00
-//            4       1.04 1.02 / 0.90 0.92; 1.25 1.25 / 1.12 1.13; 1.09 1.08 / 0.94 0.96; 0.86 0.92 / 0.73 0.80
-//            5       1.17 1.22 / 1.02 1.07; 1.19 1.21 / 1.08 1.10; 1.04 1.07 / 0.91 0.94; 0.93 1.00 / 0.80 0.90
-//            8       0.92 0.94 / 0.81 0.84; 1.18 1.22 / 1.04 1.06; 1.01 1.05 / 0.88 0.91; 0.78 0.84 / 0.66 0.74
-//            16      0.86 0.90 / 0.75 0.80; 1.05 1.08 / 0.94 0.98; 0.89 0.93 / 0.79 0.83; 0.76 0.84 / 0.66 0.73
-// (against sweeps of up to 4 blobs), bf16 up to a tenth more; off alignment 1.14 to 5.3 at every size and count.
+//   aligned, 2 blobs 1.31 1.31 / 1.12 1.13; 1.46 1.56 / 1.33 1.36; 1.38 1.38 / 1.18 1.14; 1.04 1.07 / 0.92 0.94
+//            3       1.16 1.17 / 1.05 1.03; 1.33 1.46 / 1.29 1.27; 1.22 1.23 / 1.08 1.07; 1.09 1.07 / 0.93 0.91
+//            4       1.04 1.04 / 0.91 0.93; 1.22 1.36 / 1.16 1.22; 1.11 1.12 / 0.98 0.96; 1.00 0.96 / 0.85 0.82
+//            5       1.11 1.17 / 0.99 1.03; 1.17 1.30 / 1.15 1.19; 1.07 1.10 / 0.95 0.96; 0.97 0.98 / 0.84 0.84
+//            8       0.94 0.98 / 0.86 0.87; 1.13 1.30 / 1.09 1.16; 1.01 1.04 / 0.89 0.90; 0.92 0.89 / 0.77 0.76
+//            16      0.87 0.91 / 0.80 0.83; 1.03 1.21 / 1.02 1.09; 0.92 0.97 / 0.82 0.84; 0.87 0.85 / 0.75 0.75
+//   off it,  2       1.61 1.52 / 1.39 1.30; 1.70 1.81 / 1.54 1.56; 1.62 1.56 / 1.41 1.24; 1.36 1.34 / 1.16 1.16
+//            4       1.26 1.25 / 1.07 1.05; 1.35 1.43 / 1.22 1.22; 1.26 1.21 / 1.06 1.02; 1.00 0.96 / 0.84 0.84
+//            6       1.13 1.13 / 0.95 0.96; 1.18 1.27 / 1.05 1.08; 1.09 1.07 / 0.90 0.90; 1.01 0.99 / 0.86 0.86
+//            8       1.04 1.05 / 0.88 0.88; 1.11 1.20 / 0.99 1.02; 1.03 1.01 / 0.84 0.84; 0.93 0.89 / 0.78 0.79
+//            16      0.98 1.01 / 0.83 0.85; 1.05 1.16 / 0.93 0.98; 0.96 0.96 / 0.79 0.81; 0.88 0.85 / 0.75 0.77
+// and codes above 7 bits (4 bits, one scale; ten layers'; hardly a kept symbol), 8 blobs, on or off alignment 1.26 1.26 / 1.03 1.03; 2.1
+// 1.6 / 1.5 1.5; 1.34 1.36 / 1.13 1.15; bf16 the same to a tenth.  Off alignment every list goes into the one launch: above a chunk per
+// compute unit and 5 blobs short codes lose by it what long ones would lose by the check ahead of it (6 to 20 % of the call).
 // binary64, whose other route is a sweep per blob: up to a chunk per compute unit 0.87 to 2.3, above that 1.4 to 2.9 where the strings
 // are dense and 0.66 to 0.95 where they are not.
 bool many_in_one(const DeviceState* ds, uint64_t n, int count, const void* w_ref, int dtype) {
@@ -618,8 +627,9 @@ bool many_in_one(const DeviceState* ds, uint64_t n, int count, const void* w_ref
     if (count == 1 || dtype == LC_F64) return count == 1 || one_each;
     return misaligned(w_ref, dtype == LC_F32 ? 16 : 8) || count <= (one_each ? 5 : 3);
 }
-// ... once they have been checked: codes above 7 bits, for which the fused sweep has a slow form only (1.3 to 4.1 without the
-// check); binary64, strings of 1.5 bits per element and more.
+// ... once they have been checked: codes above 7 bits, for which the sweeps are the slower ones (by the above; the call with its check
+// against the sweeps, 6 to 16 blobs, one scale; ten layers'; hardly a kept symbol: up to a chunk per compute unit 1.10 to 1.25, 1.5 to 2,
+// 1.13 to 1.27, above that 0.90 to 1.0, 1.25 to 1.45, 0.98 to 1.1); binary64, strings of 1.5 bits per element and more.
 bool many_in_one_checked(const DeviceState* ds, uint64_t n, int count, int dtype, const HostResult& got) {
     if (!fits_in_one(ds, n)) return false;
     int longs = 0;
