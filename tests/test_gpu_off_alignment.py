@@ -42,6 +42,22 @@ def test_same_blob(lc, dtype, n):
                     assert torch.equal(got[:size2], want2[:size2]), turn
 
 
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("n", [4096 * CHUNK, 4096 * CHUNK + 1029])
+def test_same_blob_on_both_sides_of_the_counts_limit(lc, dtype, n):
+    """2-byte elements between two dwords: counted element by element up to 4,096 chunks, by vectors beyond."""
+    print("between dwords", dtype, n, flush=True)
+    g = torch.Generator(device=DEV); g.manual_seed(n % 1009)
+    ref = torch.randn(n, generator=g, device=DEV).to(dtype)
+    w = (ref.float() + 0.1 * torch.randn(n, generator=g, device=DEV) * (torch.rand(n, generator=g, device=DEV) < 0.2)).to(dtype)
+    want = lc.alloc_out(n, 3, DEV); size = lc.lc_encode_t(w, ref, 3, want)
+    for off, off_ref in ((1, 1), (0, 3), (1, 2)):
+        bw, br = (torch.full((n + 4,), float("nan"), dtype=dtype, device=DEV) for _ in range(2))
+        bw[off:off + n] = w; br[off_ref:off_ref + n] = ref
+        got = lc.alloc_out(n, 3, DEV)
+        assert lc.lc_encode_t(bw[off:off + n], br[off_ref:off_ref + n], 3, got) == size and torch.equal(got[:size], want[:size]), (off, off_ref)
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16, torch.float64])
 @pytest.mark.parametrize("n", [1023, 600 * CHUNK, 600 * CHUNK + 7 * 1024 + 1, 2100 * CHUNK - 1])
 def test_same_restore(lc, dtype, n):

@@ -130,6 +130,21 @@ def test_encode_of_chunks_with_few_parts_to_read(lc):
     assert times["one"] < 0.92 * times["all"], times         # (0.99 when all parts were read, 0.85 now)
 
 
+def test_encode_of_halves_between_dwords(lc):
+    """An unchanged bf16 vector of 3,000 chunks that starts between two dwords, against one that starts on a dword off alignment."""
+    n, times = 3000 * 16384, {}
+    buf, out = torch.zeros(2, n + 64, device=DEV, dtype=torch.bfloat16), lc.alloc_out(n, 3, DEV)
+    for offset in (1, 2):
+        w, ref = buf[0, offset:offset + n], buf[1, offset:offset + n]
+        size = lc.lc_encode_t(w, ref, 3, out)
+        if offset == 1:
+            want = out[:size].clone()
+        assert torch.equal(out[:size], want)
+        times[offset] = best_us(lambda: lc.lc_encode_t(w, ref, 3, out))
+    print("encode off dwords and on them: %.1f us, %.1f us" % (times[1], times[2]), flush=True)
+    assert times[1] < 1.1 * times[2], times               # (1.19 by vectors)
+
+
 def test_long_lists_of_sparse_updates(lc):
     """Five checkpoints of 2^27 elements in one call, none changed, or with a few heavy tails in a tenth of their chunks, against
     four, which another kernel restores: a blob more costs no more than its share."""
