@@ -1088,7 +1088,6 @@ lc_ssize lc_encode_batch_t(const void* const* w, const void* const* w_ref, const
         Seg& sg = g_batch->segs[t];
         sg.w = w[t]; sg.w_ref = w_ref[t]; sg.out = static_cast<uint8_t*>(out[t]); sg.n = n[t];
         sg.nchunks = (uint32_t)num_chunks_of(n[t]); sg.chunk0 = chunks; sg.group0 = groups;
-        sg.pad = 0;
         chunks += sg.nchunks; groups += (sg.nchunks + 63) / 64;
         g_batch->results[t].bytes = 0; g_batch->results[t].status = LC_ERR_HIP; g_batch->results[t].used_cache = 0;
     }

@@ -805,7 +805,7 @@ __device__ __forceinline__ void fused_row(const FusedHead<T>& H, const u32* pay,
             // a compiler vector type, the first sweep over parameters that a device copy had just written took 830-880 us
             // instead of 600-650)
             if constexpr (DT == kF32) *reinterpret_cast<float4*>(static_cast<float*>(w_ref) + idx) = make_float4(x[0], x[1], x[2], x[3]);
-            else store4<DT, false>(w_ref, idx, x);
+            else store4<DT>(w_ref, idx, x);
         }
     } else {
 #pragma unroll
@@ -819,7 +819,7 @@ __device__ __forceinline__ void fused_row(const FusedHead<T>& H, const u32* pay,
     }
 }
 
-// All rows of a full, aligned chunk with staged payloads: w_ref is read PF rows ahead in two
+// All rows of a full chunk with staged payloads: w_ref is read PF rows ahead in two
 // alternating register batches, so the reads of the next rows are in flight while these decode.
 template <int T, bool LONG, int DT>
 __device__ __forceinline__ void fused_rows_fast(const FusedHead<T>& H, const u32* pay, u32 pay_words, const u32* const (&gw)[T],
@@ -851,7 +851,7 @@ __device__ __forceinline__ void fused_rows_fast(const FusedHead<T>& H, const u32
     }
 }
 
-// Any chunk (ragged, unaligned, or payloads read from memory), row by row.
+// Any chunk (ragged, or payloads read from memory), row by row.
 template <int T, bool FAST, bool LONG, int DT>
 __device__ __forceinline__ void fused_rows_plain(const FusedHead<T>& H, const u32* const (&gw)[T], const u32 (&nw)[T], u32 (&pos)[T],
                                               void* __restrict__ w_ref, u64 n, u32 c) {
@@ -963,7 +963,7 @@ __device__ __forceinline__ void fused_chunk(const FusedHead<T>& H, u32* pay, u32
 
 template <int T, bool LONG, int DT>
 __global__ __launch_bounds__(64) void k_decode_fused(BlobList blobs, u32 first, void* __restrict__ w_ref, u64 n,
-                                                     Workspace* ws, u32 nchunks, int aligned, u64 epoch,
+                                                     Workspace* ws, u32 nchunks, u64 epoch,
                                                      HostResult* host, u32 pay_words) {
     __shared__ FusedHead<T> H;
     static_assert(sizeof(FusedHead<T>) % 16 == 0, "payload area must stay 16-byte aligned");
@@ -1008,7 +1008,7 @@ __global__ __launch_bounds__(64) void k_decode_fused(BlobList blobs, u32 first, 
     __syncthreads();
     for (u32 c = blockIdx.x; c < nchunks; c += gridDim.x) {
         const bool full = (u64)(c + 1) * kChunk <= n;
-        if (full && aligned) fused_chunk<T, true, LONG, DT>(H, pay, pay_words, w_ref, n, ws, host, c, nchunks, epoch);
+        if (full) fused_chunk<T, true, LONG, DT>(H, pay, pay_words, w_ref, n, ws, host, c, nchunks, epoch);
         else fused_chunk<T, false, LONG, DT>(H, pay, pay_words, w_ref, n, ws, host, c, nchunks, epoch);
     }
 }
@@ -1525,11 +1525,10 @@ template <int T, int DT>
 static void launch_fused_td(const BlobList& blobs, int first, void* w_ref, uint64_t n, Workspace* ws, uint64_t epoch,
                             HostResult* host, u32 blocks, u32 pay_words, bool long_codes, hipStream_t s) {
     const size_t lds = 4 * (size_t)(pay_words + kFusedSlack);
-    const int al = aligned_rows(w_ref, DT);
     if (long_codes) hipLaunchKernelGGL((k_decode_fused<T, true, DT>), dim3(blocks), dim3(64), lds, s, blobs, (u32)first, w_ref,
-                                       (u64)n, ws, (u32)num_chunks_of(n), al, (u64)epoch, host, pay_words);
+                                       (u64)n, ws, (u32)num_chunks_of(n), (u64)epoch, host, pay_words);
     else hipLaunchKernelGGL((k_decode_fused<T, false, DT>), dim3(blocks), dim3(64), lds, s, blobs, (u32)first, w_ref,
-                            (u64)n, ws, (u32)num_chunks_of(n), al, (u64)epoch, host, pay_words);
+                            (u64)n, ws, (u32)num_chunks_of(n), (u64)epoch, host, pay_words);
 }
 
 template <int T>

@@ -123,14 +123,8 @@ template <int DT>
 __device__ __forceinline__ typename Raw<DT>::type load_raw(const void* base, u64 i) {
     if constexpr (DT == kF32) {
         return load_stream(reinterpret_cast<const float4*>(static_cast<const float*>(base) + i));
-    } else if constexpr (DT == kF64) {
-        const float4* p = reinterpret_cast<const float4*>(static_cast<const double*>(base) + i);
-        const float4 a = load_stream(p), b = load_stream(p + 1);
-        Row64 r;
-        r.x[0] = __hiloint2double(__float_as_int(a.y), __float_as_int(a.x)); r.x[1] = __hiloint2double(__float_as_int(a.w), __float_as_int(a.z));
-        r.x[2] = __hiloint2double(__float_as_int(b.y), __float_as_int(b.x)); r.x[3] = __hiloint2double(__float_as_int(b.w), __float_as_int(b.z));
-        return r;
     } else {
+        static_assert(DT != kF64, "binary64 rows: load_raw_any");
         const u32x2 v = __builtin_nontemporal_load(reinterpret_cast<const u32x2*>(static_cast<const uint16_t*>(base) + i));
         return make_uint2(v.x, v.y);
     }
@@ -207,23 +201,16 @@ __device__ __forceinline__ void store_one(void* base, u64 i, float x) {
     else static_cast<uint16_t*>(base)[i] = (uint16_t)narrow16(x, DT == kBF16);
 }
 
-// Restored rows are written once and not read again by the sweep: non-temporal stores, like the loads (a bare
-// read-modify-write sweep in this access pattern runs 4-5 % faster with both marked than with the loads alone).
-// (STREAM false: plain stores, which the sweep over several blobs keeps.)
-template <int DT, bool STREAM = true>
+// A row of 2-byte elements, aligned to 8 bytes, by a plain store (the sweep over several blobs, see fused_row).
+template <int DT>
 __device__ __forceinline__ void store4(void* base, u64 i, const float (&x)[4]) {
-    if constexpr (DT == kF32) {
-        const f32x4 v = {x[0], x[1], x[2], x[3]};
-        if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<f32x4*>(static_cast<float*>(base) + i));
-        else *reinterpret_cast<f32x4*>(static_cast<float*>(base) + i) = v;
-    } else {
-        const u32x2 v = {narrow16_pair(x[0], x[1], DT == kBF16), narrow16_pair(x[2], x[3], DT == kBF16)};
-        if constexpr (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<u32x2*>(static_cast<uint16_t*>(base) + i));
-        else *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(base) + i) = v;
-    }
+    static_assert(elem_bytes<DT>() == 2, "2-byte elements");
+    *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(base) + i) = u32x2{narrow16_pair(x[0], x[1], DT == kBF16), narrow16_pair(x[2], x[3], DT == kBF16)};
 }
 
-// the same on an array that is aligned to its elements only
+// Restored rows are written once and not read again by the sweep: non-temporal stores, like the loads (a bare
+// read-modify-write sweep in this access pattern runs 4-5 % faster with both marked than with the loads alone).  The array may be
+// aligned to its elements only.
 template <int DT>
 __device__ __forceinline__ void store4_any(void* base, u64 i, const typename Val<DT>::type (&x)[4]) {
     if constexpr (DT == kF32) {
@@ -457,10 +444,6 @@ static inline uint64_t balanced_workers(uint64_t items, uint64_t cap) {
     if (items <= cap || cap == 0) return items;
     const uint64_t rounds = (items + cap - 1) / cap;
     return (items + rounds - 1) / rounds;
-}
-static inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-static inline bool aligned_rows(const void* p, int dtype) {     // 4 consecutive elements per access
-    return (reinterpret_cast<uintptr_t>(p) & (dtype == kF32 || dtype == kF64 ? 15 : 7)) == 0;
 }
 
 }  // namespace lc

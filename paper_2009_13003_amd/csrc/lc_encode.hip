@@ -116,7 +116,7 @@ __device__ __forceinline__ float max_magnitude(const u32 (&u)[EPU], float m) {
 // A wavefront keeps the maxima of its last 64 batches in LDS and writes them out 64 at a time, one per lane: a
 // global write after every batch, however small, holds back the loads issued behind it (both are counted, in
 // order, by the one vector-memory counter) and cost the sweep 4 % of its rate.
-// KEYS (binary32, aligned arrays): the sweep also stages a 9-bit key per element of every whole batch -- the 16
+// KEYS (binary32): the sweep also stages a 9-bit key per element of every whole batch -- the 16
 // exponent bytes and the 16 sign bits of the 16 elements a lane holds of a batch, which are the lane's own elements of
 // 4 rows of the coding sweep's chunk -- and, being then the only sweep that sees the mantissas, tracks the smallest and
 // largest delta bit pattern of every bucket (Section 3.1.1: the representative is the mean of these two).
@@ -2389,7 +2389,7 @@ void launch_reset_chunks(Workspace* ws, uint32_t* group_words, uint32_t* chunk_m
     hipLaunchKernelGGL(k_reset_chunks, dim3(1), dim3(1024), 0, s, ws, group_words, (nchunks + 63) / 64, chunk_maxexp, nchunks);
 }
 
-// keys.exp != null: stage keys (binary32, both arrays 16-byte aligned: the caller has checked)
+// keys.exp != null: stage keys (binary32)
 void launch_hist(const void* w, const void* w_ref, uint64_t n, int dtype, Workspace* ws, uint32_t* chunk_maxexp, uint8_t* batch_max,
                  KeyPlanes keys, const Tuning& tune, hipStream_t s) {
     if (n == 0) return;

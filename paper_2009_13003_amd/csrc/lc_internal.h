@@ -181,7 +181,7 @@ void launch_reset(Workspace* ws, uint32_t* group_words, uint32_t* chunk_maxexp, 
 // meetings, counts and extremes.
 void launch_reset_one(Workspace* ws, hipStream_t s);
 void launch_reset_chunks(Workspace* ws, uint32_t* group_words, uint32_t* chunk_maxexp, uint32_t nchunks, hipStream_t s);
-// The keys of an encode with staged keys (fp32, 16-byte aligned arrays): sweep 1 leaves, for every whole batch of 4 rows
+// The keys of an encode with staged keys (fp32; which ones: see stage_keys): sweep 1 leaves, for every whole batch of 4 rows
 // (1024 elements) and lane, the 16 exponent bytes of the lane's elements (row-major: byte 4 k + v = row k, element v) and
 // their 16 sign bits, and sweep 2 codes from those 9 bits per element instead of reading w and w_ref again.
 struct KeyPlanes {
@@ -219,7 +219,7 @@ void launch_encode_one(const void* w, const void* w_ref, uint64_t n, int nbits, 
 struct Seg {
     const void* w; const void* w_ref; uint8_t* out;
     uint64_t n;
-    uint32_t nchunks, chunk0, group0, pad;
+    uint32_t nchunks, chunk0, group0;
 };
 constexpr int kMaxBatch = 1024;
 constexpr uint32_t kPartBytes = 16;
@@ -268,7 +268,7 @@ void launch_decode(const uint8_t* blob, void* w_ref, uint64_t n, int dtype, Work
 // met: as launch_encode_one.
 void launch_decode_one(const BlobList& blobs, int count, void* w_ref, uint64_t n, int dtype, uint64_t max_total, Workspace* ws, uint64_t epoch,
                        HostResult* host, uint64_t (&met)[kMeetLines], int looks, hipStream_t s);
-// Applies blobs.p[first .. first+count), count <= kMaxMany, using dec_set[first ..].
+// Applies blobs.p[first .. first+count), count <= kMaxMany, using dec_set[first ..]; w_ref is aligned to 4 elements.
 // pay_words: LDS words each wavefront gets for the payloads of one chunk of all `count` blobs; long_codes: some code is longer
 // than kDecLut1Bits.
 void launch_decode_fused(const BlobList& blobs, int first, int count, void* w_ref, uint64_t n, int dtype, Workspace* ws,

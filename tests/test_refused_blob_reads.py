@@ -100,8 +100,8 @@ int main() {
     every_thread(2304, 256, [&] { k_decode<kF32, true>(blob, w_ref, n, ws, nchunks, 1, epoch, host, 2048, 0); });
     BlobList blobs;
     for (int i = 0; i < kMaxSets; ++i) blobs.p[i] = blob;
-    every_thread(2048, 64, [&] { k_decode_fused<4, false, kF32>(blobs, 0u, w_ref, n, ws, nchunks, 1, epoch, host, 4096u); });
-    every_thread(2048, 64, [&] { k_decode_fused<4, true, kBF16>(blobs, 0u, w_ref, n, ws, nchunks, 1, epoch, host, 4096u); });
+    every_thread(2048, 64, [&] { k_decode_fused<4, false, kF32>(blobs, 0u, w_ref, n, ws, nchunks, epoch, host, 4096u); });
+    every_thread(2048, 64, [&] { k_decode_fused<4, true, kBF16>(blobs, 0u, w_ref, n, ws, nchunks, epoch, host, 4096u); });
     puts("nothing read");
     return 0;
 }
