@@ -819,39 +819,50 @@ __device__ __forceinline__ void fused_row(const FusedHead<T>& H, const u32* pay,
     }
 }
 
-// All rows of a full chunk with staged payloads: w_ref is read PF rows ahead in two
-// alternating register batches, so the reads of the next rows are in flight while these decode.
-template <int T, bool LONG, int DT>
+// All rows of a chunk with staged payloads: w_ref is read PF rows ahead in two
+// alternating register batches, so the reads of the next rows are in flight while these decode.  Of a ragged chunk (not FULL),
+// which is one wavefront's work from start to end and the sweep's last, the whole rows go the same way, only what is left of it
+// element by element: by elements from the first row on, with payloads from memory, fp32, a blob of 738 chunks less 777 elements took
+// 77 us the call, and 61 so, 8 blobs of 1 to 15 chunks 139 and 97, 12 of 1,197 chunks 397 and 262.
+template <int T, bool FULL, bool LONG, int DT>
 __device__ __forceinline__ void fused_rows_fast(const FusedHead<T>& H, const u32* pay, u32 pay_words, const u32* const (&gw)[T],
                                                 const u32 (&nw)[T], u32 (&pos)[T], void* __restrict__ w_ref, u64 n, u32 c) {
     constexpr int PF = 4;
     typedef typename Raw<DT>::type RowT;
     const u32 lane = lane_id();
     const u64 base = (u64)c * kChunk + lane * kV;
+    const u32 rows = FULL ? kR : (u32)(n - (u64)c * kChunk) / kRowElems;
     RowT A[PF], B[PF];
+    auto fetch = [&](RowT (&X)[PF], u32 r0) {
 #pragma unroll
-    for (int k = 0; k < PF; ++k) A[k] = load_raw<DT>(w_ref, base + (u64)k * kRowElems);
+        for (int k = 0; k < PF; ++k)                      // (no branch, or the loads would be waited for: the last whole row again)
+            X[k] = load_raw<DT>(w_ref, base + (u64)(FULL ? r0 + k : min(r0 + k, rows - 1)) * kRowElems);
+    };
     auto batch = [&](RowT (&X)[PF], u32 r0) {
 #pragma unroll
         for (int k = 0; k < PF; ++k) {
+            if (!FULL && r0 + k >= rows) break;
             float x[4];
             unpack<DT>(X[k], x);
             fused_row<T, true, true, LONG, DT>(H, pay, pay_words, gw, nw, pos, w_ref, n, base + (u64)(r0 + k) * kRowElems, x);
         }
     };
-    for (u32 r0 = 0; r0 < kR; r0 += 2 * PF) {
-#pragma unroll
-        for (int k = 0; k < PF; ++k) B[k] = load_raw<DT>(w_ref, base + (u64)(r0 + PF + k) * kRowElems);
+    if (FULL || rows > 0) fetch(A, 0);
+    for (u32 r0 = 0; r0 < rows; r0 += 2 * PF) {
+        fetch(B, r0 + PF);
         batch(A, r0);
-        if (r0 + 2 * PF < kR) {
-#pragma unroll
-            for (int k = 0; k < PF; ++k) A[k] = load_raw<DT>(w_ref, base + (u64)(r0 + 2 * PF + k) * kRowElems);
-        }
+        if (r0 + 2 * PF < kR) fetch(A, r0 + 2 * PF);
         batch(B, r0 + PF);
+    }
+    if (!FULL) {
+        const u64 idx = base + (u64)rows * kRowElems;
+        float x[4];
+        load_row<false, DT>(w_ref, idx, n, x);
+        fused_row<T, false, true, LONG, DT>(H, pay, pay_words, gw, nw, pos, w_ref, n, idx, x);
     }
 }
 
-// Any chunk (ragged, or payloads read from memory), row by row.
+// A chunk whose payloads are read from memory, row by row.
 template <int T, bool FAST, bool LONG, int DT>
 __device__ __forceinline__ void fused_rows_plain(const FusedHead<T>& H, const u32* const (&gw)[T], const u32 (&nw)[T], u32 (&pos)[T],
                                               void* __restrict__ w_ref, u64 n, u32 c) {
@@ -873,10 +884,11 @@ __device__ __forceinline__ P* uniform_ptr(P* p) {        // a pointer every lane
     return reinterpret_cast<P*>(((u64)hi << 32) | lo);
 }
 
-template <int T, bool FAST, bool LONG, int DT>
+template <int T, bool LONG, int DT>
 __device__ __forceinline__ void fused_chunk(const FusedHead<T>& H, u32* pay, u32 pay_words, void* __restrict__ w_ref, u64 n,
                                             Workspace* ws, HostResult* host, u32 c, u32 nchunks, u64 epoch) {
     const u32 lane = lane_id();
+    const bool full = (u64)(c + 1) * kChunk <= n;
     const u32* gw[T];
     u32 nw[T], k0[T], wbase[T], pos[T], start[T], lane_bits[T];
     u32 total = 0;
@@ -892,7 +904,7 @@ __device__ __forceinline__ void fused_chunk(const FusedHead<T>& H, u32* pay, u32
         wbase[t] = total;
         total += (nw[t] + k0[t] + 3) & ~3u;
     }
-    const bool staged = FAST && total <= pay_words;
+    const bool staged = total <= pay_words;
     if (staged) {
         // Coalesced copies of [16-byte aligned start, payload end) into the LDS area; the words before a
         // payload are its record's lane lengths.  A last partial vector may read up to 12 bytes past the
@@ -938,8 +950,9 @@ __device__ __forceinline__ void fused_chunk(const FusedHead<T>& H, u32* pay, u32
                 }
             }
         }
-        // every blob's chunk holds merged symbols only (see zero_chunk_bits): nothing changes, w_ref is not read
-        bool all_merged = true;
+        // every blob's chunk holds merged symbols only (see zero_chunk_bits; a ragged chunk's lanes are not alike): nothing changes,
+        // w_ref is not read
+        bool all_merged = full;
 #pragma unroll
         for (int t = 0; t < T; ++t) all_merged = all_merged && H.zero_bits[t] != 0 && lane_bits[t] == H.zero_bits[t];
         if (!__any(!all_merged || nonzero != 0)) return;
@@ -949,11 +962,13 @@ __device__ __forceinline__ void fused_chunk(const FusedHead<T>& H, u32* pay, u32
     if (staged) {
 #pragma unroll
         for (int t = 0; t < T; ++t) { start[t] += 32 * (wbase[t] + k0[t]); pos[t] = start[t]; }
-        fused_rows_fast<T, LONG, DT>(H, pay, pay_words, gw, nw, pos, w_ref, n, c);
+        if (full) fused_rows_fast<T, true, LONG, DT>(H, pay, pay_words, gw, nw, pos, w_ref, n, c);
+        else fused_rows_fast<T, false, LONG, DT>(H, pay, pay_words, gw, nw, pos, w_ref, n, c);
     } else {
 #pragma unroll
         for (int t = 0; t < T; ++t) pos[t] = start[t];
-        fused_rows_plain<T, FAST, LONG, DT>(H, gw, nw, pos, w_ref, n, c);
+        if (full) fused_rows_plain<T, true, LONG, DT>(H, gw, nw, pos, w_ref, n, c);
+        else fused_rows_plain<T, false, LONG, DT>(H, gw, nw, pos, w_ref, n, c);
     }
     bool bad = false;
 #pragma unroll
@@ -961,8 +976,11 @@ __device__ __forceinline__ void fused_chunk(const FusedHead<T>& H, u32* pay, u32
     if (__any(bad) && lane == 0) raise_status(ws, host, epoch, 4u);
 }
 
+// Wavefronts per SIMD that the registers leave, where the LDS does too, with sparse blobs (4 of them, two of 1 % kept symbols, one
+// unchanged, fp32, 5,919 chunks with one wavefront per SIMD less 235 us and 195, 2^27 elements 318 and 263).
+constexpr int fused_waves(int blobs, bool long_codes, int dt) { return blobs <= 2 || (blobs == 3 && long_codes && dt == kF32) ? 4 : blobs <= 5 ? 3 : 2; }
 template <int T, bool LONG, int DT>
-__global__ __launch_bounds__(64) void k_decode_fused(BlobList blobs, u32 first, void* __restrict__ w_ref, u64 n,
+__global__ __launch_bounds__(64, fused_waves(T, LONG, DT)) void k_decode_fused(BlobList blobs, u32 first, void* __restrict__ w_ref, u64 n,
                                                      Workspace* ws, u32 nchunks, u64 epoch,
                                                      HostResult* host, u32 pay_words) {
     __shared__ FusedHead<T> H;
@@ -1006,11 +1024,7 @@ __global__ __launch_bounds__(64) void k_decode_fused(BlobList blobs, u32 first, 
     }
     if (tid == 0) H.before_pay = 0;
     __syncthreads();
-    for (u32 c = blockIdx.x; c < nchunks; c += gridDim.x) {
-        const bool full = (u64)(c + 1) * kChunk <= n;
-        if (full) fused_chunk<T, true, LONG, DT>(H, pay, pay_words, w_ref, n, ws, host, c, nchunks, epoch);
-        else fused_chunk<T, false, LONG, DT>(H, pay, pay_words, w_ref, n, ws, host, c, nchunks, epoch);
-    }
+    for (u32 c = blockIdx.x; c < nchunks; c += gridDim.x) fused_chunk<T, LONG, DT>(H, pay, pay_words, w_ref, n, ws, host, c, nchunks, epoch);
 }
 // ----------------------------------------------------------------------------- k_decode_pairs
 // The same for more blobs in one sweep, up to 8 where the other kernel takes 4 (dense ones; of sparse ones some 6).  What stands in the way of

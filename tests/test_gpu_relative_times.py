@@ -166,3 +166,22 @@ def test_long_lists_of_sparse_updates(lc):
             times[count] = best_us(lambda: lc.lc_decode_many(blobs[:count], many), reps=30)
         print("%s, 4 and 5 blobs: %.1f us, %.1f us" % (kind, times[4], times[5]), flush=True)
         assert times[5] < 0.5 * (slow + now) * times[4], (kind, times)
+
+
+def test_short_lists_that_end_in_a_ragged_chunk(lc):
+    """Eight checkpoints of three chunks in one call, the last one whole or all but 777 elements of it: the ragged chunk is a
+    wavefront's work from start to end, as the others are."""
+    times = {}
+    for n in (3 * 16384, 3 * 16384 - 777):
+        g = torch.Generator(device=DEV); g.manual_seed(13)
+        u = torch.rand(n, generator=g, device=DEV) - 0.5
+        d = -1e-3 * torch.sign(u) * torch.log1p(-2 * u.abs().clamp_(max=0.49999997))
+        blob, many, single = blob_of(lc, d, torch.zeros_like(d), 3), torch.zeros(n, device=DEV), torch.zeros(n, device=DEV)
+        blobs = [blob.clone() for _ in range(8)]
+        for b in blobs:
+            lc.lc_decode(b, single)
+        lc.lc_decode_many(blobs, many)
+        assert torch.equal(single, many)
+        times[n % 16384] = best_us(lambda: lc.lc_decode_many(blobs, many))
+    print("8 blobs, whole and ragged: %.1f us, %.1f us" % (times[0], times[16384 - 777]), flush=True)
+    assert times[16384 - 777] < 1.2 * times[0], times        # (1.44 by elements, 1.0 by rows)
