@@ -795,11 +795,18 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
     //   4 bits: 4, 3: 101 / 77; 64, 2, 3, 8: 70 / 71, 102 / 79, 196 / 149; 2,048, 2, 3, 8: 89 / 103, 144 / 120, 278 / 227; ten layers', 64, 4:
     //     207 / 147, 8,192, 3, 8: 1,030 / 354, 2,523 / 865; of a short vector with hardly a kept symbol, whose codes all have at most 7
     //     bits, 4, 3, 6: 56 / 66, 75 / 103
+    //   3 bits, 2.9 per element, of which the first takes 3: 1, 4 chunks, 8: 124 / 110, 119 / 110; 15, 6, 8, 12: 99 / 96, 121 / 108, 165 /
+    //     159; 600, 5, 8, 9: 1.19, 1.26, 1.18 times as long; 800, 6, 8, 10, 12: 128 / 112, 163 / 130, 195 / 179, 231 / 197; 1,500, 8: 199 / 165
+    //   2 bytes, hardly a kept symbol: 4 to 64, 6, 7, 8, 12 blobs: 1.0, 1.08, 1.08, 1.0 times as long; fp32 0.93 to 1.0, 1.0, 1.0, 0.92
     // So: of 16 symbols 3 and more blobs by the second, unless all their codes are short and the first takes as few sweeps.  Of 8
-    // symbols 5 and more, from 6 chunks per compute unit on, and from 3 on unless the first takes dense ones in full sweeps of 4.
-    // (Left: sparse lists of one to three chunks per compute unit.)  Between such runs of 8 symbols, blobs of either kind go
-    // together, since the tables of 16 hold them too: 3 and 4 bits in turn, 8 blobs, told apart and so a sweep each / together, 64
-    // chunks 249 / 140, 600 307 / 154, 8,192 1,880 / 599, off alignment 600 557 / 155.  Arrays off alignment, for which the first has a slow form
+    // symbols 5 and more, from 6 chunks per compute unit on, from 3 on unless the first takes dense ones in full sweeps of 4, and from 2
+    // on where it takes fewer than 4; sweeps of 6 to 8 that the first takes fewer than 4 of, and 7 or 8 sparse ones of 2-byte elements,
+    // at any size.  (Left: sparse lists of fp32 at one to three chunks per compute unit.)  Between such runs of 8 symbols, blobs of
+    // either kind go together, since the tables of 16 hold them too: 3 and 4 bits in turn, 8 blobs, told apart and so a sweep each /
+    // together, 64 chunks 249 / 140, 600 307 / 154, 8,192 1,880 / 599, off alignment 600 557 / 155.  But sparse ones, whose own sweep
+    // passes over their chunks, do not join dense ones with long codes: dense and sparse of 3 and 4 bits in runs, 10 blobs of 7,832
+    // chunks of bf16 612 / 563, 8 of 3,119 off alignment 277 / 240 (all together / sparse ones apart).
+    // Arrays off alignment, for which the first has a slow form
     // only, 2.1 to 4.1 times as fast by the second; a blob alone there goes to the kernel of single restores, whose loads and stores
     // do at any address: 600 chunks 87 / 54, 8,192 499 / 243, heavy tails 475 / 42 (aligned ones 57 / 53, 123 / 134 of 4,096, 252 / 228).
     const uint64_t nchunks = num_chunks_of(n), area_at = chunk_area_of(nchunks);
@@ -833,42 +840,52 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
     const bool by_rows = !misaligned(w_ref, dtype == LC_F32 ? 16 : 8), all = !by_rows || ds->tune.pairs == 1, none = by_rows && ds->tune.pairs == 2;
     auto wide = [&](int i) { return got.kept[i] > 7; };
     auto shared = [](int blobs, int most) { const int sweeps = (blobs + most - 1) / most; return (blobs + sweeps - 1) / sweeps; };
-    auto run_of = [&](int i) {                                  // blobs of at most 8 symbols from i on
-        const int first = i;
-        while (i < count && !wide(i)) ++i;
-        return i - first;
+    auto run_of = [&](int i) {                                  // blobs alike in that, from i on
+        int end = i + 1;
+        while (end < count && wide(end) == wide(i)) ++end;
+        return end - i;
     };
-    auto own_sweeps = [&](int i, int run) {                     // whether k_decode_pairs takes such a run in sweeps of its own
+    auto dense = [&](int i, int run) {                          // whether one of them has more than merged symbols in most chunks (512 words each)
+        while (run > 0 && got.bytes[i] <= area_at + 4 * nchunks * (kLaneBitsWords + 516)) { ++i; --run; }
+        return run > 0;
+    };
+    auto long_codes = [&](int i, int run) {
+        while (run > 0 && got.max_len[i] <= kDecLut1Bits) { ++i; --run; }
+        return run > 0;
+    };
+    auto own_sweeps = [&](int i, int run) {                     // whether k_decode_pairs takes such a run of 8 symbols in sweeps of its own
+        const int most = shared(run, kMaxMany);
         double words;
-        if (none || run == 0 || shared(run, kMaxMany) < 5) return false;
+        if (none || wide(i) || most < 5) return false;
         if (all || nchunks >= 6 * cus) return true;
         const int T = fused(i, i + run, &words);
-        return nchunks >= 3 * cus && (T > 4 || run % T != 0);
+        if (nchunks >= 3 * cus) return T != 4 || run % T != 0;
+        if (T < 4) return most >= 6 || nchunks > 2 * cus;
+        return T > 4 && most >= 7 && dtype != LC_F32;
     };
     const int slots[] = {kSlotDecCheck, kSlotDecodeFused, kSlotDecodePairs, kSlotDecode};
     collect(slots, 1);
     for (int g0 = 0; g0 < count;) {
-        // the blobs from g0 on up to the next run that has sweeps of its own: of 8 symbols only, or some of 16
-        const int run = run_of(g0);
+        // the blobs from g0 on up to the next run that has sweeps of its own or goes elsewhere: of 8 symbols only, or some of 16
+        const int run = run_of(g0), narrow = wide(g0) ? 0 : run;
         int end = g0 + run, T = 0, used = 1;
         double words = 0;
-        bool longs = false;
+        bool sixteen = wide(g0);
         if (!own_sweeps(g0, run)) {
-            while (end < count) {
-                const int next = run_of(++end);
-                if (own_sweeps(end, next)) break;
-                end += next;
+            for (int next; end < count; end += next) {
+                next = run_of(end);
+                if (own_sweeps(end, next) || (ds->tune.pairs != 1 && dense(end, next) != dense(g0, run) && long_codes(g0, end + next - g0))) break;
+                sixteen = sixteen || wide(end);
             }
         }
-        const bool sixteen = end > g0 + run;
         const int pairs = shared(end - g0, sixteen ? kMaxWide : kMaxMany);
-        for (int i = g0; i < end; ++i) longs = longs || got.max_len[i] > kDecLut1Bits;
-        if (pairs > 1 && (all || (sixteen ? !none && pairs >= 3 && pairs > run && (longs || (end - g0 + pairs - 1) / pairs < fused_sweeps(g0, end)) : own_sweeps(g0, run)))) {
+        const bool longs = long_codes(g0, end - g0);
+        if (pairs > 1 && (all || (sixteen ? !none && pairs >= 3 && pairs > narrow && (longs || (end - g0 + pairs - 1) / pairs < fused_sweeps(g0, end)) : own_sweeps(g0, run)))) {
             uint64_t bytes = 0;                                 // the longest blob's
             for (int i = g0; i < g0 + pairs; ++i) bytes = got.bytes[i] > bytes ? got.bytes[i] : bytes;
             const double row_bits = nchunks ? 8.0 * (double)(bytes - area_at) / (double)(nchunks * kW * kR) : 0;
             Timed tm(kSlotDecodePairs, s);
-            launch_decode_pairs(list, g0, pairs, w_ref, n, dtype, ws, epoch, host, row_bits, pairs > run, ds->tune, s);
+            launch_decode_pairs(list, g0, pairs, w_ref, n, dtype, ws, epoch, host, row_bits, pairs > narrow, ds->tune, s);
             T = pairs; used = 2;
         } else if (!by_rows) {
             // (one blob between such runs, or a list of one)
@@ -1084,11 +1101,12 @@ lc_ssize lc_encode_batch_t(const void* const* w, const void* const* w_ref, const
     uint8_t* base = reinterpret_cast<uint8_t*>(ws) + kWorkspaceHead;
     BatchArgs a;
     uint32_t chunks = 0, groups = 0;
+    uint64_t elements = 0;
     for (int t = 0; t < count; ++t) {
         Seg& sg = g_batch->segs[t];
         sg.w = w[t]; sg.w_ref = w_ref[t]; sg.out = static_cast<uint8_t*>(out[t]); sg.n = n[t];
         sg.nchunks = (uint32_t)num_chunks_of(n[t]); sg.chunk0 = chunks; sg.group0 = groups;
-        chunks += sg.nchunks; groups += (sg.nchunks + 63) / 64;
+        chunks += sg.nchunks; groups += (sg.nchunks + 63) / 64; elements += n[t];
         g_batch->results[t].bytes = 0; g_batch->results[t].status = LC_ERR_HIP; g_batch->results[t].used_cache = 0;
     }
     a.states = reinterpret_cast<EncState*>(base);            base += up((uint64_t)count * sizeof(EncState));
@@ -1103,7 +1121,7 @@ lc_ssize lc_encode_batch_t(const void* const* w, const void* const* w_ref, const
     a.prov = reinterpret_cast<uint32_t*>(base);
     a.results = g_batch_dev->results;
     a.count = (uint32_t)count; a.total_chunks = chunks; a.total_groups = groups;
-    a.slot_words = slot_words_of(nbits); a.nbits = nbits; a.dtype = dtype;
+    a.slot_words = slot_words_of(nbits); a.nbits = nbits; a.dtype = dtype; a.mean = chunks ? (uint32_t)(elements / chunks) : 0;
     a.host_segs = g_batch_dev->segs;
     launch_batch_encode(a, ds->tune, s);
     LC_HIP(hipGetLastError());

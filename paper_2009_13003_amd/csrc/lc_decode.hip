@@ -1226,10 +1226,11 @@ __device__ __forceinline__ void pairs_store(void* w_ref, u64 idx, const float (&
 }
 
 // off: the chunk's entries of blob t's offset table in lane t (its start) and lane kMaxMany + t (its end); lane_bits: the lane
-// lengths of its records; midway: called at most once, where loads for the next chunk cost no wait
-template <int T, bool WIDE, int DT, typename Midway>
+// lengths of its records; take, lengths: take the next chunk and ask for its entries, then for its lane lengths; each is called at
+// most once, where its loads cost no wait, and of a chunk that is decoded late, so that it is a wavefront soon free that takes it
+template <int T, bool WIDE, int DT, typename Take, typename Lengths>
 __device__ __forceinline__ void pairs_chunk(PairsLds<T, WIDE>& L, u32 wave, void* __restrict__ w_ref, u64 n, Workspace* ws, HostResult* host,
-                                            u32 c, u32 nchunks, u32 off, const u32 (&lane_bits)[T], u32 turns, u32 row_bits, u64 epoch, Midway& midway) {
+                                            u32 c, u32 nchunks, u32 off, const u32 (&lane_bits)[T], u32 turns, u32 row_bits, u64 epoch, Take& take, Lengths& lengths) {
     typedef PairsLds<T, WIDE> Lds;
     typedef typename Raw<DT>::type RowT;
     const u32 lane = lane_id();
@@ -1250,11 +1251,12 @@ __device__ __forceinline__ void pairs_chunk(PairsLds<T, WIDE>& L, u32 wave, void
         // after the other, 5 blobs of a sparse update of 2^27 elements 200 us; chunks taken as below and so, 138)
         typedef typename PairsWords<T, WIDE>::vec_any vec_any;
         u32x4 x[T][2], any = {0, 0, 0, 0};
+        take();
 #pragma unroll
         for (int t = 0; t < T; ++t)
 #pragma unroll
             for (u32 h = 0; h < 2; ++h) x[t][h] = *reinterpret_cast<const vec_any*>(S.gw[t] + 4 * (h * kW + lane));
-        midway();
+        lengths();
 #pragma unroll
         for (int t = 0; t < T; ++t) any |= x[t][0] | x[t][1];
 #pragma unroll
@@ -1332,7 +1334,8 @@ __device__ __forceinline__ void pairs_chunk(PairsLds<T, WIDE>& L, u32 wave, void
     for (; r < whole; r += PF) {
         place_words();                                       // (ahead of the rows, whose loads it would wait for)
         ask_for_words(rows - r);
-        if (r == kR / 2 && !quiet) midway();
+        if (r == kR / 2 && !quiet) take();
+        if (r == kR / 2 + 4 * PF && !quiet) lengths();
         if (r + 2 * PF < whole) fetch(C, r + 2 * PF);
 #pragma unroll
         for (u32 k = 0; k < PF; k += 2) {
@@ -1433,16 +1436,11 @@ __global__ __launch_bounds__(kPairsWaves * kW, T > 4 || WIDE ? 2 : 4) void k_dec
         if (lane < Lds::kSyms && len) { L.lj[t][rank] = code << (32 - len); L.e_rank[t][rank] = (len << 4) | lane; }
     }
     __syncthreads();
-    // A workgroup's wavefronts take its chunks as they come to them, one ahead: what a chunk costs differs a lot where some hold
-    // merged symbols only (dealt out in advance, 8 blobs of a sparse
-    // update of 2^27 elements 273 us, of 2^28 416; so, 186 and 252; of equally dense chunks the same to 1 %).  The next chunk's entries of the T offset tables are asked for
-    // ahead of this one, its lane lengths halfway through.
+    // A workgroup's wavefronts take its chunks as they come to them: what a chunk costs differs a lot where some hold merged symbols
+    // only (dealt out in advance, 8 blobs of a sparse update of 2^27 elements 273 us, of 2^28 416; so, 186 and 252; of equally dense
+    // chunks the same to 1 %).  One is taken halfway through the chunk before it (taken as that one began, 2^27 elements in layers
+    // off alignment, of whose chunks a third is dense, 2 and 4 blobs 119 and 143 us, 103 and 120 so; 8 blobs 222 in advance, 187 so).
     auto chunk = [&](u32 k) { return blockIdx.x + gridDim.x * k; };         // (few chunks: on as many compute units as there are)
-    auto take = [&]() {
-        u32 k = 0;
-        if (lane == 0) k = atomicAdd(&L.taken, 1u);
-        return chunk(__builtin_amdgcn_readfirstlane(k));
-    };
     auto offsets = [&](u32 c) {
         const u32 which = lane & (kMaxMany - 1);
         return lane < 2 * kMaxMany && which < T && c < nchunks ? L.off_tab[which][c + lane / kMaxMany] : 0u;
@@ -1456,13 +1454,19 @@ __global__ __launch_bounds__(kPairsWaves * kW, T > 4 || WIDE ? 2 : 4) void k_dec
     u32 off = offsets(c), bits[T] = {};
     lengths(c, off, bits);
     while (c < nchunks) {
-        const u32 after = take();
-        const u32 next = offsets(after);
-        u32 next_bits[T] = {};
-        bool have = false;
-        auto midway = [&]() { lengths(after, next, next_bits); have = true; };
-        pairs_chunk<T, WIDE, DT>(L, wave, w_ref, n, ws, host, c, nchunks, off, bits, turns, row_bits, epoch, midway);
-        if (!have) lengths(after, next, next_bits);
+        u32 after = 0, next = 0, next_bits[T] = {};
+        bool taken = false, have = false;
+        auto take = [&]() {
+            u32 k = 0;
+            if (lane == 0) k = atomicAdd(&L.taken, 1u);
+            after = chunk(__builtin_amdgcn_readfirstlane(k));
+            next = offsets(after);
+            taken = true;
+        };
+        auto its_lengths = [&]() { lengths(after, next, next_bits); have = true; };
+        pairs_chunk<T, WIDE, DT>(L, wave, w_ref, n, ws, host, c, nchunks, off, bits, turns, row_bits, epoch, take, its_lengths);
+        if (!taken) take();
+        if (!have) its_lengths();
 #pragma unroll
         for (int t = 0; t < T; ++t) bits[t] = next_bits[t];
         off = next;

@@ -2221,8 +2221,12 @@ __global__ __launch_bounds__(256) void kb_setup(BatchArgs a) {
 // 117 -> 113, 32 of 138 M 268 -> 249, 60 of 2^25 bf16 130 -> 105, off alignment fp32 200 -> 160, bf16 353 -> 152.
 // It also notes the largest |delta| exponent of every chunk and of each of its 4 KiB parts: from these the chunks that hold
 // merged elements only are told before the coding sweep, and of a mostly merged chunk the parts that have to be read.
-template <int DT, bool STAY>
-__global__ __launch_bounds__(kWgThreads, 4) void kb_hist(BatchArgs a, u32 run) {
+// SHORT: for tensors of a few rows.  Wavefronts without a row leave theirs alone, and rows are read by parts, so that a fourth
+// workgroup of fp32 fits a compute unit beside three: 1,000 tensors of 64 elements 89.0 us the call by the other form, whose last
+// workgroups wait for a second round, 83.3 so (a wavefront per chunk 84.5); bf16 84.7 and 82.8; of 8,000 elements 110 and 105.5,
+// 105.8 and 104.0.
+template <int DT, bool STAY, bool SHORT = false>
+__global__ __launch_bounds__(kWgThreads, SHORT ? 8 : 4) void kb_hist(BatchArgs a, u32 run) {
     typedef typename Raw<DT>::type raw_t;
     constexpr u32 kCopies = 16, kPartRows = 4096 / (kRowElems * elem_bytes<DT>());      // 4 rows per 4 KiB part, or 8
     __shared__ alignas(16) u32 hist[512 * kCopies];
@@ -2238,40 +2242,75 @@ __global__ __launch_bounds__(kWgThreads, 4) void kb_hist(BatchArgs a, u32 run) {
         const u64 n = sg.n;
         const u32 c = g - sg.chunk0;
         const bool full = (u64)(c + 1) * kChunk <= n;
-        raw_t A[kWgRows], B[kWgRows];
-        if (full) {
-#pragma unroll
-            for (u32 k = 0; k < kWgRows; ++k) { A[k] = load_raw_any<DT>(sg.w, row_at(c, first_row + k)); B[k] = load_raw_any<DT>(sg.w_ref, row_at(c, first_row + k)); }
-        } else {
-#pragma unroll
-            for (u32 k = 0; k < kWgRows; ++k) {
-                const u64 i = row_at(c, first_row + k);
-                const bool whole = i - lane * kV + kRowElems <= n;              // (the same in every lane)
-                A[k] = whole ? load_raw_any<DT>(sg.w, i) : load_raw_guarded<DT>(sg.w, i, n);
-                B[k] = whole ? load_raw_any<DT>(sg.w_ref, i) : load_raw_guarded<DT>(sg.w_ref, i, n);
-            }
-        }
-        __syncthreads();                             // (the counts are cleared, the last chunk's maxima read)
         u32 largest = 0;
+        if constexpr (SHORT) {
+            __syncthreads();
+#pragma unroll 1
+            for (u32 part = 0; part < kWgRows / kPartRows; ++part) {
+                const u32 r0 = first_row + part * kPartRows;
+                u32 most = 0;
+                if ((u64)c * kChunk + r0 * kRowElems < n) {
+                    raw_t A[kPartRows], B[kPartRows];
 #pragma unroll
-        for (u32 part = 0; part < kWgRows / kPartRows; ++part) {
-            u32 most = 0;
-#pragma unroll
-            for (u32 k = part * kPartRows; k < (part + 1) * kPartRows; ++k) {
-                float xa[4], xb[4];
-                unpack<DT>(A[k], xa); unpack<DT>(B[k], xb);
-#pragma unroll
-                for (u32 e = 0; e < kV; ++e) {
-                    const u32 u = delta_bits(xa[e], xb[e]);
-                    if (full || row_at(c, first_row + k) + e < n) {
-                        atomicAdd(&hist[(u >> 23) * kCopies + (lane & (kCopies - 1))], 1u);
-                        most = max(most, u & 0x7FFFFFFFu);
+                    for (u32 k = 0; k < kPartRows; ++k) {
+                        const u64 i = row_at(c, r0 + k);
+                        const bool whole = i - lane * kV + kRowElems <= n;      // (the same in every lane)
+                        A[k] = whole ? load_raw_any<DT>(sg.w, i) : load_raw_guarded<DT>(sg.w, i, n);
+                        B[k] = whole ? load_raw_any<DT>(sg.w_ref, i) : load_raw_guarded<DT>(sg.w_ref, i, n);
                     }
+#pragma unroll
+                    for (u32 k = 0; k < kPartRows; ++k) {
+                        float xa[4], xb[4];
+                        unpack<DT>(A[k], xa); unpack<DT>(B[k], xb);
+#pragma unroll
+                        for (u32 e = 0; e < kV; ++e) {
+                            const u32 u = delta_bits(xa[e], xb[e]);
+                            if (row_at(c, r0 + k) + e < n) {
+                                atomicAdd(&hist[(u >> 23) * kCopies + (lane & (kCopies - 1))], 1u);
+                                most = max(most, u & 0x7FFFFFFFu);
+                            }
+                        }
+                    }
+                    most = wave_max_u32(most) >> 23;
+                }
+                if (lane == 0) a.part_max[(u64)g * kPartBytes + first_row / kPartRows + part] = (uint8_t)most;
+                largest = max(largest, most);
+            }
+        } else {
+            raw_t A[kWgRows], B[kWgRows];
+            if (full) {
+#pragma unroll
+                for (u32 k = 0; k < kWgRows; ++k) { A[k] = load_raw_any<DT>(sg.w, row_at(c, first_row + k)); B[k] = load_raw_any<DT>(sg.w_ref, row_at(c, first_row + k)); }
+            } else {
+#pragma unroll
+                for (u32 k = 0; k < kWgRows; ++k) {
+                    const u64 i = row_at(c, first_row + k);
+                    const bool whole = i - lane * kV + kRowElems <= n;              // (the same in every lane)
+                    A[k] = whole ? load_raw_any<DT>(sg.w, i) : load_raw_guarded<DT>(sg.w, i, n);
+                    B[k] = whole ? load_raw_any<DT>(sg.w_ref, i) : load_raw_guarded<DT>(sg.w_ref, i, n);
                 }
             }
-            most = wave_max_u32(most) >> 23;
-            if (lane == 0) a.part_max[(u64)g * kPartBytes + first_row / kPartRows + part] = (uint8_t)most;
-            largest = max(largest, most);
+            __syncthreads();                             // (the counts are cleared, the last chunk's maxima read)
+#pragma unroll
+            for (u32 part = 0; part < kWgRows / kPartRows; ++part) {
+                u32 most = 0;
+#pragma unroll
+                for (u32 k = part * kPartRows; k < (part + 1) * kPartRows; ++k) {
+                    float xa[4], xb[4];
+                    unpack<DT>(A[k], xa); unpack<DT>(B[k], xb);
+#pragma unroll
+                    for (u32 e = 0; e < kV; ++e) {
+                        const u32 u = delta_bits(xa[e], xb[e]);
+                        if (full || row_at(c, first_row + k) + e < n) {
+                            atomicAdd(&hist[(u >> 23) * kCopies + (lane & (kCopies - 1))], 1u);
+                            most = max(most, u & 0x7FFFFFFFu);
+                        }
+                    }
+                }
+                most = wave_max_u32(most) >> 23;
+                if (lane == 0) a.part_max[(u64)g * kPartBytes + first_row / kPartRows + part] = (uint8_t)most;
+                largest = max(largest, most);
+            }
         }
         if (lane == 0) s_largest[v] = largest;
         __syncthreads();
@@ -2537,10 +2576,13 @@ void launch_batch_encode(const BatchArgs& args, const Tuning& tune, hipStream_t 
         // some 40 counts each to the same few lines of memory, and few streams of long bursts read faster.  Whole calls, us, per
         // chunk / staying: fp32 2^24.6 115 / 117, 2^25 131 / 137, 2^26 233 / 215, 138 M 284 / 249, 2^27 471 / 435; bf16 2^25 105 /
         // 115, 2^26 158 / 165, 2^27 270 / 258.  (1, 3 and 4 per unit 458, 467, 443 for the last fp32 one)
+        // Up to half a chunk on average, the form for few rows.
         const bool stay = a.total_chunks >= (u32)tune.num_cu * (a.dtype == kF32 ? 12u : 24u);
         const u32 most = 2 * (u32)tune.num_cu, run = stay ? (a.total_chunks + most - 1) / most : 1;
         const dim3 grid((a.total_chunks + run - 1) / run), wg(kWgThreads);
-#define LC_HIST(DT) do { if (stay) hipLaunchKernelGGL((kb_hist<DT, true>), grid, wg, 0, s, a, run); else hipLaunchKernelGGL((kb_hist<DT, false>), grid, wg, 0, s, a, run); } while (0)
+#define LC_HIST(DT) do { if (stay) hipLaunchKernelGGL((kb_hist<DT, true>), grid, wg, 0, s, a, run); \
+                         else if (a.mean <= 4 * kWgRows * kRowElems) hipLaunchKernelGGL((kb_hist<DT, false, true>), grid, wg, 0, s, a, run); \
+                         else hipLaunchKernelGGL((kb_hist<DT, false>), grid, wg, 0, s, a, run); } while (0)
         if (a.dtype == kBF16) LC_HIST(kBF16);
         else if (a.dtype == kF16) LC_HIST(kF16);
         else LC_HIST(kF32);

@@ -236,7 +236,8 @@ struct BatchArgs {
     uint32_t* list_count;        // how many those are
     uint32_t count, total_chunks, total_groups, slot_words;
     int nbits, dtype;                                  // dtype: element type of every tensor of the call
-    uint32_t listed, pad_b;                            // 1: the coding sweep takes its chunks from chunk_list
+    uint32_t listed;                                   // 1: the coding sweep takes its chunks from chunk_list
+    uint32_t mean;                                     // elements per chunk, on average
 };
 void launch_batch_encode(const BatchArgs& a, const Tuning& tune, hipStream_t s);
 

@@ -185,3 +185,24 @@ def test_short_lists_that_end_in_a_ragged_chunk(lc):
         times[n % 16384] = best_us(lambda: lc.lc_decode_many(blobs, many))
     print("8 blobs, whole and ragged: %.1f us, %.1f us" % (times[0], times[16384 - 777]), flush=True)
     assert times[16384 - 777] < 1.2 * times[0], times        # (1.44 by elements, 1.0 by rows)
+
+
+def test_lists_whose_dense_chunks_lie_together(lc):
+    """Four checkpoints of 2^27 elements off alignment, of which three layers out of eleven change: their chunks come one after the other to
+    the workgroups, and each wavefront of those takes one when it is free.  Against checkpoints that change everywhere."""
+    n, times = 1 << 27, {}
+    g = torch.Generator(device=DEV); g.manual_seed(15)
+    for kind in ("dense", "layers"):
+        u = torch.rand(n, generator=g, device=DEV) - 0.5
+        d = -1e-3 * torch.sign(u) * torch.log1p(-2 * u.abs().clamp_(max=0.49999997))
+        if kind == "layers":
+            d *= 10.0 ** -((torch.arange(n, device=DEV) * 11 // n) * 3 % 4).float()
+        blob, many, single = blob_of(lc, d, torch.zeros_like(d), 3), torch.zeros(n + 1, device=DEV)[1:], torch.zeros(n, device=DEV)
+        blobs = [blob.clone() for _ in range(4)]
+        for b in blobs:
+            lc.lc_decode(b, single)
+        lc.lc_decode_many(blobs, many)
+        assert torch.equal(single, many)
+        times[kind] = best_us(lambda: lc.lc_decode_many(blobs, many), reps=30)
+    print("dense and in layers: %.1f us, %.1f us" % (times["dense"], times["layers"]), flush=True)
+    assert times["layers"] < 0.45 * times["dense"], times     # (0.49 where a chunk was taken as the one before it began, 0.41 now)
