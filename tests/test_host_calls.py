@@ -65,6 +65,7 @@ static bool meet = true;                 // whether the workgroups of a call in 
 static uint64_t blob_bytes = 1000;       // of every blob that is checked or restored, and its longest code
 static uint32_t blob_max_len = 3, blob_kept = 3;
 static std::vector<uint32_t> kept_of;    // ... of each blob of a list, where they differ
+static std::vector<uint64_t> bytes_of;
 static int fused_fits = 8;               // blobs that a fused sweep by symbols takes at once
 static int fail_launches = 0;            // the next launches that fail
 static std::function<void()> waiting;    // runs (once) in a thread that waits for its stream
@@ -89,7 +90,7 @@ void launch_batch_encode(const BatchArgs&, const Tuning&, hipStream_t) {}
 void launch_batch_decode(const BatchDecArgs&, const Tuning&, hipStream_t) {}
 void launch_dec_check(const BlobList&, int, int count, uint64_t, int, uint64_t, Workspace*, uint64_t, HostResult* host, hipStream_t) {
     launched += 'c';
-    for (int i = 0; i < count; ++i) { host->bytes[i] = blob_bytes; host->max_len[i] = blob_max_len; host->kept[i] = kept_of.empty() ? blob_kept : kept_of[i]; }
+    for (int i = 0; i < count; ++i) { host->bytes[i] = bytes_of.empty() ? blob_bytes : bytes_of[i]; host->max_len[i] = blob_max_len; host->kept[i] = kept_of.empty() ? blob_kept : kept_of[i]; }
 }
 void launch_decode(const uint8_t*, void* w_ref, uint64_t, int, Workspace*, int, uint64_t, HostResult*, const Tuning&, hipStream_t) { launched += w_ref ? 'd' : 'v'; }
 void launch_decode_one(const BlobList&, int count, void*, uint64_t, int, uint64_t, Workspace*, uint64_t, HostResult* host, uint64_t (&)[kMeetLines], int, hipStream_t) {
@@ -254,10 +255,10 @@ static void scenarios() {
     blob_bytes = large / 4;
     is("cD", 2, large, LC_F64); is("cD", 8, large, LC_F64, 8); is("cdd", 2, beyond, LC_F64);
     // which of the two kernels takes a list, and in how many sweeps: of few symbols the second from 5 blobs and 3 or 6 chunks per
-    // compute unit on, of 16 from 3 blobs on; either shares them out evenly
+    // compute unit on, or where the first takes less than 4 at a time, of 16 from 3 blobs on; either shares them out evenly
     blob_bytes = 1000;
     for (uint64_t per_cu : {2, 3, 5, 6, 20})
-        for (int fits : {2, 4, 6, 8})
+        for (int fits : {2, 3, 4, 6, 8})
             for (int count = 2; count <= 20; ++count) {
                 const int in_fused = (count + fits - 1) / fits;
                 const uint64_t size = (per_cu * 256 + 1) * 16384;
@@ -267,13 +268,14 @@ static void scenarios() {
                     std::string want = "c";
                     for (int left = count; left > 0;) {              // (the last few of 9, 10, ... may be too few for the second)
                         const int sweeps = (left + 7) / 8, pairs = (left + sweeps - 1) / sweeps, rounds = (left + fits - 1) / fits;
-                        const bool second = pairs >= 5 && per_cu >= 3 && (per_cu >= 6 || fits > 4 || left % fits);
+                        const bool second = pairs >= 5 && (per_cu >= 6 || (per_cu >= 3 ? fits != 4 || left % fits : fits < 4));
                         want += second ? "g" : "f";
                         left -= second ? pairs : (left + rounds - 1) / rounds;
                     }
                     is(want.c_str(), count, size, LC_F32);
                     is(("c" + times((count + 7) / 8, "g")).c_str(), count, size, LC_BF16, 2);
                 }
+                if (fits == 3) continue;
                 blob_kept = 15;
                 const int sweeps = (count + 3) / 4;
                 if (count > 2 && count != 5) is(("c" + times(sweeps < in_fused ? sweeps : in_fused, sweeps < in_fused ? "g" : "f")).c_str(), count, size, LC_F16);
@@ -300,6 +302,29 @@ static void scenarios() {
     }
     mixed("cfg", {15, 7, 7, 7, 7, 7, 7}, 8192); mixed("cgf", {7, 7, 7, 7, 7, 7, 15}, 8192); blob_max_len = 8; mixed("cfg", {7, 7, 7, 7, 15, 15, 15}, 8192); blob_max_len = 3;
     mixed("cdg", {15, 7, 7, 7, 7, 7, 7}, 8192, 4); mixed("cgd", {7, 7, 7, 7, 7, 7, 15}, 600, 4); mixed("cdggd", {15, 7, 7, 7, 7, 7, 7, 7, 7, 7, 7, 15}, 8192, 4);
+    // ... and sparse blobs (532 words a chunk here) do not go with dense ones (564) of the other kind, where some codes are long
+    blob_max_len = 8;
+    const uint64_t chunks = 8192, sparse = 512 + 4 * (chunks + 4) + 4 * 532 * chunks, more = sparse + 4 * 32 * chunks;
+    auto kinds = [&](const char* want, std::vector<uint32_t> kept, std::vector<uint64_t> bytes, int offset = 0) {
+        kept_of = kept; bytes_of = bytes;
+        uint64_t total = 0;
+        for (uint64_t b : bytes) total += b;
+        ok(decode_many_t((int)kept.size(), chunks * 16384, LC_F32, offset), (lc_ssize)total);
+        expect(want, want);
+        kept_of.clear(); bytes_of.clear();
+    };
+    kinds("cfff", {15, 0, 15}, {more, sparse, more}); kinds("cddd", {15, 0, 15}, {more, sparse, more}, 4);
+    kinds("cg", {15, 7, 15}, {more, more, more}); kinds("cg", {15, 0, 15}, {sparse, sparse, sparse}); kinds("cfg", {0, 15, 15, 15}, {sparse, more, more, sparse});
+    kinds("cgf", {7, 7, 15, 7}, {more, sparse, more, sparse});
+    blob_max_len = 3; kinds("cf", {15, 0, 15}, {more, sparse, more});
+    // few chunks: the second where the first takes less than 4 dense ones, and of 2-byte elements 7 or 8 sparse ones
+    blob_bytes = 1000; blob_kept = 7;
+    for (int fits : {3, 4, 6}) {
+        fused_fits = fits;
+        is(fits == 3 ? "cg" : "cff", 8, small, LC_F32); is(fits == 4 ? "cff" : "cg", 8, small, LC_BF16); is(fits == 3 ? "cgg" : fits == 4 ? "cfff" : "cff", 12, small, LC_F16);
+        is(fits == 3 ? "cfg" : fits == 4 ? "cfff" : "cff", 10, small, LC_F32);
+    }
+    fused_fits = 8;
     is("cd", 1, beyond, LC_F32, 4); is("cd", 1, beyond, LC_BF16, 2); is("cf", 1, beyond, LC_F32);
     blob_kept = 3; fused_fits = 8;
     // given up behind the check
