@@ -1101,11 +1101,12 @@ lc_ssize lc_encode_batch_t(const void* const* w, const void* const* w_ref, const
     uint8_t* base = reinterpret_cast<uint8_t*>(ws) + kWorkspaceHead;
     BatchArgs a;
     uint32_t chunks = 0, groups = 0;
+    uint64_t elements = 0;
     for (int t = 0; t < count; ++t) {
         Seg& sg = g_batch->segs[t];
         sg.w = w[t]; sg.w_ref = w_ref[t]; sg.out = static_cast<uint8_t*>(out[t]); sg.n = n[t];
         sg.nchunks = (uint32_t)num_chunks_of(n[t]); sg.chunk0 = chunks; sg.group0 = groups;
-        chunks += sg.nchunks; groups += (sg.nchunks + 63) / 64;
+        chunks += sg.nchunks; groups += (sg.nchunks + 63) / 64; elements += n[t];
         g_batch->results[t].bytes = 0; g_batch->results[t].status = LC_ERR_HIP; g_batch->results[t].used_cache = 0;
     }
     a.states = reinterpret_cast<EncState*>(base);            base += up((uint64_t)count * sizeof(EncState));
@@ -1120,7 +1121,7 @@ lc_ssize lc_encode_batch_t(const void* const* w, const void* const* w_ref, const
     a.prov = reinterpret_cast<uint32_t*>(base);
     a.results = g_batch_dev->results;
     a.count = (uint32_t)count; a.total_chunks = chunks; a.total_groups = groups;
-    a.slot_words = slot_words_of(nbits); a.nbits = nbits; a.dtype = dtype;
+    a.slot_words = slot_words_of(nbits); a.nbits = nbits; a.dtype = dtype; a.mean = chunks ? (uint32_t)(elements / chunks) : 0;
     a.host_segs = g_batch_dev->segs;
     launch_batch_encode(a, ds->tune, s);
     LC_HIP(hipGetLastError());

@@ -51,3 +51,31 @@ def test_counts(lc, dtype, chunks, offset):
             one = lc.alloc_out(w.numel(), 3, DEV)
             assert lc.lc_encode_t(w, ref, 3, one) == size, (i, sizes[i])
             assert torch.equal(one[:size], got[:size]), (i, sizes[i])
+
+
+@pytest.mark.parametrize("offset", [0, 1])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float16])
+def test_short_tensors(lc, dtype, offset):
+    """The form for chunks of few rows: ends at every edge of rows, parts and wavefronts, whole chunks between them."""
+    g = torch.Generator(device=DEV); g.manual_seed(offset)
+    sizes = [m + d for m in (1, 64, 256, 512, 1024, 2048, 4096, 6144, 8192, 10240, CHUNK) for d in (-1, 0, 1)] + [0, 2 * CHUNK, CHUNK + 1025] + [300] * 40
+    assert sum(sizes) / sum((m + CHUNK - 1) // CHUNK for m in sizes) < CHUNK // 2
+    ws, refs, outs = [], [], []
+    for i, m in enumerate(sizes):
+        d = 10.0 ** (i % 5 - 5) * torch.randn(m, generator=g, device=DEV)
+        if i % 3 == 1:
+            d = d * (torch.rand(m, generator=g, device=DEV) < 0.01)
+        ref, w = (torch.full((m + offset + 1,), float("nan"), dtype=dtype, device=DEV) for _ in range(2))     # (a NaN beside would show)
+        ref[offset:offset + m] = (0.05 * torch.randn(m, generator=g, device=DEV)).to(dtype)
+        w[offset:offset + m] = (ref[offset:offset + m].float() + d).to(dtype)
+        if i == 20:
+            w[offset + m // 2] = float("inf")
+        ws.append(w[offset:offset + m]); refs.append(ref[offset:offset + m]); outs.append(lc.alloc_out(m, 3, DEV))
+    sizes_got = lc.EncodeBatch(ws, refs, 3, outs).run()
+    for i, (w, ref, got, size) in enumerate(zip(ws, refs, outs, sizes_got)):
+        if i == 20:
+            assert size == -lc.ERR_NONFINITE, (i, size)
+            continue
+        one = lc.alloc_out(w.numel(), 3, DEV)
+        assert lc.lc_encode_t(w, ref, 3, one) == size, (i, sizes[i])
+        assert torch.equal(one[:size], got[:size]), (i, sizes[i])

@@ -206,3 +206,19 @@ def test_lists_whose_dense_chunks_lie_together(lc):
         times[kind] = best_us(lambda: lc.lc_decode_many(blobs, many), reps=30)
     print("dense and in layers: %.1f us, %.1f us" % (times["dense"], times["layers"]), flush=True)
     assert times["layers"] < 0.45 * times["dense"], times     # (0.49 where a chunk was taken as the one before it began, 0.41 now)
+
+
+def test_batch_of_tiny_tensors(lc):
+    """A thousand tensors of 64 elements: the counting sweep has a workgroup for each, whose empty rows cost nothing."""
+    times = {}
+    for dtype in (torch.float32, torch.bfloat16):
+        ws = [torch.full((64,), 0.5 + i, device=DEV, dtype=dtype) for i in range(1000)]
+        refs, outs = [torch.zeros_like(w) for w in ws], [lc.alloc_out(64, 3, DEV) for _ in ws]
+        batch = lc.EncodeBatch(ws, refs, 3, outs)
+        one = lc.alloc_out(64, 3, DEV)
+        sizes = batch.run()
+        for i in (0, 500, 999):
+            assert lc.lc_encode_t(ws[i], refs[i], 3, one) == sizes[i] and torch.equal(one[:sizes[i]], outs[i][:sizes[i]])
+        times[dtype] = best_us(batch.run)
+    print("1,000 tensors, fp32 and bf16: %.1f us, %.1f us" % (times[torch.float32], times[torch.bfloat16]), flush=True)
+    assert times[torch.float32] < 1.03 * times[torch.bfloat16], times        # (1.05 where three workgroups fit a compute unit, 1.01 where four do)
