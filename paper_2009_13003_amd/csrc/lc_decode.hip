@@ -977,12 +977,17 @@ __device__ __forceinline__ void fused_chunk(const FusedHead<T>& H, u32* pay, u32
 }
 
 // Wavefronts per SIMD that the registers leave, where the LDS does too, with sparse blobs (4 of them, two of 1 % kept symbols, one
-// unchanged, fp32, 5,919 chunks with one wavefront per SIMD less 235 us and 195, 2^27 elements 318 and 263).
-constexpr int fused_waves(int blobs, bool long_codes, int dt) { return blobs <= 2 || (blobs == 3 && long_codes && dt == kF32) ? 4 : blobs <= 5 ? 3 : 2; }
+// unchanged, fp32, 5,919 chunks with one wavefront per SIMD less 235 us and 195, 2^27 elements 318 and 263), and may leave: of 4 dense
+// blobs 8 wavefronts fit a compute unit, which with 2-byte elements had better be 2 per SIMD than 3 on some (1,831 chunks that no cache
+// holds 95 us and 104).
+constexpr bool fused_twos(int blobs, bool long_codes, int dt) { return blobs == 4 && !long_codes && dt != kF32; }
+constexpr int fused_waves(int blobs, bool long_codes, int dt) {
+    return blobs <= 2 || (blobs == 3 && long_codes && dt == kF32) ? 4 : blobs <= 5 && !fused_twos(blobs, long_codes, dt) ? 3 : 2;
+}
 template <int T, bool LONG, int DT>
-__global__ __launch_bounds__(64, fused_waves(T, LONG, DT)) void k_decode_fused(BlobList blobs, u32 first, void* __restrict__ w_ref, u64 n,
-                                                     Workspace* ws, u32 nchunks, u64 epoch,
-                                                     HostResult* host, u32 pay_words) {
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(fused_waves(T, LONG, DT), fused_twos(T, LONG, DT) ? 2 : 8)))
+void k_decode_fused(BlobList blobs, u32 first, void* __restrict__ w_ref, u64 n, Workspace* ws, u32 nchunks, u64 epoch, HostResult* host,
+                    u32 pay_words) {
     __shared__ FusedHead<T> H;
     static_assert(sizeof(FusedHead<T>) % 16 == 0, "payload area must stay 16-byte aligned");
     extern __shared__ uint4 fused_pay[];                 // pay_words + kFusedSlack payload words, right behind H
@@ -1039,8 +1044,8 @@ __global__ __launch_bounds__(64, fused_waves(T, LONG, DT)) void k_decode_fused(B
 // - A step takes two symbols: one look-up over the next 10 bits gives both and their length together, one more their two
 //   representatives (8 bytes at an aligned place cost the LDS hardly more than 4).  18 vector and 5 LDS instructions per row of
 //   4 symbols and blob; one symbol per look-up took 24 and 9.
-// 8 blobs of 355 M elements, codes of 1.65 bits: 1,240 us in two sweeps, 910 so; vector issue 49 %, LDS 60 % of the time, and
-// 5.9 TB/s past the L2.  Without the windows' words it would take 740, without w_ref 750.
+// 8 blobs of 355 M elements, codes of 1.65 bits: 1,240 us in two sweeps, 930 so; vector issue 51 %, LDS 56 % of its cycles, and
+// 5.6 TB/s past the L2.  Without the windows' words it would take 740, without w_ref 750.
 // WIDE: some blob of the sweep has more than 8 symbols: pairs of 4-bit symbols, 11 bits to look up, since its codes
 // are longer, and twice the words.  Two codes that do not fit the table's bits (under 0.1 % of the pairs of codes of
 // 1.7 bits on average, 0.3 % of those of 3.5; most of them in a layer whose symbols are all rare ones) are told from their
