@@ -815,14 +815,17 @@ lc_ssize decode_many_impl(const void* const* blobs, int count, void* w_ref, uint
         uint32_t w = ((uint32_t)(words * 1.1) + 63u) & ~63u;
         return w < kFusedMinWords ? kFusedMinWords : w;
     };
-    // the blobs from i on that a sweep of k_decode_fused takes, up to `end`, and the payload words of them together
+    // the blobs from i on that a sweep of k_decode_fused takes, up to `end`, and the payload words of them together in a full chunk
+    // (with a ragged chunk counted as a whole one, the average lay below the full ones' payloads, which then did not fit: 7 blobs of 3.3
+    // chunks at 3 bits 110 us the call, and 90 so, 12 of 1.4 at 2 bits 150 and 120)
+    const double chunks = n > kChunk ? (double)n / kChunk : 1.0;
     auto fused = [&](int i, int end, double* words) {
         const bool short_codes = got.max_len[i] <= kDecLut1Bits;
         int T = 0;
         *words = 0;
         while (i + T < end && T < kMaxMany && (got.max_len[i + T] <= kDecLut1Bits) == short_codes) {
             if (nchunks) {
-                const double avg = (double)(got.bytes[i + T] - area_at) / 4.0 / (double)nchunks - kLaneBitsWords + 6.0;
+                const double avg = ((double)(got.bytes[i + T] - area_at) / 4.0 - (double)(kLaneBitsWords * nchunks)) / chunks + 6.0;
                 if (T > 0 && fused_lds_bytes(T + 1, pay_words_of(*words + avg)) > lds_budget) break;
                 *words += avg;
             }

@@ -168,23 +168,25 @@ def test_long_lists_of_sparse_updates(lc):
         assert times[5] < 0.5 * (slow + now) * times[4], (kind, times)
 
 
-def test_short_lists_that_end_in_a_ragged_chunk(lc):
-    """Eight checkpoints of three chunks in one call, the last one whole or all but 777 elements of it: the ragged chunk is a
-    wavefront's work from start to end, as the others are."""
+@pytest.mark.parametrize("chunks,ragged,count,bound", [(3, 3 * 16384 - 777, 8, 1.2),           # (1.44 by elements, 1.0 by rows)
+                                                       (4, 3 * 16384 + 4460, 7, 1.05)])        # (1.15 by payloads from memory, 0.95)
+def test_short_lists_that_end_in_a_ragged_chunk(lc, chunks, ragged, count, bound):
+    """A few chunks' checkpoints in one call, the last chunk whole or ragged: that one is a wavefront's work from start to end, as the others
+    are, and does not keep their payloads out of the LDS."""
     times = {}
-    for n in (3 * 16384, 3 * 16384 - 777):
+    for n in (chunks * 16384, ragged):
         g = torch.Generator(device=DEV); g.manual_seed(13)
         u = torch.rand(n, generator=g, device=DEV) - 0.5
         d = -1e-3 * torch.sign(u) * torch.log1p(-2 * u.abs().clamp_(max=0.49999997))
         blob, many, single = blob_of(lc, d, torch.zeros_like(d), 3), torch.zeros(n, device=DEV), torch.zeros(n, device=DEV)
-        blobs = [blob.clone() for _ in range(8)]
+        blobs = [blob.clone() for _ in range(count)]
         for b in blobs:
             lc.lc_decode(b, single)
         lc.lc_decode_many(blobs, many)
         assert torch.equal(single, many)
-        times[n % 16384] = best_us(lambda: lc.lc_decode_many(blobs, many))
-    print("8 blobs, whole and ragged: %.1f us, %.1f us" % (times[0], times[16384 - 777]), flush=True)
-    assert times[16384 - 777] < 1.2 * times[0], times        # (1.44 by elements, 1.0 by rows)
+        times[n] = best_us(lambda: lc.lc_decode_many(blobs, many))
+    print("%d blobs, whole and ragged: %.1f us, %.1f us" % (count, times[chunks * 16384], times[ragged]), flush=True)
+    assert times[ragged] < bound * times[chunks * 16384], times
 
 
 def test_lists_whose_dense_chunks_lie_together(lc):
