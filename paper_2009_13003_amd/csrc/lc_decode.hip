@@ -985,7 +985,7 @@ constexpr int fused_waves(int blobs, bool long_codes, int dt) {
     return blobs <= 2 || (blobs == 3 && long_codes && dt == kF32) ? 4 : blobs <= 5 && !fused_twos(blobs, long_codes, dt) ? 3 : 2;
 }
 template <int T, bool LONG, int DT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(fused_waves(T, LONG, DT), fused_twos(T, LONG, DT) ? 2 : 8)))
+__global__ __launch_bounds__(64) LC_WAVES_PER_SIMD(fused_waves(T, LONG, DT), fused_twos(T, LONG, DT) ? 2 : 8)
 void k_decode_fused(BlobList blobs, u32 first, void* __restrict__ w_ref, u64 n, Workspace* ws, u32 nchunks, u64 epoch, HostResult* host,
                     u32 pay_words) {
     __shared__ FusedHead<T> H;

@@ -3,6 +3,14 @@
 #pragma once
 #include "lc_internal.h"
 
+// Wavefronts per SIMD that a kernel's registers are to allow, at least and at most.  (Its source is compiled for the host as well, by
+// tests, where there is no such attribute.)
+#ifdef __HIP__
+#define LC_WAVES_PER_SIMD(least, most) __attribute__((amdgpu_waves_per_eu(least, most)))
+#else
+#define LC_WAVES_PER_SIMD(least, most)
+#endif
+
 namespace lc {
 
 typedef unsigned long long u64;
