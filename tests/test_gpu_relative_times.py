@@ -212,15 +212,17 @@ def test_lists_whose_dense_chunks_lie_together(lc):
 
 def test_batch_of_tiny_tensors(lc):
     """A thousand tensors of 64 elements: the counting sweep has a workgroup for each, whose empty rows cost nothing."""
-    times = {}
+    times, batches = {}, {}
     for dtype in (torch.float32, torch.bfloat16):
         ws = [torch.full((64,), 0.5 + i, device=DEV, dtype=dtype) for i in range(1000)]
         refs, outs = [torch.zeros_like(w) for w in ws], [lc.alloc_out(64, 3, DEV) for _ in ws]
-        batch = lc.EncodeBatch(ws, refs, 3, outs)
+        batch = batches[dtype] = lc.EncodeBatch(ws, refs, 3, outs)
         one = lc.alloc_out(64, 3, DEV)
         sizes = batch.run()
         for i in (0, 500, 999):
             assert lc.lc_encode_t(ws[i], refs[i], 3, one) == sizes[i] and torch.equal(one[:sizes[i]], outs[i][:sizes[i]])
-        times[dtype] = best_us(batch.run)
+    for _ in range(3):                                       # (in turn: the two are a few percent apart)
+        for dtype, batch in batches.items():
+            times[dtype] = min(times.get(dtype, 1e9), best_us(batch.run))
     print("1,000 tensors, fp32 and bf16: %.1f us, %.1f us" % (times[torch.float32], times[torch.bfloat16]), flush=True)
     assert times[torch.float32] < 1.03 * times[torch.bfloat16], times        # (1.05 where three workgroups fit a compute unit, 1.01 where four do)
